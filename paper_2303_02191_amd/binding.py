@@ -17,6 +17,7 @@ RULE_ALL, RULE_ANYPAIR4, RULE_CONNECTED4, RULE_CONNECTED8 = 0, 1, 2, 3
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "librtoss.so")
 _lib = None
+_host = None
 
 
 class RtossError(RuntimeError):
@@ -104,6 +105,27 @@ def lib():
                                                     u16p, i, vp, vp, vp, vp]
         _lib = L
     return _lib
+
+
+def host():
+    """The native call path of pipeline.py (csrc/host_ext.cpp): torch tensors in, C ABI calls out."""
+    global _host
+    if _host is None:
+        lib()  # torch and librtoss.so first: the extension binds to both
+        try:
+            from . import _host as ext
+        except ImportError as e:
+            raise ImportError("_host.so is not built: run `python -m paper_2303_02191_amd.build`") from e
+        ext.set_error_type(RtossError)
+        _host = ext
+    return _host
+
+
+def dictionary(masks):
+    """masks as the contiguous uint16 array the native call path takes."""
+    if type(masks) is np.ndarray and masks.dtype == np.uint16 and masks.flags.c_contiguous:
+        return masks
+    return np.ascontiguousarray(masks, dtype=np.uint16)
 
 
 def _check(st):

@@ -8,6 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librtoss.so")
+HOST = os.path.join(HERE, "_host.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -142,6 +143,29 @@ def build_library(verbose=True):
     return LIB
 
 
+def build_host(verbose=True):
+    """The native call path (csrc/host_ext.cpp): host code only, against torch's headers; needs librtoss.so."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    tmp = HOST + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    for d in [*cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", d]
+    cmd += ["-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "host_ext.cpp"), "-o", tmp, "-L", HERE,
+            "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lrtoss", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip",
+            "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print("g++ host_ext.cpp -> _host.so", flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, HOST)
+    return HOST
+
+
 if __name__ == "__main__":
     build_library()
+    build_host()
     sys.exit(0)
