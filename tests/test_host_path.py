@@ -29,7 +29,7 @@ def test_arguments_are_checked_before_the_library_is_called(layer):
 
 def test_library_errors_carry_status_and_message():
     with pytest.raises(B.RtossError) as e:
-        pl.select_patterns_batch([], 7, B.rtoss_pattern_dict(3))
+        pl.select_patterns_batch([], 7, B.rtoss_pattern_dict(3), stream=0)
     assert e.value.status == B.EDTYPE and "dtype" in str(e.value)
     # dictionaries of other integer types are converted, as everywhere in the binding
-    assert pl.select_patterns_batch([], B.F16, B.rtoss_pattern_dict(3).astype(np.int64)) == []
+    assert pl.select_patterns_batch([], B.F16, B.rtoss_pattern_dict(3).astype(np.int64), stream=0) == []
