@@ -366,7 +366,7 @@ rtoss_status rtoss_pack_batch(const rtoss_pack_item* items_host, int n_items, co
     hipStream_t s = (hipStream_t)hip_stream;
     // layers of the two common formats go out in batched launches, per dtype; the rest one by one
     for (int fmt : {(int)kFormatSparse24, (int)kFormatDenseStream})
-        for (int dt : {(int)RTOSS_F16, (int)RTOSS_BF16}) {
+        for (int dt : {(int)RTOSS_F32, (int)RTOSS_F16, (int)RTOSS_BF16}) {
             std::vector<PackItem> group;
             for (int i = 0; i < n_items; ++i)
                 if ((int)geo[i].format == fmt && (int)items[i].d.dt == dt) group.push_back(items[i]);

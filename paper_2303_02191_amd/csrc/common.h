@@ -35,10 +35,10 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // ----- packed blob geometry (host side; the kernels receive section pointers) -----
 enum MatrixFormat {
     kFormatNone = 0,     // only the live list (section 0): direct kernels
-    kFormatDense = 1,    // 1x1: zero-filled matrix-core fragments
+    kFormatDense = 1,    // 1x1, rows of any multiple of 4 bytes: zero-filled matrix-core fragments
     kFormatSparse24 = 2, // 3x3: 2-of-4 compressed fragments + indices
     kFormatStem = 3,     // 3x3 with <= 3 input channels: one zero-filled fragment per 16 output channels
-    kFormatDenseStream = 4,  // 1x1 with Ci = 32 * 2^n <= 1024: zero-filled fragments in the streaming kernel's order
+    kFormatDenseStream = 4,  // 1x1 with Ci = 32 * 2^n <= 1024 (fp32: 16 * 2^n <= 512): zero-filled fragments in the streaming kernel's order
     kFormatDense3x3 = 5,     // 3x3 whose dictionary has no 2-of-4 shape: zero-filled fragments, one per tap
     kFormatGather3x3 = 6     // 3x3, on request (rtoss_pack_coherent): per-block tap lists on the dense instruction
 };

@@ -1,7 +1,7 @@
-// 1x1 pattern-pruned convolution on the CDNA4 matrix cores (fp16 / bf16, fp32 accumulate),
-// and the packer that writes its weight fragments: the general kernel, for any input channel
-// count that is a multiple of 32.  (Channel counts of the form 32 * 2^n up to 1024 take the
-// streaming kernel with register-resident weights instead.)
+// 1x1 pattern-pruned convolution on the CDNA4 matrix cores (fp16 / bf16 / fp32, fp32 accumulate),
+// and the packer that writes its weight fragments: the general kernel, for any channel counts whose
+// input rows are a multiple of 4 bytes.  (64-byte multiples of 2^n stages with whole channel tiles
+// take the streaming kernel with register-resident weights instead.)
 //
 // Section IV.D prunes a 1x1 layer by cutting the flattened [Co][Ci] weight matrix into groups
 // of 9 and keeping k weights per group, so the pruned layer is a GEMM
@@ -12,14 +12,21 @@
 // once.  So the weights are expanded to zero-filled dense fragments (they are tiny and stay in
 // L2), and the kernel is built to stream activations: channels-last rows are contiguous, a
 // workgroup owns 128 consecutive positions x up to 128 output channels, and K runs over stages
-// of 32 input channels through a 5-deep ring of LDS buffers filled by global -> LDS copies four
-// stages ahead (an HBM-bound kernel lives on bytes in flight: two resident workgroups per CU x
+// of 64 bytes of input channels through a 5-deep ring of LDS buffers filled by global -> LDS copies
+// four stages ahead (an HBM-bound kernel lives on bytes in flight: two resident workgroups per CU x
 // four stages x 8 KB of activations).  Activation rows sit in LDS at a 64-byte pitch with their
 // four 16-byte chunks XOR-swizzled by (position / 2) % 4, which makes the 16-byte operand reads
 // of 8 neighbouring positions hit 8 different bank groups without any padding.
 //
+// Ragged channel counts (RAG): the last stage's lanes past the row end copy the block of zeros, rows that are
+// not 16-byte aligned are copied 4 bytes per lane (COPY), and the output rows leave LDS element by element
+// with consecutive lanes on consecutive channels (a row of 255 channels has no alignment to exploit, but
+// every store instruction still covers 64 neighbouring elements).  These shapes ran on the vector ALUs
+// before, at 74 us for 72 -> 255 channels on 28 028 positions (now 16 us).
+//
 // Operand layout of v_mfma_f32_16x16x32 (wave64; r = lane % 16, q = lane / 16): A lane holds
 // row r, K = 8q..8q+7; B lane holds column r, K = 8q..8q+7; D lane holds column r, rows 4q..4q+3.
+// fp32: four v_mfma_f32_16x16x4_f32 per step, instruction s on element s of every lane's 16 bytes.
 #include <algorithm>
 
 #include "common.h"
@@ -32,13 +39,14 @@ namespace rtoss {
 
 namespace {
 
-constexpr int kFrag = 1024;      // one A fragment: 64 lanes x 16 bytes = 16 output channels x 32 input channels
+constexpr int kFrag = 1024;      // one A fragment: 64 lanes x 16 bytes = 16 output channels x 64 bytes of input channels
 constexpr int kTilePos = 128;    // positions per workgroup
 constexpr int kRing = 5;
 
 inline int padded_tiles(int Co) { return ((Co + 15) / 16 + 7) / 8 * 8; }
-inline size_t frag_bytes(const rtoss_wdesc& d) { return (size_t)(d.Ci / 32) * padded_tiles(d.Co) * kFrag; }
-inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)2 * d.Ci + 16, 256); }
+inline int stages_of(const rtoss_wdesc& d) { return (d.Ci * elem_bytes(d.dt) + 63) / 64; }
+inline size_t frag_bytes(const rtoss_wdesc& d) { return (size_t)stages_of(d) * padded_tiles(d.Co) * kFrag; }
+inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)64 * stages_of(d) + 16, 256); }
 
 template <typename T>
 __global__ __launch_bounds__(256) void pack_dense1x1_kernel(const T* __restrict__ w, const uint8_t* __restrict__ idx,
@@ -61,27 +69,25 @@ __global__ __launch_bounds__(256) void pack_dense1x1_kernel(const T* __restrict_
     const int64_t tile = item / 64;
     const int mt = (int)(tile % m_tiles), cb = (int)(tile / m_tiles);
     const int co = 16 * mt + (lane % 16), q = lane / 16;
-    uint16_t v[8];
-    for (int j = 0; j < 8; ++j) {
-        const int ci = 32 * cb + 8 * q + j;
-        v[j] = 0;
+    constexpr int PER = 16 / (int)sizeof(T);  // channels in a lane's 16 bytes
+    T v[PER];
+    for (int j = 0; j < PER; ++j) {
+        const int ci = 4 * PER * cb + PER * q + j;
+        __builtin_memset(&v[j], 0, sizeof(T));
         if (co < Co && ci < Ci) {
             // element f of the flattened matrix sits in group f/9 at tap f%9 (groups may straddle rows)
             const int64_t f = (int64_t)co * Ci + ci;
             const int64_t g = f / 9;
             const int t = (int)(f - 9 * g);
-            if (g < G && ((masks[idx[g]] >> t) & 1u)) v[j] = __builtin_bit_cast(uint16_t, w[f]);
+            if (g < G && ((masks[idx[g]] >> t) & 1u)) v[j] = w[f];
         }
     }
     u32x4 pk;
-    pk.x = v[0] | ((uint32_t)v[1] << 16);
-    pk.y = v[2] | ((uint32_t)v[3] << 16);
-    pk.z = v[4] | ((uint32_t)v[5] << 16);
-    pk.w = v[6] | ((uint32_t)v[7] << 16);
+    __builtin_memcpy(&pk, v, 16);
     *(u32x4*)(out + item * 16) = pk;
 }
 
-template <typename T, typename TO, int TM>
+template <typename T, typename TO, int TM, bool RAG, int COPY>
 __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                           const char* __restrict__ wfrag, const char* __restrict__ zeros,
                                                           int64_t P, int Ci, int Co, int m_tiles_total, int co_blocks,
@@ -90,8 +96,8 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
     constexpr int TN = 2;                                // 16-position blocks per wave
     constexpr int A_PER_WAVE = (TM + 3) / 4;             // copy instructions per wave and stage (64 lanes x 16 B each)
     constexpr int A_AREA = A_PER_WAVE * 4 * 1024;
-    constexpr int X_PER_WAVE = 2;                        // 128 positions x 4 chunks = 512 chunks = 8 copies
-    constexpr int X_AREA = X_PER_WAVE * 4 * 1024;
+    constexpr int X_PER_WAVE = 32 / COPY;                // 128 positions x 64 bytes, 64 * COPY bytes per copy instruction
+    constexpr int X_AREA = 4 * X_PER_WAVE * 64 * COPY;
     constexpr int STAGE = A_AREA + X_AREA;
     constexpr int CPW = A_PER_WAVE + X_PER_WAVE;         // copies one wave has in flight per stage
     extern __shared__ __attribute__((aligned(16))) char smem[];  // kRing stages
@@ -104,17 +110,21 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
     const int cblk = work % co_blocks;
     const int64_t p0 = (int64_t)(work / co_blocks) * kTilePos;
     const int mt0 = cblk * TM;
-    const int stages = Ci / 32;
+    const int row_bytes = Ci * (int)sizeof(T);
+    const int stages = (row_bytes + 63) / 64;
 
     // ---- copy sources: every lane copies 16 bytes in every copy instruction (no branches); lanes
     // whose slot is padding read the packer's block of zeros ----
     const char* x_ptr[X_PER_WAVE];
+    unsigned tail_ok = 0;  // RAG: bit k = the last stage still has channels at this lane's copy k
 #pragma unroll
     for (int k = 0; k < X_PER_WAVE; ++k) {
-        const int c = (k * 4 + wave) * 64 + lane;          // LDS chunk this lane fills
-        const int pos = c >> 2, q = (c & 3) ^ ((pos >> 1) & 3);  // ... holds channel chunk q of position pos
+        const int e = ((k * 4 + wave) * 64 + lane) * COPY, c = e / 16;  // LDS byte, and chunk, this lane fills
+        const int pos = c >> 2, q = (c & 3) ^ ((pos >> 1) & 3);         // ... holds channel chunk q of position pos
+        const int at = q * 16 + e % 16;                                 // byte within the stage
         const bool real = p0 + pos < P;
-        x_ptr[k] = real ? (const char*)x + ((p0 + pos) * Ci + q * 8) * 2 : zeros;
+        x_ptr[k] = real ? (const char*)x + (p0 + pos) * row_bytes + at : zeros;
+        if (RAG && (stages - 1) * 64 + at < row_bytes) tail_ok |= 1u << k;
     }
     const char* a_ptr[A_PER_WAVE];
 #pragma unroll
@@ -132,7 +142,13 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
             copy16_to_lds(kk < TM ? a_ptr[k] + stage * a_stage_stride : a_ptr[k], base + kk * 1024);
         }
 #pragma unroll
-        for (int k = 0; k < X_PER_WAVE; ++k) copy16_to_lds(x_ptr[k] + stage * 64, base + A_AREA + (k * 4 + wave) * 1024);
+        for (int k = 0; k < X_PER_WAVE; ++k) {
+            const char* src = x_ptr[k] + stage * 64;
+            if (RAG && stage == stages - 1 && !(tail_ok >> k & 1u)) src = zeros;
+            char* dst = base + A_AREA + (k * 4 + wave) * 64 * COPY;
+            if constexpr (COPY == 16) copy16_to_lds(src, dst);
+            else copy4_to_lds(src, dst);
+        }
     };
 
     const int nn = lane & 15, qq = lane >> 4;
@@ -146,7 +162,7 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
     // fetched again into a free buffer, so that every wave has issued exactly CPW copies per
     // stage and the wait below can count them.
     constexpr int AHEAD = kRing - 2;  // stages still in flight when a stage must have landed
-    static_assert(AHEAD * CPW < 64, "outstanding copies must fit the counter");
+    static_assert(AHEAD * CPW < 64 && X_PER_WAVE <= 32, "outstanding copies must fit the counter");
 #pragma unroll
     for (int s = 0; s < kRing - 1; ++s) issue_stage(min(s, stages - 1), s);
     int buf = 0;
@@ -168,13 +184,12 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
         for (int m = 0; m < TM; ++m) {
             const u32x4 a = *(const u32x4*)(A + m * kFrag);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) Mat<T>::dense(a, b[j], acc[m][j]);
+            for (int j = 0; j < TN; ++j) acc[m][j] = Dense16<T>::mma(a, b[j], acc[m][j]);
         }
         buf = buf + 1 == kRing ? 0 : buf + 1;
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);  // the surplus copies have landed: LDS may be reused
     __syncthreads();
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // last matrix results are in the accumulators
 
     // ---- epilogue: transpose through LDS so that whole channel rows are written, 16 bytes per lane ----
     {
@@ -196,8 +211,12 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
                         const int64_t p_f = p0 + wave * (TN * 16) + j * 16 + nn;
                         if (p_f < P && co4 < Co) {
                             float vv[4] = {v.x, v.y, v.z, v.w};
-                            epi_scale_bias_act<4>(vv, ep, co4);
-                            epi_residual<TO, 4>(vv, ep, p_f, co4);
+                            if constexpr (RAG) {
+                                epi_ragged<TO, 4>(vv, ep, p_f, co4, Co);
+                            } else {
+                                epi_scale_bias_act<4>(vv, ep, co4);
+                                epi_residual<TO, 4>(vv, ep, p_f, co4);
+                            }
                             v = f32x4{vv[0], vv[1], vv[2], vv[3]};
                         }
                     }
@@ -216,6 +235,33 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
             constexpr int POS_PER_PASS = 64 / CH;
             constexpr int PASSES = (16 * TN) / POS_PER_PASS;
             const int co_first = 16 * (mt0 + h * TMH);
+            if constexpr (RAG) {
+                if (Co * EB % 16 != 0 || ep.ldy * EB % 16 != 0) {  // uniform: rows without a 16-byte alignment
+                    // a lane takes 4 bytes of a row (two 16-bit channels: the store need not be aligned), eight rows at a
+                    // time so that their LDS reads are in flight together
+                    constexpr int PER = 4 / EB, LANES = TMH * 16 / PER;  // lanes a row of this block occupies
+                    constexpr int ROWS = LANES >= 64 ? 1 : 64 / LANES;   // rows per instruction
+                    static_assert(LANES <= 64 && 64 % LANES == 0 && (16 * TN) % (8 * ROWS) == 0, "rows tile the wave");
+                    const int c = (lane % LANES) * PER, live = min(PER, Co - co_first - c);
+                    const int64_t first = p0 + wave * (TN * 16) + lane / LANES;
+                    TO* yp = y + first * ep.ldy + co_first + c;
+                    for (int r0 = 0; r0 < 16 * TN; r0 += 8 * ROWS) {
+                        uint32_t v[8];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            v[i] = *(const uint32_t*)(stage_out + (r0 + i * ROWS + lane / LANES) * ROW + c * EB);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            const int r = r0 + i * ROWS;
+                            if (first + r >= P || live <= 0) continue;
+                            char* at = (char*)(yp + (int64_t)r * ep.ldy);
+                            if (live == PER) __builtin_memcpy(at, &v[i], 4);
+                            else __builtin_memcpy(at, &v[i], EB);
+                        }
+                    }
+                    continue;
+                }
+            }
 #pragma unroll
             for (int ps = 0; ps < PASSES; ++ps) {
                 const int pl = ps * POS_PER_PASS + lane / CH;  // position within the wave's 32
@@ -229,7 +275,7 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
     }
 }
 
-template <typename T, typename TO, int TM>
+template <typename T, typename TO, int TM, bool RAG = false, int COPY = 16>
 rtoss_status launch_tm(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     const int64_t P = (int64_t)c.N * c.H * c.W;
@@ -240,7 +286,7 @@ rtoss_status launch_tm(const rtoss_wdesc& d, const ConvParams& c, const char* wf
     const int work_per_xcd = (int)((total + 7) / 8);
     constexpr int stage_bytes = ((TM + 3) / 4) * 4096 + 2 * 4096;
     const size_t smem = (size_t)kRing * stage_bytes;
-    auto kern = conv1x1_mma_kernel<T, TO, TM>;
+    auto kern = conv1x1_mma_kernel<T, TO, TM, RAG, COPY>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv1x1 shared memory attribute")) return st;
     dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
@@ -254,6 +300,15 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 {
     // the fragment section is padded to a multiple of 8 channel tiles, so a block of TM <= 8 tiles never reads past it
     const int tiles = (d.Co + 15) / 16;
+    const int row_bytes = d.Ci * (int)sizeof(T);
+    if (row_bytes % 16) {  // input rows are 4-byte aligned only
+        if (tiles <= 4) return launch_tm<T, TO, 4, true, 4>(d, c, wfrag, x, y, s);
+        return launch_tm<T, TO, 8, true, 4>(d, c, wfrag, x, y, s);
+    }
+    if (row_bytes % 64 || d.Co % 16) {
+        if (tiles <= 4) return launch_tm<T, TO, 4, true>(d, c, wfrag, x, y, s);
+        return launch_tm<T, TO, 8, true>(d, c, wfrag, x, y, s);
+    }
     if (tiles <= 2) return launch_tm<T, TO, 2>(d, c, wfrag, x, y, s);
     if (tiles <= 4) return launch_tm<T, TO, 4>(d, c, wfrag, x, y, s);
     return launch_tm<T, TO, 8>(d, c, wfrag, x, y, s);
@@ -263,7 +318,7 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 
 bool dense1x1_shape_ok(const rtoss_wdesc& d)
 {
-    return d.ksize == 1 && (d.dt == RTOSS_F16 || d.dt == RTOSS_BF16) && d.Ci % 32 == 0 && d.Co % 16 == 0;
+    return d.ksize == 1 && d.Ci * elem_bytes(d.dt) % 4 == 0;
 }
 
 size_t dense1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_bytes(d); }
@@ -272,12 +327,14 @@ rtoss_status launch_pack_dense1x1(const rtoss_wdesc& d, const void* w, const uin
                                   void* live_values, uint8_t* live_idx, hipStream_t s)
 {
     const int m_tiles = padded_tiles(d.Co);
-    const int64_t items = (int64_t)(d.Ci / 32) * m_tiles * 64;
+    const int64_t items = (int64_t)stages_of(d) * m_tiles * 64;
     const int zero_items = (int)(zero_bytes(d) / 16);
     const int64_t G = (int64_t)d.Co * d.Ci / 9;
     const LiveJob job = make_live_job(live_values, live_idx, G);
     dim3 grid((unsigned)(job.blocks + (items + zero_items + 255) / 256)), block(256);
-    if (d.dt == RTOSS_F16)
+    if (d.dt == RTOSS_F32)
+        pack_dense1x1_kernel<float><<<grid, block, 0, s>>>((const float*)w, idx, dict, (char*)section, d.Co, d.Ci, m_tiles, G, items, zero_items, job);
+    else if (d.dt == RTOSS_F16)
         pack_dense1x1_kernel<f16_t><<<grid, block, 0, s>>>((const f16_t*)w, idx, dict, (char*)section, d.Co, d.Ci, m_tiles, G, items, zero_items, job);
     else
         pack_dense1x1_kernel<bf16_t><<<grid, block, 0, s>>>((const bf16_t*)w, idx, dict, (char*)section, d.Co, d.Ci, m_tiles, G, items, zero_items, job);
@@ -289,6 +346,7 @@ rtoss_status launch_conv1x1_mma(const rtoss_wdesc& d, const ConvParams& c, const
 {
     const char* wf = (const char*)section;
     const bool f32out = c.out_dt == RTOSS_F32;
+    if (d.dt == RTOSS_F32) return launch_typed<float, float>(d, c, wf, x, y, s);
     if (d.dt == RTOSS_F16)
         return f32out ? launch_typed<f16_t, float>(d, c, wf, x, y, s) : launch_typed<f16_t, f16_t>(d, c, wf, x, y, s);
     return f32out ? launch_typed<bf16_t, float>(d, c, wf, x, y, s) : launch_typed<bf16_t, bf16_t>(d, c, wf, x, y, s);

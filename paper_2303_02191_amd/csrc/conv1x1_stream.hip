@@ -1,5 +1,5 @@
 // 1x1 pattern-pruned convolution as a streaming kernel with register-resident weights
-// (fp16 / bf16, fp32 accumulate), and the packer that writes its weight fragments.
+// (fp16 / bf16 / fp32, fp32 accumulate), and the packer that writes its weight fragments.
 //
 // Section IV.D prunes a 1x1 layer by cutting the flattened [Co][Ci] weight matrix into groups
 // of 9 and keeping k weights per group; the pruned layer is the GEMM
@@ -25,6 +25,11 @@
 //     4q+i of the wave's m-th fragment is channel 4*MT*q + 4*m + i of the wave's slice, and the
 //     four lane quarters of a position together write one contiguous run of 16*MT channels.
 //
+// fp32 tensors run through the same kernel: a stage is then 16 channels (the same 64 bytes per position) and
+// a fragment step is four v_mfma_f32_16x16x4_f32, instruction s on element s of every lane's 16 bytes.  The
+// fp32 instruction has 1/16 of the 16-bit one's rate, so these layers sit near the ridge instead of far below
+// it; measured 128 -> 64 channels on 25 600 positions: 8.8-11 us, against 32 us on the vector ALUs.
+//
 // Operand layout of v_mfma_f32_16x16x32 (wave64; r = lane % 16, q = lane / 16): A lane holds
 // row r, K = 8q..8q+7; B lane holds column r, K = 8q..8q+7; D lane holds column r, rows 4q..4q+3.
 #include <algorithm>
@@ -42,10 +47,12 @@ namespace {
 constexpr int kFrag = 1024;  // one A fragment: 64 lanes x 16 bytes = 16 output channels x 32 input channels
 constexpr int kHeadBuffers = 2;  // buffers of a workgroup's range that the consumer waves copy themselves
 
-// Shape plan, a function of KS = Ci / 32 (1, 2, 4 ... 32) and of WM, the number of waves a
+constexpr int mt_of(int KS) { return KS <= 8 ? 4 : (KS == 16 ? 2 : 1); }
+
+// Shape plan, a function of KS = Ci / 32 (fp32: Ci / 16; 1, 2, 4 ... 32) and of WM, the number of waves a
 // workgroup spreads over output channels (the other 4 / WM spread over positions).
 template <int KS, int WM> struct Plan {
-    static constexpr int MT = KS <= 8 ? 4 : (KS == 16 ? 2 : 1);  // fragments per wave along output channels
+    static constexpr int MT = mt_of(KS);  // fragments per wave along output channels
     static constexpr int WN = 4 / WM;
     // 16-position blocks per wave and buffer: one.  (Buffers of up to four blocks per wave, 16 KB for most shapes,
     // measured slower on a 57-layer model, 0.906 against 0.892-0.895 ms: small buffers mean small workgroups in LDS,
@@ -78,7 +85,7 @@ template <int MAXL, int COPIES> __device__ __forceinline__ void wait_tail(int64_
     }
 }
 
-inline int mt_of(int KS) { return KS <= 8 ? 4 : (KS == 16 ? 2 : 1); }
+inline int stages_of(const rtoss_wdesc& d) { return d.Ci * elem_bytes(d.dt) / 64; }  // 64 bytes of channels per stage
 inline int wm_of(int KS, int Co)
 {
     const int tiles = (Co + 15) / 16, groups = (tiles + mt_of(KS) - 1) / mt_of(KS);
@@ -94,10 +101,10 @@ inline int co_blocks_of(int KS, int Co)
 }
 inline size_t frag_bytes(const rtoss_wdesc& d)
 {
-    const int KS = d.Ci / 32;
+    const int KS = stages_of(d);
     return (size_t)co_blocks_of(KS, d.Co) * wm_of(KS, d.Co) * mt_of(KS) * KS * kFrag;
 }
-inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)2 * d.Ci + 16, 256); }
+inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)elem_bytes(d.dt) * d.Ci + 16, 256); }
 
 // Fragment order: [channel block][wave slice wm][fragment m][stage s][lane].
 struct StreamPackArgs {
@@ -141,23 +148,21 @@ __device__ __forceinline__ void pack_stream1x1_body(const StreamPackArgs& a, con
     const int cb = (int)(f / WM);
     const int r = lane % 16, q = lane / 16;
     const int co = cb * (16 * MT * WM) + wm * (16 * MT) + (r / 4) * (4 * MT) + 4 * m + (r % 4);
-    uint16_t v[8];
-    for (int j = 0; j < 8; ++j) {
-        const int ci = 32 * s + 8 * q + j;
-        v[j] = 0;
+    constexpr int PER = 16 / (int)sizeof(T);  // channels in a lane's 16 bytes
+    T v[PER];
+    for (int j = 0; j < PER; ++j) {
+        const int ci = 4 * PER * s + PER * q + j;
+        __builtin_memset(&v[j], 0, sizeof(T));
         if (co < Co) {
             // element e of the flattened matrix sits in group e/9 at tap e%9 (groups may straddle rows)
             const int64_t e = (int64_t)co * Ci + ci;
             const int64_t g = e / 9;
             const int t = (int)(e - 9 * g);
-            if (g < G && ((masks[idx[g]] >> t) & 1u)) v[j] = __builtin_bit_cast(uint16_t, w[e]);
+            if (g < G && ((masks[idx[g]] >> t) & 1u)) v[j] = w[e];
         }
     }
     u32x4 pk;
-    pk.x = v[0] | ((uint32_t)v[1] << 16);
-    pk.y = v[2] | ((uint32_t)v[3] << 16);
-    pk.z = v[4] | ((uint32_t)v[5] << 16);
-    pk.w = v[6] | ((uint32_t)v[7] << 16);
+    __builtin_memcpy(&pk, v, 16);
     *(u32x4*)(out + item * 16) = pk;
 }
 
@@ -189,7 +194,7 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
 {
     using PL = Plan<KS, WM>;
     constexpr int MT = PL::MT, WN = PL::WN, NB = PL::NB, PB = PL::PB, BUF = PL::BUF, COPIES = PL::COPIES, RING = PL::RING;
-    constexpr int Ci = 32 * KS;
+    constexpr int ROW = 64 * KS;  // bytes of one position
     extern __shared__ __attribute__((aligned(16))) char smem[];  // RING buffers
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -212,11 +217,11 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
             const int s = c / (PB * 4), rem = c % (PB * 4);
             const int pos = rem >> 2, q = (rem & 3) ^ ((pos >> 1) & 3);
             src_pos[k] = pos;
-            src_off[k] = (pos * Ci + s * 32 + q * 8) * 2;
+            src_off[k] = pos * ROW + s * 64 + q * 16;
         }
         auto issue_buffer = [&](int64_t b, int slot) {
             const int64_t p0 = b * PB;
-            const char* base = (const char*)x + p0 * (Ci * 2);
+            const char* base = (const char*)x + p0 * ROW;
             char* dst = smem + slot * BUF;
             if (p0 + PB <= P) {
 #pragma unroll
@@ -268,7 +273,7 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
         const int64_t bb = b0 + i;
         if (bb >= b1) break;
         const int64_t p0 = bb * PB;
-        const char* base = (const char*)x + p0 * (Ci * 2);
+        const char* base = (const char*)x + p0 * ROW;
         char* dst = smem + i * BUF;
 #pragma unroll
         for (int t = 0; t < (COPIES + 3) / 4; ++t) {
@@ -277,7 +282,7 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
             const int c = k * 64 + lane;
             const int st = c / (PB * 4), rem = c % (PB * 4);
             const int pos = rem >> 2, q = (rem & 3) ^ ((pos >> 1) & 3);
-            copy16_to_lds(p0 + pos < P ? base + (pos * Ci + st * 32 + q * 8) * 2 : zeros, dst + k * 1024);
+            copy16_to_lds(p0 + pos < P ? base + pos * ROW + st * 64 + q * 16 : zeros, dst + k * 1024);
         }
     }
     asm volatile("" ::: "memory");
@@ -373,11 +378,12 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     DeviceInfo dev;
     if (rtoss_status st = current_device(&dev)) return st;
     const int resident = std::max(8, dev.cus) * per_cu;
-    const int64_t by_work = std::max<int64_t>(1, (nbuf + 1) / 2);
+    // (fp32 steps take 16 times as long: one buffer is enough work to be worth the fragments)
+    const int64_t by_work = sizeof(T) == 4 ? nbuf : std::max<int64_t>(1, (nbuf + 1) / 2);
     const int wgs_per_cb = (int)std::max<int64_t>(1, std::min<int64_t>(by_work, resident / co_blocks));
     const int total = wgs_per_cb * co_blocks;
     const int work_per_xcd = (total + 7) / 8;
-    if (P * d.Ci * 2 / PL::PB > 0x7fffffffffffll || nbuf > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv1x1: too many positions");
+    if (P * d.Ci * (int)sizeof(T) / PL::PB > 0x7fffffffffffll || nbuf > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv1x1: too many positions");
     dim3 grid((unsigned)(work_per_xcd * 8)), block(320);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Co, co_blocks, nbuf, wgs_per_cb,
                                    total, work_per_xcd, c.ep);
@@ -398,7 +404,7 @@ rtoss_status launch_ks(const rtoss_wdesc& d, const ConvParams& c, const char* wf
 template <typename T, typename TO>
 rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
-    switch (d.Ci / 32) {
+    switch (stages_of(d)) {
     case 1: return launch_ks<T, TO, 1>(d, c, wfrag, x, y, s);
     case 2: return launch_ks<T, TO, 2>(d, c, wfrag, x, y, s);
     case 4: return launch_ks<T, TO, 4>(d, c, wfrag, x, y, s);
@@ -415,9 +421,8 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 
 bool stream1x1_shape_ok(const rtoss_wdesc& d)
 {
-    const int KS = d.Ci / 32;
-    return d.ksize == 1 && (d.dt == RTOSS_F16 || d.dt == RTOSS_BF16) && d.Ci % 32 == 0 && d.Co % 16 == 0 && KS >= 1 &&
-           KS <= 32 && (KS & (KS - 1)) == 0;
+    const int KS = stages_of(d);
+    return d.ksize == 1 && d.Ci * elem_bytes(d.dt) % 64 == 0 && d.Co % 16 == 0 && KS >= 1 && KS <= 32 && (KS & (KS - 1)) == 0;
 }
 
 size_t stream1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_bytes(d); }
@@ -431,7 +436,7 @@ static StreamPackArgs stream_pack_args(const rtoss_wdesc& d, const void* w, cons
     a.out = (char*)section;
     a.Co = d.Co;
     a.Ci = d.Ci;
-    a.KS = d.Ci / 32;
+    a.KS = stages_of(d);
     a.MT = mt_of(a.KS);
     a.WM = wm_of(a.KS, d.Co);
     a.G = (int64_t)d.Co * d.Ci / 9;
@@ -448,7 +453,8 @@ rtoss_status launch_pack_stream1x1(const rtoss_wdesc& d, const void* w, const ui
     int blocks = 0;
     const StreamPackArgs a = stream_pack_args(d, w, idx, section, live_values, live_idx, &blocks);
     dim3 grid((unsigned)blocks), block(256);
-    if (d.dt == RTOSS_F16) pack_stream1x1_kernel<f16_t><<<grid, block, 0, s>>>(a, dict);
+    if (d.dt == RTOSS_F32) pack_stream1x1_kernel<float><<<grid, block, 0, s>>>(a, dict);
+    else if (d.dt == RTOSS_F16) pack_stream1x1_kernel<f16_t><<<grid, block, 0, s>>>(a, dict);
     else pack_stream1x1_kernel<bf16_t><<<grid, block, 0, s>>>(a, dict);
     return check_hip(hipGetLastError(), "pack stream1x1 launch");
 }
@@ -468,7 +474,8 @@ rtoss_status launch_pack_stream1x1_batch(const PackItem* items, int n, const Dic
         }
         b.first_block[b.n] = total;
         dim3 grid((unsigned)total), block(256);
-        if (items[base].d.dt == RTOSS_F16) pack_stream1x1_batch_kernel<f16_t><<<grid, block, 0, s>>>(b, dict);
+        if (items[base].d.dt == RTOSS_F32) pack_stream1x1_batch_kernel<float><<<grid, block, 0, s>>>(b, dict);
+        else if (items[base].d.dt == RTOSS_F16) pack_stream1x1_batch_kernel<f16_t><<<grid, block, 0, s>>>(b, dict);
         else pack_stream1x1_batch_kernel<bf16_t><<<grid, block, 0, s>>>(b, dict);
         if (rtoss_status st = check_hip(hipGetLastError(), "pack stream1x1 batch launch")) return st;
     }
@@ -480,6 +487,7 @@ rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, co
 {
     const char* wf = (const char*)section;
     const bool f32out = c.out_dt == RTOSS_F32;
+    if (d.dt == RTOSS_F32) return launch_typed<float, float>(d, c, wf, x, y, s);
     if (d.dt == RTOSS_F16)
         return f32out ? launch_typed<f16_t, float>(d, c, wf, x, y, s) : launch_typed<f16_t, f16_t>(d, c, wf, x, y, s);
     return f32out ? launch_typed<bf16_t, float>(d, c, wf, x, y, s) : launch_typed<bf16_t, bf16_t>(d, c, wf, x, y, s);

@@ -51,12 +51,13 @@ constexpr int kTM = 4;                 // channel fragments per block of the blo
 constexpr int kBlockBytes = kTM * 9 * kFrag;  // weights of one (stage, channel block)
 inline int stage_channels(rtoss_dtype dt) { return dt == RTOSS_F32 ? 16 : 32; }  // 64 bytes per position
 
+inline int stages_of(const rtoss_wdesc& d) { return (d.Ci + stage_channels(d.dt) - 1) / stage_channels(d.dt); }
 inline int channel_blocks(int Co) { return (Co + 16 * kTM - 1) / (16 * kTM); }
 inline size_t frag_bytes(const rtoss_wdesc& d)
 {
-    return (size_t)(d.Ci / stage_channels(d.dt)) * channel_blocks(d.Co) * kBlockBytes;
+    return (size_t)stages_of(d) * channel_blocks(d.Co) * kBlockBytes;
 }
-inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)elem_bytes(d.dt) * d.Ci + 16, 256); }
+inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)64 * stages_of(d) + 16, 256); }
 
 // Fragment order: [stage][channel block][fragment m][tap t][lane].
 template <typename T>
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(256) void pack_dense3x3_kernel(const T* __restrict_
     for (int j = 0; j < PER_LANE; ++j) {
         const int ci = (4 * PER_LANE) * stage + PER_LANE * q + j;
         __builtin_memset(&v[j], 0, sizeof(T));
-        if (co < Co) {
+        if (co < Co && ci < Ci) {
             const int64_t g = (int64_t)co * Ci + ci;
             if ((masks[idx[g]] >> t) & 1u) v[j] = w[g * 9 + t];
         }
@@ -103,7 +104,9 @@ __global__ __launch_bounds__(256) void pack_dense3x3_kernel(const T* __restrict_
 
 
 // TM channel fragments (of the blob's blocks of 4) and RT x CT position blocks per workgroup.
-template <typename T, typename TO, int S, int TM, int RT, int CT>
+// RAG: channel counts between the stages (in; rows stay 16-byte multiples) and tiles (out): the last stage's copy
+// lanes past the row end read the block of zeros, outputs are stored under a per-channel bound.
+template <typename T, typename TO, int S, int TM, int RT, int CT, bool RAG>
 __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                             const char* __restrict__ wfrag, const char* __restrict__ zeros,
                                                             int H, int W, int Ci, int Co, int Ho, int Wo, int cblocks,
@@ -128,15 +131,18 @@ __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict_
     const int cb = blockIdx.y / (kTM / TM), m_first = (blockIdx.y % (kTM / TM)) * TM, n_img = blockIdx.z;
     const int oh0 = tile_r * G::TH, ow0 = tile_c * G::TW;
     const int ih0 = oh0 * S - 1, iw0 = ow0 * S - 1;
-    const int stages = Ci / (64 / EBI);
+    const int stages = RAG ? (Ci * EBI + 63) / 64 : Ci / (64 / EBI);
 
     // Copy sources of stage 0.  Every lane copies 16 bytes in every copy instruction; a lane whose LDS
     // slot is zero padding of the tile (or a pad chunk) reads the block of zeros behind the fragments.
     const char* x_ptr[X_PER_WAVE];
+    static_assert(X_PER_WAVE <= 32, "one bit per copy");
+    unsigned tail_ok = 0;  // RAG: bit k = the last stage still has channels at this lane's copy k
 #pragma unroll
     for (int k = 0; k < X_PER_WAVE; ++k) {
         const int c = (k * 4 + wave) * 64 + lane;
         const int pos = c / G::kChunks, q = c % G::kChunks;
+        if (RAG && (stages - 1) * 64 + 16 * q < Ci * EBI) tail_ok |= 1u << k;
         const int pr = pos / G::LW, pc = pos % G::LW;
         const int ih = ih0 + pr, iw = iw0 + pc;
         const bool inside = q < 4 && pr < G::IH && pc < G::IW && ih >= 0 && ih < H && iw >= 0 && iw < W;
@@ -167,7 +173,11 @@ __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict_
             copy16_to_lds(kk < A_COPIES ? a_src + stage * a_stage_stride + kk * 1024 : zeros, lds_a + kk * 1024);
         }
 #pragma unroll
-        for (int k = 0; k < X_PER_WAVE; ++k) copy16_to_lds(x_ptr[k] + stage * 64, lds_x + (k * 4 + wave) * 1024);
+        for (int k = 0; k < X_PER_WAVE; ++k) {
+            const char* src = x_ptr[k] + stage * 64;
+            if (RAG && stage == stages - 1 && !(tail_ok >> k & 1u)) src = zeros;
+            copy16_to_lds(src, lds_x + (k * 4 + wave) * 1024);
+        }
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies have landed in LDS
         __syncthreads();                     // ... and everybody's
 #pragma unroll
@@ -196,7 +206,7 @@ __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict_
     for (int j = 0; j < kTN; ++j) {
         const int blk = wave * kTN + j;
         const int oh = oh0 + 4 * (blk / CT) + pr, ow = ow0 + 4 * (blk % CT) + pc;
-        if (oh >= Ho || ow >= Wo || co_lane >= Co) continue;  // Co is a multiple of 16: a run is all in or all out
+        if (oh >= Ho || ow >= Wo || co_lane >= Co) continue;  // (not RAG: Co is a multiple of 16, a run is all in or all out)
         const int64_t pos = ((int64_t)n_img * Ho + oh) * Wo + ow;
         TO* yp = y + pos * ep.ldy + co_lane;
         float v[RUN];
@@ -204,6 +214,11 @@ __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict_
         for (int m = 0; m < TM; ++m)
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][j][e];
+        if constexpr (RAG) {
+            epi_ragged<TO, RUN>(v, ep, pos, co_lane, Co);
+            store_ragged<TO, RUN>(yp - co_lane, v, co_lane, Co, ep.ldy);
+            continue;
+        }
         epi_scale_bias_act<RUN>(v, ep, co_lane);
         epi_residual<TO, RUN>(v, ep, pos, co_lane);
         if constexpr (EB == 4) {
@@ -228,7 +243,7 @@ __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict_
     }
 }
 
-template <typename T, typename TO, int S, int TM, int RT, int CT>
+template <typename T, typename TO, int S, int TM, int RT, int CT, bool RAG = false>
 rtoss_status launch_shape(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     using G = Geom<S, RT, CT>;
@@ -238,7 +253,7 @@ rtoss_status launch_shape(const rtoss_wdesc& d, const ConvParams& c, const char*
     constexpr int x_copies_per_wave = ((G::x_bytes / 16 + 63) / 64 + 3) / 4;
     constexpr int a_copies_per_wave = (TM * 9 + 3) / 4;
     const size_t smem = (size_t)(a_copies_per_wave + x_copies_per_wave) * 4096;
-    auto kern = conv3x3_dense_kernel<T, TO, S, TM, RT, CT>;
+    auto kern = conv3x3_dense_kernel<T, TO, S, TM, RT, CT, RAG>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv3x3 dense shared memory attribute")) return st;
     const int ygrid = cblocks * (kTM / TM);
@@ -256,6 +271,7 @@ rtoss_status launch_stride(const rtoss_wdesc& d, const ConvParams& c, const char
     // 16 channels x 4x16 positions (16 times as many workgroups).
     const int Ho = (c.H + 2 - 3) / S + 1, Wo = (c.W + 2 - 3) / S + 1;
     const int64_t big = (int64_t)((Ho + 15) / 16) * ((Wo + 15) / 16) * channel_blocks(d.Co) * c.N;
+    if (d.Ci % stage_channels(d.dt) || d.Co % 16) return launch_shape<T, TO, S, 1, 1, 4, true>(d, c, wfrag, x, y, s);
     if (big < 256) return launch_shape<T, TO, S, 1, 1, 4>(d, c, wfrag, x, y, s);
     return launch_shape<T, TO, S, 4, 4, 4>(d, c, wfrag, x, y, s);
 }
@@ -273,7 +289,7 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 
 bool dense3x3_shape_ok(const rtoss_wdesc& d)
 {
-    return d.ksize == 3 && d.Ci % stage_channels(d.dt) == 0 && d.Co % 16 == 0;
+    return d.ksize == 3 && d.Ci * elem_bytes(d.dt) % 16 == 0;  // rows of whole 16-byte copies
 }
 
 size_t dense3x3_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_bytes(d); }

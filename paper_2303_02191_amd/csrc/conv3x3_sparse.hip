@@ -121,9 +121,11 @@ __device__ __forceinline__ void pack_sparse3x3_body(const SparsePackArgs& a, con
         slots[e] = (uint16_t)(tp[0] | (tp[1] << 4) | (f[0] << 8) | (f[1] << 10));
     }
     // ---- stage: 16 rows x 36 chunks of weights, 16 rows x 2 chunks of indices (rows past Co are zeros) ----
-    // (rows start at multiples of 576 and 32 bytes from the tensors' first elements; the interface asks for
-    // element alignment only, so tensors that do not start on a 16-byte boundary are staged element-wise)
-    if (((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(idx)) & 15) == 0) {
+    // (rows start at multiples of 18 Ci and Ci bytes from the tensors' first elements; the interface asks for
+    // element alignment only, so rows that do not start on 16-byte boundaries are staged element-wise, and so is a
+    // last stage with fewer than 32 channels)
+    const int channels = min(32, Ci - 32 * cb);
+    if (Ci % 32 == 0 && ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(idx)) & 15) == 0) {
         for (int c = threadIdx.x; c < 16 * 36; c += 256) {
             const int r = c / 36, k = c % 36;
             const int co = tile_row_channel(mt, r);
@@ -143,12 +145,12 @@ __device__ __forceinline__ void pack_sparse3x3_body(const SparsePackArgs& a, con
         for (int c = threadIdx.x; c < 16 * 288; c += 256) {
             const int r = c / 288, e = c % 288;
             const int co = tile_row_channel(mt, r);
-            wl[r][e] = co < Co ? w16[((int64_t)co * Ci + 32 * cb) * 9 + e] : (uint16_t)0;
+            wl[r][e] = co < Co && e < 9 * channels ? w16[((int64_t)co * Ci + 32 * cb) * 9 + e] : (uint16_t)0;
         }
         for (int c = threadIdx.x; c < 16 * 32; c += 256) {
             const int r = c / 32, e = c % 32;
             const int co = tile_row_channel(mt, r);
-            il[r][e] = co < Co ? idx[(int64_t)co * Ci + 32 * cb + e] : (uint8_t)0;
+            il[r][e] = co < Co && e < channels ? idx[(int64_t)co * Ci + 32 * cb + e] : (uint8_t)0;
         }
     }
     __syncthreads();
@@ -223,7 +225,10 @@ __global__ __launch_bounds__(256) void pack_sparse3x3_batch_kernel(SparsePackBat
 // DB: two LDS buffers; the copies of the next stage are issued right after the barrier that opens a stage and land
 // while it is multiplied (one barrier per stage).  For deep stride-1 layers, whose schedule with operand reads ahead
 // is held to two workgroups per compute unit by its registers anyway: two buffers of 38 KB each still fit twice.
-template <typename T, typename TO, int S, int TM, int TN, int RT, int CT, bool AHEAD, int LAY = 0, bool DB = false>
+// RAG: channel counts that are no multiples of 32 (in; a multiple of 8, so that rows stay 16-byte aligned) or 16
+// (out): the last stage's copy lanes past the row end read the block of zeros, and outputs are stored under a
+// per-channel bound.
+template <typename T, typename TO, int S, int TM, int TN, int RT, int CT, bool AHEAD, int LAY = 0, bool DB = false, bool RAG = false>
 __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                                 const char* __restrict__ wfrag,
                                                                 const char* __restrict__ zeros, int H, int W, int Ci,
@@ -260,7 +265,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     const int tile_r = tile / tiles_c, tile_c = tile % tiles_c;
     const int oh0 = tile_r * G::TH, ow0 = tile_c * G::TW;
     const int ih0 = oh0 * S - 1, iw0 = ow0 * S - 1;
-    const int stages = Ci / 32;
+    const int stages = RAG ? (Ci + 31) / 32 : Ci / 32;
 
     const char* a_src = wfrag + (int64_t)mt0 * TILE + lane * 16;
     const int64_t a_stage_stride = (int64_t)m_tiles_total * TILE;
@@ -277,10 +282,13 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     // Copy sources of stage 0.  Every lane copies 16 bytes in every copy instruction; a lane whose LDS
     // slot is zero padding of the tile (or a pad chunk) reads the block of zeros behind the fragments.
     const char* x_ptr[X_PER_WAVE];
+    static_assert(X_PER_WAVE <= 32, "one bit per copy");
+    unsigned tail_ok = 0;  // RAG: bit k = the last stage still has channels at this lane's copy k
 #pragma unroll
     for (int k = 0; k < X_PER_WAVE; ++k) {
         const int c = (k * 4 + wave) * 64 + lane;
         const int pos = c / G::kChunks, q = c % G::kChunks;
+        if (RAG && (stages - 1) * 32 + 8 * q < Ci) tail_ok |= 1u << k;
         const int xr = pos / G::LW, xc = pos % G::LW;
         const int ih = ih0 + xr, iw = iw0 + xc;
         const bool inside = q < 4 && xr < G::IH && xc < G::IW && ih >= 0 && ih < H && iw >= 0 && iw < W;
@@ -306,7 +314,11 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     auto issue_copies = [&](int stage, char* buf, bool with_weights) {
         if (with_weights) issue_weight_copies(stage, buf);
 #pragma unroll
-        for (int k = 0; k < X_PER_WAVE; ++k) copy16_to_lds(x_ptr[k] + stage * 64, buf + A_BYTES + (k * 4 + wave) * 1024);
+        for (int k = 0; k < X_PER_WAVE; ++k) {
+            const char* src = x_ptr[k] + stage * 64;
+            if (RAG && stage == stages - 1 && !(tail_ok >> k & 1u)) src = zeros;
+            copy16_to_lds(src, buf + A_BYTES + (k * 4 + wave) * 1024);
+        }
     };
     if constexpr (DB) issue_copies(0, smem, false);
     auto run_stage = [&](auto first_tag, int stage) {
@@ -453,12 +465,17 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
 #pragma unroll
         for (int mg = 0; mg < TM; mg += 4) {
             const int co = 16 * mt0 + tile_quarter_offset(mg, qq);
-            if (co >= Co) continue;  // Co is a multiple of 16 and the run of 16 starts at a multiple of 16: all in or all out
+            if (co >= Co) continue;  // (not RAG: Co is a multiple of 16, a run of 16 channels is all in or all out)
             float vv[16];
 #pragma unroll
             for (int m = 0; m < 4; ++m)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) vv[4 * m + e] = acc[mg + m][j][e];
+            if constexpr (RAG) {
+                epi_ragged<TO, 16>(vv, ep, pos, co, Co);
+                store_ragged<TO, 16>(yp, vv, co, Co, ep.ldy);
+                continue;
+            }
             epi_scale_bias_act<16>(vv, ep, co);
             epi_residual<TO, 16>(vv, ep, pos, co);
             if constexpr (sizeof(TO) == 4) {
@@ -479,7 +496,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     }
 }
 
-template <typename T, typename TO, int S, int TM, int TN, int RT, int CT, bool AHEAD = true, int LAY = 0, bool DB = false>
+template <typename T, typename TO, int S, int TM, int TN, int RT, int CT, bool AHEAD = true, int LAY = 0, bool DB = false, bool RAG = false>
 rtoss_status launch_variant_sb(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y,
                             hipStream_t s)
 {
@@ -490,7 +507,7 @@ rtoss_status launch_variant_sb(const rtoss_wdesc& d, const ConvParams& c, const 
     const int co_blocks = ((d.Co + 15) / 16 + TM - 1) / TM;
     constexpr int x_copies_per_wave = ((G::x_bytes / 16 + 63) / 64 + 3) / 4;
     const size_t smem = (DB ? 2 : 1) * ((size_t)TM * layout_tile_bytes(kLayouts[LAY]) + (size_t)x_copies_per_wave * 4096);
-    auto kern = conv3x3_sparse_sb_kernel<T, TO, S, TM, TN, RT, CT, AHEAD, LAY, DB>;
+    auto kern = conv3x3_sparse_sb_kernel<T, TO, S, TM, TN, RT, CT, AHEAD, LAY, DB, RAG>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)tiles_r * tiles_c * co_blocks * c.N;
@@ -503,11 +520,21 @@ rtoss_status launch_variant_sb(const rtoss_wdesc& d, const ConvParams& c, const 
     return check_hip(hipGetLastError(), "conv3x3 sparse launch");
 }
 
+inline bool ragged(const rtoss_wdesc& d) { return d.Ci % 32 != 0 || d.Co % 16 != 0; }
+
+// Ragged channel counts: one variant per stride and layout, small tiles and few registers (such layers are narrow).
+template <typename T, typename TO, int LAY>
+rtoss_status launch_typed_ragged(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+{
+    if (c.stride == 1) return launch_variant_sb<T, TO, 1, 4, 2, 2, 4, false, LAY, false, true>(d, c, wfrag, x, y, s);
+    return launch_variant_sb<T, TO, 2, 4, 1, 1, 4, false, LAY, false, true>(d, c, wfrag, x, y, s);
+}
+
 // Large stride-1 layers (more than 64 channels in and out, enough 16x16 x 128-channel tiles to give most
 // compute units one) take the pipelined kernel of conv3x3_rows.hip.
 inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
 {
-    if (c.stride != 1 || d.Co <= 64 || d.Ci <= 64) return false;
+    if (c.stride != 1 || d.Co <= 64 || d.Ci <= 64 || ragged(d)) return false;
     const int64_t tiles8 = (int64_t)((c.H + 15) / 16) * ((c.W + 15) / 16) * c.N * (((d.Co + 15) / 16 + 7) / 8);
     return tiles8 >= 200;
 }
@@ -517,6 +544,7 @@ template <typename T, typename TO>
 rtoss_status launch_typed_layout1(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y,
                                   hipStream_t s)
 {
+    if (ragged(d)) return launch_typed_ragged<T, TO, 1>(d, c, wfrag, x, y, s);
     if (c.stride == 1) return launch_variant_sb<T, TO, 1, 4, 2, 2, 4, false, 1>(d, c, wfrag, x, y, s);
     if (d.Ci == 32) return launch_variant_sb<T, TO, 2, 4, 1, 1, 4, false, 1>(d, c, wfrag, x, y, s);
     return launch_variant_sb<T, TO, 2, 4, 2, 2, 4, false, 1>(d, c, wfrag, x, y, s);
@@ -526,6 +554,7 @@ template <typename T, typename TO>
 rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y,
                           hipStream_t s)
 {
+    if (ragged(d)) return launch_typed_ragged<T, TO, 0>(d, c, wfrag, x, y, s);
     // The fragment section is padded to a multiple of 8 channel tiles, so any TM <= 8 may over-read rows
     // that hold zeros; outputs beyond Co are never stored.
     // Layers with at most 64 output channels, or too few stages to amortise the pipelined kernel's
@@ -572,7 +601,8 @@ int sparse3x3_layout(const Dict& dict)
 
 bool sparse3x3_shape_ok(const rtoss_wdesc& d)
 {
-    return d.ksize == 3 && (d.dt == RTOSS_F16 || d.dt == RTOSS_BF16) && d.Ci % 32 == 0 && d.Co % 16 == 0;
+    // (rows of 16-byte multiples: the activation copies move 8 channels per lane)
+    return d.ksize == 3 && (d.dt == RTOSS_F16 || d.dt == RTOSS_BF16) && d.Ci % 8 == 0;
 }
 
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout)
@@ -591,7 +621,7 @@ static SparsePackArgs sparse_pack_args(const rtoss_wdesc& d, int layout, const v
     a.Co = d.Co;
     a.Ci = d.Ci;
     a.m_tiles = padded_m_tiles(d.Co);
-    a.total_items = (int64_t)(d.Ci / 32) * a.m_tiles * items_per_tile;
+    a.total_items = (int64_t)sparse_stages(d) * a.m_tiles * items_per_tile;
     a.zero_items = (int)(zero_block_bytes(d) / 16);
     a.job = make_live_job(live_values, live_idx, (int64_t)d.Co * d.Ci);
     *blocks = (int)(a.job.blocks + a.total_items / items_per_tile + (a.zero_items + 255) / 256);  // public section, tiles, zeros

@@ -1,8 +1,8 @@
 // Direct pattern-sparse convolution on the vector ALUs (fp32 accumulate).
 //
-// This is the path for layers the matrix cores do not fit: fp32 tensors, very small
-// channel counts, any shape the fragment layouts do not cover, and NCHW activations (the
-// matrix-core kernels stream channels-last tensors).  It multiplies only
+// This is the path for what the matrix-core kernels do not take: NCHW activations (those
+// kernels stream channels-last tensors) and channels-last rows that are no multiple of 16 bytes
+// (3x3 layers; 4 bytes for 1x1 layers), such as a 3-channel fp32 stem.  It multiplies only
 // the k surviving taps of every kernel (Section II.B: zero weights are skipped).
 //
 // Mapping: a workgroup owns an 8x8 tile of output positions (one position per lane) and a

@@ -85,4 +85,41 @@ template <typename TO, int N> __device__ __forceinline__ void epi_residual(float
     }
 }
 
+// The whole output stage for a run of N channels of which only those below Co exist (layers whose channel count is
+// no multiple of a matrix tile): element by element, nothing past channel Co is read.
+template <typename TO, int N> __device__ __forceinline__ void epi_ragged(float (&v)[N], const Epilogue& ep, int64_t pos, int co, int Co)
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if (co + i >= Co) break;
+        if (ep.scale) v[i] *= ep.scale[co + i];
+        if (ep.bias) v[i] += ep.bias[co + i];
+        v[i] = epi_act(v[i], ep.act);
+        if (ep.residual) v[i] += to_f32(((const TO*)ep.residual)[pos * ep.ldr + co + i]);
+    }
+}
+
+// ... and its store.  `yp` is the position's channel 0.  Whole runs of rows whose pitch keeps them aligned go out as
+// vectors (16-bit types: N % 4 == 0, 8 bytes at a time), anything else element by element.
+template <typename TO, int N> __device__ __forceinline__ void store_ragged(TO* yp, const float (&v)[N], int co, int Co, int ldy)
+{
+    if (co + N <= Co && ldy % 4 == 0) {
+#pragma unroll
+        for (int g = 0; g < N / 4; ++g) {
+            if constexpr (sizeof(TO) == 4) {
+                *(f32x4*)(yp + co + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+            } else {
+                uint2 o;
+                o.x = pack2_from_f32<TO>(v[4 * g], v[4 * g + 1]);
+                o.y = pack2_from_f32<TO>(v[4 * g + 2], v[4 * g + 3]);
+                *(uint2*)(yp + co + 4 * g) = o;
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (co + i < Co) store_from_f32<TO>(yp + co + i, v[i]);
+}
+
 }  // namespace rtoss

@@ -54,10 +54,12 @@ __device__ __forceinline__ int tile_quarter_offset(int mm, int q)
 // Channel tiles per stage in the packed section: padded so that every block of 8 tiles is complete.
 inline int padded_m_tiles(int Co) { return ((Co + 15) / 16 + 7) / 8 * 8; }
 // The section is [fragments][block of zeros]; the zeros feed the copy lanes that fill padding.
+// Stages of 32 input channels; a last stage with fewer channels is filled with zero weights.
+inline int sparse_stages(const rtoss_wdesc& d) { return (d.Ci + 31) / 32; }
 inline size_t fragment_bytes(const rtoss_wdesc& d, int layout = 0)
 {
-    return (size_t)(d.Ci / 32) * padded_m_tiles(d.Co) * layout_tile_bytes(kLayouts[layout]);
+    return (size_t)sparse_stages(d) * padded_m_tiles(d.Co) * layout_tile_bytes(kLayouts[layout]);
 }
-inline size_t zero_block_bytes(const rtoss_wdesc& d) { return align_up((size_t)2 * d.Ci + 16, 256); }
+inline size_t zero_block_bytes(const rtoss_wdesc& d) { return align_up((size_t)64 * sparse_stages(d) + 16, 256); }
 
 }  // namespace rtoss
