@@ -195,7 +195,7 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     using PL = Plan<KS, WM>;
     constexpr int MT = PL::MT, WN = PL::WN, NB = PL::NB, PB = PL::PB, BUF = PL::BUF, COPIES = PL::COPIES, RING = PL::RING;
     constexpr int ROW = 64 * KS;  // bytes of one position
-    extern __shared__ __attribute__((aligned(16))) char smem[];  // RING buffers
+    extern __shared__ __attribute__((aligned(16))) char smem[];  // RING buffers, then scale and bias of SPAN channels
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -256,6 +256,9 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
 
     // ---- consumer waves ----
     const int wm = wave % WM, wn = wave / WM;
+    float* lds_ep = (float*)(smem + RING * BUF);
+    EpiScaleBias<PL::SPAN> scale_bias;
+    scale_bias.load(ep, cb * PL::SPAN, Co, tid);
     // this wave's weight fragments, resident for the whole kernel
     u32x4 a[MT][KS];
     {
@@ -288,13 +291,16 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     asm volatile("" ::: "memory");
+    scale_bias.store(lds_ep, ep, tid);
 
     const int nn = lane & 15, qq = lane >> 4;
     // operand read offset within a buffer for stage 0, block 0 (the swizzle depends on nn only)
     const int x_lane = (wn * 16 + nn) * 64 + ((qq ^ ((nn >> 1) & 3)) * 16);
     const int co_lane = cb * PL::SPAN + wm * (16 * MT) + 4 * MT * qq;  // first of this lane's 4*MT channels
+    const int co_local = wm * (16 * MT) + 4 * MT * qq;
     constexpr int EB = (int)sizeof(TO);
 
+    static_assert(NB == 1, "one block per wave and buffer");
     int slot = 0;
     for (int64_t b = b0; b < b1; ++b) {
         asm volatile("" ::: "memory");
@@ -317,18 +323,16 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
                 for (int m = 0; m < MT; ++m) acc[m][j] = Dense16<T>::mma(a[m][s], bv, acc[m][j]);
             }
 
-        // ---- store: this lane's 4*MT consecutive channels of position nn of each of its blocks ----
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int64_t p = b * PB + 16 * (wn + WN * j) + nn;
-            if (p >= P || co_lane >= Co) continue;  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
+        // ---- store: this lane's 4*MT consecutive channels of its position ----
+        const int64_t p = b * PB + 16 * wn + nn;
+        if (p < P && co_lane < Co) {  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
             TO* yp = y + p * ep.ldy + co_lane;
             float v[4 * MT];
 #pragma unroll
             for (int m = 0; m < MT; ++m)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][j][e];
-            epi_scale_bias_act<4 * MT>(v, ep, co_lane);
+                for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][0][e];
+            epi_scale_bias_act<TO, 4 * MT>(v, ep, lds_ep + co_local, lds_ep + PL::SPAN + co_local);
             epi_residual<TO, 4 * MT>(v, ep, p, co_lane);
             if constexpr (EB == 4) {
 #pragma unroll
@@ -361,7 +365,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const int64_t P = (int64_t)c.N * c.H * c.W;
     const int64_t nbuf = (P + PL::PB - 1) / PL::PB;
     const int co_blocks = co_blocks_of(KS, d.Co);
-    const size_t smem = (size_t)PL::RING * PL::BUF;
+    const size_t smem = (size_t)PL::RING * PL::BUF + EpiScaleBias<PL::SPAN>::kBytes;
     auto kern = conv1x1_stream_kernel<T, TO, KS, WM>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv1x1 shared memory attribute")) return st;

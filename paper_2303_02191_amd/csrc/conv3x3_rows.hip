@@ -410,7 +410,7 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
                                     const int co4 = 16 * (cur.mt0 + h * TMH) + tile_quarter_offset(mm, qq_e);
                                     if (inside_f && co4 < Co) {
                                         float vv[4] = {vals[mm].x, vals[mm].y, vals[mm].z, vals[mm].w};
-                                        epi_scale_bias_act<4>(vv, ep, co4);
+                                        epi_scale_bias_act<TO, 4>(vv, ep, co4);
                                         epi_residual<TO, 4>(vv, ep, pos_f, co4);
                                         vals[mm] = f32x4{vv[0], vv[1], vv[2], vv[3]};
                                     }

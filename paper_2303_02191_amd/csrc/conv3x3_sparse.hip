@@ -277,6 +277,9 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     };
     // (the weight fragments of stage 0 need only the channel block: they are under way while the lanes work out
     // their activation sources)
+    float* lds_ep = (float*)(smem + (DB ? 2 : 1) * BUF);  // scale and bias of the workgroup's channels
+    EpiScaleBias<16 * TM> scale_bias;
+    scale_bias.load(ep, 16 * mt0, Co, tid);
     issue_weight_copies(0, smem);
 
     // Copy sources of stage 0.  Every lane copies 16 bytes in every copy instruction; a lane whose LDS
@@ -325,6 +328,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
         constexpr bool FIRST = decltype(first_tag)::value;
         if constexpr (DB) {
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies of this stage have landed in LDS
+            if constexpr (FIRST) scale_bias.store(lds_ep, ep, tid);
             __syncthreads();                     // ... and everybody's; and every wave is done reading the other buffer
             const int par = stage & 1;
             if (stage + 1 < stages) issue_copies(stage + 1, smem + (par ^ 1) * BUF, true);
@@ -334,6 +338,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
             __syncthreads();  // every wave is done reading the previous stage
             issue_copies(stage, smem, !FIRST);  // (stage 0's weight fragments are already under way)
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies have landed in LDS
+            if constexpr (FIRST) scale_bias.store(lds_ep, ep, tid);
             __syncthreads();                     // ... and everybody's
         }
 
@@ -455,45 +460,63 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     // ---- epilogue: a D lane holds column nn (position) and rows 4*qq .. 4*qq+3 of every channel tile,
     // which tile_row_channel makes 16 consecutive output channels per group of 4 tiles ----
     static_assert(TM % 4 == 0, "whole groups of 4 channel tiles");
+    auto finish = [&](auto shortcut_tag) {
+        constexpr bool SHORTCUT = decltype(shortcut_tag)::value;
+        EpiResidual<TO, 16> shortcut[TN][TM / 4];
+        if constexpr (SHORTCUT) {  // its loads go out together, before any of them is needed
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int blk = wave * TN + j;
-        const int oh = oh0 + 4 * (blk / CT) + pr, ow = ow0 + 4 * (blk % CT) + pc;
-        if (oh >= Ho || ow >= Wo) continue;
-        const int64_t pos = ((int64_t)n_img * Ho + oh) * Wo + ow;
-        TO* yp = y + pos * ep.ldy;
+            for (int j = 0; j < TN; ++j) {
+                const int blk = wave * TN + j;
+                const int oh = oh0 + 4 * (blk / CT) + pr, ow = ow0 + 4 * (blk % CT) + pc;
 #pragma unroll
-        for (int mg = 0; mg < TM; mg += 4) {
-            const int co = 16 * mt0 + tile_quarter_offset(mg, qq);
-            if (co >= Co) continue;  // (not RAG: Co is a multiple of 16, a run of 16 channels is all in or all out)
-            float vv[16];
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) vv[4 * m + e] = acc[mg + m][j][e];
-            if constexpr (RAG) {
-                epi_ragged<TO, 16>(vv, ep, pos, co, Co);
-                store_ragged<TO, 16>(yp, vv, co, Co, ep.ldy);
-                continue;
-            }
-            epi_scale_bias_act<16>(vv, ep, co);
-            epi_residual<TO, 16>(vv, ep, pos, co);
-            if constexpr (sizeof(TO) == 4) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) *(f32x4*)(yp + co + 4 * g) = f32x4{vv[4 * g], vv[4 * g + 1], vv[4 * g + 2], vv[4 * g + 3]};
-            } else {
-#pragma unroll
-                for (int g = 0; g < 2; ++g) {
-                    u32x4 o;
-                    o.x = pack2_from_f32<TO>(vv[8 * g + 0], vv[8 * g + 1]);
-                    o.y = pack2_from_f32<TO>(vv[8 * g + 2], vv[8 * g + 3]);
-                    o.z = pack2_from_f32<TO>(vv[8 * g + 4], vv[8 * g + 5]);
-                    o.w = pack2_from_f32<TO>(vv[8 * g + 6], vv[8 * g + 7]);
-                    *(u32x4*)(yp + co + 8 * g) = o;
+                for (int mg = 0; mg < TM; mg += 4) {
+                    const int co = 16 * mt0 + tile_quarter_offset(mg, qq);
+                    if (oh < Ho && ow < Wo && co < Co) shortcut[j][mg / 4].load(ep, ((int64_t)n_img * Ho + oh) * Wo + ow, co);
                 }
             }
         }
-    }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int blk = wave * TN + j;
+            const int oh = oh0 + 4 * (blk / CT) + pr, ow = ow0 + 4 * (blk % CT) + pc;
+            if (oh >= Ho || ow >= Wo) continue;
+            const int64_t pos = ((int64_t)n_img * Ho + oh) * Wo + ow;
+            TO* yp = y + pos * ep.ldy;
+#pragma unroll
+            for (int mg = 0; mg < TM; mg += 4) {
+                const int co = 16 * mt0 + tile_quarter_offset(mg, qq);
+                if (co >= Co) continue;  // (not RAG: Co is a multiple of 16, a run of 16 channels is all in or all out)
+                float vv[16];
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) vv[4 * m + e] = acc[mg + m][j][e];
+                if constexpr (RAG) {
+                    epi_ragged<TO, 16>(vv, ep, pos, co, Co);
+                    store_ragged<TO, 16>(yp, vv, co, Co, ep.ldy);
+                    continue;
+                }
+                epi_scale_bias_act<TO, 16>(vv, ep, lds_ep + co - 16 * mt0, lds_ep + 16 * TM + co - 16 * mt0);
+                if constexpr (SHORTCUT) shortcut[j][mg / 4].add(vv);
+                if constexpr (sizeof(TO) == 4) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) *(f32x4*)(yp + co + 4 * g) = f32x4{vv[4 * g], vv[4 * g + 1], vv[4 * g + 2], vv[4 * g + 3]};
+                } else {
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+                        u32x4 o;
+                        o.x = pack2_from_f32<TO>(vv[8 * g + 0], vv[8 * g + 1]);
+                        o.y = pack2_from_f32<TO>(vv[8 * g + 2], vv[8 * g + 3]);
+                        o.z = pack2_from_f32<TO>(vv[8 * g + 4], vv[8 * g + 5]);
+                        o.w = pack2_from_f32<TO>(vv[8 * g + 6], vv[8 * g + 7]);
+                        *(u32x4*)(yp + co + 8 * g) = o;
+                    }
+                }
+            }
+        }
+    };
+    if (!RAG && ep.residual) finish(std::true_type{});
+    else finish(std::false_type{});
 }
 
 template <typename T, typename TO, int S, int TM, int TN, int RT, int CT, bool AHEAD = true, int LAY = 0, bool DB = false, bool RAG = false>
@@ -506,7 +529,7 @@ rtoss_status launch_variant_sb(const rtoss_wdesc& d, const ConvParams& c, const 
     const int m_tiles_total = padded_m_tiles(d.Co);  // pitch of the packed section
     const int co_blocks = ((d.Co + 15) / 16 + TM - 1) / TM;
     constexpr int x_copies_per_wave = ((G::x_bytes / 16 + 63) / 64 + 3) / 4;
-    const size_t smem = (DB ? 2 : 1) * ((size_t)TM * layout_tile_bytes(kLayouts[LAY]) + (size_t)x_copies_per_wave * 4096);
+    const size_t smem = (DB ? 2 : 1) * ((size_t)TM * layout_tile_bytes(kLayouts[LAY]) + (size_t)x_copies_per_wave * 4096) + EpiScaleBias<16 * TM>::kBytes;
     auto kern = conv3x3_sparse_sb_kernel<T, TO, S, TM, TN, RT, CT, AHEAD, LAY, DB, RAG>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv3x3 shared memory attribute")) return st;

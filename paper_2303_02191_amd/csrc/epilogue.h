@@ -25,22 +25,33 @@ struct ConvParams : rtoss_cdesc {
     Epilogue ep;
 };
 
-__device__ __forceinline__ float epi_act(float v, int act)
+// v * sigmoid(v), for a result stored as TO.  The IEEE division is ten vector instructions, four cycles each, and was
+// most of the output stage (a 3 -> 32 stem at 640x640, batch 16: 38 us without SiLU, 63 us with it).  Where the result
+// is rounded to 16 bits anyway, the hardware reciprocal (1 ulp of fp32) takes its place; fp32 results keep the division.
+template <typename TO> __device__ __forceinline__ float epi_silu(float v)
+{
+    const float d = 1.f + __expf(-v);
+    if constexpr (sizeof(TO) == 2) return v * __builtin_amdgcn_rcpf(d);  // (d = inf: v * 0)
+    else return v / d;
+}
+template <typename TO> __device__ __forceinline__ float epi_act(float v, int act)
 {
     if (act == 1) return __builtin_fmaxf(v, 0.f);
-    if (act == 2) return v / (1.f + __expf(-v));  // v * sigmoid(v)
+    if (act == 2) return epi_silu<TO>(v);
     return v;
 }
 
 // v[0..N) are N consecutive output channels, starting at channel co, of one position (N and co are
-// multiples of 4).  Scale, bias and activation; the branches are uniform over the launch.
-template <int N> __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue& ep, int co)
+// multiples of 4).  Scale, bias and activation; the branches are uniform over the launch.  `scale` and `bias` point at
+// the run's first channel (in device memory, or at a copy in LDS) and are read only where ep has them.
+template <typename TO, int N>
+__device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
 {
     static_assert(N % 4 == 0, "runs of 4 channels");
     if (ep.scale) {
 #pragma unroll
         for (int g = 0; g < N / 4; ++g) {
-            const f32x4 s = *(const f32x4*)(ep.scale + co + 4 * g);
+            const f32x4 s = *(const f32x4*)(scale + 4 * g);
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[4 * g + i] *= s[i];
         }
@@ -48,7 +59,7 @@ template <int N> __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N
     if (ep.bias) {
 #pragma unroll
         for (int g = 0; g < N / 4; ++g) {
-            const f32x4 b = *(const f32x4*)(ep.bias + co + 4 * g);
+            const f32x4 b = *(const f32x4*)(bias + 4 * g);
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[4 * g + i] += b[i];
         }
@@ -59,8 +70,12 @@ template <int N> __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N
         for (int i = 0; i < N; ++i) v[i] = __builtin_fmaxf(v[i], 0.f);
     } else if (ep.act == 2) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = epi_act(v[i], 2);
+        for (int i = 0; i < N; ++i) v[i] = epi_silu<TO>(v[i]);
     }
+}
+template <typename TO, int N> __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue& ep, int co)
+{
+    epi_scale_bias_act<TO, N>(v, ep, ep.scale + co, ep.bias + co);
 }
 
 // Adds the residual's N consecutive channels, starting at channel co, of position number `pos` (n, oh, ow
@@ -85,6 +100,58 @@ template <typename TO, int N> __device__ __forceinline__ void epi_residual(float
     }
 }
 
+// The same in two steps for kernels that have something to do while the shortcut is on its way: N channels of the
+// residual as they lie in memory, and their addition.
+template <typename TO, int N> struct EpiResidual {
+    static constexpr int kWords = N * (int)sizeof(TO) / 4;
+    uint32_t w[kWords];
+    __device__ __forceinline__ void load(const Epilogue& ep, int64_t pos, int co)
+    {
+        const char* r = (const char*)((const TO*)ep.residual + pos * ep.ldr + co);
+#pragma unroll
+        for (int g = 0; g < kWords / 4; ++g) *(u32x4*)(w + 4 * g) = *(const u32x4*)(r + 16 * g);
+        if constexpr (kWords % 4 == 2) *(uint2*)(w + kWords - 2) = *(const uint2*)(r + 4 * (kWords - 2));
+    }
+    __device__ __forceinline__ void add(float (&v)[N]) const
+    {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if constexpr (sizeof(TO) == 4) {
+                v[i] += __builtin_bit_cast(float, w[i]);
+            } else {
+                TO t;
+                t.bits = (uint16_t)(w[i / 2] >> (16 * (i & 1)));
+                v[i] += to_f32(t);
+            }
+        }
+    }
+};
+
+// Scale and bias of the N <= 256 channels of a workgroup of 256 lanes, copied to LDS ([0, N) scale, [N, 2N) bias;
+// nothing where ep has none), so that the output stage reads LDS instead of memory no one has touched yet behind the
+// last matrix instruction.  In two steps: load() goes in front of a kernel's own first loads, store() behind the wait
+// for those, before a barrier.
+template <int N> struct EpiScaleBias {
+    static_assert(N <= 256, "one channel per lane");
+    static constexpr int kBytes = 8 * N;
+    float s = 0.f, b = 0.f;
+    __device__ __forceinline__ void load(const Epilogue& ep, int co0, int Co, int tid)
+    {
+        if (!(ep.scale || ep.bias)) return;  // uniform, here and below: a plain convolution pays one branch
+        const bool mine = tid < N && co0 + tid < Co;
+        if (ep.scale && mine) s = ep.scale[co0 + tid];
+        if (ep.bias && mine) b = ep.bias[co0 + tid];
+    }
+    __device__ __forceinline__ void store(float* lds, const Epilogue& ep, int tid) const
+    {
+        if (!(ep.scale || ep.bias)) return;
+        if (tid < N) {
+            lds[tid] = s;
+            lds[N + tid] = b;
+        }
+    }
+};
+
 // The whole output stage for a run of N channels of which only those below Co exist (layers whose channel count is
 // no multiple of a matrix tile): element by element, nothing past channel Co is read.
 template <typename TO, int N> __device__ __forceinline__ void epi_ragged(float (&v)[N], const Epilogue& ep, int64_t pos, int co, int Co)
@@ -94,7 +161,7 @@ template <typename TO, int N> __device__ __forceinline__ void epi_ragged(float (
         if (co + i >= Co) break;
         if (ep.scale) v[i] *= ep.scale[co + i];
         if (ep.bias) v[i] += ep.bias[co + i];
-        v[i] = epi_act(v[i], ep.act);
+        v[i] = epi_act<TO>(v[i], ep.act);
         if (ep.residual) v[i] += to_f32(((const TO*)ep.residual)[pos * ep.ldr + co + i]);
     }
 }
