@@ -130,6 +130,13 @@ rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, in
 rtoss_status launch_conv3x3_rows(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                  hipStream_t s);
 
+// ... launches too small to fill the chip: input channels split over the waves of a workgroup (conv3x3_ksplit.hip).  Reads
+// the packed sections of the sparse kernels (layout 0 or 1) and of the dense-mode kernel (layout 2).
+// ksplit3x3_plan: variant to launch, 0 = another kernel serves the launch better.
+int ksplit3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout);
+rtoss_status launch_conv3x3_ksplit(const rtoss_wdesc& d, const ConvParams& c, int layout, int plan, const void* section, const void* zeros,
+                                   const void* x, void* y, hipStream_t s);
+
 // 3x3 convolution with live taps gathered onto the dense matrix instruction, for block-shared patterns
 // (conv3x3_gather.hip); its own blob format, chosen by the caller (rtoss_pack_coherent)
 bool gather3x3_shape_ok(const rtoss_wdesc& d);
