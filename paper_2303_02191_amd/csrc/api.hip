@@ -320,17 +320,6 @@ static rtoss_status check_pack(const rtoss_wdesc* desc, const Dict& dict, const 
     return RTOSS_OK;
 }
 
-// one launch per layer: the fragment packers also write the public section in their first blocks
-static rtoss_status pack_one(const PackItem& it, const BlobGeometry& g, const Dict& dict, hipStream_t s)
-{
-    if (g.format == kFormatSparse24) return launch_pack_sparse3x3(it.d, it.w, it.idx, dict, it.section, it.live, it.live_idx, s);
-    if (g.format == kFormatDense3x3) return launch_pack_dense3x3(it.d, it.w, it.idx, dict, it.section, it.live, it.live_idx, s);
-    if (g.format == kFormatDenseStream) return launch_pack_stream1x1(it.d, it.w, it.idx, dict, it.section, it.live, it.live_idx, s);
-    if (g.format == kFormatDense) return launch_pack_dense1x1(it.d, it.w, it.idx, dict, it.section, it.live, it.live_idx, s);
-    if (g.format == kFormatStem) return launch_pack_stem3x3(it.d, it.w, it.idx, dict, it.section, it.live, it.live_idx, s);
-    return launch_pack_live(it.d, it.w, it.idx, dict, it.live, it.live_idx, g.G, s);
-}
-
 rtoss_status rtoss_pack(const rtoss_wdesc* desc, const void* w_dev, const uint8_t* idx_dev, const uint16_t* masks_host,
                         int P, void* packed_dev, size_t packed_bytes, void* workspace_dev, size_t workspace_bytes,
                         void* hip_stream)
@@ -343,7 +332,7 @@ rtoss_status rtoss_pack(const rtoss_wdesc* desc, const void* w_dev, const uint8_
     BlobGeometry g;
     PackItem it;
     if (rtoss_status st = check_pack(desc, dict, w_dev, idx_dev, packed_dev, packed_bytes, &g, &it)) return st;
-    return pack_one(it, g, dict, (hipStream_t)hip_stream);
+    return launch_pack(&it, &g, 1, dict, (hipStream_t)hip_stream);
 }
 
 rtoss_status rtoss_pack_batch(const rtoss_pack_item* items_host, int n_items, const uint16_t* masks_host, int P,
@@ -363,23 +352,7 @@ rtoss_status rtoss_pack_batch(const rtoss_pack_item* items_host, int n_items, co
             return fail(st, "item %d: %s", i, msg.c_str());
         }
     }
-    hipStream_t s = (hipStream_t)hip_stream;
-    // layers of the two common formats go out in batched launches, per dtype; the rest one by one
-    for (int fmt : {(int)kFormatSparse24, (int)kFormatDenseStream})
-        for (int dt : {(int)RTOSS_F32, (int)RTOSS_F16, (int)RTOSS_BF16}) {
-            std::vector<PackItem> group;
-            for (int i = 0; i < n_items; ++i)
-                if ((int)geo[i].format == fmt && (int)items[i].d.dt == dt) group.push_back(items[i]);
-            if (group.empty()) continue;
-            const rtoss_status st = fmt == kFormatSparse24 ? launch_pack_sparse3x3_batch(group.data(), (int)group.size(), dict, s)
-                                                           : launch_pack_stream1x1_batch(group.data(), (int)group.size(), dict, s);
-            if (st) return st;
-        }
-    for (int i = 0; i < n_items; ++i) {
-        if (geo[i].format == kFormatSparse24 || geo[i].format == kFormatDenseStream) continue;
-        if (rtoss_status st = pack_one(items[i], geo[i], dict, s)) return st;
-    }
-    return RTOSS_OK;
+    return launch_pack(items.data(), geo.data(), n_items, dict, (hipStream_t)hip_stream);
 }
 
 static rtoss_status conv_impl(const rtoss_wdesc* desc, const rtoss_cdesc* c, const rtoss_epilogue* e,

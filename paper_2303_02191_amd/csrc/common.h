@@ -85,44 +85,25 @@ rtoss_status launch_select_batch(const rtoss_select_item* items, int n, rtoss_dt
 // counts of each pattern index (select.hip)
 rtoss_status launch_histogram(const uint8_t* idx, int64_t G, int P, uint32_t* hist, hipStream_t s);
 
-rtoss_status launch_pack_live(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict,
-                              void* live_values, uint8_t* live_idx, int64_t G, hipStream_t s);
-
 rtoss_status launch_conv_direct(const rtoss_wdesc& d, const ConvParams& c, const Dict& dict, const void* live_values,
                                 const uint8_t* live_idx, const void* x, void* y, hipStream_t s);
 
-// Several layers packed by one launch (layers of one format and dtype; the table travels in the launch arguments).
+// Prune and pack layers of one dictionary, as few launches as possible (pack.hip).
 struct PackItem {
     rtoss_wdesc d;
     const void* w;
     const uint8_t* idx;
     void* section;      // private section of the blob
-    void* live;         // public section: values
+    void* live;         // public section: values (the blob's start)
     uint8_t* live_idx;  // public section: indices
 };
-constexpr int kPackBatchMax = 24;
-// block -> (entry, block within the entry) for the batched kernels: first_block[t] <= block < first_block[t+1]
-template <typename Batch> __device__ __forceinline__ int batch_entry(const Batch& b, int block)
-{
-    // binary search: the table sits in the kernel arguments, and every probe is a dependent scalar load
-    int lo = 0, hi = b.n - 1;  // the entry is in [lo, hi]
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (block >= b.first_block[mid]) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-rtoss_status launch_pack_sparse3x3_batch(const PackItem* items, int n, const Dict& dict, hipStream_t s);
-rtoss_status launch_pack_stream1x1_batch(const PackItem* items, int n, const Dict& dict, hipStream_t s);
+rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, const Dict& dict, hipStream_t s);
 
 // 3x3 convolution on the sparse matrix instruction (conv3x3_sparse.hip)
 // which tap layout (sparse_frag.h) fits every pattern of the dictionary, cheapest first; -1: none
 int sparse3x3_layout(const Dict& dict);
 bool sparse3x3_shape_ok(const rtoss_wdesc& d);
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout);
-rtoss_status launch_pack_sparse3x3(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict,
-                                   void* section, void* live_values, uint8_t* live_idx, hipStream_t s);
 rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, int layout, const void* section, const void* x,
                                    void* y, hipStream_t s);
 
@@ -150,32 +131,24 @@ rtoss_status launch_conv3x3_gather(const rtoss_wdesc& d, const ConvParams& c, co
 // 3x3 convolution in dense mode on the matrix cores (conv3x3_dense.hip)
 bool dense3x3_shape_ok(const rtoss_wdesc& d);
 size_t dense3x3_section_bytes(const rtoss_wdesc& d);
-rtoss_status launch_pack_dense3x3(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict, void* section,
-                                  void* live_values, uint8_t* live_idx, hipStream_t s);
 rtoss_status launch_conv3x3_dense(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                   hipStream_t s);
 
 // 1x1 convolution on the dense matrix instruction (conv1x1_mma.hip)
 bool dense1x1_shape_ok(const rtoss_wdesc& d);
 size_t dense1x1_section_bytes(const rtoss_wdesc& d);
-rtoss_status launch_pack_dense1x1(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict, void* section,
-                                  void* live_values, uint8_t* live_idx, hipStream_t s);
 rtoss_status launch_conv1x1_mma(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                 hipStream_t s);
 
 // 1x1 convolution, streaming kernel with register-resident weights (conv1x1_stream.hip)
 bool stream1x1_shape_ok(const rtoss_wdesc& d);
 size_t stream1x1_section_bytes(const rtoss_wdesc& d);
-rtoss_status launch_pack_stream1x1(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict, void* section,
-                                   void* live_values, uint8_t* live_idx, hipStream_t s);
 rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                    hipStream_t s);
 
 // 3x3 convolution with <= 3 input channels (conv3x3_stem.hip)
 bool stem3x3_shape_ok(const rtoss_wdesc& d);
 size_t stem3x3_section_bytes(const rtoss_wdesc& d);
-rtoss_status launch_pack_stem3x3(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict, void* section,
-                                 void* live_values, uint8_t* live_idx, hipStream_t s);
 rtoss_status launch_conv3x3_stem(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                  hipStream_t s);
 

@@ -1,5 +1,5 @@
-// 1x1 pattern-pruned convolution on the CDNA4 matrix cores (fp16 / bf16 / fp32, fp32 accumulate),
-// and the packer that writes its weight fragments: the general kernel, for any channel counts whose
+// 1x1 pattern-pruned convolution on the CDNA4 matrix cores (fp16 / bf16 / fp32, fp32 accumulate):
+// the general kernel, for any channel counts whose
 // input rows are a multiple of 4 bytes.  (64-byte multiples of 2^n stages with whole channel tiles
 // take the streaming kernel with register-resident weights instead.)
 //
@@ -33,7 +33,7 @@
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
-#include "pack_live.h"
+#include "pack_plan.h"
 
 namespace rtoss {
 
@@ -43,49 +43,7 @@ constexpr int kFrag = 1024;      // one A fragment: 64 lanes x 16 bytes = 16 out
 constexpr int kTilePos = 128;    // positions per workgroup
 constexpr int kRing = 5;
 
-inline int padded_tiles(int Co) { return ((Co + 15) / 16 + 7) / 8 * 8; }
-inline int stages_of(const rtoss_wdesc& d) { return (d.Ci * elem_bytes(d.dt) + 63) / 64; }
-inline size_t frag_bytes(const rtoss_wdesc& d) { return (size_t)stages_of(d) * padded_tiles(d.Co) * kFrag; }
-inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)64 * stages_of(d) + 16, 256); }
-
-template <typename T>
-__global__ __launch_bounds__(256) void pack_dense1x1_kernel(const T* __restrict__ w, const uint8_t* __restrict__ idx,
-                                                            Dict dict, char* __restrict__ out, int Co, int Ci, int m_tiles,
-                                                            int64_t G, int64_t total_items, int zero_items, LiveJob job)
-{
-    __shared__ uint16_t masks[256];
-    masks[threadIdx.x] = dict.mask[threadIdx.x];
-    __syncthreads();
-    if ((int)blockIdx.x < job.blocks) {  // the first blocks write the blob's public section
-        pack_live_block<T>(w, idx, masks, dict.k, job, blockIdx.x);
-        return;
-    }
-    const int64_t item = (int64_t)(blockIdx.x - job.blocks) * 256 + threadIdx.x;  // (stage, m_tile, lane)
-    if (item >= total_items) {
-        if (item < total_items + zero_items) *(u32x4*)(out + total_items * 16 + (item - total_items) * 16) = u32x4{0, 0, 0, 0};
-        return;
-    }
-    const int lane = (int)(item % 64);
-    const int64_t tile = item / 64;
-    const int mt = (int)(tile % m_tiles), cb = (int)(tile / m_tiles);
-    const int co = 16 * mt + (lane % 16), q = lane / 16;
-    constexpr int PER = 16 / (int)sizeof(T);  // channels in a lane's 16 bytes
-    T v[PER];
-    for (int j = 0; j < PER; ++j) {
-        const int ci = 4 * PER * cb + PER * q + j;
-        __builtin_memset(&v[j], 0, sizeof(T));
-        if (co < Co && ci < Ci) {
-            // element f of the flattened matrix sits in group f/9 at tap f%9 (groups may straddle rows)
-            const int64_t f = (int64_t)co * Ci + ci;
-            const int64_t g = f / 9;
-            const int t = (int)(f - 9 * g);
-            if (g < G && ((masks[idx[g]] >> t) & 1u)) v[j] = w[f];
-        }
-    }
-    u32x4 pk;
-    __builtin_memcpy(&pk, v, 16);
-    *(u32x4*)(out + item * 16) = pk;
-}
+inline size_t frag_bytes(const rtoss_wdesc& d) { return (size_t)stage_count(d) * ring_padded_tiles(d.Co) * kFrag; }
 
 template <typename T, typename TO, int TM, bool RAG, int COPY>
 __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ x, TO* __restrict__ y,
@@ -290,7 +248,7 @@ rtoss_status launch_tm(const rtoss_wdesc& d, const ConvParams& c, const char* wf
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv1x1 shared memory attribute")) return st;
     dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
-    kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Ci, d.Co, padded_tiles(d.Co),
+    kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Ci, d.Co, ring_padded_tiles(d.Co),
                                    co_blocks, (int)total, work_per_xcd, c.ep);
     return check_hip(hipGetLastError(), "conv1x1 launch");
 }
@@ -321,25 +279,7 @@ bool dense1x1_shape_ok(const rtoss_wdesc& d)
     return d.ksize == 1 && d.Ci * elem_bytes(d.dt) % 4 == 0;
 }
 
-size_t dense1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_bytes(d); }
-
-rtoss_status launch_pack_dense1x1(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict, void* section,
-                                  void* live_values, uint8_t* live_idx, hipStream_t s)
-{
-    const int m_tiles = padded_tiles(d.Co);
-    const int64_t items = (int64_t)stages_of(d) * m_tiles * 64;
-    const int zero_items = (int)(zero_bytes(d) / 16);
-    const int64_t G = (int64_t)d.Co * d.Ci / 9;
-    const LiveJob job = make_live_job(live_values, live_idx, G);
-    dim3 grid((unsigned)(job.blocks + (items + zero_items + 255) / 256)), block(256);
-    if (d.dt == RTOSS_F32)
-        pack_dense1x1_kernel<float><<<grid, block, 0, s>>>((const float*)w, idx, dict, (char*)section, d.Co, d.Ci, m_tiles, G, items, zero_items, job);
-    else if (d.dt == RTOSS_F16)
-        pack_dense1x1_kernel<f16_t><<<grid, block, 0, s>>>((const f16_t*)w, idx, dict, (char*)section, d.Co, d.Ci, m_tiles, G, items, zero_items, job);
-    else
-        pack_dense1x1_kernel<bf16_t><<<grid, block, 0, s>>>((const bf16_t*)w, idx, dict, (char*)section, d.Co, d.Ci, m_tiles, G, items, zero_items, job);
-    return check_hip(hipGetLastError(), "pack dense1x1 launch");
-}
+size_t dense1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_section_bytes(stage_count(d)); }
 
 rtoss_status launch_conv1x1_mma(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                 hipStream_t s)

@@ -1,5 +1,5 @@
 // 1x1 pattern-pruned convolution as a streaming kernel with register-resident weights
-// (fp16 / bf16 / fp32, fp32 accumulate), and the packer that writes its weight fragments.
+// (fp16 / bf16 / fp32, fp32 accumulate).
 //
 // Section IV.D prunes a 1x1 layer by cutting the flattened [Co][Ci] weight matrix into groups
 // of 9 and keeping k weights per group; the pruned layer is the GEMM
@@ -38,7 +38,7 @@
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
-#include "pack_live.h"
+#include "pack_plan.h"
 
 namespace rtoss {
 
@@ -47,12 +47,10 @@ namespace {
 constexpr int kFrag = 1024;  // one A fragment: 64 lanes x 16 bytes = 16 output channels x 32 input channels
 constexpr int kHeadBuffers = 2;  // buffers of a workgroup's range that the consumer waves copy themselves
 
-constexpr int mt_of(int KS) { return KS <= 8 ? 4 : (KS == 16 ? 2 : 1); }
-
 // Shape plan, a function of KS = Ci / 32 (fp32: Ci / 16; 1, 2, 4 ... 32) and of WM, the number of waves a
 // workgroup spreads over output channels (the other 4 / WM spread over positions).
 template <int KS, int WM> struct Plan {
-    static constexpr int MT = mt_of(KS);  // fragments per wave along output channels
+    static constexpr int MT = stream_mt_of(KS);  // fragments per wave along output channels
     static constexpr int WN = 4 / WM;
     // 16-position blocks per wave and buffer: one.  (Buffers of up to four blocks per wave, 16 KB for most shapes,
     // measured slower on a 57-layer model, 0.906 against 0.892-0.895 ms: small buffers mean small workgroups in LDS,
@@ -85,106 +83,11 @@ template <int MAXL, int COPIES> __device__ __forceinline__ void wait_tail(int64_
     }
 }
 
-inline int stages_of(const rtoss_wdesc& d) { return d.Ci * elem_bytes(d.dt) / 64; }  // 64 bytes of channels per stage
-inline int wm_of(int KS, int Co)
-{
-    const int tiles = (Co + 15) / 16, groups = (tiles + mt_of(KS) - 1) / mt_of(KS);
-    const int by_channels = groups >= 3 ? 4 : groups;  // 1, 2 or 4 waves along output channels
-    // deep layers: fewer waves along positions, so that a buffer (16 positions per such wave x Ci) stays <= 32 KB
-    const int by_depth = KS >= 32 ? 4 : (KS == 16 ? 2 : 1);
-    return std::max(by_channels, by_depth);
-}
-inline int co_blocks_of(int KS, int Co)
-{
-    const int span = 16 * mt_of(KS) * wm_of(KS, Co);
-    return (Co + span - 1) / span;
-}
 inline size_t frag_bytes(const rtoss_wdesc& d)
 {
-    const int KS = stages_of(d);
-    return (size_t)co_blocks_of(KS, d.Co) * wm_of(KS, d.Co) * mt_of(KS) * KS * kFrag;
+    const int KS = stage_count(d);
+    return (size_t)stream_co_blocks_of(KS, d.Co) * stream_wm_of(KS, d.Co) * stream_mt_of(KS) * KS * kFrag;
 }
-inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)elem_bytes(d.dt) * d.Ci + 16, 256); }
-
-// Fragment order: [channel block][wave slice wm][fragment m][stage s][lane].
-struct StreamPackArgs {
-    const void* w;
-    const uint8_t* idx;
-    char* out;
-    int Co, Ci, KS, MT, WM, zero_items;
-    int64_t G, total_items;
-    LiveJob job;
-};
-
-// One block of 256 items of one layer (`block` counts from the layer's first block).
-template <typename T>
-__device__ __forceinline__ void pack_stream1x1_body(const StreamPackArgs& a, const Dict& dict, int block)
-{
-    const T* __restrict__ w = (const T*)a.w;
-    const uint8_t* __restrict__ idx = a.idx;
-    char* __restrict__ out = a.out;
-    const int Co = a.Co, Ci = a.Ci, KS = a.KS, MT = a.MT, WM = a.WM, zero_items = a.zero_items;
-    const int64_t G = a.G, total_items = a.total_items;
-    const LiveJob job = a.job;
-    __shared__ uint16_t masks[256];
-    masks[threadIdx.x] = dict.mask[threadIdx.x];
-    __syncthreads();
-    if (block < job.blocks) {  // the first blocks write the blob's public section
-        pack_live_block<T>(w, idx, masks, dict.k, job, block);
-        return;
-    }
-    const int64_t item = (int64_t)(block - job.blocks) * 256 + threadIdx.x;
-    if (item >= total_items) {
-        if (item < total_items + zero_items) *(u32x4*)(out + total_items * 16 + (item - total_items) * 16) = u32x4{0, 0, 0, 0};
-        return;
-    }
-    const int lane = (int)(item % 64);
-    int64_t f = item / 64;
-    const int s = (int)(f % KS);
-    f /= KS;
-    const int m = (int)(f % MT);
-    f /= MT;
-    const int wm = (int)(f % WM);
-    const int cb = (int)(f / WM);
-    const int r = lane % 16, q = lane / 16;
-    const int co = cb * (16 * MT * WM) + wm * (16 * MT) + (r / 4) * (4 * MT) + 4 * m + (r % 4);
-    constexpr int PER = 16 / (int)sizeof(T);  // channels in a lane's 16 bytes
-    T v[PER];
-    for (int j = 0; j < PER; ++j) {
-        const int ci = 4 * PER * s + PER * q + j;
-        __builtin_memset(&v[j], 0, sizeof(T));
-        if (co < Co) {
-            // element e of the flattened matrix sits in group e/9 at tap e%9 (groups may straddle rows)
-            const int64_t e = (int64_t)co * Ci + ci;
-            const int64_t g = e / 9;
-            const int t = (int)(e - 9 * g);
-            if (g < G && ((masks[idx[g]] >> t) & 1u)) v[j] = w[e];
-        }
-    }
-    u32x4 pk;
-    __builtin_memcpy(&pk, v, 16);
-    *(u32x4*)(out + item * 16) = pk;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void pack_stream1x1_kernel(StreamPackArgs a, Dict dict)
-{
-    pack_stream1x1_body<T>(a, dict, (int)blockIdx.x);
-}
-
-struct StreamPackBatch {
-    StreamPackArgs a[kPackBatchMax];
-    int first_block[kPackBatchMax + 1];
-    int n;
-};
-
-template <typename T>
-__global__ __launch_bounds__(256) void pack_stream1x1_batch_kernel(StreamPackBatch b, Dict dict)
-{
-    const int t = batch_entry(b, (int)blockIdx.x);  // block-uniform
-    pack_stream1x1_body<T>(b.a[t], dict, (int)blockIdx.x - b.first_block[t]);
-}
-
 
 template <typename T, typename TO, int KS, int WM>
 __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y,
@@ -364,7 +267,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     using PL = Plan<KS, WM>;
     const int64_t P = (int64_t)c.N * c.H * c.W;
     const int64_t nbuf = (P + PL::PB - 1) / PL::PB;
-    const int co_blocks = co_blocks_of(KS, d.Co);
+    const int co_blocks = stream_co_blocks_of(KS, d.Co);
     const size_t smem = (size_t)PL::RING * PL::BUF + EpiScaleBias<PL::SPAN>::kBytes;
     auto kern = conv1x1_stream_kernel<T, TO, KS, WM>;
     static LaunchOnce lds_once;  // per instantiation
@@ -397,7 +300,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
 template <typename T, typename TO, int KS>
 rtoss_status launch_ks(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
-    const int wm = wm_of(KS, d.Co);
+    const int wm = stream_wm_of(KS, d.Co);
     if constexpr (KS <= 8)
         if (wm == 1) return launch_plan<T, TO, KS, 1>(d, c, wfrag, x, y, s);
     if constexpr (KS <= 16)
@@ -408,7 +311,7 @@ rtoss_status launch_ks(const rtoss_wdesc& d, const ConvParams& c, const char* wf
 template <typename T, typename TO>
 rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
-    switch (stages_of(d)) {
+    switch (stage_count(d)) {
     case 1: return launch_ks<T, TO, 1>(d, c, wfrag, x, y, s);
     case 2: return launch_ks<T, TO, 2>(d, c, wfrag, x, y, s);
     case 4: return launch_ks<T, TO, 4>(d, c, wfrag, x, y, s);
@@ -425,66 +328,11 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 
 bool stream1x1_shape_ok(const rtoss_wdesc& d)
 {
-    const int KS = stages_of(d);
+    const int KS = stage_count(d);
     return d.ksize == 1 && d.Ci * elem_bytes(d.dt) % 64 == 0 && d.Co % 16 == 0 && KS >= 1 && KS <= 32 && (KS & (KS - 1)) == 0;
 }
 
-size_t stream1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_bytes(d); }
-
-static StreamPackArgs stream_pack_args(const rtoss_wdesc& d, const void* w, const uint8_t* idx, void* section,
-                                       void* live_values, uint8_t* live_idx, int* blocks)
-{
-    StreamPackArgs a;
-    a.w = w;
-    a.idx = idx;
-    a.out = (char*)section;
-    a.Co = d.Co;
-    a.Ci = d.Ci;
-    a.KS = stages_of(d);
-    a.MT = mt_of(a.KS);
-    a.WM = wm_of(a.KS, d.Co);
-    a.G = (int64_t)d.Co * d.Ci / 9;
-    a.total_items = (int64_t)(frag_bytes(d) / 16);
-    a.zero_items = (int)(zero_bytes(d) / 16);
-    a.job = make_live_job(live_values, live_idx, a.G);
-    *blocks = (int)(a.job.blocks + (a.total_items + a.zero_items + 255) / 256);
-    return a;
-}
-
-rtoss_status launch_pack_stream1x1(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict, void* section,
-                                   void* live_values, uint8_t* live_idx, hipStream_t s)
-{
-    int blocks = 0;
-    const StreamPackArgs a = stream_pack_args(d, w, idx, section, live_values, live_idx, &blocks);
-    dim3 grid((unsigned)blocks), block(256);
-    if (d.dt == RTOSS_F32) pack_stream1x1_kernel<float><<<grid, block, 0, s>>>(a, dict);
-    else if (d.dt == RTOSS_F16) pack_stream1x1_kernel<f16_t><<<grid, block, 0, s>>>(a, dict);
-    else pack_stream1x1_kernel<bf16_t><<<grid, block, 0, s>>>(a, dict);
-    return check_hip(hipGetLastError(), "pack stream1x1 launch");
-}
-
-rtoss_status launch_pack_stream1x1_batch(const PackItem* items, int n, const Dict& dict, hipStream_t s)
-{
-    for (int base = 0; base < n; base += kPackBatchMax) {
-        StreamPackBatch b;
-        b.n = std::min(kPackBatchMax, n - base);
-        int total = 0;
-        for (int i = 0; i < b.n; ++i) {
-            const PackItem& it = items[base + i];
-            int blocks = 0;
-            b.a[i] = stream_pack_args(it.d, it.w, it.idx, it.section, it.live, it.live_idx, &blocks);
-            b.first_block[i] = total;
-            total += blocks;
-        }
-        b.first_block[b.n] = total;
-        dim3 grid((unsigned)total), block(256);
-        if (items[base].d.dt == RTOSS_F32) pack_stream1x1_batch_kernel<float><<<grid, block, 0, s>>>(b, dict);
-        else if (items[base].d.dt == RTOSS_F16) pack_stream1x1_batch_kernel<f16_t><<<grid, block, 0, s>>>(b, dict);
-        else pack_stream1x1_batch_kernel<bf16_t><<<grid, block, 0, s>>>(b, dict);
-        if (rtoss_status st = check_hip(hipGetLastError(), "pack stream1x1 batch launch")) return st;
-    }
-    return RTOSS_OK;
-}
+size_t stream1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_section_bytes(stage_count(d)); }
 
 rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                    hipStream_t s)

@@ -39,7 +39,7 @@
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
-#include "pack_live.h"
+#include "pack_plan.h"
 #include "tile3x3.h"
 
 namespace rtoss {
@@ -49,59 +49,11 @@ namespace {
 constexpr int kFrag = 1024;            // 64 lanes x 16 bytes = 16 output channels x 32 input channels of one tap
 constexpr int kTM = 4;                 // channel fragments per block of the blob (64 output channels)
 constexpr int kBlockBytes = kTM * 9 * kFrag;  // weights of one (stage, channel block)
-inline int stage_channels(rtoss_dtype dt) { return dt == RTOSS_F32 ? 16 : 32; }  // 64 bytes per position
 
-inline int stages_of(const rtoss_wdesc& d) { return (d.Ci + stage_channels(d.dt) - 1) / stage_channels(d.dt); }
-inline int channel_blocks(int Co) { return (Co + 16 * kTM - 1) / (16 * kTM); }
 inline size_t frag_bytes(const rtoss_wdesc& d)
 {
-    return (size_t)stages_of(d) * channel_blocks(d.Co) * kBlockBytes;
+    return (size_t)stage_count(d) * dense_channel_blocks(d.Co) * kBlockBytes;
 }
-inline size_t zero_bytes(const rtoss_wdesc& d) { return align_up((size_t)64 * stages_of(d) + 16, 256); }
-
-// Fragment order: [stage][channel block][fragment m][tap t][lane].
-template <typename T>
-__global__ __launch_bounds__(256) void pack_dense3x3_kernel(const T* __restrict__ w, const uint8_t* __restrict__ idx,
-                                                            Dict dict, char* __restrict__ out, int Co, int Ci, int cblocks,
-                                                            int64_t total_items, int zero_items, LiveJob job)
-{
-    __shared__ uint16_t masks[256];
-    masks[threadIdx.x] = dict.mask[threadIdx.x];
-    __syncthreads();
-    if ((int)blockIdx.x < job.blocks) {  // the first blocks write the blob's public section
-        pack_live_block<T>(w, idx, masks, dict.k, job, blockIdx.x);
-        return;
-    }
-    const int64_t item = (int64_t)(blockIdx.x - job.blocks) * 256 + threadIdx.x;
-    if (item >= total_items) {
-        if (item < total_items + zero_items) *(u32x4*)(out + total_items * 16 + (item - total_items) * 16) = u32x4{0, 0, 0, 0};
-        return;
-    }
-    const int lane = (int)(item % 64);
-    int64_t f = item / 64;
-    const int t = (int)(f % 9);
-    f /= 9;
-    const int m = (int)(f % kTM);
-    f /= kTM;
-    const int cb = (int)(f % cblocks);
-    const int stage = (int)(f / cblocks);
-    const int r = lane % 16, q = lane / 16;
-    const int co = cb * (16 * kTM) + (r / 4) * 16 + 4 * m + (r % 4);
-    constexpr int PER_LANE = 16 / (int)sizeof(T);  // elements in a lane's 16 bytes: 8 (16-bit) or 4 (fp32)
-    T v[PER_LANE];
-    for (int j = 0; j < PER_LANE; ++j) {
-        const int ci = (4 * PER_LANE) * stage + PER_LANE * q + j;
-        __builtin_memset(&v[j], 0, sizeof(T));
-        if (co < Co && ci < Ci) {
-            const int64_t g = (int64_t)co * Ci + ci;
-            if ((masks[idx[g]] >> t) & 1u) v[j] = w[g * 9 + t];
-        }
-    }
-    u32x4 pk;
-    __builtin_memcpy(&pk, v, 16);
-    *(u32x4*)(out + item * 16) = pk;
-}
-
 
 // TM channel fragments (of the blob's blocks of 4) and RT x CT position blocks per workgroup.
 // RAG: channel counts between the stages (in; rows stay 16-byte multiples) and tiles (out): the last stage's copy
@@ -249,7 +201,7 @@ rtoss_status launch_shape(const rtoss_wdesc& d, const ConvParams& c, const char*
     using G = Geom<S, RT, CT>;
     const int Ho = (c.H + 2 - 3) / S + 1, Wo = (c.W + 2 - 3) / S + 1;
     const int tiles_r = (Ho + G::TH - 1) / G::TH, tiles_c = (Wo + G::TW - 1) / G::TW;
-    const int cblocks = channel_blocks(d.Co);
+    const int cblocks = dense_channel_blocks(d.Co);
     constexpr int x_copies_per_wave = ((G::x_bytes / 16 + 63) / 64 + 3) / 4;
     constexpr int a_copies_per_wave = (TM * 9 + 3) / 4;
     const size_t smem = (size_t)(a_copies_per_wave + x_copies_per_wave) * 4096;
@@ -270,7 +222,7 @@ rtoss_status launch_stride(const rtoss_wdesc& d, const ConvParams& c, const char
     // 64 channels x 16x16 positions per workgroup; launches that would not fill the chip that way take
     // 16 channels x 4x16 positions (16 times as many workgroups).
     const int Ho = (c.H + 2 - 3) / S + 1, Wo = (c.W + 2 - 3) / S + 1;
-    const int64_t big = (int64_t)((Ho + 15) / 16) * ((Wo + 15) / 16) * channel_blocks(d.Co) * c.N;
+    const int64_t big = (int64_t)((Ho + 15) / 16) * ((Wo + 15) / 16) * dense_channel_blocks(d.Co) * c.N;
     if (d.Ci % stage_channels(d.dt) || d.Co % 16) return launch_shape<T, TO, S, 1, 1, 4, true>(d, c, wfrag, x, y, s);
     if (big < 256) return launch_shape<T, TO, S, 1, 1, 4>(d, c, wfrag, x, y, s);
     return launch_shape<T, TO, S, 4, 4, 4>(d, c, wfrag, x, y, s);
@@ -292,24 +244,7 @@ bool dense3x3_shape_ok(const rtoss_wdesc& d)
     return d.ksize == 3 && d.Ci * elem_bytes(d.dt) % 16 == 0;  // rows of whole 16-byte copies
 }
 
-size_t dense3x3_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_bytes(d); }
-
-rtoss_status launch_pack_dense3x3(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict, void* section,
-                                  void* live_values, uint8_t* live_idx, hipStream_t s)
-{
-    const LiveJob job = make_live_job(live_values, live_idx, (int64_t)d.Co * d.Ci);
-    const int cblocks = channel_blocks(d.Co);
-    const int64_t items = (int64_t)(frag_bytes(d) / 16);
-    const int zero_items = (int)(zero_bytes(d) / 16);
-    dim3 grid((unsigned)(job.blocks + (items + zero_items + 255) / 256)), block(256);
-    if (d.dt == RTOSS_F16)
-        pack_dense3x3_kernel<f16_t><<<grid, block, 0, s>>>((const f16_t*)w, idx, dict, (char*)section, d.Co, d.Ci, cblocks, items, zero_items, job);
-    else if (d.dt == RTOSS_BF16)
-        pack_dense3x3_kernel<bf16_t><<<grid, block, 0, s>>>((const bf16_t*)w, idx, dict, (char*)section, d.Co, d.Ci, cblocks, items, zero_items, job);
-    else
-        pack_dense3x3_kernel<float><<<grid, block, 0, s>>>((const float*)w, idx, dict, (char*)section, d.Co, d.Ci, cblocks, items, zero_items, job);
-    return check_hip(hipGetLastError(), "pack dense3x3 launch");
-}
+size_t dense3x3_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_section_bytes(stage_count(d)); }
 
 rtoss_status launch_conv3x3_dense(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                   hipStream_t s)

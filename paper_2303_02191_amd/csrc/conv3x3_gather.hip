@@ -64,11 +64,12 @@ __global__ __launch_bounds__(256) void pack_gather3x3_kernel(const T* __restrict
     __shared__ uint16_t masks[256];
     __shared__ unsigned uni[4];
     __shared__ GatherHeader hdr;
+    __shared__ __attribute__((aligned(16))) char live_lds[live_block_lds_bytes<T>()];
     masks[threadIdx.x] = dict.mask[threadIdx.x];
     if (threadIdx.x < 4) uni[threadIdx.x] = 0;
     __syncthreads();
     if ((int)blockIdx.x < job.blocks) {  // the first blocks write the blob's public section
-        pack_live_block<T>(w, idx, masks, dict.k, job, blockIdx.x);
+        pack_live_block<T>(w, idx, masks, dict.k, job, blockIdx.x, live_lds);
         return;
     }
     const int b = (int)blockIdx.x - job.blocks;

@@ -1,5 +1,4 @@
-// 3x3 pattern-sparse convolution on the CDNA4 matrix cores (fp16 / bf16, fp32 accumulate),
-// and the packer that writes the weight fragments it streams.
+// 3x3 pattern-sparse convolution on the CDNA4 matrix cores (fp16 / bf16, fp32 accumulate).
 //
 // Why 2-of-4 structured sparsity fits pattern pruning (Section IV.B / IV.C): every kernel
 // keeps k taps chosen per kernel, so at matrix-tile granularity the zeros are unstructured
@@ -31,7 +30,7 @@
 // (8 channels of one tap) and the 4x4 (tap, channel) blocks are transposed in registers
 // with byte permutes so that one lane holds, for 4 channels, the 4 taps of a group.
 //
-// This file holds the packer and the single-buffered kernel (stride 2, and stride-1 layers with few channels or
+// This file holds the single-buffered kernel (stride 2, and stride-1 layers with few channels or
 // few tiles): a plain loop nest with small tiles, several workgroups per compute unit.  Large stride-1 layers
 // take the pipelined kernel of conv3x3_rows.hip, which reads the same packed section.
 #include <algorithm>
@@ -41,179 +40,12 @@
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
-#include "pack_live.h"
 #include "sparse_frag.h"
 #include "tile3x3.h"
 
 namespace rtoss {
 
 namespace {
-
-// Input channel (within a 32-channel stage) that pair g of lane-quarter q refers to in
-// sparse step `half`.
-__device__ __forceinline__ int stage_channel(int q, int g, int half)
-{
-    return 8 * (2 * (q & 1) + (g >> 1)) + 4 * half + 2 * (q >> 1) + (g & 1);
-}
-
-constexpr int kMaxTapGroups = 3;  // tap groups of a layout (TapLayout::tap)
-
-struct SparsePackArgs {
-    const void* w;
-    const uint8_t* idx;
-    char* out;
-    int Co, Ci, m_tiles, zero_items;
-    int64_t total_items;  // 64 * fragments per tile * tiles
-    LiveJob job;
-};
-
-// One workgroup of one layer (`block` counts from the layer's first block): the first blocks write the
-// public section, then comes one block per (stage, channel tile) and last the block of zeros.
-// A tile's 16 x 32 kernels (16 rows of 576 contiguous bytes) and their pattern indices are staged in LDS with
-// coalesced 16-byte loads; the fragment pieces (64 per fragment) are then assembled from LDS.
-template <typename T>
-__device__ __forceinline__ void pack_sparse3x3_body(const SparsePackArgs& a, const TapLayout& lay, const Dict& dict, int block)
-{
-    const T* __restrict__ w = (const T*)a.w;
-    const uint8_t* __restrict__ idx = a.idx;
-    char* __restrict__ out = a.out;
-    const int Co = a.Co, Ci = a.Ci, m_tiles = a.m_tiles, zero_items = a.zero_items;
-    const LiveJob job = a.job;
-    const int frags = layout_fragments(lay), tile_bytes = layout_tile_bytes(lay);
-    __shared__ uint16_t masks[256];
-    __shared__ __attribute__((aligned(16))) uint16_t wl[16][32 * 9];  // [row][channel][tap]
-    __shared__ __attribute__((aligned(16))) uint8_t il[16][32];       // [row][channel]
-    __shared__ uint16_t slots[256 * kMaxTapGroups];
-    constexpr unsigned kNoTaps = 15u | (15u << 4) | (0u << 8) | (1u << 10);  // a row past Co: zeros, slots 0 and 1
-    masks[threadIdx.x] = dict.mask[threadIdx.x];
-    if (block < job.blocks) {  // the first blocks write the blob's public section
-        __syncthreads();
-        pack_live_block<T>(w, idx, masks, dict.k, job, block);
-        return;
-    }
-    const int n_tiles = (int)(a.total_items / (64 * frags));
-    const int tile = block - job.blocks;  // stage * m_tiles + m_tile
-    if (tile >= n_tiles) {  // the blocks behind the fragments write the block of zeros, 16 bytes per lane
-        const int item = (tile - n_tiles) * 256 + (int)threadIdx.x;
-        if (item < zero_items) *(u32x4*)(out + (size_t)n_tiles * tile_bytes + (size_t)item * 16) = u32x4{0, 0, 0, 0};
-        return;
-    }
-    const int mt = tile % m_tiles, cb = tile / m_tiles;
-    // slots[p][group]: taps of pattern p's first and second live tap in the group (bits 0-3, 4-7; 15: none) and the
-    // slots they take (bits 8-9, 10-11; a missing second value points at the slot after the first, a group without
-    // live taps at slots 0 and 1: padding values of 0 may point anywhere, as long as the two differ)
-    for (int e = threadIdx.x; e < dict.P * kMaxTapGroups; e += 256) {
-        const int p = e / kMaxTapGroups, group = e % kMaxTapGroups;
-        unsigned tp[2] = {15u, 15u}, f[2] = {0u, 1u};
-        if (group < lay.groups) {
-            const unsigned m = dict.mask[p];
-            int n = 0;
-            for (int sl = 0; sl < 4; ++sl) {
-                const int tt = lay.tap[group][sl];
-                if (tt >= 0 && ((m >> tt) & 1u) && n < 2) {
-                    tp[n] = (unsigned)tt;
-                    f[n] = (unsigned)sl;
-                    ++n;
-                }
-            }
-            if (n == 1) f[1] = (f[0] + 1) & 3;
-        }
-        slots[e] = (uint16_t)(tp[0] | (tp[1] << 4) | (f[0] << 8) | (f[1] << 10));
-    }
-    // ---- stage: 16 rows x 36 chunks of weights, 16 rows x 2 chunks of indices (rows past Co are zeros) ----
-    // (rows start at multiples of 18 Ci and Ci bytes from the tensors' first elements; the interface asks for
-    // element alignment only, so rows that do not start on 16-byte boundaries are staged element-wise, and so is a
-    // last stage with fewer than 32 channels)
-    const int channels = min(32, Ci - 32 * cb);
-    if (Ci % 32 == 0 && ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(idx)) & 15) == 0) {
-        for (int c = threadIdx.x; c < 16 * 36; c += 256) {
-            const int r = c / 36, k = c % 36;
-            const int co = tile_row_channel(mt, r);
-            u32x4 v = {0, 0, 0, 0};
-            if (co < Co) v = *(const u32x4*)((const char*)w + ((int64_t)co * Ci + 32 * cb) * 18 + k * 16);
-            *(u32x4*)((char*)&wl[r][0] + k * 16) = v;
-        }
-        if (threadIdx.x < 32) {
-            const int r = threadIdx.x / 2, k = threadIdx.x % 2;
-            const int co = tile_row_channel(mt, r);
-            u32x4 v = {0, 0, 0, 0};
-            if (co < Co) v = *(const u32x4*)(idx + (int64_t)co * Ci + 32 * cb + k * 16);
-            *(u32x4*)(&il[r][k * 16]) = v;
-        }
-    } else {
-        const uint16_t* w16 = (const uint16_t*)w;
-        for (int c = threadIdx.x; c < 16 * 288; c += 256) {
-            const int r = c / 288, e = c % 288;
-            const int co = tile_row_channel(mt, r);
-            wl[r][e] = co < Co && e < 9 * channels ? w16[((int64_t)co * Ci + 32 * cb) * 9 + e] : (uint16_t)0;
-        }
-        for (int c = threadIdx.x; c < 16 * 32; c += 256) {
-            const int r = c / 32, e = c % 32;
-            const int co = tile_row_channel(mt, r);
-            il[r][e] = co < Co && e < channels ? idx[(int64_t)co * Ci + 32 * cb + e] : (uint8_t)0;
-        }
-    }
-    __syncthreads();
-    // ---- assemble: item = (fragment, lane).  What a pattern puts into a tap group -- which of the group's four slots
-    // its (at most two) live taps take, and which taps those are -- comes from the table built above, so the walk over
-    // the 4 x 4 (channel, slot) pairs of an item has no data-dependent branch. ----
-    char* tile_out = out + (size_t)tile * tile_bytes;
-    for (int item = threadIdx.x; item < 64 * frags; item += 256) {
-        const int lane = item % 64, step = item / 64;  // (step is uniform over a wave)
-        const int r = lane % 16, q = lane / 16;
-        const bool row_live = tile_row_channel(mt, r) < Co;
-        uint16_t vals[8];
-        if (step == 2 * lay.groups) {  // dense centre tap: K = 8q + j
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int c = 8 * q + j;
-                const uint16_t v = wl[r][c * 9 + 4];
-                vals[j] = (row_live && ((masks[il[r][c]] >> 4) & 1u)) ? v : (uint16_t)0;
-            }
-        } else {
-            const int group = step >> 1, half = step & 1;
-            unsigned fields = 0;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int c = stage_channel(q, g, half);
-                const unsigned e = row_live ? slots[il[r][c] * kMaxTapGroups + group] : kNoTaps;
-                const unsigned t0 = e & 15u, t1 = (e >> 4) & 15u;  // taps of the two values (15: none)
-                const uint16_t v0 = wl[r][c * 9 + (t0 < 9 ? t0 : 0)], v1 = wl[r][c * 9 + (t1 < 9 ? t1 : 0)];
-                vals[2 * g] = t0 < 9 ? v0 : (uint16_t)0;
-                vals[2 * g + 1] = t1 < 9 ? v1 : (uint16_t)0;
-                fields |= ((e >> 8) & 15u) << (4 * g);  // slot of the first value | slot of the second << 2
-            }
-            uint16_t* ip = (uint16_t*)(tile_out + frags * kFragBytes + (group * 64 + lane) * 4 + half * 2);
-            *ip = (uint16_t)fields;
-        }
-        u32x4 pk;
-        pk.x = vals[0] | ((uint32_t)vals[1] << 16);
-        pk.y = vals[2] | ((uint32_t)vals[3] << 16);
-        pk.z = vals[4] | ((uint32_t)vals[5] << 16);
-        pk.w = vals[6] | ((uint32_t)vals[7] << 16);
-        *(u32x4*)(tile_out + step * kFragBytes + lane * 16) = pk;
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void pack_sparse3x3_kernel(SparsePackArgs a, TapLayout lay, Dict dict)
-{
-    pack_sparse3x3_body<T>(a, lay, dict, (int)blockIdx.x);
-}
-
-struct SparsePackBatch {
-    SparsePackArgs a[kPackBatchMax];
-    int first_block[kPackBatchMax + 1];
-    int n;
-    TapLayout layout;  // (one dictionary per batch: one layout)
-};
-
-template <typename T>
-__global__ __launch_bounds__(256) void pack_sparse3x3_batch_kernel(SparsePackBatch b, Dict dict)
-{
-    const int t = batch_entry(b, (int)blockIdx.x);  // block-uniform
-    pack_sparse3x3_body<T>(b.a[t], b.layout, dict, (int)blockIdx.x - b.first_block[t]);
-}
 
 // Single-buffered variant: one LDS buffer, two barriers per stage, plain loop nest scheduled by the
 // compiler.  It needs half the LDS of the pipelined kernel below and few registers, so several
@@ -631,62 +463,6 @@ bool sparse3x3_shape_ok(const rtoss_wdesc& d)
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout)
 {
     return fragment_bytes(d, layout) + zero_block_bytes(d);
-}
-
-static SparsePackArgs sparse_pack_args(const rtoss_wdesc& d, int layout, const void* w, const uint8_t* idx, void* section,
-                                       void* live_values, uint8_t* live_idx, int* blocks)
-{
-    const int items_per_tile = 64 * layout_fragments(kLayouts[layout]);
-    SparsePackArgs a;
-    a.w = w;
-    a.idx = idx;
-    a.out = (char*)section;
-    a.Co = d.Co;
-    a.Ci = d.Ci;
-    a.m_tiles = padded_m_tiles(d.Co);
-    a.total_items = (int64_t)sparse_stages(d) * a.m_tiles * items_per_tile;
-    a.zero_items = (int)(zero_block_bytes(d) / 16);
-    a.job = make_live_job(live_values, live_idx, (int64_t)d.Co * d.Ci);
-    *blocks = (int)(a.job.blocks + a.total_items / items_per_tile + (a.zero_items + 255) / 256);  // public section, tiles, zeros
-    return a;
-}
-
-rtoss_status launch_pack_sparse3x3(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict,
-                                   void* section, void* live_values, uint8_t* live_idx, hipStream_t s)
-{
-    int blocks = 0;
-    const int layout = sparse3x3_layout(dict);
-    if (layout < 0) return fail(RTOSS_EINVAL, "pack: the dictionary has no 2-of-4 tap layout");
-    const SparsePackArgs a = sparse_pack_args(d, layout, w, idx, section, live_values, live_idx, &blocks);
-    dim3 grid((unsigned)blocks), block(256);
-    if (d.dt == RTOSS_F16) pack_sparse3x3_kernel<f16_t><<<grid, block, 0, s>>>(a, kLayouts[layout], dict);
-    else pack_sparse3x3_kernel<bf16_t><<<grid, block, 0, s>>>(a, kLayouts[layout], dict);
-    return check_hip(hipGetLastError(), "pack sparse3x3 launch");
-}
-
-rtoss_status launch_pack_sparse3x3_batch(const PackItem* items, int n, const Dict& dict, hipStream_t s)
-{
-    const int layout = sparse3x3_layout(dict);
-    if (layout < 0) return fail(RTOSS_EINVAL, "pack: the dictionary has no 2-of-4 tap layout");
-    for (int base = 0; base < n; base += kPackBatchMax) {
-        SparsePackBatch b;
-        b.layout = kLayouts[layout];
-        b.n = std::min(kPackBatchMax, n - base);
-        int total = 0;
-        for (int i = 0; i < b.n; ++i) {
-            const PackItem& it = items[base + i];
-            int blocks = 0;
-            b.a[i] = sparse_pack_args(it.d, layout, it.w, it.idx, it.section, it.live, it.live_idx, &blocks);
-            b.first_block[i] = total;
-            total += blocks;
-        }
-        b.first_block[b.n] = total;
-        dim3 grid((unsigned)total), block(256);
-        if (items[base].d.dt == RTOSS_F16) pack_sparse3x3_batch_kernel<f16_t><<<grid, block, 0, s>>>(b, dict);
-        else pack_sparse3x3_batch_kernel<bf16_t><<<grid, block, 0, s>>>(b, dict);
-        if (rtoss_status st = check_hip(hipGetLastError(), "pack sparse3x3 batch launch")) return st;
-    }
-    return RTOSS_OK;
 }
 
 rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, int layout, const void* section, const void* x,

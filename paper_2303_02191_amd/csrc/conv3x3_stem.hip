@@ -14,7 +14,6 @@
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
-#include "pack_live.h"
 
 namespace rtoss {
 
@@ -22,43 +21,6 @@ namespace {
 
 constexpr int kTH = 8, kTW = 32;  // output tile: 8 rows x 32 columns = 16 blocks of 16 positions
 
-
-template <typename T>
-__global__ __launch_bounds__(256) void pack_stem_kernel(const T* __restrict__ w, const uint8_t* __restrict__ idx, Dict dict,
-                                                        char* __restrict__ out, int Co, int Ci, int m_tiles, LiveJob job)
-{
-    __shared__ uint16_t masks[256];
-    masks[threadIdx.x] = dict.mask[threadIdx.x];
-    __syncthreads();
-    if ((int)blockIdx.x < job.blocks) {  // the first blocks write the blob's public section
-        pack_live_block<T>(w, idx, masks, dict.k, job, blockIdx.x);
-        return;
-    }
-    const int item = (blockIdx.x - job.blocks) * 256 + threadIdx.x;  // (m_tile, lane)
-    if (item >= m_tiles * 64) return;
-    const int lane = item % 64, mt = item / 64;
-    // Rows are dealt over each pair of channel tiles so that the 4 + 4 accumulator values a lane holds
-    // (rows 4q .. 4q+3 of both tiles) are the 8 consecutive channels 32*(mt/2) + 8q .. +7.
-    const int r = lane % 16, q = lane / 16;
-    const int co = 32 * (mt >> 1) + 8 * (r >> 2) + 4 * (mt & 1) + (r & 3);
-    uint16_t v[8];
-    for (int j = 0; j < 8; ++j) {
-        const int k = 8 * q + j;
-        v[j] = 0;
-        if (co < Co && k < 9 * Ci) {
-            const int kh = k / (3 * Ci), kw = (k % (3 * Ci)) / Ci, ci = k % Ci;
-            const int t = 3 * kh + kw;
-            const int64_t g9 = (int64_t)co * Ci + ci;
-            if ((masks[idx[g9]] >> t) & 1u) v[j] = __builtin_bit_cast(uint16_t, w[g9 * 9 + t]);
-        }
-    }
-    u32x4 pk;
-    pk.x = v[0] | ((uint32_t)v[1] << 16);
-    pk.y = v[2] | ((uint32_t)v[3] << 16);
-    pk.z = v[4] | ((uint32_t)v[5] << 16);
-    pk.w = v[6] | ((uint32_t)v[7] << 16);
-    *(u32x4*)(out + (size_t)item * 16) = pk;
-}
 
 // Ci is a template parameter: the index arithmetic below divides by it (and by 3 * Ci) per element, which
 // as run-time divisions made the kernel bound by integer ALU work.
@@ -196,18 +158,6 @@ bool stem3x3_shape_ok(const rtoss_wdesc& d)
 }
 
 size_t stem3x3_section_bytes(const rtoss_wdesc& d) { return (size_t)4 * 1024; }  // 4 tiles, unused ones zero
-
-rtoss_status launch_pack_stem3x3(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict, void* section,
-                                 void* live_values, uint8_t* live_idx, hipStream_t s)
-{
-    const LiveJob job = make_live_job(live_values, live_idx, (int64_t)d.Co * d.Ci);
-    dim3 grid((unsigned)(job.blocks + 1)), block(256);
-    if (d.dt == RTOSS_F16)
-        pack_stem_kernel<f16_t><<<grid, block, 0, s>>>((const f16_t*)w, idx, dict, (char*)section, d.Co, d.Ci, 4, job);
-    else
-        pack_stem_kernel<bf16_t><<<grid, block, 0, s>>>((const bf16_t*)w, idx, dict, (char*)section, d.Co, d.Ci, 4, job);
-    return check_hip(hipGetLastError(), "pack stem launch");
-}
 
 rtoss_status launch_conv3x3_stem(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                  hipStream_t s)

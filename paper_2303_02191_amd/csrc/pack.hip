@@ -1,42 +1,451 @@
-// Packing (Section II.B mask semantics: survivors keep their value, the rest are dropped;
-// Section IV.D: the tail of a flattened 1x1 tensor is dropped).
+// Packing: prune (Section II.B mask semantics: survivors keep their value, the rest are dropped; Section IV.D: the tail
+// of a flattened 1x1 tensor is dropped) and write the packed blobs of any number of layers in one launch.
 //
-// pack_live_kernel writes section 0 of the blob: for every group the k surviving weights
-// in ascending tap order, and a copy of the group's pattern index.
+// A blob is the public section (k survivors and the pattern index of every group) and a private one: weight fragments
+// in the order one of the convolution kernels reads them (formats: pack_plan.h, sparse_frag.h).  All formats of one
+// dtype share this kernel, so a model is packed by one launch: the layers are small (0.1-1 MB) and a launch per format,
+// or per 24 layers, left the chip idle between them.
+//
+// What bounds it: latency (index -> mask -> weight are dependent loads), then HBM.  So nothing is gathered from memory:
+//   * 3x3 fragments: a workgroup owns one (stage of input channels, tile of 16 output channels).  Its kernels are 16
+//     rows of 576 contiguous bytes; they and their indices are staged in LDS with 16-byte loads, and both the public
+//     section's part and the fragments are assembled from there.  Every weight is read once.
+//   * 1x1 fragments: a lane's 16 bytes are consecutive elements of one row of [Co][Ci], which touch at most two groups:
+//     one vector load and two index loads, all independent.
+//   * public sections of 1x1 layers: 256 groups per workgroup through LDS (pack_live.h).
+// Measured, 57 layers with 7.0 M fp16 weights, 2-entry patterns: 13.6 us in one launch; 38 us in four before.
+#include <algorithm>
+#include <vector>
+
 #include "common.h"
 #include "dtypes.h"
+#include "mma.h"
 #include "pack_live.h"
+#include "pack_plan.h"
+#include "sparse_frag.h"
 
 namespace rtoss {
 
-template <typename T>
-__global__ __launch_bounds__(256) void pack_live_kernel(const T* __restrict__ w, const uint8_t* __restrict__ idx,
-                                                        Dict dict, LiveJob job)
+namespace {
+
+// One layer of a launch.  Kept small: the table travels in the launch arguments (4 KB).
+struct PackEntry {
+    const void* w;
+    const uint8_t* idx;
+    char* blob;
+    uint32_t idx_off, mat_off;  // sections of the blob, in units of 256 bytes
+    int Co, Ci;
+    uint32_t items;             // 3x3: (stage, channel tile) pairs; 1x1 and stem: 16-byte pieces of the fragments
+    uint8_t format, a, b, c;    // MatrixFormat; 3x3: tap layout; streaming 1x1: KS, MT, WM
+};
+constexpr int kPackMax = 60;
+struct PackTable {
+    PackEntry e[kPackMax];
+    int first_block[64];  // entries past n: past every block
+};
+static_assert(sizeof(PackTable) + sizeof(Dict) <= 4096, "launch arguments");
+
+// Input channel (within a 32-channel stage) that pair g of lane-quarter q refers to in sparse step `half`.
+__device__ __forceinline__ int stage_channel(int q, int g, int half)
 {
-    __shared__ uint16_t masks[256];
-    masks[threadIdx.x] = dict.mask[threadIdx.x];
-    __syncthreads();
-    pack_live_block<T>(w, idx, masks, dict.k, job, blockIdx.x);
+    return 8 * (2 * (q & 1) + (g >> 1)) + 4 * half + 2 * (q >> 1) + (g & 1);
 }
 
-rtoss_status launch_pack_live(const rtoss_wdesc& d, const void* w, const uint8_t* idx, const Dict& dict,
-                              void* live_values, uint8_t* live_idx, int64_t G, hipStream_t s)
+constexpr int kTapGroups = 3;  // at most (TapLayout::tap)
+
+// LDS of a workgroup
+template <typename T> struct TileLds {
+    static constexpr int SC = 64 / (int)sizeof(T);  // channels of a stage
+    __attribute__((aligned(16))) T w[16][SC * 9];   // [row][channel][tap]
+    uint8_t idx[16][SC];
+    uint64_t taps[256];                             // 4 bits per live tap of a pattern, ascending; 15: none
+    uint16_t slots[256 * kTapGroups];
+};
+
+// (stage, tile) of a 3x3 layer: public section and fragments
+// (LAY: tap layout, or kDenseTaps; a template parameter so that the walks over a layout's taps are constants)
+constexpr int kDenseTaps = kNumLayouts;
+template <typename T, int LAY>
+__device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigned mask, const uint16_t* masks, int tile, int m_tiles,
+                                             TileLds<T>& L)
 {
-    if (G == 0) return RTOSS_OK;
-    const LiveJob job = make_live_job(live_values, live_idx, G);
-    dim3 grid((unsigned)job.blocks), block(256);
-    switch (d.dt) {
-    case RTOSS_F32:
-        pack_live_kernel<float><<<grid, block, 0, s>>>((const float*)w, idx, dict, job);
+    constexpr int SC = TileLds<T>::SC;
+    const T* __restrict__ w = (const T*)en.w;
+    const uint8_t* __restrict__ idx = en.idx;
+    constexpr bool SPARSE = LAY != kDenseTaps;
+    constexpr TapLayout lay = kLayouts[SPARSE ? LAY : 0];
+    const int Co = en.Co, Ci = en.Ci, tid = threadIdx.x;
+    const int mt = tile % m_tiles, stage = tile / m_tiles;
+    const int channels = min(SC, Ci - SC * stage);
+    // ---- stage weights and indices (rows past Co and channels past Ci: zeros), all of a lane's loads in flight ----
+    constexpr int IDX_PER = 16 * SC / 256;
+    uint8_t iv[IDX_PER];
+#pragma unroll
+    for (int i = 0; i < IDX_PER; ++i) {
+        const int c = tid + 256 * i, r = c / SC, e = c % SC, co = tile_row_channel(mt, r);
+        iv[i] = co < Co && e < channels ? idx[(int64_t)co * Ci + SC * stage + e] : (uint8_t)0;
+    }
+    if (Ci % SC == 0 && (reinterpret_cast<uintptr_t>(w) & 15) == 0) {
+        u32x4 v[3];  // 16 rows x 36 vectors
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int c = tid + 256 * i, r = c / 36, q = c % 36, co = tile_row_channel(mt, r);
+            v[i] = u32x4{0, 0, 0, 0};
+            if (c < 16 * 36 && co < Co) v[i] = *(const u32x4*)((const char*)w + ((int64_t)co * Ci + SC * stage) * (9 * (int)sizeof(T)) + q * 16);
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int c = tid + 256 * i, r = c / 36, q = c % 36;
+            if (c < 16 * 36) *(u32x4*)((char*)&L.w[r][0] + q * 16) = v[i];
+        }
+    } else {  // (the interface asks for element alignment only)
+#pragma unroll 6
+        for (int c = tid; c < 16 * SC * 9; c += 256) {
+            const int r = c / (SC * 9), e = c % (SC * 9), co = tile_row_channel(mt, r);
+            T v;
+            __builtin_memset(&v, 0, sizeof(T));
+            if (co < Co && e < 9 * channels) v = w[((int64_t)co * Ci + SC * stage) * 9 + e];
+            L.w[r][e] = v;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < IDX_PER; ++i) L.idx[(tid + 256 * i) / SC][(tid + 256 * i) % SC] = iv[i];
+    // ---- per-pattern tables, pattern tid (under the loads above) ----
+    {
+        uint64_t t = ~(uint64_t)0;
+        unsigned m = mask;
+        for (int j = 0; m; ++j, m &= m - 1) t = (t & ~((uint64_t)15 << (4 * j))) | (uint64_t)__builtin_ctz(m) << (4 * j);
+        L.taps[tid] = t;
+    }
+    // slots[p][group]: taps of pattern p's first and second live tap in the group (bits 0-3, 4-7; 15: none) and the
+    // slots they take (bits 8-9, 10-11; a missing second value points at the slot after the first, a group without
+    // live taps at slots 0 and 1: padding values of 0 may point anywhere, as long as the two differ)
+    constexpr unsigned kNoTaps = 15u | (15u << 4) | (0u << 8) | (1u << 10);
+    if constexpr (SPARSE) {
+#pragma unroll
+        for (int g = 0; g < lay.groups; ++g) {
+            unsigned t0 = 15u, t1 = 15u, f0 = 0u, f1 = 1u;
+            int n = 0;
+#pragma unroll
+            for (int sl = 0; sl < 4; ++sl) {
+                if (lay.tap[g][sl] < 0) continue;
+                const unsigned tt = (unsigned)lay.tap[g][sl];
+                const bool live = ((mask >> tt) & 1u) && n < 2;
+                t0 = live && n == 0 ? tt : t0;
+                f0 = live && n == 0 ? (unsigned)sl : f0;
+                t1 = live && n == 1 ? tt : t1;
+                f1 = live && n == 1 ? (unsigned)sl : f1;
+                n += live;
+            }
+            if (n == 1) f1 = (f0 + 1) & 3;
+            L.slots[tid * kTapGroups + g] = (uint16_t)(t0 | (t1 << 4) | (f0 << 8) | (f1 << 10));
+        }
+    }
+    __syncthreads();
+    // ---- public section: rows of 32 (or 16) groups, k values and an index each ----
+    T* live = (T*)en.blob;
+    uint8_t* live_idx = (uint8_t*)en.blob + (size_t)en.idx_off * 256;
+    // (a lane takes a group at a time and writes its k values; consecutive lanes, consecutive groups of a row)
+#pragma unroll
+    for (int i = 0; i < IDX_PER; ++i) {
+        const int c = (tid + 256 * i) % SC, r = (tid + 256 * i) / SC, co = tile_row_channel(mt, r);
+        if (co >= Co || c >= channels) continue;
+        const int64_t g = (int64_t)co * Ci + SC * stage + c;
+        live_idx[g] = iv[i];
+        const uint64_t taps = L.taps[iv[i]];
+        for (int j = 0; j < k; ++j) {
+            const unsigned t = (unsigned)(taps >> (4 * j)) & 15u;
+            T v = L.w[r][c * 9 + (t < 9 ? t : 0)];
+            if (t >= 9) __builtin_memset(&v, 0, sizeof(T));  // an index outside the dictionary
+            live[g * k + j] = v;
+        }
+    }
+    // ---- fragments: item = (fragment, lane) ----
+    char* out = en.blob + (size_t)en.mat_off * 256;
+    if constexpr (SPARSE) {
+        constexpr int frags = layout_fragments(lay);
+        char* tile_out = out + (size_t)tile * layout_tile_bytes(lay);
+        for (int item = tid; item < 64 * frags; item += 256) {
+            const int lane = item % 64, step = item / 64;  // (step is uniform over a wave)
+            const int r = lane % 16, q = lane / 16;
+            const bool row_live = tile_row_channel(mt, r) < Co;
+            uint16_t vals[8];
+            if (step == 2 * lay.groups) {  // dense centre tap: K = 8q + j
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int c = 8 * q + j;
+                    const uint16_t v = __builtin_bit_cast(uint16_t, L.w[r][c * 9 + 4]);
+                    vals[j] = (row_live && ((masks[L.idx[r][c]] >> 4) & 1u)) ? v : (uint16_t)0;
+                }
+            } else {
+                const int group = step >> 1, half = step & 1;
+                unsigned fields = 0;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int c = stage_channel(q, g, half), p = L.idx[r][c];
+                    const unsigned e = row_live ? L.slots[p * kTapGroups + group] : kNoTaps;
+                    const unsigned t0 = e & 15u, t1 = (e >> 4) & 15u;  // taps of the two values (15: none)
+                    const uint16_t v0 = __builtin_bit_cast(uint16_t, L.w[r][c * 9 + (t0 < 9 ? t0 : 0)]);
+                    const uint16_t v1 = __builtin_bit_cast(uint16_t, L.w[r][c * 9 + (t1 < 9 ? t1 : 0)]);
+                    vals[2 * g] = t0 < 9 ? v0 : (uint16_t)0;
+                    vals[2 * g + 1] = t1 < 9 ? v1 : (uint16_t)0;
+                    fields |= ((e >> 8) & 15u) << (4 * g);  // slot of the first value | slot of the second << 2
+                }
+                *(uint16_t*)(tile_out + frags * kFragBytes + (group * 64 + lane) * 4 + half * 2) = (uint16_t)fields;
+            }
+            u32x4 pk;
+            __builtin_memcpy(&pk, vals, 16);
+            *(u32x4*)(tile_out + step * kFragBytes + lane * 16) = pk;
+        }
+    } else {
+        constexpr int PER = 16 / (int)sizeof(T);
+        char* tile_out = out + (size_t)tile * kDenseTileBytes;
+        for (int item = tid; item < 64 * 9; item += 256) {
+            const int lane = item % 64, t = item / 64;
+            const int r = lane % 16, q = lane / 16;
+            T v[PER];
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const int c = PER * q + j;
+                v[j] = L.w[r][c * 9 + t];
+                if (!((masks[L.idx[r][c]] >> t) & 1u)) __builtin_memset(&v[j], 0, sizeof(T));  // (rows past Co are zeros)
+            }
+            u32x4 pk;
+            __builtin_memcpy(&pk, v, 16);
+            *(u32x4*)(tile_out + item * 16) = pk;
+        }
+    }
+}
+
+// A lane's 16 bytes of a 1x1 fragment: consecutive elements of row co starting at channel ci0, pruned.
+template <typename T>
+__device__ __forceinline__ u32x4 pack_piece1x1(const T* __restrict__ w, const uint8_t* __restrict__ idx, const uint16_t* masks,
+                                               int Co, int Ci, int co, int ci0)
+{
+    constexpr int PER = 16 / (int)sizeof(T);
+    u32x4 pk = {0, 0, 0, 0};
+    if (co >= Co || ci0 >= Ci) return pk;
+    // element f of the flattened matrix sits in group f/9 at tap f%9 (groups may straddle rows; the tail has no group)
+    const int64_t f0 = (int64_t)co * Ci + ci0, G = (int64_t)Co * Ci / 9;
+    const int64_t g0 = f0 < (int64_t)1 << 31 ? (int64_t)((uint32_t)f0 / 9u) : f0 / 9;
+    const int t0 = (int)(f0 - 9 * g0);
+    if (g0 >= G) return pk;  // all tail (a tensor of fewer than nine weights may come without pointers)
+    const unsigned m0 = masks[idx[g0]], m1 = g0 + 1 < G ? masks[idx[g0 + 1]] : 0u;
+    const unsigned live = (m0 | m1 << 9) >> t0;  // bit j: element f0 + j survives
+    T v[PER];
+    if (Ci % PER == 0 && (reinterpret_cast<uintptr_t>(w) & 15) == 0) {
+        const u32x4 raw = *(const u32x4*)(w + f0);
+        __builtin_memcpy(v, &raw, 16);
+    } else {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            __builtin_memset(&v[j], 0, sizeof(T));
+            if (ci0 + j < Ci) v[j] = w[f0 + j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (!((live >> j) & 1u)) __builtin_memset(&v[j], 0, sizeof(T));
+    __builtin_memcpy(&pk, v, 16);
+    return pk;
+}
+
+// A lane's 16 bytes of a stem fragment (Ci <= 3): K = kh*3*Ci + kw*Ci + ci.  Rows are dealt over each pair of channel
+// tiles so that the 4 + 4 accumulator values a lane holds are the 8 consecutive channels 32*(mt/2) + 8q .. +7.
+template <typename T>
+__device__ __forceinline__ u32x4 pack_piece_stem(const T* __restrict__ w, const uint8_t* __restrict__ idx, const uint16_t* masks,
+                                                 int Co, int Ci, int item)
+{
+    const int lane = item % 64, mt = item / 64, r = lane % 16, q = lane / 16;
+    const int co = 32 * (mt >> 1) + 8 * (r >> 2) + 4 * (mt & 1) + (r & 3);
+    uint16_t v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int k = 8 * q + j;
+        v[j] = 0;
+        if (co < Co && k < 9 * Ci) {
+            const int t = k / Ci, ci = k - t * Ci;
+            const int g9 = co * Ci + ci;
+            if ((masks[idx[g9]] >> t) & 1u) v[j] = __builtin_bit_cast(uint16_t, w[g9 * 9 + t]);
+        }
+    }
+    u32x4 pk;
+    __builtin_memcpy(&pk, v, 16);
+    return pk;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
+{
+    __shared__ uint16_t masks[256];
+    union Lds {
+        TileLds<T> tile;
+        __attribute__((aligned(16))) char live[live_block_lds_bytes<T>()];
+    };
+    __shared__ Lds lds;
+    const int tid = threadIdx.x;
+    // A block's layer is the last entry that starts at or before it.  Every lane loads one entry along with the table of
+    // first blocks and its mask, and the layer's is broadcast from its lane: one round trip to the launch arguments,
+    // which no cache holds yet, instead of two.
+    const int lane0 = tid & 63;
+    const int my_first = tab.first_block[lane0];
+    union {
+        PackEntry e;
+        uint32_t w[sizeof(PackEntry) / 4];
+    } row, pick;
+    row.e = tab.e[lane0 < kPackMax ? lane0 : 0];
+    const unsigned mask = dict.mask[tid];
+    masks[tid] = (uint16_t)mask;
+    const int t = __builtin_popcountll(__ballot(my_first <= (int)blockIdx.x)) - 1;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(PackEntry) / 4); ++i) pick.w[i] = (uint32_t)__builtin_amdgcn_readlane((int)row.w[i], t);
+    const PackEntry en = pick.e;
+    int block = (int)blockIdx.x - __builtin_amdgcn_readlane(my_first, t);
+    __syncthreads();
+    const bool is3x3 = en.format == kFormatSparse24 || en.format == kFormatDense3x3;
+    char* section = en.blob + (size_t)en.mat_off * 256;
+    const int stages = (en.Ci + stage_channels(sizeof(T) == 4 ? RTOSS_F32 : RTOSS_F16) - 1) / (64 / (int)sizeof(T));
+    if (is3x3) {
+        const int m_tiles = (int)en.items / stages;
+        if (block < (int)en.items) {
+            if constexpr (sizeof(T) == 2)
+                if (en.format == kFormatSparse24) {
+                    if (en.a == 0) pack_tile3x3<T, 0>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
+                    else pack_tile3x3<T, 1>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
+                    return;
+                }
+            pack_tile3x3<T, kDenseTaps>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
+            return;
+        }
+        // the block behind the tiles writes the block of zeros
+        const size_t end = (size_t)en.items * (en.format == kFormatSparse24 ? layout_tile_bytes(kLayouts[en.a]) : kDenseTileBytes);
+        for (int b = tid * 16; b < zero_section_bytes(stages); b += 4096) *(u32x4*)(section + end + b) = u32x4{0, 0, 0, 0};
+        return;
+    }
+    // other formats: first the public section, 256 groups per block
+    const int ks2 = en.format == kFormatStem || en.c == 9 ? 9 : 1;  // (c of a layer without fragments: weights per kernel)
+    LiveJob job;
+    job.G = (int64_t)en.Co * en.Ci * ks2 / 9;
+    job.blocks = (int)((job.G + 255) / 256);
+    if (block < job.blocks) {
+        job.live = en.blob;
+        job.live_idx = (uint8_t*)en.blob + (size_t)en.idx_off * 256;
+        pack_live_block<T>((const T*)en.w, en.idx, masks, dict.k, job, block, lds.live);
+        return;
+    }
+    const int item = (block - job.blocks) * 256 + tid;
+    const T* w = (const T*)en.w;
+    if (item >= (int)en.items) {
+        const int zeros = en.format == kFormatStem ? 0 : zero_section_bytes(stages) / 16;
+        if (item < (int)en.items + zeros) *(u32x4*)(section + (size_t)item * 16) = u32x4{0, 0, 0, 0};
+        return;
+    }
+    const int lane = item % 64, r = lane % 16, q = lane / 16;
+    constexpr int PER = 16 / (int)sizeof(T);
+    int f = item / 64;
+    if (en.format == kFormatDenseStream) {
+        // rows permuted so that a lane's 4*MT accumulator values are consecutive channels
+        const int KS = en.a, MT = en.b, WM = en.c;
+        const int s = f % KS;
+        f /= KS;
+        const int m = f % MT;
+        f /= MT;
+        const int co = f * (16 * MT) + (r / 4) * (4 * MT) + 4 * m + (r % 4);  // (f: channel block and wave slice)
+        (void)WM;
+        *(u32x4*)(section + (size_t)item * 16) = pack_piece1x1<T>(w, en.idx, masks, en.Co, en.Ci, co, 4 * PER * s + PER * q);
+    } else if (en.format == kFormatDense) {
+        const int m_tiles = (int)en.items / (64 * stages);
+        const int mt = f % m_tiles, s = f / m_tiles;
+        *(u32x4*)(section + (size_t)item * 16) = pack_piece1x1<T>(w, en.idx, masks, en.Co, en.Ci, 16 * mt + r, 4 * PER * s + PER * q);
+    } else if constexpr (sizeof(T) == 2) {  // stem
+        *(u32x4*)(section + (size_t)item * 16) = pack_piece_stem<T>(w, en.idx, masks, en.Co, en.Ci, item);
+    }
+}
+
+// Table entry of one layer and the number of blocks it takes.
+rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, PackEntry* en, int64_t* blocks)
+{
+    const rtoss_wdesc& d = it.d;
+    en->w = it.w;
+    en->idx = it.idx;
+    en->blob = (char*)it.live;  // section 0 starts the blob
+    if (g.total / 256 > 0xffffffffull) return fail(RTOSS_ESHAPE, "pack: blob too large");
+    en->idx_off = (uint32_t)(g.idx_off / 256);
+    en->mat_off = (uint32_t)(g.mat_off / 256);
+    en->Co = d.Co;
+    en->Ci = d.Ci;
+    en->format = (uint8_t)g.format;
+    en->a = en->b = en->c = 0;
+    const int stages = stage_count(d);
+    const int64_t live_blocks = (g.G + 255) / 256;
+    int64_t items = 0;
+    switch (g.format) {
+    case kFormatSparse24:
+        en->a = (uint8_t)layout;
+        items = (int64_t)stages * padded_m_tiles(d.Co);
+        *blocks = items + 1;
         break;
-    case RTOSS_F16:
-        pack_live_kernel<f16_t><<<grid, block, 0, s>>>((const f16_t*)w, idx, dict, job);
+    case kFormatDense3x3:
+        items = (int64_t)stages * 4 * dense_channel_blocks(d.Co);
+        *blocks = items + 1;
         break;
-    case RTOSS_BF16:
-        pack_live_kernel<bf16_t><<<grid, block, 0, s>>>((const bf16_t*)w, idx, dict, job);
+    case kFormatDenseStream: {
+        const int KS = stages, MT = stream_mt_of(KS), WM = stream_wm_of(KS, d.Co);
+        en->a = (uint8_t)KS;
+        en->b = (uint8_t)MT;
+        en->c = (uint8_t)WM;
+        items = (int64_t)stream_co_blocks_of(KS, d.Co) * WM * MT * KS * 64;
+        *blocks = live_blocks + (items + zero_section_bytes(stages) / 16 + 255) / 256;
         break;
     }
-    return check_hip(hipGetLastError(), "pack launch");
+    case kFormatDense:
+        items = (int64_t)stages * ring_padded_tiles(d.Co) * 64;
+        *blocks = live_blocks + (items + zero_section_bytes(stages) / 16 + 255) / 256;
+        break;
+    case kFormatStem:
+        items = 4 * 64;
+        *blocks = live_blocks + 1;
+        break;
+    default:
+        en->c = d.ksize == 3 ? 9 : 0;
+        *blocks = live_blocks;
+    }
+    if (items > 0x7fffff00 || *blocks > 0x7fffff00) return fail(RTOSS_ESHAPE, "pack: layer too large");
+    en->items = (uint32_t)items;
+    return RTOSS_OK;
+}
+
+}  // namespace
+
+rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, const Dict& dict, hipStream_t s)
+{
+    const int layout = std::max(0, sparse3x3_layout(dict));
+    for (int dt : {(int)RTOSS_F32, (int)RTOSS_F16, (int)RTOSS_BF16})
+        for (int i = 0; i < n;) {  // i runs on across launches
+            PackTable tab;
+            int m = 0;
+            int64_t total = 0;
+            for (; i < n && m < kPackMax; ++i) {
+                if ((int)items[i].d.dt != dt) continue;
+                int64_t blocks = 0;
+                if (rtoss_status st = make_entry(items[i], geo[i], layout, &tab.e[m], &blocks)) return st;
+                if (blocks == 0) continue;
+                if (total + blocks > 0x7fffff00) {
+                    if (m == 0) return fail(RTOSS_ESHAPE, "pack: layer too large");
+                    break;
+                }
+                tab.first_block[m++] = (int)total;
+                total += blocks;
+            }
+            if (m == 0) continue;
+            for (int t = m; t < 64; ++t) tab.first_block[t] = 0x7fffffff;
+            dim3 grid((unsigned)total), block(256);
+            if (dt == RTOSS_F32) pack_kernel<float><<<grid, block, 0, s>>>(tab, dict);
+            else if (dt == RTOSS_F16) pack_kernel<f16_t><<<grid, block, 0, s>>>(tab, dict);
+            else pack_kernel<bf16_t><<<grid, block, 0, s>>>(tab, dict);
+            if (rtoss_status st = check_hip(hipGetLastError(), "pack launch")) return st;
+        }
+    return RTOSS_OK;
 }
 
 }  // namespace rtoss
