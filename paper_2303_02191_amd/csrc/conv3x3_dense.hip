@@ -252,6 +252,7 @@ rtoss_status launch_conv3x3_dense(const rtoss_wdesc& d, const ConvParams& c, con
     const char* wf = (const char*)section;
     const bool f32out = c.out_dt == RTOSS_F32;
     if (const int plan = ksplit3x3_plan(d, c, 2)) return launch_conv3x3_ksplit(d, c, 2, plan, section, wf + frag_bytes(d), x, y, s);
+    if (const int plan = strip3x3_plan(d, c, 2)) return launch_conv3x3_strip(d, c, 2, plan, section, wf + frag_bytes(d), x, y, s);
     if (d.dt == RTOSS_F32) return launch_typed<float, float>(d, c, wf, x, y, s);
     if (d.dt == RTOSS_F16)
         return f32out ? launch_typed<f16_t, float>(d, c, wf, x, y, s) : launch_typed<f16_t, f16_t>(d, c, wf, x, y, s);

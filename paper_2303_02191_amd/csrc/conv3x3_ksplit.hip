@@ -33,20 +33,6 @@ namespace rtoss {
 
 namespace {
 
-template <typename T> struct Sparse64;  // D = A * B + C, A 2-of-4 sparse: v_smfmac_f32_16x16x64
-template <> struct Sparse64<f16_t> {
-    template <int ABID> static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x8 b, f32x4 c, int idx)
-    {
-        return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h16, b), c, idx, 0, ABID);
-    }
-};
-template <> struct Sparse64<bf16_t> {
-    template <int ABID> static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x8 b, f32x4 c, int idx)
-    {
-        return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b16, b), c, idx, 0, ABID);
-    }
-};
-
 // How a stage of one channel tile is multiplied: the tap layouts of sparse_frag.h, or one dense step per tap.
 constexpr int kDenseTaps = 2;
 constexpr int steps_tile_bytes(int lay) { return lay == kDenseTaps ? 9 * kFragBytes : layout_tile_bytes(kLayouts[lay]); }

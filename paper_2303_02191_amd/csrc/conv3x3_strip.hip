@@ -1,0 +1,332 @@
+// 3x3 pattern-pruned convolution, stride 1, over strips of output rows: the kernel for launches between the ones that
+// cannot fill the chip (conv3x3_ksplit.hip) and the ones large enough for the persistent pipeline (conv3x3_rows.hip).
+// Reads the packed sections of sparse_frag.h (2-of-4 steps) and of the dense mode (one step per tap: 16-bit dictionaries
+// without a 2-of-4 shape, and fp32).
+//
+// What bounds these layers is LDS bandwidth: a 16-byte operand read per lane is 8 cycles of the compute unit's LDS, a
+// matrix instruction 16 cycles of one of its four SIMDs.  With the 16 columns of an instruction as a 4x4 block of
+// positions every tap of every block is a read of its own, nine per block.  Here the 16 columns are 16 consecutive
+// positions of one output row, so the operands of the nine taps are overlapping windows of the same input rows: with
+// R[i][kw] = the read of input row i at column shift kw, output row j takes tap (kh, kw) from R[j + kh][kw].  A wave owns
+// TN rows and all 64 channels of the workgroup and reads 3*(TN + 2) activation vectors per stage of input channels
+// instead of 9*TN; with the weight fragments, TN = 5: 49 reads for 100 matrix instructions (92 with 4x4 blocks).
+//
+// Two workgroups per compute unit cover each other's copies and barriers.  TN is chosen per launch (strip3x3_plan).  Where
+// two buffers of a workgroup fit LDS twice, the next stage's copies are issued behind the barrier that opens a stage (DB).
+#include <algorithm>
+#include <type_traits>
+
+#include "common.h"
+#include "dtypes.h"
+#include "epilogue.h"
+#include "mma.h"
+#include "pack_plan.h"
+#include "sparse_frag.h"
+
+namespace rtoss {
+
+namespace {
+
+constexpr int kTM = 4;         // channel tiles of a workgroup (64 channels)
+constexpr int kCols = 16;      // output columns of a workgroup
+constexpr int kLW = kCols + 2; // input columns
+constexpr int kDenseTaps = kNumLayouts;
+constexpr int kTwoBuffers = 8; // in a plan: rows per wave + kTwoBuffers
+constexpr int strip_tile_bytes(int lay) { return lay == kDenseTaps ? kDenseTileBytes : layout_tile_bytes(kLayouts[lay]); }
+
+template <int TN, int LAY, bool DB> struct Strip {
+    static constexpr int ROWS = 4 * TN;                      // output rows of a workgroup
+    static constexpr int TILE = strip_tile_bytes(LAY);
+    static constexpr int A_BYTES = kTM * TILE;
+    static constexpr int A_COPIES = A_BYTES / 1024;          // 64 lanes x 16 bytes each
+    static constexpr int X_CHUNKS = (ROWS + 2) * kLW * 4;
+    static constexpr int X_COPIES = (X_CHUNKS + 63) / 64;
+    static constexpr int A_PER_WAVE = (A_COPIES + 3) / 4, X_PER_WAVE = (X_COPIES + 3) / 4;
+    static constexpr int X_AREA = X_PER_WAVE * 4096;
+    static constexpr int BUF = A_BYTES + X_AREA;             // one stage
+    static constexpr int LDS = (DB ? 2 : 1) * BUF + EpiScaleBias<16 * kTM>::kBytes;
+    static_assert(A_BYTES % 1024 == 0, "weight fragments are whole copy instructions");
+};
+
+template <typename T, typename TO, int TN, int LAY, bool DB>
+__global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
+                                                               const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                                               int H, int W, int Ci, int Co, int m_tiles_total, int strips,
+                                                               int tiles_per_image, int co_blocks, int total, int work_per_xcd,
+                                                               Epilogue ep)
+{
+    using P = Strip<TN, LAY, DB>;
+    constexpr TapLayout LY = kLayouts[LAY == kDenseTaps ? 0 : LAY];
+    constexpr int NG = LY.groups, FR = layout_fragments(LY);
+    constexpr int PER = 16 / (int)sizeof(T);  // channels in a lane's 16 bytes; a stage is four of them
+    extern __shared__ __attribute__((aligned(16))) char smem[];  // [weights][activations][scale, bias]
+    float* const lds_ep = (float*)(smem + (DB ? 2 : 1) * P::BUF);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // XCD-contiguous work order, channel block fastest: the workgroups of one activation tile share an L2
+    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
+    if (work >= total) return;
+    const int cb = work % co_blocks;
+    const int tile = (work / co_blocks) % tiles_per_image;
+    const int n_img = (work / co_blocks) / tiles_per_image;
+    const int oh0 = (tile / strips) * P::ROWS, ow0 = (tile % strips) * kCols;
+    const int stages = Ci / (4 * PER);
+
+    EpiScaleBias<16 * kTM> scale_bias;
+    scale_bias.load(ep, 64 * cb, Co, tid);
+
+    const char* a_src = wfrag + (int64_t)cb * P::A_BYTES + lane * 16;
+    const int64_t a_stage_stride = (int64_t)m_tiles_total * P::TILE;
+    const char* x_ptr[P::X_PER_WAVE];
+#pragma unroll
+    for (int k = 0; k < P::X_PER_WAVE; ++k) {
+        const int pos = (k * 4 + wave) * 16 + (lane >> 2);
+        const int xr = pos / kLW, xc = pos % kLW;
+        const int ih = oh0 - 1 + xr, iw = ow0 - 1 + xc;
+        const bool inside = xr < P::ROWS + 2 && (unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W;
+        const int off = ((n_img * H + ih) * W + iw) * (Ci / PER) + (lane & 3);  // in 16-byte chunks (31 bits: checked by the launcher)
+        x_ptr[k] = inside ? (const char*)x + (int64_t)off * 16 : zeros;
+    }
+
+    const int nn = lane & 15, qq = lane >> 4;
+    const int xoff = (wave * TN * kLW + nn) * 64 + qq * 16;
+    f32x4 acc[kTM][TN];
+    auto issue_copies = [&](int stage, char* buf) {
+#pragma unroll
+        for (int k = 0; k < P::A_PER_WAVE; ++k) {
+            const int kk = k * 4 + wave;  // wave-uniform
+            if (kk < P::A_COPIES) copy16_to_lds(a_src + stage * a_stage_stride + kk * 1024, buf + kk * 1024);
+        }
+#pragma unroll
+        for (int k = 0; k < P::X_PER_WAVE; ++k) copy16_to_lds(x_ptr[k] + stage * 64, buf + P::A_BYTES + (k * 4 + wave) * 1024);
+    };
+    issue_copies(0, smem);
+    auto run_stage = [&](auto first_tag, int stage) {
+        constexpr bool FIRST = decltype(first_tag)::value;
+        const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+        const char* lds_a = smem + (DB ? (stage & 1) * P::BUF : 0);
+        const char* lds_x = lds_a + P::A_BYTES;
+        if constexpr (DB) {
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies of this stage have landed in LDS
+            if constexpr (FIRST) scale_bias.store(lds_ep, ep, tid);
+            __syncthreads();  // ... and everybody's; and everybody is done reading the other buffer
+            if (stage + 1 < stages) issue_copies(stage + 1, smem + ((stage & 1) ^ 1) * P::BUF);
+        } else {
+            if constexpr (!FIRST) {
+                __syncthreads();  // everybody is done reading the previous stage
+                issue_copies(stage, smem);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies have landed in LDS
+            if constexpr (FIRST) scale_bias.store(lds_ep, ep, tid);
+            __syncthreads();                     // ... and everybody's
+        }
+        u32x4 R[TN + 2][3];
+#pragma unroll
+        for (int i = 0; i < TN + 2; ++i)
+#pragma unroll
+            for (int kw = 0; kw < 3; ++kw) R[i][kw] = *(const u32x4*)(lds_x + xoff + (i * kLW + kw) * 64);
+        const char* A = lds_a + lane * 16;
+        if constexpr (LAY == kDenseTaps) {
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+#pragma unroll
+                for (int m = 0; m < kTM; ++m) {
+                    const u32x4 a = *(const u32x4*)(A + m * P::TILE + t * kFragBytes);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[m][j] = Dense16<T>::mma(a, R[j + t / 3][t % 3], FIRST && t == 0 ? none : acc[m][j]);
+                }
+        } else {
+            if constexpr (LY.centre) {
+#pragma unroll
+                for (int m = 0; m < kTM; ++m) {
+                    const u32x4 a = *(const u32x4*)(A + m * P::TILE + 2 * NG * kFragBytes);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[m][j] = Dense16<T>::mma(a, R[j + 1][1], FIRST ? none : acc[m][j]);
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                u32x4 a[kTM][2];
+                int idx[kTM];
+#pragma unroll
+                for (int m = 0; m < kTM; ++m) {
+                    a[m][0] = *(const u32x4*)(A + m * P::TILE + (2 * g) * kFragBytes);
+                    a[m][1] = *(const u32x4*)(A + m * P::TILE + (2 * g + 1) * kFragBytes);
+                    idx[m] = *(const int*)(lds_a + m * P::TILE + FR * kFragBytes + (g * 64 + lane) * 4);
+                }
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    // B operands of both sparse steps: element 4*c + f of a step = channel c (of this lane's 4), tap slot f
+                    u32x4 r[4];
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) {
+                        const int t = LY.tap[g][f] >= 0 ? LY.tap[g][f] : LY.tap[g][0];  // (an empty slot weighs 0)
+                        r[f] = R[j + t / 3][t % 3];
+                    }
+                    u32x8 b[2];
+#pragma unroll
+                    for (int half = 0; half < 2; ++half)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) {
+                            const int d = 2 * half + p;
+                            b[half][4 * p + 0] = __builtin_amdgcn_perm(r[1][d], r[0][d], 0x05040100u);
+                            b[half][4 * p + 1] = __builtin_amdgcn_perm(r[3][d], r[2][d], 0x05040100u);
+                            b[half][4 * p + 2] = __builtin_amdgcn_perm(r[1][d], r[0][d], 0x07060302u);
+                            b[half][4 * p + 3] = __builtin_amdgcn_perm(r[3][d], r[2][d], 0x07060302u);
+                        }
+#pragma unroll
+                    for (int m = 0; m < kTM; ++m)
+                        acc[m][j] = Sparse64<T>::template mma<0>(a[m][0], b[0], FIRST && !LY.centre && g == 0 ? none : acc[m][j], idx[m]);
+#pragma unroll
+                    for (int m = 0; m < kTM; ++m) acc[m][j] = Sparse64<T>::template mma<1>(a[m][1], b[1], acc[m][j], idx[m]);
+                }
+            }
+        }
+    };
+    run_stage(std::true_type{}, 0);
+    for (int stage = 1; stage < stages; ++stage) run_stage(std::false_type{}, stage);
+
+    // ---- store: a lane holds column nn (position) and 16 consecutive channels of each of its rows ----
+    const int co = 64 * cb + 16 * qq, ow = ow0 + nn;
+    if (co >= Co || ow >= W) return;  // (Co is a multiple of 16: a run of 16 channels is all in or all out)
+    auto finish = [&](auto shortcut_tag) {
+        constexpr bool SHORTCUT = decltype(shortcut_tag)::value;
+        EpiResidual<TO, 16> shortcut[TN];
+        const int64_t pos0 = ((int64_t)n_img * H + oh0 + wave * TN) * W + ow;
+        if constexpr (SHORTCUT) {  // its loads go out together, before any of them is needed
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                if (oh0 + wave * TN + j < H) shortcut[j].load(ep, pos0 + (int64_t)j * W, co);
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            if (oh0 + wave * TN + j >= H) continue;
+            TO* yp = y + (pos0 + (int64_t)j * W) * ep.ldy + co;
+            float v[16];
+#pragma unroll
+            for (int m = 0; m < kTM; ++m)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][j][e];
+            epi_scale_bias_act<TO, 16>(v, ep, lds_ep + 16 * qq, lds_ep + 64 + 16 * qq);
+            if constexpr (SHORTCUT) shortcut[j].add(v);
+            if constexpr (sizeof(TO) == 4) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+            } else {
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    u32x4 o;
+                    o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
+                    o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
+                    o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
+                    o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
+                    *(u32x4*)(yp + 8 * g) = o;
+                }
+            }
+        }
+    };
+    if (ep.residual) finish(std::true_type{});
+    else finish(std::false_type{});
+}
+
+template <typename T, typename TO, int TN, int LAY, bool DB>
+rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
+{
+    using P = Strip<TN, LAY, DB>;
+    const int strips = (c.W + kCols - 1) / kCols, rows = (c.H + P::ROWS - 1) / P::ROWS;
+    const int co_blocks = (d.Co + 63) / 64;
+    auto kern = conv3x3_strip_kernel<T, TO, TN, LAY, DB>;
+    static LaunchOnce lds_once;  // per instantiation
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, P::LDS, lds_once, "conv3x3 shared memory attribute")) return st;
+    const int64_t total = (int64_t)strips * rows * co_blocks * c.N;
+    if (total > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
+    if ((int64_t)c.N * c.H * c.W * d.Ci * (int)sizeof(T) / 16 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
+    const int work_per_xcd = (int)((total + 7) / 8);
+    dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
+    kern<<<grid, block, P::LDS, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co,
+                                     LAY == kDenseTaps ? kTM * co_blocks : padded_m_tiles(d.Co), strips, strips * rows, co_blocks,
+                                     (int)total, work_per_xcd, c.ep);
+    return check_hip(hipGetLastError(), "conv3x3 strip launch");
+}
+
+template <typename T, typename TO, int LAY>
+rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, int plan, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
+{
+    switch (plan) {
+    case 2: return launch_rows<T, TO, 2, LAY, false>(d, c, wf, zeros, x, y, s);
+    case 3: return launch_rows<T, TO, 3, LAY, false>(d, c, wf, zeros, x, y, s);
+    case 4: return launch_rows<T, TO, 4, LAY, false>(d, c, wf, zeros, x, y, s);
+    case 5: if constexpr (LAY != 0) return launch_rows<T, TO, 5, LAY, false>(d, c, wf, zeros, x, y, s); else break;
+    case 2 + kTwoBuffers: if constexpr (sizeof(T) == 2) return launch_rows<T, TO, 2, LAY, true>(d, c, wf, zeros, x, y, s); else break;
+    case 3 + kTwoBuffers: if constexpr (LAY == 0) return launch_rows<T, TO, 3, LAY, true>(d, c, wf, zeros, x, y, s); else break;
+    }
+    return fail(RTOSS_EINVAL, "conv: unknown strip plan %d", plan);
+}
+
+template <int LAY>
+rtoss_status launch_layout(const rtoss_wdesc& d, const ConvParams& c, int plan, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
+{
+    const bool f32out = c.out_dt == RTOSS_F32;
+    if constexpr (LAY == kDenseTaps)
+        if (d.dt == RTOSS_F32) return launch_typed<float, float, LAY>(d, c, plan, wf, zeros, x, y, s);
+    if (d.dt == RTOSS_F16)
+        return f32out ? launch_typed<f16_t, float, LAY>(d, c, plan, wf, zeros, x, y, s) : launch_typed<f16_t, f16_t, LAY>(d, c, plan, wf, zeros, x, y, s);
+    return f32out ? launch_typed<bf16_t, float, LAY>(d, c, plan, wf, zeros, x, y, s) : launch_typed<bf16_t, bf16_t, LAY>(d, c, plan, wf, zeros, x, y, s);
+}
+
+}  // namespace
+
+// When a launch belongs here, and with how many rows per wave.  The time of a launch is set by how many rounds of
+// workgroups it takes (two per compute unit at once) and the depth of the layer; measured per stage with the chip filled
+// once / twice: TN = 2 0.88 / 1.45 us, 3 1.12 / 1.85, 4 1.6 / 3.1, plus 3 us.  So: the smallest TN whose workgroups fit
+// one round.  (bf16, layout 0, batch x channels @ image: 1x256@100x168 18.0 us with TN = 3, 23.2 with the single-buffered
+// kernel; 4x128@60x70 8.0 and 9.6; 16x128@40x40 9.2 and 10.3; 4x64@112x130 7.3 and 8.0.  Layout 1: 2x256@100x168 33.6 and
+// 40.3.  Dense mode: 36.3 and 49.0.)
+int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
+{
+    if (c.stride != 1 || d.Ci * elem_bytes(d.dt) % 64 || d.Co % 16) return 0;
+    DeviceInfo dev;
+    if (current_device(&dev)) return 0;
+    const int64_t cus = dev.cus;
+    const int stages = stage_count(d);
+    const auto groups = [&](int tn) {
+        return (int64_t)((c.W + kCols - 1) / kCols) * ((c.H + 4 * tn - 1) / (4 * tn)) * ((d.Co + 63) / 64) * c.N;
+    };
+    if (d.dt == RTOSS_F32) {
+        // matrix-bound: what counts is the rows per compute unit.  Below one 64-channel x 16x16 tile per compute unit the
+        // dense-mode kernel's small tiles win; above, its 16 rows win ties.
+        const int64_t tiles = (int64_t)((c.H + 15) / 16) * ((c.W + 15) / 16) * ((d.Co + 63) / 64) * c.N;
+        if (tiles < cus) return 0;
+        int best = 0;
+        int64_t rows = (tiles + cus - 1) / cus * 4;
+        for (int tn = 5; tn >= 2; --tn) {
+            const int64_t r = (groups(tn) + cus - 1) / cus * tn;
+            if (r < rows) best = tn, rows = r;
+        }
+        return best;
+    }
+    // shallow narrow launches of the dense mode: its own 16-channel tiles
+    if (layout == kDenseTaps && groups(2) <= cus / 2) return 0;
+    if (stages == 1) return groups(2) <= 4 * cus ? 2 : 0;  // (nothing to fetch ahead: four workgroups per compute unit)
+    if (groups(2) <= 2 * cus) {
+        if (layout == 0 && groups(2) > cus && groups(3) <= cus) return 3 + kTwoBuffers;
+        return layout != kDenseTaps || groups(2) <= cus ? 2 + kTwoBuffers : 2;  // (dense mode: two buffers fit once)
+    }
+    if (groups(3) <= 2 * cus) return layout == 0 ? 3 + kTwoBuffers : 3;
+    if (groups(4) <= 2 * cus) return 4;
+    if (layout == 0) return 0;  // several rounds: the single-buffered kernel's four workgroups per compute unit
+    // several rounds: the height that pads the image least, the taller one on a tie
+    return (c.H + 19) / 20 * 20 <= (c.H + 15) / 16 * 16 || groups(5) <= 2 * cus ? 5 : 4;
+}
+
+rtoss_status launch_conv3x3_strip(const rtoss_wdesc& d, const ConvParams& c, int layout, int plan, const void* section, const void* zeros,
+                                  const void* x, void* y, hipStream_t s)
+{
+    const char *wf = (const char*)section, *z = (const char*)zeros;
+    if (layout == kDenseTaps) return launch_layout<kDenseTaps>(d, c, plan, wf, z, x, y, s);
+    return layout == 1 ? launch_layout<1>(d, c, plan, wf, z, x, y, s) : launch_layout<0>(d, c, plan, wf, z, x, y, s);
+}
+
+}  // namespace rtoss

@@ -111,6 +111,21 @@ template <> struct Dense16<float> {
     }
 };
 
+// Sparse step D = A * B + C, A 2-of-4 sparse (v_smfmac_f32_16x16x64), scheduled by the compiler like Dense16.
+template <typename T> struct Sparse64;
+template <> struct Sparse64<f16_t> {
+    template <int ABID> static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x8 b, f32x4 c, int idx)
+    {
+        return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h16, b), c, idx, 0, ABID);
+    }
+};
+template <> struct Sparse64<bf16_t> {
+    template <int ABID> static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x8 b, f32x4 c, int idx)
+    {
+        return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b16, b), c, idx, 0, ABID);
+    }
+};
+
 // One 16-byte global -> LDS copy per lane without passing through registers: lane i of the
 // wave writes LDS address lds_wave_base + 16 * i (the base must be wave-uniform).
 __device__ __forceinline__ void copy16_to_lds(const void* gsrc, char* lds_wave_base)
