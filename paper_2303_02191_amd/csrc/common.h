@@ -152,6 +152,12 @@ size_t stream1x1_section_bytes(const rtoss_wdesc& d);
 rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                    hipStream_t s);
 
+// ... launches too small for it: input channels split over the waves of a workgroup (conv1x1_ksplit.hip); same packed section.
+// ksplit1x1_plan: variant to launch, 0 = the streaming kernel serves the launch better.
+int ksplit1x1_plan(const rtoss_wdesc& d, const ConvParams& c);
+rtoss_status launch_conv1x1_ksplit(const rtoss_wdesc& d, const ConvParams& c, int plan, const void* section, const void* x, void* y,
+                                   hipStream_t s);
+
 // 3x3 convolution with <= 3 input channels (conv3x3_stem.hip)
 bool stem3x3_shape_ok(const rtoss_wdesc& d);
 size_t stem3x3_section_bytes(const rtoss_wdesc& d);

@@ -339,6 +339,7 @@ rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, co
 {
     const char* wf = (const char*)section;
     const bool f32out = c.out_dt == RTOSS_F32;
+    if (const int plan = ksplit1x1_plan(d, c)) return launch_conv1x1_ksplit(d, c, plan, section, x, y, s);
     if (d.dt == RTOSS_F32) return launch_typed<float, float>(d, c, wf, x, y, s);
     if (d.dt == RTOSS_F16)
         return f32out ? launch_typed<f16_t, float>(d, c, wf, x, y, s) : launch_typed<f16_t, f16_t>(d, c, wf, x, y, s);
