@@ -156,7 +156,7 @@ def build_host(verbose=True):
     for d in [*cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", d]
     cmd += ["-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "host_ext.cpp"), "-o", tmp, "-L", HERE,
-            "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lrtoss", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip",
+            "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lrtoss", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip",
             "-Wl,-rpath,$ORIGIN"]
     if verbose:
         print("g++ host_ext.cpp -> _host.so", flush=True)

@@ -119,17 +119,22 @@ static rtoss_status load_dict(const uint16_t* masks_host, int P, Dict* out)
     if (!masks_host) return fail(RTOSS_EINVAL, "dictionary pointer is NULL");
     if (P < 1 || P > kMaxPatterns) return fail(RTOSS_EINVAL, "dictionary size P=%d outside 1..%d", P, kMaxPatterns);
     std::memset(out, 0, sizeof *out);
-    const int k = __builtin_popcount(masks_host[0]);
+    const auto taps = [](unsigned m) {  // (no population count instruction on the baseline host target)
+        int n = 0;
+        for (; m; m &= m - 1) ++n;
+        return n;
+    };
+    const int k = taps(masks_host[0]);
     for (int p = 0; p < P; ++p) {
         const unsigned m = masks_host[p];
         if (m == 0 || m > 0x1ffu) return fail(RTOSS_EINVAL, "pattern %d (0x%x) is not a non-empty 9-bit mask", p, m);
-        if (__builtin_popcount(m) != k)
-            return fail(RTOSS_EINVAL, "pattern %d keeps %d taps but pattern 0 keeps %d: one k per dictionary", p,
-                        __builtin_popcount(m), k);
+        if (taps(m) != k)
+            return fail(RTOSS_EINVAL, "pattern %d keeps %d taps but pattern 0 keeps %d: one k per dictionary", p, taps(m), k);
         out->mask[p] = (uint16_t)m;
     }
     out->P = P;
     out->k = k;
+    out->layout = sparse3x3_layout(out->mask, P);
     return RTOSS_OK;
 }
 
@@ -162,10 +167,10 @@ rtoss_status blob_geometry(const rtoss_wdesc* d, const Dict& dict, BlobGeometry*
         g->mat_off = end;
         g->mat_bytes = gather3x3_section_bytes(*d);
         end = align_up(end + g->mat_bytes, 256);
-    } else if (sparse3x3_shape_ok(*d) && sparse3x3_layout(dict) >= 0) {
+    } else if (sparse3x3_shape_ok(*d) && dict.layout >= 0) {
         g->format = kFormatSparse24;
         g->mat_off = end;
-        g->mat_bytes = sparse3x3_section_bytes(*d, sparse3x3_layout(dict));
+        g->mat_bytes = sparse3x3_section_bytes(*d, dict.layout);
         end = align_up(end + g->mat_bytes, 256);
     } else if (stem3x3_shape_ok(*d)) {
         g->format = kFormatStem;
@@ -428,7 +433,7 @@ static rtoss_status conv_impl(const rtoss_wdesc* desc, const rtoss_cdesc* c, con
         return launch_conv_direct(*desc, cp, dict, blob + g.live_off, (const uint8_t*)(blob + g.idx_off), x_dev, y_dev,
                                   (hipStream_t)hip_stream);
     if (g.format == kFormatSparse24)
-        return launch_conv3x3_sparse(*desc, cp, sparse3x3_layout(dict), blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
+        return launch_conv3x3_sparse(*desc, cp, dict.layout, blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
     if (g.format == kFormatStem)
         return launch_conv3x3_stem(*desc, cp, blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
     if (g.format == kFormatDense3x3)

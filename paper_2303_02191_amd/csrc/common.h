@@ -21,6 +21,7 @@ struct Dict {
     uint16_t mask[256];
     int P;
     int k;
+    int layout;  // tap layout of the 2-of-4 fragments (sparse_frag.h) that fits every pattern, cheapest first; -1: none
 };
 
 // Decoded dictionary for the convolution kernels: tap[p][j] = j-th live tap of pattern p
@@ -100,8 +101,7 @@ struct PackItem {
 rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, const Dict& dict, hipStream_t s);
 
 // 3x3 convolution on the sparse matrix instruction (conv3x3_sparse.hip)
-// which tap layout (sparse_frag.h) fits every pattern of the dictionary, cheapest first; -1: none
-int sparse3x3_layout(const Dict& dict);
+int sparse3x3_layout(const uint16_t* masks, int P);  // Dict::layout
 bool sparse3x3_shape_ok(const rtoss_wdesc& d);
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout);
 rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, int layout, const void* section, const void* x,

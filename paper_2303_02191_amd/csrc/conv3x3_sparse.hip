@@ -439,7 +439,7 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 
 // ---- host-visible entry points of this file ----
 
-int sparse3x3_layout(const Dict& dict)
+int sparse3x3_layout(const uint16_t* masks, int P)
 {
     for (int l = 0; l < kNumLayouts; ++l) {
         bool fits = true;
@@ -447,7 +447,13 @@ int sparse3x3_layout(const Dict& dict)
             unsigned set = 0;
             for (int f = 0; f < 4; ++f)
                 if (kLayouts[l].tap[g][f] >= 0) set |= 1u << kLayouts[l].tap[g][f];
-            for (int p = 0; p < dict.P && fits; ++p) fits = __builtin_popcount(dict.mask[p] & set) <= 2;
+            unsigned third = 0;  // non-zero once a pattern has three live taps in the set
+            for (int p = 0; p < P; ++p) {
+                unsigned m = masks[p] & set;
+                m &= m - 1;
+                third |= m & (m - 1);
+            }
+            fits = third == 0;
         }
         if (fits) return l;
     }

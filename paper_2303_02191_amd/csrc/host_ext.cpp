@@ -6,9 +6,8 @@
 // layer by layer waited for the host.  Here the same work is one call; the launch itself is most of what is left.
 #include <Python.h>
 
-#include <ATen/ops/empty.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/zeros.h>
-#include <c10/core/InferenceMode.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -98,11 +97,10 @@ void* stream_arg(PyObject* o)
     if (!s && PyErr_Occurred()) throw PyError{};
     return s;
 }
-// outputs carry no gradient: skip the autograd layers of the dispatcher
+// The device's own allocation function, at the end of at::empty's dispatch (which costs 0.5 us of a 4 us call).
 at::Tensor allocate(at::IntArrayRef shape, at::ScalarType st, const at::Device& dev)
 {
-    at::AutoDispatchBelowADInplaceOrView below;
-    return at::empty(shape, at::TensorOptions().dtype(st).device(dev));
+    return at::Tensor(at::detail::empty_cuda(shape, st, dev, std::nullopt));
 }
 
 // a dictionary: one-dimensional contiguous array of uint16

@@ -419,7 +419,7 @@ rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, P
 
 rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, const Dict& dict, hipStream_t s)
 {
-    const int layout = std::max(0, sparse3x3_layout(dict));
+    const int layout = std::max(0, dict.layout);
     for (int dt : {(int)RTOSS_F32, (int)RTOSS_F16, (int)RTOSS_BF16})
         for (int i = 0; i < n;) {  // i runs on across launches
             PackTable tab;
