@@ -274,33 +274,47 @@ __global__ __launch_bounds__(256) void conv3x3_gather_kernel(const T* __restrict
 // counts in its blocks or stages (patterns that are not shared after all), takes the general body: weight
 // fragments from global memory, slowly but correctly.
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kGrSteps = 5;
 constexpr int kGrWaves = 8;                           // two per SIMD: wave = (row group, block of the pair)
-constexpr int kGrABytes = kGrSteps * 2 * kStepBytes;  // [step][block of the pair][fragment]: 40 KB
 constexpr int kGrXChunks = (4 * kTall + 2) * kLW * 4;
-constexpr int kGrXPerWave = ((kGrXChunks + 63) / 64 + kGrWaves - 1) / kGrWaves;
-constexpr int kGrXArea = kGrXPerWave * kGrWaves * 1024;
-constexpr int kGrRegion = kGrABytes + kGrXArea;
-constexpr int kGrAPerWave = kGrABytes / 1024 / kGrWaves;
-constexpr int kGrCopySlots = kGrAPerWave + kGrXPerWave;
+constexpr int kGrXCopies = (kGrXChunks + 63) / 64;    // copy instructions (64 lanes x 16 B) that hold part of the tile
+constexpr int kGrXPerWave = (kGrXCopies + kGrWaves - 1) / kGrWaves;
+constexpr int kGrXArea = (kGrXCopies + 1) * 1024;     // ... and one for the copies past it, which all land there
 constexpr int kGrOffPitch = 8;  // int16 entries per (stage, block, quarter): steps 0..7, one 16-byte read
-constexpr size_t kGrSmem = 2 * (size_t)kGrRegion + kMaxStages * 4 + (size_t)kMaxStages * 2 * 4 * kGrOffPitch * 2;
-static_assert(kGrABytes / 1024 == kGrAPerWave * kGrWaves, "every wave issues the same number of weight copies");
+constexpr size_t kGrTables = kMaxStages * 4 + (size_t)kMaxStages * 2 * 4 * kGrOffPitch * 2;
 static_assert(kMaxStages * 8 <= 64 * kGrWaves, "one table entry per thread");
+
+// How LDS is cut into regions of one stage each.  CAP: steps whose weight fragments a region holds.
+// With up to three steps per stage a stage is 1.9 k cycles of matrix work, less than a copy takes to arrive (1 us and
+// more with all compute units copying), and 50 KB: three regions fit, and copies are issued two stages ahead.
+// 256 -> 256 at 100x168, batch 4, three shared taps: 32.8 us with two regions of five steps, 30.9 us with three of three.
+// What is left: an operand read (8 cycles of the compute unit's LDS) per two matrix instructions, so that LDS is as busy as
+// the matrix cores.
+template <int CAP> struct GrRegions {
+    static constexpr int A_BYTES = CAP * 2 * kStepBytes;  // [step][block of the pair][fragment]
+    static constexpr int REGION = A_BYTES + kGrXArea;
+    static constexpr int RING = CAP <= 3 ? 3 : 2;
+    static constexpr int A_PER_WAVE = A_BYTES / 1024 / kGrWaves;
+    static constexpr int COPY_SLOTS = A_PER_WAVE + kGrXPerWave;
+    static constexpr size_t SMEM = (size_t)RING * REGION + kGrTables;
+    static_assert(A_BYTES / 1024 == A_PER_WAVE * kGrWaves, "every wave issues the same number of weight copies");
+    static_assert(SMEM <= 160 * 1024, "a compute unit's LDS");
+};
+constexpr int kGrFew = 3, kGrSteps = 5;  // the two values of CAP
+constexpr size_t kGrSmem = GrRegions<kGrFew>::SMEM > GrRegions<kGrSteps>::SMEM ? GrRegions<kGrFew>::SMEM : GrRegions<kGrSteps>::SMEM;
 
 __device__ __forceinline__ int pair_block(int cb0, int half, int cblocks) { return cb0 + (half && cb0 + 1 < cblocks ? 1 : 0); }
 
-template <typename T, typename TO>
-__global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(const T* __restrict__ x, TO* __restrict__ y,
-                                                                                const GatherHeader* __restrict__ headers,
-                                                                                const char* __restrict__ wfrag,
-                                                                                const char* __restrict__ zeros, int H, int W,
-                                                                                int Ci, int Co, int cblocks, RowPlan plan,
-                                                                                float relu_floor, int ldy)
+template <typename T, typename TO, int CAP>
+__device__ __forceinline__ void gather_rows_body(char* smem, const T* __restrict__ x, TO* __restrict__ y,
+                                                 const GatherHeader* __restrict__ headers, const char* __restrict__ wfrag,
+                                                 const char* __restrict__ zeros, int H, int W, int Ci, int Co, int cblocks,
+                                                 RowPlan plan, float relu_floor, int ldy)
 {
     static_assert(sizeof(TO) == 2, "direct epilogue: 16-bit output");
-    extern __shared__ __attribute__((aligned(16))) char smem[];  // two regions, then the tile's step counts and tap offsets
-    int* lds_steps = (int*)(smem + 2 * kGrRegion);               // [stage]: steps of block 0 | steps of block 1 << 8
+    using RG = GrRegions<CAP>;
+    constexpr int RING = RG::RING, AHEAD = RING - 1;  // stages between the one copied and the one multiplied
+    constexpr int kGrCopySlots = RG::COPY_SLOTS, kGrAPerWave = RG::A_PER_WAVE;
+    int* lds_steps = (int*)(smem + RING * RG::REGION);           // [stage]: steps of block 0 | steps of block 1 << 8
     int16_t* lds_off = (int16_t*)(lds_steps + kMaxStages);       // [stage][block][quarter][kGrOffPitch]
 
     const int tid = threadIdx.x;
@@ -361,18 +375,19 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
     };
     // One copy instruction (64 lanes x 16 bytes) of stage `stage` of the copy state's tile into region `par`: slots
     // 0 .. kGrAPerWave-1 move weight fragments (a_src: this wave's block's fragments of that stage), the rest activations.
-    auto issue_copy_slot = [&](int cslot, int stage, int par, const char* a_src) {
+    auto issue_copy_slot = [&](int cslot, int stage, int reg, const char* a_src) {
         // (the LDS address of a copy travels in a scalar register: keep the region's offset scalar)
-        char* region = smem + __builtin_amdgcn_readfirstlane(par * kGrRegion);
+        char* region = smem + __builtin_amdgcn_readfirstlane(reg * RG::REGION);
         if (cslot < kGrAPerWave) {
             // piece 8 * cslot + wave of the region is (step, block, fragment) = (cslot, wave / 4, wave % 4).  All
-            // kGrSteps steps are copied whatever the stage's own count (what lies behind a block's last step in the
+            // CAP steps are copied whatever the stage's own count (what lies behind a block's last step in the
             // blob is never multiplied): a count would put a branch around every copy, and branches between the
             // matrix instructions cost more than the surplus copies.
             copy16_to_lds(a_src + (cslot * kTM + vrow) * kFrag, region + (cslot * kGrWaves + wave) * 1024);
         } else {
             const int k = cslot - kGrAPerWave;
-            copy16_to_lds(x_ptr[k] + stage * 64, region + kGrABytes + (k * kGrWaves + wave) * 1024);
+            const int piece = min(k * kGrWaves + wave, kGrXCopies);  // (past the tile: the spare kilobyte behind it)
+            copy16_to_lds(x_ptr[k] + stage * 64, region + RG::A_BYTES + piece * 1024);
         }
     };
     // this wave's share of the weight fragments of stage `stage` of the copy state's tile: fragment wave % 4 of its
@@ -384,7 +399,10 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
     const int nn = lane & 15, qq = lane >> 4;
     f32x4 acc[kTM][kTall];
     u32x4 a_op[kTM], b_op[kTall];  // operands of the step being multiplied (the partner wave on the SIMD covers their latency)
-    int gpar = 0;                        // region that holds the stage about to be multiplied
+    int here = 0;                        // region that holds the stage about to be multiplied
+    // the region AHEAD stages on (the one multiplied last), and the next one
+    auto region_ahead = [&]() { return here == 0 ? RING - 1 : here - 1; };
+    auto region_next = [&]() { return here + 1 == RING ? 0 : here + 1; };
 
     // A tile's table entries (stage, block of the pair, quarter): the offsets in the activation tile of the taps of
     // steps 0..7, and per stage the two step counts.  A thread fetches one entry from the headers in global memory
@@ -445,10 +463,10 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
             return (int)((pk[st >> 1] >> ((st & 1) * 16)) & 0xffffu);
         };
         // operands of a step: the block's four weight fragments and, per output row, this quarter's tap
-        auto load_operands = [&](int par, int st, int off, u32x4 (&a)[kTM], u32x4 (&b)[kTall]) {
-            const int region = __builtin_amdgcn_readfirstlane(par * kGrRegion);
+        auto load_operands = [&](int reg, int st, int off, u32x4 (&a)[kTM], u32x4 (&b)[kTall]) {
+            const int region = __builtin_amdgcn_readfirstlane(reg * RG::REGION);
             const char* A = smem + region + lane * 16 + ((st * 2) * kTM) * kFrag + hsel * (kTM * kFrag);
-            const char* X = smem + region + kGrABytes + xrd + off;
+            const char* X = smem + region + RG::A_BYTES + xrd + off;
 #pragma unroll
             for (int m = 0; m < kTM; ++m) a[m] = *(const u32x4*)(A + m * kFrag);
 #pragma unroll
@@ -456,23 +474,25 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
         };
         u32x4 off_cur = load_offsets(0), off_nxt = off_cur;
 
-        auto run_stage = [&](auto first_tag, auto last_tag, auto body_tag, int stage) {
-            constexpr bool FIRST = decltype(first_tag)::value, LAST = decltype(last_tag)::value;
+        // LEFT: stages left in the tile after this one, or AHEAD for more than that
+        auto run_stage = [&](auto first_tag, auto left_tag, auto body_tag, int stage) {
+            constexpr bool FIRST = decltype(first_tag)::value;
+            constexpr int LEFT = decltype(left_tag)::value;
+            constexpr bool LAST = LEFT == 0, SWITCH = LEFT == AHEAD - 1;  // SWITCH: the copies move on to the next tile
             constexpr int BODY = decltype(body_tag)::value;  // steps of the branch-free body, 0: the general body
             // bodies of two steps or more work the next tile's activation sources out between their matrix instructions
-            constexpr bool SPREAD_SOURCES = LAST && BODY > 1;
+            constexpr bool SPREAD_SOURCES = SWITCH && BODY > 1;
             const int st = __builtin_amdgcn_readfirstlane(lds_steps[stage]);
             const int my_steps = hsel ? st >> 8 : st & 0xff, steps = max(st & 0xff, st >> 8);
-            const int copy_stage = LAST ? 0 : stage + 1;
-            // (in the very last stage of the last tile nothing is left to fetch; `nxt` is the same tile then and its
-            // stage 0 is fetched again into the free region, which keeps this code free of branches)
-            if constexpr (LAST) {
+            const int copy_stage = LEFT >= AHEAD ? stage + AHEAD : AHEAD - 1 - LEFT;
+            // (in the very last stages of the last tile nothing is left to fetch; `nxt` is the same tile then and its
+            // first stages are fetched again into free regions, which keeps this code free of branches)
+            if constexpr (SWITCH) {
                 c_cb0 = nxt.mt0 / kTM;
-                prefetch_headers(nxt.mt0 / kTM);
                 if constexpr (!SPREAD_SOURCES) setup_tile_sources(nxt, nxt_in_rows);
-            } else {
-                off_nxt = load_offsets(stage + 1);
             }
+            if constexpr (LAST) prefetch_headers(nxt.mt0 / kTM);
+            else off_nxt = load_offsets(stage + 1);
             const char* const a_src = weight_source(copy_stage);
             auto multiply = [&](auto first_step_tag, const u32x4 (&a)[kTM], const u32x4 (&b)[kTall], auto&& between) {
                 static_for<kTM * TN>([&](auto I) {
@@ -483,15 +503,17 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
                     __builtin_amdgcn_sched_barrier(0);
                 });
             };
-            // Stage hand-over: every copy of the next stage issued, this wave's landed and its reads of this region
-            // done, a bare barrier.
+            // Stage hand-over: every copy this stage has to issue issued, this wave's copies of the next stage landed
+            // (all but those just issued, where copies run two stages ahead) and its reads of this region done, a bare
+            // barrier.
             auto hand_over = [&](int first_unissued) {
                 static_for<kGrCopySlots>([&](auto C) {
                     constexpr int c = decltype(C)::value;
-                    if (c >= first_unissued) issue_copy_slot(c, copy_stage, gpar ^ 1, a_src);
+                    if (c >= first_unissued) issue_copy_slot(c, copy_stage, region_ahead(), a_src);
                 });
                 asm volatile("" ::: "memory");
-                __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+                static_assert((AHEAD - 1) * kGrCopySlots < 16, "the low bits of the counter");
+                __builtin_amdgcn_s_waitcnt(0x0070 | (AHEAD - 1) * kGrCopySlots);  // vmcnt, and lgkmcnt(0)
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             };
@@ -509,7 +531,7 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
                     constexpr int s = decltype(S)::value;
                     constexpr int c0 = (s < CS ? s : CS) * kGrCopySlots / CS, c1 = (s + 1 < CS ? s + 1 : CS) * kGrCopySlots / CS;
                     constexpr int n = STEPS > 1 ? c1 - c0 : 0, total = kTM * TN;
-                    load_operands(gpar, s, offset_of(off_cur, s), a_op, b_op);
+                    load_operands(here, s, offset_of(off_cur, s), a_op, b_op);
                     if constexpr (s + 1 == STEPS) hand_over(STEPS > 1 ? kGrCopySlots : 0);
                     multiply(std::integral_constant<bool, FIRST && s == 0>{}, a_op, b_op, [&](auto I) {
                         constexpr int i = decltype(I)::value;
@@ -527,7 +549,7 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
                         if constexpr (s + 1 < STEPS) {
                             static_for<(n > 0 ? n : 0)>([&](auto K) {
                                 constexpr int k = decltype(K)::value;
-                                if constexpr (i == k * total / (n > 0 ? n : 1)) issue_copy_slot(c0 + k, copy_stage, gpar ^ 1, a_src);
+                                if constexpr (i == k * total / (n > 0 ? n : 1)) issue_copy_slot(c0 + k, copy_stage, region_ahead(), a_src);
                             });
                         }
                     });
@@ -539,8 +561,8 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
             // of them the region holds) and the matrix instructions unconditional: a block that has no step s
             // multiplies by zero, which keeps the accumulators out of every branch.
             auto generic_body = [&]() {
-                static_for<kGrCopySlots>([&](auto C) { issue_copy_slot(decltype(C)::value, copy_stage, gpar ^ 1, a_src); });
-                const char* X = smem + __builtin_amdgcn_readfirstlane(gpar * kGrRegion) + kGrABytes + xrd;
+                static_for<kGrCopySlots>([&](auto C) { issue_copy_slot(decltype(C)::value, copy_stage, region_ahead(), a_src); });
+                const char* X = smem + __builtin_amdgcn_readfirstlane(here * RG::REGION) + RG::A_BYTES + xrd;
                 const int cb = pair_block(cb0, hsel, cblocks);
                 auto step = [&](auto first_step_tag, int st_i) {
                     const char* Ag = wfrag + ((int64_t)stage * cblocks + cb) * kBlockBytes + (st_i * kTM) * kFrag + lane * 16;
@@ -569,16 +591,18 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
             if constexpr (BODY > 0) static_body(body_tag);
             else generic_body();
             off_cur = off_nxt;
-            gpar ^= 1;
+            here = region_next();
         };
 
         // One path per tile: the stages and the epilogue for a given body.  (Choosing the body per stage would join
         // the paths while the accumulators are live; the compiler then moves accumulators between the registers the
         // paths happen to use, right behind matrix instructions whose latency it does not know.)
         auto tile_path = [&](auto body_tag) {
-            run_stage(std::true_type{}, std::false_type{}, body_tag, 0);  // (the launcher admits Ci >= 96: three stages or more)
-            for (int stage = 1; stage + 1 < stages; ++stage) run_stage(std::false_type{}, std::false_type{}, body_tag, stage);
-            run_stage(std::false_type{}, std::true_type{}, body_tag, stages - 1);
+            using std::integral_constant;
+            run_stage(std::true_type{}, integral_constant<int, AHEAD>{}, body_tag, 0);  // (the launcher admits Ci >= 96: three stages or more)
+            for (int stage = 1; stage + AHEAD < stages; ++stage) run_stage(std::false_type{}, integral_constant<int, AHEAD>{}, body_tag, stage);
+            if constexpr (AHEAD == 2) run_stage(std::false_type{}, integral_constant<int, 1>{}, body_tag, stages - 2);
+            run_stage(std::false_type{}, integral_constant<int, 0>{}, body_tag, stages - 1);
 
             // the last matrix instructions must have written their accumulators before anything reads them
             asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
@@ -621,8 +645,18 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
         case 1: tile_path(std::integral_constant<int, 1>{}); break;
         case 2: tile_path(std::integral_constant<int, 2>{}); break;
         case 3: tile_path(std::integral_constant<int, 3>{}); break;
-        case 4: tile_path(std::integral_constant<int, 4>{}); break;
-        case 5: tile_path(std::integral_constant<int, 5>{}); break;
+        case 4:
+            if constexpr (CAP >= 4) {
+                tile_path(std::integral_constant<int, 4>{});
+                break;
+            }
+            [[fallthrough]];
+        case 5:
+            if constexpr (CAP >= 5) {
+                tile_path(std::integral_constant<int, 5>{});
+                break;
+            }
+            [[fallthrough]];
         default: tile_path(std::integral_constant<int, 0>{}); break;
         }
     };
@@ -635,10 +669,11 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
     prefetch_headers(cur.mt0 / kTM);
     c_cb0 = cur.mt0 / kTM;
     setup_tile_sources(cur, cur_tall ? 4 * kTall + 2 : 4 * kShort + 2);
-    {
-        const char* const a_src = weight_source(0);
 #pragma unroll
-        for (int c = 0; c < kGrCopySlots; ++c) issue_copy_slot(c, 0, 0, a_src);
+    for (int ahead = 0; ahead < AHEAD; ++ahead) {
+        const char* const a_src = weight_source(ahead);
+#pragma unroll
+        for (int c = 0; c < kGrCopySlots; ++c) issue_copy_slot(c, ahead, ahead, a_src);
     }
     bool first_tile = true;
     for (;;) {
@@ -651,8 +686,12 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
             else short_next += slots;
         }
         if (first_tile) {
-            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies have landed in LDS
-            __syncthreads();                     // ... and everybody's
+            // this wave's copies of stage 0 have landed in LDS, and everybody's (a bare barrier: a fence would wait for
+            // the stage behind it, too; store_headers is followed by a full one)
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0x0f70 | (AHEAD - 1) * kGrCopySlots);
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
             first_tile = false;
         }
         if (cur_tall) run_tile(std::integral_constant<int, kTall>{}, cur, has_next, nxt, nxt_tall);
@@ -661,6 +700,30 @@ __global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(c
         cur = nxt;
         cur_tall = nxt_tall;
     }
+    // copies still on their way must not land in LDS that is someone else's by then
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+}
+
+// few: the dictionary keeps at most kGrFew taps, so that shared patterns give at most kGrFew steps.  Whether they do is
+// the packer's finding: every workgroup looks at the step counts of the whole layer first (one load per thread).
+template <typename T, typename TO>
+__global__ __launch_bounds__(64 * kGrWaves, 1) void conv3x3_gather_rows_kernel(const T* __restrict__ x, TO* __restrict__ y,
+                                                                                const GatherHeader* __restrict__ headers,
+                                                                                const char* __restrict__ wfrag,
+                                                                                const char* __restrict__ zeros, int H, int W,
+                                                                                int Ci, int Co, int cblocks, RowPlan plan,
+                                                                                float relu_floor, int ldy, bool few)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];  // regions, then the tile's step counts and tap offsets
+    if (few) {
+        bool more = false;
+        for (int i = threadIdx.x; i < Ci / 32 * cblocks; i += 64 * kGrWaves) more |= headers[i].steps > kGrFew;
+        if (!__syncthreads_or(more)) {
+            gather_rows_body<T, TO, kGrFew>(smem, x, y, headers, wfrag, zeros, H, W, Ci, Co, cblocks, plan, relu_floor, ldy);
+            return;
+        }
+    }
+    gather_rows_body<T, TO, kGrSteps>(smem, x, y, headers, wfrag, zeros, H, W, Ci, Co, cblocks, plan, relu_floor, ldy);
 }
 
 template <typename T, typename TO, int S>
@@ -712,7 +775,7 @@ rtoss_status launch_gather_rows(const rtoss_wdesc& d, const ConvParams& c, const
     const float relu_floor = c.ep.act == 1 ? 0.f : -__builtin_inff();
     dim3 grid((unsigned)(slots * 8)), block(64 * kGrWaves);
     kern<<<grid, block, kGrSmem, s>>>((const T*)x, (T*)y, (const GatherHeader*)section, frags, frags + frag_bytes(d), c.H, c.W, d.Ci,
-                                      d.Co, channel_blocks(d.Co), plan, relu_floor, c.ep.ldy);
+                                      d.Co, channel_blocks(d.Co), plan, relu_floor, c.ep.ldy, d.k <= kGrFew);
     return check_hip(hipGetLastError(), "conv3x3 gather rows launch");
 }
 
