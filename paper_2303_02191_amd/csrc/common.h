@@ -117,6 +117,9 @@ rtoss_status launch_conv3x3_rows(const rtoss_wdesc& d, const ConvParams& c, cons
 int ksplit3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout);
 rtoss_status launch_conv3x3_ksplit(const rtoss_wdesc& d, const ConvParams& c, int layout, int plan, const void* section, const void* zeros,
                                    const void* x, void* y, hipStream_t s);
+// the same for the section of conv3x3_gather.hip (layout 3)
+rtoss_status launch_conv3x3_ksplit_gather(const rtoss_wdesc& d, const ConvParams& c, int plan, const void* headers, const void* frags,
+                                          const void* zeros, const void* x, void* y, hipStream_t s);
 
 // ... stride 1, launches of medium size: strips of output rows (conv3x3_strip.hip); same sections and layouts.
 // strip3x3_plan: variant to launch, 0 = another kernel serves the launch better.

@@ -1,6 +1,7 @@
 // 3x3 pattern-pruned convolution on the CDNA4 matrix cores for launches that cannot fill the chip with work: the
-// input channels are split over the waves of a workgroup.  Reads the packed sections of sparse_frag.h (2-of-4 steps) and
-// of the dense-mode kernel (one step per tap: 16-bit dictionaries without a 2-of-4 shape, and fp32).
+// input channels are split over the waves of a workgroup.  Reads the packed sections of sparse_frag.h (2-of-4 steps), of
+// the dense-mode kernel (one step per tap: 16-bit dictionaries without a 2-of-4 shape, and fp32) and of the gather
+// kernel (one step per tap that a block of kernels keeps).
 //
 // What bounds such a launch (a 20x20 or 40x40 image, one frame, a small pyramid level) is not a rate but a chain of
 // latencies: the single-buffered kernel walks the stages of 32 input channels one after the other, and each stage is
@@ -34,8 +35,10 @@ namespace rtoss {
 namespace {
 
 // How a stage of one channel tile is multiplied: the tap layouts of sparse_frag.h, or one dense step per tap.
-constexpr int kDenseTaps = 2;
-constexpr int steps_tile_bytes(int lay) { return lay == kDenseTaps ? 9 * kFragBytes : layout_tile_bytes(kLayouts[lay]); }
+// (kGathered: one dense step per tap that any kernel of the block keeps, conv3x3_gather.hip.)
+constexpr int kDenseTaps = 2, kGathered = 3;
+constexpr int kGatherSteps = 3;  // steps of a gathered stage in LDS at a time
+constexpr int steps_tile_bytes(int lay) { return lay == kGathered ? kGatherSteps * kFragBytes : lay == kDenseTaps ? 9 * kFragBytes : layout_tile_bytes(kLayouts[lay]); }
 
 // Channel tiles that hold rows of the layer: 64 channels are dealt over the rows of four tiles (tile_row_channel).
 inline int channel_tiles(int Co) { return 4 * ((Co + 63) / 64); }
@@ -47,8 +50,9 @@ template <int S, int TM, int RT, int CT, int LAY> struct KSplit {
     static constexpr int TILE = steps_tile_bytes(LAY);
     static constexpr int A_BYTES = TM * TILE;
     static constexpr int A_COPIES = (A_BYTES + 1023) / 1024;  // 64 lanes x 16 bytes each
+    static constexpr int H_COPIES = LAY == kGathered;         // the block's step count and tap lists
     static constexpr int X_COPIES = (G::x_bytes + 1023) / 1024;
-    static constexpr int COPIES = A_COPIES + X_COPIES;
+    static constexpr int COPIES = A_COPIES + X_COPIES + H_COPIES;
     static constexpr int SLOT = COPIES * 1024;                // one stage
     static constexpr int LDS = 4 * SLOT;
     static constexpr int MPT = TM * TN >= 4 ? TM * TN / 4 : 1;  // channel tiles whose outputs one lane stores
@@ -62,11 +66,12 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
                                                              const char* __restrict__ wfrag, const char* __restrict__ zeros,
                                                              int H, int W, int Ci, int Co, int Ho, int Wo, int m_tiles_total,
                                                              int tiles_c, int tiles_per_image, int co_blocks, int total,
-                                                             int work_per_xcd, Epilogue ep)
+                                                             int work_per_xcd, const char* __restrict__ headers,
+                                                             Epilogue ep)
 {
     using K = KSplit<S, TM, RT, CT, LAY>;
     using G = typename K::G;
-    constexpr TapLayout LY = kLayouts[LAY == kDenseTaps ? 0 : LAY];
+    constexpr TapLayout LY = kLayouts[LAY >= kDenseTaps ? 0 : LAY];
     constexpr int NG = LY.groups, FR = layout_fragments(LY), TN = K::TN;
     constexpr int PER = 16 / (int)sizeof(T);  // channels in a lane's 16 bytes; a stage is four of them
     extern __shared__ __attribute__((aligned(16))) char smem[];  // [wave][weights | activations]; at the end the partial sums
@@ -85,10 +90,25 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
     char* mine = smem + wave * K::SLOT;
 
     // ---- this wave's copies ----
-    const char* a_src = wfrag + (int64_t)mt0 * K::TILE + lane * 16;
-    const int64_t a_stage_stride = (int64_t)m_tiles_total * K::TILE;
+    // (gathered: [stage][block of four tiles][step][tile], else [stage][tile][step])
+    constexpr int FILE_TILE = LAY == kGathered ? 9 * kFragBytes : K::TILE;
+    const char* a_src = wfrag + (LAY == kGathered ? (int64_t)(mt0 / 4) * (4 * FILE_TILE) + (mt0 % 4) * kFragBytes : (int64_t)mt0 * FILE_TILE) + lane * 16;
+    const int64_t a_stage_stride = (int64_t)m_tiles_total * FILE_TILE;
     const char* x_ptr[K::X_COPIES];
+    // gathered: the fragments of steps first .. first+kGatherSteps-1 (those past the stage's own count are not multiplied)
+    auto issue_steps = [&](int stage, char* slot, int first) {
+        const char* src = a_src + stage * a_stage_stride + first * (4 * kFragBytes);
+#pragma unroll
+        for (int st = 0; st < kGatherSteps; ++st)
+#pragma unroll
+            for (int m = 0; m < TM; ++m) copy16_to_lds(src + (4 * st + m) * kFragBytes, slot + (st * TM + m) * kFragBytes);
+    };
     auto issue_weights = [&](int stage, char* slot) {
+        if constexpr (LAY == kGathered) {
+            copy16_to_lds(headers + ((int64_t)stage * (m_tiles_total / 4) + mt0 / 4) * 64 + (lane & 3) * 16, slot + (K::A_COPIES + K::X_COPIES) * 1024);
+            issue_steps(stage, slot, 0);
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < K::A_COPIES; ++k) {
             const char* src = a_src + stage * a_stage_stride + k * 1024;
@@ -133,13 +153,43 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    auto multiply = [&](const char* slot) {
+    auto multiply = [&](char* slot, int stage) {
         const char* lds_a = slot + lane * 16;
         const char* lds_x = slot + K::A_COPIES * 1024 + xb0;
         auto x_at = [&](int j, int t) {
             return *(const u32x4*)(lds_x + ((4 * (j / CT) * S + t / 3) * G::LW + 4 * (j % CT) * S + t % 3) * G::kPos);
         };
-        if constexpr (LAY == kDenseTaps) {
+        if constexpr (LAY == kGathered) {
+            const char* hdr = slot + (K::A_COPIES + K::X_COPIES) * 1024;
+            int steps = __builtin_amdgcn_readfirstlane(*(const int*)hdr);
+            steps = steps < 0 || steps > 9 ? 9 : steps;  // (a corrupt header cannot run the loops out of bounds)
+            for (int first = 0; first < steps; first += kGatherSteps) {
+                int tap[kGatherSteps];
+#pragma unroll
+                for (int st = 0; st < kGatherSteps; ++st) tap[st] = *(const uint8_t*)(hdr + 8 + qq * 9 + first + st);
+                if (first > 0) {
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads of the steps before
+                    issue_steps(stage, slot, first);
+                    __builtin_amdgcn_s_waitcnt(0x0f70);
+                    asm volatile("" ::: "memory");
+                }
+#pragma unroll
+                for (int st = 0; st < kGatherSteps; ++st) {
+                    if (first + st >= steps) break;
+                    const int t3 = (tap[st] * 11) >> 5;  // tap / 3
+                    const char* at = lds_x + (t3 * G::LW + tap[st] - 3 * t3) * G::kPos;
+                    u32x4 b[TN];
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) b[j] = *(const u32x4*)(at + (4 * (j / CT) * S * G::LW + 4 * (j % CT) * S) * G::kPos);
+#pragma unroll
+                    for (int m = 0; m < TM; ++m) {
+                        const u32x4 a = *(const u32x4*)(lds_a + (st * TM + m) * kFragBytes);
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) acc[m][j] = Dense16<T>::mma(a, b[j], acc[m][j]);
+                    }
+                }
+            }
+        } else if constexpr (LAY == kDenseTaps) {
 #pragma unroll
             for (int t = 0; t < 9; ++t) {
                 u32x4 b[TN];
@@ -202,7 +252,7 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies have landed
         asm volatile("" ::: "memory");
-        multiply(mine);
+        multiply(mine, s);
         if (s + 4 < stages) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's reads of the slot are complete
             issue_weights(s + 4, mine);
@@ -264,7 +314,8 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
 }
 
 template <typename T, typename TO, int S, int TM, int RT, int CT, int LAY>
-rtoss_status launch_variant(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const char* zeros, const void* x, void* y, hipStream_t s)
+rtoss_status launch_variant(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const char* zeros, const void* x, void* y, hipStream_t s,
+                            const char* headers = nullptr)
 {
     using K = KSplit<S, TM, RT, CT, LAY>;
     using G = typename K::G;
@@ -280,7 +331,8 @@ rtoss_status launch_variant(const rtoss_wdesc& d, const ConvParams& c, const cha
     const int work_per_xcd = (int)((total + 7) / 8);
     dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
     kern<<<grid, block, K::LDS, s>>>((const T*)x, (TO*)y, wfrag, zeros, c.H, c.W, d.Ci, d.Co, Ho, Wo,
-                                     LAY == kDenseTaps ? channel_tiles(d.Co) : padded_m_tiles(d.Co), tiles_c, tiles_r * tiles_c, co_blocks, (int)total, work_per_xcd, c.ep);
+                                     LAY >= kDenseTaps ? channel_tiles(d.Co) : padded_m_tiles(d.Co), tiles_c, tiles_r * tiles_c, co_blocks, (int)total, work_per_xcd,
+                                     headers, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 K-split launch");
 }
 
@@ -333,6 +385,16 @@ int ksplit3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
     const auto groups = [&](int tm, int rows, int cols) {
         return (int64_t)(channel_tiles(d.Co) / tm) * ((Ho + rows - 1) / rows) * ((Wo + cols - 1) / cols) * c.N;
     };
+    if (layout == kGathered) {
+        // 48 KB of LDS with 8 rows of 4, 60 KB with 8 of 8: three and two workgroups per compute unit.  A second round
+        // is still the better choice for deep layers: the other kernel has their every stage's copy in front of it.
+        // 256 -> 256 with shared patterns of 3: 14x30 4.0 us (12.2 before), 30x40 4.9 (12.5), 60x80 9.1 (12.6), 80x100
+        // stays (13.6 against 14.3); 64 -> 64: 60x80 4.0 (6.1), 112x140 5.1 (6.3).  Independent patterns gain as much.
+        if (c.stride != 1) return kNone;
+        if (groups(1, 4, 8) <= cus) return k16x4x8;
+        if (groups(2, 4, 8) <= (stages >= 4 ? 5 : 3) * cus) return k32x4x8;
+        return groups(2, 8, 8) <= 2 * cus ? k32x8x8 : kNone;
+    }
     if (layout == kDenseTaps) {
         // the dense-mode kernel has small tiles of its own: only the depth of the layer is left to gain here
         if (stages < 4 && c.stride == 1) return kNone;
@@ -357,6 +419,23 @@ rtoss_status launch_conv3x3_ksplit(const rtoss_wdesc& d, const ConvParams& c, in
     const char *wf = (const char*)section, *z = (const char*)zeros;
     if (layout == kDenseTaps) return launch_layout<kDenseTaps>(d, c, plan, wf, z, x, y, s);
     return layout == 1 ? launch_layout<1>(d, c, plan, wf, z, x, y, s) : launch_layout<0>(d, c, plan, wf, z, x, y, s);
+}
+
+rtoss_status launch_conv3x3_ksplit_gather(const rtoss_wdesc& d, const ConvParams& c, int plan, const void* headers, const void* frags,
+                                          const void* zeros, const void* x, void* y, hipStream_t s)
+{
+    const char *wf = (const char*)frags, *z = (const char*)zeros, *h = (const char*)headers;
+    const auto launch = [&](auto t, auto to) {
+        using T = decltype(t);
+        using TO = decltype(to);
+        if (plan == k16x4x8) return launch_variant<T, TO, 1, 1, 1, 2, kGathered>(d, c, wf, z, x, y, s, h);
+        if (plan == k32x4x8) return launch_variant<T, TO, 1, 2, 1, 2, kGathered>(d, c, wf, z, x, y, s, h);
+        if (plan == k32x8x8) return launch_variant<T, TO, 1, 2, 2, 2, kGathered>(d, c, wf, z, x, y, s, h);
+        return fail(RTOSS_EINVAL, "conv: unknown K-split plan %d", plan);
+    };
+    const bool f32out = c.out_dt == RTOSS_F32;
+    if (d.dt == RTOSS_F16) return f32out ? launch(f16_t{}, 0.f) : launch(f16_t{}, f16_t{});
+    return f32out ? launch(bf16_t{}, 0.f) : launch(bf16_t{}, bf16_t{});
 }
 
 }  // namespace rtoss

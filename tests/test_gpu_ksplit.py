@@ -69,3 +69,29 @@ def test_channel_split_output_stage(dt, N, Ci, Co, H, W, stride, k):
                                act=B.ACT_SILU, residual=wl.nhwc_to_nchw(res).astype(np.float64))
     check(wl.nhwc_to_nchw(out[..., 16:16 + Co]), want, dt)
     assert (out[..., :16] == 7.0).all() and (out[..., 16 + Co:] == 7.0).all()
+
+
+@pytest.mark.parametrize("shared", [True, False])
+@pytest.mark.parametrize("dt,N,Ci,Co,H,W,k", [
+    (wl.F16, 1, 32, 16, 1, 1, 3),      # 16 channels x 4x8 positions: one stage, one position
+    (wl.BF16, 1, 160, 144, 9, 17, 2),  # ... five stages, an unpaired channel block
+    (wl.F16, 2, 96, 80, 31, 33, 5),    # 32 channels x 4x8, more steps than LDS holds at a time
+    (wl.BF16, 1, 128, 128, 62, 81, 3),  # ... more than one round of workgroups
+    (wl.F16, 1, 64, 64, 90, 121, 3),   # 32 channels x 8x8
+])
+def test_channel_split_of_block_shared_patterns(dt, N, Ci, Co, H, W, k, shared):
+    rng = np.random.default_rng(Ci + H + k)
+    masks = B.rtoss_pattern_dict(k)
+    xs = wl.round_to_dtype(rng.standard_normal((N, Ci, H, W)), dt)
+    ws = wl.round_to_dtype(rng.standard_normal((Co, Ci, 3, 3)) * 0.05, dt)
+    idx = rng.integers(0, len(masks), (Co, Ci)).astype(np.uint8)
+    if shared:
+        idx[:] = np.repeat(idx[:1, ::8], 8, 1)
+    ref = oracle.conv2d(wl.to_f64(xs, dt), oracle.mask(wl.to_f64(ws, dt), masks, idx.reshape(-1)), relu=True)
+    lay = pl.CoherentLayer(Co, Ci, k, dt, masks).pack(pl.to_device(ws, dt), torch.from_numpy(idx.reshape(-1)).cuda())
+    x = pl.to_device(wl.nchw_to_nhwc(xs), dt)
+    y32, y16 = lay.conv(x, relu=True, out_dt=wl.F32), lay.conv(x, relu=True)
+    torch.cuda.synchronize()
+    got = wl.nhwc_to_nchw(pl.to_host(y32)).astype(np.float64)
+    assert np.max(np.abs(got - ref)) <= 2e-3 * np.sqrt(np.mean(ref ** 2))
+    assert np.array_equal(wl.nhwc_to_nchw(pl.to_host(y16)), wl.round_to_dtype(got, dt))
