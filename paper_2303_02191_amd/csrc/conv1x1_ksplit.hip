@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void conv1x1_ksplit_kernel(const T* __restrict
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[4 * m + e] = sum[e];
         }
-        epi_scale_bias_act<TO, RUN>(v, ep, o_co[i]);
+        epi_scale_bias_act<RUN>(v, ep, o_co[i]);
         if (ep.residual) shortcut[i].add(v);
         TO* yp = y + (int64_t)o_pos[i] * ep.ldy + o_co[i];
         if constexpr (sizeof(TO) == 4) {

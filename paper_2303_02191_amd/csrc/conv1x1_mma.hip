@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
                             if constexpr (RAG) {
                                 epi_ragged<TO, 4>(vv, ep, p_f, co4, Co);
                             } else {
-                                epi_scale_bias_act<TO, 4>(vv, ep, co4);
+                                epi_scale_bias_act<4>(vv, ep, co4);
                                 epi_residual<TO, 4>(vv, ep, p_f, co4);
                             }
                             v = f32x4{vv[0], vv[1], vv[2], vv[3]};

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
             for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][0][e];
-            epi_scale_bias_act<TO, 4 * MT>(v, ep, lds_ep + co_local, lds_ep + PL::SPAN + co_local);
+            epi_scale_bias_act<4 * MT>(v, ep, lds_ep + co_local, lds_ep + PL::SPAN + co_local);
             epi_residual<TO, 4 * MT>(v, ep, p, co_lane);
             if constexpr (EB == 4) {
 #pragma unroll

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict_
             store_ragged<TO, RUN>(yp - co_lane, v, co_lane, Co, ep.ldy);
             continue;
         }
-        epi_scale_bias_act<TO, RUN>(v, ep, co_lane);
+        epi_scale_bias_act<RUN>(v, ep, co_lane);
         epi_residual<TO, RUN>(v, ep, pos, co_lane);
         if constexpr (EB == 4) {
 #pragma unroll

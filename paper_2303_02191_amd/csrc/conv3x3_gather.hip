@@ -242,7 +242,7 @@ __global__ __launch_bounds__(256) void conv3x3_gather_kernel(const T* __restrict
         for (int m = 0; m < TM; ++m)
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][j][e];
-        epi_scale_bias_act<TO, RUN>(v, ep, co_lane);
+        epi_scale_bias_act<RUN>(v, ep, co_lane);
         epi_residual<TO, RUN>(v, ep, pos, co_lane);
         if constexpr (EB == 4) {
 #pragma unroll

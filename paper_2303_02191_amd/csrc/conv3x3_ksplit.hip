@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[4 * m + e] = sum[e];
     }
-    epi_scale_bias_act<TO, RUN>(v, ep, scale, bias);
+    epi_scale_bias_act<RUN>(v, ep, scale, bias);
     if (ep.residual) shortcut.add(v);
     TO* yp = y + o_pos * ep.ldy + o_co;
     if constexpr (sizeof(TO) == 4) {

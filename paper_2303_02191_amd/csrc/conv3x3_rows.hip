@@ -389,14 +389,14 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
                     }
                 }
             } else {
-#pragma unroll
-                for (int h = 0; h < HALVES; ++h) {
-#pragma unroll
-                    for (int j0 = 0; j0 < TN; j0 += JG) {
-                        const int jn = j0 + JG <= TN ? JG : TN - j0;  // rows in this group
-#pragma unroll
-                        for (int jj = 0; jj < jn; ++jj) {
-                            const int j = j0 + jj;
+                // (loops over types: a pragma gives up on bodies of this size, and the accumulators would go to memory)
+                static_for<HALVES>([&](auto h_tag) {
+                    constexpr int h = decltype(h_tag)::value;
+                    static_for<(TN + JG - 1) / JG>([&](auto g_tag) {
+                        constexpr int j0 = decltype(g_tag)::value * JG;
+                        constexpr int jn = j0 + JG <= TN ? JG : TN - j0;  // rows in this group
+                        static_for<jn>([&](auto jj_tag) {
+                            constexpr int jj = decltype(jj_tag)::value, j = j0 + jj;
                             f32x4 vals[TMH];
 #pragma unroll
                             for (int mm = 0; mm < TMH; ++mm) vals[mm] = acc[h * TMH + mm][j];
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
                                     const int co4 = 16 * (cur.mt0 + h * TMH) + tile_quarter_offset(mm, qq_e);
                                     if (inside_f && co4 < Co) {
                                         float vv[4] = {vals[mm].x, vals[mm].y, vals[mm].z, vals[mm].w};
-                                        epi_scale_bias_act<TO, 4>(vv, ep, co4);
+                                        epi_scale_bias_act<4>(vv, ep, co4);
                                         epi_residual<TO, 4>(vv, ep, pos_f, co4);
                                         vals[mm] = f32x4{vv[0], vv[1], vv[2], vv[3]};
                                     }
@@ -439,14 +439,14 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
                                     *(uint2*)dst = o;
                                 }
                             }
-                        }
+                        });
                         // read back: a row of 16*TMH channels is CH 16-byte chunks; 64 lanes cover 64/CH positions
                         // per pass.  (A wave's LDS accesses execute in order, so the next group's writes to this
                         // slice cannot pass these reads.)
                         constexpr int CH = TMH * 16 * EB / 16;
                         static_assert(64 % CH == 0, "row chunks must tile the wave");
                         constexpr int POS_PER_PASS = 64 / CH;
-                        const int passes = (16 * jn) / POS_PER_PASS;
+                        constexpr int passes = (16 * jn) / POS_PER_PASS;
                         const int co_first = 16 * (cur.mt0 + h * TMH);
                         const int sub = lane_e / CH, chunk = lane_e % CH;  // position within the pass, chunk within the row
                         const int co = co_first + chunk * (16 / EB);
@@ -458,8 +458,8 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
                             if (cur.oh0 + dr < Ho && cur.ow0 + dc < Wo && co < Co)  // Co is a multiple of 16: a chunk is all in or all out
                                 *(u32x4*)(y_tile + (dr * Wo + dc) * ep.ldy + co) = v;
                         }
-                    }
-                }
+                    });
+                });
             }
         }
         // staging slices are read (LDS only): the region may be overwritten by the next copies.  A bare

@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
                     store_ragged<TO, 16>(yp, vv, co, Co, ep.ldy);
                     continue;
                 }
-                epi_scale_bias_act<TO, 16>(vv, ep, lds_ep + co - 16 * mt0, lds_ep + 16 * TM + co - 16 * mt0);
+                epi_scale_bias_act<16>(vv, ep, lds_ep + co - 16 * mt0, lds_ep + 16 * TM + co - 16 * mt0);
                 if constexpr (SHORTCUT) shortcut[j][mg / 4].add(vv);
                 if constexpr (sizeof(TO) == 4) {
 #pragma unroll

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 8 : 4) void conv3x3_stem_kernel(cons
             const int co = 16 * mp + 8 * qq;  // this lane's 8 consecutive channels of the pair
             if (inside && co < Co) {
                 float vv[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-                epi_scale_bias_act<TO, 8>(vv, ep, co);
+                epi_scale_bias_act<8>(vv, ep, co);
                 epi_residual<TO, 8>(vv, ep, pos, co);
                 if constexpr (sizeof(TO) == 4) {
                     *(f32x4*)(yp + co) = f32x4{vv[0], vv[1], vv[2], vv[3]};

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
             for (int m = 0; m < kTM; ++m)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][j][e];
-            epi_scale_bias_act<TO, 16>(v, ep, lds_ep + 16 * qq, lds_ep + 64 + 16 * qq);
+            epi_scale_bias_act<16>(v, ep, lds_ep + 16 * qq, lds_ep + 64 + 16 * qq);
             if constexpr (SHORTCUT) shortcut[j].add(v);
             if constexpr (sizeof(TO) == 4) {
 #pragma unroll

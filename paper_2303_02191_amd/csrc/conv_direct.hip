@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(const T* __restrict__ 
                 float v = acc[i];
                 if (ep.scale) v *= ep.scale[co];
                 if (ep.bias) v += ep.bias[co];
-                v = epi_act<TO>(v, ep.act);
+                v = epi_act(v, ep.act);
                 if (ep.residual) v += to_f32(rp[co * st.r.c]);
                 store_from_f32<TO>(yp + co * st.y.c, v);
             }

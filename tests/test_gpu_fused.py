@@ -159,3 +159,45 @@ def test_two_layers_write_one_concatenation(case):
             got = wl.to_f64(wl.nhwc_to_nchw(pl.to_host(ysl.contiguous())), out_dt)
             err = np.max(np.abs(got - ref))
             assert err <= _tolerance(ref, dt, out_dt), (err, _tolerance(ref, dt, out_dt), out_dt)
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "dt%d_%dx%d_k%d_s%d_%d-%d" % (c[0], c[6], c[6], c[8], c[7], c[2], c[3]))
+def test_silu_of_chosen_values(case):
+    """With activations of zero the output stage's argument is the bias: SiLU over the whole range of fp32, where the
+    correction of the reciprocal takes over from the division and beyond, and one rounding for 16-bit results."""
+    dt, N, Ci, Co, H, W, ks, stride, k, rule = case
+    rng = np.random.default_rng(Ci + Co)
+    ends = np.array([0.0, 1e-45, -1e-45, 1e-38, -1e-38, 1e-30, 1.0, -1.0, 79.99999, 80.0, 80.00001, -79.99999, -80.0, -80.00001, -87.0,
+                     -87.5, -88.5, -89.0, -104.0, -3e38, 3e38, np.inf, -np.inf, np.nan, 16.7, -16.7, 104.0, -60.0])
+    bias = np.concatenate([ends, rng.standard_normal(Co) * 4])[rng.permutation(len(ends) + Co)][:Co].astype(np.float32)
+    x = torch.zeros((N, H, W, Ci), dtype=pl.TORCH_DTYPE[dt], device="cuda")
+    layer = GpuLayer(wl.round_to_dtype(rng.standard_normal((Co, Ci, ks, ks)), dt), dt, B.rtoss_pattern_dict(k, rule), k).layer
+    b = torch.from_numpy(bias).cuda()
+    y = layer.conv_fused(x, stride=stride, bias=b, act=B.ACT_SILU, out_dt=wl.F32)
+    v = bias.astype(np.float64)
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = v / (1.0 + np.exp(-v))
+    got = y.cpu().numpy().astype(np.float64)
+    # fp32 error of exp(-v): its argument's rounding (2^-24 of |v| / ln 2) and one unit; then an addition and a division.
+    # Below -87 exp(-v) nears the end of the fp32 range and results are under 1e-36.
+    bound = np.abs(want) * (np.abs(v) * 2.0 ** -23 + 2.0 ** -22) + 1e-36
+    ok = (np.abs(got - want) <= bound) | (got == want) | (np.isnan(got) & np.isnan(want))
+    assert ok.all(), (v[np.argwhere(~ok)[0][-1]], got[~ok][0])
+    if dt != wl.F32:
+        y16 = layer.conv_fused(x, stride=stride, bias=b, act=B.ACT_SILU)
+        rounded = y.to(y16.dtype)
+        assert bool(((y16 == rounded) | (y16.isnan() & rounded.isnan())).all())
+
+
+@pytest.mark.parametrize("dt", [wl.F16, wl.BF16])
+def test_16bit_silu_is_the_fp32_result_rounded_once(dt):
+    """2.6 million outputs: a reciprocal in the place of the division would round a few dozen of them differently."""
+    rng = np.random.default_rng(17)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17)
+    layer = GpuLayer(wl.round_to_dtype(rng.standard_normal((64, 32, 1, 1)) * 0.4, dt), dt, B.rtoss_pattern_dict(3), 3).layer
+    x = torch.randn((1, 200, 200, 32), generator=g, device="cuda").to(pl.TORCH_DTYPE[dt])
+    bias = torch.randn(64, generator=g, device="cuda")
+    y32 = layer.conv_fused(x, bias=bias, act=B.ACT_SILU, out_dt=wl.F32)
+    y16 = layer.conv_fused(x, bias=bias, act=B.ACT_SILU)
+    assert torch.equal(y16, y32.to(y16.dtype))
