@@ -310,16 +310,18 @@ PyObject* py_select(PyObject*, PyObject* const* a, Py_ssize_t n)
     });
 }
 
-// a sequence argument as a fast sequence, released on scope exit
+// A sequence argument's elements as they are at the start of the call, held until it returns.  (A list can be changed by
+// any Python code that runs meanwhile: attribute lookups here, other threads while the ABI call is without the lock.)
 struct Seq {
     PyObject* o;
-    explicit Seq(PyObject* s) : o(PySequence_Fast(s, "a sequence is expected"))
+    explicit Seq(PyObject* s) : o(PySequence_Tuple(s))
     {
         if (!o) throw PyError{};
     }
+    Seq(const Seq&) = delete;
     ~Seq() { Py_DECREF(o); }
-    Py_ssize_t size() const { return PySequence_Fast_GET_SIZE(o); }
-    PyObject* operator[](Py_ssize_t i) const { return PySequence_Fast_GET_ITEM(o, i); }
+    Py_ssize_t size() const { return PyTuple_GET_SIZE(o); }
+    PyObject* operator[](Py_ssize_t i) const { return PyTuple_GET_ITEM(o, i); }
 };
 struct Owned {
     PyObject* o;
@@ -327,6 +329,7 @@ struct Owned {
     {
         if (!o) throw PyError{};
     }
+    Owned(Owned&& other) noexcept : o(other.release()) {}
     ~Owned() { Py_XDECREF(o); }
     PyObject* release()
     {
@@ -366,7 +369,7 @@ PyObject* py_select_batch(PyObject*, PyObject* const* a, Py_ssize_t n)
         call([&] { return rtoss_select_patterns_batch(count ? items.data() : &none, (int)count, (rtoss_dtype)dt, m.data(), m.size(), s); });
         Owned out(PyList_New(count));
         for (Py_ssize_t i = 0; i < count; ++i) {
-            PyObject* t = first_entries(idxs[i], tensor(ws[i]).numel() / 9);
+            PyObject* t = first_entries(idxs[i], items[i].n_elems / 9);
             if (!t) throw PyError{};
             PyList_SET_ITEM(out.o, i, t);
         }
@@ -384,12 +387,15 @@ PyObject* py_pack_batch(PyObject*, PyObject* const* a, Py_ssize_t n)
         Seq layers(a[0]), ws(a[1]), idxs(a[2]);
         const Py_ssize_t count = std::min(layers.size(), std::min(ws.size(), idxs.size()));
         std::vector<rtoss_pack_item> items((size_t)count);
+        std::vector<Owned> held;  // the layers' attributes: replacing one during the call must not free it
+        held.reserve(2 * (size_t)count);
         const Layer* first = nullptr;
         for (Py_ssize_t i = 0; i < count; ++i) {
-            Owned cap(PyObject_GetAttr(layers[i], k_native)), blob(PyObject_GetAttr(layers[i], k_blob));
-            const Layer& l = layer_of(cap.o);
+            held.emplace_back(PyObject_GetAttr(layers[i], k_native));
+            const Layer& l = layer_of(held.back().o);
             if (!first) first = &l;
-            const at::Tensor &b = tensor(blob.o), &w = tensor(ws[i]), &x = tensor(idxs[i]);
+            held.emplace_back(PyObject_GetAttr(layers[i], k_blob));
+            const at::Tensor &b = tensor(held.back().o), &w = tensor(ws[i]), &x = tensor(idxs[i]);
             require(w.is_cuda() && w.is_contiguous() && x.is_cuda(), "weights and indices are cuda tensors, weights contiguous");
             items[i] = rtoss_pack_item{l.d, w.data_ptr(), (const uint8_t*)x.data_ptr(), b.data_ptr(), (size_t)b.nbytes()};
         }
