@@ -12,6 +12,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstring>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -103,26 +104,41 @@ at::Tensor allocate(at::IntArrayRef shape, at::ScalarType st, const at::Device& 
     return at::Tensor(at::detail::empty_cuda(shape, st, dev, std::nullopt));
 }
 
-// a dictionary: one-dimensional contiguous array of uint16
+// a dictionary: contiguous array of uint16
+void acquire_masks(PyObject* o, Py_buffer* view)
+{
+    if (PyObject_GetBuffer(o, view, PyBUF_FORMAT | PyBUF_C_CONTIGUOUS)) throw PyError{};
+    if (view->itemsize != 2 || !view->format || std::strcmp(view->format, "H") != 0) {
+        PyBuffer_Release(view);
+        raise(PyExc_TypeError, "the dictionary must be an array of uint16");
+    }
+}
 struct Masks {
     Py_buffer view{};
-    explicit Masks(PyObject* o)
-    {
-        if (PyObject_GetBuffer(o, &view, PyBUF_FORMAT | PyBUF_C_CONTIGUOUS)) throw PyError{};
-        if (view.itemsize != 2 || !view.format || std::strcmp(view.format, "H") != 0) {
-            PyBuffer_Release(&view);
-            raise(PyExc_TypeError, "the dictionary must be an array of uint16");
-        }
-    }
+    explicit Masks(PyObject* o) { acquire_masks(o, &view); }
     ~Masks() { PyBuffer_Release(&view); }
     const uint16_t* data() const { return (const uint16_t*)view.buf; }
     int size() const { return (int)(view.len / 2); }
 };
 
-// ---- a layer's descriptor and dictionary, kept by the Python layer object ----
+// ---- a layer's descriptor and dictionary, where the Python layer object keeps them ----
+// (Buffers of its own attributes, not copies: a field of the descriptor or an entry of the dictionary that the program
+// changes counts from the next call on, as it does for the calls that go through ctypes.)
 struct Layer {
-    rtoss_wdesc d;
-    std::vector<uint16_t> masks;
+    Py_buffer desc{}, masks{};
+    ~Layer()
+    {
+        PyBuffer_Release(&desc);  // (nothing for a buffer that was not acquired)
+        PyBuffer_Release(&masks);
+    }
+    rtoss_wdesc d() const
+    {
+        rtoss_wdesc v;
+        std::memcpy(&v, desc.buf, sizeof v);
+        return v;
+    }
+    const uint16_t* dict() const { return (const uint16_t*)masks.buf; }
+    int P() const { return (int)(masks.len / 2); }
 };
 constexpr const char* kCapsule = "rtoss.layer";
 void free_layer(PyObject* cap) { delete (Layer*)PyCapsule_GetPointer(cap, kCapsule); }
@@ -138,25 +154,18 @@ void arity(Py_ssize_t n, Py_ssize_t want)
     if (n != want) raise(PyExc_TypeError, "wrong number of arguments");
 }
 
-// layer(Co, Ci, ksize, k, dt, masks) -> capsule
+// layer(wdesc, masks) -> capsule
 PyObject* py_layer(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     return guarded([&]() -> PyObject* {
-        arity(n, 6);
-        auto* l = new Layer;
-        PyObject* cap = PyCapsule_New(l, kCapsule, free_layer);
-        if (!cap) {
-            delete l;
-            throw PyError{};
-        }
-        try {
-            l->d = rtoss_wdesc{(int)integer(a[0]), (int)integer(a[1]), (int)integer(a[2]), (int)integer(a[3]), (rtoss_dtype)integer(a[4])};
-            Masks m(a[5]);
-            l->masks.assign(m.data(), m.data() + m.size());
-        } catch (...) {
-            Py_DECREF(cap);
-            throw;
-        }
+        arity(n, 2);
+        auto l = std::make_unique<Layer>();
+        if (PyObject_GetBuffer(a[0], &l->desc, PyBUF_SIMPLE)) throw PyError{};
+        if (l->desc.len != sizeof(rtoss_wdesc)) raise(PyExc_TypeError, "the descriptor must be a WDesc");
+        acquire_masks(a[1], &l->masks);
+        PyObject* cap = PyCapsule_New(l.get(), kCapsule, free_layer);
+        if (!cap) throw PyError{};
+        l.release();
         return cap;
     });
 }
@@ -171,12 +180,12 @@ Spatial spatial_of(const at::Tensor& x, bool nchw)
     return nchw ? Spatial{s[0], s[2], s[3], s[1]} : Spatial{s[0], s[1], s[2], s[3]};
 }
 
-at::Tensor new_output(const Layer& l, const Spatial& x, long stride, bool nchw, int out_dt, const at::Device& dev)
+at::Tensor new_output(const rtoss_wdesc& d, const Spatial& x, long stride, bool nchw, int out_dt, const at::Device& dev)
 {
-    const int64_t p = 2 * (l.d.ksize / 2) - l.d.ksize;
+    const int64_t p = 2 * (d.ksize / 2) - d.ksize;
     const int64_t Ho = (x.H + p) / stride + 1, Wo = (x.W + p) / stride + 1;
-    if (nchw) return allocate({x.N, l.d.Co, Ho, Wo}, scalar_type(out_dt), dev);
-    return allocate({x.N, Ho, Wo, l.d.Co}, scalar_type(out_dt), dev);
+    if (nchw) return allocate({x.N, d.Co, Ho, Wo}, scalar_type(out_dt), dev);
+    return allocate({x.N, Ho, Wo, d.Co}, scalar_type(out_dt), dev);
 }
 
 // conv(layer, blob, x, stride, relu, out_dt, y, layout, coherent)
@@ -185,28 +194,29 @@ PyObject* py_conv(PyObject*, PyObject* const* a, Py_ssize_t n)
     return guarded([&]() -> PyObject* {
         arity(n, 9);
         const Layer& l = layer_of(a[0]);
+        const rtoss_wdesc d = l.d();
         const at::Tensor &blob = tensor(a[1]), &x = tensor(a[2]);
         const long stride = integer(a[3]);
         const bool relu = truth(a[4]), coherent = truth(a[8]);
-        const int out_dt = a[5] == Py_None ? (int)l.d.dt : (int)integer(a[5]);
+        const int out_dt = a[5] == Py_None ? (int)d.dt : (int)integer(a[5]);
         const int layout = (int)integer(a[7]);
         require(x.is_cuda() && x.is_contiguous(), "x must be a contiguous cuda tensor");
         const bool nchw = layout == RTOSS_NCHW;
         const Spatial xs = spatial_of(x, nchw);
-        require(xs.C == l.d.Ci, "x has another number of channels than the layer");
+        require(xs.C == d.Ci, "x has another number of channels than the layer");
         at::Tensor y;
         void* yp = nullptr;
         if (a[6] != Py_None) yp = tensor(a[6]).data_ptr();
         else if (stride > 0) {  // (a bad stride is the library's error to report)
-            y = new_output(l, xs, stride, nchw, out_dt, x.device());
+            y = new_output(d, xs, stride, nchw, out_dt, x.device());
             yp = y.data_ptr();
         }
-        const rtoss_cdesc c{(int)xs.N, (int)xs.H, (int)xs.W, (int)stride, l.d.ksize / 2, (rtoss_layout)layout, (rtoss_dtype)out_dt, relu ? 1 : 0};
+        const rtoss_cdesc c{(int)xs.N, (int)xs.H, (int)xs.W, (int)stride, d.ksize / 2, (rtoss_layout)layout, (rtoss_dtype)out_dt, relu ? 1 : 0};
         void* s = current_stream();
         const void *bp = blob.data_ptr(), *xp = x.data_ptr();
         call([&] {
-            return coherent ? rtoss_conv2d_pattern_coherent(&l.d, &c, nullptr, l.masks.data(), (int)l.masks.size(), bp, xp, yp, s)
-                            : rtoss_conv2d_pattern(&l.d, &c, l.masks.data(), (int)l.masks.size(), bp, xp, yp, s);
+            return coherent ? rtoss_conv2d_pattern_coherent(&d, &c, nullptr, l.dict(), l.P(), bp, xp, yp, s)
+                            : rtoss_conv2d_pattern(&d, &c, l.dict(), l.P(), bp, xp, yp, s);
         });
         if (a[6] != Py_None) {
             Py_INCREF(a[6]);
@@ -238,25 +248,26 @@ PyObject* py_conv_fused(PyObject*, PyObject* const* a, Py_ssize_t n)
     return guarded([&]() -> PyObject* {
         arity(n, 10);
         const Layer& l = layer_of(a[0]);
+        const rtoss_wdesc d = l.d();
         const at::Tensor &blob = tensor(a[1]), &x = tensor(a[2]);
         const long stride = integer(a[3]);
-        const int out_dt = a[8] == Py_None ? (int)l.d.dt : (int)integer(a[8]);
+        const int out_dt = a[8] == Py_None ? (int)d.dt : (int)integer(a[8]);
         require(x.is_cuda() && x.is_contiguous(), "x must be a contiguous cuda tensor");
         const Spatial xs = spatial_of(x, false);
-        require(xs.C == l.d.Ci, "x has another number of channels than the layer");
+        require(xs.C == d.Ci, "x has another number of channels than the layer");
         if (stride < 1) raise(stride ? PyExc_ValueError : PyExc_ZeroDivisionError, "stride must be positive");
         rtoss_epilogue e{};
-        e.scale_dev = per_channel(a[4], l.d.Co);
-        e.bias_dev = per_channel(a[5], l.d.Co);
+        e.scale_dev = per_channel(a[4], d.Co);
+        e.bias_dev = per_channel(a[5], d.Co);
         e.act = (rtoss_act)integer(a[6]);
         at::Tensor made;
-        if (a[9] == Py_None) made = new_output(l, xs, stride, false, out_dt, x.device());
+        if (a[9] == Py_None) made = new_output(d, xs, stride, false, out_dt, x.device());
         const at::Tensor& y = a[9] == Py_None ? made : tensor(a[9]);
         if (a[9] != Py_None) {
-            const int64_t p = 2 * (l.d.ksize / 2) - l.d.ksize;
+            const int64_t p = 2 * (d.ksize / 2) - d.ksize;
             const auto z = y.sizes();
             require(y.dim() == 4 && z[0] == xs.N && z[1] == (xs.H + p) / stride + 1 && z[2] == (xs.W + p) / stride + 1 &&
-                        z[3] == l.d.Co && y.scalar_type() == scalar_type(out_dt),
+                        z[3] == d.Co && y.scalar_type() == scalar_type(out_dt),
                     "y has the wrong shape or dtype");
             e.y_ld = pitch_of(y);
         }
@@ -266,11 +277,11 @@ PyObject* py_conv_fused(PyObject*, PyObject* const* a, Py_ssize_t n)
             e.residual_dev = r.data_ptr();
             e.residual_ld = pitch_of(r);
         }
-        const rtoss_cdesc c{(int)xs.N, (int)xs.H, (int)xs.W, (int)stride, l.d.ksize / 2, RTOSS_NHWC, (rtoss_dtype)out_dt, 0};
+        const rtoss_cdesc c{(int)xs.N, (int)xs.H, (int)xs.W, (int)stride, d.ksize / 2, RTOSS_NHWC, (rtoss_dtype)out_dt, 0};
         void* s = current_stream();
         const void *bp = blob.data_ptr(), *xp = x.data_ptr();
         void* yp = y.data_ptr();
-        call([&] { return rtoss_conv2d_pattern_fused(&l.d, &c, &e, l.masks.data(), (int)l.masks.size(), bp, xp, yp, s); });
+        call([&] { return rtoss_conv2d_pattern_fused(&d, &c, &e, l.dict(), l.P(), bp, xp, yp, s); });
         if (a[9] != Py_None) {
             Py_INCREF(a[9]);
             return a[9];
@@ -377,30 +388,32 @@ PyObject* py_select_batch(PyObject*, PyObject* const* a, Py_ssize_t n)
     });
 }
 
-// pack_batch(layers, ws, idxs, stream or None); the layers are objects with _native and blob, of one dictionary
+// pack_batch(layers, ws, idxs, stream or None); the layers are objects with _native, _bound and blob (pipeline.py), of one dictionary
 PyObject* py_pack_batch(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     return guarded([&]() -> PyObject* {
         arity(n, 4);
         static PyObject* const k_native = PyUnicode_InternFromString("_native");
+        static PyObject* const k_bound = PyUnicode_InternFromString("_bound");
         static PyObject* const k_blob = PyUnicode_InternFromString("blob");
         Seq layers(a[0]), ws(a[1]), idxs(a[2]);
         const Py_ssize_t count = std::min(layers.size(), std::min(ws.size(), idxs.size()));
         std::vector<rtoss_pack_item> items((size_t)count);
         std::vector<Owned> held;  // the layers' attributes: replacing one during the call must not free it
-        held.reserve(2 * (size_t)count);
+        held.reserve(3 * (size_t)count);
         const Layer* first = nullptr;
         for (Py_ssize_t i = 0; i < count; ++i) {
             held.emplace_back(PyObject_GetAttr(layers[i], k_native));
+            if (held.back().o == Py_None) held.emplace_back(PyObject_CallMethodNoArgs(layers[i], k_bound));
             const Layer& l = layer_of(held.back().o);
             if (!first) first = &l;
             held.emplace_back(PyObject_GetAttr(layers[i], k_blob));
             const at::Tensor &b = tensor(held.back().o), &w = tensor(ws[i]), &x = tensor(idxs[i]);
             require(w.is_cuda() && w.is_contiguous() && x.is_cuda(), "weights and indices are cuda tensors, weights contiguous");
-            items[i] = rtoss_pack_item{l.d, w.data_ptr(), (const uint8_t*)x.data_ptr(), b.data_ptr(), (size_t)b.nbytes()};
+            items[i] = rtoss_pack_item{l.d(), w.data_ptr(), (const uint8_t*)x.data_ptr(), b.data_ptr(), (size_t)b.nbytes()};
         }
         void* s = stream_arg(a[3]);
-        if (first) call([&] { return rtoss_pack_batch(items.data(), (int)count, first->masks.data(), (int)first->masks.size(), s); });
+        if (first) call([&] { return rtoss_pack_batch(items.data(), (int)count, first->dict(), first->P(), s); });
         Py_RETURN_NONE;
     });
 }

@@ -9,6 +9,7 @@ import torch
 from . import binding as B
 
 TORCH_DTYPE = {B.F32: torch.float32, B.F16: torch.float16, B.BF16: torch.bfloat16}
+_host = None  # binding.host(), once there is a layer
 
 
 def _stream():
@@ -64,15 +65,43 @@ def reduce_dictionary(masks, w_random, dt, M):
     return out, kept, counts
 
 
-class CoherentLayer:
+class _Layer:
+    """What both kinds of layer share: the native handle through which calls read the descriptor (wdesc) and the
+    dictionary (masks).  It reads them where the attributes keep them, follows an attribute that is replaced, and is made
+    anew for copies and unpickled layers."""
+
+    def _bound(self):
+        return B.host().layer(self.wdesc, B.dictionary(self.masks))
+
+    def _bind(self):
+        global _host
+        _host = B.host()
+        self._native = None
+        # (a dictionary that is no uint16 array, such as a list, is converted at every call instead)
+        if B.dictionary(self.masks) is self.masks:
+            self._native = self._bound()
+
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        if name in ("wdesc", "masks") and "_native" in self.__dict__:
+            self._bind()
+
+    def __getstate__(self):
+        return {name: value for name, value in self.__dict__.items() if name != "_native"}
+
+    def __setstate__(self, state):
+        self.__dict__.update(state)
+        self._bind()
+
+
+class CoherentLayer(_Layer):
     """A 3x3 layer packed for the dense-instruction gather path (block-shared patterns)."""
 
     def __init__(self, Co, Ci, k, dt, masks, device="cuda"):
         self.wdesc = B.WDesc(Co, Ci, 3, k, dt)
         self.masks, self.dt = masks, dt
         self.packed_bytes, self.steps_offset = B.rtoss_pack_size_coherent(self.wdesc, masks)
-        self._native = B.host().layer(Co, Ci, 3, k, dt, B.dictionary(masks))
-        self._conv = B.host().conv
+        self._bind()
         self.blob = torch.empty(self.packed_bytes, dtype=torch.uint8, device=device)
 
     def pack(self, w, idx):
@@ -89,10 +118,11 @@ class CoherentLayer:
         return rec[:, :, :4].copy().view("<u4").reshape(stages, blocks)
 
     def conv(self, x, stride=1, relu=False, out_dt=None, y=None):
-        return self._conv(self._native, self.blob, x, stride, relu, out_dt, y, B.NHWC, True)
+        return _host.conv(self._native or self._bound(), self.blob, x, stride, relu, self.dt if out_dt is None else out_dt, y, B.NHWC,
+                          True)
 
 
-class PackedLayer:
+class PackedLayer(_Layer):
     """One layer's packed blob plus the descriptors the convolution call needs."""
 
     def __init__(self, Co, Ci, ksize, k, dt, masks, device="cuda"):
@@ -100,8 +130,7 @@ class PackedLayer:
         self.masks = masks
         self.dt = dt
         self.packed_bytes, self.workspace_bytes = B.rtoss_pack_size(self.wdesc, masks)
-        self._native = B.host().layer(Co, Ci, ksize, k, dt, B.dictionary(masks))
-        self._conv, self._conv_fused = B.host().conv, B.host().conv_fused
+        self._bind()
         # torch's caching allocator returns 512-byte aligned blocks
         self.blob = torch.empty(self.packed_bytes, dtype=torch.uint8, device=device)
         self.workspace = torch.empty(max(self.workspace_bytes, 1), dtype=torch.uint8, device=device)
@@ -122,10 +151,12 @@ class PackedLayer:
     def conv(self, x, stride=1, relu=False, out_dt=None, y=None, layout=B.NHWC):
         """x: cuda tensor of the layer's dtype, channels-last [N, H, W, Ci] (or [N, Ci, H, W] with layout=B.NCHW).
         Returns y [N, Ho, Wo, Co] (or [N, Co, Ho, Wo])."""
-        return self._conv(self._native, self.blob, x, stride, relu, out_dt, y, layout, False)
+        return _host.conv(self._native or self._bound(), self.blob, x, stride, relu, self.dt if out_dt is None else out_dt, y, layout,
+                          False)
 
     def conv_fused(self, x, stride=1, scale=None, bias=None, act=B.ACT_NONE, residual=None, out_dt=None, y=None):
         """y = act(scale[co] * conv + bias[co]) + residual.  scale/bias: float32 cuda tensors [Co] or None;
         residual: cuda tensor of y's dtype and shape or None.  y and residual may be channel slices
         buf[..., c0:c0+Co] of wider channels-last buffers (a concatenation the layer writes its part of)."""
-        return self._conv_fused(self._native, self.blob, x, stride, scale, bias, act, residual, out_dt, y)
+        return _host.conv_fused(self._native or self._bound(), self.blob, x, stride, scale, bias, act, residual,
+                                self.dt if out_dt is None else out_dt, y)

@@ -1,11 +1,14 @@
 """The native call path behind pipeline.py: its own argument checks, what it holds on to during a call, and layers as
 ordinary Python objects (no GPU needed)."""
+import copy
+import pickle
 import subprocess
 import sys
 
 import numpy as np
 import pytest
 import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
 
 from paper_2303_02191_amd import binding as B
 from paper_2303_02191_amd import pipeline as pl
@@ -97,3 +100,71 @@ def test_lists_that_change_during_a_call():
     p = subprocess.run([sys.executable, "-c", LISTS_CHANGED_DURING_A_CALL], capture_output=True, text=True, timeout=300,
                        cwd=ROOT)
     assert p.returncode == 0 and "survived" in p.stdout, (p.returncode, p.stderr[-2000:])
+
+
+KINDS = [lambda masks, device="cpu": pl.PackedLayer(32, 32, 3, 3, B.F16, masks, device=device),
+         lambda masks, device="cpu": pl.CoherentLayer(32, 32, 3, B.F16, masks, device=device)]
+
+
+def refusal(layer):
+    """What the library says to packing the layer from tensors without memory: the descriptor and the dictionary are looked
+    at before the pointers."""
+    with FakeTensorMode():
+        w = torch.empty(32, 32, 3, 3, dtype=torch.float16, device="cuda")
+        idx = torch.empty(1024, dtype=torch.uint8, device="cuda")
+    with pytest.raises(B.RtossError) as e:
+        pl.pack_layers([layer], [w], [idx], stream=0)
+    return str(e.value)
+
+
+@pytest.mark.parametrize("make", KINDS)
+def test_layers_can_be_copied_and_pickled(make):
+    layer = make(B.rtoss_pattern_dict(3))
+    layer.blob.random_(0, 255)
+    for other in (copy.copy(layer), copy.deepcopy(layer), pickle.loads(pickle.dumps(layer))):
+        assert type(other) is type(layer) and other.packed_bytes == layer.packed_bytes and other.dt == layer.dt
+        assert bytes(other.wdesc) == bytes(layer.wdesc) and np.array_equal(other.masks, layer.masks)
+        assert torch.equal(other.blob, layer.blob)
+        assert "taps" not in refusal(other)
+        other.masks = B.rtoss_pattern_dict(2)  # its own from here on
+        assert "dictionary keeps 2 taps" in refusal(other) and "taps" not in refusal(layer)
+
+
+@pytest.mark.parametrize("make", KINDS)
+def test_calls_follow_a_layers_attributes(make):
+    masks = B.rtoss_pattern_dict(3)
+    layer = make(masks)
+    assert "taps" not in refusal(layer)
+    layer.wdesc.k = 2  # in place
+    assert "dictionary keeps 3 taps, descriptor says k=2" in refusal(layer)
+    layer.wdesc = B.WDesc(32, 32, 3, 3, B.F16)
+    assert "taps" not in refusal(layer)
+    masks[1] = 3  # in place
+    assert "pattern 1 keeps 2 taps" in refusal(layer)
+    layer.masks = [7, 0x1c0]  # any sequence
+    assert "taps" not in refusal(layer)
+    layer.masks.append(3)
+    assert "pattern 2 keeps 2 taps" in refusal(layer)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("make", KINDS)
+def test_copies_compute_and_follow_their_attributes(make):
+    masks = B.rtoss_pattern_dict(3)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    w = torch.randn((32, 32, 3, 3), generator=g, device="cuda").half()
+    x = torch.randn((1, 9, 11, 32), generator=g, device="cuda").half()
+    layer = make(masks, "cuda").pack(w, pl.select_patterns(w, B.F16, masks))
+    y = layer.conv(x)
+    for other in (copy.copy(layer), copy.deepcopy(layer), pickle.loads(pickle.dumps(layer))):
+        assert torch.equal(other.conv(x), y)
+        other.dt = B.F32  # the default type of results
+        assert other.conv(x).dtype == torch.float32
+        other.masks = list(masks)
+        other.dt = B.F16
+        assert torch.equal(other.conv(x), y)
+        other.masks = B.rtoss_pattern_dict(2)
+        with pytest.raises(B.RtossError):
+            other.conv(x)
+    assert torch.equal(layer.conv(x), y)
