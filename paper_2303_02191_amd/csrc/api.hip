@@ -429,7 +429,12 @@ static rtoss_status conv_impl(const rtoss_wdesc* desc, const rtoss_cdesc* c, con
         if (c->layout != RTOSS_NHWC) return fail(RTOSS_ELAYOUT, "the coherent path takes channels-last tensors");
         return launch_conv3x3_gather(*desc, cp, blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
     }
-    if (c->layout == RTOSS_NCHW)  // the element-wise kernel reads section 0 and takes any strides
+    // The element-wise kernel reads section 0 and takes any strides (NCHW) and any size.
+    const bool fits = g.format == kFormatSparse24   ? sparse3x3_launch_ok(*desc, cp)
+                      : g.format == kFormatDense3x3 ? dense3x3_launch_ok(*desc, cp)
+                      : g.format == kFormatDense    ? dense1x1_launch_ok(*desc, cp)
+                                                    : true;
+    if (c->layout == RTOSS_NCHW || !fits)
         return launch_conv_direct(*desc, cp, dict, blob + g.live_off, (const uint8_t*)(blob + g.idx_off), x_dev, y_dev,
                                   (hipStream_t)hip_stream);
     if (g.format == kFormatSparse24)

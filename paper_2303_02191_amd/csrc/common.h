@@ -30,6 +30,12 @@ struct TapTable {
     uint8_t tap[256][9];
 };
 
+// Most workgroups in the first dimension of a grid, rounded down to a multiple of the 8 XCDs: the runtime refuses launches
+// with 2^32 or more work items in a dimension, and no kernel with this limit has more than 256 lanes.
+constexpr int64_t kMaxGridGroups = 0xffffffff / 256 / 8 * 8;
+// Most 16-byte chunks of an input whose copy sources are 32-bit chunk offsets.
+constexpr int64_t kMaxChunks = 0x7fffffff;
+
 inline int elem_bytes(rtoss_dtype dt) { return dt == RTOSS_F32 ? 4 : 2; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -100,7 +106,11 @@ struct PackItem {
 };
 rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, const Dict& dict, hipStream_t s);
 
+// The matrix-core kernels took over shapes that the element-wise kernel serves at any size.  *_launch_ok: the launch is
+// within the kernel's limits, or of a shape that the kernel alone serves (which then reports the error).
+
 // 3x3 convolution on the sparse matrix instruction (conv3x3_sparse.hip)
+bool sparse3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c);
 int sparse3x3_layout(const uint16_t* masks, int P);  // Dict::layout
 bool sparse3x3_shape_ok(const rtoss_wdesc& d);
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout);
@@ -138,12 +148,14 @@ rtoss_status launch_conv3x3_gather(const rtoss_wdesc& d, const ConvParams& c, co
                                    hipStream_t s);
 
 // 3x3 convolution in dense mode on the matrix cores (conv3x3_dense.hip)
+bool dense3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c);
 bool dense3x3_shape_ok(const rtoss_wdesc& d);
 size_t dense3x3_section_bytes(const rtoss_wdesc& d);
 rtoss_status launch_conv3x3_dense(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                   hipStream_t s);
 
 // 1x1 convolution on the dense matrix instruction (conv1x1_mma.hip)
+bool dense1x1_launch_ok(const rtoss_wdesc& d, const ConvParams& c);
 bool dense1x1_shape_ok(const rtoss_wdesc& d);
 size_t dense1x1_section_bytes(const rtoss_wdesc& d);
 rtoss_status launch_conv1x1_mma(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,

@@ -201,7 +201,7 @@ int ksplit1x1_plan(const rtoss_wdesc& d, const ConvParams& c)
     if (current_device(&dev)) return kNone;
     const int64_t cus = dev.cus, P = (int64_t)c.N * c.H * c.W;
     const auto groups = [&](int tm, int tn) { return (int64_t)((section_tiles(KS, d.Co) + tm - 1) / tm) * ((P + 16 * tn - 1) / (16 * tn)); };
-    if (P > 0x7fffff00 || groups(2, 1) > 0x3fffffff) return kNone;
+    if (P > 0x7fffff00 || groups(2, 1) > kMaxGridGroups) return kNone;
     if (d.dt == RTOSS_F32) return KS <= 8 || groups(2, 1) <= cus * 8 / 5 ? k32x16 : kNone;
     if (groups(2, 1) <= cus) return k32x16;
     if (groups(2, 2) <= cus) return k32x32;

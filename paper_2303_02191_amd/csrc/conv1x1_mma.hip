@@ -279,6 +279,13 @@ bool dense1x1_shape_ok(const rtoss_wdesc& d)
     return d.ksize == 1 && d.Ci * elem_bytes(d.dt) % 4 == 0;
 }
 
+bool dense1x1_launch_ok(const rtoss_wdesc& d, const ConvParams& c)
+{
+    if (d.dt != RTOSS_F32 && d.Ci % 32 == 0 && d.Co % 16 == 0) return true;
+    const int tiles = (d.Co + 15) / 16, per_block = tiles <= 4 ? 4 : 8;  // (a smaller block of a few-channel layer: the same number of them)
+    return ((int64_t)c.N * c.H * c.W + kTilePos - 1) / kTilePos * ((tiles + per_block - 1) / per_block) <= kMaxGridGroups;
+}
+
 size_t dense1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_section_bytes(stage_count(d)); }
 
 rtoss_status launch_conv1x1_mma(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,

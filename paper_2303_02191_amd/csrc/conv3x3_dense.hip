@@ -216,6 +216,8 @@ rtoss_status launch_shape(const rtoss_wdesc& d, const ConvParams& c, const char*
     return check_hip(hipGetLastError(), "conv3x3 dense launch");
 }
 
+inline bool ragged(const rtoss_wdesc& d) { return d.Ci % stage_channels(d.dt) || d.Co % 16; }
+
 template <typename T, typename TO, int S>
 rtoss_status launch_stride(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
@@ -223,7 +225,7 @@ rtoss_status launch_stride(const rtoss_wdesc& d, const ConvParams& c, const char
     // 16 channels x 4x16 positions (16 times as many workgroups).
     const int Ho = (c.H + 2 - 3) / S + 1, Wo = (c.W + 2 - 3) / S + 1;
     const int64_t big = (int64_t)((Ho + 15) / 16) * ((Wo + 15) / 16) * dense_channel_blocks(d.Co) * c.N;
-    if (d.Ci % stage_channels(d.dt) || d.Co % 16) return launch_shape<T, TO, S, 1, 1, 4, true>(d, c, wfrag, x, y, s);
+    if (ragged(d)) return launch_shape<T, TO, S, 1, 1, 4, true>(d, c, wfrag, x, y, s);
     if (big < 256) return launch_shape<T, TO, S, 1, 1, 4>(d, c, wfrag, x, y, s);
     return launch_shape<T, TO, S, 4, 4, 4>(d, c, wfrag, x, y, s);
 }
@@ -242,6 +244,13 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 bool dense3x3_shape_ok(const rtoss_wdesc& d)
 {
     return d.ksize == 3 && d.Ci * elem_bytes(d.dt) % 16 == 0;  // rows of whole 16-byte copies
+}
+
+bool dense3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c)
+{
+    if (!ragged(d)) return true;
+    const int Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1;  // tiles of 4x16 positions x 16 channels
+    return (int64_t)((Ho + 3) / 4) * ((Wo + 15) / 16) <= kMaxGridGroups && dense_channel_blocks(d.Co) * kTM <= 65535;
 }
 
 size_t dense3x3_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_section_bytes(stage_count(d)); }

@@ -376,6 +376,7 @@ rtoss_status launch_layout(const rtoss_wdesc& d, const ConvParams& c, int plan, 
 int ksplit3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
 {
     if (d.Ci * elem_bytes(d.dt) % 64 || d.Co % 16) return kNone;
+    if ((int64_t)c.N * c.H * c.W * d.Ci * elem_bytes(d.dt) / 16 > kMaxChunks) return kNone;  // (the dense-mode kernel has no such limit)
     DeviceInfo dev;
     if (current_device(&dev)) return kNone;
     const int64_t cus = dev.cus;

@@ -466,6 +466,14 @@ bool sparse3x3_shape_ok(const rtoss_wdesc& d)
     return d.ksize == 3 && (d.dt == RTOSS_F16 || d.dt == RTOSS_BF16) && d.Ci % 8 == 0;
 }
 
+bool sparse3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c)
+{
+    if (!ragged(d)) return true;
+    const int Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1, rows = c.stride == 1 ? 8 : 4;  // launch_typed_ragged's tiles
+    return (int64_t)c.N * c.H * c.W * d.Ci / 8 <= kMaxChunks &&
+           (int64_t)((Ho + rows - 1) / rows) * ((Wo + 15) / 16) * ((d.Co + 63) / 64) * c.N <= kMaxGridGroups;
+}
+
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout)
 {
     return fragment_bytes(d, layout) + zero_block_bytes(d);

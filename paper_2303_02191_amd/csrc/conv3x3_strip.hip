@@ -284,9 +284,20 @@ rtoss_status launch_layout(const rtoss_wdesc& d, const ConvParams& c, int plan, 
 // one round.  (bf16, layout 0, batch x channels @ image: 1x256@100x168 18.0 us with TN = 3, 23.2 with the single-buffered
 // kernel; 4x128@60x70 8.0 and 9.6; 16x128@40x40 9.2 and 10.3; 4x64@112x130 7.3 and 8.0.  Layout 1: 2x256@100x168 33.6 and
 // 40.3.  Dense mode: 36.3 and 49.0.)
+static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int layout);
+
 int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
 {
     if (c.stride != 1 || d.Ci * elem_bytes(d.dt) % 64 || d.Co % 16) return 0;
+    // (the dense-mode kernel has neither limit)
+    const int plan = plan_within_limits(d, c, layout);
+    const int rows = 4 * (plan % kTwoBuffers);
+    if (plan == 0 || (int64_t)c.N * c.H * c.W * d.Ci * elem_bytes(d.dt) / 16 > kMaxChunks) return 0;
+    return (int64_t)((c.W + kCols - 1) / kCols) * ((c.H + rows - 1) / rows) * ((d.Co + 63) / 64) * c.N <= kMaxGridGroups ? plan : 0;
+}
+
+static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int layout)
+{
     DeviceInfo dev;
     if (current_device(&dev)) return 0;
     const int64_t cus = dev.cus;

@@ -410,7 +410,7 @@ rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, P
         en->c = d.ksize == 3 ? 9 : 0;
         *blocks = live_blocks;
     }
-    if (items > 0x7fffff00 || *blocks > 0x7fffff00) return fail(RTOSS_ESHAPE, "pack: layer too large");
+    if (items > 0x7fffff00 || *blocks > kMaxGridGroups) return fail(RTOSS_ESHAPE, "pack: layer too large");
     en->items = (uint32_t)items;
     return RTOSS_OK;
 }
@@ -430,10 +430,7 @@ rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, 
                 int64_t blocks = 0;
                 if (rtoss_status st = make_entry(items[i], geo[i], layout, &tab.e[m], &blocks)) return st;
                 if (blocks == 0) continue;
-                if (total + blocks > 0x7fffff00) {
-                    if (m == 0) return fail(RTOSS_ESHAPE, "pack: layer too large");
-                    break;
-                }
+                if (total + blocks > kMaxGridGroups) break;  // (one layer fits: make_entry)
                 tab.first_block[m++] = (int)total;
                 total += blocks;
             }

@@ -1,0 +1,61 @@
+"""Calls past the launch limits of a matrix-core kernel that took its shapes over from a kernel without them: more 16-byte
+chunks than a 32-bit offset numbers, more workgroups than a grid holds.  They go where they went before."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2303_02191_amd import binding as B
+from paper_2303_02191_amd import pipeline as pl
+from paper_2303_02191_amd import workloads as wl
+
+from gpu_util import GpuLayer
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dt, N, H, W, Ci, Co, ks, stride, k
+    (wl.F16, 1, 46344, 46344, 8, 4, 3, 2, 3),       # ragged 3x3: 2^31 chunks of input
+    (wl.BF16, 65535, 1, 4112, 8, 8, 3, 1, 2),       # ... 2^24 workgroups
+    (wl.F32, 1, (1 << 26) + 64, 1, 4, 4, 3, 1, 3),  # ragged 3x3, dense mode: 2^24 workgroups
+    (wl.F16, 65535, 182, 182, 2, 1, 1, 1, 2),       # ragged 1x1: 2^24 workgroups
+    (wl.F32, 1, 2800, 3000, 64, 1024, 1, 1, 2),     # fp32 1x1: 2^24 workgroups with the input channels split over waves
+    (wl.BF16, 65535, 1, 4112, 64, 16, 3, 1, 5),     # strips of rows, dense mode: both
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "dt%d_%dx%dx%d_%d-%d_%dx%d" % (c[:6] + (c[6], c[6])))
+def test_calls_past_a_kernels_launch_limits(case):
+    dt, N, H, W, Ci, Co, ks, stride, k = case
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    torch.cuda.empty_cache()
+    need = (N * H * W * Ci + N * Ho * Wo * Co) * wl.ELEM_BYTES[dt]
+    if torch.cuda.mem_get_info()[0] < need + (4 << 30):
+        pytest.skip("needs %d GB of device memory" % (need >> 30))
+    rng = np.random.default_rng(N + H)
+    masks = B.rtoss_pattern_dict(k)
+    ws = wl.round_to_dtype(rng.standard_normal((Co, Ci, ks, ks)), dt)
+    layer = GpuLayer(ws, dt, masks, k)
+    pruned = oracle.mask(wl.to_f64(ws, dt), masks, layer.idx_host())
+    # zeros with a few islands: the first and last positions, and one in the middle (at even rows and columns)
+    x = torch.zeros((N, H, W, Ci), dtype=pl.TORCH_DTYPE[dt], device="cuda")
+    islands = []
+    for n, h, w in ((0, 0, 0), (N // 2, H // 4 * 2, W // 4 * 2), (N - 1, max(0, H - 6) // 2 * 2, max(0, W - 8) // 2 * 2)):
+        v = wl.round_to_dtype(rng.standard_normal((1, Ci, min(6, H - h), min(8, W - w))), dt)
+        x[n:n + 1, h:h + v.shape[2], w:w + v.shape[3]] = pl.to_device(wl.nchw_to_nhwc(v), dt)
+        islands.append((n, h, w, wl.to_f64(v, dt)))
+    y = layer.layer.conv(x, stride=stride)
+    nonzero = 0
+    for n, h, w, v in islands:
+        pad = [(0, 0), (0, 0), (2 * (h > 0), 2 * (h + v.shape[2] < H)), (2 * (w > 0), 2 * (w + v.shape[3] < W))]
+        ref = oracle.conv2d(np.pad(v, pad), pruned, stride=stride)  # with the zeros around it, as far as they are in the image
+        h0, w0 = (h - pad[2][0]) // stride, (w - pad[3][0]) // stride
+        got = wl.nhwc_to_nchw(pl.to_host(y[n:n + 1, h0:h0 + ref.shape[2], w0:w0 + ref.shape[3]]))
+        assert got.shape == ref.shape
+        # fp32 accumulation of at most 9 * Ci products, then the rounding of the stored value
+        bound = 1e-5 * np.max(np.abs(ref)) + np.abs(ref) * {wl.F32: 0.0, wl.F16: 2.0 ** -11, wl.BF16: 2.0 ** -8}[dt]
+        assert (np.abs(wl.to_f64(got, dt) - ref) <= bound).all()
+        nonzero += np.count_nonzero(got)
+    assert sum(int(torch.count_nonzero(part)) for part in y.flatten().split(1 << 30)) == nonzero
+    del x, y
+    torch.cuda.empty_cache()
