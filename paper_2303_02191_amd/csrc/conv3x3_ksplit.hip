@@ -216,24 +216,14 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
             }
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
-                // B operands of both sparse steps: element 4*c + f of a step = channel c (of this lane's 4), tap slot f
-                u32x8 bf[2][TN];
+                u32x8 bf[2][TN];  // B operands of both sparse steps
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     u32x4 r[4];
 #pragma unroll
                     for (int f = 0; f < 4; ++f) r[f] = x_at(j, LY.tap[g][f] >= 0 ? LY.tap[g][f] : LY.tap[g][0]);  // (empty slots weigh 0)
 #pragma unroll
-                    for (int half = 0; half < 2; ++half)
-#pragma unroll
-                        for (int p = 0; p < 2; ++p)  // channel pair of the half: one dword of each tap
-                        {
-                            const uint32_t s0 = r[0][2 * half + p], s1 = r[1][2 * half + p], s2 = r[2][2 * half + p], s3 = r[3][2 * half + p];
-                            bf[half][j][4 * p + 0] = __builtin_amdgcn_perm(s1, s0, 0x05040100u);
-                            bf[half][j][4 * p + 1] = __builtin_amdgcn_perm(s3, s2, 0x05040100u);
-                            bf[half][j][4 * p + 2] = __builtin_amdgcn_perm(s1, s0, 0x07060302u);
-                            bf[half][j][4 * p + 3] = __builtin_amdgcn_perm(s3, s2, 0x07060302u);
-                        }
+                    for (int half = 0; half < 2; ++half) bf[half][j] = sparse_operand(r, half);
                 }
 #pragma unroll
                 for (int m = 0; m < TM; ++m) {
@@ -336,8 +326,7 @@ rtoss_status launch_variant(const rtoss_wdesc& d, const ConvParams& c, const cha
     return check_hip(hipGetLastError(), "conv3x3 K-split launch");
 }
 
-// The variants, smallest tiles first.
-// Variants by number: channels x positions of a workgroup's tile.
+// Variants by number, smallest tiles first: channels x positions of a workgroup's tile.
 enum Variant { kNone = 0, k16x4x8, k32x4x8, k32x8x8, kS2_32x4x4, kS2_32x4x8, kS2_64x4x8 };
 
 template <typename T, typename TO, int LAY>
@@ -346,7 +335,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, int plan, co
     switch (plan) {
     case k16x4x8: return launch_variant<T, TO, 1, 1, 1, 2, LAY>(d, c, wf, zeros, x, y, s);
     case k32x4x8: if constexpr (LAY != kDenseTaps) return launch_variant<T, TO, 1, 2, 1, 2, LAY>(d, c, wf, zeros, x, y, s); else break;
-    case k32x8x8: if constexpr (LAY != kDenseTaps) return launch_variant<T, TO, 1, 2, 2, 2, LAY>(d, c, wf, zeros, x, y, s); else break;
+    case k32x8x8: if constexpr (LAY == 0) return launch_variant<T, TO, 1, 2, 2, 2, LAY>(d, c, wf, zeros, x, y, s); else break;
     case kS2_32x4x4: return launch_variant<T, TO, 2, 2, 1, 1, LAY>(d, c, wf, zeros, x, y, s);
     case kS2_32x4x8: if constexpr (LAY != 0) return launch_variant<T, TO, 2, 2, 1, 2, LAY>(d, c, wf, zeros, x, y, s); else break;
     case kS2_64x4x8: if constexpr (LAY == 0) return launch_variant<T, TO, 2, 4, 1, 2, LAY>(d, c, wf, zeros, x, y, s); else break;
@@ -406,8 +395,8 @@ int ksplit3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
     if (c.stride == 1) {
         if (groups(1, 4, 8) <= cus) return k16x4x8;
         if (groups(2, 4, 8) <= 2 * cus) return k32x4x8;
-        // (layout 1 has larger fragments: one workgroup per compute unit)
-        return stages >= 2 && groups(2, 8, 8) <= (layout == 0 ? 2 : 1) * cus ? k32x8x8 : kNone;
+        // (layout 1 has larger fragments: one workgroup per compute unit, and what fits in one round was taken above)
+        return layout == 0 && stages >= 2 && groups(2, 8, 8) <= 2 * cus ? k32x8x8 : kNone;
     }
     if (groups(2, 4, 4) <= (layout == 0 && stages >= 2 ? 2 : 1) * cus) return kS2_32x4x4;
     if (layout == 0) return stages >= 3 && groups(4, 4, 8) <= cus ? kS2_64x4x8 : kNone;

@@ -30,9 +30,10 @@
 // (8 channels of one tap) and the 4x4 (tap, channel) blocks are transposed in registers
 // with byte permutes so that one lane holds, for 4 channels, the 4 taps of a group.
 //
-// This file holds the single-buffered kernel (stride 2, and stride-1 layers with few channels or
-// few tiles): a plain loop nest with small tiles, several workgroups per compute unit.  Large stride-1 layers
-// take the pipelined kernel of conv3x3_rows.hip, which reads the same packed section.
+// This file holds the single-buffered kernel (stride 2, ragged channel counts, and stride-1 layers of up to 64 input or
+// output channels in launches of many rounds): a plain loop nest with small tiles, several workgroups per compute unit.
+// Large stride-1 layers take the pipelined kernel of conv3x3_rows.hip, launches of medium size the strips of
+// conv3x3_strip.hip, and those that cannot fill the chip conv3x3_ksplit.hip; all read the same packed section.
 #include <algorithm>
 #include <type_traits>
 
@@ -203,31 +204,12 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
 #pragma unroll
             for (int m = 0; m < TM; ++m) load_group_a(group, m);
         };
-        // B operands of both sparse steps of a tap group: element 4*c + f of a step = channel c (of this
-        // lane's 4), tap slot f
-        u32x8 bf[2][TN];
+        u32x8 bf[2][TN];  // B operands of both sparse steps of a tap group
         auto permute_group = [&](int group) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const u32x4(&r)[4] = rr[group][j];
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const uint32_t s0 = half ? r[0].z : r[0].x, s1 = half ? r[1].z : r[1].x;
-                    const uint32_t s2 = half ? r[2].z : r[2].x, s3 = half ? r[3].z : r[3].x;
-                    const uint32_t u0 = half ? r[0].w : r[0].y, u1 = half ? r[1].w : r[1].y;
-                    const uint32_t u2 = half ? r[2].w : r[2].y, u3 = half ? r[3].w : r[3].y;
-                    u32x8 b;
-                    b[0] = __builtin_amdgcn_perm(s1, s0, 0x05040100u);  // channel 0: taps 0,1
-                    b[1] = __builtin_amdgcn_perm(s3, s2, 0x05040100u);  // channel 0: taps 2,3
-                    b[2] = __builtin_amdgcn_perm(s1, s0, 0x07060302u);  // channel 1
-                    b[3] = __builtin_amdgcn_perm(s3, s2, 0x07060302u);
-                    b[4] = __builtin_amdgcn_perm(u1, u0, 0x05040100u);  // channel 2
-                    b[5] = __builtin_amdgcn_perm(u3, u2, 0x05040100u);
-                    b[6] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);  // channel 3
-                    b[7] = __builtin_amdgcn_perm(u3, u2, 0x07060302u);
-                    bf[half][j] = b;
-                }
-            }
+                for (int half = 0; half < 2; ++half) bf[half][j] = sparse_operand(rr[group][j], half);
         };
         auto multiply_group = [&](int group, int m) {
 #pragma unroll
@@ -420,8 +402,8 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
         // (up to 64 input channels are one or two stages: nothing to gain inside a workgroup, see AHEAD; one buffer,
         // four workgroups per compute unit)
         if (d.Ci <= 64) return launch_variant_sb<T, TO, 1, 4, 2, 2, 4, false>(d, c, wfrag, x, y, s);
-        // deeper layers: two buffers per workgroup (still two workgroups per compute unit); also the launches that
-        // would leave compute units idle with the pipelined kernel's 128 channels per workgroup
+        // deeper layers of up to 64 output channels, in launches of several rounds (smaller ones: conv3x3_ksplit.hip,
+        // conv3x3_strip.hip): two buffers per workgroup, still two workgroups per compute unit
         return launch_variant_sb<T, TO, 1, 4, 2, 2, 4, true, 0, true>(d, c, wfrag, x, y, s);
     }
     // Stride 2: an output position needs four input positions, so the activation tile dominates the LDS and the

@@ -158,24 +158,13 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
                 }
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    // B operands of both sparse steps: element 4*c + f of a step = channel c (of this lane's 4), tap slot f
                     u32x4 r[4];
 #pragma unroll
                     for (int f = 0; f < 4; ++f) {
                         const int t = LY.tap[g][f] >= 0 ? LY.tap[g][f] : LY.tap[g][0];  // (an empty slot weighs 0)
                         r[f] = R[j + t / 3][t % 3];
                     }
-                    u32x8 b[2];
-#pragma unroll
-                    for (int half = 0; half < 2; ++half)
-#pragma unroll
-                        for (int p = 0; p < 2; ++p) {
-                            const int d = 2 * half + p;
-                            b[half][4 * p + 0] = __builtin_amdgcn_perm(r[1][d], r[0][d], 0x05040100u);
-                            b[half][4 * p + 1] = __builtin_amdgcn_perm(r[3][d], r[2][d], 0x05040100u);
-                            b[half][4 * p + 2] = __builtin_amdgcn_perm(r[1][d], r[0][d], 0x07060302u);
-                            b[half][4 * p + 3] = __builtin_amdgcn_perm(r[3][d], r[2][d], 0x07060302u);
-                        }
+                    const u32x8 b[2] = {sparse_operand(r, 0), sparse_operand(r, 1)};
 #pragma unroll
                     for (int m = 0; m < kTM; ++m)
                         acc[m][j] = Sparse64<T>::template mma<0>(a[m][0], b[0], FIRST && !LY.centre && g == 0 ? none : acc[m][j], idx[m]);
@@ -256,8 +245,8 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, int plan, c
 {
     switch (plan) {
     case 2: return launch_rows<T, TO, 2, LAY, false>(d, c, wf, zeros, x, y, s);
-    case 3: return launch_rows<T, TO, 3, LAY, false>(d, c, wf, zeros, x, y, s);
-    case 4: return launch_rows<T, TO, 4, LAY, false>(d, c, wf, zeros, x, y, s);
+    case 3: if constexpr (LAY != 0) return launch_rows<T, TO, 3, LAY, false>(d, c, wf, zeros, x, y, s); else break;
+    case 4: if constexpr (sizeof(T) == 2) return launch_rows<T, TO, 4, LAY, false>(d, c, wf, zeros, x, y, s); else break;
     case 5: if constexpr (LAY != 0) return launch_rows<T, TO, 5, LAY, false>(d, c, wf, zeros, x, y, s); else break;
     case 2 + kTwoBuffers: if constexpr (sizeof(T) == 2) return launch_rows<T, TO, 2, LAY, true>(d, c, wf, zeros, x, y, s); else break;
     case 3 + kTwoBuffers: if constexpr (LAY == 0) return launch_rows<T, TO, 3, LAY, true>(d, c, wf, zeros, x, y, s); else break;
@@ -312,7 +301,7 @@ static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int lay
         if (tiles < cus) return 0;
         int best = 0;
         int64_t rows = (tiles + cus - 1) / cus * 4;
-        for (int tn = 5; tn >= 2; --tn) {
+        for (const int tn : {5, 3, 2}) {  // (4: the dense-mode kernel's own height)
             const int64_t r = (groups(tn) + cus - 1) / cus * tn;
             if (r < rows) best = tn, rows = r;
         }

@@ -36,7 +36,7 @@ struct PackEntry {
     uint32_t idx_off, mat_off;  // sections of the blob, in units of 256 bytes
     int Co, Ci;
     uint32_t items;             // 3x3: (stage, channel tile) pairs; 1x1 and stem: 16-byte pieces of the fragments
-    uint8_t format, a, b, c;    // MatrixFormat; 3x3: tap layout; streaming 1x1: KS, MT, WM
+    uint8_t format, a, b, c;    // MatrixFormat; 3x3: tap layout; streaming 1x1: KS, MT; without fragments: weights per kernel
 };
 constexpr int kPackMax = 60;
 struct PackTable {
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
         return;
     }
     // other formats: first the public section, 256 groups per block
-    const int ks2 = en.format == kFormatStem || en.c == 9 ? 9 : 1;  // (c of a layer without fragments: weights per kernel)
+    const int ks2 = en.format == kFormatStem || en.c == 9 ? 9 : 1;
     LiveJob job;
     job.G = (int64_t)en.Co * en.Ci * ks2 / 9;
     job.blocks = (int)((job.G + 255) / 256);
@@ -345,13 +345,12 @@ __global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
     int f = item / 64;
     if (en.format == kFormatDenseStream) {
         // rows permuted so that a lane's 4*MT accumulator values are consecutive channels
-        const int KS = en.a, MT = en.b, WM = en.c;
+        const int KS = en.a, MT = en.b;
         const int s = f % KS;
         f /= KS;
         const int m = f % MT;
         f /= MT;
         const int co = f * (16 * MT) + (r / 4) * (4 * MT) + 4 * m + (r % 4);  // (f: channel block and wave slice)
-        (void)WM;
         *(u32x4*)(section + (size_t)item * 16) = pack_piece1x1<T>(w, en.idx, masks, en.Co, en.Ci, co, 4 * PER * s + PER * q);
     } else if (en.format == kFormatDense) {
         const int m_tiles = (int)en.items / (64 * stages);
@@ -393,7 +392,6 @@ rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, P
         const int KS = stages, MT = stream_mt_of(KS), WM = stream_wm_of(KS, d.Co);
         en->a = (uint8_t)KS;
         en->b = (uint8_t)MT;
-        en->c = (uint8_t)WM;
         items = (int64_t)stream_co_blocks_of(KS, d.Co) * WM * MT * KS * 64;
         *blocks = live_blocks + (items + zero_section_bytes(stages) / 16 + 255) / 256;
         break;

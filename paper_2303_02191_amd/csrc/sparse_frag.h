@@ -2,6 +2,7 @@
 // sparse matrix instruction stream (conv3x3_sparse.hip, conv3x3_rows.hip).
 #pragma once
 #include "common.h"
+#include "mma.h"
 
 namespace rtoss {
 
@@ -49,6 +50,22 @@ __device__ __forceinline__ int tile_row_channel(int mt, int r)
 __device__ __forceinline__ int tile_quarter_offset(int mm, int q)
 {
     return 64 * (mm >> 2) + 16 * q + 4 * (mm & 3);
+}
+
+// B operand of a sparse step from 16-byte reads of the group's four taps (8 channels each): element 4*c + f = channel c of
+// the step's four, tap slot f.  A 4x4 (tap, channel) transposition of byte pairs.  `half`: channels 0-3 or 4-7 of the reads.
+__device__ __forceinline__ u32x8 sparse_operand(const u32x4 (&r)[4], int half)
+{
+    u32x8 b;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {  // channel pair: one dword of each tap
+        const int d = 2 * half + p;
+        b[4 * p + 0] = __builtin_amdgcn_perm(r[1][d], r[0][d], 0x05040100u);  // first channel: taps 0,1
+        b[4 * p + 1] = __builtin_amdgcn_perm(r[3][d], r[2][d], 0x05040100u);  // ... taps 2,3
+        b[4 * p + 2] = __builtin_amdgcn_perm(r[1][d], r[0][d], 0x07060302u);  // second channel
+        b[4 * p + 3] = __builtin_amdgcn_perm(r[3][d], r[2][d], 0x07060302u);
+    }
+    return b;
 }
 
 // Channel tiles per stage in the packed section: padded so that every block of 8 tiles is complete.
