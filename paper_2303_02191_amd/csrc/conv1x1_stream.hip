@@ -28,7 +28,8 @@
 // fp32 tensors run through the same kernel: a stage is then 16 channels (the same 64 bytes per position) and
 // a fragment step is four v_mfma_f32_16x16x4_f32, instruction s on element s of every lane's 16 bytes.  The
 // fp32 instruction has 1/16 of the 16-bit one's rate, so these layers sit near the ridge instead of far below
-// it; measured 128 -> 64 channels on 25 600 positions: 8.8-11 us, against 32 us on the vector ALUs.
+// it: 128 -> 128 channels on 102 400 positions 43.7 us = 77 TFLOP/s, zeros included (smaller launches:
+// conv1x1_ksplit.hip).
 //
 // Operand layout of v_mfma_f32_16x16x32 (wave64; r = lane % 16, q = lane / 16): A lane holds
 // row r, K = 8q..8q+7; B lane holds column r, K = 8q..8q+7; D lane holds column r, rows 4q..4q+3.
@@ -274,6 +275,9 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv1x1 shared memory attribute")) return st;
     // Persistent workgroups: as many as are resident at once, but no fewer than 2 buffers each: every
     // workgroup loads its weight fragments once, which for deep layers is more bytes than a buffer.
+    // fp32 steps take 16 times as long: there a launch that gives most compute units one workgroup or none is spread over
+    // all of them, one buffer each (us with one buffer and with two, positions in brackets: 16 -> 16 (12 800) 2.8 and 3.2,
+    // 32 -> 128 (6400) 4.1 and 4.5, 256 -> 64 (6400) 5.7 and 8.2; past that 32 -> 128 (25 600) 9.3 and 8.4).
     // (workgroups per compute unit depend on the instantiation's registers and LDS only: asked once; the
     // number of compute units is the current device's)
     static std::atomic<int> per_cu_cached{0};  // per instantiation
@@ -285,8 +289,8 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     DeviceInfo dev;
     if (rtoss_status st = current_device(&dev)) return st;
     const int resident = std::max(8, dev.cus) * per_cu;
-    // (fp32 steps take 16 times as long: one buffer is enough work to be worth the fragments)
-    const int64_t by_work = sizeof(T) == 4 ? nbuf : std::max<int64_t>(1, (nbuf + 1) / 2);
+    const bool spread = sizeof(T) == 4 && 2 * nbuf * co_blocks <= 3 * dev.cus;
+    const int64_t by_work = spread ? nbuf : std::max<int64_t>(1, (nbuf + 1) / 2);
     const int wgs_per_cb = (int)std::max<int64_t>(1, std::min<int64_t>(by_work, resident / co_blocks));
     const int total = wgs_per_cb * co_blocks;
     const int work_per_xcd = (total + 7) / 8;
