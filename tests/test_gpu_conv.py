@@ -70,8 +70,8 @@ def test_conv_small_shapes(dt, case):
 
 
 MATRIX_CORE = [
-    # shapes that take the matrix-core path (Ci % 32 == 0, Co % 16 == 0, 16-bit types):
-    # ragged tiles, several channel blocks, odd extents, batch > 1
+    # 16-bit layers of whole stages and channel tiles, stride 1 and 2: ragged position tiles, several channel
+    # blocks, odd extents, batch > 1 (variants.py holds a call for every kernel variant)
     # N, Ci, Co,  H,  W, stride, k, relu
     (1, 32, 16, 4, 4, 1, 3, False),
     (1, 32, 16, 5, 7, 1, 2, True),
@@ -85,8 +85,7 @@ MATRIX_CORE = [
     (1, 128, 256, 40, 40, 2, 3, False),
     (1, 32, 32, 1, 1, 1, 3, False),
     (1, 32, 32, 2, 70, 2, 2, False),
-    # enough 16x16 tiles for two rounds over the compute units but one round of 20x16 tiles: the
-    # launcher takes the tall tile (5 position blocks per wave), here with ragged rows and columns
+    # launches of medium size (strips of output rows), ragged rows and columns
     (43, 128, 48, 37, 30, 1, 3, True),
     (130, 160, 16, 21, 16, 1, 2, False),
     # the pipelined kernel (more than 64 channels in and out, at least 200 tiles of 16x16 positions x 128
@@ -105,8 +104,8 @@ def test_conv3x3_matrix_core_shapes(dt, case):
 
 
 DENSE_MODE = [
-    # dictionaries with three corners or three edge midpoints in one pattern: dense mode on the matrix
-    # cores (every tap a dense step, pruned weights explicit zeros)
+    # dictionaries with three corners or three edge midpoints in one pattern: three tap groups where they fit
+    # (the 4-entry edge-connected patterns), else dense mode (every tap a dense step, pruned weights explicit zeros)
     # N, Ci, Co,  H,  W, stride, k, rule, relu
     (1, 32, 16, 4, 4, 1, 4, B.RULE_CONNECTED4, False),
     (2, 96, 48, 19, 21, 1, 4, B.RULE_CONNECTED4, True),
@@ -130,7 +129,7 @@ def test_conv3x3_dense_mode_shapes(dt, case):
 THREE_GROUP_LAYOUT = [
     # 4-entry edge-connected patterns: the T shapes keep three edge midpoints, so the corner / edge-midpoint split
     # does not fit them; the taps are laid out as three 2-of-4 groups {0,4,8}, {1,5,6}, {2,3,7} instead (6 sparse
-    # steps per 32 channels, no dense step).  Shapes for every tile variant of that path.
+    # steps per 32 channels, no dense step).
     # N, Ci, Co,  H,  W, stride, relu
     (1, 32, 16, 5, 7, 1, True),
     (2, 64, 144, 33, 18, 1, False),
@@ -178,7 +177,7 @@ def test_conv3x3_matrix_core_dictionaries():
     run_case(wl.F16, 1, 64, 64, 12, 12, 3, 1, 2, False, seed=31, rule=B.RULE_ALL)
     # single-tap patterns
     run_case(wl.BF16, 1, 32, 32, 9, 9, 3, 1, 1, False, seed=32)
-    # 4-entry connected patterns include a T shape with 3 edge midpoints -> dense mode
+    # 4-entry connected patterns include a T shape with 3 edge midpoints -> three tap groups
     run_case(wl.F16, 1, 64, 64, 12, 12, 3, 1, 4, False, seed=33)
     # identical weights in every kernel: every kernel picks pattern 0 (ties) -> coherent tiles
     masks = B.rtoss_pattern_dict(3)
@@ -203,8 +202,8 @@ MATRIX_CORE_1X1 = [
     (2, 512, 128, 20, 20, 2, False),
     (1, 288, 64, 6, 7, 3, False),  # Ci % 9 == 0: groups never straddle rows
     (1, 96, 32, 13, 11, 2, True),  # Ci / 32 not a power of two: ring kernel with weights in LDS
-    # streaming kernel (Ci = 32 * 2^n): every (depth, wave split) variant, many buffers per workgroup,
-    # ragged last buffer, channel counts that do not fill the workgroup's channel span
+    # Ci = 32 * 2^n: every depth, many buffers per workgroup, ragged last buffer, channel counts that do not fill the
+    # workgroup's channel span (streaming kernel up to 64 channels, the channel split beyond at these sizes)
     (4, 64, 32, 40, 37, 2, False),
     (2, 32, 64, 50, 33, 2, True),
     (1, 32, 256, 30, 30, 3, False),

@@ -15,24 +15,35 @@ from gpu_util import GpuLayer
 
 pytestmark = pytest.mark.gpu
 
-# dt, N, Ci, Co, H, W, ks, stride, k, rule: one case per kernel family and shape class
+# kernel (test_routes.py checks it), dt, N, Ci, Co, H, W, ks, stride, k, rule: one case per kernel family and shape class
 CASES = [
-    (wl.BF16, 13, 128, 128, 52, 50, 3, 1, 3, B.RULE_CONNECTED4),  # pipelined sparse kernel (>= 200 tiles of 16x16 x 128 channels)
-    (wl.F16, 7, 256, 272, 33, 49, 3, 1, 2, B.RULE_CONNECTED4),    # ... ragged tiles, padded channel block
-    (wl.BF16, 1, 128, 128, 20, 24, 3, 1, 3, B.RULE_CONNECTED4),   # single-buffered sparse kernel, deep layer
-    (wl.F16, 2, 64, 48, 19, 21, 3, 1, 3, B.RULE_CONNECTED4),      # single-buffered sparse kernel, stride 1
-    (wl.BF16, 1, 128, 144, 37, 41, 3, 2, 2, B.RULE_CONNECTED4),   # ... stride 2
-    (wl.F16, 1, 64, 80, 18, 20, 3, 1, 4, B.RULE_CONNECTED4),      # dense mode
-    (wl.BF16, 1, 96, 64, 21, 9, 3, 2, 5, B.RULE_CONNECTED4),      # dense mode, stride 2
-    (wl.F16, 2, 3, 32, 33, 35, 3, 2, 2, B.RULE_CONNECTED4),       # stem
-    (wl.F16, 3, 64, 32, 23, 17, 1, 1, 2, B.RULE_CONNECTED4),      # 1x1 streaming kernel, waves over positions
-    (wl.BF16, 2, 256, 256, 15, 13, 1, 1, 2, B.RULE_CONNECTED4),   # ... waves over channels
-    (wl.F16, 1, 512, 128, 11, 10, 1, 1, 3, B.RULE_CONNECTED4),    # ... two fragments per wave
-    (wl.F16, 1, 1024, 80, 7, 9, 1, 1, 2, B.RULE_CONNECTED4),      # ... one fragment per wave, padded channels
-    (wl.BF16, 1, 96, 48, 13, 11, 1, 1, 2, B.RULE_CONNECTED4),     # 1x1 ring kernel
-    (wl.F32, 1, 16, 24, 14, 15, 3, 1, 4, B.RULE_CONNECTED4),      # direct kernel, fp32
-    (wl.F16, 1, 24, 40, 9, 10, 3, 2, 3, B.RULE_CONNECTED4),       # direct kernel, odd channel counts
-    (wl.F32, 2, 40, 24, 8, 9, 1, 1, 2, B.RULE_CONNECTED4),        # direct kernel, 1x1
+    ("conv3x3_rows", wl.BF16, 13, 128, 128, 52, 50, 3, 1, 3, B.RULE_CONNECTED4),  # (>= 200 tiles of 16x16 x 128 channels)
+    ("conv3x3_rows", wl.F16, 7, 256, 272, 33, 49, 3, 1, 2, B.RULE_CONNECTED4),    # ragged tiles, padded channel block
+    ("conv3x3_ksplit", wl.BF16, 1, 128, 128, 20, 24, 3, 1, 3, B.RULE_CONNECTED4),
+    ("conv3x3_ksplit", wl.F16, 2, 64, 48, 19, 21, 3, 1, 3, B.RULE_CONNECTED4),
+    ("conv3x3_ksplit", wl.BF16, 1, 128, 144, 37, 41, 3, 2, 2, B.RULE_CONNECTED4),  # stride 2
+    ("conv3x3_ksplit", wl.F16, 1, 64, 80, 18, 20, 3, 1, 4, B.RULE_CONNECTED4),     # three tap groups
+    ("conv3x3_ksplit", wl.BF16, 1, 96, 64, 21, 9, 3, 2, 5, B.RULE_CONNECTED4),     # one step per tap, stride 2
+    ("conv3x3_sparse_sb", wl.F16, 17, 32, 16, 87, 83, 3, 1, 3, B.RULE_CONNECTED4),   # one buffer, one stage
+    ("conv3x3_sparse_sb", wl.BF16, 17, 96, 16, 83, 87, 3, 1, 2, B.RULE_CONNECTED4),  # two buffers
+    ("conv3x3_sparse_sb", wl.F16, 17, 32, 80, 19, 21, 3, 2, 3, B.RULE_CONNECTED4),   # stride 2
+    ("conv3x3_sparse_sb", wl.BF16, 17, 64, 144, 21, 19, 3, 2, 4, B.RULE_CONNECTED4),  # ... three tap groups
+    ("conv3x3_strip", wl.F16, 17, 64, 80, 19, 21, 3, 1, 3, B.RULE_CONNECTED4),
+    ("conv3x3_dense", wl.BF16, 2, 32, 80, 18, 21, 3, 1, 5, B.RULE_CONNECTED4),
+    ("conv3x3_dense", wl.F16, 17, 32, 80, 17, 19, 3, 2, 5, B.RULE_CONNECTED4),
+    ("conv3x3_stem", wl.F16, 2, 3, 32, 33, 35, 3, 2, 2, B.RULE_CONNECTED4),
+    ("conv1x1_stream", wl.F16, 3, 64, 32, 23, 17, 1, 1, 2, B.RULE_CONNECTED4),     # waves over positions
+    ("conv1x1_stream", wl.BF16, 9, 256, 464, 13, 21, 1, 1, 2, B.RULE_CONNECTED4),  # ... over channels
+    ("conv1x1_stream", wl.F16, 2, 512, 464, 23, 45, 1, 1, 3, B.RULE_CONNECTED4),   # two fragments per wave
+    ("conv1x1_stream", wl.F16, 6, 1024, 400, 13, 17, 1, 1, 2, B.RULE_CONNECTED4),  # one fragment per wave, padded channels
+    ("conv1x1_ksplit", wl.BF16, 2, 256, 256, 15, 13, 1, 1, 2, B.RULE_CONNECTED4),
+    ("conv1x1_ksplit", wl.F16, 1, 512, 128, 11, 10, 1, 1, 3, B.RULE_CONNECTED4),
+    ("conv1x1_ksplit", wl.F16, 1, 1024, 80, 7, 9, 1, 1, 2, B.RULE_CONNECTED4),
+    ("conv1x1_mma", wl.BF16, 1, 96, 48, 13, 11, 1, 1, 2, B.RULE_CONNECTED4),
+    ("conv3x3_dense", wl.F32, 1, 16, 24, 14, 15, 3, 1, 4, B.RULE_CONNECTED4),      # ragged channels out, fp32
+    ("conv3x3_sparse_sb", wl.F16, 1, 24, 40, 9, 10, 3, 2, 3, B.RULE_CONNECTED4),   # ragged channels
+    ("conv1x1_mma", wl.F32, 2, 40, 24, 8, 9, 1, 1, 2, B.RULE_CONNECTED4),          # ragged channels, fp32
+    ("conv_direct", wl.F32, 1, 3, 16, 14, 15, 3, 1, 4, B.RULE_CONNECTED4),
 ]
 STAGES = [
     dict(scale=True, bias=True, act=B.ACT_SILU, residual=True),
@@ -54,10 +65,10 @@ def _tolerance(ref, dt, out_dt):
 
 @pytest.mark.parametrize("stage", STAGES, ids=lambda s: "%s%s%d%s" % ("s" if s["scale"] else "-", "b" if s["bias"] else "-",
                                                                       s["act"], "r" if s["residual"] else "-"))
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "dt%d_%dx%d_k%d_s%d_%d-%d" % (c[0], c[6], c[6], c[8], c[7], c[2], c[3]))
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_dt%d_%dx%d_k%d_s%d_%d-%d" % (c[0], c[1], c[7], c[7], c[9], c[8], c[3], c[4]))
 def test_fused_output_stage(case, stage):
-    dt, N, Ci, Co, H, W, ks, stride, k, rule = case
-    rng = np.random.default_rng(zlib.crc32(repr((case, sorted(stage.items()))).encode()))  # the same inputs in every process
+    _, dt, N, Ci, Co, H, W, ks, stride, k, rule = case
+    rng = np.random.default_rng(zlib.crc32(repr((case[1:], sorted(stage.items()))).encode()))  # the same inputs in every process
     masks = B.rtoss_pattern_dict(k, rule)
     xs = wl.round_to_dtype(rng.standard_normal((N, Ci, H, W)), dt)
     ws = wl.round_to_dtype(rng.standard_normal((Co, Ci, ks, ks)) * (0.4 / np.sqrt(Ci)), dt)
@@ -102,29 +113,34 @@ def test_fused_relu_equals_the_plain_call_bit_for_bit():
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
-# dt, N, Ci, Co_a, Co_b, H, W, ks, stride, k: two layers over one input write the two channel slices of one buffer
+# kernels, dt, N, Ci, Co_a, Co_b, H, W, ks, stride, k: two layers over one input write the two channel slices of one buffer
 CONCAT_CASES = [
-    (wl.BF16, 13, 128, 128, 64, 52, 50, 3, 1, 3),   # pipelined sparse kernel + single-buffered sparse kernel
-    (wl.F16, 2, 64, 48, 16, 19, 21, 3, 1, 3),       # single-buffered sparse kernel, stride 1
-    (wl.BF16, 1, 128, 144, 32, 37, 41, 3, 2, 2),    # ... stride 2
-    (wl.F16, 1, 64, 80, 48, 18, 20, 3, 1, 4),       # dense mode
-    (wl.F16, 2, 3, 32, 16, 33, 35, 3, 2, 2),        # stem
-    (wl.F16, 3, 64, 32, 64, 23, 17, 1, 1, 2),       # 1x1 streaming kernel
-    (wl.BF16, 2, 256, 256, 128, 15, 13, 1, 1, 2),   # ... waves over channels
-    (wl.BF16, 1, 96, 48, 16, 13, 11, 1, 1, 2),      # 1x1 ring kernel
-    (wl.F32, 1, 16, 24, 8, 14, 15, 3, 1, 4),        # direct kernel, fp32
-    (wl.F16, 1, 24, 40, 8, 9, 10, 3, 2, 3),         # direct kernel, odd channel counts
+    ("conv3x3_rows+conv3x3_strip", wl.BF16, 13, 128, 128, 64, 52, 50, 3, 1, 3),
+    ("conv3x3_ksplit+conv3x3_ksplit", wl.F16, 2, 64, 48, 16, 19, 21, 3, 1, 3),
+    ("conv3x3_ksplit+conv3x3_ksplit", wl.BF16, 1, 128, 144, 32, 37, 41, 3, 2, 2),
+    ("conv3x3_ksplit+conv3x3_ksplit", wl.F16, 1, 64, 80, 48, 18, 20, 3, 1, 4),
+    ("conv3x3_sparse_sb+conv3x3_sparse_sb", wl.F16, 17, 32, 48, 16, 87, 83, 3, 1, 3),  # stride 1
+    ("conv3x3_sparse_sb+conv3x3_sparse_sb", wl.BF16, 17, 32, 80, 144, 19, 21, 3, 2, 2),  # stride 2
+    ("conv3x3_dense+conv3x3_dense", wl.F16, 2, 32, 80, 48, 18, 20, 3, 1, 5),
+    ("conv3x3_stem+conv3x3_stem", wl.F16, 2, 3, 32, 16, 33, 35, 3, 2, 2),
+    ("conv1x1_stream+conv1x1_stream", wl.F16, 3, 64, 32, 64, 23, 17, 1, 1, 2),
+    ("conv1x1_stream+conv1x1_stream", wl.BF16, 9, 256, 464, 528, 13, 21, 1, 1, 2),  # waves over channels
+    ("conv1x1_ksplit+conv1x1_ksplit", wl.BF16, 2, 256, 256, 128, 15, 13, 1, 1, 2),
+    ("conv1x1_mma+conv1x1_mma", wl.BF16, 1, 96, 48, 16, 13, 11, 1, 1, 2),
+    ("conv3x3_dense+conv3x3_dense", wl.F32, 1, 16, 24, 8, 14, 15, 3, 1, 4),  # ragged channels out, fp32
+    ("conv3x3_sparse_sb+conv3x3_sparse_sb", wl.F16, 1, 24, 40, 8, 9, 10, 3, 2, 3),  # ragged channels
+    ("conv_direct+conv_direct", wl.F32, 1, 3, 16, 8, 14, 15, 3, 1, 4),
 ]
 
 
-@pytest.mark.parametrize("case", CONCAT_CASES, ids=lambda c: "dt%d_%dx%d_s%d_%d-%d+%d" % (c[0], c[7], c[7], c[8], c[2], c[3], c[4]))
+@pytest.mark.parametrize("case", CONCAT_CASES, ids=lambda c: "%s_dt%d_s%d_%d-%d+%d" % (c[0], c[1], c[9], c[3], c[4], c[5]))
 def test_two_layers_write_one_concatenation(case):
     """Section V.C times whole detectors, whose blocks concatenate branch outputs along channels: two
     convolutions write their channel slices of one channels-last buffer (y_ld = the buffer's channel count),
     the second adding a shortcut read from a slice of another wide buffer (residual_ld).  Both slices are
     compared with the oracle and the channels between and around them must keep their sentinel."""
-    dt, N, Ci, Ca, Cb, H, W, ks, stride, k = case
-    rng = np.random.default_rng(zlib.crc32(repr(case).encode()))
+    _, dt, N, Ci, Ca, Cb, H, W, ks, stride, k = case
+    rng = np.random.default_rng(zlib.crc32(repr(case[1:]).encode()))
     masks = B.rtoss_pattern_dict(k)
     xs = wl.round_to_dtype(rng.standard_normal((N, Ci, H, W)), dt)
     xv = wl.to_f64(xs, dt)
@@ -161,11 +177,11 @@ def test_two_layers_write_one_concatenation(case):
             assert err <= _tolerance(ref, dt, out_dt), (err, _tolerance(ref, dt, out_dt), out_dt)
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "dt%d_%dx%d_k%d_s%d_%d-%d" % (c[0], c[6], c[6], c[8], c[7], c[2], c[3]))
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_dt%d_%dx%d_k%d_s%d_%d-%d" % (c[0], c[1], c[7], c[7], c[9], c[8], c[3], c[4]))
 def test_silu_of_chosen_values(case):
     """With activations of zero the output stage's argument is the bias: SiLU over the whole range of fp32, where the
     correction of the reciprocal takes over from the division and beyond, and one rounding for 16-bit results."""
-    dt, N, Ci, Co, H, W, ks, stride, k, rule = case
+    _, dt, N, Ci, Co, H, W, ks, stride, k, rule = case
     rng = np.random.default_rng(Ci + Co)
     ends = np.array([0.0, 1e-45, -1e-45, 1e-38, -1e-38, 1e-30, 1.0, -1.0, 79.99999, 80.0, 80.00001, -79.99999, -80.0, -80.00001, -87.0,
                      -87.5, -88.5, -89.0, -104.0, -3e38, 3e38, np.inf, -np.inf, np.nan, 16.7, -16.7, 104.0, -60.0])

@@ -41,7 +41,7 @@ def test_ragged_channel_counts(dt, case):
 
 
 FP32_1X1 = [
-    # streaming kernel (Ci = 16 * 2^n up to 512): N, Ci, Co, H, W, k, relu
+    # Ci = 16 * 2^n up to 512 (streaming kernel, from 64 on the channel split at these sizes): N, Ci, Co, H, W, k, relu
     (1, 16, 16, 1, 1, 2, False),
     (2, 32, 48, 11, 12, 3, True),
     (1, 64, 128, 33, 31, 2, False),

@@ -1,0 +1,76 @@
+"""The dispatch, replayed without a GPU: tests/variants.py names the kernel each of its calls launches, and together they
+launch every convolution kernel the library holds, so that a change of a rule cannot empty a GPU test unnoticed."""
+import pytest
+
+from paper_2303_02191_amd import binding as B
+from paper_2303_02191_amd import workloads as wl
+
+import routes
+import test_gpu_fused
+import test_gpu_ksplit
+import test_gpu_ksplit1x1
+import test_gpu_launch_limits
+import test_gpu_strip
+from variants import VARIANTS
+
+
+def call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, fused, coherent=False, rule=B.RULE_CONNECTED4):
+    return (dt, N, Ci, Co, H, W, ks, stride, k, rule, out_dt, int(fused), int(coherent))
+
+
+def split(kernel):
+    """'conv3x3_strip<f16,f32,3,0,true>' -> ('conv3x3_strip<3,0,true>', 'f16')"""
+    name, args = kernel[:-1].split("<")
+    args = args.split(",")
+    types = [a for a in args if a in ("f32", "f16", "bf16")]
+    return "%s<%s>" % (name, ",".join(a for a in args if a not in types)), types[0]
+
+
+def test_every_variant_is_reached_where_the_list_says():
+    calls, want = [], []
+    for kernel, dt, N, Ci, Co, H, W, ks, stride, k, fused, coherent in VARIANTS:
+        for out_dt in ([dt] if kernel == "conv3x3_gather_rows<>" or dt == wl.F32 else [wl.F32, dt]):
+            calls.append(call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, fused, coherent))
+            want.append((kernel, wl.DTYPE_NAMES[dt]))
+    got = [split(k) for k in routes.kernels(calls)]
+    assert [(c, g) for c, g, w in zip(calls, got, want) if g != w] == []
+
+
+def test_the_list_covers_the_library():
+    held = {(name, "f32" if dt == "f32" else "16-bit") for name, dt in map(split, routes.library_kernels("conv"))}
+    listed = {(v[0], "f32" if v[1] == wl.F32 else "16-bit") for v in VARIANTS}
+    held.discard(("conv_direct<1,1,0>", "f32"))  # NCHW tensors only
+    assert held == listed
+
+
+def families(kernels):
+    return [k if isinstance(k, int) else k.split("<")[0] for k in kernels]
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_cases_made_for_a_kernel_reach_it(fused):
+    for cases, kernel in ((test_gpu_strip.CASES, "conv3x3_strip"), (test_gpu_ksplit.CASES, "conv3x3_ksplit")):
+        calls = [call(c[0], *c[1:6], 3, c[6] if len(c) == 8 else 1, c[-1], wl.F32, fused) for c in cases]
+        assert families(routes.kernels(calls)) == [kernel] * len(cases)
+    calls = [call(dt, N, Ci, Co, H, W, 1, 1, 2, wl.F32, fused) for dt, N, Ci, Co, H, W in test_gpu_ksplit1x1.CASES]
+    assert families(routes.kernels(calls)) == ["conv1x1_ksplit"] * len(calls)
+
+
+def test_fused_cases_reach_the_kernel_they_name():
+    for kernel, dt, N, Ci, Co, H, W, ks, stride, k, rule in test_gpu_fused.CASES:
+        for out_dt in {wl.F32, dt}:
+            assert families(routes.kernels([call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, True, rule=rule)])) == [kernel]
+    for kernels, dt, N, Ci, Ca, Cb, H, W, ks, stride, k in test_gpu_fused.CONCAT_CASES:
+        for out_dt in {wl.F32, dt}:
+            got = routes.kernels([call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, True) for Co in (Ca, Cb)])
+            assert families(got) == kernels.split("+")
+
+
+def test_calls_past_launch_limits_leave_the_kernel_with_the_limit():
+    calls = [call(dt, N, Ci, Co, H, W, ks, stride, k, dt, False) for dt, N, H, W, Ci, Co, ks, stride, k in test_gpu_launch_limits.CASES]
+    assert families(routes.kernels(calls)) == ["conv_direct"] * 4 + ["conv1x1_stream", "conv3x3_dense"]
+    # one row, column or image less, where that is below the limit
+    below = [(wl.F16, 1, 46330, 46330, 8, 4, 3, 2, 3), (wl.BF16, 65280, 1, 4112, 8, 8, 3, 1, 2), (wl.F32, 1, (1 << 26) - 64, 1, 4, 4, 3, 1, 3),
+             (wl.F16, 64800, 182, 182, 2, 1, 1, 1, 2)]
+    calls = [call(dt, N, Ci, Co, H, W, ks, stride, k, dt, False) for dt, N, H, W, Ci, Co, ks, stride, k in below]
+    assert families(routes.kernels(calls)) == ["conv3x3_sparse_sb", "conv3x3_sparse_sb", "conv3x3_dense", "conv1x1_mma"]
