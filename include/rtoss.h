@@ -31,8 +31,11 @@
  *     iff tap t survives.  A dictionary is an array of P such masks that all have the
  *     same number k of set bits (one k per call: the paper's 2EP/3EP/4EP/5EP variants are
  *     separate dictionaries, Table 3), 1 <= P <= 255.
- *   - Determinism: identical inputs give bit-identical outputs (no atomics are used in any
- *     accumulation).
+ *   - Determinism: identical calls give bit-identical outputs (no atomics are used in any
+ *     accumulation).  The order in which an output's fp32 products are added belongs to the
+ *     kernel that a call is sent to, and that choice depends on the whole shape, the batch
+ *     size included, and on the device's number of compute units: an image's result may
+ *     differ in its last fp32 bits between two batch sizes.  It does not depend on out_dt.
  *   - Activations are finite numbers.  (A pruned weight is an exact zero; zero times a
  *     non-finite activation is not defined by this interface.)
  */
@@ -209,7 +212,7 @@ rtoss_status rtoss_pack(const rtoss_wdesc* desc, const void* w_dev, const uint8_
 
 /*
  * rtoss_pack for several layers of one model that share a dictionary, in as few launches as
- * possible (layers whose private section has the same format and dtype are packed by one
+ * possible (up to 60 layers of one dtype, whatever their formats, are packed by one
  * launch).  Each item is packed exactly as by rtoss_pack; no workspace is needed.
  *
  *   items_host  n_items entries {desc, w_dev, idx_dev, packed_dev, packed_bytes} with the meaning
@@ -268,7 +271,8 @@ rtoss_status rtoss_conv2d_pattern(const rtoss_wdesc* desc, const rtoss_cdesc* cd
  * evaluated in fp32 on the accumulator and rounded once on store.
  *
  *   scale_dev, bias_dev  Co floats each (device, 16-byte aligned), or NULL for 1 / 0
- *   act                  RTOSS_ACT_NONE, RTOSS_ACT_RELU (max(v, 0)) or RTOSS_ACT_SILU (v / (1 + exp(-v)))
+ *   act                  RTOSS_ACT_NONE, RTOSS_ACT_RELU (max(v, 0)) or RTOSS_ACT_SILU (v / (1 + exp(-v)), the
+ *                        exponential by the hardware's base-2 one, the quotient correctly rounded)
  *   residual_dev         tensor of y's type and shape (device, 16-byte aligned), or NULL; may not
  *                        overlap y_dev
  *   y_ld, residual_ld    channels-last only: number of elements from one position's first channel

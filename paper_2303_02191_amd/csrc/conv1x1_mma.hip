@@ -19,10 +19,10 @@
 // of 8 neighbouring positions hit 8 different bank groups without any padding.
 //
 // Ragged channel counts (RAG): the last stage's lanes past the row end copy the block of zeros, rows that are
-// not 16-byte aligned are copied 4 bytes per lane (COPY), and the output rows leave LDS element by element
-// with consecutive lanes on consecutive channels (a row of 255 channels has no alignment to exploit, but
-// every store instruction still covers 64 neighbouring elements).  These shapes ran on the vector ALUs
-// before, at 74 us for 72 -> 255 channels on 28 028 positions (now 16 us).
+// not 16-byte aligned are copied 4 bytes per lane (COPY), and output rows that are not leave LDS 4 bytes per lane
+// too, consecutive lanes on consecutive channels (a row of 255 16-bit channels has no alignment to exploit, but a
+// store instruction covers 256 neighbouring bytes).  On the vector ALUs 72 -> 255 channels on 28 028 positions took
+// 74 us, here 16; the stores' address processing is most of what is left.
 //
 // Operand layout of v_mfma_f32_16x16x32 (wave64; r = lane % 16, q = lane / 16): A lane holds
 // row r, K = 8q..8q+7; B lane holds column r, K = 8q..8q+7; D lane holds column r, rows 4q..4q+3.

@@ -17,8 +17,9 @@
 //
 // Section layout: [headers: one GatherHeader per (stage, channel block)][fragments: per (stage, channel block) 9 steps x
 // 4 channel fragments x 64 lanes x 16 B, the first `steps` of them written][block of zeros for padding copies].
-// Kernel: the dense-mode kernel's data flow (conv3x3_dense.hip: 64 channels x 16x16 positions per workgroup,
-// single LDS buffer), with a per-stage step count and a per-quarter tap offset per step.
+// Kernels: the simple one has the dense-mode kernel's data flow (conv3x3_dense.hip: 64 channels x 16x16 positions per
+// workgroup, single LDS buffer), with a per-stage step count and a per-quarter tap offset per step; the pipelined one is
+// described in front of it; launches that cannot fill the chip take conv3x3_ksplit.hip, which reads the same section.
 #include <algorithm>
 #include <type_traits>
 

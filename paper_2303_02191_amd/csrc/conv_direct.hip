@@ -153,18 +153,20 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(const T* __restrict__ 
     if (oh < Ho && ow < Wo) {
         TO* yp = y + n * st.y.n + oh * st.y.h + ow * st.y.w;
         const TO* rp = (const TO*)ep.residual + n * st.r.n + oh * st.r.h + ow * st.r.w;
+        const int co0 = co_block + wave * kCoPerWave;
 #pragma unroll
-        for (int i = 0; i < kCoPerWave; ++i) {
-            const int co = co_block + wave * kCoPerWave + i;
-            if (co < Co) {
-                float v = acc[i];
-                if (ep.scale) v *= ep.scale[co];
-                if (ep.bias) v += ep.bias[co];
-                v = epi_act(v, ep.act);
-                if (ep.residual) v += to_f32(rp[co * st.r.c]);
-                store_from_f32<TO>(yp + co * st.y.c, v);
+        for (int i = 0; i < kCoPerWave; ++i)
+            if (co0 + i < Co) {
+                if (ep.scale) acc[i] *= ep.scale[co0 + i];
+                if (ep.bias) acc[i] += ep.bias[co0 + i];
             }
-        }
+        epi_act<kCoPerWave>(acc, ep.act);
+#pragma unroll
+        for (int i = 0; i < kCoPerWave; ++i)
+            if (co0 + i < Co) {
+                if (ep.residual) acc[i] += to_f32(rp[(co0 + i) * st.r.c]);
+                store_from_f32<TO>(yp + (co0 + i) * st.y.c, acc[i]);
+            }
     }
 }
 

@@ -52,15 +52,15 @@ template <int N> __device__ __forceinline__ void epi_silu(float (&v)[N])
         v[i] = __builtin_fmaf(-__builtin_fmaf(d, q, -v[i]), r, q);
     }
 }
-__device__ __forceinline__ float epi_act(float v, int act)
+// (one uniform branch per activation around the whole run, not one per value)
+template <int N> __device__ __forceinline__ void epi_act(float (&v)[N], int act)
 {
-    if (act == 1) return __builtin_fmaxf(v, 0.f);
-    if (act == 2) {
-        float run[1] = {v};
-        epi_silu<1>(run);
-        return run[0];
+    if (act == 1) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = __builtin_fmaxf(v[i], 0.f);
+    } else if (act == 2) {
+        epi_silu<N>(v);
     }
-    return v;
 }
 
 // v[0..N) are N consecutive output channels, starting at channel co, of one position (N and co are
@@ -86,13 +86,7 @@ __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue
             for (int i = 0; i < 4; ++i) v[4 * g + i] += b[i];
         }
     }
-    // (one uniform branch per activation around the whole run, not one per value)
-    if (ep.act == 1) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = __builtin_fmaxf(v[i], 0.f);
-    } else if (ep.act == 2) {
-        epi_silu<N>(v);
-    }
+    epi_act<N>(v, ep.act);
 }
 template <int N> __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue& ep, int co)
 {
@@ -182,8 +176,13 @@ template <typename TO, int N> __device__ __forceinline__ void epi_ragged(float (
         if (co + i >= Co) break;
         if (ep.scale) v[i] *= ep.scale[co + i];
         if (ep.bias) v[i] += ep.bias[co + i];
-        v[i] = epi_act(v[i], ep.act);
-        if (ep.residual) v[i] += to_f32(((const TO*)ep.residual)[pos * ep.ldr + co + i]);
+    }
+    epi_act<N>(v, ep.act);
+    if (!ep.residual) return;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if (co + i >= Co) break;
+        v[i] += to_f32(((const TO*)ep.residual)[pos * ep.ldr + co + i]);
     }
 }
 
