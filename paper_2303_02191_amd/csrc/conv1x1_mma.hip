@@ -22,7 +22,7 @@
 // not 16-byte aligned are copied 4 bytes per lane (COPY), and output rows that are not leave LDS 4 bytes per lane
 // too, consecutive lanes on consecutive channels (a row of 255 16-bit channels has no alignment to exploit, but a
 // store instruction covers 256 neighbouring bytes).  On the vector ALUs 72 -> 255 channels on 28 028 positions took
-// 74 us, here 16; the stores' address processing is most of what is left.
+// 74 us, here 13; the stores' address processing is most of what is left.
 //
 // Operand layout of v_mfma_f32_16x16x32 (wave64; r = lane % 16, q = lane / 16): A lane holds
 // row r, K = 8q..8q+7; B lane holds column r, K = 8q..8q+7; D lane holds column r, rows 4q..4q+3.
