@@ -1,5 +1,4 @@
-// 3x3 pattern-pruned convolution in dense mode on the CDNA4 matrix cores (fp16 / bf16, fp32
-// accumulate): every tap is a dense K-step and pruned weights are explicit zeros.
+// 3x3 pattern-pruned convolution in dense mode on the CDNA4 matrix cores (fp32 accumulate): every tap is a dense K-step and pruned weights are explicit zeros.
 //
 // This is the matrix-core path for dictionaries the 2-of-4 sparse instruction cannot take: a
 // pattern with three or more corners, or three or more edge midpoints (4- and 5-entry connected
@@ -21,21 +20,22 @@
 // fragment m is channel 16q + 4m + i of the workgroup's 64), and the four lane quarters of a
 // position together write 128 contiguous bytes.
 //
-// fp32 tensors run through the same kernel on v_mfma_f32_16x16x4_f32: a stage is then 16 input
+// Small launches use 16 channels x 4x16 positions per workgroup so that they still fill the chip.
+// Those of fp32 tensors run through the same kernel on v_mfma_f32_16x16x4_f32: a stage is then 16 input
 // channels (the same 64 bytes per position), a lane's 16 bytes are 4 consecutive channels, and the
 // K step of 16 channels is 4 instructions, instruction s taking element s of every lane's 16 bytes
 // (the K slots of an instruction are the channels 4q + s: any assignment of channels to slots is
-// valid as long as both operands use it).  Small launches use 16 channels x 4x16 positions per
-// workgroup so that they still fill the chip.
+// valid as long as both operands use it).  Larger fp32 launches take the bf16 instruction with
+// every value split into three (dense3x3_f32.h).
 //
 // Operand layout of v_mfma_f32_16x16x32 (wave64; r = lane % 16, q = lane / 16): A lane holds
 // row r, K = 8q..8q+7; B lane holds column r, K = 8q..8q+7; D lane holds column r, rows 4q..4q+3.
 // v_mfma_f32_16x16x4_f32: A lane holds row r, K = q; B lane holds column r, K = q; same D.
 #include <algorithm>
-
 #include <type_traits>
 
 #include "common.h"
+#include "dense3x3_f32.h"
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
@@ -216,6 +216,40 @@ rtoss_status launch_shape(const rtoss_wdesc& d, const ConvParams& c, const char*
     return check_hip(hipGetLastError(), "conv3x3 dense launch");
 }
 
+// fp32: dense3x3_f32.h
+template <typename T, typename TO, int S, int R, bool RAG>
+__global__ __launch_bounds__(256, 2) void conv3x3_dense_kernel(const T* __restrict__ x, TO* __restrict__ y,
+                                                               const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                                               int H, int W, int Ci, int Co, int Ho, int Wo, int cblocks,
+                                                               int tiles_c, int tiles_per_image, int total, int work_per_xcd,
+                                                               Epilogue ep)
+{
+    static_assert(sizeof(T) == 4 && sizeof(TO) == 4, "fp32");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    // XCD-contiguous work order, channel block fastest: the workgroups of one activation tile share an L2
+    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
+    if (work >= total) return;
+    const int cb = work % cblocks, tile = (work / cblocks) % tiles_per_image, n_img = (work / cblocks) / tiles_per_image;
+    dense3x3_f32_tile<S, R, RAG>(x, y, wfrag, zeros, H, W, Ci, Co, Ho, Wo, cblocks, cb, n_img, (tile / tiles_c) * R, (tile % tiles_c) * 16, ep, smem);
+}
+
+template <int S, int R, bool RAG>
+rtoss_status launch_f32_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+{
+    const int Ho = (c.H - 1) / S + 1, Wo = (c.W - 1) / S + 1;
+    const int tiles_r = (Ho + R - 1) / R, tiles_c = (Wo + 15) / 16, cblocks = dense_channel_blocks(d.Co);
+    auto kern = conv3x3_dense_kernel<float, float, S, R, RAG>;
+    constexpr int lds = F32Tile<S, R>::LDS;
+    static LaunchOnce lds_once;  // per instantiation
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, "conv3x3 dense shared memory attribute")) return st;
+    if (c.N > 65535 || cblocks * kTM > 65535) return fail(RTOSS_ESHAPE, "conv: batch or channel count too large");  // (as above)
+    const int64_t total = (int64_t)tiles_r * tiles_c * cblocks * c.N;  // (at most kMaxGridGroups: dense3x3_launch_ok)
+    const int work_per_xcd = (int)((total + 7) / 8);
+    kern<<<dim3((unsigned)(work_per_xcd * 8)), dim3(256), lds, s>>>((const float*)x, (float*)y, wfrag, wfrag + frag_bytes(d), c.H, c.W, d.Ci, d.Co,
+                                                                   Ho, Wo, cblocks, tiles_c, tiles_r * tiles_c, (int)total, work_per_xcd, c.ep);
+    return check_hip(hipGetLastError(), "conv3x3 dense launch");
+}
+
 inline bool ragged(const rtoss_wdesc& d) { return d.Ci % stage_channels(d.dt) || d.Co % 16; }
 
 template <typename T, typename TO, int S>
@@ -228,6 +262,45 @@ rtoss_status launch_stride(const rtoss_wdesc& d, const ConvParams& c, const char
     if (ragged(d)) return launch_shape<T, TO, S, 1, 1, 4, true>(d, c, wfrag, x, y, s);
     if (big < 256) return launch_shape<T, TO, S, 1, 1, 4>(d, c, wfrag, x, y, s);
     return launch_shape<T, TO, S, 4, 4, 4>(d, c, wfrag, x, y, s);
+}
+
+// Workgroups of an fp32 launch with R output rows each.
+inline int64_t f32_groups(const rtoss_wdesc& d, const ConvParams& c, int rows)
+{
+    const int Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1;
+    return (int64_t)((Ho + rows - 1) / rows) * ((Wo + 15) / 16) * dense_channel_blocks(d.Co) * c.N;
+}
+
+// fp32.  Rows of a workgroup's tile on the bf16 instruction, or 0: too few workgroups for it, the small tile above on the fp32
+// instruction is faster (a launch waits for the split of 64 channels' weights, and ragged channel counts pad the larger tiles).
+// us on the small tile / with 2 / 4 / 8 rows (eight: conv3x3_strip.hip), workgroups with 2 rows in brackets:
+//      32 ->  32 1x40x50 (80)    4.2  5.1  6.7           64 ->  64 4x80x80 (800)    24.0  18.7  15.0  16.1
+//      96 ->  96 1x40x50 (160)  10.2  9.3 11.7           96 ->  96 2x80x100 (1120)  40.7  26.2  26.4  27.4
+//     128 -> 128 1x56x60 (224)  13.5 11.8 15.3           32 ->  32 4x112x140 (2016) 25.0  17.5  15.4  13.4
+//      64 ->  64 2x60x70 (300)  11.9  9.6  9.7          256 -> 256 4x80x80 (3200)   274   164   141   135
+//     ragged: 40 -> 72 2x40x60 (320) 8.8 9.9 9.9; 80 -> 80 1x100x120 (800) 25.6 22.4 18.4; 48 -> 72 4x77x91 (1872) 33.1 29.8 24.0
+//     stride 2, two rows (four would leave one workgroup per compute unit): 64 -> 128 2x80x100 13.5 10.6, 32 -> 64 4x112x140 15.4 10.7
+int f32_rows(const rtoss_wdesc& d, const ConvParams& c, int64_t cus)
+{
+    const int64_t g2 = f32_groups(d, c, 2);
+    if (c.stride == 2) return g2 > cus / 2 ? 2 : 0;
+    if (ragged(d) ? 2 * g2 < 3 * cus : 8 * g2 < 5 * cus) return 0;
+    return 2 * f32_groups(d, c, 4) >= cus ? 4 : 2;
+}
+
+template <bool RAG> rtoss_status launch_f32(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+{
+    DeviceInfo dev;
+    if (rtoss_status st = current_device(&dev)) return st;
+    const int rows = f32_rows(d, c, dev.cus);
+    if (c.stride == 2) {
+        if (rows == 0) return launch_shape<float, float, 2, 1, 1, 4, RAG>(d, c, wfrag, x, y, s);
+        return launch_f32_rows<2, 2, RAG>(d, c, wfrag, x, y, s);
+    }
+    if (rows == 0) return launch_shape<float, float, 1, 1, 1, 4, RAG>(d, c, wfrag, x, y, s);
+    if constexpr (!RAG)  // (ragged launches that small take the tile above)
+        if (rows == 2) return launch_f32_rows<1, 2, false>(d, c, wfrag, x, y, s);
+    return launch_f32_rows<1, 4, RAG>(d, c, wfrag, x, y, s);
 }
 
 template <typename T, typename TO>
@@ -248,6 +321,7 @@ bool dense3x3_shape_ok(const rtoss_wdesc& d)
 
 bool dense3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c)
 {
+    if (d.dt == RTOSS_F32 && f32_groups(d, c, c.stride == 1 ? 4 : 2) > kMaxGridGroups) return false;
     if (!ragged(d)) return true;
     const int Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1;  // tiles of 4x16 positions x 16 channels
     return (int64_t)((Ho + 3) / 4) * ((Wo + 15) / 16) <= kMaxGridGroups && dense_channel_blocks(d.Co) * kTM <= 65535;
@@ -262,7 +336,7 @@ rtoss_status launch_conv3x3_dense(const rtoss_wdesc& d, const ConvParams& c, con
     const bool f32out = c.out_dt == RTOSS_F32;
     if (const int plan = ksplit3x3_plan(d, c, 2)) return launch_conv3x3_ksplit(d, c, 2, plan, section, wf + frag_bytes(d), x, y, s);
     if (const int plan = strip3x3_plan(d, c, 2)) return launch_conv3x3_strip(d, c, 2, plan, section, wf + frag_bytes(d), x, y, s);
-    if (d.dt == RTOSS_F32) return launch_typed<float, float>(d, c, wf, x, y, s);
+    if (d.dt == RTOSS_F32) return ragged(d) ? launch_f32<true>(d, c, wf, x, y, s) : launch_f32<false>(d, c, wf, x, y, s);
     if (d.dt == RTOSS_F16)
         return f32out ? launch_typed<f16_t, float>(d, c, wf, x, y, s) : launch_typed<f16_t, f16_t>(d, c, wf, x, y, s);
     return f32out ? launch_typed<bf16_t, float>(d, c, wf, x, y, s) : launch_typed<bf16_t, bf16_t>(d, c, wf, x, y, s);

@@ -1,7 +1,7 @@
 // 3x3 pattern-pruned convolution, stride 1, over strips of output rows: the kernel for launches between the ones that
 // cannot fill the chip (conv3x3_ksplit.hip) and the ones large enough for the persistent pipeline (conv3x3_rows.hip).
-// Reads the packed sections of sparse_frag.h (2-of-4 steps) and of the dense mode (one step per tap: 16-bit dictionaries
-// without a 2-of-4 shape, and fp32).
+// Reads the packed sections of sparse_frag.h (2-of-4 steps) and of the dense mode (one step per tap: dictionaries without a
+// 2-of-4 shape).  Large fp32 launches use the same operand scheme with every value split into three (dense3x3_f32.h).
 //
 // With the 16 columns of a matrix instruction as a 4x4 block of positions every tap of every block is an operand read of
 // its own, nine per block, and LDS bandwidth bounds these layers: a 16-byte read per lane is 8 cycles of the compute
@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "dense3x3_f32.h"
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
@@ -225,6 +226,36 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
     else finish(std::false_type{});
 }
 
+// fp32: dense3x3_f32.h
+constexpr int kF32Rows = 8;
+template <typename T, typename TO, int ROWS>
+__global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
+                                                               const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                                               int H, int W, int Ci, int Co, int strips, int tiles_per_image,
+                                                               int co_blocks, int total, int work_per_xcd, Epilogue ep)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
+    if (work >= total) return;
+    const int cb = work % co_blocks, tile = (work / co_blocks) % tiles_per_image, n_img = (work / co_blocks) / tiles_per_image;
+    dense3x3_f32_tile<1, ROWS, false>(x, y, wfrag, zeros, H, W, Ci, Co, H, W, co_blocks, cb, n_img, (tile / strips) * ROWS,
+                                      (tile % strips) * kCols, ep, smem);
+}
+
+rtoss_status launch_f32(const rtoss_wdesc& d, const ConvParams& c, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
+{
+    const int strips = (c.W + kCols - 1) / kCols, rows = (c.H + kF32Rows - 1) / kF32Rows, co_blocks = (d.Co + 63) / 64;
+    auto kern = conv3x3_strip_kernel<float, float, kF32Rows>;
+    constexpr int lds = F32Tile<1, kF32Rows>::LDS;
+    static LaunchOnce lds_once;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, "conv3x3 shared memory attribute")) return st;
+    const int64_t total = (int64_t)strips * rows * co_blocks * c.N;  // (at most kMaxGridGroups: strip3x3_plan)
+    const int work_per_xcd = (int)((total + 7) / 8);
+    kern<<<dim3((unsigned)(work_per_xcd * 8)), dim3(256), lds, s>>>((const float*)x, (float*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, strips,
+                                                                   strips * rows, co_blocks, (int)total, work_per_xcd, c.ep);
+    return check_hip(hipGetLastError(), "conv3x3 strip launch");
+}
+
 template <typename T, typename TO, int TN, int LAY, bool DB>
 rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
 {
@@ -251,9 +282,9 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, int plan, c
     switch (plan) {
     case 2: return launch_rows<T, TO, 2, LAY, false>(d, c, wf, zeros, x, y, s);
     case 3: if constexpr (LAY != 0) return launch_rows<T, TO, 3, LAY, false>(d, c, wf, zeros, x, y, s); else break;
-    case 4: if constexpr (sizeof(T) == 2) return launch_rows<T, TO, 4, LAY, false>(d, c, wf, zeros, x, y, s); else break;
+    case 4: return launch_rows<T, TO, 4, LAY, false>(d, c, wf, zeros, x, y, s);
     case 5: if constexpr (LAY != 0) return launch_rows<T, TO, 5, LAY, false>(d, c, wf, zeros, x, y, s); else break;
-    case 2 + kTwoBuffers: if constexpr (sizeof(T) == 2) return launch_rows<T, TO, 2, LAY, true>(d, c, wf, zeros, x, y, s); else break;
+    case 2 + kTwoBuffers: return launch_rows<T, TO, 2, LAY, true>(d, c, wf, zeros, x, y, s);
     case 3 + kTwoBuffers: if constexpr (LAY == 0) return launch_rows<T, TO, 3, LAY, true>(d, c, wf, zeros, x, y, s); else break;
     }
     return fail(RTOSS_EINVAL, "conv: unknown strip plan %d", plan);
@@ -263,8 +294,6 @@ template <int LAY>
 rtoss_status launch_layout(const rtoss_wdesc& d, const ConvParams& c, int plan, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
 {
     const bool f32out = c.out_dt == RTOSS_F32;
-    if constexpr (LAY == kDenseTaps)
-        if (d.dt == RTOSS_F32) return launch_typed<float, float, LAY>(d, c, plan, wf, zeros, x, y, s);
     if (d.dt == RTOSS_F16)
         return f32out ? launch_typed<f16_t, float, LAY>(d, c, plan, wf, zeros, x, y, s) : launch_typed<f16_t, f16_t, LAY>(d, c, plan, wf, zeros, x, y, s);
     return f32out ? launch_typed<bf16_t, float, LAY>(d, c, plan, wf, zeros, x, y, s) : launch_typed<bf16_t, bf16_t, LAY>(d, c, plan, wf, zeros, x, y, s);
@@ -300,17 +329,10 @@ static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int lay
         return (int64_t)((c.W + kCols - 1) / kCols) * ((c.H + 4 * tn - 1) / (4 * tn)) * ((d.Co + 63) / 64) * c.N;
     };
     if (d.dt == RTOSS_F32) {
-        // matrix-bound: what counts is the rows per compute unit.  Below one 64-channel x 16x16 tile per compute unit the
-        // dense-mode kernel's small tiles win; above, its 16 rows win ties.
-        const int64_t tiles = (int64_t)((c.H + 15) / 16) * ((c.W + 15) / 16) * ((d.Co + 63) / 64) * c.N;
-        if (tiles < cus) return 0;
-        int best = 0;
-        int64_t rows = (tiles + cus - 1) / cus * 4;
-        for (const int tn : {5, 3, 2}) {  // (4: the dense-mode kernel's own height)
-            const int64_t r = (groups(tn) + cus - 1) / cus * tn;
-            if (r < rows) best = tn, rows = r;
-        }
-        return best;
+        // Eight rows from six workgroups per four compute units on; below that the dense-mode kernel's shorter tiles spread the
+        // work better (timings: f32_rows there).
+        static_assert(kF32Rows == 4 * 2, "groups(2)");
+        return 2 * groups(2) >= 3 * cus ? 2 : 0;
     }
     // shallow narrow launches of the dense mode: its own 16-channel tiles
     if (layout == kDenseTaps && groups(2) <= cus / 2) return 0;
@@ -330,6 +352,7 @@ rtoss_status launch_conv3x3_strip(const rtoss_wdesc& d, const ConvParams& c, int
                                   const void* x, void* y, hipStream_t s)
 {
     const char *wf = (const char*)section, *z = (const char*)zeros;
+    if (d.dt == RTOSS_F32) return launch_f32(d, c, wf, z, x, y, s);
     if (layout == kDenseTaps) return launch_layout<kDenseTaps>(d, c, plan, wf, z, x, y, s);
     return layout == 1 ? launch_layout<1>(d, c, plan, wf, z, x, y, s) : launch_layout<0>(d, c, plan, wf, z, x, y, s);
 }
