@@ -16,6 +16,9 @@ CASES = [
     (33, 64, 64, 25, 33, 3, 1),   # ... eight rows
     (5, 20, 72, 61, 35, 3, 1),    # ... ragged channels
     (17, 40, 80, 25, 33, 3, 2),   # ... stride 2
+    (2, 72, 255, 25, 33, 1, 1),   # 1x1: whole rows, an odd number of half steps
+    (1, 37, 85, 25, 33, 1, 1),    # ... rows without alignment
+    (1, 96, 80, 25, 33, 1, 1),    # ... whole tiles
 ]
 
 
