@@ -14,10 +14,15 @@
 // Two workgroups per compute unit cover each other's copies and barriers.  TN is chosen per launch (strip3x3_plan).  Where
 // two buffers of a workgroup fit LDS twice, the next stage's copies are issued behind the barrier that opens a stage (DB).
 //
-// What bounds it now, by counters: dense mode with TN = 5 keeps the matrix pipes busy 53 % and LDS 23 % of the time
-// (256 -> 256 at 100x168, two images), the 2-of-4 layout with TN = 3 35 % and 32 % (one image): neither rate, but what a
-// stage spends around its matrix instructions, the copies' issue and latency and the barriers, with two workgroups to
-// hide it; and with one round of workgroups nothing hides the first stage and the stores.
+// The dense mode has no operands to transpose, so a wave can take all its weights from memory and half the tiles (the second
+// kernel here): LDS then carries the activations only, through registers -- a wave with copies into LDS under way waits for
+// all of its LDS reads at once, the compiler cannot count them apart.
+//
+// What bounds it now, by counters: dense mode with 20 rows keeps the matrix pipes busy 60 % of the time where a compute unit
+// has one or two tiles (256 -> 256 at 100x168, two images; 53 % with the weights in LDS), 77 % where it has two; the 2-of-4
+// layout with TN = 3 35 %, LDS 32 % (one image): neither rate, but what a stage spends around its matrix instructions, the copies'
+// issue and latency and the barriers, with two workgroups to hide it; and with one round of workgroups nothing hides the
+// first stage and the stores.
 #include <algorithm>
 #include <type_traits>
 
@@ -38,6 +43,7 @@ constexpr int kCols = 16;      // output columns of a workgroup
 constexpr int kLW = kCols + 2; // input columns
 constexpr int kDenseTaps = kNumLayouts;
 constexpr int kTwoBuffers = 8; // in a plan: rows per wave + kTwoBuffers
+constexpr int kDenseRows = 16; // in a plan of the dense mode without weights in LDS: rows of a workgroup + kDenseRows
 constexpr int strip_tile_bytes(int lay) { return lay == kDenseTaps ? kDenseTileBytes : layout_tile_bytes(kLayouts[lay]); }
 
 template <int TN, int LAY, bool DB> struct Strip {
@@ -226,8 +232,143 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
     else finish(std::false_type{});
 }
 
-// fp32: dense3x3_f32.h
-constexpr int kF32Rows = 8;
+// Dense mode.  A tap's fragment is used for one product per row and tile and needs no transposition, so here the weights stay out
+// of LDS: wave (p, h) owns channel tiles 2p and 2p+1 and the rows of half h, and loads its fragments straight into registers,
+// the next column of taps' while the current one is multiplied.
+template <int ROWS> struct DenseStrip {
+    static constexpr int RW = ROWS / 2;                          // rows of a wave
+    static constexpr int CHUNKS = (ROWS + 2) * kLW * 4;
+    static constexpr int PER_WAVE = (CHUNKS + 255) / 256;        // copy instructions
+    static constexpr int BUF = PER_WAVE * 4096;
+    static constexpr int LDS = 2 * BUF + EpiScaleBias<64>::kBytes;
+};
+
+template <typename T, typename TO, int ROWS>
+__device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+                                                 const char* __restrict__ zeros, int H, int W, int Ci, int Co, int co_blocks, int cb,
+                                                 int n_img, int oh0, int ow0, const Epilogue& ep, char* smem)
+{
+    using P = DenseStrip<ROWS>;
+    constexpr int RW = P::RW;
+    float* const lds_ep = (float*)(smem + 2 * P::BUF);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), pair = wave >> 1, half = wave & 1;
+    const int stages = Ci / 32;
+    EpiScaleBias<64> scale_bias;
+    scale_bias.load(ep, 64 * cb, Co, tid);
+
+    const char* a_src = wfrag + (int64_t)(4 * cb + 2 * pair) * kDenseTileBytes + lane * 16;
+    const int64_t a_stage = (int64_t)co_blocks * (4 * kDenseTileBytes);
+    struct Column {
+        u32x4 a[2][3];  // [tile][kh]
+    };
+    auto load_column = [&](Column& c, int stage, int kw) {
+        const char* p = a_src + stage * a_stage + kw * kFragBytes;
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int kh = 0; kh < 3; ++kh) c.a[m][kh] = *(const u32x4*)(p + m * kDenseTileBytes + 3 * kh * kFragBytes);
+    };
+    Column column[3];  // of the stage; each is replaced by the next stage's behind its products
+#pragma unroll
+    for (int kw = 0; kw < 3; ++kw) load_column(column[kw], 0, kw);
+    const char* x_ptr[P::PER_WAVE];
+#pragma unroll
+    for (int k = 0; k < P::PER_WAVE; ++k) {
+        const int pos = (k * 4 + wave) * 16 + (lane >> 2);
+        const int xr = pos / kLW, xc = pos % kLW;
+        const int ih = oh0 - 1 + xr, iw = ow0 - 1 + xc;
+        const bool inside = xr < ROWS + 2 && (unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W;
+        const int off = ((n_img * H + ih) * W + iw) * (Ci / 8) + (lane & 3);  // in 16-byte chunks (31 bits: strip3x3_plan)
+        x_ptr[k] = inside ? (const char*)x + (int64_t)off * 16 : zeros;
+    }
+    u32x4 raw[P::PER_WAVE];
+    auto load_activations = [&](int stage) {
+#pragma unroll
+        for (int k = 0; k < P::PER_WAVE; ++k) raw[k] = *(const u32x4*)(x_ptr[k] + stage * 64);
+    };
+    auto store_activations = [&](char* buf) {
+#pragma unroll
+        for (int k = 0; k < P::PER_WAVE; ++k) *(u32x4*)(buf + (k * 4 + wave) * 1024 + lane * 16) = raw[k];
+    };
+    load_activations(0);
+    const int nn = lane & 15, qq = lane >> 4;
+    f32x4 acc[2][RW];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int j = 0; j < RW; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    store_activations(smem);
+    scale_bias.store(lds_ep, ep, tid);
+    for (int stage = 0; stage < stages; ++stage) {
+        const int next = min(stage + 1, stages - 1);  // (behind the last stage: again, not used; a branch would make the waits coarser)
+        char* const other = smem + ((stage & 1) ^ 1) * P::BUF;
+        const char* X = smem + (stage & 1) * P::BUF + (half * RW * kLW + nn) * 64 + qq * 16;
+        __syncthreads();  // the stage is in LDS; everybody is done with the other buffer
+        static_for<3>([&](auto kw_tag) {
+            constexpr int kw = decltype(kw_tag)::value;
+            if constexpr (kw == 0) load_activations(next);
+            auto row = [&](int i) { return *(const u32x4*)(X + (i * kLW + kw) * 64); };
+            u32x4 b[3] = {row(0), row(1), row(2)};
+            __builtin_amdgcn_sched_barrier(0);  // (the scheduler would move the loads down to where they are used)
+#pragma unroll
+            for (int i = 0; i < RW + 2; ++i) {
+                const u32x4 r = b[i % 3];
+#pragma unroll
+                for (int kh = 0; kh < 3; ++kh) {
+                    if (i < kh || i - kh >= RW) continue;
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) acc[m][i - kh] = Dense16<T>::mma(column[kw].a[m][kh], r, acc[m][i - kh]);
+                }
+                if (i + 3 < RW + 2) b[i % 3] = row(i + 3);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            load_column(column[kw], next, kw);
+            if constexpr (kw == 2) store_activations(other);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+
+    // ---- store: a lane holds 8 consecutive channels of one position per row ----
+    const int co = 64 * cb + 16 * qq + 8 * pair, ow = ow0 + nn, oh = oh0 + half * RW;
+    if (co >= Co || ow >= W) return;  // (Co is a multiple of 16)
+    const int64_t pos0 = ((int64_t)n_img * H + oh) * W + ow;
+    auto finish = [&](auto shortcut_tag) {
+        constexpr bool SHORTCUT = decltype(shortcut_tag)::value;
+        EpiResidual<TO, 8> shortcut[RW];
+        if constexpr (SHORTCUT) {
+#pragma unroll
+            for (int j = 0; j < RW; ++j)
+                if (oh + j < H) shortcut[j].load(ep, pos0 + (int64_t)j * W, co);
+        }
+#pragma unroll
+        for (int j = 0; j < RW; ++j) {
+            if (oh + j >= H) break;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = acc[e / 4][j][e % 4];
+            epi_scale_bias_act<8>(v, ep, lds_ep + 16 * qq + 8 * pair, lds_ep + 64 + 16 * qq + 8 * pair);
+            if constexpr (SHORTCUT) shortcut[j].add(v);
+            TO* yp = y + (pos0 + (int64_t)j * W) * ep.ldy + co;
+            if constexpr (sizeof(TO) == 4) {
+#pragma unroll
+                for (int g = 0; g < 2; ++g) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+            } else {
+                u32x4 o;
+                o.x = pack2_from_f32<TO>(v[0], v[1]);
+                o.y = pack2_from_f32<TO>(v[2], v[3]);
+                o.z = pack2_from_f32<TO>(v[4], v[5]);
+                o.w = pack2_from_f32<TO>(v[6], v[7]);
+                *(u32x4*)yp = o;
+            }
+        }
+    };
+    if (ep.residual) finish(std::true_type{});
+    else finish(std::false_type{});
+}
+
+// (fp32: dense3x3_f32.h, eight rows)
+template <typename T, int ROWS> constexpr int dense_strip_lds = sizeof(T) == 4 ? F32Tile<1, ROWS>::LDS : DenseStrip<ROWS>::LDS;
 template <typename T, typename TO, int ROWS>
 __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                                const char* __restrict__ wfrag, const char* __restrict__ zeros,
@@ -238,20 +379,22 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total) return;
     const int cb = work % co_blocks, tile = (work / co_blocks) % tiles_per_image, n_img = (work / co_blocks) / tiles_per_image;
-    dense3x3_f32_tile<1, ROWS, false>(x, y, wfrag, zeros, H, W, Ci, Co, H, W, co_blocks, cb, n_img, (tile / strips) * ROWS,
-                                      (tile % strips) * kCols, ep, smem);
+    const int oh0 = (tile / strips) * ROWS, ow0 = (tile % strips) * kCols;
+    if constexpr (sizeof(T) == 4) dense3x3_f32_tile<1, ROWS, false>(x, y, wfrag, zeros, H, W, Ci, Co, H, W, co_blocks, cb, n_img, oh0, ow0, ep, smem);
+    else dense_strip_tile<T, TO, ROWS>(x, y, wfrag, zeros, H, W, Ci, Co, co_blocks, cb, n_img, oh0, ow0, ep, smem);
 }
 
-rtoss_status launch_f32(const rtoss_wdesc& d, const ConvParams& c, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
+template <typename T, typename TO, int ROWS>
+rtoss_status launch_dense_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
 {
-    const int strips = (c.W + kCols - 1) / kCols, rows = (c.H + kF32Rows - 1) / kF32Rows, co_blocks = (d.Co + 63) / 64;
-    auto kern = conv3x3_strip_kernel<float, float, kF32Rows>;
-    constexpr int lds = F32Tile<1, kF32Rows>::LDS;
-    static LaunchOnce lds_once;
+    const int strips = (c.W + kCols - 1) / kCols, rows = (c.H + ROWS - 1) / ROWS, co_blocks = (d.Co + 63) / 64;
+    auto kern = conv3x3_strip_kernel<T, TO, ROWS>;
+    constexpr int lds = dense_strip_lds<T, ROWS>;
+    static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)strips * rows * co_blocks * c.N;  // (at most kMaxGridGroups: strip3x3_plan)
     const int work_per_xcd = (int)((total + 7) / 8);
-    kern<<<dim3((unsigned)(work_per_xcd * 8)), dim3(256), lds, s>>>((const float*)x, (float*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, strips,
+    kern<<<dim3((unsigned)(work_per_xcd * 8)), dim3(256), lds, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, strips,
                                                                    strips * rows, co_blocks, (int)total, work_per_xcd, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 strip launch");
 }
@@ -284,16 +427,35 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, int plan, c
     case 3: if constexpr (LAY != 0) return launch_rows<T, TO, 3, LAY, false>(d, c, wf, zeros, x, y, s); else break;
     case 4: return launch_rows<T, TO, 4, LAY, false>(d, c, wf, zeros, x, y, s);
     case 5: if constexpr (LAY != 0) return launch_rows<T, TO, 5, LAY, false>(d, c, wf, zeros, x, y, s); else break;
-    case 2 + kTwoBuffers: return launch_rows<T, TO, 2, LAY, true>(d, c, wf, zeros, x, y, s);
+    case 2 + kTwoBuffers: if constexpr (LAY != kDenseTaps) return launch_rows<T, TO, 2, LAY, true>(d, c, wf, zeros, x, y, s); else break;
     case 3 + kTwoBuffers: if constexpr (LAY == 0) return launch_rows<T, TO, 3, LAY, true>(d, c, wf, zeros, x, y, s); else break;
     }
     return fail(RTOSS_EINVAL, "conv: unknown strip plan %d", plan);
+}
+
+template <typename T, typename TO>
+rtoss_status launch_dense(const rtoss_wdesc& d, const ConvParams& c, int rows, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
+{
+    switch (rows) {
+    case 8: return launch_dense_rows<T, TO, 8>(d, c, wf, zeros, x, y, s);
+    case 12: if constexpr (sizeof(T) == 2) return launch_dense_rows<T, TO, 12>(d, c, wf, zeros, x, y, s); else break;
+    case 16: if constexpr (sizeof(T) == 2) return launch_dense_rows<T, TO, 16>(d, c, wf, zeros, x, y, s); else break;
+    case 20: if constexpr (sizeof(T) == 2) return launch_dense_rows<T, TO, 20>(d, c, wf, zeros, x, y, s); else break;
+    }
+    return fail(RTOSS_EINVAL, "conv: unknown strip plan of %d rows", rows);
 }
 
 template <int LAY>
 rtoss_status launch_layout(const rtoss_wdesc& d, const ConvParams& c, int plan, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
 {
     const bool f32out = c.out_dt == RTOSS_F32;
+    if constexpr (LAY == kDenseTaps)
+        if (plan > kDenseRows) {
+            const int rows = plan - kDenseRows;
+            if (d.dt == RTOSS_F32) return launch_dense<float, float>(d, c, rows, wf, zeros, x, y, s);
+            if (d.dt == RTOSS_F16) return f32out ? launch_dense<f16_t, float>(d, c, rows, wf, zeros, x, y, s) : launch_dense<f16_t, f16_t>(d, c, rows, wf, zeros, x, y, s);
+            return f32out ? launch_dense<bf16_t, float>(d, c, rows, wf, zeros, x, y, s) : launch_dense<bf16_t, bf16_t>(d, c, rows, wf, zeros, x, y, s);
+        }
     if (d.dt == RTOSS_F16)
         return f32out ? launch_typed<f16_t, float, LAY>(d, c, plan, wf, zeros, x, y, s) : launch_typed<f16_t, f16_t, LAY>(d, c, plan, wf, zeros, x, y, s);
     return f32out ? launch_typed<bf16_t, float, LAY>(d, c, plan, wf, zeros, x, y, s) : launch_typed<bf16_t, bf16_t, LAY>(d, c, plan, wf, zeros, x, y, s);
@@ -314,7 +476,7 @@ int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
     if (c.stride != 1 || d.Ci * elem_bytes(d.dt) % 64 || d.Co % 16) return 0;
     // (the dense-mode kernel has neither limit)
     const int plan = plan_within_limits(d, c, layout);
-    const int rows = 4 * (plan % kTwoBuffers);
+    const int rows = plan > kDenseRows ? plan - kDenseRows : 4 * (plan % kTwoBuffers);
     if (plan == 0 || (int64_t)c.N * c.H * c.W * d.Ci * elem_bytes(d.dt) / 16 > kMaxChunks) return 0;
     return (int64_t)((c.W + kCols - 1) / kCols) * ((c.H + rows - 1) / rows) * ((d.Co + 63) / 64) * c.N <= kMaxGridGroups ? plan : 0;
 }
@@ -331,15 +493,30 @@ static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int lay
     if (d.dt == RTOSS_F32) {
         // Eight rows from six workgroups per four compute units on; below that the dense-mode kernel's shorter tiles spread the
         // work better (timings: f32_rows there).
-        static_assert(kF32Rows == 4 * 2, "groups(2)");
-        return 2 * groups(2) >= 3 * cus ? 2 : 0;
+        return 2 * groups(2) >= 3 * cus ? kDenseRows + 8 : 0;
     }
     // shallow narrow launches of the dense mode: its own 16-channel tiles
     if (layout == kDenseTaps && groups(2) <= cus / 2) return 0;
+    if (layout == kDenseTaps && (stages > 2 || (stages == 2 && groups(2) <= cus))) {
+        // Weights past LDS: the height with the fewest rows per compute unit, three more counted for a tile's start and end
+        // (us, weights through LDS and past it with 8 / 12 / 16 / 20 rows, bf16):
+        //     1x256@100x168 25.7  25.4 24.6 28.6 22.6    1x128@80x100 8.5   7.3  8.5 10.3 11.6    3x96@100x140 11.9  12.5 11.9 14.0 16.1
+        //     2x256@100x168 40.5  44.5 43.5 43.6 39.0    4x128@60x80 10.7  10.9  9.0 11.1 12.4    1x256@50x84  13.7  10.4 12.8 16.3 18.8
+        //     4x256@100x168 72.4  77.6 73.6 73.0 67.0    2x192@70x90 15.3  13.5 11.4 14.2 16.2
+        // Shallow launches of several tiles per compute unit keep the smaller registers (4x64@112x140 8.3  8.7 9.5 8.7 9.5).
+        int best = 0;
+        int64_t cost = 0;
+        for (const int rows : {20, 16, 12, 8}) {
+            const int64_t tiles = (int64_t)((c.W + kCols - 1) / kCols) * ((c.H + rows - 1) / rows) * ((d.Co + 63) / 64) * c.N;
+            const int64_t rounds = (tiles + cus - 1) / cus * (rows + 3);
+            if (best == 0 || rounds < cost) best = rows, cost = rounds;
+        }
+        return kDenseRows + best;
+    }
     if (stages == 1) return groups(2) <= 4 * cus ? 2 : 0;  // (nothing to fetch ahead: four workgroups per compute unit)
     if (groups(2) <= 2 * cus) {
         if (layout == 0 && groups(2) > cus && groups(3) <= cus) return 3 + kTwoBuffers;
-        return layout != kDenseTaps || groups(2) <= cus ? 2 + kTwoBuffers : 2;  // (dense mode: two buffers fit once)
+        return layout != kDenseTaps ? 2 + kTwoBuffers : 2;  // (dense mode: two buffers fit once)
     }
     if (groups(3) <= 2 * cus) return layout == 0 ? 3 + kTwoBuffers : 3;
     if (groups(4) <= 2 * cus) return 4;
@@ -352,7 +529,6 @@ rtoss_status launch_conv3x3_strip(const rtoss_wdesc& d, const ConvParams& c, int
                                   const void* x, void* y, hipStream_t s)
 {
     const char *wf = (const char*)section, *z = (const char*)zeros;
-    if (d.dt == RTOSS_F32) return launch_f32(d, c, wf, z, x, y, s);
     if (layout == kDenseTaps) return launch_layout<kDenseTaps>(d, c, plan, wf, z, x, y, s);
     return layout == 1 ? launch_layout<1>(d, c, plan, wf, z, x, y, s) : launch_layout<0>(d, c, plan, wf, z, x, y, s);
 }
