@@ -12,8 +12,11 @@
 //     section's part and the fragments are assembled from there.  Every weight is read once.
 //   * 1x1 fragments: a lane's 16 bytes are consecutive elements of one row of [Co][Ci], which touch at most two groups:
 //     one vector load and two index loads, all independent.
-//   * public sections of 1x1 layers: 256 groups per workgroup through LDS (pack_live.h).
-// Measured, 57 layers with 7.0 M fp16 weights, 2-entry patterns: 13.6 us in one launch; 38 us in four before.
+//   * public sections of 1x1 layers: runs of 256 groups through LDS (pack_live.h).
+//   * workgroups of the 1x1 formats do several runs or pieces each, and the 3x3 tiles, which take longest, come first.
+// Measured, 57 layers with 7.0 M fp16 weights, 2-entry patterns: 10.3 us in one launch (13.1 with a workgroup per run, in the order
+// of the layers; 38 in four launches).  A workgroup of the 3x3 path takes 10 000 cycles, 2000 of them for the launch arguments, 2000
+// for weights and indices, 1800 for its part of the public section and 3300 for the fragments.
 #include <algorithm>
 #include <vector>
 
@@ -36,7 +39,7 @@ struct PackEntry {
     uint32_t idx_off, mat_off;  // sections of the blob, in units of 256 bytes
     int Co, Ci;
     uint32_t items;             // 3x3: (stage, channel tile) pairs; 1x1 and stem: 16-byte pieces of the fragments
-    uint8_t format, a, b, c;    // MatrixFormat; 3x3: tap layout; streaming 1x1: KS, MT; without fragments: weights per kernel
+    uint8_t format, a, b, c;    // MatrixFormat; 3x3: tap layout; streaming 1x1: log2 of KS, of MT; without fragments: weights per kernel
 };
 constexpr int kPackMax = 60;
 struct PackTable {
@@ -52,6 +55,11 @@ __device__ __forceinline__ int stage_channel(int q, int g, int half)
 }
 
 constexpr int kTapGroups = 3;  // at most (TapLayout::tap)
+constexpr int kOneWave = 64;   // patterns from which on the per-pattern tables take all waves of a workgroup
+
+// 16-byte pieces of a 1x1 section that a lane writes, and runs of 256 groups of a public section that a workgroup does: what a
+// workgroup spends to find its layer is as much as one of either.
+constexpr int kPieces = 4, kLiveRuns = 2;
 
 // LDS of a workgroup
 template <typename T> struct TileLds {
@@ -66,8 +74,8 @@ template <typename T> struct TileLds {
 // (LAY: tap layout, or kDenseTaps; a template parameter so that the walks over a layout's taps are constants)
 constexpr int kDenseTaps = kNumLayouts;
 template <typename T, int LAY>
-__device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigned mask, const uint16_t* masks, int tile, int m_tiles,
-                                             TileLds<T>& L)
+__device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, int P, unsigned mask, const uint16_t* masks, int tile,
+                                             int m_tiles, TileLds<T>& L)
 {
     constexpr int SC = TileLds<T>::SC;
     const T* __restrict__ w = (const T*)en.w;
@@ -108,20 +116,27 @@ __device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigne
             L.w[r][e] = v;
         }
     }
+    uint8_t entry[IDX_PER];  // of the per-pattern tables: an index outside the dictionary finds an entry without taps
 #pragma unroll
-    for (int i = 0; i < IDX_PER; ++i) L.idx[(tid + 256 * i) / SC][(tid + 256 * i) % SC] = iv[i];
-    // ---- per-pattern tables, pattern tid (under the loads above) ----
-    {
+    for (int i = 0; i < IDX_PER; ++i) {
+        entry[i] = P < kOneWave ? (uint8_t)min((int)iv[i], kOneWave - 1) : iv[i];
+        L.idx[(tid + 256 * i) / SC][(tid + 256 * i) % SC] = entry[i];
+    }
+    // ---- per-pattern tables (under the loads above); a dictionary of fewer than 64 patterns: one wave, not the first, which has
+    // a fragment more than the others ----
+    const bool tables = P >= kOneWave || tid >= 192;  // (uniform over a wave)
+    const int pattern = P >= kOneWave ? tid : tid & (kOneWave - 1);
+    if (tables) {
         uint64_t t = ~(uint64_t)0;
         unsigned m = mask;
         for (int j = 0; m; ++j, m &= m - 1) t = (t & ~((uint64_t)15 << (4 * j))) | (uint64_t)__builtin_ctz(m) << (4 * j);
-        L.taps[tid] = t;
+        L.taps[pattern] = t;
     }
     // slots[p][group]: taps of pattern p's first and second live tap in the group (bits 0-3, 4-7; 15: none) and the
     // slots they take (bits 8-9, 10-11; a missing second value points at the slot after the first, a group without
     // live taps at slots 0 and 1: padding values of 0 may point anywhere, as long as the two differ)
     constexpr unsigned kNoTaps = 15u | (15u << 4) | (0u << 8) | (1u << 10);
-    if constexpr (SPARSE) {
+    if (SPARSE && tables) {
 #pragma unroll
         for (int g = 0; g < lay.groups; ++g) {
             unsigned t0 = 15u, t1 = 15u, f0 = 0u, f1 = 1u;
@@ -138,7 +153,7 @@ __device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigne
                 n += live;
             }
             if (n == 1) f1 = (f0 + 1) & 3;
-            L.slots[tid * kTapGroups + g] = (uint16_t)(t0 | (t1 << 4) | (f0 << 8) | (f1 << 10));
+            L.slots[pattern * kTapGroups + g] = (uint16_t)(t0 | (t1 << 4) | (f0 << 8) | (f1 << 10));
         }
     }
     __syncthreads();
@@ -152,7 +167,7 @@ __device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigne
         if (co >= Co || c >= channels) continue;
         const int64_t g = (int64_t)co * Ci + SC * stage + c;
         live_idx[g] = iv[i];
-        const uint64_t taps = L.taps[iv[i]];
+        const uint64_t taps = L.taps[entry[i]];
         for (int j = 0; j < k; ++j) {
             const unsigned t = (unsigned)(taps >> (4 * j)) & 15u;
             T v = L.w[r][c * 9 + (t < 9 ? t : 0)];
@@ -217,38 +232,59 @@ __device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigne
     }
 }
 
-// A lane's 16 bytes of a 1x1 fragment: consecutive elements of row co starting at channel ci0, pruned.
-template <typename T>
-__device__ __forceinline__ u32x4 pack_piece1x1(const T* __restrict__ w, const uint8_t* __restrict__ idx, const uint16_t* masks,
-                                               int Co, int Ci, int co, int ci0)
-{
-    constexpr int PER = 16 / (int)sizeof(T);
-    u32x4 pk = {0, 0, 0, 0};
-    if (co >= Co || ci0 >= Ci) return pk;
-    // element f of the flattened matrix sits in group f/9 at tap f%9 (groups may straddle rows; the tail has no group)
-    const int64_t f0 = (int64_t)co * Ci + ci0, G = (int64_t)Co * Ci / 9;
-    const int64_t g0 = f0 < (int64_t)1 << 31 ? (int64_t)((uint32_t)f0 / 9u) : f0 / 9;
-    const int t0 = (int)(f0 - 9 * g0);
-    if (g0 >= G) return pk;  // all tail (a tensor of fewer than nine weights may come without pointers)
-    const unsigned m0 = masks[idx[g0]], m1 = g0 + 1 < G ? masks[idx[g0 + 1]] : 0u;
-    const unsigned live = (m0 | m1 << 9) >> t0;  // bit j: element f0 + j survives
-    T v[PER];
-    if (Ci % PER == 0 && (reinterpret_cast<uintptr_t>(w) & 15) == 0) {
-        const u32x4 raw = *(const u32x4*)(w + f0);
-        __builtin_memcpy(v, &raw, 16);
-    } else {
+// A lane's 16 bytes of a 1x1 fragment: consecutive elements of row co starting at channel ci0, pruned.  In two steps, so that the
+// loads of a lane's pieces are in flight together: what is loaded, and what becomes of it.
+template <typename T> struct Piece1x1 {
+    static constexpr int PER = 16 / (int)sizeof(T);
+    u32x4 raw;
+    uint8_t p0, p1;  // pattern indices of the two groups the piece touches (p1 past the last group: none)
+    int t0;          // first element's tap in its group
+    bool first, second;  // which of them exist
+    __device__ __forceinline__ void load(const T* __restrict__ w, const uint8_t* __restrict__ idx, int Co, int Ci, int co, int ci0)
+    {
+        raw = u32x4{0, 0, 0, 0};
+        p0 = p1 = 0;
+        t0 = 0;
+        first = second = false;
+        if (co >= Co || ci0 >= Ci) return;
+        // element f of the flattened matrix sits in group f/9 at tap f%9 (groups may straddle rows; the tail has no group)
+        const int64_t f0 = (int64_t)co * Ci + ci0, G = (int64_t)Co * Ci / 9;
+        const int64_t g0 = f0 < (int64_t)1 << 31 ? (int64_t)((uint32_t)f0 / 9u) : f0 / 9;
+        t0 = (int)(f0 - 9 * g0);
+        first = g0 < G;  // else all tail (a tensor of fewer than nine weights may come without pointers)
+        if (!first) return;
+        second = g0 + 1 < G;
+        p0 = idx[g0];
+        if (second) p1 = idx[g0 + 1];
+        if (Ci % PER == 0 && (reinterpret_cast<uintptr_t>(w) & 15) == 0) {
+            raw = *(const u32x4*)(w + f0);
+        } else {
+            T v[PER];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            __builtin_memset(&v[j], 0, sizeof(T));
-            if (ci0 + j < Ci) v[j] = w[f0 + j];
+            for (int j = 0; j < PER; ++j) {
+                __builtin_memset(&v[j], 0, sizeof(T));
+                if (ci0 + j < Ci) v[j] = w[f0 + j];
+            }
+            __builtin_memcpy(&raw, v, 16);
         }
     }
+    __device__ __forceinline__ u32x4 pruned(const uint16_t* masks) const
+    {
+        const unsigned m0 = first ? masks[p0] : 0u, m1 = second ? masks[p1] : 0u;
+        const unsigned live = (m0 | m1 << 9) >> t0;  // bit j: the piece's element j survives
+        u32x4 pk;
 #pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (!((live >> j) & 1u)) __builtin_memset(&v[j], 0, sizeof(T));
-    __builtin_memcpy(&pk, v, 16);
-    return pk;
-}
+        for (int d = 0; d < 4; ++d) {
+            if constexpr (sizeof(T) == 4) {
+                pk[d] = (live >> d) & 1u ? raw[d] : 0u;
+            } else {
+                const unsigned pair = live >> (2 * d);
+                pk[d] = raw[d] & (((pair & 1u) ? 0xffffu : 0u) | ((pair & 2u) ? 0xffff0000u : 0u));
+            }
+        }
+        return pk;
+    }
+};
 
 // A lane's 16 bytes of a stem fragment (Ci <= 3): K = kh*3*Ci + kw*Ci + ci.  Rows are dealt over each pair of channel
 // tiles so that the 4 + 4 accumulator values a lane holds are the 8 consecutive channels 32*(mt/2) + 8q .. +7.
@@ -294,14 +330,13 @@ __global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
         uint32_t w[sizeof(PackEntry) / 4];
     } row, pick;
     row.e = tab.e[lane0 < kPackMax ? lane0 : 0];
-    const unsigned mask = dict.mask[tid];
-    masks[tid] = (uint16_t)mask;
+    const unsigned mask = dict.mask[dict.P < kOneWave ? tid & (kOneWave - 1) : tid];  // of the pattern whose table entries this lane makes
+    masks[tid] = dict.mask[tid];
     const int t = __builtin_popcountll(__ballot(my_first <= (int)blockIdx.x)) - 1;
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(PackEntry) / 4); ++i) pick.w[i] = (uint32_t)__builtin_amdgcn_readlane((int)row.w[i], t);
     const PackEntry en = pick.e;
     int block = (int)blockIdx.x - __builtin_amdgcn_readlane(my_first, t);
-    __syncthreads();
     const bool is3x3 = en.format == kFormatSparse24 || en.format == kFormatDense3x3;
     char* section = en.blob + (size_t)en.mat_off * 256;
     const int stages = (en.Ci + stage_channels(sizeof(T) == 4 ? RTOSS_F32 : RTOSS_F16) - 1) / (64 / (int)sizeof(T));
@@ -310,11 +345,11 @@ __global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
         if (block < (int)en.items) {
             if constexpr (sizeof(T) == 2)
                 if (en.format == kFormatSparse24) {
-                    if (en.a == 0) pack_tile3x3<T, 0>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
-                    else pack_tile3x3<T, 1>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
+                    if (en.a == 0) pack_tile3x3<T, 0>(en, dict.k, dict.P, mask, masks, block, m_tiles, lds.tile);
+                    else pack_tile3x3<T, 1>(en, dict.k, dict.P, mask, masks, block, m_tiles, lds.tile);
                     return;
                 }
-            pack_tile3x3<T, kDenseTaps>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
+            pack_tile3x3<T, kDenseTaps>(en, dict.k, dict.P, mask, masks, block, m_tiles, lds.tile);
             return;
         }
         // the block behind the tiles writes the block of zeros
@@ -322,42 +357,59 @@ __global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
         for (int b = tid * 16; b < zero_section_bytes(stages); b += 4096) *(u32x4*)(section + end + b) = u32x4{0, 0, 0, 0};
         return;
     }
-    // other formats: first the public section, 256 groups per block
+    __syncthreads();  // masks  (3x3 tiles have a barrier of their own in front of their first use)
+    // other formats: first the public section
     const int ks2 = en.format == kFormatStem || en.c == 9 ? 9 : 1;
     LiveJob job;
     job.G = (int64_t)en.Co * en.Ci * ks2 / 9;
-    job.blocks = (int)((job.G + 255) / 256);
+    job.blocks = (int)((job.G + 256 * kLiveRuns - 1) / (256 * kLiveRuns));
     if (block < job.blocks) {
         job.live = en.blob;
         job.live_idx = (uint8_t*)en.blob + (size_t)en.idx_off * 256;
-        pack_live_block<T>((const T*)en.w, en.idx, masks, dict.k, job, block, lds.live);
+        for (int i = 0; i < kLiveRuns && (int64_t)(block * kLiveRuns + i) * 256 < job.G; ++i)
+            pack_live_block<T>((const T*)en.w, en.idx, masks, dict.k, job, block * kLiveRuns + i, lds.live);
         return;
     }
-    const int item = (block - job.blocks) * 256 + tid;
+    const int base = (block - job.blocks) * 256 * kPieces + tid;
     const T* w = (const T*)en.w;
-    if (item >= (int)en.items) {
-        const int zeros = en.format == kFormatStem ? 0 : zero_section_bytes(stages) / 16;
-        if (item < (int)en.items + zeros) *(u32x4*)(section + (size_t)item * 16) = u32x4{0, 0, 0, 0};
-        return;
-    }
-    const int lane = item % 64, r = lane % 16, q = lane / 16;
     constexpr int PER = 16 / (int)sizeof(T);
-    int f = item / 64;
-    if (en.format == kFormatDenseStream) {
-        // rows permuted so that a lane's 4*MT accumulator values are consecutive channels
-        const int KS = en.a, MT = en.b;
-        const int s = f % KS;
-        f /= KS;
-        const int m = f % MT;
-        f /= MT;
-        const int co = f * (16 * MT) + (r / 4) * (4 * MT) + 4 * m + (r % 4);  // (f: channel block and wave slice)
-        *(u32x4*)(section + (size_t)item * 16) = pack_piece1x1<T>(w, en.idx, masks, en.Co, en.Ci, co, 4 * PER * s + PER * q);
-    } else if (en.format == kFormatDense) {
-        const int m_tiles = (int)en.items / (64 * stages);
-        const int mt = f % m_tiles, s = f / m_tiles;
-        *(u32x4*)(section + (size_t)item * 16) = pack_piece1x1<T>(w, en.idx, masks, en.Co, en.Ci, 16 * mt + r, 4 * PER * s + PER * q);
-    } else if constexpr (sizeof(T) == 2) {  // stem
-        *(u32x4*)(section + (size_t)item * 16) = pack_piece_stem<T>(w, en.idx, masks, en.Co, en.Ci, item);
+    const int zeros = en.format == kFormatStem ? 0 : zero_section_bytes(stages) / 16;
+    if constexpr (sizeof(T) == 2)
+        if (en.format == kFormatStem) {
+            for (int i = 0; i < kPieces; ++i) {
+                const int item = base + 256 * i;
+                if (item < (int)en.items) *(u32x4*)(section + (size_t)item * 16) = pack_piece_stem<T>(w, en.idx, masks, en.Co, en.Ci, item);
+            }
+            return;
+        }
+    if (en.format != kFormatDenseStream && en.format != kFormatDense) return;
+    Piece1x1<T> piece[kPieces];
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+        const int item = base + 256 * i, lane = item % 64, r = lane % 16, q = lane / 16;
+        int co = en.Co, s = 0;  // (past the fragments: nothing)
+        int f = item / 64;
+        if (item < (int)en.items) {
+            if (en.format == kFormatDenseStream) {
+                // rows permuted so that a lane's 4*MT accumulator values are consecutive channels (KS and MT are powers of two)
+                const int log_ks = en.a, log_mt = en.b;
+                s = f & ((1 << log_ks) - 1);
+                f >>= log_ks;
+                const int m = f & ((1 << log_mt) - 1);
+                f >>= log_mt;
+                co = ((f * 16 + (r / 4) * 4) << log_mt) + 4 * m + (r % 4);  // (f: channel block and wave slice)
+            } else {
+                const int m_tiles = (int)en.items / (64 * stages);
+                s = f / m_tiles;
+                co = 16 * (f - s * m_tiles) + r;
+            }
+        }
+        piece[i].load(w, en.idx, en.Co, en.Ci, co, 4 * PER * s + PER * q);
+    }
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+        const int item = base + 256 * i;
+        if (item < (int)en.items + zeros) *(u32x4*)(section + (size_t)item * 16) = piece[i].pruned(masks);
     }
 }
 
@@ -376,7 +428,8 @@ rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, P
     en->format = (uint8_t)g.format;
     en->a = en->b = en->c = 0;
     const int stages = stage_count(d);
-    const int64_t live_blocks = (g.G + 255) / 256;
+    const int64_t live_blocks = (g.G + 256 * kLiveRuns - 1) / (256 * kLiveRuns);
+    const auto piece_blocks = [](int64_t pieces) { return (pieces + 256 * kPieces - 1) / (256 * kPieces); };
     int64_t items = 0;
     switch (g.format) {
     case kFormatSparse24:
@@ -390,15 +443,15 @@ rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, P
         break;
     case kFormatDenseStream: {
         const int KS = stages, MT = stream_mt_of(KS), WM = stream_wm_of(KS, d.Co);
-        en->a = (uint8_t)KS;
-        en->b = (uint8_t)MT;
+        en->a = (uint8_t)__builtin_ctz(KS);
+        en->b = (uint8_t)__builtin_ctz(MT);
         items = (int64_t)stream_co_blocks_of(KS, d.Co) * WM * MT * KS * 64;
-        *blocks = live_blocks + (items + zero_section_bytes(stages) / 16 + 255) / 256;
+        *blocks = live_blocks + piece_blocks(items + zero_section_bytes(stages) / 16);
         break;
     }
     case kFormatDense:
         items = (int64_t)stages * ring_padded_tiles(d.Co) * 64;
-        *blocks = live_blocks + (items + zero_section_bytes(stages) / 16 + 255) / 256;
+        *blocks = live_blocks + piece_blocks(items + zero_section_bytes(stages) / 16);
         break;
     case kFormatStem:
         items = 4 * 64;
@@ -418,15 +471,22 @@ rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, P
 rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, const Dict& dict, hipStream_t s)
 {
     const int layout = std::max(0, dict.layout);
+    // 3x3 layers first: their workgroups take longest
+    std::vector<int> order((size_t)n);
+    int at = 0;
+    for (const int ksize : {3, 1})
+        for (int i = 0; i < n; ++i)
+            if (items[i].d.ksize == ksize) order[at++] = i;
     for (int dt : {(int)RTOSS_F32, (int)RTOSS_F16, (int)RTOSS_BF16})
         for (int i = 0; i < n;) {  // i runs on across launches
             PackTable tab;
             int m = 0;
             int64_t total = 0;
             for (; i < n && m < kPackMax; ++i) {
-                if ((int)items[i].d.dt != dt) continue;
+                const PackItem& it = items[order[i]];
+                if ((int)it.d.dt != dt) continue;
                 int64_t blocks = 0;
-                if (rtoss_status st = make_entry(items[i], geo[i], layout, &tab.e[m], &blocks)) return st;
+                if (rtoss_status st = make_entry(it, geo[order[i]], layout, &tab.e[m], &blocks)) return st;
                 if (blocks == 0) continue;
                 if (total + blocks > kMaxGridGroups) break;  // (one layer fits: make_entry)
                 tab.first_block[m++] = (int)total;
