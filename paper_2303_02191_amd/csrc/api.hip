@@ -9,6 +9,7 @@
 
 #include "common.h"
 #include "epilogue.h"
+#include "sparse_frag.h"
 
 namespace rtoss {
 
@@ -47,10 +48,8 @@ rtoss_status current_device(DeviceInfo* out)
     return RTOSS_OK;
 }
 
-rtoss_status ensure_dynamic_lds(const void* kernel, size_t bytes, LaunchOnce& once, const char* what)
+rtoss_status ensure_dynamic_lds(const void* kernel, size_t bytes, LaunchOnce& once, int dev, const char* what)
 {
-    int dev = 0;
-    if (rtoss_status st = check_hip(hipGetDevice(&dev), "hipGetDevice")) return st;
     const bool tracked = dev >= 0 && dev < 64;
     if (tracked && (once.done.load(std::memory_order_acquire) >> dev & 1u)) return RTOSS_OK;
     if (rtoss_status st = check_hip(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes), what))
@@ -113,28 +112,51 @@ static unsigned reverse9(unsigned m)
     return r;
 }
 
+// Of every 9-bit mask: its taps, and the 2-of-4 layouts (sparse_frag.h) it fits, one bit each: at most two live taps in each set.
+struct MaskTable {
+    uint8_t taps[512] = {}, layouts[512] = {};
+};
+static constexpr MaskTable make_mask_table()
+{
+    MaskTable t;
+    for (unsigned m = 0; m < 512; ++m) {
+        for (unsigned r = m; r; r &= r - 1) ++t.taps[m];
+        for (int l = 0; l < kNumLayouts; ++l) {
+            bool fits = true;
+            for (int g = 0; g < kLayouts[l].groups; ++g) {
+                int live = 0;
+                for (int f = 0; f < 4; ++f)
+                    if (kLayouts[l].tap[g][f] >= 0) live += m >> kLayouts[l].tap[g][f] & 1u;
+                fits = fits && live <= 2;
+            }
+            if (fits) t.layouts[m] |= 1u << l;
+        }
+    }
+    return t;
+}
+static constexpr MaskTable kMaskTable = make_mask_table();
+static int tap_count(unsigned m) { return m < 512 ? kMaskTable.taps[m] : __builtin_popcount(m); }
+
 // Validates a caller dictionary and copies it into launch-argument form.
 static rtoss_status load_dict(const uint16_t* masks_host, int P, Dict* out)
 {
     if (!masks_host) return fail(RTOSS_EINVAL, "dictionary pointer is NULL");
     if (P < 1 || P > kMaxPatterns) return fail(RTOSS_EINVAL, "dictionary size P=%d outside 1..%d", P, kMaxPatterns);
+    // (every convolution call comes through here: table look-ups, no loops over taps)
     std::memset(out, 0, sizeof *out);
-    const auto taps = [](unsigned m) {  // (no population count instruction on the baseline host target)
-        int n = 0;
-        for (; m; m &= m - 1) ++n;
-        return n;
-    };
-    const int k = taps(masks_host[0]);
+    const int k = tap_count(masks_host[0]);
+    unsigned layouts = ~0u;
     for (int p = 0; p < P; ++p) {
         const unsigned m = masks_host[p];
         if (m == 0 || m > 0x1ffu) return fail(RTOSS_EINVAL, "pattern %d (0x%x) is not a non-empty 9-bit mask", p, m);
-        if (taps(m) != k)
-            return fail(RTOSS_EINVAL, "pattern %d keeps %d taps but pattern 0 keeps %d: one k per dictionary", p, taps(m), k);
+        if (tap_count(m) != k)
+            return fail(RTOSS_EINVAL, "pattern %d keeps %d taps but pattern 0 keeps %d: one k per dictionary", p, tap_count(m), k);
         out->mask[p] = (uint16_t)m;
+        layouts &= kMaskTable.layouts[m];
     }
     out->P = P;
     out->k = k;
-    out->layout = sparse3x3_layout(out->mask, P);
+    out->layout = layouts ? __builtin_ctz(layouts) : -1;
     return RTOSS_OK;
 }
 
@@ -425,10 +447,9 @@ static rtoss_status conv_impl(const rtoss_wdesc* desc, const rtoss_cdesc* c, con
     BlobGeometry g;
     if (rtoss_status st = blob_geometry(desc, dict, &g, coherent)) return st;
     const char* blob = (const char*)packed_dev;
-    if (coherent) {
-        if (c->layout != RTOSS_NHWC) return fail(RTOSS_ELAYOUT, "the coherent path takes channels-last tensors");
-        return launch_conv3x3_gather(*desc, cp, blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
-    }
+    if (coherent && c->layout != RTOSS_NHWC) return fail(RTOSS_ELAYOUT, "the coherent path takes channels-last tensors");
+    if (rtoss_status st = current_device(&cp.dev)) return st;
+    if (coherent) return launch_conv3x3_gather(*desc, cp, blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
     // The element-wise kernel reads section 0 and takes any strides (NCHW) and any size.
     const bool fits = g.format == kFormatSparse24   ? sparse3x3_launch_ok(*desc, cp)
                       : g.format == kFormatDense3x3 ? dense3x3_launch_ok(*desc, cp)

@@ -75,13 +75,13 @@ struct DeviceInfo {
     int cus;
 };
 rtoss_status current_device(DeviceInfo* out);
-// Raises a kernel's dynamic-LDS limit to `bytes` on the current device, once per (kernel instantiation,
+// Raises a kernel's dynamic-LDS limit to `bytes` on device `dev` (the current one), once per (kernel instantiation,
 // device): `done` is the instantiation's own word, bit d = done on device d.  Safe to call from several
 // threads (the attribute call is idempotent; the word only saves repeating it).
 struct LaunchOnce {
     std::atomic<uint64_t> done{0};
 };
-rtoss_status ensure_dynamic_lds(const void* kernel, size_t bytes, LaunchOnce& once, const char* what);
+rtoss_status ensure_dynamic_lds(const void* kernel, size_t bytes, LaunchOnce& once, int dev, const char* what);
 
 // ----- launchers (one per kernel family; defined next to the kernels) -----
 rtoss_status launch_select(const void* w, rtoss_dtype dt, int64_t G, const Dict& dict, uint8_t* idx, hipStream_t s);
@@ -89,7 +89,9 @@ rtoss_status launch_select(const void* w, rtoss_dtype dt, int64_t G, const Dict&
 constexpr int kSelectBatchMax = 64;  // tensors per batched selection launch
 rtoss_status launch_select_batch(const rtoss_select_item* items, int n, rtoss_dtype dt, const Dict& dict, hipStream_t s);
 
-// counts of each pattern index (select.hip)
+// counts of each pattern index (select.hip); clear_counts: zeros the counters of a dictionary of at most 256 patterns (also called
+// by host_ext.cpp, whose fresh counters need no trip through the framework's fill)
+rtoss_status clear_counts(uint32_t* hist, int P, hipStream_t s);
 rtoss_status launch_histogram(const uint8_t* idx, int64_t G, int P, uint32_t* hist, hipStream_t s);
 
 rtoss_status launch_conv_direct(const rtoss_wdesc& d, const ConvParams& c, const Dict& dict, const void* live_values,
@@ -111,7 +113,6 @@ rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, 
 
 // 3x3 convolution on the sparse matrix instruction (conv3x3_sparse.hip)
 bool sparse3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c);
-int sparse3x3_layout(const uint16_t* masks, int P);  // Dict::layout
 bool sparse3x3_shape_ok(const rtoss_wdesc& d);
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout);
 rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, int layout, const void* section, const void* x,

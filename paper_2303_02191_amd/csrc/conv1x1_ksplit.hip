@@ -204,8 +204,7 @@ int ksplit1x1_plan(const rtoss_wdesc& d, const ConvParams& c)
 {
     const int KS = stage_count(d);
     if (KS < 4) return kNone;
-    DeviceInfo dev;
-    if (current_device(&dev)) return kNone;
+    const DeviceInfo& dev = c.dev;
     const int64_t cus = dev.cus, P = (int64_t)c.N * c.H * c.W;
     const auto groups = [&](int tm, int tn) { return (int64_t)((section_tiles(KS, d.Co) + tm - 1) / tm) * ((P + 16 * tn - 1) / (16 * tn)); };
     if (P > 0x7fffff00 || groups(2, 1) > kMaxGridGroups) return kNone;

@@ -400,7 +400,7 @@ rtoss_status launch_whole_rows_tile(const rtoss_wdesc& d, const ConvParams& c, c
     constexpr int extra = 16 + EpiScaleBias<64 * TM>::kBytes;
     auto kern = conv1x1_mma_kernel<T, TO, TM, TN, ROW16>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, kTileBytes + extra, lds_once, "conv1x1 shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, kTileBytes + extra, lds_once, c.dev.device, "conv1x1 shared memory attribute")) return st;
     const int64_t groups = std::min<int64_t>(8 * per_xcd, kMaxGridGroups);
     kern<<<dim3((unsigned)groups), dim3(256), (size_t)pitch * PT + extra, s>>>(
         (const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Ci, d.Co, ring_padded_tiles(d.Co), (int)total, (int)per_xcd, pitch, span, blocks,
@@ -417,8 +417,7 @@ rtoss_status launch_whole_rows(const rtoss_wdesc& d, const ConvParams& c, const 
     if (tiles <= 4) return launch_whole_rows_tile<T, TO, 1, 2, ROW16>(d, c, wfrag, x, y, s);
     if (tiles <= 8) return launch_whole_rows_tile<T, TO, 2, 2, ROW16>(d, c, wfrag, x, y, s);
     if constexpr (sizeof(T) == 2) {
-        DeviceInfo dev;
-        if (rtoss_status st = current_device(&dev)) return st;
+        const DeviceInfo& dev = c.dev;
         if ((int64_t)c.N * c.H * c.W > 64 * (int64_t)dev.cus) return launch_whole_rows_tile<T, TO, 4, 4, ROW16>(d, c, wfrag, x, y, s);
     }
     return launch_whole_rows_tile<T, TO, 4, 2, ROW16>(d, c, wfrag, x, y, s);
@@ -437,7 +436,7 @@ rtoss_status launch_tm(const rtoss_wdesc& d, const ConvParams& c, const char* wf
     const size_t smem = (size_t)kRing * stage_bytes;
     auto kern = conv1x1_mma_kernel<T, TO, TM>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv1x1 shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv1x1 shared memory attribute")) return st;
     dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Ci, d.Co, ring_padded_tiles(d.Co),
                                    co_blocks, (int)total, work_per_xcd, c.ep);
@@ -457,8 +456,7 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
     //     fp16  96 -> 128 (6400) 6.6 4.6   192 -> 256 (6400) 7.9 6.1   384 -> 256 (6400) 10.0 7.7   192 -> 256 (12 800) 8.3 8.4  stays
     //     fp16 192 ->  48 (6400) 5.2 5.1  stays   384 -> 512 (6400) 10.6 13.1  stays
     //     fp32  96 -> 128 (6400) 11.9 6.2  240 ->  48 (6400) 12.2 7.0  240 -> 256 (400) 21.1 12.2   240 -> 48 (25 600) 13.0 19.5  stays
-    DeviceInfo dev;
-    if (rtoss_status st = current_device(&dev)) return st;
+    const DeviceInfo& dev = c.dev;
     if ((int64_t)c.N * c.H * c.W <= 32 * (int64_t)dev.cus && tiles <= 16 && (tiles > 4 || sizeof(T) == 4))
         return launch_whole_rows<T, TO, true>(d, c, wfrag, x, y, s);
     if (tiles <= 2) return launch_tm<T, TO, 2>(d, c, wfrag, x, y, s);

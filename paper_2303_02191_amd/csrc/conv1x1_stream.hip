@@ -272,7 +272,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const size_t smem = (size_t)PL::RING * PL::BUF + EpiScaleBias<PL::SPAN>::kBytes;
     auto kern = conv1x1_stream_kernel<T, TO, KS, WM>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv1x1 shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv1x1 shared memory attribute")) return st;
     // Persistent workgroups: as many as are resident at once, but no fewer than 2 buffers each: every
     // workgroup loads its weight fragments once, which for deep layers is more bytes than a buffer.
     // fp32 steps take 16 times as long: there a launch that gives most compute units one workgroup or none is spread over
@@ -286,8 +286,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, 320, smem) != hipSuccess || per_cu < 1) per_cu = 1;
         per_cu_cached.store(per_cu, std::memory_order_relaxed);
     }
-    DeviceInfo dev;
-    if (rtoss_status st = current_device(&dev)) return st;
+    const DeviceInfo& dev = c.dev;
     const int resident = std::max(8, dev.cus) * per_cu;
     const bool spread = sizeof(T) == 4 && 2 * nbuf * co_blocks <= 3 * dev.cus;
     const int64_t by_work = spread ? nbuf : std::max<int64_t>(1, (nbuf + 1) / 2);

@@ -207,7 +207,7 @@ rtoss_status launch_shape(const rtoss_wdesc& d, const ConvParams& c, const char*
     const size_t smem = (size_t)(a_copies_per_wave + x_copies_per_wave) * 4096;
     auto kern = conv3x3_dense_kernel<T, TO, S, TM, RT, CT, RAG>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv3x3 dense shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv3x3 dense shared memory attribute")) return st;
     const int ygrid = cblocks * (kTM / TM);
     if (c.N > 65535 || ygrid > 65535) return fail(RTOSS_ESHAPE, "conv: batch or channel count too large");
     dim3 grid((unsigned)(tiles_r * tiles_c), (unsigned)ygrid, (unsigned)c.N), block(256);
@@ -241,7 +241,7 @@ rtoss_status launch_f32_rows(const rtoss_wdesc& d, const ConvParams& c, const ch
     auto kern = conv3x3_dense_kernel<float, float, S, R, RAG>;
     constexpr int lds = F32Tile<S, R>::LDS;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, "conv3x3 dense shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, c.dev.device, "conv3x3 dense shared memory attribute")) return st;
     if (c.N > 65535 || cblocks * kTM > 65535) return fail(RTOSS_ESHAPE, "conv: batch or channel count too large");  // (as above)
     const int64_t total = (int64_t)tiles_r * tiles_c * cblocks * c.N;  // (at most kMaxGridGroups: dense3x3_launch_ok)
     const int work_per_xcd = (int)((total + 7) / 8);
@@ -290,8 +290,7 @@ int f32_rows(const rtoss_wdesc& d, const ConvParams& c, int64_t cus)
 
 template <bool RAG> rtoss_status launch_f32(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
-    DeviceInfo dev;
-    if (rtoss_status st = current_device(&dev)) return st;
+    const DeviceInfo& dev = c.dev;
     const int rows = f32_rows(d, c, dev.cus);
     if (c.stride == 2) {
         if (rows == 0) return launch_shape<float, float, 2, 1, 1, 4, RAG>(d, c, wfrag, x, y, s);

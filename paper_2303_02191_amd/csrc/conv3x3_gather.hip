@@ -739,7 +739,7 @@ rtoss_status launch_gather(const rtoss_wdesc& d, const ConvParams& c, const char
     const size_t smem = (size_t)(a_copies_per_wave + x_copies_per_wave) * 4096 + kMaxStages * 4 + kMaxStages * 4 * 12 * 2;
     auto kern = conv3x3_gather_kernel<T, TO, S>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv3x3 gather shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv3x3 gather shared memory attribute")) return st;
     if (c.N > 65535 || cblocks > 65535) return fail(RTOSS_ESHAPE, "conv: batch or channel count too large");
     dim3 grid((unsigned)(tiles_r * tiles_c), (unsigned)cblocks, (unsigned)c.N), block(256);
     const char* frags = section + header_bytes(d);
@@ -764,9 +764,8 @@ rtoss_status launch_gather_rows(const rtoss_wdesc& d, const ConvParams& c, const
 {
     auto kern = conv3x3_gather_rows_kernel<T, T>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, kGrSmem, lds_once, "conv3x3 gather shared memory attribute")) return st;
-    DeviceInfo dev;
-    if (rtoss_status st = current_device(&dev)) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, kGrSmem, lds_once, c.dev.device, "conv3x3 gather shared memory attribute")) return st;
+    const DeviceInfo& dev = c.dev;
     const int co_blocks = ((d.Co + 15) / 16 + kRowsTM - 1) / kRowsTM;
     if (c.stride != 1 || d.Ci % 32 || d.Ci < 96) return fail(RTOSS_ESHAPE, "conv: the pipelined kernel needs stride 1 and three or more stages of 32 input channels");
     if ((int64_t)c.N * c.H * c.W * d.Ci / 8 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");

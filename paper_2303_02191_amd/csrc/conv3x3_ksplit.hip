@@ -314,7 +314,7 @@ rtoss_status launch_variant(const rtoss_wdesc& d, const ConvParams& c, const cha
     const int co_blocks = channel_tiles(d.Co) / TM;
     auto kern = conv3x3_ksplit_kernel<T, TO, S, TM, RT, CT, LAY>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, K::LDS, lds_once, "conv3x3 shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, K::LDS, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)tiles_r * tiles_c * co_blocks * c.N;
     if (total > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
     if ((int64_t)c.N * c.H * c.W * d.Ci * (int)sizeof(T) / 16 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
@@ -366,8 +366,7 @@ int ksplit3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
 {
     if (d.Ci * elem_bytes(d.dt) % 64 || d.Co % 16) return kNone;
     if ((int64_t)c.N * c.H * c.W * d.Ci * elem_bytes(d.dt) / 16 > kMaxChunks) return kNone;  // (the dense-mode kernel has no such limit)
-    DeviceInfo dev;
-    if (current_device(&dev)) return kNone;
+    const DeviceInfo& dev = c.dev;
     const int64_t cus = dev.cus;
     const int stages = d.Ci * elem_bytes(d.dt) / 64;
     const int Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1;

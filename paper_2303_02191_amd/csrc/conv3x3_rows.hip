@@ -635,9 +635,8 @@ rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const size_t smem = 2 * ((size_t)kRowsTM * kTileBytes + (size_t)x_copies_per_wave * 4096);
     auto kern = conv3x3_rows_kernel<T, TO, FUSED>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv3x3 shared memory attribute")) return st;
-    DeviceInfo dev;
-    if (rtoss_status st = current_device(&dev)) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
+    const DeviceInfo& dev = c.dev;
     const int co_blocks = ((d.Co + 15) / 16 + kRowsTM - 1) / kRowsTM;
     if (c.stride != 1 || d.Ci % 32 || d.Ci < 96) return fail(RTOSS_ESHAPE, "conv: the pipelined kernel needs stride 1 and three or more stages of 32 input channels");
     if ((int64_t)c.N * c.H * c.W * d.Ci / 8 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");

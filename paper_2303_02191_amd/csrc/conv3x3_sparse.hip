@@ -346,7 +346,7 @@ rtoss_status launch_variant_sb(const rtoss_wdesc& d, const ConvParams& c, const 
     const size_t smem = (DB ? 2 : 1) * ((size_t)TM * layout_tile_bytes(kLayouts[LAY]) + (size_t)x_copies_per_wave * 4096) + EpiScaleBias<16 * TM>::kBytes;
     auto kern = conv3x3_sparse_sb_kernel<T, TO, S, TM, TN, RT, CT, AHEAD, LAY, DB, RAG>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, "conv3x3 shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)tiles_r * tiles_c * co_blocks * c.N;
     if (total > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
     if ((int64_t)c.N * c.H * c.W * d.Ci / 8 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
@@ -420,27 +420,6 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 }  // namespace
 
 // ---- host-visible entry points of this file ----
-
-int sparse3x3_layout(const uint16_t* masks, int P)
-{
-    for (int l = 0; l < kNumLayouts; ++l) {
-        bool fits = true;
-        for (int g = 0; g < kLayouts[l].groups && fits; ++g) {
-            unsigned set = 0;
-            for (int f = 0; f < 4; ++f)
-                if (kLayouts[l].tap[g][f] >= 0) set |= 1u << kLayouts[l].tap[g][f];
-            unsigned third = 0;  // non-zero once a pattern has three live taps in the set
-            for (int p = 0; p < P; ++p) {
-                unsigned m = masks[p] & set;
-                m &= m - 1;
-                third |= m & (m - 1);
-            }
-            fits = third == 0;
-        }
-        if (fits) return l;
-    }
-    return -1;
-}
 
 bool sparse3x3_shape_ok(const rtoss_wdesc& d)
 {

@@ -391,7 +391,7 @@ rtoss_status launch_dense_rows(const rtoss_wdesc& d, const ConvParams& c, const 
     auto kern = conv3x3_strip_kernel<T, TO, ROWS>;
     constexpr int lds = dense_strip_lds<T, ROWS>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, "conv3x3 shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)strips * rows * co_blocks * c.N;  // (at most kMaxGridGroups: strip3x3_plan)
     const int work_per_xcd = (int)((total + 7) / 8);
     kern<<<dim3((unsigned)(work_per_xcd * 8)), dim3(256), lds, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, strips,
@@ -407,7 +407,7 @@ rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const int co_blocks = (d.Co + 63) / 64;
     auto kern = conv3x3_strip_kernel<T, TO, TN, LAY, DB>;
     static LaunchOnce lds_once;  // per instantiation
-    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, P::LDS, lds_once, "conv3x3 shared memory attribute")) return st;
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, P::LDS, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)strips * rows * co_blocks * c.N;
     if (total > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
     if ((int64_t)c.N * c.H * c.W * d.Ci * (int)sizeof(T) / 16 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
@@ -483,8 +483,7 @@ int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
 
 static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int layout)
 {
-    DeviceInfo dev;
-    if (current_device(&dev)) return 0;
+    const DeviceInfo& dev = c.dev;
     const int64_t cus = dev.cus;
     const int stages = stage_count(d);
     const auto groups = [&](int tn) {

@@ -4,6 +4,7 @@
 // blocks the pruned layers sit in; Section V reports whole-model inference).  All arithmetic is
 // fp32; the result is rounded once when it is stored.
 #pragma once
+#include "common.h"
 #include "dtypes.h"
 #include "mma.h"
 
@@ -23,6 +24,7 @@ struct Epilogue {
 
 struct ConvParams : rtoss_cdesc {
     Epilogue ep;
+    DeviceInfo dev;  // asked for once per call
 };
 
 // v[i] / (1 + exp(-v[i])), each quotient correctly rounded, whatever type the result is stored in.

@@ -7,7 +7,6 @@
 #include <Python.h>
 
 #include <ATen/hip/EmptyTensor.h>
-#include <ATen/ops/zeros.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -17,6 +16,10 @@
 #include <vector>
 
 #include "rtoss.h"
+
+namespace rtoss {
+rtoss_status clear_counts(uint32_t* hist, int P, hipStream_t s);  // select.hip
+}
 
 namespace {
 
@@ -427,12 +430,18 @@ PyObject* py_histogram(PyObject*, PyObject* const* a, Py_ssize_t n)
         const int P = (int)integer(a[1]);
         require(idx.is_cuda() && idx.scalar_type() == at::kByte && idx.is_contiguous(), "idx must be a contiguous uint8 cuda tensor");
         at::Tensor made;
-        if (a[2] == Py_None) made = at::zeros({P}, at::TensorOptions().dtype(at::kInt).device(idx.device()));
+        const bool fresh = a[2] == Py_None;
+        if (fresh) made = allocate({P}, at::kInt, idx.device());
         const at::Tensor& hist = a[2] == Py_None ? made : tensor(a[2]);
         void* s = current_stream();
         const auto* ip = (const uint8_t*)idx.data_ptr();
         auto* hp = (uint32_t*)hist.data_ptr();
-        call([&] { return rtoss_pattern_histogram(ip, idx.numel(), P, hp, s); });
+        call([&] {
+            // (a P that the library refuses is the library's error to report)
+            if (fresh && P >= 1 && P <= 255)
+                if (const rtoss_status st = rtoss::clear_counts(hp, P, (hipStream_t)s)) return st;
+            return rtoss_pattern_histogram(ip, idx.numel(), P, hp, s);
+        });
         if (a[2] != Py_None) {
             Py_INCREF(a[2]);
             return a[2];

@@ -18,6 +18,7 @@
 // of the layers; 38 in four launches).  A workgroup of the 3x3 path takes 10 000 cycles, 2000 of them for the launch arguments, 2000
 // for weights and indices, 1800 for its part of the public section and 3300 for the fragments.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -41,12 +42,19 @@ struct PackEntry {
     uint32_t items;             // 3x3: (stage, channel tile) pairs; 1x1 and stem: 16-byte pieces of the fragments
     uint8_t format, a, b, c;    // MatrixFormat; 3x3: tap layout; streaming 1x1: log2 of KS, of MT; without fragments: weights per kernel
 };
-constexpr int kPackMax = 60;
-struct PackTable {
-    PackEntry e[kPackMax];
-    int first_block[64];  // entries past n: past every block
+constexpr int kPackMax = 60, kPackFew = 8;
+template <int N> struct PackTable {
+    PackEntry e[N];
+    int first_block[N];
 };
-static_assert(sizeof(PackTable) + sizeof(Dict) <= 4096, "launch arguments");
+static_assert(sizeof(PackTable<kPackMax>) + sizeof(Dict) <= 4096, "launch arguments");
+constexpr int kOneWave = 64;  // patterns from which on the per-pattern tables take all waves of a workgroup
+// The dictionary of a launch, by size.  (A launch with few layers and patterns writes 0.6 KB of arguments instead of 3.7, which takes
+// the host 1.3 us less.)
+struct SmallDict {
+    uint16_t mask[kOneWave];
+    int P, k;
+};
 
 // Input channel (within a 32-channel stage) that pair g of lane-quarter q refers to in sparse step `half`.
 __device__ __forceinline__ int stage_channel(int q, int g, int half)
@@ -55,7 +63,6 @@ __device__ __forceinline__ int stage_channel(int q, int g, int half)
 }
 
 constexpr int kTapGroups = 3;  // at most (TapLayout::tap)
-constexpr int kOneWave = 64;   // patterns from which on the per-pattern tables take all waves of a workgroup
 
 // 16-byte pieces of a 1x1 section that a lane writes, and runs of 256 groups of a public section that a workgroup does: what a
 // workgroup spends to find its layer is as much as one of either.
@@ -73,8 +80,8 @@ template <typename T> struct TileLds {
 // (stage, tile) of a 3x3 layer: public section and fragments
 // (LAY: tap layout, or kDenseTaps; a template parameter so that the walks over a layout's taps are constants)
 constexpr int kDenseTaps = kNumLayouts;
-template <typename T, int LAY>
-__device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, int P, unsigned mask, const uint16_t* masks, int tile,
+template <typename T, int LAY, bool SMALL>
+__device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigned mask, const uint16_t* masks, int tile,
                                              int m_tiles, TileLds<T>& L)
 {
     constexpr int SC = TileLds<T>::SC;
@@ -119,13 +126,13 @@ __device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, int P, 
     uint8_t entry[IDX_PER];  // of the per-pattern tables: an index outside the dictionary finds an entry without taps
 #pragma unroll
     for (int i = 0; i < IDX_PER; ++i) {
-        entry[i] = P < kOneWave ? (uint8_t)min((int)iv[i], kOneWave - 1) : iv[i];
+        entry[i] = SMALL ? (uint8_t)min((int)iv[i], kOneWave - 1) : iv[i];
         L.idx[(tid + 256 * i) / SC][(tid + 256 * i) % SC] = entry[i];
     }
-    // ---- per-pattern tables (under the loads above); a dictionary of fewer than 64 patterns: one wave, not the first, which has
+    // ---- per-pattern tables (under the loads above); a small dictionary (one entry at least without a pattern): one wave, not the first, which has
     // a fragment more than the others ----
-    const bool tables = P >= kOneWave || tid >= 192;  // (uniform over a wave)
-    const int pattern = P >= kOneWave ? tid : tid & (kOneWave - 1);
+    const bool tables = !SMALL || tid >= 192;  // (uniform over a wave)
+    const int pattern = SMALL ? tid & (kOneWave - 1) : tid;
     if (tables) {
         uint64_t t = ~(uint64_t)0;
         unsigned m = mask;
@@ -310,9 +317,10 @@ __device__ __forceinline__ u32x4 pack_piece_stem(const T* __restrict__ w, const 
     return pk;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
+template <typename T, int N, typename D>
+__global__ __launch_bounds__(256) void pack_kernel(PackTable<N> tab, D dict)
 {
+    constexpr bool SMALL = std::is_same_v<D, SmallDict>;
     __shared__ uint16_t masks[256];
     union Lds {
         TileLds<T> tile;
@@ -324,14 +332,15 @@ __global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
     // first blocks and its mask, and the layer's is broadcast from its lane: one round trip to the launch arguments,
     // which no cache holds yet, instead of two.
     const int lane0 = tid & 63;
-    const int my_first = tab.first_block[lane0];
+    const int slot = lane0 < N ? lane0 : 0;
+    const int my_first = lane0 < N ? tab.first_block[slot] : 0x7fffffff;  // (entries past the last layer: past every block)
     union {
         PackEntry e;
         uint32_t w[sizeof(PackEntry) / 4];
     } row, pick;
-    row.e = tab.e[lane0 < kPackMax ? lane0 : 0];
-    const unsigned mask = dict.mask[dict.P < kOneWave ? tid & (kOneWave - 1) : tid];  // of the pattern whose table entries this lane makes
-    masks[tid] = dict.mask[tid];
+    row.e = tab.e[slot];
+    const unsigned mask = dict.mask[SMALL ? tid & (kOneWave - 1) : tid];  // of the pattern whose table entries this lane makes
+    masks[tid] = SMALL && tid >= kOneWave ? (uint16_t)0 : (uint16_t)mask;
     const int t = __builtin_popcountll(__ballot(my_first <= (int)blockIdx.x)) - 1;
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(PackEntry) / 4); ++i) pick.w[i] = (uint32_t)__builtin_amdgcn_readlane((int)row.w[i], t);
@@ -345,11 +354,11 @@ __global__ __launch_bounds__(256) void pack_kernel(PackTable tab, Dict dict)
         if (block < (int)en.items) {
             if constexpr (sizeof(T) == 2)
                 if (en.format == kFormatSparse24) {
-                    if (en.a == 0) pack_tile3x3<T, 0>(en, dict.k, dict.P, mask, masks, block, m_tiles, lds.tile);
-                    else pack_tile3x3<T, 1>(en, dict.k, dict.P, mask, masks, block, m_tiles, lds.tile);
+                    if (en.a == 0) pack_tile3x3<T, 0, SMALL>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
+                    else pack_tile3x3<T, 1, SMALL>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
                     return;
                 }
-            pack_tile3x3<T, kDenseTaps>(en, dict.k, dict.P, mask, masks, block, m_tiles, lds.tile);
+            pack_tile3x3<T, kDenseTaps, SMALL>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
             return;
         }
         // the block behind the tiles writes the block of zeros
@@ -468,6 +477,30 @@ rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, P
 
 }  // namespace
 
+namespace {
+
+template <typename T, int N, typename D> rtoss_status launch_table(const PackTable<N>& tab, const D& dict, int64_t blocks, hipStream_t s)
+{
+    pack_kernel<T, N, D><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(tab, dict);
+    return check_hip(hipGetLastError(), "pack launch");
+}
+
+template <typename T> rtoss_status launch_entries(const PackTable<kPackMax>& tab, int m, const Dict& dict, int64_t blocks, hipStream_t s)
+{
+    if (dict.P >= kOneWave) return launch_table<T>(tab, dict, blocks, s);
+    SmallDict d{};
+    std::copy(dict.mask, dict.mask + dict.P, d.mask);
+    d.P = dict.P;
+    d.k = dict.k;
+    if (m > kPackFew) return launch_table<T>(tab, d, blocks, s);
+    PackTable<kPackFew> few;
+    std::copy(tab.e, tab.e + kPackFew, few.e);
+    std::copy(tab.first_block, tab.first_block + kPackFew, few.first_block);
+    return launch_table<T>(few, d, blocks, s);
+}
+
+}  // namespace
+
 rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, const Dict& dict, hipStream_t s)
 {
     const int layout = std::max(0, dict.layout);
@@ -479,7 +512,7 @@ rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, 
             if (items[i].d.ksize == ksize) order[at++] = i;
     for (int dt : {(int)RTOSS_F32, (int)RTOSS_F16, (int)RTOSS_BF16})
         for (int i = 0; i < n;) {  // i runs on across launches
-            PackTable tab;
+            PackTable<kPackMax> tab;
             int m = 0;
             int64_t total = 0;
             for (; i < n && m < kPackMax; ++i) {
@@ -493,12 +526,11 @@ rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, 
                 total += blocks;
             }
             if (m == 0) continue;
-            for (int t = m; t < 64; ++t) tab.first_block[t] = 0x7fffffff;
-            dim3 grid((unsigned)total), block(256);
-            if (dt == RTOSS_F32) pack_kernel<float><<<grid, block, 0, s>>>(tab, dict);
-            else if (dt == RTOSS_F16) pack_kernel<f16_t><<<grid, block, 0, s>>>(tab, dict);
-            else pack_kernel<bf16_t><<<grid, block, 0, s>>>(tab, dict);
-            if (rtoss_status st = check_hip(hipGetLastError(), "pack launch")) return st;
+            for (int t = m; t < kPackMax; ++t) tab.first_block[t] = 0x7fffffff;
+            const rtoss_status st = dt == RTOSS_F32   ? launch_entries<float>(tab, m, dict, total, s)
+                                    : dt == RTOSS_F16 ? launch_entries<f16_t>(tab, m, dict, total, s)
+                                                      : launch_entries<bf16_t>(tab, m, dict, total, s);
+            if (st) return st;
         }
     return RTOSS_OK;
 }

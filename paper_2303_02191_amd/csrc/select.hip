@@ -19,6 +19,7 @@
 // All tensors of a call share a launch: the table of tensors travels in the launch arguments, every lane loads one
 // entry of it, and a chunk's entry is broadcast from its lane.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "dtypes.h"
@@ -32,14 +33,16 @@ constexpr int kSelGroupsPerChunk = kSelBlock * kSelPerLane;  // 256
 
 // Tensors of one launch (the selection of a 1x1 tensor is over its own flattening, Section IV.D, so tensors cannot
 // simply be concatenated); chunks are numbered through the tensors in table order.
-struct SelectBatch {
-    const void* w[kSelectBatchMax];
-    uint8_t* idx[kSelectBatchMax];
-    int64_t G[kSelectBatchMax];
-    int first_chunk[kSelectBatchMax];  // entries past the last tensor hold the total
+// (One tensor has a table of its own size: 1 KB of launch arguments takes the host 0.4 us to write.)
+template <int N> struct SelectBatch {
+    const void* w[N];
+    uint8_t* idx[N];
+    int64_t G[N];
+    int first_chunk[N];  // entries past the last tensor hold the total
     int chunks;
 };
 static_assert(kSelectBatchMax == 64, "one entry per lane");
+struct NoDict {};  // in the launch arguments of a compiled-in dictionary
 
 template <typename T> constexpr int kSelSpan = kSelGroupsPerChunk * 9 * (int)sizeof(T);  // bytes of a chunk: 4608 or 9216
 
@@ -102,14 +105,15 @@ template <unsigned M, int END> __device__ __forceinline__ double tap_sum(const d
 }
 
 // K: the edge-connected dictionary of K-entry patterns; 0: the dictionary in the launch arguments.
-template <typename T, int K>
-__global__ __launch_bounds__(kSelBlock) void select_kernel(SelectBatch batch, Dict dict)
+template <typename T, int K, int N>
+__global__ __launch_bounds__(kSelBlock) void select_kernel(SelectBatch<N> batch, std::conditional_t<(K > 0), NoDict, Dict> dict)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];  // one chunk
     constexpr int SPAN = kSelSpan<T>, COPIES = (SPAN + 1023) / 1024;
     const int lane = threadIdx.x;
-    const int my_first = batch.first_chunk[lane];
-    const uint64_t my_w = (uint64_t)batch.w[lane], my_idx = (uint64_t)batch.idx[lane], my_G = (uint64_t)batch.G[lane];
+    const int entry = N == 1 ? 0 : lane;
+    const int my_first = batch.first_chunk[entry];
+    const uint64_t my_w = (uint64_t)batch.w[entry], my_idx = (uint64_t)batch.idx[entry], my_G = (uint64_t)batch.G[entry];
 
     struct Chunk {
         const T* span;
@@ -118,7 +122,7 @@ __global__ __launch_bounds__(kSelBlock) void select_kernel(SelectBatch batch, Di
     };
     // finds a chunk and starts copying it; whole chunks on 16-byte boundaries go straight to LDS
     auto fetch = [&](int chunk, char* lds) -> Chunk {
-        const int t = __builtin_popcountll(__ballot(my_first <= chunk)) - 1;
+        const int t = N == 1 ? 0 : __builtin_popcountll(__ballot(my_first <= chunk)) - 1;
         const int64_t g0 = (int64_t)(chunk - __builtin_amdgcn_readlane(my_first, t)) * kSelGroupsPerChunk;
         const int64_t remaining = (int64_t)from_lane(my_G, t) - g0;
         Chunk c;
@@ -225,7 +229,7 @@ __global__ __launch_bounds__(kSelBlock) void select_kernel(SelectBatch batch, Di
     }
 }
 
-template <typename T, int K> static rtoss_status launch_dict(const SelectBatch& b, const Dict& dict, hipStream_t s)
+template <typename T, int K, int N> static rtoss_status launch_dict(const SelectBatch<N>& b, const Dict& dict, hipStream_t s)
 {
     DeviceInfo dev;
     if (rtoss_status st = current_device(&dev)) return st;
@@ -233,7 +237,8 @@ template <typename T, int K> static rtoss_status launch_dict(const SelectBatch& 
     // slower (2^20 groups: 13.3 us with 16 waves per compute unit, 14.8 with 12, 17.4 with 8)
     constexpr int kPerCu = 16;
     dim3 grid((unsigned)std::min(b.chunks, dev.cus * kPerCu)), block(kSelBlock);
-    select_kernel<T, K><<<grid, block, kSelSpan<T>, s>>>(b, dict);
+    if constexpr (K > 0) select_kernel<T, K, N><<<grid, block, kSelSpan<T>, s>>>(b, NoDict{});
+    else select_kernel<T, K, N><<<grid, block, kSelSpan<T>, s>>>(b, dict);
     return check_hip(hipGetLastError(), "select launch");
 }
 
@@ -243,19 +248,24 @@ template <int K> static bool is_connected(const Dict& dict)
     return dict.P == c.P && std::equal(c.mask, c.mask + c.P, dict.mask);
 }
 
-template <typename T> static rtoss_status launch_table(const SelectBatch& b, const Dict& dict, hipStream_t s)
+template <typename T, int N> static rtoss_status launch_table(const SelectBatch<N>& b, const Dict& dict, hipStream_t s)
 {
-    if (is_connected<2>(dict)) return launch_dict<T, 2>(b, dict, s);
-    if (is_connected<3>(dict)) return launch_dict<T, 3>(b, dict, s);
-    if (is_connected<4>(dict)) return launch_dict<T, 4>(b, dict, s);
-    if (is_connected<5>(dict)) return launch_dict<T, 5>(b, dict, s);
-    return launch_dict<T, 0>(b, dict, s);
+    if (is_connected<2>(dict)) return launch_dict<T, 2, N>(b, dict, s);
+    if (is_connected<3>(dict)) return launch_dict<T, 3, N>(b, dict, s);
+    if (is_connected<4>(dict)) return launch_dict<T, 4, N>(b, dict, s);
+    if (is_connected<5>(dict)) return launch_dict<T, 5, N>(b, dict, s);
+    return launch_dict<T, 0, N>(b, dict, s);
+}
+
+template <int N> static rtoss_status launch_dtype(const SelectBatch<N>& b, rtoss_dtype dt, const Dict& dict, hipStream_t s)
+{
+    return dt == RTOSS_F32 ? launch_table<float, N>(b, dict, s) : dt == RTOSS_F16 ? launch_table<f16_t, N>(b, dict, s) : launch_table<bf16_t, N>(b, dict, s);
 }
 
 rtoss_status launch_select_batch(const rtoss_select_item* items, int n, rtoss_dtype dt, const Dict& dict, hipStream_t s)
 {
     for (int i = 0; i < n;) {  // i runs on across launches: tensors without a whole group take no table entry
-        SelectBatch b;
+        SelectBatch<kSelectBatchMax> b;
         int m = 0;
         int64_t chunks = 0;
         for (; i < n && m < kSelectBatchMax; ++i) {
@@ -272,9 +282,9 @@ rtoss_status launch_select_batch(const rtoss_select_item* items, int n, rtoss_dt
         if (m == 0) continue;
         for (int t = m; t < kSelectBatchMax; ++t) b.first_chunk[t] = (int)chunks;  // never at or before a chunk
         b.chunks = (int)chunks;
-        const rtoss_status st = dt == RTOSS_F32   ? launch_table<float>(b, dict, s)
-                                : dt == RTOSS_F16 ? launch_table<f16_t>(b, dict, s)
-                                                  : launch_table<bf16_t>(b, dict, s);
+        rtoss_status st;
+        if (m == 1) st = launch_dtype(SelectBatch<1>{{b.w[0]}, {b.idx[0]}, {b.G[0]}, {0}, b.chunks}, dt, dict, s);
+        else st = launch_dtype(b, dt, dict, s);
         if (st) return st;
     }
     return RTOSS_OK;
@@ -329,6 +339,17 @@ __global__ __launch_bounds__(BLOCK) void histogram_kernel(const uint8_t* __restr
         for (int i = 0; i < kHistCopies; ++i) c += bins[tid * kHistCopies + (i + tid) % kHistCopies];
         if (c != 0) atomicAdd(&hist[tid], c);
     }
+}
+
+__global__ __launch_bounds__(256) void clear_kernel(uint32_t* p, int n)
+{
+    if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
+}
+
+rtoss_status clear_counts(uint32_t* hist, int P, hipStream_t s)
+{
+    clear_kernel<<<dim3(1), dim3(256), 0, s>>>(hist, P);
+    return check_hip(hipGetLastError(), "histogram launch");
 }
 
 rtoss_status launch_histogram(const uint8_t* idx, int64_t G, int P, uint32_t* hist, hipStream_t s)
