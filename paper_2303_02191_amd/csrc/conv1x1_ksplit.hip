@@ -190,16 +190,14 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, int plan, c
 //     512 -> 256 (400)  3.0  4.8      256 -> 128 (6400)  4.5  5.3      512 -> 128 (6400)   5.7  5.2  stays
 //     128 -> 128 (6400) 3.8  4.4      1024 -> 512 (400)  4.6  5.2      128 -> 128 (25600)  7.7  6.1  stays
 // The smallest tile that leaves about one workgroup per compute unit.
-// fp32: the matrix instruction takes 16 times as long, so a small tile per workgroup rereads its weights at little cost and
-// spreads the work evenly, for longer the shallower the layer: workgroups of 32 channels x 16 positions per compute unit up
-// to which this kernel is not the slower one.  Swept over 64 to 512 channels in, 16 to 512 out and 400 to 204 800 positions
-// (us, this kernel and the streaming one; positions in brackets):
-//     64 ->  64 (25 600)    6.1   7.6      64 -> 256 (38 400) 22.0  23.8      64 -> 128 (102 400) 37.8  32.5  stays
-//     64 -> 512 (12 800)   16.2  18.8      64 ->  48 (153 600) 27.0 26.5      64 -> 512 (102 400) 134    93   stays
-//    128 ->  64 (25 600)    8.5  10.3     128 -> 128 (25 600) 13.8  15.2     128 -> 128 (51 200)  24.1  22.9  stays
-//    128 ->  64 (51 200)   13.9  17.1     128 -> 256 (12 800) 14.0  14.4     128 -> 512 (25 600)  43.8  35.9  stays
-//    128 ->  32 (51 200)   12.6  15.2     128 ->  32 (76 800) 17.5  17.8     128 ->  32 (102 400) 24.9  22.8  stays
-//    256 ->  64 (6400)      5.7   5.7     256 -> 256 (400)     3.1   5.2     512 ->  32 (6400)     6.1   9.3
+// fp32 (the matrix instruction takes 16 times as long, so a small tile per workgroup rereads its weights at little cost):
+// workgroups of 32 channels x 16 positions per compute unit up to which this kernel is not the slower one (us, this kernel
+// and the streaming one, which has its products on the bf16 instruction; positions in brackets):
+//     64 ->  64 (6400)      3.4   3.4      64 -> 256 (3192)    4.2   3.9  stays    64 ->  64 (12 769)    4.2  4.0  stays
+//    128 ->  64 (6400)      4.0   4.2     128 -> 256 (1600)    4.0   4.2          128 ->  64 (12 769)    5.4  5.2  stays
+//    128 -> 256 (3192)      5.5   5.2 stays
+//    256 ->  64 (3192)      4.0   5.1     256 -> 256 (812)     4.0   5.1          256 ->  64 (6400)      5.8  5.4  stays
+//    512 ->  32 (6400)      6.1   9.3     512 -> 256 (400)     4.0   6.2
 int ksplit1x1_plan(const rtoss_wdesc& d, const ConvParams& c)
 {
     const int KS = stage_count(d);
@@ -210,7 +208,7 @@ int ksplit1x1_plan(const rtoss_wdesc& d, const ConvParams& c)
     if (P > 0x7fffff00 || groups(2, 1) > kMaxGridGroups) return kNone;
     if (d.dt == RTOSS_F32) {
         // (tenths of a workgroup per compute unit)
-        const int64_t most = KS == 4 ? 800 : KS > 8 ? 16 : d.Co > 32 ? 280 : 180;
+        const int64_t most = KS <= 8 ? 50 : KS == 16 ? 25 : 16;
         return 10 * groups(2, 1) <= most * cus ? k32x16 : kNone;
     }
     if (groups(2, 1) <= cus) return k32x16;

@@ -25,11 +25,11 @@
 //     4q+i of the wave's m-th fragment is channel 4*MT*q + 4*m + i of the wave's slice, and the
 //     four lane quarters of a position together write one contiguous run of 16*MT channels.
 //
-// fp32 tensors run through the same kernel: a stage is then 16 channels (the same 64 bytes per position) and
-// a fragment step is four v_mfma_f32_16x16x4_f32, instruction s on element s of every lane's 16 bytes.  The
-// fp32 instruction has 1/16 of the 16-bit one's rate, so these layers sit near the ridge instead of far below
-// it: 128 -> 128 channels on 102 400 positions 43.7 us = 77 TFLOP/s, zeros included (smaller launches:
-// conv1x1_ksplit.hip).
+// fp32 tensors of 32 to 256 channels have a kernel of their own, on the bf16 matrix instruction (the second one here).  Those of
+// 16 and of 512 channels run through the first: a stage is then 16 channels (the same 64 bytes per position) and a fragment
+// step is four v_mfma_f32_16x16x4_f32, instruction s on element s of every lane's 16 bytes.  (16 channels would fill half a
+// step of the other instruction: 12 800 positions 3.0 us here, 3.3 there.  512 channels in three parts are more registers
+// than a wave has room for beside what it prefetches: 512 -> 256 on 6400 positions 19.9 us here, 21.7 there.)
 //
 // Operand layout of v_mfma_f32_16x16x32 (wave64; r = lane % 16, q = lane / 16): A lane holds
 // row r, K = 8q..8q+7; B lane holds column r, K = 8q..8q+7; D lane holds column r, rows 4q..4q+3.
@@ -38,6 +38,7 @@
 #include "common.h"
 #include "dtypes.h"
 #include "epilogue.h"
+#include "fp32_split.h"
 #include "mma.h"
 #include "pack_plan.h"
 
@@ -70,6 +71,19 @@ template <int KS, int WM> struct Plan {
     static_assert(RING >= 3 && (RING - 2) * COPIES < 64, "outstanding copies must fit the counter");
 };
 
+// The buffers of a launch, dealt out to workgroups in contiguous ranges whose lengths differ by one at most.  (Worked out from
+// the host's quotient: dividing in the kernel is some hundred scalar instructions before a workgroup's first load.)
+struct Range { int first, end; };
+struct Share {
+    int each, more;  // buffers of a workgroup; the first `more` workgroups take one more
+    Share(int64_t buffers, int workgroups) : each((int)(buffers / workgroups)), more((int)(buffers % workgroups)) {}
+    __device__ Range of(int workgroup) const
+    {
+        const int first = workgroup * each + min(workgroup, more);
+        return {first, first + each + (workgroup < more ? 1 : 0)};
+    }
+};
+
 // s_waitcnt immediate that waits for the vector-memory counter only (6 bits, split 4 + 2)
 __device__ __host__ constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
 
@@ -93,8 +107,8 @@ inline size_t frag_bytes(const rtoss_wdesc& d)
 template <typename T, typename TO, int KS, int WM>
 __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                              const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                             int64_t P, int Co, int co_blocks, int64_t nbuf, int wgs_per_cb,
-                                                             int total_wgs, int work_per_xcd, Epilogue ep)
+                                                             int64_t P, int Co, int co_blocks, Share share, int total_wgs,
+                                                             int work_per_xcd, Epilogue ep)
 {
     using PL = Plan<KS, WM>;
     constexpr int MT = PL::MT, WN = PL::WN, NB = PL::NB, PB = PL::PB, BUF = PL::BUF, COPIES = PL::COPIES, RING = PL::RING;
@@ -107,8 +121,8 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total_wgs) return;
     const int cb = work % co_blocks, part = work / co_blocks;
-    const int64_t b0 = nbuf * part / wgs_per_cb, b1 = nbuf * (part + 1) / wgs_per_cb;
-    if (b0 >= b1) return;
+    const Range range = share.of(part);
+    const int64_t b0 = range.first, b1 = range.end;
 
     if (wave == 4) {
         // ---- producer wave: all global -> LDS copies of the workgroup.  It issues nothing else, so its
@@ -262,6 +276,164 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     }
 }
 
+// fp32, 32 to 256 channels: products on the bf16 matrix instruction, every value split into three parts (fp32_split.h).
+//
+// A workgroup owns 64 output channels and a contiguous range of buffers of 32 or 64 positions; each wave holds 16 channels' weights,
+// split once, in registers.  Per buffer all four waves split its activations into LDS (the next buffer's are on their way
+// meanwhile), each multiplies all positions, and the outputs go through LDS, so that they leave in rows of 256 bytes with
+// scale, bias and shortcut read the same way.  Chunks of 16 bytes in LDS are permuted by position, for reads without bank
+// conflicts.
+// What bounds it: large launches of few channels the memory (64 -> 128 on 102 400 positions 17.5 us for 79 MB, 4.5 TB/s;
+// 29 on the fp32 instruction), deeper ones the matrix and the splitting instructions together, which the waves of a compute unit,
+// started at once, do at the same time rather than in turn (128 -> 128 on 25 600 positions: 28 % of the cycles matrix, 55 %
+// vector): 11.8 us, before 14.5; 256 -> 256 on 25 600: 26.5 us, before 33.  Buffers of 64 positions, which halve the
+// splitting of weights, leave two workgroups on a compute unit instead of four: no faster at 128 channels, slower at 64.
+constexpr int f32_positions(int KS) { return KS == 2 ? 64 : 32; }
+
+template <typename T, typename TO, int KS>
+__global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(const float* __restrict__ x, float* __restrict__ y,
+                                                             const char* __restrict__ wfrag, int64_t P, int Co, int co_blocks,
+                                                             Share share, int total_wgs, int work_per_xcd, Epilogue ep)
+{
+    constexpr int KK = KS / 2, PB = f32_positions(KS), TN = PB / 16;  // steps of 32 channels; blocks of 16 positions
+    constexpr int ROW = 64 * KS, PLANE = KK * PB * 64;  // bytes of a position; of one bf16 part of a buffer
+    constexpr int U = PB * KK / 64;                     // pieces of 2 x 4 channels a lane splits per buffer
+    static_assert(U * 64 == PB * KK, "whole rounds of pieces");
+    __shared__ __attribute__((aligned(16))) char X[3 * PLANE];
+    __shared__ __attribute__((aligned(16))) char out[PB * 256];  // 64 channels of a position, its 16-byte chunks permuted by position % 16
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // XCD-contiguous order: the channel blocks of one position range, and neighbouring ranges, share an L2
+    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
+    if (work >= total_wgs) return;
+    const int cb = work % co_blocks, part = work / co_blocks;
+    const Range range = share.of(part);
+
+    u32x4 raw[U][2];
+    auto load_activations = [&](int b) {
+        const char* base = (const char*)x + (int64_t)b * (PB * ROW);
+        const int last = (int)std::min<int64_t>(P - 1 - (int64_t)b * PB, PB - 1);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = u * 256 + tid, q = c & 3, pos = (c >> 2) % PB, kk = (c >> 2) / PB;
+            const char* at = base + (min(pos, last) * ROW + kk * 128 + q * 16);  // (past the end: any, it is not stored)
+            raw[u][0] = *(const u32x4*)at;
+            raw[u][1] = *(const u32x4*)(at + 64);
+        }
+    };
+    load_activations(range.first);
+    // this wave's 16 channels, resident for the whole kernel
+    Split8 a[KK];
+    {
+        const char* af = wfrag + (int64_t)(4 * cb + wave) * KS * kFrag + lane * 16;
+        u32x4 r[KK][2];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) r[s / 2][s % 2] = *(const u32x4*)(af + s * kFrag);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) a[kk] = split8(r[kk][0], r[kk][1]);
+    }
+    // ... and the 4 channels it stores
+    const int co = 64 * cb + 4 * (tid & 15);
+    f32x4 scale, bias;
+    if (co < Co) {
+        if (ep.scale) scale = *(const f32x4*)(ep.scale + co);
+        if (ep.bias) bias = *(const f32x4*)(ep.bias + co);
+    }
+
+    const int nn = lane & 15, qq = lane >> 4;
+    constexpr int MT = stream_mt_of(KS);
+    const char* x_lane = X + nn * 64 + ((qq ^ ((nn >> 1) & 3)) * 16);
+    // matrix rows 4 qq .. 4 qq + 3 of this wave's tile are these channels of the block (pack_plan.h)
+    char* o_lane = out + nn * 256 + ((((wave / MT) * (4 * MT) + MT * qq + wave % MT) ^ nn) * 16);
+
+    for (int b = range.first; b < range.end; ++b) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = u * 256 + tid, q = c & 3, row = c >> 2;  // (step, position)
+            const Split8 s = split8(raw[u][0], raw[u][1]);
+            char* at = X + row * 64 + ((q ^ ((row >> 1) & 3)) * 16);
+            *(u32x4*)at = s.h;
+            *(u32x4*)(at + PLANE) = s.m;
+            *(u32x4*)(at + 2 * PLANE) = s.l;
+        }
+        if (b + 1 < range.end) load_activations(b + 1);
+        const int64_t p0 = (int64_t)b * PB;
+        EpiResidual<float, 4> shortcut[TN];
+        if (ep.residual && co < Co)
+#pragma unroll
+            for (int i = 0; i < TN; ++i) {
+                const int64_t p = p0 + 16 * i + (tid >> 4);
+                if (p < P) shortcut[i].load(ep, p, co);
+            }
+        __syncthreads();
+        f32x4 main[TN], small[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) main[j] = small[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            Split8 v[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const char* at = x_lane + (kk * PB + 16 * j) * 64;
+                v[j] = Split8{*(const u32x4*)at, *(const u32x4*)(at + PLANE), *(const u32x4*)(at + 2 * PLANE)};
+            }
+            static_for<kSplitSteps>([&](auto step) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) split_step<decltype(step)::value>(a[kk], v[j], main[j], small[j]);
+            });
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) *(f32x4*)(o_lane + 16 * j * 256) = main[j] + small[j];
+        __syncthreads();
+        if (co >= Co) continue;
+        float v[4 * TN];
+#pragma unroll
+        for (int i = 0; i < TN; ++i) {
+            f32x4 t = *(const f32x4*)(out + (16 * i + (tid >> 4)) * 256 + (((tid & 15) ^ (tid >> 4)) * 16));
+            if (ep.scale) t *= scale;
+            if (ep.bias) t += bias;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * i + e] = t[e];
+        }
+        epi_act<4 * TN>(v, ep.act);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) {
+            const int64_t p = p0 + 16 * i + (tid >> 4);
+            if (p >= P) break;
+            float o[4] = {v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
+            if (ep.residual) shortcut[i].add(o);
+            *(f32x4*)(y + p * ep.ldy + co) = f32x4{o[0], o[1], o[2], o[3]};
+        }
+    }
+}
+
+template <int KS>
+rtoss_status launch_f32(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+{
+    const int64_t P = (int64_t)c.N * c.H * c.W;
+    constexpr int PB = f32_positions(KS);
+    const int64_t nbuf = (P + PB - 1) / PB;
+    const int co_blocks = (d.Co + 63) / 64;
+    auto kern = conv1x1_stream_kernel<float, float, KS>;
+    static std::atomic<int> per_cu_cached{0};  // per instantiation
+    int per_cu = per_cu_cached.load(std::memory_order_relaxed);
+    if (per_cu == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, 256, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+        per_cu_cached.store(per_cu, std::memory_order_relaxed);
+    }
+    const int resident = std::max(8, c.dev.cus) * per_cu;
+    const int wgs_per_cb = (int)std::max<int64_t>(1, std::min<int64_t>(nbuf, resident / co_blocks));
+    const int total = wgs_per_cb * co_blocks;
+    const int work_per_xcd = (total + 7) / 8;
+    if (P * d.Ci * 4 / PB > 0x7fffffffffffll || nbuf > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv1x1: too many positions");
+    dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
+    kern<<<grid, block, 0, s>>>((const float*)x, (float*)y, wfrag, P, d.Co, co_blocks, Share(nbuf, wgs_per_cb), total, work_per_xcd,
+                             c.ep);
+    return check_hip(hipGetLastError(), "conv1x1 stream launch");
+}
+
 template <typename T, typename TO, int KS, int WM>
 rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
@@ -276,8 +448,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     // Persistent workgroups: as many as are resident at once, but no fewer than 2 buffers each: every
     // workgroup loads its weight fragments once, which for deep layers is more bytes than a buffer.
     // fp32 steps take 16 times as long: there a launch that gives most compute units one workgroup or none is spread over
-    // all of them, one buffer each (us with one buffer and with two, positions in brackets: 16 -> 16 (12 800) 2.8 and 3.2,
-    // 32 -> 128 (6400) 4.1 and 4.5, 256 -> 64 (6400) 5.7 and 8.2; past that 32 -> 128 (25 600) 9.3 and 8.4).
+    // all of them, one buffer each (16 -> 16 channels on 12 800 positions: 2.8 us with one buffer, 3.2 with two).
     // (workgroups per compute unit depend on the instantiation's registers and LDS only: asked once; the
     // number of compute units is the current device's)
     static std::atomic<int> per_cu_cached{0};  // per instantiation
@@ -295,8 +466,8 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const int work_per_xcd = (total + 7) / 8;
     if (P * d.Ci * (int)sizeof(T) / PL::PB > 0x7fffffffffffll || nbuf > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv1x1: too many positions");
     dim3 grid((unsigned)(work_per_xcd * 8)), block(320);
-    kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Co, co_blocks, nbuf, wgs_per_cb,
-                                   total, work_per_xcd, c.ep);
+    kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Co, co_blocks,
+                                   Share(nbuf, wgs_per_cb), total, work_per_xcd, c.ep);
     return check_hip(hipGetLastError(), "conv1x1 stream launch");
 }
 
@@ -314,13 +485,19 @@ rtoss_status launch_ks(const rtoss_wdesc& d, const ConvParams& c, const char* wf
 template <typename T, typename TO>
 rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
-    switch (stage_count(d)) {
-    case 1: return launch_ks<T, TO, 1>(d, c, wfrag, x, y, s);
-    case 2: return launch_ks<T, TO, 2>(d, c, wfrag, x, y, s);
-    case 4: return launch_ks<T, TO, 4>(d, c, wfrag, x, y, s);
-    case 8: return launch_ks<T, TO, 8>(d, c, wfrag, x, y, s);
-    case 16: return launch_ks<T, TO, 16>(d, c, wfrag, x, y, s);
-    case 32: return launch_ks<T, TO, 32>(d, c, wfrag, x, y, s);
+    const int KS = stage_count(d);
+    if (KS == 1) return launch_ks<T, TO, 1>(d, c, wfrag, x, y, s);
+    if (KS == 32) return launch_ks<T, TO, 32>(d, c, wfrag, x, y, s);
+    if constexpr (sizeof(T) == 4) {
+        if (KS == 2) return launch_f32<2>(d, c, wfrag, x, y, s);
+        if (KS == 4) return launch_f32<4>(d, c, wfrag, x, y, s);
+        if (KS == 8) return launch_f32<8>(d, c, wfrag, x, y, s);
+        if (KS == 16) return launch_f32<16>(d, c, wfrag, x, y, s);
+    } else {
+        if (KS == 2) return launch_ks<T, TO, 2>(d, c, wfrag, x, y, s);
+        if (KS == 4) return launch_ks<T, TO, 4>(d, c, wfrag, x, y, s);
+        if (KS == 8) return launch_ks<T, TO, 8>(d, c, wfrag, x, y, s);
+        if (KS == 16) return launch_ks<T, TO, 16>(d, c, wfrag, x, y, s);
     }
     return fail(RTOSS_ESHAPE, "conv1x1 stream: unsupported input channel count %d", d.Ci);
 }

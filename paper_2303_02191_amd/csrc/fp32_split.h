@@ -1,6 +1,6 @@
 // fp32 products on the bf16 matrix instruction.
 //
-// v_mfma_f32_16x16x4_f32 does 64 multiply-adds per SIMD and cycle, v_mfma_f32_16x16x32_bf16 sixteen times as many.  An
+// v_mfma_f32_16x16x4_f32 does 32 multiply-adds per SIMD and cycle, v_mfma_f32_16x16x32_bf16 sixteen times as many.  An
 // fp32 value is the sum of three bf16 values exactly (24 bits of mantissa, 8 each):
 //     x = h + m + l,   h = x truncated to 8 bits,  m = x - h rounded to 8,  l = x - h - m.
 // Of the nine products of two such sums the three below 2^-23 of the whole are dropped (m*l, l*m, l*l); the other six

@@ -19,6 +19,10 @@ CASES = [
     (2, 72, 255, 25, 33, 1, 1),   # 1x1: whole rows, an odd number of half steps
     (1, 37, 85, 25, 33, 1, 1),    # ... rows without alignment
     (1, 96, 80, 25, 33, 1, 1),    # ... whole tiles
+    (5, 32, 80, 77, 95, 1, 1),    # ... buffers of 64 positions, one or two a workgroup
+    (9, 64, 16, 35, 33, 1, 1),    # ... of 32, the last one with 27
+    (3, 128, 80, 77, 91, 1, 1),   # ... one or two
+    (3, 256, 48, 77, 91, 1, 1),
 ]
 
 
