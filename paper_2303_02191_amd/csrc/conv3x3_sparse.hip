@@ -25,7 +25,7 @@
 // (RT x CT) blocks of 4x4 output positions; every wave owns all 16*TM channels and TN of
 // the position blocks.  K runs over stages of 32 input channels: the stage's weight
 // fragments (one contiguous chunk of the packed blob) and its activation tile with halo
-// (channels-last, 32 channels per position, 64-byte position pitch at stride 1 and 80 at stride 2) are copied global ->
+// (channels-last, 32 channels per position, 64 bytes) are copied global ->
 // LDS without passing through registers.  B operands are read from LDS as 16-byte vectors
 // (8 channels of one tap) and the 4x4 (tap, channel) blocks are transposed in registers
 // with byte permutes so that one lane holds, for 4 channels, the 4 taps of a group.
@@ -48,6 +48,17 @@ namespace rtoss {
 
 namespace {
 
+// Stride 2.  An output position needs four input positions, so blocks of 4x4 output positions share little: a wave takes its TN
+// blocks from the list of all blocks of the launch, wherever they lie, and copies 9x9 input positions for each.  A tile of
+// 8x8 or 4x16 positions for the workgroup copies 5 to 12 % less, but pads the image: 20x20 outputs are 25 blocks, or 9 tiles of four
+// (256 -> 256 channels at 40x40, 16 images: 18.6 us with tiles, now 12.7; the tile's pitch of 80 bytes against bank conflicts
+// was 25 % more copies besides: 32 -> 64 at 112x140 4.4 us, now 3.8).
+// In LDS the even input columns of a row come first, so that a tap's reads are contiguous, and the 16-byte chunks of a
+// position are in reverse order in every other pair of rows.  A 16-byte read is served in passes of 16 lanes -- 0-3, 12-15,
+// 20-27, then 4-11, 16-19, 28-31, ... -- and so no two lanes of a pass meet in a bank.
+constexpr int kPatch = 81 * 64;
+constexpr int patch_copies(int TN) { return (TN * kPatch + 1023) / 1024; }
+
 // Single-buffered variant: one LDS buffer, two barriers per stage, plain loop nest scheduled by the
 // compiler.  It needs half the LDS of the pipelined kernel below and few registers, so several
 // workgroups share a compute unit and hide each other's copy latency and epilogue.  Used for stride 2
@@ -67,17 +78,18 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
                                                                 const char* __restrict__ zeros, int H, int W, int Ci,
                                                                 int Co, int Ho, int Wo, int m_tiles_total,
                                                                 int tiles_c, int tiles_per_image, int co_blocks, int total,
-                                                                int work_per_xcd, Epilogue ep)
+                                                                int work_per_xcd, int blocks, Epilogue ep)
 {
     using G = Geom<S, RT, CT>;
     static_assert(RT * CT == 4 * TN, "four waves share the position blocks of a workgroup");
+    constexpr bool PATCH = S == 2;
     constexpr TapLayout LY = kLayouts[LAY];
     constexpr int NG = LY.groups, FR = layout_fragments(LY), TILE = layout_tile_bytes(LY);
     constexpr int A_BYTES = TM * TILE;
     constexpr int A_WAVE_COPIES = A_BYTES / 1024;            // 64 lanes x 16 B per copy instruction
     constexpr int A_PER_WAVE = (A_WAVE_COPIES + 3) / 4;
-    constexpr int X_CHUNKS = G::x_bytes / 16;                // including the pad chunk of every position
-    constexpr int X_PER_WAVE = ((X_CHUNKS + 63) / 64 + 3) / 4;
+    constexpr int X_CHUNKS = G::x_bytes / 16;                // (stride 1)
+    constexpr int X_PER_WAVE = PATCH ? patch_copies(TN) : ((X_CHUNKS + 63) / 64 + 3) / 4;
     static_assert(A_BYTES % 1024 == 0, "weight fragments are whole copy instructions");
     extern __shared__ __attribute__((aligned(16))) char smem[];  // [weights][activations, rounded up to whole copies] (x2 with DB)
     constexpr int BUF = A_BYTES + X_PER_WAVE * 4096;
@@ -93,11 +105,25 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total) return;
     const int mt0 = (work % co_blocks) * TM;
-    const int tile = (work / co_blocks) % tiles_per_image;
-    const int n_img = (work / co_blocks) / tiles_per_image;
-    const int tile_r = tile / tiles_c, tile_c = tile % tiles_c;
-    const int oh0 = tile_r * G::TH, ow0 = tile_c * G::TW;
-    const int ih0 = oh0 * S - 1, iw0 = ow0 * S - 1;
+    // this wave's blocks of 4x4 output positions
+    int n_of[TN], oh_of[TN], ow_of[TN];
+    bool live[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        if constexpr (PATCH) {  // (tiles_c, tiles_per_image: blocks)
+            const int blk = work / co_blocks * (4 * TN) + wave * TN + j, at = blk % tiles_per_image;
+            live[j] = blk < blocks;
+            n_of[j] = blk / tiles_per_image;
+            oh_of[j] = 4 * (at / tiles_c);
+            ow_of[j] = 4 * (at % tiles_c);
+        } else {
+            const int blk = wave * TN + j, tile = (work / co_blocks) % tiles_per_image;
+            live[j] = true;
+            n_of[j] = work / co_blocks / tiles_per_image;
+            oh_of[j] = tile / tiles_c * G::TH + 4 * (blk / CT);
+            ow_of[j] = tile % tiles_c * G::TW + 4 * (blk % CT);
+        }
+    }
     const int stages = RAG ? (Ci + 31) / 32 : Ci / 32;
 
     const char* a_src = wfrag + (int64_t)mt0 * TILE + lane * 16;
@@ -122,27 +148,53 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     unsigned tail_ok = 0;  // RAG: bit k = the last stage still has channels at this lane's copy k
 #pragma unroll
     for (int k = 0; k < X_PER_WAVE; ++k) {
-        const int c = (k * 4 + wave) * 64 + lane;
-        const int pos = c / G::kChunks, q = c % G::kChunks;
+        int n, ih, iw, q;
+        bool inside;
+        if constexpr (PATCH) {
+            const int c = k * 64 + lane, pos = c / 4 % 81, r = pos / 9, i = pos % 9;
+            const bool second = TN == 2 && c >= kPatch / 16;
+            q = (c & 3) ^ (r & 2 ? 3 : 0);
+            n = second ? n_of[TN - 1] : n_of[0];
+            ih = (second ? oh_of[TN - 1] : oh_of[0]) * 2 - 1 + r;
+            iw = (second ? ow_of[TN - 1] : ow_of[0]) * 2 - 1 + (i < 5 ? 2 * i : 2 * i - 9);  // even columns first
+            inside = c < TN * kPatch / 16 && (second ? live[TN - 1] : live[0]);
+        } else {
+            const int c = (k * 4 + wave) * 64 + lane, pos = c / G::kChunks;
+            const int tile = (work / co_blocks) % tiles_per_image;
+            q = c % G::kChunks;
+            n = n_of[0];
+            ih = tile / tiles_c * G::TH - 1 + pos / G::LW;
+            iw = tile % tiles_c * G::TW - 1 + pos % G::LW;
+            inside = pos / G::LW < G::IH && pos % G::LW < G::IW;
+        }
         if (RAG && (stages - 1) * 32 + 8 * q < Ci) tail_ok |= 1u << k;
-        const int xr = pos / G::LW, xc = pos % G::LW;
-        const int ih = ih0 + xr, iw = iw0 + xc;
-        const bool inside = q < 4 && xr < G::IH && xc < G::IW && ih >= 0 && ih < H && iw >= 0 && iw < W;
+        inside = inside && (unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W;
         // offset in 16-byte chunks: fits 31 bits (checked by the launcher)
-        const int off = ((n_img * H + ih) * W + iw) * (Ci >> 3) + q;
+        const int off = ((n * H + ih) * W + iw) * (Ci >> 3) + q;
         x_ptr[k] = inside ? (const char*)x + (int64_t)off * 16 : zeros;
     }
 
     // ---- per-lane read addresses of the B operand ----
     const int nn = lane & 15, qq = lane >> 4;
     const int pr = nn >> 2, pc = nn & 3;
-    int xb[TN];  // byte offset in lds_x of this lane's output position for each of its blocks (tap (0,0))
+    // byte offset in lds_x of this lane's output position for each of its blocks, tap (0,0) (stride 2: kernel rows 0 and 1, row 2)
+    int xb[TN][PATCH ? 2 : 1];
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        const int blk = wave * TN + j;
-        const int br = blk / CT, bc = blk % CT;
-        xb[j] = (((4 * br + pr) * S) * G::LW + (4 * bc + pc) * S) * G::kPos + qq * 16;
+        if constexpr (PATCH) {
+            const int at = wave * (X_PER_WAVE * 1024) + j * kPatch + (2 * pr * 9 + pc) * 64;
+            xb[j][0] = at + (pr & 1 ? 3 - qq : qq) * 16;
+            xb[j][1] = at + (pr & 1 ? qq : 3 - qq) * 16;
+        } else {
+            const int blk = wave * TN + j;
+            xb[j][0] = ((4 * (blk / CT) + pr) * G::LW + 4 * (blk % CT) + pc) * G::kPos + qq * 16;
+        }
     }
+    auto read_tap = [&](int j, int t) {
+        const int kh = t / 3, kw = t % 3;
+        if constexpr (PATCH) return *(const u32x4*)(lds_x + xb[j][kh >> 1] + (kh * 9 + (kw & 1 ? 5 : kw >> 1)) * 64);
+        else return *(const u32x4*)(lds_x + xb[j][0] + (kh * G::LW + kw) * G::kPos);
+    };
 
     f32x4 acc[TM][TN];
     // (no clearing of the accumulators: the centre step comes first in a stage, and the first stage's
@@ -153,7 +205,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
         for (int k = 0; k < X_PER_WAVE; ++k) {
             const char* src = x_ptr[k] + stage * 64;
             if (RAG && stage == stages - 1 && !(tail_ok >> k & 1u)) src = zeros;
-            copy16_to_lds(src, buf + A_BYTES + (k * 4 + wave) * 1024);
+            copy16_to_lds(src, buf + A_BYTES + (PATCH ? wave * X_PER_WAVE + k : k * 4 + wave) * 1024);
         }
     };
     if constexpr (DB) issue_copies(0, smem, false);
@@ -190,7 +242,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
                 for (int f = 0; f < 4; ++f) {
                     // (an empty slot carries weight 0: it reads the group's first tap, any finite value does)
                     const int t = LY.tap[group][f] >= 0 ? LY.tap[group][f] : LY.tap[group][0];
-                    rr[group][j][f] = *(const u32x4*)(lds_x + xb[j] + ((t / 3) * G::LW + (t % 3)) * G::kPos);
+                    rr[group][j][f] = read_tap(j, t);
                 }
         };
         auto load_group_a = [&](int group, int m) {
@@ -224,7 +276,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
         };
         auto load_centre = [&]() {
 #pragma unroll
-            for (int j = 0; j < TN; ++j) bc[j] = *(const u32x4*)(lds_x + xb[j] + (G::LW + 1) * G::kPos);
+            for (int j = 0; j < TN; ++j) bc[j] = read_tap(j, 4);
 #pragma unroll
             for (int m = 0; m < TM; ++m) ac[m] = *(const u32x4*)(lds_a + m * TILE + 2 * NG * kFragBytes + lane * 16);
         };
@@ -280,21 +332,19 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
         if constexpr (SHORTCUT) {  // its loads go out together, before any of them is needed
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const int blk = wave * TN + j;
-                const int oh = oh0 + 4 * (blk / CT) + pr, ow = ow0 + 4 * (blk % CT) + pc;
+                const int oh = oh_of[j] + pr, ow = ow_of[j] + pc;
 #pragma unroll
                 for (int mg = 0; mg < TM; mg += 4) {
                     const int co = 16 * mt0 + tile_quarter_offset(mg, qq);
-                    if (oh < Ho && ow < Wo && co < Co) shortcut[j][mg / 4].load(ep, ((int64_t)n_img * Ho + oh) * Wo + ow, co);
+                    if (live[j] && oh < Ho && ow < Wo && co < Co) shortcut[j][mg / 4].load(ep, ((int64_t)n_of[j] * Ho + oh) * Wo + ow, co);
                 }
             }
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const int blk = wave * TN + j;
-            const int oh = oh0 + 4 * (blk / CT) + pr, ow = ow0 + 4 * (blk % CT) + pc;
-            if (oh >= Ho || ow >= Wo) continue;
-            const int64_t pos = ((int64_t)n_img * Ho + oh) * Wo + ow;
+            const int oh = oh_of[j] + pr, ow = ow_of[j] + pc;
+            if (!live[j] || oh >= Ho || ow >= Wo) continue;
+            const int64_t pos = ((int64_t)n_of[j] * Ho + oh) * Wo + ow;
             TO* yp = y + pos * ep.ldy;
 #pragma unroll
             for (int mg = 0; mg < TM; mg += 4) {
@@ -339,21 +389,24 @@ rtoss_status launch_variant_sb(const rtoss_wdesc& d, const ConvParams& c, const 
 {
     using G = Geom<S, RT, CT>;
     const int Ho = (c.H + 2 - 3) / S + 1, Wo = (c.W + 2 - 3) / S + 1;
-    const int tiles_r = (Ho + G::TH - 1) / G::TH, tiles_c = (Wo + G::TW - 1) / G::TW;
+    constexpr int th = S == 2 ? 4 : G::TH, tw = S == 2 ? 4 : G::TW;  // (stride 2: blocks)
+    const int tiles_r = (Ho + th - 1) / th, tiles_c = (Wo + tw - 1) / tw;
+    const int64_t blocks = (int64_t)tiles_r * tiles_c * c.N;
     const int m_tiles_total = padded_m_tiles(d.Co);  // pitch of the packed section
     const int co_blocks = ((d.Co + 15) / 16 + TM - 1) / TM;
-    constexpr int x_copies_per_wave = ((G::x_bytes / 16 + 63) / 64 + 3) / 4;
-    const size_t smem = (DB ? 2 : 1) * ((size_t)TM * layout_tile_bytes(kLayouts[LAY]) + (size_t)x_copies_per_wave * 4096) + EpiScaleBias<16 * TM>::kBytes;
+    constexpr size_t x_area = S == 2 ? patch_copies(TN) * 4096 : ((G::x_bytes / 16 + 63) / 64 + 3) / 4 * 4096;
+    const size_t smem = (DB ? 2 : 1) * ((size_t)TM * layout_tile_bytes(kLayouts[LAY]) + x_area) + EpiScaleBias<16 * TM>::kBytes;
     auto kern = conv3x3_sparse_sb_kernel<T, TO, S, TM, TN, RT, CT, AHEAD, LAY, DB, RAG>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
-    const int64_t total = (int64_t)tiles_r * tiles_c * co_blocks * c.N;
-    if (total > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
+    const int64_t total = (S == 2 ? (blocks + 4 * TN - 1) / (4 * TN) : blocks) * co_blocks;
+    if (total > 0x3fffffff || blocks > 0x7fffff00) return fail(RTOSS_ESHAPE, "conv: too many tiles");
     if ((int64_t)c.N * c.H * c.W * d.Ci / 8 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
     const int work_per_xcd = (int)((total + 7) / 8);
     dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + fragment_bytes(d, LAY), c.H, c.W, d.Ci, d.Co, Ho, Wo,
-                                   m_tiles_total, tiles_c, tiles_r * tiles_c, co_blocks, (int)total, work_per_xcd, c.ep);
+                                   m_tiles_total, tiles_c, tiles_r * tiles_c, co_blocks, (int)total, work_per_xcd, (int)blocks,
+                                   c.ep);
     return check_hip(hipGetLastError(), "conv3x3 sparse launch");
 }
 
@@ -376,6 +429,18 @@ inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
     return tiles8 >= 200;
 }
 
+// Stride 2, one or two blocks per wave: three workgroups per compute unit with one, two with two, whose rounds take about 4/3 as
+// long (two halve the weights a block reads from LDS).  Two where that is the smaller sum; not for one or two stages, which
+// the memory bounds (us, one and two; layout 0 / 1, batch x channels in -> out @ image):
+//     16x256->256@40  12.7 16.4 / 15.4 19.2  one    16x256->512@40 25.6 20.8 / 31.3 24.5  two     4x64->128@112x140  6.1 8.0 / 6.8 8.6  one
+//     4x128->256@56x70 7.2  9.7 /  8.5 11.0  one    4x128->256@112x140 15.4 13.1 / 17.6 14.4  two  16x64->128@160   25.9 28.5 / 29.7 31.3  one
+inline bool two_blocks_per_wave(const rtoss_wdesc& d, const ConvParams& c)
+{
+    const int64_t blocks = (int64_t)(((c.H - 1) / 2 + 4) / 4) * (((c.W - 1) / 2 + 4) / 4) * c.N, co_blocks = (d.Co + 63) / 64, cus = c.dev.cus;
+    const int64_t one = ((blocks + 3) / 4 * co_blocks + 3 * cus - 1) / (3 * cus), two = ((blocks + 7) / 8 * co_blocks + 2 * cus - 1) / (2 * cus);
+    return d.Ci > 64 && 4 * two <= 3 * one;
+}
+
 // Layout 1 (three tap groups, 4-entry dictionaries): the single-buffered kernel for every shape.
 template <typename T, typename TO>
 rtoss_status launch_typed_layout1(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y,
@@ -383,8 +448,8 @@ rtoss_status launch_typed_layout1(const rtoss_wdesc& d, const ConvParams& c, con
 {
     if (ragged(d)) return launch_typed_ragged<T, TO, 1>(d, c, wfrag, x, y, s);
     if (c.stride == 1) return launch_variant_sb<T, TO, 1, 4, 2, 2, 4, false, 1>(d, c, wfrag, x, y, s);
-    if (d.Ci == 32) return launch_variant_sb<T, TO, 2, 4, 1, 1, 4, false, 1>(d, c, wfrag, x, y, s);
-    return launch_variant_sb<T, TO, 2, 4, 2, 2, 4, false, 1>(d, c, wfrag, x, y, s);
+    if (two_blocks_per_wave(d, c)) return launch_variant_sb<T, TO, 2, 4, 2, 2, 4, false, 1>(d, c, wfrag, x, y, s);
+    return launch_variant_sb<T, TO, 2, 4, 1, 1, 4, false, 1>(d, c, wfrag, x, y, s);
 }
 
 template <typename T, typename TO>
@@ -406,14 +471,7 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
         // conv3x3_strip.hip): two buffers per workgroup, still two workgroups per compute unit
         return launch_variant_sb<T, TO, 1, 4, 2, 2, 4, true, 0, true>(d, c, wfrag, x, y, s);
     }
-    // Stride 2: an output position needs four input positions, so the activation tile dominates the LDS and the
-    // copies.  Small tiles of 64 output positions (50 KB with 64 channels per workgroup: three workgroups per compute
-    // unit, which overlap each other's copies) measured faster than 8x16 tiles on every stride-2 layer of a
-    // YOLOv5s-shaped model; 8x8 where that shape pads the image less than 4x16 (40x40 and 20x20 outputs), else 4x16.
-    const int Ho = (c.H - 1) / 2 + 1, Wo = (c.W - 1) / 2 + 1;
-    const int64_t padded_4x16 = (int64_t)((Ho + 3) / 4 * 4) * ((Wo + 15) / 16 * 16);
-    const int64_t padded_8x8 = (int64_t)((Ho + 7) / 8 * 8) * ((Wo + 7) / 8 * 8);
-    if (padded_8x8 < padded_4x16) return launch_variant_sb<T, TO, 2, 4, 1, 2, 2>(d, c, wfrag, x, y, s);
+    if (two_blocks_per_wave(d, c)) return launch_variant_sb<T, TO, 2, 4, 2, 2, 4>(d, c, wfrag, x, y, s);
     return launch_variant_sb<T, TO, 2, 4, 1, 1, 4>(d, c, wfrag, x, y, s);
 }
 
@@ -430,7 +488,8 @@ bool sparse3x3_shape_ok(const rtoss_wdesc& d)
 bool sparse3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c)
 {
     if (!ragged(d)) return true;
-    const int Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1, rows = c.stride == 1 ? 8 : 4;  // launch_typed_ragged's tiles
+    // launch_typed_ragged's tiles (stride 2: four blocks, at least as many positions as a tile of 4x16)
+    const int Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1, rows = c.stride == 1 ? 8 : 4;
     return (int64_t)c.N * c.H * c.W * d.Ci / 8 <= kMaxChunks &&
            (int64_t)((Ho + rows - 1) / rows) * ((Wo + 15) / 16) * ((d.Co + 63) / 64) * c.N <= kMaxGridGroups;
 }
