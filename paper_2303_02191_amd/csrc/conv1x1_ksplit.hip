@@ -82,7 +82,10 @@ __global__ __launch_bounds__(256) void conv1x1_ksplit_kernel(const T* __restrict
     int o_co[PER];
     int o_pos[PER];
     bool o_live[PER];
+    // (scale, bias and shortcut are asked for before the partial sums meet: behind that they would be a wait of their own, from
+    // memory no one has touched yet)
     EpiResidual<TO, RUN> shortcut[PER];
+    float scale[PER][RUN], bias[PER][RUN];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const int item = tid + 256 * i, q = item & 3, n = (item >> 2) & 15, g = (item >> 6) % GROUPS, j = (item >> 6) / GROUPS;
@@ -90,50 +93,59 @@ __global__ __launch_bounds__(256) void conv1x1_ksplit_kernel(const T* __restrict
         o_co[i] = (f / MT) * (16 * MT) + 4 * MT * q + 4 * (f % MT);
         o_pos[i] = p0 + 16 * j + n;
         o_live[i] = item < ITEMS && o_pos[i] < P && o_co[i] < Co;  // (Co is a multiple of 16: a run is all in or all out)
-        if (ep.residual && o_live[i]) shortcut[i].load(ep, o_pos[i], o_co[i]);
+        if (!o_live[i]) continue;
+        if (ep.residual) shortcut[i].load(ep, o_pos[i], o_co[i]);
+        if (ep.scale)
+#pragma unroll
+            for (int g4 = 0; g4 < RUNT; ++g4) *(f32x4*)(scale[i] + 4 * g4) = *(const f32x4*)(ep.scale + o_co[i] + 4 * g4);
+        if (ep.bias)
+#pragma unroll
+            for (int g4 = 0; g4 < RUNT; ++g4) *(f32x4*)(bias[i] + 4 * g4) = *(const f32x4*)(ep.bias + o_co[i] + 4 * g4);
     }
 #pragma unroll
     for (int m = 0; m < TM; ++m)
 #pragma unroll
         for (int j = 0; j < TN; ++j) *(f32x4*)(part + ((wave * TM + m) * TN + j) * 1024 + lane * 16) = acc[m][j];
     __syncthreads();
+    epi_by_form(ep, [&](auto form) {
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        if (!o_live[i]) continue;
-        const int item = tid + 256 * i, q = item & 3, n = (item >> 2) & 15, g = (item >> 6) % GROUPS, j = (item >> 6) / GROUPS;
-        float v[RUN];
+        for (int i = 0; i < PER; ++i) {
+            if (!o_live[i]) continue;
+            const int item = tid + 256 * i, q = item & 3, n = (item >> 2) & 15, g = (item >> 6) % GROUPS, j = (item >> 6) / GROUPS;
+            float v[RUN];
 #pragma unroll
-        for (int m = 0; m < RUNT; ++m) {
-            const char* at = part + ((g * RUNT + m) * TN + j) * 1024 + (q * 16 + n) * 16;
-            f32x4 sum = *(const f32x4*)at;
+            for (int m = 0; m < RUNT; ++m) {
+                const char* at = part + ((g * RUNT + m) * TN + j) * 1024 + (q * 16 + n) * 16;
+                f32x4 sum = *(const f32x4*)at;
 #pragma unroll
-            for (int w = 1; w < 4; ++w) sum += *(const f32x4*)(at + w * TM * TN * 1024);
+                for (int w = 1; w < 4; ++w) sum += *(const f32x4*)(at + w * TM * TN * 1024);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * m + e] = sum[e];
-        }
-        epi_scale_bias_act<RUN>(v, ep, o_co[i]);
-        if (ep.residual) shortcut[i].add(v);
-        TO* yp = y + (int64_t)o_pos[i] * ep.ldy + o_co[i];
-        if constexpr (sizeof(TO) == 4) {
+                for (int e = 0; e < 4; ++e) v[4 * m + e] = sum[e];
+            }
+            epi_scale_bias_act_of<decltype(form)::value, RUN>(v, ep, scale[i], bias[i]);
+            if (ep.residual) shortcut[i].add(v);
+            TO* yp = y + (int64_t)o_pos[i] * ep.ldy + o_co[i];
+            if constexpr (sizeof(TO) == 4) {
 #pragma unroll
-            for (int g4 = 0; g4 < RUNT; ++g4) *(f32x4*)(yp + 4 * g4) = f32x4{v[4 * g4], v[4 * g4 + 1], v[4 * g4 + 2], v[4 * g4 + 3]};
-        } else if constexpr (RUNT == 1) {
-            uint2 o;
-            o.x = pack2_from_f32<TO>(v[0], v[1]);
-            o.y = pack2_from_f32<TO>(v[2], v[3]);
-            *(uint2*)yp = o;
-        } else {
+                for (int g4 = 0; g4 < RUNT; ++g4) *(f32x4*)(yp + 4 * g4) = f32x4{v[4 * g4], v[4 * g4 + 1], v[4 * g4 + 2], v[4 * g4 + 3]};
+            } else if constexpr (RUNT == 1) {
+                uint2 o;
+                o.x = pack2_from_f32<TO>(v[0], v[1]);
+                o.y = pack2_from_f32<TO>(v[2], v[3]);
+                *(uint2*)yp = o;
+            } else {
 #pragma unroll
-            for (int g8 = 0; g8 < RUNT / 2; ++g8) {
-                u32x4 o;
-                o.x = pack2_from_f32<TO>(v[8 * g8 + 0], v[8 * g8 + 1]);
-                o.y = pack2_from_f32<TO>(v[8 * g8 + 2], v[8 * g8 + 3]);
-                o.z = pack2_from_f32<TO>(v[8 * g8 + 4], v[8 * g8 + 5]);
-                o.w = pack2_from_f32<TO>(v[8 * g8 + 6], v[8 * g8 + 7]);
-                *(u32x4*)(yp + 8 * g8) = o;
+                for (int g8 = 0; g8 < RUNT / 2; ++g8) {
+                    u32x4 o;
+                    o.x = pack2_from_f32<TO>(v[8 * g8 + 0], v[8 * g8 + 1]);
+                    o.y = pack2_from_f32<TO>(v[8 * g8 + 2], v[8 * g8 + 3]);
+                    o.z = pack2_from_f32<TO>(v[8 * g8 + 4], v[8 * g8 + 5]);
+                    o.w = pack2_from_f32<TO>(v[8 * g8 + 6], v[8 * g8 + 7]);
+                    *(u32x4*)(yp + 8 * g8) = o;
+                }
             }
         }
-    }
+    });
 }
 
 // Channel tiles of the packed section that hold rows of the layer (the section is padded to whole slices).

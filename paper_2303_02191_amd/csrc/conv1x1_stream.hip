@@ -219,61 +219,63 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     constexpr int EB = (int)sizeof(TO);
 
     static_assert(NB == 1, "one block per wave and buffer");
-    int slot = 0;
-    for (int64_t b = b0; b < b1; ++b) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's reads of the previous buffer are complete
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+    epi_by_form(ep, [&](auto form) {
+        int slot = 0;
+        for (int64_t b = b0; b < b1; ++b) {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's reads of the previous buffer are complete
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
 
-        const char* X = smem + slot * BUF + x_lane;
-        f32x4 acc[MT][NB];
-#pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const u32x4 bv = *(const u32x4*)(X + (s * PB + 16 * WN * j) * 64);
-#pragma unroll
-                for (int m = 0; m < MT; ++m) acc[m][j] = Dense16<T>::mma(a[m][s], bv, acc[m][j]);
-            }
-
-        // ---- store: this lane's 4*MT consecutive channels of its position ----
-        const int64_t p = b * PB + 16 * wn + nn;
-        if (p < P && co_lane < Co) {  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
-            TO* yp = y + p * ep.ldy + co_lane;
-            float v[4 * MT];
+            const char* X = smem + slot * BUF + x_lane;
+            f32x4 acc[MT][NB];
 #pragma unroll
             for (int m = 0; m < MT; ++m)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][0][e];
-            epi_scale_bias_act<4 * MT>(v, ep, lds_ep + co_local, lds_ep + PL::SPAN + co_local);
-            epi_residual<TO, 4 * MT>(v, ep, p, co_lane);
-            if constexpr (EB == 4) {
+                for (int j = 0; j < NB; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int g = 0; g < MT; ++g) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
-            } else if constexpr (MT == 1) {
-                uint2 o;
-                o.x = pack2_from_f32<TO>(v[0], v[1]);
-                o.y = pack2_from_f32<TO>(v[2], v[3]);
-                *(uint2*)yp = o;
-            } else {
+            for (int s = 0; s < KS; ++s)
 #pragma unroll
-                for (int g = 0; g < MT / 2; ++g) {
-                    u32x4 o;
-                    o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
-                    o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
-                    o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
-                    o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
-                    *(u32x4*)(yp + 8 * g) = o;
+                for (int j = 0; j < NB; ++j) {
+                    const u32x4 bv = *(const u32x4*)(X + (s * PB + 16 * WN * j) * 64);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) acc[m][j] = Dense16<T>::mma(a[m][s], bv, acc[m][j]);
+                }
+
+            // ---- store: this lane's 4*MT consecutive channels of its position ----
+            const int64_t p = b * PB + 16 * wn + nn;
+            if (p < P && co_lane < Co) {  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
+                TO* yp = y + p * ep.ldy + co_lane;
+                float v[4 * MT];
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][0][e];
+                epi_scale_bias_act_of<decltype(form)::value, 4 * MT>(v, ep, lds_ep + co_local, lds_ep + PL::SPAN + co_local);
+                epi_residual<TO, 4 * MT>(v, ep, p, co_lane);
+                if constexpr (EB == 4) {
+#pragma unroll
+                    for (int g = 0; g < MT; ++g) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+                } else if constexpr (MT == 1) {
+                    uint2 o;
+                    o.x = pack2_from_f32<TO>(v[0], v[1]);
+                    o.y = pack2_from_f32<TO>(v[2], v[3]);
+                    *(uint2*)yp = o;
+                } else {
+#pragma unroll
+                    for (int g = 0; g < MT / 2; ++g) {
+                        u32x4 o;
+                        o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
+                        o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
+                        o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
+                        o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
+                        *(u32x4*)(yp + 8 * g) = o;
+                    }
                 }
             }
+            slot = slot + 1 == RING ? 0 : slot + 1;
         }
-        slot = slot + 1 == RING ? 0 : slot + 1;
-    }
+    });
 }
 
 // fp32, 32 to 256 channels: products on the bf16 matrix instruction, every value split into three parts (fp32_split.h).

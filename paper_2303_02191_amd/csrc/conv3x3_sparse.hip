@@ -326,7 +326,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     // ---- epilogue: a D lane holds column nn (position) and rows 4*qq .. 4*qq+3 of every channel tile,
     // which tile_row_channel makes 16 consecutive output channels per group of 4 tiles ----
     static_assert(TM % 4 == 0, "whole groups of 4 channel tiles");
-    auto finish = [&](auto shortcut_tag) {
+    auto finish = [&](auto shortcut_tag, auto form) {
         constexpr bool SHORTCUT = decltype(shortcut_tag)::value;
         EpiResidual<TO, 16> shortcut[TN][TM / 4];
         if constexpr (SHORTCUT) {  // its loads go out together, before any of them is needed
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
                     store_ragged<TO, 16>(yp, vv, co, Co, ep.ldy);
                     continue;
                 }
-                epi_scale_bias_act<16>(vv, ep, lds_ep + co - 16 * mt0, lds_ep + 16 * TM + co - 16 * mt0);
+                epi_scale_bias_act_of<decltype(form)::value, 16>(vv, ep, lds_ep + co - 16 * mt0, lds_ep + 16 * TM + co - 16 * mt0);
                 if constexpr (SHORTCUT) shortcut[j][mg / 4].add(vv);
                 if constexpr (sizeof(TO) == 4) {
 #pragma unroll
@@ -379,8 +379,9 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
             }
         }
     };
-    if (!RAG && ep.residual) finish(std::true_type{});
-    else finish(std::false_type{});
+    if constexpr (RAG) finish(std::false_type{}, std::integral_constant<int, kEpiAny>{});
+    else if (ep.residual) epi_by_form(ep, [&](auto form) { finish(std::true_type{}, form); });
+    else epi_by_form(ep, [&](auto form) { finish(std::false_type{}, form); });
 }
 
 template <typename T, typename TO, int S, int TM, int TN, int RT, int CT, bool AHEAD = true, int LAY = 0, bool DB = false, bool RAG = false>

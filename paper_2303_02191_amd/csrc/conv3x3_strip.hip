@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
     // ---- store: a lane holds column nn (position) and 16 consecutive channels of each of its rows ----
     const int co = 64 * cb + 16 * qq, ow = ow0 + nn;
     if (co >= Co || ow >= W) return;  // (Co is a multiple of 16: a run of 16 channels is all in or all out)
-    auto finish = [&](auto shortcut_tag) {
+    auto finish = [&](auto shortcut_tag, auto form) {
         constexpr bool SHORTCUT = decltype(shortcut_tag)::value;
         EpiResidual<TO, 16> shortcut[TN];
         const int64_t pos0 = ((int64_t)n_img * H + oh0 + wave * TN) * W + ow;
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
             for (int m = 0; m < kTM; ++m)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][j][e];
-            epi_scale_bias_act<16>(v, ep, lds_ep + 16 * qq, lds_ep + 64 + 16 * qq);
+            epi_scale_bias_act_of<decltype(form)::value, 16>(v, ep, lds_ep + 16 * qq, lds_ep + 64 + 16 * qq);
             if constexpr (SHORTCUT) shortcut[j].add(v);
             if constexpr (sizeof(TO) == 4) {
 #pragma unroll
@@ -228,8 +228,8 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
             }
         }
     };
-    if (ep.residual) finish(std::true_type{});
-    else finish(std::false_type{});
+    if (ep.residual) epi_by_form<false>(ep, [&](auto form) { finish(std::true_type{}, form); });
+    else epi_by_form<false>(ep, [&](auto form) { finish(std::false_type{}, form); });
 }
 
 // Dense mode.  A tap's fragment is used for one product per row and tile and needs no transposition, so here the weights stay out
@@ -333,7 +333,7 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
     const int co = 64 * cb + 16 * qq + 8 * pair, ow = ow0 + nn, oh = oh0 + half * RW;
     if (co >= Co || ow >= W) return;  // (Co is a multiple of 16)
     const int64_t pos0 = ((int64_t)n_img * H + oh) * W + ow;
-    auto finish = [&](auto shortcut_tag) {
+    auto finish = [&](auto shortcut_tag, auto form) {
         constexpr bool SHORTCUT = decltype(shortcut_tag)::value;
         EpiResidual<TO, 8> shortcut[RW];
         if constexpr (SHORTCUT) {
@@ -347,7 +347,7 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
             float v[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = acc[e / 4][j][e % 4];
-            epi_scale_bias_act<8>(v, ep, lds_ep + 16 * qq + 8 * pair, lds_ep + 64 + 16 * qq + 8 * pair);
+            epi_scale_bias_act_of<decltype(form)::value, 8>(v, ep, lds_ep + 16 * qq + 8 * pair, lds_ep + 64 + 16 * qq + 8 * pair);
             if constexpr (SHORTCUT) shortcut[j].add(v);
             TO* yp = y + (pos0 + (int64_t)j * W) * ep.ldy + co;
             if constexpr (sizeof(TO) == 4) {
@@ -363,8 +363,8 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
             }
         }
     };
-    if (ep.residual) finish(std::true_type{});
-    else finish(std::false_type{});
+    if (ep.residual) epi_by_form<false>(ep, [&](auto form) { finish(std::true_type{}, form); });
+    else epi_by_form<false>(ep, [&](auto form) { finish(std::false_type{}, form); });
 }
 
 // (fp32: dense3x3_f32.h, eight rows)

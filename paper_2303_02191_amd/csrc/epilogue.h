@@ -4,6 +4,8 @@
 // blocks the pruned layers sit in; Section V reports whole-model inference).  All arithmetic is
 // fp32; the result is rounded once when it is stored.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 #include "dtypes.h"
 #include "mma.h"
@@ -93,6 +95,34 @@ __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue
 template <int N> __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue& ep, int co)
 {
     epi_scale_bias_act<N>(v, ep, ep.scale + co, ep.bias + co);
+}
+
+// The forms of the stage that a kernel may have code of its own for, chosen once per workgroup (epi_by_form): nothing at all, the
+// folded normalisation with SiLU (scale and bias in one rounding), and everything else.  A branch around a run of values costs
+// a copy of every value where its paths meet, a quarter of the instructions of a short output loop (3 -> 32 channels on
+// 16x640x640, where the vector instructions bound the kernel: 42.4 us with the branches inside, 38.3; a 1x1 of 400 positions 3.3 and 3.0).
+// NONE: a form for nothing at all, where the plain convolution gains too (1x1, 8x80x80 128 -> 128: 12.1 and 11.5 us).
+enum EpiForm { kEpiAny = 0, kEpiNone, kEpiSilu };
+template <bool NONE = true, typename F> __device__ __forceinline__ void epi_by_form(const Epilogue& ep, F&& run)
+{
+    if (ep.act == 2 && ep.scale && ep.bias) run(std::integral_constant<int, kEpiSilu>{});
+    else if (NONE && ep.act == 0 && !ep.scale && !ep.bias) run(std::integral_constant<int, NONE ? kEpiNone : kEpiAny>{});
+    else run(std::integral_constant<int, kEpiAny>{});
+}
+template <int FORM, int N>
+__device__ __forceinline__ void epi_scale_bias_act_of(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
+{
+    if constexpr (FORM == kEpiSilu) {
+#pragma unroll
+        for (int g = 0; g < N / 4; ++g) {
+            const f32x4 s = *(const f32x4*)(scale + 4 * g), b = *(const f32x4*)(bias + 4 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[4 * g + i] = __builtin_fmaf(v[4 * g + i], s[i], b[i]);
+        }
+        epi_silu<N>(v);
+    } else if constexpr (FORM == kEpiAny) {
+        epi_scale_bias_act<N>(v, ep, scale, bias);
+    }
 }
 
 // Adds the residual's N consecutive channels, starting at channel co, of position number `pos` (n, oh, ow
