@@ -295,7 +295,11 @@ __global__ __launch_bounds__(256, 2) void conv1x1_mma_kernel(const T* __restrict
             const int co = c0 + 16 * wave * TM + 4 * qq;
             float v[4 * TM * TN];
 #pragma unroll
-            for (int i = 0; i < 4 * TM * TN; ++i) v[i] = sizeof(T) == 4 ? acc[i / 4 / TN][i / 4 % TN][i % 4] + small[i / 4 / TN][i / 4 % TN][i % 4] : acc[i / 4 / TN][i / 4 % TN][i % 4];
+            for (int i = 0; i < TM * TN; ++i) {
+                const f32x4 sum = sizeof(T) == 4 ? split_sum(acc[i / TN][i % TN], small[i / TN][i % TN]) : acc[i / TN][i % TN];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * i + e] = sum[e];
+            }
             if (ep.scale || ep.bias) {
                 scale_bias.store(lds_ep, ep, tid);
                 __syncthreads();

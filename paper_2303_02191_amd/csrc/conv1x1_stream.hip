@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
             });
         }
 #pragma unroll
-        for (int j = 0; j < TN; ++j) *(f32x4*)(o_lane + 16 * j * 256) = main[j] + small[j];
+        for (int j = 0; j < TN; ++j) *(f32x4*)(o_lane + 16 * j * 256) = split_sum(main[j], small[j]);
         __syncthreads();
         if (co >= Co) continue;
         float v[4 * TN];

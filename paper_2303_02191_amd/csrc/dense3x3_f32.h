@@ -146,7 +146,7 @@ __device__ __forceinline__ void dense3x3_f32_tile(const float* __restrict__ x, f
         for (int j = 0; j < R; ++j) {
             if (oh0 + j >= Ho) break;
             const int64_t pos = pos0 + (int64_t)j * Wo;
-            const f32x4 sum = main[j] + small[j];
+            const f32x4 sum = split_sum(main[j], small[j]);
             float v[4] = {sum.x, sum.y, sum.z, sum.w};
             epi_ragged<float, 4>(v, ep, pos, co, Co);
             store_ragged<float, 4>(y + pos * ep.ldy, v, co, Co, ep.ldy);
@@ -160,7 +160,7 @@ __device__ __forceinline__ void dense3x3_f32_tile(const float* __restrict__ x, f
         float v[4 * R];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            f32x4 t = main[j] + small[j];
+            f32x4 t = split_sum(main[j], small[j]);
             if (ep.scale) t *= scale;
             if (ep.bias) t += bias;
 #pragma unroll

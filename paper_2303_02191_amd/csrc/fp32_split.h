@@ -12,8 +12,8 @@
 // Relative error (2-norm) of random sums against 64 bits, fp32 instruction / this: K = 32 6.3e-8 / 3.8e-8, 576
 // 2.5e-7 / 0.9e-7, 4608 7.1e-7 / 2.9e-7; a sum that is split over four accumulators before (the K-split kernels): 5.4e-8,
 // 1.3e-7, 3.5e-7.  (All six into one accumulator would be less precise than the fp32 instruction: 3.3e-7 at 576.)
-// Limits: an infinite value has no finite h, so it gives NaN wherever it is multiplied (with the zero-filled weights of
-// these kernels it did already, by 0 * inf); l of a value below 2^-110 is subnormal or lost.
+// An infinite value has h = itself and NaN for m and l: the sum of h*h alone is then the result (split_sum).  Limits: a signalling
+// NaN whose payload lies in its low 16 bits has an infinite h; l of a value below 2^-110 is subnormal or lost.
 #pragma once
 #include "dtypes.h"
 #include "mma.h"
@@ -61,5 +61,15 @@ template <int STEP> __device__ __forceinline__ void split_step(const Split8& a, 
     if constexpr (STEP == 5) main = Dense16<bf16_t>::mma(a.h, b.h, main);
 }
 constexpr int kSplitSteps = 6;
+
+// The result.  Infinite terms stand in `main` with their signs and make `small` NaN (inf - inf when split, inf * 0), so an
+// infinite `main` is the result as it is; terms of both signs, 0 * inf and NaN have made `main` NaN.
+__device__ __forceinline__ f32x4 split_sum(f32x4 main, f32x4 small)
+{
+    f32x4 sum = main + small;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum[e] = __builtin_isinf(main[e]) ? main[e] : sum[e];
+    return sum;
+}
 
 }  // namespace rtoss

@@ -78,3 +78,25 @@ def test_largest_values_stay_finite(case):
     x = torch.full((N, H, W, Ci), -big, device="cuda")
     got, want, _ = run(*case, w, x)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_infinite_values_give_what_an_fp32_sum_gives(case):
+    """Infinities in the input, kept weights with and without bits below the first eight: the result's infinities and NaN stand
+    where 64 bits has them (0 * inf under a pruned weight, sums of both signs), and the rest keeps its bound."""
+    N, Ci, Co, H, W, ks, stride = case
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Ci - Co)
+    w = torch.randn((Co, Ci, ks, ks), generator=g, device="cuda")
+    w[:, ::2] = torch.where(w[:, ::2] < 0, -1.0, 1.0)
+    x = torch.randn((N, H, W, Ci), generator=g, device="cuda")
+    for i, value in enumerate([np.inf, -np.inf, np.nan]):
+        x[0, 4 + 9 * (i % 2), 3 + 8 * i, i % Ci] = float(value)
+    x[N - 1, H - 1, W - 2: W, Ci - 1] = float("inf")
+    got, want, size = run(*case, w, x)
+    if ks == 1:  # (groups of nine lie across the flat 1x1 weights: every pruned one under an infinite value gives NaN)
+        assert bool(want.isinf().any()) and bool(want.isnan().any())
+    finite = want.isfinite()
+    assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got[want.isinf()], want[want.isinf()])
+    steps = -(-Ci // 32) * ks * ks
+    assert bool(((got - want).abs()[finite] <= (size * (2.0 ** -22 + (4 * steps + 2) * 2.0 ** -24))[finite]).all())
