@@ -46,6 +46,17 @@ constexpr int kTwoBuffers = 8; // in a plan: rows per wave + kTwoBuffers
 constexpr int kDenseRows = 16; // in a plan of the dense mode without weights in LDS: rows of a workgroup + kDenseRows
 constexpr int strip_tile_bytes(int lay) { return lay == kDenseTaps ? kDenseTileBytes : layout_tile_bytes(kLayouts[lay]); }
 
+// The phase of a 2-of-4 layout (the centre's, then one per group) that reads input row i at column shift kw first.
+constexpr int first_phase(const TapLayout& l, int tn, int i, int kw)
+{
+    const auto reads = [&](int t) { return kw == t % 3 && i >= t / 3 && i < t / 3 + tn; };
+    if (l.centre && reads(4)) return 0;
+    for (int g = 0; g < l.groups; ++g)
+        for (int f = 0; f < 4; ++f)
+            if (l.tap[g][f] >= 0 && reads(l.tap[g][f])) return g + l.centre;
+    return -1;
+}
+
 template <int TN, int LAY, bool DB> struct Strip {
     static constexpr int ROWS = 4 * TN;                      // output rows of a workgroup
     static constexpr int TILE = strip_tile_bytes(LAY);
@@ -57,6 +68,7 @@ template <int TN, int LAY, bool DB> struct Strip {
     static constexpr int X_AREA = X_PER_WAVE * 4096;
     static constexpr int BUF = A_BYTES + X_AREA;             // one stage
     static constexpr int LDS = (DB ? 2 : 1) * BUF + EpiScaleBias<16 * kTM>::kBytes;
+    static constexpr bool AHEAD = DB && LAY == 0;            // operands a phase ahead (run_stage)
     static_assert(A_BYTES % 1024 == 0, "weight fragments are whole copy instructions");
 };
 
@@ -134,12 +146,12 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
             __syncthreads();                     // ... and everybody's
         }
         u32x4 R[TN + 2][3];
-#pragma unroll
-        for (int i = 0; i < TN + 2; ++i)
-#pragma unroll
-            for (int kw = 0; kw < 3; ++kw) R[i][kw] = *(const u32x4*)(lds_x + xoff + (i * kLW + kw) * 64);
         const char* A = lds_a + lane * 16;
         if constexpr (LAY == kDenseTaps) {
+#pragma unroll
+            for (int i = 0; i < TN + 2; ++i)
+#pragma unroll
+                for (int kw = 0; kw < 3; ++kw) R[i][kw] = *(const u32x4*)(lds_x + xoff + (i * kLW + kw) * 64);
 #pragma unroll
             for (int t = 0; t < 9; ++t)
 #pragma unroll
@@ -150,40 +162,61 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
                         acc[m][j] = Dense16<T>::mma(a, R[j + t / 3][t % 3], FIRST && t == 0 ? none : acc[m][j]);
                 }
         } else {
-            if constexpr (LY.centre) {
+            // Phases: the centre, then the groups of four taps.  With copies into LDS under way a wave cannot wait for some of its
+            // reads, only for all it has asked for: 26 of the stage's 35 stood in front of the first product.  With two buffers a
+            // phase's operands are asked for in front of the products of the phase before, so the first product waits for 7.
+            // (256 -> 256 on 1x50x84 10.5 -> 10.0 us, 512 -> 512 on 2x40x40 18.1 -> 16.9; TN = 3, whose two workgroups per compute
+            // unit cover each other, 19.7 -> 19.3 on 4x50x84.  Layout 1 and one buffer gained nothing from it.)
+            constexpr int PHASES = NG + LY.centre;
+            u32x4 a[2][kTM][2];
+            int idx[2][kTM];
+            auto fetch = [&](auto phase_tag) {
+                constexpr int phase = decltype(phase_tag)::value, g = phase - LY.centre, at = P::AHEAD ? phase % 2 : 0;
+                static_for<3 * (TN + 2)>([&](auto window) {
+                    constexpr int i = decltype(window)::value / 3, kw = decltype(window)::value % 3;
+                    if constexpr ((P::AHEAD ? first_phase(LY, TN, i, kw) : 0) == phase) R[i][kw] = *(const u32x4*)(lds_x + xoff + (i * kLW + kw) * 64);
+                });
 #pragma unroll
                 for (int m = 0; m < kTM; ++m) {
-                    const u32x4 a = *(const u32x4*)(A + m * P::TILE + 2 * NG * kFragBytes);
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[m][j] = Dense16<T>::mma(a, R[j + 1][1], FIRST ? none : acc[m][j]);
+                    a[at][m][0] = *(const u32x4*)(A + m * P::TILE + (g < 0 ? 2 * NG : 2 * g) * kFragBytes);
+                    if constexpr (g >= 0) {
+                        a[at][m][1] = *(const u32x4*)(A + m * P::TILE + (2 * g + 1) * kFragBytes);
+                        idx[at][m] = *(const int*)(lds_a + m * P::TILE + FR * kFragBytes + (g * 64 + lane) * 4);
+                    }
                 }
-            }
-#pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                u32x4 a[kTM][2];
-                int idx[kTM];
-#pragma unroll
-                for (int m = 0; m < kTM; ++m) {
-                    a[m][0] = *(const u32x4*)(A + m * P::TILE + (2 * g) * kFragBytes);
-                    a[m][1] = *(const u32x4*)(A + m * P::TILE + (2 * g + 1) * kFragBytes);
-                    idx[m] = *(const int*)(lds_a + m * P::TILE + FR * kFragBytes + (g * 64 + lane) * 4);
+            };
+            fetch(std::integral_constant<int, 0>{});
+            static_for<PHASES>([&](auto phase_tag) {
+                constexpr int phase = decltype(phase_tag)::value, g = phase - LY.centre, at = P::AHEAD ? phase % 2 : 0;
+                if constexpr (P::AHEAD) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+                    if constexpr (phase + 1 < PHASES) fetch(std::integral_constant<int, phase + 1>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                } else if constexpr (phase > 0) {
+                    fetch(phase_tag);
                 }
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    u32x4 r[4];
+                    if constexpr (g < 0) {
 #pragma unroll
-                    for (int f = 0; f < 4; ++f) {
-                        const int t = LY.tap[g][f] >= 0 ? LY.tap[g][f] : LY.tap[g][0];  // (an empty slot weighs 0)
-                        r[f] = R[j + t / 3][t % 3];
+                        for (int m = 0; m < kTM; ++m) acc[m][j] = Dense16<T>::mma(a[at][m][0], R[j + 1][1], FIRST ? none : acc[m][j]);
+                    } else {
+                        u32x4 r[4];
+#pragma unroll
+                        for (int f = 0; f < 4; ++f) {
+                            const int t = LY.tap[g][f] >= 0 ? LY.tap[g][f] : LY.tap[g][0];  // (an empty slot weighs 0)
+                            r[f] = R[j + t / 3][t % 3];
+                        }
+                        const u32x8 b[2] = {sparse_operand(r, 0), sparse_operand(r, 1)};
+#pragma unroll
+                        for (int m = 0; m < kTM; ++m)
+                            acc[m][j] = Sparse64<T>::template mma<0>(a[at][m][0], b[0], FIRST && phase == 0 ? none : acc[m][j], idx[at][m]);
+#pragma unroll
+                        for (int m = 0; m < kTM; ++m) acc[m][j] = Sparse64<T>::template mma<1>(a[at][m][1], b[1], acc[m][j], idx[at][m]);
                     }
-                    const u32x8 b[2] = {sparse_operand(r, 0), sparse_operand(r, 1)};
-#pragma unroll
-                    for (int m = 0; m < kTM; ++m)
-                        acc[m][j] = Sparse64<T>::template mma<0>(a[m][0], b[0], FIRST && !LY.centre && g == 0 ? none : acc[m][j], idx[m]);
-#pragma unroll
-                    for (int m = 0; m < kTM; ++m) acc[m][j] = Sparse64<T>::template mma<1>(a[m][1], b[1], acc[m][j], idx[m]);
                 }
-            }
+            });
         }
     };
     run_stage(std::true_type{}, 0);
