@@ -14,6 +14,7 @@
 #include "common.h"
 #include "dtypes.h"
 #include "epilogue.h"
+#include "fp32_split.h"
 #include "mma.h"
 #include "pack_plan.h"
 
@@ -219,7 +220,9 @@ int ksplit1x1_plan(const rtoss_wdesc& d, const ConvParams& c)
     const auto groups = [&](int tm, int tn) { return (int64_t)((section_tiles(KS, d.Co) + tm - 1) / tm) * ((P + 16 * tn - 1) / (16 * tn)); };
     if (P > 0x7fffff00 || groups(2, 1) > kMaxGridGroups) return kNone;
     if (d.dt == RTOSS_F32) {
-        // (tenths of a workgroup per compute unit)
+        // (tenths of a workgroup per compute unit; one live weight per group of 64 channels: the streaming kernel's six products
+        // would be less precise than the fp32 instruction here, fp32_split.h)
+        if (KS == 4 && few_live_products(d)) return k32x16;
         const int64_t most = KS <= 8 ? 50 : KS == 16 ? 25 : 16;
         return 10 * groups(2, 1) <= most * cus ? k32x16 : kNone;
     }

@@ -201,11 +201,10 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
 // on 48 000 positions 23.0 us on the fp32 instruction, now 18.5.
 // Column n of position block j is position TN*n + j of the tile: neighbouring lanes write rows TN apart, whose LDS addresses spread
 // over the banks (512-byte rows, as 16 neighbouring positions, would all meet in one).
-template <typename T, typename TO, int TM, int TN, bool ROW16>
-__global__ __launch_bounds__(256, 2) void conv1x1_mma_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
-                                                          const char* __restrict__ zeros, int64_t P, int Ci, int Co, int m_tiles_total,
-                                                          int work_total, int work_per_xcd, int pitch, int span, int blocks,
-                                                          uint32_t per_chunks, uint32_t per_last_chunks, Epilogue ep)
+template <typename T, typename TO, int TM, int TN, bool ROW16, int STEPS>
+__device__ __forceinline__ void whole_rows(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                           int64_t P, int Ci, int Co, int m_tiles_total, int work_total, int work_per_xcd, int pitch, int span,
+                                           int blocks, uint32_t per_chunks, uint32_t per_last_chunks, const Epilogue& ep)
 {
     constexpr int EB = (int)sizeof(TO), PT = 16 * TN;
     extern __shared__ __attribute__((aligned(16))) char smem[];  // [position][channel] of the tile, rows `pitch` bytes apart
@@ -272,7 +271,7 @@ __global__ __launch_bounds__(256, 2) void conv1x1_mma_kernel(const T* __restrict
 #pragma unroll
                     for (int m = 0; m < TM; ++m) {
                         const Split8 a = split8(o.a[m][0], o.a[m][1]);
-                        static_for<kSplitSteps>([&](auto step) {
+                        split_steps<STEPS>([&](auto step) {
 #pragma unroll
                             for (int j = 0; j < TN; ++j) split_step<decltype(step)::value>(a, b[j], acc[m][j], small[m][j]);
                         });
@@ -384,6 +383,26 @@ __global__ __launch_bounds__(256, 2) void conv1x1_mma_kernel(const T* __restrict
 }
 
 template <typename T, typename TO, int TM, int TN, bool ROW16>
+__global__ __launch_bounds__(256, 2) void conv1x1_mma_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+                                                          const char* __restrict__ zeros, int64_t P, int Ci, int Co, int m_tiles_total,
+                                                          int work_total, int work_per_xcd, int pitch, int span, int blocks,
+                                                          uint32_t per_chunks, uint32_t per_last_chunks, Epilogue ep)
+{
+    whole_rows<T, TO, TM, TN, ROW16, kSplitSix>(x, y, wfrag, zeros, P, Ci, Co, m_tiles_total, work_total, work_per_xcd, pitch, span, blocks,
+                                                per_chunks, per_last_chunks, ep);
+}
+// (fp32 sums of few products: fp32_split.h.  A kernel of its own, 36 -> 120 channels on 28 028 positions 10.1 us; one for both with a branch 11.6)
+template <typename T, typename TO, int TM, int TN, bool ROW16, int STEPS>
+__global__ __launch_bounds__(256, 2) void conv1x1_mma_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+                                                          const char* __restrict__ zeros, int64_t P, int Ci, int Co, int m_tiles_total,
+                                                          int work_total, int work_per_xcd, int pitch, int span, int blocks,
+                                                          uint32_t per_chunks, uint32_t per_last_chunks, Epilogue ep)
+{
+    whole_rows<T, TO, TM, TN, ROW16, STEPS>(x, y, wfrag, zeros, P, Ci, Co, m_tiles_total, work_total, work_per_xcd, pitch, span, blocks,
+                                            per_chunks, per_last_chunks, ep);
+}
+
+template <typename T, typename TO, int TM, int TN, bool ROW16, int... STEPS>
 rtoss_status launch_whole_rows_tile(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     constexpr int EB = (int)sizeof(TO), PT = 16 * TN, kTileBytes = 64 * 1024;
@@ -402,7 +421,7 @@ rtoss_status launch_whole_rows_tile(const rtoss_wdesc& d, const ConvParams& c, c
     const int64_t total = (P + PT - 1) / PT * blocks, per_xcd = (total + 7) / 8;
     if (total > 0x7ffffff0) return fail(RTOSS_ESHAPE, "conv1x1: too many tiles");  // (not within the limit of dense1x1_launch_ok)
     constexpr int extra = 16 + EpiScaleBias<64 * TM>::kBytes;
-    auto kern = conv1x1_mma_kernel<T, TO, TM, TN, ROW16>;
+    auto kern = conv1x1_mma_kernel<T, TO, TM, TN, ROW16, STEPS...>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, kTileBytes + extra, lds_once, c.dev.device, "conv1x1 shared memory attribute")) return st;
     const int64_t groups = std::min<int64_t>(8 * per_xcd, kMaxGridGroups);
@@ -412,19 +431,27 @@ rtoss_status launch_whole_rows_tile(const rtoss_wdesc& d, const ConvParams& c, c
     return check_hip(hipGetLastError(), "conv1x1 launch");
 }
 
-template <typename T, typename TO, bool ROW16>
-rtoss_status launch_whole_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+template <typename T, typename TO, bool ROW16, int... STEPS>
+rtoss_status launch_whole_rows_steps(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     // Tiles of 32 positions; of 64 where that still leaves more than one workgroup per compute unit and a workgroup's weights are
     // many (72 -> 255, 28 028 positions: 8.6 us and 9.3; 80 -> 85, 48 000: 8.1 and 7.6).  fp32 has no registers for that.
     const int tiles = (d.Co + 15) / 16;
-    if (tiles <= 4) return launch_whole_rows_tile<T, TO, 1, 2, ROW16>(d, c, wfrag, x, y, s);
-    if (tiles <= 8) return launch_whole_rows_tile<T, TO, 2, 2, ROW16>(d, c, wfrag, x, y, s);
+    if (tiles <= 4) return launch_whole_rows_tile<T, TO, 1, 2, ROW16, STEPS...>(d, c, wfrag, x, y, s);
+    if (tiles <= 8) return launch_whole_rows_tile<T, TO, 2, 2, ROW16, STEPS...>(d, c, wfrag, x, y, s);
     if constexpr (sizeof(T) == 2) {
         const DeviceInfo& dev = c.dev;
         if ((int64_t)c.N * c.H * c.W > 64 * (int64_t)dev.cus) return launch_whole_rows_tile<T, TO, 4, 4, ROW16>(d, c, wfrag, x, y, s);
     }
-    return launch_whole_rows_tile<T, TO, 4, 2, ROW16>(d, c, wfrag, x, y, s);
+    return launch_whole_rows_tile<T, TO, 4, 2, ROW16, STEPS...>(d, c, wfrag, x, y, s);
+}
+
+template <typename T, typename TO, bool ROW16>
+rtoss_status launch_whole_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+{
+    if constexpr (sizeof(T) == 4)
+        if (few_live_products(d)) return launch_whole_rows_steps<T, TO, ROW16, kSplitAll>(d, c, wfrag, x, y, s);
+    return launch_whole_rows_steps<T, TO, ROW16>(d, c, wfrag, x, y, s);
 }
 
 template <typename T, typename TO, int TM>

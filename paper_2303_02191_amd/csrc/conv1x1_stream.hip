@@ -300,6 +300,7 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
     constexpr int KK = KS / 2, PB = f32_positions(KS), TN = PB / 16;  // steps of 32 channels; blocks of 16 positions
     constexpr int ROW = 64 * KS, PLANE = KK * PB * 64;  // bytes of a position; of one bf16 part of a buffer
     constexpr int U = PB * KK / 64;                     // pieces of 2 x 4 channels a lane splits per buffer
+    constexpr int STEPS = KS == 2 ? kSplitAll : kSplitSix;  // (few_live_products; 64 channels with k = 1 take the K split)
     static_assert(U * 64 == PB * KK, "whole rounds of pieces");
     __shared__ __attribute__((aligned(16))) char X[3 * PLANE];
     __shared__ __attribute__((aligned(16))) char out[PB * 256];  // 64 channels of a position, its 16-byte chunks permuted by position % 16
@@ -374,17 +375,19 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
 #pragma unroll
         for (int j = 0; j < TN; ++j) main[j] = small[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            Split8 v[TN];
+        for (int i = 0; i < KK * TN / 2; ++i) {  // two blocks of positions at a time: the operands of four do not fit beside the rest
+            const int kk = i % KK, j0 = i / KK * 2;
+            Split8 v[2];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const char* at = x_lane + (kk * PB + 16 * j) * 64;
+            for (int j = 0; j < 2; ++j) {
+                const char* at = x_lane + (kk * PB + 16 * (j0 + j)) * 64;
                 v[j] = Split8{*(const u32x4*)at, *(const u32x4*)(at + PLANE), *(const u32x4*)(at + 2 * PLANE)};
             }
-            static_for<kSplitSteps>([&](auto step) {
+            split_steps<STEPS>([&](auto step) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j) split_step<decltype(step)::value>(a[kk], v[j], main[j], small[j]);
+                for (int j = 0; j < 2; ++j) split_step<decltype(step)::value>(a[kk], v[j], main[j0 + j], small[j0 + j]);
             });
+            if constexpr (KS == 2) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) *(f32x4*)(o_lane + 16 * j * 256) = split_sum(main[j], small[j]);

@@ -280,8 +280,10 @@ inline int64_t f32_groups(const rtoss_wdesc& d, const ConvParams& c, int rows)
 //      64 ->  64 2x60x70 (300)  11.9  9.6  9.7          256 -> 256 4x80x80 (3200)   274   164   141   135
 //     ragged: 40 -> 72 2x40x60 (320) 8.8 9.9 9.9; 80 -> 80 1x100x120 (800) 25.6 22.4 18.4; 48 -> 72 4x77x91 (1872) 33.1 29.8 24.0
 //     stride 2, two rows (four would leave one workgroup per compute unit): 64 -> 128 2x80x100 13.5 10.6, 32 -> 64 4x112x140 15.4 10.7
+// Sums of few live products stay on the fp32 instruction, for their precision (8 -> 72 4x77x91, k = 2: 14.7 us, split 13.9; stride 2 8.5, 7.0).
 int f32_rows(const rtoss_wdesc& d, const ConvParams& c, int64_t cus)
 {
+    if (few_live_products(d)) return 0;
     const int64_t g2 = f32_groups(d, c, 2);
     if (c.stride == 2) return g2 > cus / 2 ? 2 : 0;
     if (ragged(d) ? 2 * g2 < 3 * cus : 8 * g2 < 5 * cus) return 0;

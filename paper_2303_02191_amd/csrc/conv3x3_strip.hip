@@ -524,7 +524,8 @@ static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int lay
     };
     if (d.dt == RTOSS_F32) {
         // Eight rows from six workgroups per four compute units on; below that the dense-mode kernel's shorter tiles spread the
-        // work better (timings: f32_rows there).
+        // work better (timings, and why sums of few products stay out: f32_rows there).
+        if (few_live_products(d)) return 0;
         return 2 * groups(2) >= 3 * cus ? kDenseRows + 8 : 0;
     }
     // shallow narrow launches of the dense mode: its own 16-channel tiles

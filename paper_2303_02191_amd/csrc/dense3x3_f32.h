@@ -125,7 +125,7 @@ __device__ __forceinline__ void dense3x3_f32_tile(const float* __restrict__ x, f
                 Split8 coming;
                 if (i + 1 < P::IH) coming = row(i + 1);
                 __builtin_amdgcn_sched_barrier(0);  // (likewise)
-                static_for<kSplitSteps>([&](auto step) {
+                split_steps<kSplitSix>([&](auto step) {
 #pragma unroll
                     for (int kh = 0; kh < 3; ++kh) {
                         const int j = (i - kh) / S;

@@ -26,10 +26,11 @@ CASES = [
 ]
 
 
-def run(N, Ci, Co, H, W, ks, stride, w, x):
-    masks = B.rtoss_pattern_dict(9 if ks == 3 else 5)
+def run(N, Ci, Co, H, W, ks, stride, w, x, k=None):
+    k = k or (9 if ks == 3 else 5)
+    masks = B.rtoss_pattern_dict(k)
     idx = pl.select_patterns(w, B.F32, masks)
-    y = pl.PackedLayer(Co, Ci, ks, 9 if ks == 3 else 5, B.F32, masks).pack(w, idx).conv(x, stride=stride)
+    y = pl.PackedLayer(Co, Ci, ks, k, B.F32, masks).pack(w, idx).conv(x, stride=stride)
     flat = w.reshape(-1).double().clone()
     G = flat.numel() // 9
     taps = torch.tensor([[int(m) >> t & 1 for t in range(9)] for m in masks], dtype=torch.float64, device="cuda")
@@ -66,6 +67,41 @@ def test_ordinary_sums_are_as_precise_as_the_fp32_instruction(case):
     g.manual_seed(Ci * Co)
     got, want, _ = run(*case, torch.randn((Co, Ci, ks, ks), generator=g, device="cuda"), torch.randn((N, H, W, Ci), generator=g, device="cuda"))
     assert float((got - want).norm() / want.norm()) <= 1.04e-8 * np.sqrt(Ci * ks * ks)
+
+
+FEW = [
+    # N, Ci, Co, H, W, ksize, stride, k: sums of few live products
+    (3, 1, 80, 77, 91, 1, 1, 2),
+    (3, 5, 40, 77, 91, 1, 1, 2),     # rows without alignment
+    (3, 8, 255, 77, 91, 1, 1, 3),
+    (3, 20, 80, 77, 91, 1, 1, 2),
+    (1, 48, 80, 25, 33, 1, 1, 2),    # whole tiles, few positions
+    (5, 32, 80, 77, 95, 1, 1, 2),    # streaming
+]
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("case", FEW)
+def test_short_sums_lose_one_rounding(case, relu):
+    """1x1 sums of 0 to 11 live products: with eight partial products little is lost but the last addition's rounding, whose 2-norm
+    over random mantissas is 2^-24 / sqrt(3) / sqrt(2) = 2.4e-8 of the result (2.5 to 2.6e-8 measured; 3.2 to 3.7e-8 with six)."""
+    N, Ci, Co, H, W, ks, stride, k = case
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Ci * Co + k)
+    x = torch.randn((N, H, W, Ci), generator=g, device="cuda")
+    got, want, _ = run(*case[:7], torch.randn((Co, Ci, ks, ks), generator=g, device="cuda"), x.relu() if relu else x, k)
+    assert float((got - want).norm() / want.norm()) <= 2.8e-8
+
+
+@pytest.mark.parametrize("Co", [16, 80])
+def test_single_products_are_rounded_correctly(Co):
+    """One input channel: no output is further from its product than half a unit of its last place, 2^-24 of it, and the roundings of the
+    small products, seven of 2^-24 of their accumulator (2^-6 of the product at most)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Co)
+    case = (3, 1, Co, 77, 91, 1, 1)
+    got, want, size = run(*case, torch.randn((Co, 1, 1, 1), generator=g, device="cuda"), torch.randn((3, 77, 91, 1), generator=g, device="cuda"), 2)
+    assert bool(((got - want).abs() <= size * 2.0 ** -24 * (1 + 7 * 2.0 ** -6)).all())
 
 
 @pytest.mark.parametrize("case", CASES[:1] + CASES[-1:])
