@@ -38,7 +38,9 @@ __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(cons
     constexpr int kPer = (kRow / 2 + 64) / 64;    // rounds of 64 aligned words that cover such a row, wherever it begins
     constexpr int kPitch = 128 * kPer;            // halves of a row in LDS: whole rounds
     constexpr int kRows = (IH + 3) / 4;
-    __shared__ __attribute__((aligned(16))) uint16_t smem[2 + IH * kPitch];
+    // Behind the tile: the zeros of the K slots past the reduction, one half for each of a lane's four blocks below.
+    constexpr int kNone = IH * kPitch, kDown = S * kPitch, kRight = 16 * S * Ci;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[2 + kNone + kDown + kRight + 1];
     uint16_t* const xs = smem + 2;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -103,17 +105,18 @@ __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(cons
             }
         }
     }
+    if (tid < 4) xs[kNone + (tid >> 1) * kDown + (tid & 1) * kRight] = 0;
     const int begin = alternate ? 0 : odd[0];  // of a row in LDS
     __syncthreads();
 
-    // LDS offset of each of this lane's 8 K values relative to the block's first tap (same for all blocks).  Those past the
-    // reduction weigh 0: they read the first tap.
+    // LDS offset of each of this lane's 8 K values relative to the block's first position (same for all blocks).  Those past the
+    // reduction weigh 0 and read zeros (a value of the tile may be infinite).
     constexpr int k3 = 3 * Ci, K = 9 * Ci;
     int koff[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int k = 8 * qq + j, kh = k / k3;
-        koff[j] = (k < K ? kh * kPitch + k - kh * k3 : 0) + 2 * wave * S * kPitch + nn * S * Ci + begin;
+        koff[j] = k < K ? kh * kPitch + k - kh * k3 + 2 * wave * S * kPitch + nn * S * Ci + begin : kNone;
     }
     // (position and address of this lane's first output; a block's distance from it is uniform)
     const int64_t pos0 = ((int64_t)n_img * Ho + oh0 + 2 * wave) * Wo + ow0 + nn;
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(cons
 #pragma unroll 1
         for (int jb = 0; jb < 4; ++jb) {  // 16 blocks: 8 rows x 2 half-rows of 16 columns
             const int r = jb >> 1, c = (jb & 1) * 16;
-            const uint16_t* at = xs + r * S * kPitch + c * S * Ci;
+            const uint16_t* at = xs + r * kDown + (jb & 1) * kRight;
             u32x4 b;
 #pragma unroll
             for (int j = 0; j < 4; ++j) b[j] = at[koff[2 * j]] | ((uint32_t)at[koff[2 * j + 1]] << 16);
