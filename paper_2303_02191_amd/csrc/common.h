@@ -176,6 +176,7 @@ rtoss_status launch_conv1x1_ksplit(const rtoss_wdesc& d, const ConvParams& c, in
 
 // 3x3 convolution with <= 3 input channels (conv3x3_stem.hip)
 bool stem3x3_shape_ok(const rtoss_wdesc& d);
+bool stem3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c);
 size_t stem3x3_section_bytes(const rtoss_wdesc& d);
 rtoss_status launch_conv3x3_stem(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                  hipStream_t s);

@@ -18,6 +18,7 @@
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
+#include "stem_rows.h"
 
 namespace rtoss {
 
@@ -31,7 +32,7 @@ constexpr int kTH = 8, kTW = 32;  // output tile: 8 rows x 32 columns = 16 block
 template <typename T, typename TO, int S, int TM, int Ci>
 __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                            const char* __restrict__ wfrag, int H, int W, int Co,
-                                                           int Ho, int Wo, int tiles_c, Epilogue ep)
+                                                           int Ho, int Wo, int tiles_c, int odd_image, Epilogue ep)
 {
     constexpr int IH = (kTH - 1) * S + 3, IW = (kTW - 1) * S + 3;
     constexpr int kRow = IW * Ci;                 // halves of an input row of the tile
@@ -51,22 +52,22 @@ __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(cons
     const int ih0 = oh0 * S - 1, iw0 = ow0 * S - 1;
 
     // ---- stage the input tile (with halo, zero padded): wave w takes rows w, w + 4, ... as aligned words, all of them asked for
-    // before the first one is used.  (Of words without a half of the row inside the image the nearest one is read instead; an
-    // aligned word with such a half never leaves its page.) ----
+    // before the first one is used.  Of a tensor of an odd number of halves the last one is read by itself, below. ----
     const int lo = iw0 < 0 ? Ci : 0, hi = min(IW, W - iw0) * Ci;  // halves of a row inside the image
     const bool edge = lo > 0 || hi < kRow;                        // uniform, and so is the next
     const bool alternate = (W & Ci & 1) != 0;                     // rows begin in the lower and the upper half of a word in turn
+    const int cut_row = n_img == odd_image && W - iw0 <= IW ? H - 1 : -1;  // input row of the tile that ends a tensor of an odd number of halves
     uint32_t word[kRows][kPer];
     int odd[kRows];  // uniform: the row begins in the upper half of its first word
 #pragma unroll
     for (int i = 0; i < kRows; ++i) {
         const int ih = min(max(ih0 + wave + 4 * i, 0), H - 1);
-        const char* row = (const char*)x + ((((int64_t)n_img * H + ih) * W + iw0) * Ci) * 2;
-        odd[i] = (int)((uintptr_t)row >> 1 & 1);
-        row -= 2 * odd[i];
-        const int first = (lo + odd[i]) / 2, last = (hi - 1 + odd[i]) / 2;
+        const int64_t at = (((int64_t)n_img * H + ih) * W + iw0) * Ci;
+        const StemRow row((int)at & 1, lo, hi, ih == cut_row);
+        odd[i] = row.odd;
+        const char* src = (const char*)x + (at - row.odd) * 2;
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) word[i][k] = *(const uint32_t*)(row + 4 * min(max(k * 64 + lane, first), last));
+        for (int k = 0; k < kPer; ++k) word[i][k] = *(const uint32_t*)(src + 4 * row.word(k * 64 + lane));
     }
     // weight fragments stay in registers: TM tiles of 16 output channels; so do scale and bias of this lane's channels
     u32x4 afrag[TM];
@@ -104,6 +105,11 @@ __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(cons
                 *(uint32_t*)(row + 2 * d) = w;
             }
         }
+    }
+    if (cut_row >= 0) {  // uniform: the tensor's last half
+        const int r = cut_row - ih0;
+        asm volatile("" ::: "memory");  // (behind the wave's own write of that row)
+        if (r < IH && wave == (r & 3) && lane == 0) xs[r * kPitch + hi - 1] = ((const uint16_t*)x)[(((int64_t)n_img + 1) * H * W) * Ci - 1];
     }
     if (tid < 4) xs[kNone + (tid >> 1) * kDown + (tid & 1) * kRight] = 0;
     const int begin = alternate ? 0 : odd[0];  // of a row in LDS
@@ -169,7 +175,7 @@ rtoss_status launch_stem_ci(const rtoss_wdesc& d, const ConvParams& c, const cha
     if (c.N > 65535) return fail(RTOSS_ESHAPE, "conv: batch too large");
     dim3 grid((unsigned)(tiles_r * tiles_c), (unsigned)c.N), block(256);
     conv3x3_stem_kernel<T, TO, S, TM, Ci><<<grid, block, 0, s>>>((const T*)x, (TO*)y, wfrag, c.H, c.W, d.Co, Ho, Wo, tiles_c,
-                                                                 c.ep);
+                                                                 c.N & c.H & c.W & Ci & 1 ? c.N - 1 : -1, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 stem launch");
 }
 
@@ -199,6 +205,9 @@ bool stem3x3_shape_ok(const rtoss_wdesc& d)
 {
     return d.ksize == 3 && (d.dt == RTOSS_F16 || d.dt == RTOSS_BF16) && d.Ci <= 3 && d.Co % 16 == 0 && d.Co <= 64;
 }
+
+// (rows are read as words of two values: stem_rows.h)
+bool stem3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c) { return (int64_t)c.N * c.H * c.W * d.Ci > 1; }
 
 size_t stem3x3_section_bytes(const rtoss_wdesc& d) { return (size_t)4 * 1024; }  // 4 tiles, unused ones zero
 

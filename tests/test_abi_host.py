@@ -4,12 +4,14 @@ before touching the GPU."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
 
 import oracle
 from paper_2303_02191_amd import binding as B
+from paper_2303_02191_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -246,3 +248,10 @@ def test_coherent_path_argument_errors():
     with pytest.raises(B.RtossError) as e:
         B.rtoss_conv2d_pattern_coherent(d, ok, None, masks, 0, 512, 1 << 20)
     assert e.value.status == B.EINVAL
+
+
+def test_stem_reads_stay_inside_the_tensor(tmp_path):
+    exe = str(tmp_path / "stem_rows_check")
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-I", build.CSRC, os.path.join(ROOT, "tests", "stem_rows_check.cpp"), "-o", exe])
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
