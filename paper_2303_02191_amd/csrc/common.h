@@ -89,9 +89,7 @@ rtoss_status launch_select(const void* w, rtoss_dtype dt, int64_t G, const Dict&
 constexpr int kSelectBatchMax = 64;  // tensors per batched selection launch
 rtoss_status launch_select_batch(const rtoss_select_item* items, int n, rtoss_dtype dt, const Dict& dict, hipStream_t s);
 
-// counts of each pattern index (select.hip); clear_counts: zeros the counters of a dictionary of at most 256 patterns (also called
-// by host_ext.cpp, whose fresh counters need no trip through the framework's fill)
-rtoss_status clear_counts(uint32_t* hist, int P, hipStream_t s);
+// counts of each pattern index (select.hip; counts.h: zeroing them)
 rtoss_status launch_histogram(const uint8_t* idx, int64_t G, int P, uint32_t* hist, hipStream_t s);
 
 rtoss_status launch_conv_direct(const rtoss_wdesc& d, const ConvParams& c, const Dict& dict, const void* live_values,

@@ -15,11 +15,8 @@
 #include <string>
 #include <vector>
 
+#include "counts.h"
 #include "rtoss.h"
-
-namespace rtoss {
-rtoss_status clear_counts(uint32_t* hist, int P, hipStream_t s);  // select.hip
-}
 
 namespace {
 

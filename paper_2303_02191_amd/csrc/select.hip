@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "counts.h"
 #include "dtypes.h"
 #include "mma.h"
 
