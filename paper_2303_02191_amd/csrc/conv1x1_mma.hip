@@ -406,14 +406,17 @@ template <typename T, typename TO, int TM, int TN, bool ROW16, int... STEPS>
 rtoss_status launch_whole_rows_tile(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     constexpr int EB = (int)sizeof(TO), PT = 16 * TN, kTileBytes = 64 * 1024;
+    constexpr int kSpan = (kTileBytes / PT - 32) / EB / (64 * TM) * (64 * TM);  // channels of a block, where a row is too long for the tile
+    static_assert(kSpan > 0, "a block is at least one step of the channel loop");
     const int64_t P = (int64_t)c.N * c.H * c.W;
     // The output rows of a tile without gaps where rows are not aligned to 16 bytes and the tile is one piece of the output; else a
-    // pitch that keeps them aligned.  Channels in blocks where a row is too long for the tile.
-    const auto padded = [](int bytes) { return (bytes + 15) / 16 * 16 + 16; };
-    int span = d.Co, pitch = d.Co * EB;
+    // pitch that keeps them aligned.
+    const auto padded = [](int64_t bytes) { return (bytes + 15) / 16 * 16 + 16; };
+    int span = d.Co;
+    int64_t pitch = (int64_t)d.Co * EB;
     if (pitch % 16 == 0 || c.ep.ldy != d.Co || d.Co < 16) pitch = padded(pitch);  // (fewer: a row's end runs over into an unordered one)
     if (pitch * PT > kTileBytes) {
-        span = (kTileBytes / PT - 32) / EB / (64 * TM) * (64 * TM);
+        span = kSpan;
         pitch = padded(span * EB);
     }
     const int blocks = (d.Co + span - 1) / span;
@@ -426,7 +429,7 @@ rtoss_status launch_whole_rows_tile(const rtoss_wdesc& d, const ConvParams& c, c
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, kTileBytes + extra, lds_once, c.dev.device, "conv1x1 shared memory attribute")) return st;
     const int64_t groups = std::min<int64_t>(8 * per_xcd, kMaxGridGroups);
     kern<<<dim3((unsigned)groups), dim3(256), (size_t)pitch * PT + extra, s>>>(
-        (const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Ci, d.Co, ring_padded_tiles(d.Co), (int)total, (int)per_xcd, pitch, span, blocks,
+        (const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Ci, d.Co, ring_padded_tiles(d.Co), (int)total, (int)per_xcd, (int)pitch, span, blocks,
         reciprocal(span), reciprocal(d.Co - (blocks - 1) * span), c.ep);
     return check_hip(hipGetLastError(), "conv1x1 launch");
 }
@@ -435,11 +438,12 @@ template <typename T, typename TO, bool ROW16, int... STEPS>
 rtoss_status launch_whole_rows_steps(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     // Tiles of 32 positions; of 64 where that still leaves more than one workgroup per compute unit and a workgroup's weights are
-    // many (72 -> 255, 28 028 positions: 8.6 us and 9.3; 80 -> 85, 48 000: 8.1 and 7.6).  fp32 has no registers for that.
+    // many (72 -> 255, 28 028 positions: 8.6 us and 9.3; 80 -> 85, 48 000: 8.1 and 7.6).  fp32 has no registers for that, and fp32
+    // output no room in LDS: 64 positions of a step's 256 channels are the whole tile (72 -> 240, where they fit: 11.6 us, 32 positions 9.4).
     const int tiles = (d.Co + 15) / 16;
     if (tiles <= 4) return launch_whole_rows_tile<T, TO, 1, 2, ROW16, STEPS...>(d, c, wfrag, x, y, s);
     if (tiles <= 8) return launch_whole_rows_tile<T, TO, 2, 2, ROW16, STEPS...>(d, c, wfrag, x, y, s);
-    if constexpr (sizeof(T) == 2) {
+    if constexpr (sizeof(T) == 2 && sizeof(TO) == 2) {
         const DeviceInfo& dev = c.dev;
         if ((int64_t)c.N * c.H * c.W > 64 * (int64_t)dev.cus) return launch_whole_rows_tile<T, TO, 4, 4, ROW16>(d, c, wfrag, x, y, s);
     }

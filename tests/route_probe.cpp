@@ -1,26 +1,30 @@
 // Which kernel a convolution call launches, without a GPU: librtoss.so linked against stand-ins for the few runtime calls it
 // makes, on a device of 256 compute units.  Reads calls, one a line,
 //     coherent Co Ci ksize k rule dt  N H W stride out_dt  fused
-// and prints the status and the launched kernel's handle (its offset in the library).
+// and prints the status, the launched kernel's handle (its offset in the library), the dynamic LDS it was launched with and the
+// limit that was set for it.
 #include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
-#include <vector>
+#include <map>
 
 #include "rtoss.h"
 
 static const void* g_kernel;
+static size_t g_lds;
+static std::map<const void*, int> g_limit;
 
 extern "C" {
 hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
-hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void* kernel, hipFuncAttribute, int bytes) { return g_limit[kernel] = bytes, hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { return *n = 2, hipSuccess; }
-hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t, hipStream_t) { return g_kernel = kernel, hipSuccess; }
+hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void**, size_t lds, hipStream_t) { return g_kernel = kernel, g_lds = lds, hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
-hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+static size_t g_call_lds;
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t lds, hipStream_t) { return g_call_lds = lds, hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t* lds, hipStream_t*) { return *lds = g_call_lds, hipSuccess; }
 }
 
 int main()
@@ -45,13 +49,15 @@ int main()
         e.act = RTOSS_ACT_SILU;
         e.y_ld = e.residual_ld = (d.Co + 7) / 8 * 8 + 16;  // a channel slice
         g_kernel = nullptr;
+        g_lds = 0;
         const rtoss_status st = coherent ? rtoss_conv2d_pattern_coherent(&d, &c, fused ? &e : nullptr, masks, P, base, x, y, nullptr)
                                 : fused  ? rtoss_conv2d_pattern_fused(&d, &c, &e, masks, P, base, x, y, nullptr)
                                          : rtoss_conv2d_pattern(&d, &c, masks, P, base, x, y, nullptr);
         Dl_info info{};
         size_t at = 0;
         if (g_kernel && dladdr(g_kernel, &info)) at = (size_t)((const char*)g_kernel - (const char*)info.dli_fbase);
-        printf("%d %zx\n", (int)st, at);
+        const auto limit = g_limit.find(g_kernel);
+        printf("%d %zx %zu %d\n", (int)st, at, g_lds, limit == g_limit.end() ? 64 * 1024 : limit->second);  // (64 KB: the runtime's default)
     }
     return 0;
 }

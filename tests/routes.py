@@ -29,18 +29,22 @@ def _probe():
     return exe, names
 
 
-def kernels(calls):
-    """calls: tuples (dt, N, Ci, Co, H, W, ksize, stride, k, rule, out_dt, fused, coherent).  Returns for each the kernel, as
-    'conv3x3_strip<bf16,f32,3,0,true>', or the status of a call that was refused."""
+def launches(calls):
+    """calls: tuples (dt, N, Ci, Co, H, W, ksize, stride, k, rule, out_dt, fused, coherent).  Returns for each (kernel, dynamic LDS bytes,
+    their limit), the kernel as 'conv3x3_strip<bf16,f32,3,0,true>' or the status of a call that was refused."""
     exe, names = _probe()
     text = "".join("%d %d %d %d %d %d %d  %d %d %d %d %d  %d\n" % (coherent, Co, Ci, ks, k, rule, dt, N, H, W, stride, out_dt, fused)
                    for dt, N, Ci, Co, H, W, ks, stride, k, rule, out_dt, fused, coherent in calls)
     out = []
     for line in subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines():
-        status, at = line.split()
-        out.append(names[int(at, 16)] if int(status) == B.OK else int(status))
+        status, at, lds, limit = line.split()
+        out.append((names[int(at, 16)] if int(status) == B.OK else int(status), int(lds), int(limit)))
     assert len(out) == len(calls)
     return out
+
+
+def kernels(calls):
+    return [kernel for kernel, lds, limit in launches(calls)]
 
 
 def library_kernels(prefix):

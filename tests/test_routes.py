@@ -11,7 +11,7 @@ import test_gpu_ksplit
 import test_gpu_ksplit1x1
 import test_gpu_launch_limits
 import test_gpu_strip
-from variants import VARIANTS
+from variants import OWN_TYPE_OUT, VARIANTS
 
 
 def call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, fused, coherent=False, rule=B.RULE_CONNECTED4):
@@ -29,7 +29,7 @@ def split(kernel):
 def test_every_variant_is_reached_where_the_list_says():
     calls, want = [], []
     for kernel, dt, N, Ci, Co, H, W, ks, stride, k, fused, coherent in VARIANTS:
-        for out_dt in ([dt] if kernel == "conv3x3_gather_rows<>" or dt == wl.F32 else [wl.F32, dt]):
+        for out_dt in ([dt] if kernel in OWN_TYPE_OUT or dt == wl.F32 else [wl.F32, dt]):
             calls.append(call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, fused, coherent))
             want.append((kernel, wl.DTYPE_NAMES[dt]))
     got = [split(k) for k in routes.kernels(calls)]
@@ -41,6 +41,19 @@ def test_the_list_covers_the_library():
     listed = {(v[0], "f32" if v[1] == wl.F32 else "16-bit") for v in VARIANTS}
     held.discard(("conv_direct<1,1,0>", "f32"))  # NCHW tensors only
     assert held == listed
+
+
+def test_launches_stay_within_the_lds_they_declare():
+    """... and a compute unit has: every variant in both output types, and long output rows of 1x1 layers."""
+    calls = [call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, fused, coherent)
+             for kernel, dt, N, Ci, Co, H, W, ks, stride, k, fused, coherent in VARIANTS for out_dt in {wl.F32, dt}]
+    for dt in (wl.F16, wl.BF16, wl.F32):
+        for Ci in (18, 24):
+            for Co in (129, 248, 255, 256, 517, 700, 2000, (1 << 24) + 8, (1 << 25) + 3):
+                for H, W in ((1, 1), (131, 129)):
+                    calls += [call(dt, 1, Ci, Co, H, W, 1, 1, 2, out_dt, fused) for out_dt in {wl.F32, dt} for fused in (False, True)]
+    wrong = [(c, l) for c, l in zip(calls, routes.launches(calls)) if isinstance(l[0], str) and not l[1] <= l[2] <= 160 * 1024]
+    assert wrong == []
 
 
 def families(kernels):
