@@ -41,6 +41,7 @@
 #include "fp32_split.h"
 #include "mma.h"
 #include "pack_plan.h"
+#include "share.h"
 
 namespace rtoss {
 
@@ -69,19 +70,6 @@ template <int KS, int WM> struct Plan {
     static constexpr int RING = 3;
     static_assert(COPIES >= 1 && COPIES * 16 == PB * KS, "a buffer is a whole number of copy instructions");
     static_assert(RING >= 3 && (RING - 2) * COPIES < 64, "outstanding copies must fit the counter");
-};
-
-// The buffers of a launch, dealt out to workgroups in contiguous ranges whose lengths differ by one at most.  (Worked out from
-// the host's quotient: dividing in the kernel is some hundred scalar instructions before a workgroup's first load.)
-struct Range { int first, end; };
-struct Share {
-    int each, more;  // buffers of a workgroup; the first `more` workgroups take one more
-    Share(int64_t buffers, int workgroups) : each((int)(buffers / workgroups)), more((int)(buffers % workgroups)) {}
-    __device__ Range of(int workgroup) const
-    {
-        const int first = workgroup * each + min(workgroup, more);
-        return {first, first + each + (workgroup < more ? 1 : 0)};
-    }
 };
 
 // s_waitcnt immediate that waits for the vector-memory counter only (6 bits, split 4 + 2)

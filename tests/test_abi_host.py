@@ -250,8 +250,10 @@ def test_coherent_path_argument_errors():
     assert e.value.status == B.EINVAL
 
 
-def test_stem_reads_stay_inside_the_tensor(tmp_path):
-    exe = str(tmp_path / "stem_rows_check")
-    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-I", build.CSRC, os.path.join(ROOT, "tests", "stem_rows_check.cpp"), "-o", exe])
+@pytest.mark.parametrize("check", ["stem_rows_check", "share_check"])
+def test_index_arithmetic(tmp_path, check):
+    """tests/<check>.cpp walks a header of the kernels on the CPU."""
+    exe = str(tmp_path / check)
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-I", build.CSRC, os.path.join(ROOT, "tests", check + ".cpp"), "-o", exe])
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
