@@ -8,8 +8,8 @@
 // activation byte once for at most Ci*k/9 multiply-adds per output: it is bound by HBM, not by
 // arithmetic.  So the weights are expanded to zero-filled dense fragments and the kernel is
 // organised around the activation stream:
-//   * Workgroups are persistent.  Each owns one block of output channels and a contiguous range
-//     of positions, and every wave loads its share of the weight fragments into registers once
+//   * Workgroups are persistent.  Each owns one block of output channels and a share of the buffers
+//     of positions (share.h), and every wave loads its share of the weight fragments into registers once
 //     (at most 32 fragments = 128 registers), so the K loop reads weights from nowhere.
 //   * Activations arrive through a ring of 3 LDS buffers filled by global -> LDS copies.  A
 //     buffer holds PB positions (16 per wave along positions) x all Ci channels, laid out
@@ -105,12 +105,12 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // XCD-contiguous order: the channel blocks of one position range, and neighbouring ranges, share an L2
+    // XCD-contiguous order: the channel blocks of one share's positions meet in an L2
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total_wgs) return;
     const int cb = work % co_blocks, part = work / co_blocks;
-    const Range range = share.of(part);
-    const int64_t b0 = range.first, b1 = range.end;
+    const Buffers buffers = share.of(part);
+    const int64_t count = buffers.count;  // (64 bits: 32 measured 1 to 2 % slower in small launches)
 
     if (wave == 4) {
         // ---- producer wave: all global -> LDS copies of the workgroup.  It issues nothing else, so its
@@ -125,8 +125,8 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
             src_pos[k] = pos;
             src_off[k] = pos * ROW + s * 64 + q * 16;
         }
-        auto issue_buffer = [&](int64_t b, int slot) {
-            const int64_t p0 = b * PB;
+        auto issue_buffer = [&](int64_t b, int slot) {  // (b: of this workgroup's)
+            const int64_t p0 = buffers.at(b) * PB;
             const char* base = (const char*)x + p0 * ROW;
             char* dst = smem + slot * BUF;
             if (p0 + PB <= P) {
@@ -140,20 +140,20 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
         };
         // (the first kHeadBuffers buffers are copied by the consumer waves, see below)
         for (int i = kHeadBuffers; i < RING - 1; ++i)
-            if (b0 + i < b1) issue_buffer(b0 + i, i);
+            if (i < count) issue_buffer(i, i);
         int slot = 0;
-        for (int64_t b = b0; b < b1; ++b) {
+        for (int64_t b = 0; b < count; ++b) {
             asm volatile("" ::: "memory");
-            if (b - b0 >= kHeadBuffers) {
+            if (b >= kHeadBuffers) {
                 // buffer b has landed once no more copies are outstanding than were issued after it
-                const int64_t later = std::min<int64_t>(b1 - 1 - b, RING - 2);
+                const int64_t later = std::min<int64_t>(count - 1 - b, RING - 2);
                 if (later >= RING - 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm((RING - 2) * COPIES));
                 else if (later == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
                 else wait_tail<RING - 3, COPIES>(later);
             }
             __builtin_amdgcn_s_barrier();  // consumers may read buffer b; they are done with the slot refilled next
             asm volatile("" ::: "memory");
-            if (b + RING - 1 < b1) issue_buffer(b + RING - 1, (slot + RING - 1) % RING);
+            if (b + RING - 1 < count) issue_buffer(b + RING - 1, (slot + RING - 1) % RING);
             slot = slot + 1 == RING ? 0 : slot + 1;
         }
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -179,9 +179,9 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     // first kHeadBuffers buffers (every fourth copy instruction each), and wait for them together with
     // their weight fragments before the first barrier.
     for (int i = 0; i < kHeadBuffers; ++i) {
-        const int64_t bb = b0 + i;
-        if (bb >= b1) break;
-        const int64_t p0 = bb * PB;
+        const int64_t b = i;
+        if (b >= count) break;
+        const int64_t p0 = buffers.at(b) * PB;
         const char* base = (const char*)x + p0 * ROW;
         char* dst = smem + i * BUF;
 #pragma unroll
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     static_assert(NB == 1, "one block per wave and buffer");
     epi_by_form(ep, [&](auto form) {
         int slot = 0;
-        for (int64_t b = b0; b < b1; ++b) {
+        for (int64_t b = 0; b < count; ++b) {
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's reads of the previous buffer are complete
             __builtin_amdgcn_s_barrier();
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
                 }
 
             // ---- store: this lane's 4*MT consecutive channels of its position ----
-            const int64_t p = b * PB + 16 * wn + nn;
+            const int64_t p = buffers.at(b) * PB + 16 * wn + nn;
             if (p < P && co_lane < Co) {  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
                 TO* yp = y + p * ep.ldy + co_lane;
                 float v[4 * MT];
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
 
 // fp32, 32 to 256 channels: products on the bf16 matrix instruction, every value split into three parts (fp32_split.h).
 //
-// A workgroup owns 64 output channels and a contiguous range of buffers of 32 or 64 positions; each wave holds 16 channels' weights,
+// A workgroup owns 64 output channels and its share (share.h) of the buffers of 32 or 64 positions; each wave holds 16 channels' weights,
 // split once, in registers.  Per buffer all four waves split its activations into LDS (the next buffer's are on their way
 // meanwhile), each multiplies all positions, and the outputs go through LDS, so that they leave in rows of 256 bytes with
 // scale, bias and shortcut read the same way.  Chunks of 16 bytes in LDS are permuted by position, for reads without bank
@@ -295,11 +295,11 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // XCD-contiguous order: the channel blocks of one position range, and neighbouring ranges, share an L2
+    // XCD-contiguous order: the channel blocks of one share's positions meet in an L2
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total_wgs) return;
     const int cb = work % co_blocks, part = work / co_blocks;
-    const Range range = share.of(part);
+    const Buffers buffers = share.of(part);
 
     u32x4 raw[U][2];
     auto load_activations = [&](int b) {
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
             raw[u][1] = *(const u32x4*)(at + 64);
         }
     };
-    load_activations(range.first);
+    load_activations((int)buffers.at(0));
     // this wave's 16 channels, resident for the whole kernel
     Split8 a[KK];
     {
@@ -339,7 +339,8 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
     // matrix rows 4 qq .. 4 qq + 3 of this wave's tile are these channels of the block (pack_plan.h)
     char* o_lane = out + nn * 256 + ((((wave / MT) * (4 * MT) + MT * qq + wave % MT) ^ nn) * 16);
 
-    for (int b = range.first; b < range.end; ++b) {
+    for (int i = 0; i < buffers.count; ++i) {
+        const int b = (int)buffers.at(i);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int c = u * 256 + tid, q = c & 3, row = c >> 2;  // (step, position)
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
             *(u32x4*)(at + PLANE) = s.m;
             *(u32x4*)(at + 2 * PLANE) = s.l;
         }
-        if (b + 1 < range.end) load_activations(b + 1);
+        if (i + 1 < buffers.count) load_activations(b + buffers.step);
         const int64_t p0 = (int64_t)b * PB;
         EpiResidual<float, 4> shortcut[TN];
         if (ep.residual && co < Co)
