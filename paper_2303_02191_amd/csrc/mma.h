@@ -134,11 +134,4 @@ __device__ __forceinline__ void copy16_to_lds(const void* gsrc, char* lds_wave_b
                                      (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
 }
 
-// The same with 4 bytes per lane (LDS address lds_wave_base + 4 * i): sources that are only 4-byte aligned.
-__device__ __forceinline__ void copy4_to_lds(const void* gsrc, char* lds_wave_base)
-{
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gsrc,
-                                     (__attribute__((address_space(3))) void*)lds_wave_base, 4, 0, 0);
-}
-
 }  // namespace rtoss

@@ -52,8 +52,8 @@ constexpr int kOneWave = 64;  // patterns from which on the per-pattern tables t
 // The dictionary of a launch, by size.  (A launch with few layers and patterns writes 0.6 KB of arguments instead of 3.7, which takes
 // the host 1.3 us less.)
 struct SmallDict {
-    uint16_t mask[kOneWave];
-    int P, k;
+    uint16_t mask[kOneWave];  // (entries past the last pattern: 0)
+    int k;
 };
 
 // Input channel (within a 32-channel stage) that pair g of lane-quarter q refers to in sparse step `half`.
@@ -490,7 +490,6 @@ template <typename T> rtoss_status launch_entries(const PackTable<kPackMax>& tab
     if (dict.P >= kOneWave) return launch_table<T>(tab, dict, blocks, s);
     SmallDict d{};
     std::copy(dict.mask, dict.mask + dict.P, d.mask);
-    d.P = dict.P;
     d.k = dict.k;
     if (m > kPackFew) return launch_table<T>(tab, d, blocks, s);
     PackTable<kPackFew> few;

@@ -14,7 +14,7 @@ struct LiveJob {
     void* live;         // [G][k] values
     uint8_t* live_idx;  // [G]
     int64_t G;
-    int blocks;         // ceil(G / 256)
+    int blocks;         // workgroups: of 256 groups each, or of as many runs of 256 as the caller has them do
 };
 
 inline LiveJob make_live_job(void* live, uint8_t* live_idx, int64_t G)
