@@ -32,7 +32,8 @@
  *     same number k of set bits (one k per call: the paper's 2EP/3EP/4EP/5EP variants are
  *     separate dictionaries, Table 3), 1 <= P <= 255.
  *   - Determinism: identical calls give bit-identical outputs (no atomics are used in any
- *     accumulation).  The order in which an output's fp32 products are added belongs to the
+ *     accumulation).  The order in which an output's fp32 products are added, and whether
+ *     an output stage's scale and bias round once (fused) or twice, belong to the
  *     kernel that a call is sent to, and that choice depends on the whole shape, the batch
  *     size included, and on the device's number of compute units: an image's result may
  *     differ in its last fp32 bits between two batch sizes.  It does not depend on out_dt.

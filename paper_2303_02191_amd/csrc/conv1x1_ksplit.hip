@@ -210,6 +210,8 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, int plan, c
 //    128 ->  64 (6400)      4.0   4.2     128 -> 256 (1600)    4.0   4.2          128 ->  64 (12 769)    5.4  5.2  stays
 //    128 -> 256 (3192)      5.5   5.2 stays
 //    256 ->  64 (3192)      4.0   5.1     256 -> 256 (812)     4.0   5.1          256 ->  64 (6400)      5.8  5.4  stays
+//     64 ->  16 (12 800)    3.6   3.6      64 ->  48 (25 600)  5.4   4.9  stays   128 ->  16 (25 600)    7.0  6.4  stays
+//    128 ->  48 (12 800)    5.1   4.9 stays   256 -> 48 (6400) 5.5   5.1  stays   256 ->  32 (12 800)    5.5  6.7  stays: the smaller error
 //    512 ->  32 (6400)      6.1   9.3     512 -> 256 (400)     4.0   6.2
 int ksplit1x1_plan(const rtoss_wdesc& d, const ConvParams& c)
 {

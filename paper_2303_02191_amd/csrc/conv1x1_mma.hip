@@ -1,7 +1,7 @@
 // 1x1 pattern-pruned convolution on the CDNA4 matrix cores (fp16 / bf16 / fp32, fp32 accumulate):
-// the general kernel, for any channel counts whose
-// input rows are a multiple of 4 bytes.  (64-byte multiples of 2^n stages with whole channel tiles
-// take the streaming kernel with register-resident weights instead.)
+// the general kernels, for any channel counts whose input rows are a multiple of 4 bytes: a ring of LDS buffers for large
+// launches of whole stages and channel tiles, and whole output rows for everything else (second half of this comment).
+// (64-byte multiples of 2^n stages with whole channel tiles take conv1x1_stream.hip and conv1x1_ksplit.hip instead.)
 //
 // Section IV.D prunes a 1x1 layer by cutting the flattened [Co][Ci] weight matrix into groups
 // of 9 and keeping k weights per group, so the pruned layer is a GEMM
@@ -10,7 +10,7 @@
 // structure a matrix instruction could skip (groups straddle rows and have no 2-of-4 shape),
 // and the layer is bound by HBM traffic anyway: activations in, activations out, every byte
 // once.  So the weights are expanded to zero-filled dense fragments (they are tiny and stay in
-// L2), and the kernel is built to stream activations: channels-last rows are contiguous, a
+// L2), and the ring is built to stream activations: channels-last rows are contiguous, a
 // workgroup owns 128 consecutive positions x up to 128 output channels, and K runs over stages
 // of 64 bytes of input channels through a 5-deep ring of LDS buffers filled by global -> LDS copies
 // four stages ahead (an HBM-bound kernel lives on bytes in flight: two resident workgroups per CU x

@@ -273,10 +273,10 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
 // meanwhile), each multiplies all positions, and the outputs go through LDS, so that they leave in rows of 256 bytes with
 // scale, bias and shortcut read the same way.  Chunks of 16 bytes in LDS are permuted by position, for reads without bank
 // conflicts.
-// What bounds it: large launches of few channels the memory (64 -> 128 on 102 400 positions 17.5 us for 79 MB, 4.5 TB/s;
+// What bounds it: large launches of few channels the memory (64 -> 128 on 102 400 positions 18.3 us for 79 MB, 4.3 TB/s;
 // 29 on the fp32 instruction), deeper ones the matrix and the splitting instructions together, which the waves of a compute unit,
 // started at once, do at the same time rather than in turn (128 -> 128 on 25 600 positions: 28 % of the cycles matrix, 55 %
-// vector): 11.8 us, before 14.5; 256 -> 256 on 25 600: 26.5 us, before 33.  Buffers of 64 positions, which halve the
+// vector): 9.6 us, on the fp32 instruction 14.5; 256 -> 256 on 25 600: 23.8 us, 33 there.  Buffers of 64 positions, which halve the
 // splitting of weights, leave two workgroups on a compute unit instead of four: no faster at 128 channels, slower at 64.
 constexpr int f32_positions(int KS) { return KS == 2 ? 64 : 32; }
 

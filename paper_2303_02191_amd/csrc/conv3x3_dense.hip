@@ -280,6 +280,9 @@ inline int64_t f32_groups(const rtoss_wdesc& d, const ConvParams& c, int rows)
 //      64 ->  64 2x60x70 (300)  11.9  9.6  9.7          256 -> 256 4x80x80 (3200)   274   164   141   135
 //     ragged: 40 -> 72 2x40x60 (320) 8.8 9.9 9.9; 80 -> 80 1x100x120 (800) 25.6 22.4 18.4; 48 -> 72 4x77x91 (1872) 33.1 29.8 24.0
 //     stride 2, two rows (four would leave one workgroup per compute unit): 64 -> 128 2x80x100 13.5 10.6, 32 -> 64 4x112x140 15.4 10.7
+// Layers of up to 16 input channels, half of whose stage is zeros, would be faster on the small tile in launches of up to three
+// workgroups per compute unit (16 -> 16 4x56x56 6.7 us, 5.2 there; 16 -> 64 2x126x83 8.8 and 7.5; stride 2 16 -> 16 1x320x320 11.3 and 10.4), with the
+// fp32 instruction's larger error: not taken.
 // Sums of few live products stay on the fp32 instruction, for their precision (8 -> 72 4x77x91, k = 2: 14.7 us, split 13.9; stride 2 8.5, 7.0).
 int f32_rows(const rtoss_wdesc& d, const ConvParams& c, int64_t cus)
 {

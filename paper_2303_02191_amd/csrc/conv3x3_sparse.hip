@@ -59,11 +59,11 @@ namespace {
 constexpr int kPatch = 81 * 64;
 constexpr int patch_copies(int TN) { return (TN * kPatch + 1023) / 1024; }
 
-// Single-buffered variant: one LDS buffer, two barriers per stage, plain loop nest scheduled by the
-// compiler.  It needs half the LDS of the pipelined kernel below and few registers, so several
-// workgroups share a compute unit and hide each other's copy latency and epilogue.  Used for stride 2
-// (whose activation tile is too large to keep twice in LDS) and for layers too small for the
-// pipelined kernel's 128-channel, 8-stage appetite: TM = 4 covers 64 output channels per workgroup.
+// Single-buffered kernel: one LDS buffer, two barriers per stage, plain loop nest scheduled by the
+// compiler.  It needs half the LDS of the pipelined kernel (conv3x3_rows.hip) and few registers, so several
+// workgroups share a compute unit and hide each other's copy latency and epilogue.  Used for stride 2, for ragged channel
+// counts and for layers too shallow or narrow for the pipelined kernel's 128-channel, 8-stage appetite: TM = 4 covers 64
+// output channels per workgroup.
 // LAY: tap layout (sparse_frag.h).  Layout 1 (4-entry dictionaries) has three tap groups and no dense centre
 // step; it always takes the one-group-at-a-time schedule.
 // DB: two LDS buffers; the copies of the next stage are issued right after the barrier that opens a stage and land

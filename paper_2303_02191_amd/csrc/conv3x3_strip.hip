@@ -166,7 +166,8 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
             // reads, only for all it has asked for: 26 of the stage's 35 stood in front of the first product.  With two buffers a
             // phase's operands are asked for in front of the products of the phase before, so the first product waits for 7.
             // (256 -> 256 on 1x50x84 10.5 -> 10.0 us, 512 -> 512 on 2x40x40 18.1 -> 16.9; TN = 3, whose two workgroups per compute
-            // unit cover each other, 19.7 -> 19.3 on 4x50x84.  Layout 1 and one buffer gained nothing from it.)
+            // unit cover each other, gains less: 4x50x84 18.1 -> 17.6, 1x100x168 19.4 -> 18.9, 512 -> 256 on 1x100x160 30.8 -> 29.6.
+            // Layout 1 and one buffer gained nothing from it.)
             constexpr int PHASES = NG + LY.centre;
             u32x4 a[2][kTM][2];
             int idx[2][kTM];
@@ -501,7 +502,7 @@ rtoss_status launch_layout(const rtoss_wdesc& d, const ConvParams& c, int plan, 
 // once / twice: TN = 2 0.88 / 1.45 us, 3 1.12 / 1.85, 4 1.6 / 3.1, plus 3 us.  So: the smallest TN whose workgroups fit
 // one round.  (bf16, layout 0, batch x channels @ image: 1x256@100x168 18.0 us with TN = 3, 23.2 with the single-buffered
 // kernel; 4x128@60x70 8.0 and 9.6; 16x128@40x40 9.2 and 10.3; 4x64@112x130 7.3 and 8.0.  Layout 1: 2x256@100x168 33.6 and
-// 40.3.  Dense mode: 36.3 and 49.0.)
+// 40.3.  Dense mode: below.)
 static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int layout);
 
 int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)

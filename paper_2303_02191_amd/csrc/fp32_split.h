@@ -23,7 +23,9 @@
 // (At two to four live products the largest error of eight is 2.3 where the fp32 instruction's is 1.9, with the smaller 2-norm: the
 // sum of h*h and the last addition round once each.)
 // An infinite value has h = itself and NaN for m and l: the sum of h*h alone is then the result (split_sum).  Limits: a signalling
-// NaN whose payload lies in its low 16 bits has an infinite h; l of a value below 2^-110 is subnormal or lost.
+// NaN whose payload lies in its low 16 bits has an infinite h (quieting every value first: 3x3 64 -> 64 on 80x80 7.2 -> 7.5 us, 96 -> 96
+// on 2x80x100 25.5 -> 26.9, 256 -> 256 on 4x80x80 130.9 -> 133.9; activations are finite by contract); l of a value below 2^-110 is
+// subnormal or lost.
 #pragma once
 #include "common.h"
 #include "dtypes.h"
