@@ -19,7 +19,6 @@
 // for weights and indices, 1800 for its part of the public section and 3300 for the fragments.
 #include <algorithm>
 #include <type_traits>
-#include <vector>
 
 #include "common.h"
 #include "dtypes.h"
@@ -503,22 +502,19 @@ template <typename T> rtoss_status launch_entries(const PackTable<kPackMax>& tab
 rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, const Dict& dict, hipStream_t s)
 {
     const int layout = std::max(0, dict.layout);
-    // 3x3 layers first: their workgroups take longest
-    std::vector<int> order((size_t)n);
-    int at = 0;
-    for (const int ksize : {3, 1})
-        for (int i = 0; i < n; ++i)
-            if (items[i].d.ksize == ksize) order[at++] = i;
+    // 3x3 layers first: their workgroups take longest.  (Two walks over the layers instead of a sorted list: nothing here allocates,
+    // so that nothing can throw through the C interface.)
     for (int dt : {(int)RTOSS_F32, (int)RTOSS_F16, (int)RTOSS_BF16})
-        for (int i = 0; i < n;) {  // i runs on across launches
+        for (int64_t i = 0; i < 2 * (int64_t)n;) {  // i runs on across launches
             PackTable<kPackMax> tab;
             int m = 0;
             int64_t total = 0;
-            for (; i < n && m < kPackMax; ++i) {
-                const PackItem& it = items[order[i]];
-                if ((int)it.d.dt != dt) continue;
+            for (; i < 2 * (int64_t)n && m < kPackMax; ++i) {
+                const int l = (int)(i < n ? i : i - n);
+                const PackItem& it = items[l];
+                if ((int)it.d.dt != dt || it.d.ksize != (i < n ? 3 : 1)) continue;
                 int64_t blocks = 0;
-                if (rtoss_status st = make_entry(it, geo[order[i]], layout, &tab.e[m], &blocks)) return st;
+                if (rtoss_status st = make_entry(it, geo[l], layout, &tab.e[m], &blocks)) return st;
                 if (blocks == 0) continue;
                 if (total + blocks > kMaxGridGroups) break;  // (one layer fits: make_entry)
                 tab.first_block[m++] = (int)total;

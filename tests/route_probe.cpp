@@ -1,19 +1,33 @@
 // Which kernel a convolution call launches, without a GPU: librtoss.so linked against stand-ins for the few runtime calls it
 // makes, on a device of 256 compute units.  Reads calls, one a line,
 //     coherent Co Ci ksize k rule dt  N H W stride out_dt  fused
+// (dt + 16: packs the layer instead, with every allocation refused)
 // and prints the status, the launched kernel's handle (its offset in the library), the dynamic LDS it was launched with and the
 // limit that was set for it.
 #include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
+#include <cstdlib>
 #include <map>
+#include <new>
 
 #include "rtoss.h"
 
 static const void* g_kernel;
 static size_t g_lds;
 static std::map<const void*, int> g_limit;
+
+// the library's allocations come here too
+static bool g_refuse;
+void* operator new(size_t n)
+{
+    void* p = g_refuse ? nullptr : std::malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 extern "C" {
 hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
@@ -34,7 +48,7 @@ int main()
     int coherent, rule, dt, out_dt, fused;
     while (scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d", &coherent, &d.Co, &d.Ci, &d.ksize, &d.k, &rule, &dt, &c.N, &c.H, &c.W, &c.stride,
                  &out_dt, &fused) == 13) {
-        d.dt = (rtoss_dtype)dt;
+        d.dt = (rtoss_dtype)(dt & 15);
         c.out_dt = (rtoss_dtype)out_dt;
         c.pad = d.ksize / 2;
         c.layout = RTOSS_NHWC;
@@ -50,9 +64,12 @@ int main()
         e.y_ld = e.residual_ld = (d.Co + 7) / 8 * 8 + 16;  // a channel slice
         g_kernel = nullptr;
         g_lds = 0;
-        const rtoss_status st = coherent ? rtoss_conv2d_pattern_coherent(&d, &c, fused ? &e : nullptr, masks, P, base, x, y, nullptr)
-                                : fused  ? rtoss_conv2d_pattern_fused(&d, &c, &e, masks, P, base, x, y, nullptr)
-                                         : rtoss_conv2d_pattern(&d, &c, masks, P, base, x, y, nullptr);
+        g_refuse = dt & 16;
+        const rtoss_status st = dt & 16    ? rtoss_pack(&d, x, (const uint8_t*)x, masks, P, base, (size_t)1 << 40, nullptr, 0, nullptr)
+                                : coherent ? rtoss_conv2d_pattern_coherent(&d, &c, fused ? &e : nullptr, masks, P, base, x, y, nullptr)
+                                : fused    ? rtoss_conv2d_pattern_fused(&d, &c, &e, masks, P, base, x, y, nullptr)
+                                           : rtoss_conv2d_pattern(&d, &c, masks, P, base, x, y, nullptr);
+        g_refuse = false;
         Dl_info info{};
         size_t at = 0;
         if (g_kernel && dladdr(g_kernel, &info)) at = (size_t)((const char*)g_kernel - (const char*)info.dli_fbase);

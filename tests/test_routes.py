@@ -56,6 +56,13 @@ def test_launches_stay_within_the_lds_they_declare():
     assert wrong == []
 
 
+def test_packing_allocates_nothing():
+    """... so that no exception can leave the C interface there (the probe refuses every allocation and ends at the first)."""
+    for dt in (wl.F32, wl.F16, wl.BF16):
+        calls = [call(dt + 16, 1, Ci, 48, 9, 19, ks, 1, 3, dt, False) for Ci, ks in ((64, 3), (3, 3), (64, 1), (40, 1))]
+        assert families(routes.kernels(calls)) == ["pack"] * len(calls)
+
+
 def families(kernels):
     return [k if isinstance(k, int) else k.split("<")[0] for k in kernels]
 
