@@ -15,15 +15,21 @@
 //     buffer holds PB positions (16 per wave along positions) x all Ci channels, laid out
 //     [32-channel stage][position][64 bytes] with the four 16-byte chunks of a position
 //     XOR-swizzled by (position / 2) % 4: conflict-free 16-byte operand reads without padding.
-//   * A fifth wave is the producer: it issues every copy (but for the first two buffers of a
-//     workgroup, which the consumers fetch while they would otherwise idle) and nothing else, so its count of
-//     outstanding memory operations counts copies only and "buffer b has landed" is an exact
-//     counted wait (the four consumer waves also store outputs, which would share the counter).
-//     One barrier per buffer hands a filled buffer to the consumers and a drained one back.
-//   * Output rows are stored straight from the accumulators.  The packer assigns output channels
-//     to matrix rows so that a lane's 4*MT accumulator values are consecutive channels: row
-//     4q+i of the wave's m-th fragment is channel 4*MT*q + 4*m + i of the wave's slice, and the
-//     four lane quarters of a position together write one contiguous run of 16*MT channels.
+//   * One or two helper waves move everything: they issue the copies (but for the first two buffers of a
+//     workgroup, which the consumers fetch while they would otherwise idle) and store the outputs.  Both are
+//     counted by the same counter in the order they were issued, and a turn issues a fixed number of each (lanes
+//     with nothing to store write past the end of a bounded buffer), so "buffer b has landed" is an exact counted wait.
+//     One barrier per buffer hands a filled buffer to the consumers, a drained one back, and an output tile over.
+//   * The packer assigns output channels to matrix rows so that a lane's 4*MT accumulator values are
+//     consecutive channels: row 4q+i of the wave's m-th fragment is channel 4*MT*q + 4*m + i of the wave's slice.  The
+//     consumers put them into a tile in LDS, from which the helpers store whole rows, past the L2's
+//     write-back: outputs of a few MB fit the L2s, and a launch that leaves them there ends with writing all of
+//     them back (copies of 13 MB: 6.1 us, past it 5.4).  In pieces of 16 bytes that would cost more than it saves.
+//     us with stores from the accumulators / with tiles / with tiles past the write-back: 64 -> 64 channels on 102 400
+//     positions with SiLU 8.0  8.2  6.6, 128 -> 128 on 102 400 12.3  12.6  11.1, 256 -> 256 on 25 600 11.0  11.0  9.6.
+//   * 512 channels: two or three buffers a workgroup and a wave to a SIMD, so that a turn is the sum of its parts.  The consumers
+//     put the output stage of a buffer between the matrix instructions of the next one instead, and store from there (rows of
+//     64 bytes; a tile would be a turn more): 512 -> 256 on 6400 positions with SiLU 7.0 -> 6.2 us, 512 -> 512 9.4 -> 7.9.
 //
 // fp32 tensors of 32 to 256 channels have a kernel of their own, on the bf16 matrix instruction (the second one here).  Those of
 // 16 and of 512 channels run through the first: a stage is then 16 channels (the same 64 bytes per position) and a fragment
@@ -50,6 +56,11 @@ namespace {
 constexpr int kFrag = 1024;  // one A fragment: 64 lanes x 16 bytes = 16 output channels x 32 input channels
 constexpr int kHeadBuffers = 2;  // buffers of a workgroup's range that the consumer waves copy themselves
 
+// Copies and stores cost a wave about 70 cycles each, a turn of the consumers 1000 to 2000: two helpers where one would be the slower side
+// (1024 -> 512 on 6400 positions 18.2 and 14.3 us, 256 -> 256 on 51 200 11.4 and 10.8), and at 16 copies a turn, whose
+// addresses would cost a workgroup per compute unit (128 -> 64 on 102 400: 9.0 and 8.5).
+constexpr int helper_waves(int KS, int WM) { return KS >= 8 || 4 / WM * KS >= 16 ? 2 : 1; }
+
 // Shape plan, a function of KS = Ci / 32 (fp32: Ci / 16; 1, 2, 4 ... 32) and of WM, the number of waves a
 // workgroup spreads over output channels (the other 4 / WM spread over positions).
 template <int KS, int WM> struct Plan {
@@ -68,23 +79,15 @@ template <int KS, int WM> struct Plan {
     // faster (0.900 vs 0.907 ms with four and 0.915 ms with up to six buffers): its 48 KB let three workgroups share a
     // compute unit, and their producers together keep more copies in flight than one deep ring can count.
     static constexpr int RING = 3;
+    static constexpr bool TILE = KS != 16;                         // outputs through LDS
+    static constexpr int HELPERS = helper_waves(KS, WM);
+    static constexpr int LANES = 64 * (4 + HELPERS);
     static_assert(COPIES >= 1 && COPIES * 16 == PB * KS, "a buffer is a whole number of copy instructions");
-    static_assert(RING >= 3 && (RING - 2) * COPIES < 64, "outstanding copies must fit the counter");
+    static_assert(RING == 3, "the waits below count two turns");
 };
 
 // s_waitcnt immediate that waits for the vector-memory counter only (6 bits, split 4 + 2)
 __device__ __host__ constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
-
-// wait until at most `later` buffers (1 .. MAXL) of COPIES copy instructions each are outstanding
-template <int MAXL, int COPIES> __device__ __forceinline__ void wait_tail(int64_t later)
-{
-    if constexpr (MAXL >= 1) {
-        if (later == MAXL) __builtin_amdgcn_s_waitcnt(vmcnt_imm(MAXL * COPIES));
-        else wait_tail<MAXL - 1, COPIES>(later);
-    } else {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    }
-}
 
 inline size_t frag_bytes(const rtoss_wdesc& d)
 {
@@ -93,7 +96,7 @@ inline size_t frag_bytes(const rtoss_wdesc& d)
 }
 
 template <typename T, typename TO, int KS, int WM>
-__global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y,
+__global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                              const char* __restrict__ wfrag, const char* __restrict__ zeros,
                                                              int64_t P, int Co, int co_blocks, Share share, int total_wgs,
                                                              int work_per_xcd, Epilogue ep)
@@ -112,51 +115,90 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     const Buffers buffers = share.of(part);
     const int64_t count = buffers.count;  // (64 bits: 32 measured 1 to 2 % slower in small launches)
 
-    if (wave == 4) {
-        // ---- producer wave: all global -> LDS copies of the workgroup.  It issues nothing else, so its
-        // memory counter counts copies only and "at most (RING-2) buffers outstanding" is exact. ----
-        int src_off[COPIES];  // byte offset from the buffer's first position of the chunk this lane fills
-        int src_pos[COPIES];
+    constexpr int EB = (int)sizeof(TO), SPAN = PL::SPAN;
+    constexpr bool TILE = PL::TILE;
+    constexpr int CPR = SPAN * EB / 16;                        // 16-byte chunks of a row of the output tile
+    constexpr int OUT = PB * SPAN * EB, STORES = OUT / 1024;   // bytes and store instructions of a tile
+    char* out = smem + RING * BUF + EpiScaleBias<SPAN>::kBytes;  // two output tiles
+    // (chunks permuted by row, for writes and reads without bank conflicts)
+    const auto chunk_at = [](int row, int c) { return row * CPR + (CPR >= 16 ? c ^ (row & 15) : c ^ ((row >> 1) & 7)); };
+    static_assert(CPR >= 8 && STORES >= 1 && STORES * 1024 == OUT, "whole store instructions");
+    // stores the tile of buffer b, one in `step` of its store instructions
+    auto flush = [&](int64_t b, int first, auto step) {
+        const char* tile = out + (b & 1) * OUT;
+        const int64_t p0 = buffers.at(b) * PB;
+        const auto base = store_base(y + p0 * ep.ldy + cb * SPAN);
+        const int rows = (int)std::min<int64_t>(P - p0, PB), cols = Co - cb * SPAN;
+        constexpr int STEP = decltype(step)::value, N = (STORES + STEP - 1) / STEP, AT_ONCE = N < 4 ? N : 4;
 #pragma unroll
-        for (int k = 0; k < COPIES; ++k) {
-            const int c = k * 64 + lane;
+        for (int i0 = 0; i0 < N; i0 += AT_ONCE) {
+            u32x4 v[AT_ONCE];
+            uint32_t at[AT_ONCE];
+#pragma unroll
+            for (int i = 0; i < AT_ONCE; ++i) {
+                const int store = first + (i0 + i) * STEP, k = store * 64 + lane, r = k / CPR, c = k % CPR;
+                const bool whole = STORES % STEP == 0 || store < STORES;
+                v[i] = *(const u32x4*)(tile + (whole ? chunk_at(r, c) * 16 : 0));
+                at[i] = whole && r < rows && c * (16 / EB) < cols ? (uint32_t)r * ep.ldy * EB + c * 16 : kNoStore;
+            }
+#pragma unroll
+            for (int i = 0; i < AT_ONCE; ++i) store16_through(base, at[i], v[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if (wave >= 4) {
+        constexpr int H = PL::HELPERS, MINE = COPIES / H, FLUSH = STORES / H;
+        static_assert(COPIES % H == 0 && STORES % H == 0, "helpers share the work");
+        const int helper = wave - 4;
+        // ---- helper waves: every H-th copy and store of the workgroup ----
+        int src_off[MINE];  // byte offset from the buffer's first position of the chunk this lane fills
+#pragma unroll
+        for (int k = 0; k < MINE; ++k) {
+            const int c = (k * H + helper) * 64 + lane;
             const int s = c / (PB * 4), rem = c % (PB * 4);
             const int pos = rem >> 2, q = (rem & 3) ^ ((pos >> 1) & 3);
-            src_pos[k] = pos;
             src_off[k] = pos * ROW + s * 64 + q * 16;
         }
         auto issue_buffer = [&](int64_t b, int slot) {  // (b: of this workgroup's)
             const int64_t p0 = buffers.at(b) * PB;
             const char* base = (const char*)x + p0 * ROW;
-            char* dst = smem + slot * BUF;
+            char* dst = smem + slot * BUF + helper * 1024;
             if (p0 + PB <= P) {
 #pragma unroll
-                for (int k = 0; k < COPIES; ++k) copy16_to_lds(base + src_off[k], dst + k * 1024);
+                for (int k = 0; k < MINE; ++k) copy16_to_lds(base + src_off[k], dst + k * H * 1024);
             } else {  // ragged last buffer: positions past the end read the packer's block of zeros
+                const int left = (int)(P - p0) * ROW;
 #pragma unroll
-                for (int k = 0; k < COPIES; ++k)
-                    copy16_to_lds(p0 + src_pos[k] < P ? base + src_off[k] : zeros, dst + k * 1024);
+                for (int k = 0; k < MINE; ++k) copy16_to_lds(src_off[k] < left ? base + src_off[k] : zeros, dst + k * H * 1024);
             }
         };
         // (the first kHeadBuffers buffers are copied by the consumer waves, see below)
-        for (int i = kHeadBuffers; i < RING - 1; ++i)
-            if (i < count) issue_buffer(i, i);
+        static_assert(kHeadBuffers == RING - 1, "the helpers' first copies are of the first turn");
         int slot = 0;
         for (int64_t b = 0; b < count; ++b) {
             asm volatile("" ::: "memory");
-            if (b >= kHeadBuffers) {
-                // buffer b has landed once no more copies are outstanding than were issued after it
-                const int64_t later = std::min<int64_t>(count - 1 - b, RING - 2);
-                if (later >= RING - 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm((RING - 2) * COPIES));
-                else if (later == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-                else wait_tail<RING - 3, COPIES>(later);
+            if (!TILE && b >= kHeadBuffers) {
+                if (b + 1 < count) __builtin_amdgcn_s_waitcnt(vmcnt_imm(MINE));
+                else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            } else if (b >= kHeadBuffers) {
+                // buffer b has landed once no more is outstanding than was issued after its copies, two turns ago: the stores of
+                // two turns (the first turn has none) and the copies of one (none at last)
+                const bool first = b < 3, last = b + 1 == count;
+                if (!first && !last) __builtin_amdgcn_s_waitcnt(vmcnt_imm(std::min(63, 2 * FLUSH + MINE)));
+                else if (!first) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * FLUSH));
+                else if (!last) __builtin_amdgcn_s_waitcnt(vmcnt_imm(std::min(63, FLUSH + MINE)));
+                else __builtin_amdgcn_s_waitcnt(vmcnt_imm(FLUSH));
             }
             __builtin_amdgcn_s_barrier();  // consumers may read buffer b; they are done with the slot refilled next
             asm volatile("" ::: "memory");
             if (b + RING - 1 < count) issue_buffer(b + RING - 1, (slot + RING - 1) % RING);
+            if (TILE && b) flush(b - 1, helper, std::integral_constant<int, H>{});
             slot = slot + 1 == RING ? 0 : slot + 1;
         }
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        if constexpr (TILE) {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();  // the last output tile is complete (the consumers store it)
+        }
         return;
     }
 
@@ -174,8 +216,8 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
 #pragma unroll
             for (int s = 0; s < KS; ++s) a[m][s] = *(const u32x4*)(af + (m * KS + s) * kFrag);
     }
-    // Start-up: one wave needs about 70 cycles per copy instruction, so a producer that fills the ring alone
-    // delivers the first buffer late.  The four consumer waves, idle until then, issue the copies of the
+    // Start-up: one wave needs about 70 cycles per copy instruction, so helpers that fill the ring alone
+    // deliver the first buffer late.  The four consumer waves, idle until then, issue the copies of the
     // first kHeadBuffers buffers (every fourth copy instruction each), and wait for them together with
     // their weight fragments before the first barrier.
     for (int i = 0; i < kHeadBuffers; ++i) {
@@ -204,8 +246,102 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
     const int x_lane = (wn * 16 + nn) * 64 + ((qq ^ ((nn >> 1) & 3)) * 16);
     const int co_lane = cb * PL::SPAN + wm * (16 * MT) + 4 * MT * qq;  // first of this lane's 4*MT channels
     const int co_local = wm * (16 * MT) + 4 * MT * qq;
-    constexpr int EB = (int)sizeof(TO);
 
+    if constexpr (!TILE) {
+        // ---- each buffer's output stage between the matrix instructions of the next ----
+        constexpr int RUN = 4 * MT;
+        const int row = 16 * wn + nn;
+        int slot = 0;
+        auto next_buffer = [&] {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's reads of the previous buffer are complete
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+        auto multiply = [&](f32x4 (&acc)[MT]) {
+            const char* X = smem + slot * BUF + x_lane;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const u32x4 bv = *(const u32x4*)(X + s * PB * 64);
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[m] = Dense16<T>::mma(a[m][s], bv, acc[m]);
+            }
+            slot = slot + 1 == RING ? 0 : slot + 1;
+        };
+        auto values = [&](float (&u)[RUN], const f32x4 (&acc)[MT]) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) u[4 * m + e] = acc[m][e];
+        };
+        auto finish = [&](float (&v)[RUN], int64_t b) {
+            const int64_t p = buffers.at(b) * PB + row;
+            const bool live = p < P && co_lane < Co;  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
+            if (ep.residual && live) epi_residual<TO, RUN>(v, ep, p, co_lane);
+            const auto base = store_base(y + buffers.at(b) * PB * ep.ldy);
+            const uint32_t at = live ? ((uint32_t)row * ep.ldy + co_lane) * EB : kNoStore;
+#pragma unroll
+            for (int g = 0; g < RUN * EB / 16; ++g) {
+                u32x4 o;
+                if constexpr (EB == 4) {
+                    o = __builtin_bit_cast(u32x4, f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]});
+                } else {
+                    o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
+                    o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
+                    o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
+                    o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
+                }
+                store16_through(base, at + 16 * g, o);
+            }
+        };
+        epi_by_form(ep, [&](auto form) {
+            constexpr int FORM = decltype(form)::value;
+            f32x4 held[MT];
+            next_buffer();
+            multiply(held);
+            for (int64_t b = 1; b < count; ++b) {
+                next_buffer();
+                float v[RUN];
+                f32x4 acc[MT];
+                if constexpr (FORM == kEpiSilu) {
+                    const char* X = smem + slot * BUF + x_lane;
+                    u32x4 bv[KS];
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) bv[s] = *(const u32x4*)(X + s * PB * 64);
+                    float u[RUN], e[RUN], top = 0.f;
+                    values(u, held);
+                    epi_scale_bias_of<FORM, RUN>(u, ep, lds_ep + co_local, lds_ep + SPAN + co_local);
+                    __builtin_amdgcn_sched_barrier(0);
+                    static_for<MT * KS>([&](auto step) {
+                        constexpr int i = decltype(step)::value, SLOTS = RUN + 2;
+                        constexpr int s = i / MT, m = i % MT;
+                        acc[m] = Dense16<T>::mma(a[m][s], bv[s], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[m]);
+                        static_for<(i + 1) * SLOTS / (MT * KS) - i * SLOTS / (MT * KS)>([&](auto part) {
+                            epi_silu_part<i * SLOTS / (MT * KS) + decltype(part)::value, RUN>(u, v, e, top);
+                        });
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                    slot = slot + 1 == RING ? 0 : slot + 1;
+                    epi_silu_end<RUN>(u, v, top);
+                } else {
+                    values(v, held);
+                    epi_scale_bias_of<FORM, RUN>(v, ep, lds_ep + co_local, lds_ep + SPAN + co_local);
+                    multiply(acc);
+                    if constexpr (FORM == kEpiAny) epi_act<RUN>(v, ep.act);
+                }
+                finish(v, b - 1);
+#pragma unroll
+                for (int m = 0; m < MT; ++m) held[m] = acc[m];
+            }
+            float v[RUN];
+            values(v, held);
+            epi_scale_bias_act_of<FORM, RUN>(v, ep, lds_ep + co_local, lds_ep + SPAN + co_local);
+            finish(v, count - 1);
+        });
+        return;
+    }
     static_assert(NB == 1, "one block per wave and buffer");
     epi_by_form(ep, [&](auto form) {
         int slot = 0;
@@ -221,49 +357,61 @@ __global__ __launch_bounds__(320) void conv1x1_stream_kernel(const T* __restrict
             for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int j = 0; j < NB; ++j) acc[m][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // (deep layers: eight reads in flight, where the scheduler would have two.  1024 -> 512 on 6400 positions 14.4 -> 11.9 us;
+            // shallower ones have other workgroups to fill in)
+            constexpr int AHEAD = KS < 8 ? KS : 8;
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
+            for (int s0 = 0; s0 < KS; s0 += AHEAD) {
+                u32x4 bv[AHEAD];
 #pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    const u32x4 bv = *(const u32x4*)(X + (s * PB + 16 * WN * j) * 64);
+                for (int s = 0; s < AHEAD; ++s) bv[s] = *(const u32x4*)(X + (s0 + s) * PB * 64);
+                if constexpr (KS >= 8) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int m = 0; m < MT; ++m) acc[m][j] = Dense16<T>::mma(a[m][s], bv, acc[m][j]);
-                }
+                for (int s = 0; s < AHEAD; ++s)
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) acc[m][0] = Dense16<T>::mma(a[m][s0 + s], bv[s], acc[m][0]);
+            }
 
-            // ---- store: this lane's 4*MT consecutive channels of its position ----
-            const int64_t p = buffers.at(b) * PB + 16 * wn + nn;
-            if (p < P && co_lane < Co) {  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
-                TO* yp = y + p * ep.ldy + co_lane;
-                float v[4 * MT];
+            float v[4 * MT];
 #pragma unroll
-                for (int m = 0; m < MT; ++m)
+            for (int m = 0; m < MT; ++m)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][0][e];
-                epi_scale_bias_act_of<decltype(form)::value, 4 * MT>(v, ep, lds_ep + co_local, lds_ep + PL::SPAN + co_local);
-                epi_residual<TO, 4 * MT>(v, ep, p, co_lane);
-                if constexpr (EB == 4) {
+                for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][0][e];
+            epi_scale_bias_act_of<decltype(form)::value, 4 * MT>(v, ep, lds_ep + co_local, lds_ep + SPAN + co_local);
+            const int row = 16 * wn + nn;
+            if (ep.residual) {
+                const int64_t p = buffers.at(b) * PB + row;
+                if (p < P && co_lane < Co) epi_residual<TO, 4 * MT>(v, ep, p, co_lane);
+            }
+            char* tile = out + (b & 1) * OUT;
+            if constexpr (EB == 4) {
 #pragma unroll
-                    for (int g = 0; g < MT; ++g) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
-                } else if constexpr (MT == 1) {
-                    uint2 o;
-                    o.x = pack2_from_f32<TO>(v[0], v[1]);
-                    o.y = pack2_from_f32<TO>(v[2], v[3]);
-                    *(uint2*)yp = o;
-                } else {
+                for (int g = 0; g < MT; ++g)
+                    *(f32x4*)(tile + chunk_at(row, co_local / 4 + g) * 16) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+            } else if constexpr (MT == 1) {
+                uint2 o;
+                o.x = pack2_from_f32<TO>(v[0], v[1]);
+                o.y = pack2_from_f32<TO>(v[2], v[3]);
+                *(uint2*)(tile + chunk_at(row, co_local / 8) * 16 + (co_local & 4) * 2) = o;
+            } else {
 #pragma unroll
-                    for (int g = 0; g < MT / 2; ++g) {
-                        u32x4 o;
-                        o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
-                        o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
-                        o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
-                        o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
-                        *(u32x4*)(yp + 8 * g) = o;
-                    }
+                for (int g = 0; g < MT / 2; ++g) {
+                    u32x4 o;
+                    o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
+                    o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
+                    o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
+                    o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
+                    *(u32x4*)(tile + chunk_at(row, co_local / 8 + g) * 16) = o;
                 }
             }
             slot = slot + 1 == RING ? 0 : slot + 1;
         }
     });
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_s_barrier();  // the last output tile is complete
+    asm volatile("" ::: "memory");
+    flush(count - 1, wave, std::integral_constant<int, 4>{});
 }
 
 // fp32, 32 to 256 channels: products on the bf16 matrix instruction, every value split into three parts (fp32_split.h).
@@ -382,6 +530,7 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
         for (int j = 0; j < TN; ++j) *(f32x4*)(o_lane + 16 * j * 256) = split_sum(main[j], small[j]);
         __syncthreads();
         if (co >= Co) continue;
+        const auto base = store_base(y + p0 * ep.ldy);
         float v[4 * TN];
 #pragma unroll
         for (int i = 0; i < TN; ++i) {
@@ -398,7 +547,7 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
             if (p >= P) break;
             float o[4] = {v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
             if (ep.residual) shortcut[i].add(o);
-            *(f32x4*)(y + p * ep.ldy + co) = f32x4{o[0], o[1], o[2], o[3]};
+            store16_through(base, ((uint32_t)(16 * i + (tid >> 4)) * ep.ldy + co) * 4, __builtin_bit_cast(u32x4, f32x4{o[0], o[1], o[2], o[3]}));
         }
     }
 }
@@ -435,7 +584,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const int64_t P = (int64_t)c.N * c.H * c.W;
     const int64_t nbuf = (P + PL::PB - 1) / PL::PB;
     const int co_blocks = stream_co_blocks_of(KS, d.Co);
-    const size_t smem = (size_t)PL::RING * PL::BUF + EpiScaleBias<PL::SPAN>::kBytes;
+    const size_t smem = (size_t)PL::RING * PL::BUF + EpiScaleBias<PL::SPAN>::kBytes + (PL::TILE ? 2 * PL::PB * PL::SPAN * sizeof(TO) : 0);
     auto kern = conv1x1_stream_kernel<T, TO, KS, WM>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv1x1 shared memory attribute")) return st;
@@ -448,7 +597,14 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     static std::atomic<int> per_cu_cached{0};  // per instantiation
     int per_cu = per_cu_cached.load(std::memory_order_relaxed);
     if (per_cu == 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, 320, smem) != hipSuccess || per_cu < 1) per_cu = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, PL::LANES, smem) != hipSuccess || per_cu < 1) per_cu = 1;
+        // The dispatcher spreads a workgroup's waves over the four SIMDs but does not fill every hole: of `waves` that fit a SIMD,
+        // workgroups of five were resident at two per compute unit for four, three for five and four for six, one less
+        // than the query says.  Workgroups beyond that are a second round of a launch planned for one
+        // (128 -> 128 on 102 400 positions: 13.5 us with 768 of which 512 fit, 12.3 with 512).
+        int waves = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&waves, (const void*)kern, 256, 0) == hipSuccess)
+            per_cu = std::max(1, std::min(per_cu, (4 * waves - 4 + PL::HELPERS) / (4 + PL::HELPERS)));
         per_cu_cached.store(per_cu, std::memory_order_relaxed);
     }
     const DeviceInfo& dev = c.dev;
@@ -459,7 +615,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const int total = wgs_per_cb * co_blocks;
     const int work_per_xcd = (total + 7) / 8;
     if (P * d.Ci * (int)sizeof(T) / PL::PB > 0x7fffffffffffll || nbuf > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv1x1: too many positions");
-    dim3 grid((unsigned)(work_per_xcd * 8)), block(320);
+    dim3 grid((unsigned)(work_per_xcd * 8)), block(PL::LANES);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Co, co_blocks,
                                    Share(nbuf, wgs_per_cb), total, work_per_xcd, c.ep);
     return check_hip(hipGetLastError(), "conv1x1 stream launch");
@@ -507,6 +663,9 @@ bool stream1x1_shape_ok(const rtoss_wdesc& d)
 }
 
 size_t stream1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_section_bytes(stage_count(d)); }
+
+// The kernels' stores are 32-bit offsets from the first position of a buffer (of at most 64).
+bool stream1x1_launch_ok(const ConvParams& c) { return (int64_t)c.ep.ldy * 64 * elem_bytes(c.out_dt) < kNoStore; }
 
 rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                    hipStream_t s)

@@ -56,6 +56,31 @@ template <int N> __device__ __forceinline__ void epi_silu(float (&v)[N])
         v[i] = __builtin_fmaf(-__builtin_fmaf(d, q, -v[i]), r, q);
     }
 }
+// The same in N + 2 parts without a branch, for kernels that put matrix instructions between them, and an end: part J takes value
+// J's exponential, the reciprocal of the value before and the quotient of the one before that; the end divides where that
+// does not hold.
+template <int J, int N>
+__device__ __forceinline__ void epi_silu_part(const float (&u)[N], float (&v)[N], float (&d)[N], float& top)
+{
+    if constexpr (J < N) {
+        top = __builtin_fmaxf(top, __builtin_fabsf(u[J]));
+        d[J] = 1.f + __expf(-u[J]);
+    }
+    if constexpr (J >= 1 && J - 1 < N) v[J - 1] = __builtin_amdgcn_rcpf(d[J - 1]);
+    if constexpr (J >= 2) {
+        const float r = v[J - 2], q = u[J - 2] * r;
+        v[J - 2] = __builtin_fmaf(-__builtin_fmaf(d[J - 2], q, -u[J - 2]), r, q);
+    }
+}
+template <int N> __device__ __forceinline__ void epi_silu_end(const float (&u)[N], float (&v)[N], float top)
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));  // keeps the parts in front of the branch
+    if (__builtin_expect(__ballot(top > 80.f) != 0, 0)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = u[i] / (1.f + __expf(-u[i]));
+    }
+}
 // (one uniform branch per activation around the whole run, not one per value)
 template <int N> __device__ __forceinline__ void epi_act(float (&v)[N], int act)
 {
@@ -122,6 +147,36 @@ __device__ __forceinline__ void epi_scale_bias_act_of(float (&v)[N], const Epilo
         epi_silu<N>(v);
     } else if constexpr (FORM == kEpiAny) {
         epi_scale_bias_act<N>(v, ep, scale, bias);
+    }
+}
+
+template <int FORM, int N>
+__device__ __forceinline__ void epi_scale_bias_of(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
+{
+    if constexpr (FORM == kEpiSilu) {
+#pragma unroll
+        for (int g = 0; g < N / 4; ++g) {
+            const f32x4 s = *(const f32x4*)(scale + 4 * g), b = *(const f32x4*)(bias + 4 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[4 * g + i] = __builtin_fmaf(v[4 * g + i], s[i], b[i]);
+        }
+    } else if constexpr (FORM == kEpiAny) {
+        if (ep.scale) {
+#pragma unroll
+            for (int g = 0; g < N / 4; ++g) {
+                const f32x4 s = *(const f32x4*)(scale + 4 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[4 * g + i] *= s[i];
+            }
+        }
+        if (ep.bias) {
+#pragma unroll
+            for (int g = 0; g < N / 4; ++g) {
+                const f32x4 b = *(const f32x4*)(bias + 4 * g);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[4 * g + i] += b[i];
+            }
+        }
     }
 }
 

@@ -134,4 +134,16 @@ __device__ __forceinline__ void copy16_to_lds(const void* gsrc, char* lds_wave_b
                                      (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
 }
 
+// Stores of 16 bytes a lane at a wave-uniform base and a 32-bit byte offset, written through the L2 rather than left in it for the end of the
+// launch; an offset of kNoStore stores nothing (past the buffer's end).
+constexpr uint32_t kNoStore = 0xffffff00u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t store_base(void* p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, kNoStore, 0x00027000);
+}
+__device__ __forceinline__ void store16_through(__amdgpu_buffer_rsrc_t base, uint32_t offset, u32x4 v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, base, offset, 0, 16);  // (16: sc1)
+}
+
 }  // namespace rtoss

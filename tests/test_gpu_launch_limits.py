@@ -59,3 +59,29 @@ def test_calls_past_a_kernels_launch_limits(case):
     assert sum(int(torch.count_nonzero(part)) for part in y.flatten().split(1 << 30)) == nonzero
     del x, y
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dt,Ci", [(wl.F16, 64), (wl.BF16, 512), (wl.F32, 64)], ids=["f16", "bf16", "f32"])
+def test_1x1_output_pitch_past_32_bit_offsets(dt, Ci):
+    """Positions so far apart that a buffer of them spans 4 GiB: bit-equal or, by the other kernel, equal within the rounding of
+    the stored value and the fp32 sums."""
+    P, Co, k = 70, 32, 2
+    pitch = (1 << 32) // 64 // wl.ELEM_BYTES[dt]
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < (P + 1) * pitch * wl.ELEM_BYTES[dt] + (2 << 30):
+        pytest.skip("needs %d GB of device memory" % (P * pitch * wl.ELEM_BYTES[dt] >> 30))
+    rng = np.random.default_rng(Ci)
+    masks = B.rtoss_pattern_dict(k)
+    ws = wl.round_to_dtype(rng.standard_normal((Co, Ci, 1, 1)), dt)
+    layer = GpuLayer(ws, dt, masks, k).layer
+    xs = wl.round_to_dtype(rng.standard_normal((1, Ci, 1, P)), dt)
+    x = pl.to_device(wl.nchw_to_nhwc(xs), dt)
+    wide = torch.empty((1, 1, P, pitch), dtype=pl.TORCH_DTYPE[dt], device="cuda")
+    wide[..., Co:Co + 64] = 7
+    got = layer.conv_fused(x, y=wide[..., :Co]).float()
+    near = layer.conv_fused(x).float()
+    peak = float(near.abs().max())
+    bound = 1e-5 * peak + near.abs() * {wl.F32: 0.0, wl.F16: 2.0 ** -10, wl.BF16: 2.0 ** -7}[dt]
+    assert ((got - near).abs() <= bound).all()
+    assert (wide[..., Co:Co + 64] == 7).all()
+    del wide
