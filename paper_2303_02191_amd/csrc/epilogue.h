@@ -296,4 +296,32 @@ template <typename TO, int N> __device__ __forceinline__ void store_ragged(TO* y
         if (co + i < Co) store_from_f32<TO>(yp + co + i, v[i]);
 }
 
+// Output of a tile of 16 positions x 64 channels (16-bit, 2 KB) by one wave in whole rows: put() takes a lane's run of 16 channels (position
+// lane % 16, run lane / 16), store() writes the tile 16 bytes a lane, eight lanes to a row of 128 bytes.  `area` is the wave's own.
+template <typename TO> struct RowTile {
+    static constexpr int kBytes = 2048;
+    static __device__ __forceinline__ int chunk_at(int row, int c) { return (row * 8 + (c ^ ((row >> 1) & 7))) * 16; }
+    static __device__ __forceinline__ void put(char* area, int lane, const float (&v)[16])
+    {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            u32x4 o;
+            o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
+            o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
+            o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
+            o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
+            *(u32x4*)(area + chunk_at(lane & 15, (lane >> 4) * 2 + g)) = o;
+        }
+    }
+    // offset(row, chunk): in bytes from base, or kNoStore
+    template <typename F> static __device__ __forceinline__ void store(const char* area, int lane, __amdgpu_buffer_rsrc_t base, F&& offset)
+    {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const int row = 8 * g + (lane >> 3), c = lane & 7;
+            store16_through(base, offset(row, c), *(const u32x4*)(area + chunk_at(row, c)));
+        }
+    }
+};
+
 }  // namespace rtoss
