@@ -455,9 +455,8 @@ static rtoss_status conv_impl(const rtoss_wdesc* desc, const rtoss_cdesc* c, con
                       : g.format == kFormatDense3x3 ? dense3x3_launch_ok(*desc, cp)
                       : g.format == kFormatDense    ? dense1x1_launch_ok(*desc, cp)
                       : g.format == kFormatStem     ? stem3x3_launch_ok(*desc, cp)
-                      : g.format == kFormatDenseStream ? stream1x1_launch_ok(cp)
                                                     : true;
-    if (c->layout == RTOSS_NCHW || !fits)
+    if (c->layout == RTOSS_NCHW || !fits || !stores_in_reach(cp))
         return launch_conv_direct(*desc, cp, dict, blob + g.live_off, (const uint8_t*)(blob + g.idx_off), x_dev, y_dev,
                                   (hipStream_t)hip_stream);
     if (g.format == kFormatSparse24)

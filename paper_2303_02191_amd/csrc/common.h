@@ -162,7 +162,6 @@ rtoss_status launch_conv1x1_mma(const rtoss_wdesc& d, const ConvParams& c, const
 
 // 1x1 convolution, streaming kernel with register-resident weights (conv1x1_stream.hip)
 bool stream1x1_shape_ok(const rtoss_wdesc& d);
-bool stream1x1_launch_ok(const ConvParams& c);
 size_t stream1x1_section_bytes(const rtoss_wdesc& d);
 rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                    hipStream_t s);

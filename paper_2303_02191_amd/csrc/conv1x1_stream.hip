@@ -664,9 +664,6 @@ bool stream1x1_shape_ok(const rtoss_wdesc& d)
 
 size_t stream1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_section_bytes(stage_count(d)); }
 
-// The kernels' stores are 32-bit offsets from the first position of a buffer (of at most 64).
-bool stream1x1_launch_ok(const ConvParams& c) { return (int64_t)c.ep.ldy * 64 * elem_bytes(c.out_dt) < kNoStore; }
-
 rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                    hipStream_t s)
 {

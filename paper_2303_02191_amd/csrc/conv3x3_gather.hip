@@ -612,16 +612,23 @@ __device__ __forceinline__ void gather_rows_body(char* smem, const T* __restrict
             {
                 int lane_e = lane;
                 asm volatile("" : "+v"(lane_e));
-                const int nn_e = lane_e & 15, qq_e = lane_e >> 4;
                 const int row_first = cur.oh0 + vrow * TN;
                 const int64_t pos_tile = ((int64_t)cur.n_img * Ho + cur.oh0) * Wo + cur.ow0;
                 TO* const y_tile = y + pos_tile * ldy;
-                const bool col_inside = cur.ow0 + nn_e < Wo;
-                const int co_lane = 16 * (cur.mt0 + kTM * hsel) + 16 * qq_e;
+                // rows of 128 bytes past the L2's write-back, through the region multiplied last (free since the hand-over of the
+                // last stage; the barrier that opens the next tile comes before its next copies)
+                const int co_block = 16 * (cur.mt0 + kTM * hsel);
+                char* const area = smem + __builtin_amdgcn_readfirstlane(region_ahead() * RG::REGION) + wave * (2 * RowTile<TO>::kBytes);
+                static_assert(kGrWaves * 2 * RowTile<TO>::kBytes <= RG::REGION, "two tiles of every wave fit a region");
+                auto flush = [&](int j) {
+                    if (row_first + j >= Ho) return;
+                    const auto base = store_base(y_tile + (int64_t)((vrow * TN + j) * Wo) * ldy + co_block);
+                    RowTile<TO>::store(area + (j & 1) * RowTile<TO>::kBytes, lane_e, base, [&](int row, int c) {
+                        return cur.ow0 + row < Wo && co_block + 8 * c < Co ? (uint32_t)row * ldy * 2 + c * 16 : kNoStore;
+                    });
+                };
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    const bool inside = col_inside && row_first + j < Ho;
-                    TO* yp = y_tile + ((vrow * TN + j) * Wo + nn_e) * ldy + co_lane;
                     uint32_t o[8];
 #pragma unroll
                     for (int m = 0; m < kTM; ++m) {
@@ -631,11 +638,10 @@ __device__ __forceinline__ void gather_rows_body(char* smem, const T* __restrict
                         o[2 * m] = pack2_from_f32<TO>(r[0], r[1]);
                         o[2 * m + 1] = pack2_from_f32<TO>(r[2], r[3]);
                     }
-                    if (inside && co_lane < Co) {
-                        *(u32x4*)(yp) = u32x4{o[0], o[1], o[2], o[3]};
-                        *(u32x4*)(yp + 8) = u32x4{o[4], o[5], o[6], o[7]};
-                    }
+                    RowTile<TO>::put(area + (j & 1) * RowTile<TO>::kBytes, lane_e, u32x4{o[0], o[1], o[2], o[3]}, u32x4{o[4], o[5], o[6], o[7]});
+                    if (j) flush(j - 1);
                 }
+                flush(TN - 1);
             }
         };
         // every stage with the same number of steps in both blocks (one table entry per lane)?
@@ -754,7 +760,7 @@ rtoss_status launch_gather(const rtoss_wdesc& d, const ConvParams& c, const char
 inline bool takes_pipelined_gather(const rtoss_wdesc& d, const ConvParams& c)
 {
     if (c.stride != 1 || d.Co <= 64 || d.Ci <= 64 || c.out_dt == RTOSS_F32) return false;
-    if (c.ep.scale || c.ep.bias || c.ep.residual || c.ep.act > 1) return false;
+    if (c.ep.scale || c.ep.bias || c.ep.residual || c.ep.act > 1 || !stores_in_reach(c)) return false;
     const int64_t tiles8 = (int64_t)((c.H + 15) / 16) * ((c.W + 15) / 16) * c.N * (((d.Co + 15) / 16 + 7) / 8);
     return tiles8 >= (d.Ci >= 256 ? 120 : 200);
 }

@@ -341,7 +341,7 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
         // ---- epilogue ----
         // Per lane and group of 4 channel tiles the accumulators hold 16 consecutive output channels of one
         // position (tile_row_channel): column nn of row j of the wave.  16-bit outputs without a fused output
-        // stage are stored directly: 32 contiguous bytes per lane.  Otherwise each wave transposes its
+        // stage leave in rows of 128 bytes past the L2's write-back (RowTile).  Otherwise each wave transposes its
         // 16*TN positions x 16*TM channels through its own slice of the region that was multiplied last
         // (free now; the other region is receiving the next tile's first stage) and writes whole
         // channel rows, 16 bytes per lane; fp32 output goes in two halves of the channel tiles.
@@ -365,29 +365,34 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
             const int64_t pos_tile = ((int64_t)cur.n_img * Ho + cur.oh0) * Wo + cur.ow0;  // position number
             TO* const y_tile = y + pos_tile * ep.ldy;
             const float relu_floor = ep.act == 1 ? 0.f : -__builtin_inff();
-            if constexpr (kDirectEpilogue && EB == 2 && !FUSED) {
-                const bool col_inside = cur.ow0 + nn_e < Wo;
+            if constexpr (EB == 2 && !FUSED) {
+                // (four tiles of a wave in turn, two on their way: 256 -> 256 on 4x100x168 45.5 -> 44.0 us, on 2x100x168 25.4 -> 23.6,
+                // 192 -> 128 on 8x80x80 17.9 -> 16.7, against 32 bytes a lane from the accumulators, written back when the launch ends)
+                char* const area = smem + (gpar ^ 1) * REGION + wave * (4 * RowTile<TO>::kBytes);
+                auto flush = [&](auto t_tag) {
+                    constexpr int t = decltype(t_tag)::value, j = t / (TM / 4), mg = t % (TM / 4) * 4;
+                    if (row_first + j >= Ho) return;
+                    const auto base = store_base(y_tile + (int64_t)((wave * TN + j) * Wo) * ep.ldy + 16 * (cur.mt0 + mg));
+                    RowTile<TO>::store(area + t % 4 * RowTile<TO>::kBytes, lane_e, base, [&](int row, int c) {
+                        return cur.ow0 + row < Wo && 16 * (cur.mt0 + mg) + 8 * c < Co ? (uint32_t)row * ep.ldy * 2 + c * 16 : kNoStore;
+                    });
+                };
+                static_for<TN * (TM / 4)>([&](auto t_tag) {
+                    constexpr int t = decltype(t_tag)::value, j = t / (TM / 4), mg = t % (TM / 4) * 4;
+                    uint32_t o[8];
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const bool inside = col_inside && row_first + j < Ho;
-                    TO* yp = y_tile + ((wave * TN + j) * Wo + nn_e) * ep.ldy + 16 * cur.mt0 + 16 * qq_e;
+                    for (int m = 0; m < 4; ++m) {
+                        float r[4];
 #pragma unroll
-                    for (int mg = 0; mg < TM; mg += 4) {
-                        uint32_t o[8];
-#pragma unroll
-                        for (int m = 0; m < 4; ++m) {
-                            float r[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) asm("v_max_f32 %0, %1, %2" : "=v"(r[e]) : "v"(acc[mg + m][j][e]), "v"(relu_floor));
-                            o[2 * m] = pack2_from_f32<TO>(r[0], r[1]);
-                            o[2 * m + 1] = pack2_from_f32<TO>(r[2], r[3]);
-                        }
-                        if (inside && 16 * (cur.mt0 + mg) + 16 * qq_e < Co) {
-                            *(u32x4*)(yp + 16 * mg) = u32x4{o[0], o[1], o[2], o[3]};
-                            *(u32x4*)(yp + 16 * mg + 8) = u32x4{o[4], o[5], o[6], o[7]};
-                        }
+                        for (int e = 0; e < 4; ++e) asm("v_max_f32 %0, %1, %2" : "=v"(r[e]) : "v"(acc[mg + m][j][e]), "v"(relu_floor));
+                        o[2 * m] = pack2_from_f32<TO>(r[0], r[1]);
+                        o[2 * m + 1] = pack2_from_f32<TO>(r[2], r[3]);
                     }
-                }
+                    RowTile<TO>::put(area + t % 4 * RowTile<TO>::kBytes, lane_e, u32x4{o[0], o[1], o[2], o[3]}, u32x4{o[4], o[5], o[6], o[7]});
+                    if constexpr (t >= 2) flush(std::integral_constant<int, t - 2>{});
+                });
+                flush(std::integral_constant<int, TN * (TM / 4) - 2>{});
+                flush(std::integral_constant<int, TN * (TM / 4) - 1>{});
             } else {
                 // (loops over types: a pragma gives up on bodies of this size, and the accumulators would go to memory)
                 static_for<HALVES>([&](auto h_tag) {
@@ -464,9 +469,8 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
         }
         // staging slices are read (LDS only): the region may be overwritten by the next copies.  A bare
         // barrier, because __syncthreads() carries a fence that would wait here for this tile's output
-        // stores to drain; they drain behind the next tile's first stage instead.  (The direct epilogue
-        // does not touch LDS: nothing to wait for.)
-        if constexpr (!(kDirectEpilogue && sizeof(TO) == 2 && !FUSED)) {
+        // stores to drain; they drain behind the next tile's first stage instead.
+        {
             if (has_next) {
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0) only

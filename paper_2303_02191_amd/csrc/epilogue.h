@@ -29,6 +29,9 @@ struct ConvParams : rtoss_cdesc {
     DeviceInfo dev;  // asked for once per call
 };
 
+// The matrix-core kernels' stores are 32-bit offsets from a position, of up to 64 positions from there.
+inline bool stores_in_reach(const ConvParams& c) { return (int64_t)c.ep.ldy * 64 * elem_bytes(c.out_dt) < kNoStore; }
+
 // v[i] / (1 + exp(-v[i])), each quotient correctly rounded, whatever type the result is stored in.
 //
 // The IEEE division is ten vector instructions, four cycles each, and would be most of the output stage (a 57-layer
@@ -312,6 +315,11 @@ template <typename TO> struct RowTile {
             o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
             *(u32x4*)(area + chunk_at(lane & 15, (lane >> 4) * 2 + g)) = o;
         }
+    }
+    static __device__ __forceinline__ void put(char* area, int lane, u32x4 a, u32x4 b)
+    {
+        *(u32x4*)(area + chunk_at(lane & 15, (lane >> 4) * 2)) = a;
+        *(u32x4*)(area + chunk_at(lane & 15, (lane >> 4) * 2 + 1)) = b;
     }
     // offset(row, chunk): in bytes from base, or kNoStore
     template <typename F> static __device__ __forceinline__ void store(const char* area, int lane, __amdgpu_buffer_rsrc_t base, F&& offset)

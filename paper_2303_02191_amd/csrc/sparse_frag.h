@@ -33,9 +33,6 @@ constexpr int kFragBytes = 1024;
 constexpr int layout_fragments(const TapLayout& l) { return 2 * l.groups + l.centre; }
 constexpr int layout_tile_bytes(const TapLayout& l) { return layout_fragments(l) * kFragBytes + l.groups * 64 * 4; }
 constexpr int kTileBytes = layout_tile_bytes(kLayouts[0]);  // 5632: layout 0, the only one the pipelined kernel takes
-// 16-bit outputs without a fused output stage are stored straight from the accumulators (measured faster
-// than the transposition through LDS once a lane's values are 32 contiguous bytes: tile_row_channel)
-constexpr bool kDirectEpilogue = true;
 
 // Output channel held by row r of channel tile mt.  Within a group of 4 tiles (64 channels) the rows
 // are dealt so that the accumulator values one lane holds after the multiplication -- rows

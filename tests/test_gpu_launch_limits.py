@@ -61,10 +61,11 @@ def test_calls_past_a_kernels_launch_limits(case):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("dt,Ci", [(wl.F16, 64), (wl.BF16, 512), (wl.F32, 64)], ids=["f16", "bf16", "f32"])
-def test_1x1_output_pitch_past_32_bit_offsets(dt, Ci):
-    """Positions so far apart that a buffer of them spans 4 GiB: bit-equal or, by the other kernel, equal within the rounding of
-    the stored value and the fp32 sums."""
+@pytest.mark.parametrize("dt,Ci,ks", [(wl.F16, 64, 1), (wl.BF16, 512, 1), (wl.F32, 64, 1), (wl.F16, 72, 1), (wl.BF16, 128, 3), (wl.F32, 64, 3)],
+                         ids=lambda v: str(v))
+def test_output_pitch_past_32_bit_offsets(dt, Ci, ks):
+    """Positions so far apart that 64 of them span 4 GiB: by the element-wise kernel, equal within the rounding of the stored value and
+    the fp32 sums."""
     P, Co, k = 70, 32, 2
     pitch = (1 << 32) // 64 // wl.ELEM_BYTES[dt]
     torch.cuda.empty_cache()
@@ -72,7 +73,7 @@ def test_1x1_output_pitch_past_32_bit_offsets(dt, Ci):
         pytest.skip("needs %d GB of device memory" % (P * pitch * wl.ELEM_BYTES[dt] >> 30))
     rng = np.random.default_rng(Ci)
     masks = B.rtoss_pattern_dict(k)
-    ws = wl.round_to_dtype(rng.standard_normal((Co, Ci, 1, 1)), dt)
+    ws = wl.round_to_dtype(rng.standard_normal((Co, Ci, ks, ks)), dt)
     layer = GpuLayer(ws, dt, masks, k).layer
     xs = wl.round_to_dtype(rng.standard_normal((1, Ci, 1, P)), dt)
     x = pl.to_device(wl.nchw_to_nhwc(xs), dt)
