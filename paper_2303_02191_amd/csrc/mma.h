@@ -146,4 +146,11 @@ __device__ __forceinline__ void store16_through(__amdgpu_buffer_rsrc_t base, uin
     __builtin_amdgcn_raw_buffer_store_b128(v, base, offset, 0, 16);  // (16: sc1)
 }
 
+// The same at a lane's own address.  (The s_nop: the store's data may be overwritten two instructions on, which the compiler does not
+// see in an asm statement.)
+__device__ __forceinline__ void store16_through(void* p, u32x4 v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+}
+
 }  // namespace rtoss

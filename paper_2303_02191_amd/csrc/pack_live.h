@@ -71,7 +71,7 @@ __device__ __forceinline__ void pack_live_block(const T* __restrict__ w, const u
     __syncthreads();
     T* dst = (T*)job.live + g0 * k;  // (a multiple of 16 bytes from the blob's start)
     const int n_out = n * k;
-    for (int e = tid * EPV; e + EPV <= n_out; e += 256 * EPV) *(u32x4*)(dst + e) = *(const u32x4*)(out + e);
+    for (int e = tid * EPV; e + EPV <= n_out; e += 256 * EPV) store16_through(dst + e, *(const u32x4*)(out + e));
     for (int e = n_out / EPV * EPV + tid; e < n_out; e += 256) dst[e] = out[e];
 }
 
