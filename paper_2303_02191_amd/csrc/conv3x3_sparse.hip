@@ -342,20 +342,22 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
+            if (!live[j]) continue;  // uniform
             const int oh = oh_of[j] + pr, ow = ow_of[j] + pc;
-            if (!live[j] || oh >= Ho || ow >= Wo) continue;
+            const bool row_inside = oh < Ho, inside = row_inside && ow < Wo;
             const int64_t pos = ((int64_t)n_of[j] * Ho + oh) * Wo + ow;
             TO* yp = y + pos * ep.ldy;
 #pragma unroll
             for (int mg = 0; mg < TM; mg += 4) {
                 const int co = 16 * mt0 + tile_quarter_offset(mg, qq);
-                if (co >= Co) continue;  // (not RAG: Co is a multiple of 16, a run of 16 channels is all in or all out)
+                const bool mine = inside && co < Co;  // (not RAG: Co is a multiple of 16, a run of 16 channels is all in or all out)
                 float vv[16];
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) vv[4 * m + e] = acc[mg + m][j][e];
                 if constexpr (RAG) {
+                    if (!mine) continue;
                     epi_ragged<TO, 16>(vv, ep, pos, co, Co);
                     store_ragged<TO, 16>(yp, vv, co, Co, ep.ldy);
                     continue;
@@ -363,18 +365,32 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
                 epi_scale_bias_act_of<decltype(form)::value, 16>(vv, ep, lds_ep + co - 16 * mt0, lds_ep + 16 * TM + co - 16 * mt0);
                 if constexpr (SHORTCUT) shortcut[j][mg / 4].add(vv);
                 if constexpr (sizeof(TO) == 4) {
+                    if (!mine) continue;
 #pragma unroll
                     for (int g = 0; g < 4; ++g) *(f32x4*)(yp + co + 4 * g) = f32x4{vv[4 * g], vv[4 * g + 1], vv[4 * g + 2], vv[4 * g + 3]};
                 } else {
+                    u32x4 o[2];
 #pragma unroll
                     for (int g = 0; g < 2; ++g) {
-                        u32x4 o;
-                        o.x = pack2_from_f32<TO>(vv[8 * g + 0], vv[8 * g + 1]);
-                        o.y = pack2_from_f32<TO>(vv[8 * g + 2], vv[8 * g + 3]);
-                        o.z = pack2_from_f32<TO>(vv[8 * g + 4], vv[8 * g + 5]);
-                        o.w = pack2_from_f32<TO>(vv[8 * g + 6], vv[8 * g + 7]);
-                        *(u32x4*)(yp + co + 8 * g) = o;
+                        o[g].x = pack2_from_f32<TO>(vv[8 * g + 0], vv[8 * g + 1]);
+                        o[g].y = pack2_from_f32<TO>(vv[8 * g + 2], vv[8 * g + 3]);
+                        o[g].z = pack2_from_f32<TO>(vv[8 * g + 4], vv[8 * g + 5]);
+                        o[g].w = pack2_from_f32<TO>(vv[8 * g + 6], vv[8 * g + 7]);
                     }
+                    if constexpr (!PATCH) {
+                        if (!mine) continue;
+#pragma unroll
+                        for (int g = 0; g < 2; ++g) *(u32x4*)(yp + co + 8 * g) = o[g];
+                        continue;
+                    }
+                    // stride 2: rows of 128 bytes past the L2's write-back (us before, with; 16 images: 32 -> 64 @ 320 44.8 42.7, 64 -> 128 @ 160
+                    // 30.2 29.7, 128 -> 256 @ 80 27.6 26.8, 256 -> 512 @ 40 22.4 21.6; stride 1, 32 -> 32 @ 160: 25.5 26.4)
+                    const int odd = lane & 1;  // (the column's parity too)
+                    pair_pieces(o[0], o[1], odd);
+                    const bool row = row_inside && co < Co;
+                    TO* yc = yp - odd * (int64_t)ep.ldy + co + 8 * odd;
+                    if (row && ow - odd < Wo) store16_through(yc, o[0]);
+                    if (row && ow - odd + 1 < Wo) store16_through(yc + ep.ldy, o[1]);
                 }
             }
         }

@@ -299,6 +299,20 @@ template <typename TO, int N> __device__ __forceinline__ void store_ragged(TO* y
         if (co + i < Co) store_from_f32<TO>(yp + co + i, v[i]);
 }
 
+// Lanes 2i and 2i + 1 hold 16 channels each of two positions side by side, in two pieces of 16 bytes.  Exchanged between them, so that `a` is piece
+// lane % 2 of the even position and `b` of the odd one, and four such pairs with neighbouring channels store rows of 128 bytes, without
+// a detour through LDS and the barrier in front of it.  All lanes of the wave take part.
+__device__ __forceinline__ void pair_pieces(u32x4& a, u32x4& b, bool odd)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t away = odd ? a[i] : b[i];
+        const uint32_t here = (uint32_t)__builtin_amdgcn_mov_dpp((int)away, 0xb1, 0xf, 0xf, true);  // quad_perm: lane ^ 1
+        a[i] = odd ? here : a[i];
+        b[i] = odd ? b[i] : here;
+    }
+}
+
 // Output of a tile of 16 positions x 64 channels (16-bit, 2 KB) by one wave in whole rows: put() takes a lane's run of 16 channels (position
 // lane % 16, run lane / 16), store() writes the tile 16 bytes a lane, eight lanes to a row of 128 bytes.  `area` is the wave's own.
 template <typename TO> struct RowTile {

@@ -10,6 +10,7 @@ import test_gpu_fused
 import test_gpu_ksplit
 import test_gpu_ksplit1x1
 import test_gpu_launch_limits
+import test_gpu_stride2_rows
 import test_gpu_strip
 from variants import OWN_TYPE_OUT, VARIANTS
 
@@ -74,6 +75,8 @@ def test_cases_made_for_a_kernel_reach_it(fused):
         assert families(routes.kernels(calls)) == [kernel] * len(cases)
     calls = [call(dt, N, Ci, Co, H, W, 1, 1, 2, wl.F32, fused) for dt, N, Ci, Co, H, W in test_gpu_ksplit1x1.CASES]
     assert families(routes.kernels(calls)) == ["conv1x1_ksplit"] * len(calls)
+    calls = [call(c[0], *c[2:], 3, 2, c[1], c[0], fused) for c in test_gpu_stride2_rows.CASES]
+    assert families(routes.kernels(calls)) == ["conv3x3_sparse_sb"] * len(calls)
 
 
 def test_fused_cases_reach_the_kernel_they_name():
