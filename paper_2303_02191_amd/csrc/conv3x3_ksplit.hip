@@ -144,6 +144,19 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
     }
     if (wave < stages) issue_activations(wave, mine);
 
+    // Scale, bias and shortcut of this lane's outputs come with the first stage, from memory no one has touched yet (asked for behind
+    // the last stage instead: 128 -> 128 @ 40 with SiLU 4.82 us, now 4.52; stride 2, 256 -> 256 @ 40 6.36, 6.00).
+    constexpr int RUN = 4 * K::MPT;
+    EpiResidual<TO, RUN> shortcut;
+    if (ep.residual && o_live) shortcut.load(ep, o_pos, o_co);
+    float scale[RUN], bias[RUN];
+    if (ep.scale && o_live)
+#pragma unroll
+        for (int g = 0; g < K::MPT; ++g) *(f32x4*)(scale + 4 * g) = *(const f32x4*)(ep.scale + o_co + 4 * g);
+    if (ep.bias && o_live)
+#pragma unroll
+        for (int g = 0; g < K::MPT; ++g) *(f32x4*)(bias + 4 * g) = *(const f32x4*)(ep.bias + o_co + 4 * g);
+
     const int nn = lane & 15, qq = lane >> 4;
     const int pr = nn >> 2, pc = nn & 3;
     const int xb0 = (pr * S * G::LW + pc * S) * G::kPos + qq * 16;  // this lane's position of block 0, tap (0,0), its 8 channels
@@ -249,18 +262,6 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
             issue_activations(s + 4, mine);
         }
     }
-
-    // scale, bias and shortcut of this lane's outputs are on their way while the partial sums meet
-    constexpr int RUN = 4 * K::MPT;
-    EpiResidual<TO, RUN> shortcut;
-    if (ep.residual && o_live) shortcut.load(ep, o_pos, o_co);
-    float scale[RUN], bias[RUN];
-    if (ep.scale && o_live)
-#pragma unroll
-        for (int g = 0; g < K::MPT; ++g) *(f32x4*)(scale + 4 * g) = *(const f32x4*)(ep.scale + o_co + 4 * g);
-    if (ep.bias && o_live)
-#pragma unroll
-        for (int g = 0; g < K::MPT; ++g) *(f32x4*)(bias + 4 * g) = *(const f32x4*)(ep.bias + o_co + 4 * g);
 
     __syncthreads();  // everybody is done with the slots
 #pragma unroll
