@@ -30,7 +30,7 @@
 // (8 channels of one tap) and the 4x4 (tap, channel) blocks are transposed in registers
 // with byte permutes so that one lane holds, for 4 channels, the 4 taps of a group.
 //
-// This file holds the single-buffered kernel (stride 2, ragged channel counts, and stride-1 layers of up to 64 input or
+// This file holds the single-buffered kernel (stride 2, but for shallow layers in large launches, which have one of their own here; ragged channel counts, and stride-1 layers of up to 64 input or
 // output channels in launches of many rounds): a plain loop nest with small tiles, several workgroups per compute unit.
 // Large stride-1 layers take the pipelined kernel of conv3x3_rows.hip, launches of medium size the strips of
 // conv3x3_strip.hip, and those that cannot fill the chip conv3x3_ksplit.hip; all read the same packed section.
@@ -400,6 +400,189 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     else epi_by_form(ep, [&](auto form) { finish(std::false_type{}, form); });
 }
 
+// Stride 2, layers of one or two stages of input channels in large launches: half of what the kernel above copies for 64 positions is weights,
+// and its workgroups are chains of copy, products and stores.  Here a workgroup keeps the weights of its 64 channels, and its waves go over
+// blocks of 4x4 positions by themselves, without a barrier: while a wave multiplies a stage's 9x9 patch, the next one is on its way into
+// a buffer of its own.  32 -> 64 on 16x320x320 with SiLU 42.3 -> 34.3 us (4.6 TB/s, the rate of a copy), 64 -> 128 on 16x160x160 33.6 -> 28.3: bound by the
+// instructions around the products there (block numbers by division instead of addition: 29.4; three buffers a wave: 30.3).
+template <int STAGES> struct Resident {
+    static constexpr int WAVES = 8, BUFS = 2;
+    static constexpr int A_BYTES = 4 * layout_tile_bytes(kLayouts[0]);
+    static constexpr int COPIES = patch_copies(1);
+    static constexpr int LDS = STAGES * A_BYTES + WAVES * BUFS * kPatch + EpiScaleBias<64>::kBytes;
+    static_assert(LDS <= 160 * 1024 && A_BYTES % 1024 == 0, "a compute unit's LDS");
+};
+
+template <typename T, int STAGES>
+__global__ __launch_bounds__(64 * Resident<STAGES>::WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv3x3_resident_kernel(const T* __restrict__ x, T* __restrict__ y, const char* __restrict__ wfrag,
+                                                                               const char* __restrict__ zeros, int H, int W, int Co, int Ho, int Wo,
+                                                                               int m_tiles_total, int blocks_c, int blocks_per_image, int co_blocks,
+                                                                               int blocks, int blocks_per_xcd, Epilogue ep)
+{
+    using R = Resident<STAGES>;
+    constexpr TapLayout LY = kLayouts[0];
+    constexpr int TILE = layout_tile_bytes(LY), FR = layout_fragments(LY), NG = LY.groups, CHUNKS = 4 * STAGES;  // 16-byte chunks of a position
+    extern __shared__ __attribute__((aligned(16))) char smem[];  // [weights of all stages][each wave's buffers][scale, bias]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Workgroups are dealt to the 8 XCDs in turn; each XCD takes a contiguous range of blocks, the channel blocks next to each other.
+    const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8, cb = slot % co_blocks;
+    const int step = (gridDim.x / 8 / co_blocks) * R::WAVES, end = min(blocks, (xcd + 1) * blocks_per_xcd);
+    int blk = xcd * blocks_per_xcd + slot / co_blocks * R::WAVES + wave;
+
+    float* lds_ep = (float*)(smem + STAGES * R::A_BYTES + R::WAVES * R::BUFS * kPatch);
+    EpiScaleBias<64> scale_bias;
+    scale_bias.load(ep, 64 * cb, Co, tid);
+    for (int k = wave; k < STAGES * (R::A_BYTES / 1024); k += R::WAVES) {
+        const int stage = k / (R::A_BYTES / 1024), part = k % (R::A_BYTES / 1024);
+        copy16_to_lds(wfrag + ((int64_t)stage * m_tiles_total + 4 * cb) * TILE + part * 1024 + lane * 16, smem + k * 1024);
+    }
+    // ---- a lane's sources relative to a block's first input position (the layout in LDS: conv3x3_sparse_sb_kernel) ----
+    char* const mine = smem + STAGES * R::A_BYTES + wave * (R::BUFS * kPatch);
+    int rel[R::COPIES], row_of[R::COPIES], col_of[R::COPIES];
+#pragma unroll
+    for (int k = 0; k < R::COPIES; ++k) {
+        const int c = k * 64 + lane, pos = c / 4 % 81, r = pos / 9, i = pos % 9;  // (past the patch: any of its positions)
+        row_of[k] = r - 1;
+        col_of[k] = (i < 5 ? 2 * i : 2 * i - 9) - 1;
+        rel[k] = (row_of[k] * W + col_of[k]) * CHUNKS + ((c & 3) ^ (r & 2 ? 3 : 0));
+    }
+    // this wave's block: image, row and column of blocks (advanced by additions: a division is some forty scalar instructions)
+    struct Block { int n, r, c; };
+    const auto block_at = [&](int b) { return Block{b / blocks_per_image, b % blocks_per_image / blocks_c, b % blocks_per_image % blocks_c}; };
+    const int blocks_r = blocks_per_image / blocks_c;
+    Block here = block_at(blk);
+    const Block by = block_at(step);
+    auto next = [&](Block b) {
+        b.c += by.c;
+        b.r += by.r;
+        b.n += by.n;
+        if (b.c >= blocks_c) b.c -= blocks_c, ++b.r;
+        if (b.r >= blocks_r) b.r -= blocks_r, ++b.n;
+        return b;
+    };
+    auto issue_copies = [&](Block b, int stage, char* buf) {  // uniform
+        const int ih = 8 * b.r, iw = 8 * b.c;
+        const int first = ((b.n * H + ih) * W + iw) * CHUNKS + 4 * stage;  // (31 bits: checked by the launcher)
+        const bool border = ih == 0 || iw == 0 || ih + 8 > H || iw + 8 > W;
+#pragma unroll
+        for (int k = 0; k < R::COPIES; ++k) {
+            const char* src = (const char*)x + (int64_t)(first + rel[k]) * 16;
+            if (border && !((unsigned)(ih + row_of[k]) < (unsigned)H && (unsigned)(iw + col_of[k]) < (unsigned)W)) src = zeros;
+            if ((k + 1) * 1024 <= kPatch || k * 1024 + lane * 16 < kPatch) copy16_to_lds(src, buf + k * 1024);
+        }
+    };
+    if (blk < end) issue_copies(here, 0, mine);
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    scale_bias.store(lds_ep, ep, tid);
+    __syncthreads();
+
+    const int nn = lane & 15, qq = lane >> 4, pr = nn >> 2, pc = nn & 3, odd = lane & 1;
+    const int xb0 = (2 * pr * 9 + pc) * 64 + (pr & 1 ? 3 - qq : qq) * 16, xb1 = (2 * pr * 9 + pc) * 64 + (pr & 1 ? qq : 3 - qq) * 16;
+    epi_by_form(ep, [&](auto form) {
+        int buf = 0;
+        for (; blk < end; blk += step) {
+            f32x4 acc[4];
+            static_for<STAGES>([&](auto stage_tag) {
+                constexpr int stage = decltype(stage_tag)::value;
+                __builtin_amdgcn_sched_barrier(0);
+                // this stage's copies have landed; behind them are at most the two stores of the block before
+                if constexpr (stage == 0) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                const char* at = mine + buf * kPatch;
+                buf ^= 1;
+                if constexpr (stage + 1 < STAGES) issue_copies(here, stage + 1, mine + buf * kPatch);
+                else if (blk + step < end) issue_copies(next(here), 0, mine + buf * kPatch);
+                __builtin_amdgcn_sched_barrier(0);
+                const char* A = smem + stage * R::A_BYTES;
+                auto read_tap = [&](int t) {
+                    const int kh = t / 3, kw = t % 3;
+                    return *(const u32x4*)(at + (kh < 2 ? xb0 : xb1) + (kh * 9 + (kw & 1 ? 5 : kw >> 1)) * 64);
+                };
+                // (the centre's and the first group's operands are asked for together, the second group's in front of their products: with
+                // copies into LDS under way a wave waits for all of its reads, and left alone the compiler puts that wait behind every pair)
+                u32x4 xs[NG][4], as[NG][4][2], ac[4];
+                int idx[NG][4];
+                auto fetch = [&](int g) {
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) xs[g][f] = read_tap(LY.tap[g][f]);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const char* frag = A + m * TILE;
+                        idx[g][m] = *(const int*)(frag + FR * kFragBytes + (g * 64 + lane) * 4);
+                        as[g][m][0] = *(const u32x4*)(frag + 2 * g * kFragBytes + lane * 16);
+                        as[g][m][1] = *(const u32x4*)(frag + (2 * g + 1) * kFragBytes + lane * 16);
+                    }
+                };
+                const u32x4 centre = read_tap(4);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) ac[m] = *(const u32x4*)(A + m * TILE + 2 * NG * kFragBytes + lane * 16);
+                fetch(0);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+                fetch(1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) acc[m] = Dense16<T>::mma(ac[m], centre, stage == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[m]);
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    const u32x8 b[2] = {sparse_operand(xs[g], 0), sparse_operand(xs[g], 1)};
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) acc[m] = Sparse64<T>::template mma<0>(as[g][m][0], b[0], acc[m], idx[g][m]);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) acc[m] = Sparse64<T>::template mma<1>(as[g][m][1], b[1], acc[m], idx[g][m]);
+                }
+            });
+            // ---- 16 consecutive channels of one position a lane; rows of 128 bytes past the L2's write-back ----
+            const int oh0 = 4 * here.r, ow0 = 4 * here.c;
+            const int64_t pos0 = ((int64_t)here.n * Ho + oh0) * Wo + ow0;
+            here = next(here);
+            const bool row_inside = oh0 + pr < Ho && 64 * cb + 16 * qq < Co;  // (Co is a multiple of 16)
+            float v[16];
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][e];
+            epi_scale_bias_act_of<decltype(form)::value, 16>(v, ep, lds_ep + 16 * qq, lds_ep + 64 + 16 * qq);
+            if (row_inside && ow0 + pc < Wo) epi_residual<T, 16>(v, ep, pos0 + pr * Wo + pc, 64 * cb + 16 * qq);
+            u32x4 o[2];
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                o[g].x = pack2_from_f32<T>(v[8 * g + 0], v[8 * g + 1]);
+                o[g].y = pack2_from_f32<T>(v[8 * g + 2], v[8 * g + 3]);
+                o[g].z = pack2_from_f32<T>(v[8 * g + 4], v[8 * g + 5]);
+                o[g].w = pack2_from_f32<T>(v[8 * g + 6], v[8 * g + 7]);
+            }
+            pair_pieces(o[0], o[1], odd);
+            const auto base = store_base(y + pos0 * ep.ldy + 64 * cb);
+            const uint32_t to = (uint32_t)((pr * Wo + pc - odd) * ep.ldy + 16 * qq + 8 * odd) * 2;  // (within 32 bits: resident_ok)
+            uint32_t to0 = row_inside && ow0 + pc - odd < Wo ? to : kNoStore, to1 = row_inside && ow0 + pc - odd + 1 < Wo ? to + 2 * ep.ldy : kNoStore;
+            asm("" : "+v"(to0), "+v"(to1));  // (always two stores, for the count above: not a branch around each)
+            __builtin_amdgcn_sched_barrier(0);
+            store16_through(base, to0, o[0]);
+            store16_through(base, to1, o[1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    });
+}
+
+template <typename T, int STAGES>
+rtoss_status launch_resident(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+{
+    using R = Resident<STAGES>;
+    const int Ho = (c.H - 1) / 2 + 1, Wo = (c.W - 1) / 2 + 1, blocks_c = (Wo + 3) / 4, blocks_per_image = (Ho + 3) / 4 * blocks_c;
+    const int co_blocks = (d.Co + 63) / 64, blocks = blocks_per_image * c.N;
+    auto kern = conv3x3_resident_kernel<T, STAGES>;
+    static LaunchOnce lds_once;  // per instantiation
+    if (rtoss_status st = ensure_dynamic_lds((const void*)kern, R::LDS, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
+    const int slots = std::max(1, c.dev.cus / 8 / co_blocks) * co_blocks;  // workgroups of an XCD: one per compute unit
+    kern<<<dim3(8 * slots), dim3(64 * R::WAVES), R::LDS, s>>>((const T*)x, (T*)y, wfrag, wfrag + fragment_bytes(d, 0), c.H, c.W, d.Co, Ho, Wo,
+                                                                   padded_m_tiles(d.Co), blocks_c, blocks_per_image, co_blocks, blocks,
+                                                                   (blocks + 7) / 8, c.ep);
+    return check_hip(hipGetLastError(), "conv3x3 resident launch");
+}
+
 template <typename T, typename TO, int S, int TM, int TN, int RT, int CT, bool AHEAD = true, int LAY = 0, bool DB = false, bool RAG = false>
 rtoss_status launch_variant_sb(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y,
                             hipStream_t s)
@@ -458,6 +641,19 @@ inline bool two_blocks_per_wave(const rtoss_wdesc& d, const ConvParams& c)
     return d.Ci > 64 && 4 * two <= 3 * one;
 }
 
+// Stride 2, one or two stages: resident weights from one and a half blocks a wave on (us, the single-buffered kernel and the resident one; blocks of 64
+// channels x 16 positions a wave in brackets; batch x channels in -> out @ image):
+//     16x32->64@320 (12.5) 42.3 34.3    16x64->128@160 (6.3) 33.6 28.3    16x64->256@80 (3.1) 15.6 13.5    2x64->256@160 (1.6) 11.3 8.9
+//     16x32->32@160 (3.1)  13.0 11.0    4x64->128@160 (1.6)  11.6  9.3    3x64->128@160 (1.2)  8.5  9.2 stays   1x32->512@112x150 (1.0)  5.6 5.4 stays
+//     4x64->448@90 (2.0)   10.4 10.4    4x32->64@240x250 (1.8) 9.1 7.5    2x32->128@203x211 (1.4) 5.9 6.4 stays 4x64->128@112x140 (1.0) 7.1 6.9 stays
+// (offsets of a block's stores within 32 bits)
+inline bool resident_ok(const rtoss_wdesc& d, const ConvParams& c)
+{
+    const int64_t Ho = (c.H - 1) / 2 + 1, Wo = (c.W - 1) / 2 + 1, blocks = (Ho + 3) / 4 * ((Wo + 3) / 4) * c.N, co_blocks = (d.Co + 63) / 64;
+    if (d.Ci > 64 || co_blocks > 8 || 2 * (3 * Wo + 4) * c.ep.ldy >= kNoStore || blocks > 0x3fffffff || (int64_t)c.N * c.H * c.W * d.Ci / 8 > 0x7fffffff) return false;
+    return blocks * co_blocks >= 12 * c.dev.cus;
+}
+
 // Layout 1 (three tap groups, 4-entry dictionaries): the single-buffered kernel for every shape.
 template <typename T, typename TO>
 rtoss_status launch_typed_layout1(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y,
@@ -488,6 +684,8 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
         // conv3x3_strip.hip): two buffers per workgroup, still two workgroups per compute unit
         return launch_variant_sb<T, TO, 1, 4, 2, 2, 4, true, 0, true>(d, c, wfrag, x, y, s);
     }
+    if constexpr (sizeof(TO) == 2)
+        if (resident_ok(d, c)) return d.Ci == 32 ? launch_resident<T, 1>(d, c, wfrag, x, y, s) : launch_resident<T, 2>(d, c, wfrag, x, y, s);
     if (two_blocks_per_wave(d, c)) return launch_variant_sb<T, TO, 2, 4, 2, 2, 4>(d, c, wfrag, x, y, s);
     return launch_variant_sb<T, TO, 2, 4, 1, 1, 4>(d, c, wfrag, x, y, s);
 }

@@ -1,4 +1,4 @@
-"""GPU parity of the stride-2 kernel where its stores can go wrong: pairs of columns of which one is outside the image, rows of
+"""GPU parity of the stride-2 kernels where their stores can go wrong: pairs of columns of which one is outside the image, rows of
 channels that end within a block of 64, one and two blocks of positions a wave, outputs into a channel slice with a shortcut."""
 import numpy as np
 import pytest
@@ -13,12 +13,14 @@ from gpu_util import GpuLayer
 
 pytestmark = pytest.mark.gpu
 
-# dt, k, N, Ci, Co, H, W
+# dt, k, N, Ci, Co, H, W: the single-buffered kernel's, and the resident one's (images of one block, several channel blocks, a last turn of few blocks)
 CASES = [(wl.F16, 3, 17, 32, 16, 18, 17), (wl.BF16, 2, 520, 64, 112, 1, 1), (wl.F16, 2, 40, 32, 48, 5, 31), (wl.BF16, 4, 9, 32, 80, 33, 35),
          (wl.F16, 3, 40, 128, 272, 42, 41)]
+RESIDENT_CASES = [(wl.F16, 3, 17, 32, 16, 107, 109), (wl.BF16, 2, 10, 64, 144, 79, 85), (wl.F16, 2, 100, 32, 80, 5, 140),
+                  (wl.BF16, 3, 3201, 64, 64, 1, 1), (wl.F16, 3, 9, 64, 320, 66, 67)]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("case", CASES + RESIDENT_CASES, ids=lambda c: "-".join(map(str, c)))
 def test_stride_2_rows(case):
     dt, k, N, Ci, Co, H, W = case
     rng = np.random.default_rng(Ci + Co + W)

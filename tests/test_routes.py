@@ -77,6 +77,8 @@ def test_cases_made_for_a_kernel_reach_it(fused):
     assert families(routes.kernels(calls)) == ["conv1x1_ksplit"] * len(calls)
     calls = [call(c[0], *c[2:], 3, 2, c[1], c[0], fused) for c in test_gpu_stride2_rows.CASES]
     assert families(routes.kernels(calls)) == ["conv3x3_sparse_sb"] * len(calls)
+    calls = [call(c[0], *c[2:], 3, 2, c[1], c[0], fused) for c in test_gpu_stride2_rows.RESIDENT_CASES]
+    assert families(routes.kernels(calls)) == ["conv3x3_resident"] * len(calls)
 
 
 def test_fused_cases_reach_the_kernel_they_name():
