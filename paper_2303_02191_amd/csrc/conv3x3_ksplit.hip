@@ -145,17 +145,20 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
     if (wave < stages) issue_activations(wave, mine);
 
     // Scale, bias and shortcut of this lane's outputs come with the first stage, from memory no one has touched yet (asked for behind
-    // the last stage instead: 128 -> 128 @ 40 with SiLU 4.82 us, now 4.52; stride 2, 256 -> 256 @ 40 6.36, 6.00).
+    // the last stage instead: 128 -> 128 @ 40 with SiLU 4.82 us, now 4.52; stride 2, 256 -> 256 @ 40 6.36, 6.00).  One branch around all
+    // three: a layer without them pays for each (fp32 64 -> 64 @ 56: three branches 5.84 us, one 5.78, none here 5.79).
     constexpr int RUN = 4 * K::MPT;
     EpiResidual<TO, RUN> shortcut;
-    if (ep.residual && o_live) shortcut.load(ep, o_pos, o_co);
     float scale[RUN], bias[RUN];
-    if (ep.scale && o_live)
+    if (((uintptr_t)ep.residual | (uintptr_t)ep.scale | (uintptr_t)ep.bias) && o_live) {
+        if (ep.residual) shortcut.load(ep, o_pos, o_co);
+        if (ep.scale)
 #pragma unroll
-        for (int g = 0; g < K::MPT; ++g) *(f32x4*)(scale + 4 * g) = *(const f32x4*)(ep.scale + o_co + 4 * g);
-    if (ep.bias && o_live)
+            for (int g = 0; g < K::MPT; ++g) *(f32x4*)(scale + 4 * g) = *(const f32x4*)(ep.scale + o_co + 4 * g);
+        if (ep.bias)
 #pragma unroll
-        for (int g = 0; g < K::MPT; ++g) *(f32x4*)(bias + 4 * g) = *(const f32x4*)(ep.bias + o_co + 4 * g);
+            for (int g = 0; g < K::MPT; ++g) *(f32x4*)(bias + 4 * g) = *(const f32x4*)(ep.bias + o_co + 4 * g);
+    }
 
     const int nn = lane & 15, qq = lane >> 4;
     const int pr = nn >> 2, pc = nn & 3;
