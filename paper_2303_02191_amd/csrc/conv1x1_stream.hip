@@ -77,7 +77,7 @@ template <int KS, int WM> struct Plan {
     // Ring depth: three buffers (one being multiplied, one landing, one being refilled).  The 6-bit counter of
     // outstanding copies would allow up to six for most shapes; measured on a 57-layer model, the shallow ring is
     // faster (0.900 vs 0.907 ms with four and 0.915 ms with up to six buffers): its 48 KB let three workgroups share a
-    // compute unit, and their producers together keep more copies in flight than one deep ring can count.
+    // compute unit, and their helpers together keep more copies in flight than one deep ring can count.
     static constexpr int RING = 3;
     static constexpr bool TILE = KS != 16;                         // outputs through LDS
     static constexpr int HELPERS = helper_waves(KS, WM);
@@ -102,9 +102,9 @@ __global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_strea
                                                              int work_per_xcd, Epilogue ep)
 {
     using PL = Plan<KS, WM>;
-    constexpr int MT = PL::MT, WN = PL::WN, NB = PL::NB, PB = PL::PB, BUF = PL::BUF, COPIES = PL::COPIES, RING = PL::RING;
+    constexpr int MT = PL::MT, NB = PL::NB, PB = PL::PB, BUF = PL::BUF, COPIES = PL::COPIES, RING = PL::RING;
     constexpr int ROW = 64 * KS;  // bytes of one position
-    extern __shared__ __attribute__((aligned(16))) char smem[];  // RING buffers, then scale and bias of SPAN channels
+    extern __shared__ __attribute__((aligned(16))) char smem[];  // RING buffers, scale and bias of SPAN channels, two output tiles
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

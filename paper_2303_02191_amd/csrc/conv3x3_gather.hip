@@ -311,7 +311,7 @@ __device__ __forceinline__ void gather_rows_body(char* smem, const T* __restrict
                                                  const char* __restrict__ zeros, int H, int W, int Ci, int Co, int cblocks,
                                                  RowPlan plan, float relu_floor, int ldy)
 {
-    static_assert(sizeof(TO) == 2, "direct epilogue: 16-bit output");
+    static_assert(sizeof(TO) == 2, "RowTile: 16-bit output");
     using RG = GrRegions<CAP>;
     constexpr int RING = RG::RING, AHEAD = RING - 1;  // stages between the one copied and the one multiplied
     constexpr int kGrCopySlots = RG::COPY_SLOTS, kGrAPerWave = RG::A_PER_WAVE;
