@@ -102,6 +102,44 @@ def check_matrix_hazards(asm_path):
     return found
 
 
+def check_store_hazards(asm_path):
+    """Scans the device assembly for stores issued as asm statements whose data is overwritten too early.
+
+    A store of more than 8 bytes reads its data registers late: on gfx950 a vector-ALU instruction may write one of them
+    only two wait states behind it.  The compiler keeps that distance (`s_nop 1`) for the stores it emits itself and does not
+    see those inside asm statements.
+    Returns the offending (store, instruction) pairs.
+    """
+    import re
+
+    def regs(tok):
+        m = re.match(r"\s*v(?:\[(\d+):(\d+)\]|(\d+))\s*$", tok)
+        return set() if not m else set(range(int(m.group(1)), int(m.group(2)) + 1)) if m.group(1) else {int(m.group(3))}
+
+    found, in_asm = [], False
+    recent = []  # [wait states since, data registers, text] of asm stores
+    for raw in open(asm_path, errors="replace"):
+        line = raw.split(";", 1)[0].strip()
+        if raw.strip().startswith(";;#ASM"):
+            in_asm = raw.strip().startswith(";;#ASMSTART")
+            continue
+        if not line or line[0] == "." or line.endswith(":"):
+            continue
+        op, _, rest = line.partition(" ")
+        operands = rest.split(",")
+        if op.startswith("v_"):
+            for _, data, text in recent:
+                if regs(operands[0]) & data:
+                    found.append((text, line))
+        cost = int(operands[0]) + 1 if op == "s_nop" else 1
+        recent = [[age + cost, data, text] for age, data, text in recent if age + cost < 2]
+        if in_asm and re.match(r"(global|flat)_store_dwordx[34]$", op):
+            recent.append([0, regs(operands[1]), line])
+        elif in_asm and re.match(r"buffer_store_dwordx[34]$", op):
+            recent.append([0, regs(operands[0]), line])
+    return found
+
+
 def _compile_one(args):
     hipcc, src, obj = args
     flags = [f for f in HIPCC_FLAGS if f != "-shared"]
@@ -116,6 +154,10 @@ def _compile_one(args):
                 raise RuntimeError("%s: %d register hazard(s) around asm matrix instructions, e.g. `%s` -> `%s`; "
                                    "lower the register pressure of the kernel, keep accumulators out of control-flow joins, "
                                    "or define RTOSS_MFMA_SETTLE for this file"
+                                   % (os.path.basename(src), len(bad), bad[0][0], bad[0][1]))
+            bad = check_store_hazards(os.path.join(os.path.dirname(obj), f))
+            if bad:
+                raise RuntimeError("%s: the data of %d asm store(s) is overwritten less than two wait states behind it, e.g. `%s` -> `%s`"
                                    % (os.path.basename(src), len(bad), bad[0][0], bad[0][1]))
     return obj
 

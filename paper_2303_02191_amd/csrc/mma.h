@@ -146,11 +146,11 @@ __device__ __forceinline__ void store16_through(__amdgpu_buffer_rsrc_t base, uin
     __builtin_amdgcn_raw_buffer_store_b128(v, base, offset, 0, 16);  // (16: sc1)
 }
 
-// The same at a lane's own address.  (The s_nop: the store's data may be overwritten two instructions on, which the compiler does not
-// see in an asm statement.)
+// The same at a lane's own address.  (The s_nop: a store of more than 8 bytes reads its data late, a vector instruction may write it only two
+// wait states on, and the compiler, which keeps them behind its own stores, does not see this one.  build.py scans for it.)
 __device__ __forceinline__ void store16_through(void* p, u32x4 v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 
 }  // namespace rtoss

@@ -1,9 +1,12 @@
 """The build-time scan of the generated device assembly (host logic, no GPU): a value that the register
 allocator brings back from the accumulation registers right in front of an asm matrix instruction that reads
-it must fail the build; the same move far enough away, or feeding another register, must not."""
+it must fail the build; the same move far enough away, or feeding another register, must not.  Likewise for the data of a wide asm store
+that is overwritten right behind it."""
 import os
+import subprocess
 
-from paper_2303_02191_amd.build import check_matrix_hazards
+from paper_2303_02191_amd import build
+from paper_2303_02191_amd.build import check_matrix_hazards, check_store_hazards
 
 MFMA = "\t;;#ASMSTART\n\tv_smfmac_f32_16x16x64_bf16 a[0:3], v[10:13], v[20:27], v5 cbsz:0 abid:0\n\t;;#ASMEND\n"
 
@@ -51,3 +54,50 @@ def test_accumulator_moves_right_behind_an_asm_matrix_instruction_are_flagged(tm
     assert _scan(tmp_path, MFMA + "\ts_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 v9, a2\n") == []
     # the next matrix instruction on the same accumulator is the hardware's business
     assert _scan(tmp_path, MFMA + MFMA) == []
+
+
+def _scan_stores(tmp_path, text):
+    p = os.path.join(str(tmp_path), "k.s")
+    with open(p, "w") as f:
+        f.write(text)
+    return check_store_hazards(p)
+
+
+def test_store_data_overwritten_too_early_is_flagged(tmp_path):
+    store = "\t;;#ASMSTART\n\tglobal_store_dwordx4 v[8:9], v[0:3], off sc1\n\ts_nop %d\n\t;;#ASMEND\n"
+    over = "\tv_add_u32_e32 v2, v4, v5\n"
+    assert len(_scan_stores(tmp_path, store % 0 + over)) == 1
+    assert _scan_stores(tmp_path, store % 1 + over) == []
+    assert _scan_stores(tmp_path, store % 0 + "\ts_add_u32 s0, s1, s2\n" + over) == []
+    assert _scan_stores(tmp_path, store % 0 + "\tv_add_u32_e32 v8, v4, v5\n") == []  # the address is read at once
+    assert _scan_stores(tmp_path, store % 0 + "\tv_add_u32_e32 v4, v0, v1\n") == []
+    # stores the compiler emitted itself get their distance from it
+    assert _scan_stores(tmp_path, "\tglobal_store_dwordx4 v[8:9], v[0:3], off\n" + over) == []
+    wide = "\t;;#ASMSTART\n\tbuffer_store_dwordx4 v[0:3], v8, s[0:3], 0 offen sc1\n\t;;#ASMEND\n"
+    assert len(_scan_stores(tmp_path, wide + over)) == 1
+
+
+def test_store_past_the_write_back_keeps_its_data(tmp_path):
+    """mma.h's asm store, with its value changed as soon as it is issued."""
+    src, asm = os.path.join(str(tmp_path), "k.hip"), os.path.join(str(tmp_path), "k.s")
+    with open(src, "w") as f:
+        f.write("""#include "mma.h"
+namespace rtoss {
+__global__ void store_and_change(u32x4* p, u32x4 v)
+{
+    v.x += threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        store16_through(p + threadIdx.x + i * 64, v);
+        v.x = v.x * 3 + v.w;
+        v.y ^= v.x;
+        v.w += v.y;
+    }
+}
+}
+""")
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                           "-S", "--cuda-device-only", src, "-o", asm], stderr=subprocess.DEVNULL)
+    assert open(asm).read().count("global_store_dwordx4") == 6
+    assert check_store_hazards(asm) == []
