@@ -361,7 +361,7 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
             asm volatile("" : "+v"(lane_e));
             const int nn_e = lane_e & 15, qq_e = lane_e >> 4;
             const int row_first = cur.oh0 + wave * TN;  // first output row of the wave
-            // 64-bit address of the tile's first output element once; everything else is 32-bit
+            // (positions within a tile count in 32 bits, elements in 64: a channel slice's pitch may be millions)
             const int64_t pos_tile = ((int64_t)cur.n_img * Ho + cur.oh0) * Wo + cur.ow0;  // position number
             TO* const y_tile = y + pos_tile * ep.ldy;
             const float relu_floor = ep.act == 1 ? 0.f : -__builtin_inff();
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
                             const int dr = wave * TN + j0 + (p >> 4), dc = p & 15;
                             const u32x4 v = *(const u32x4*)(stage_out + p * ROW + chunk * 16);
                             if (cur.oh0 + dr < Ho && cur.ow0 + dc < Wo && co < Co)  // Co is a multiple of 16: a chunk is all in or all out
-                                *(u32x4*)(y_tile + (dr * Wo + dc) * ep.ldy + co) = v;
+                                *(u32x4*)(y_tile + (int64_t)(dr * Wo + dc) * ep.ldy + co) = v;
                         }
                     });
                 });

@@ -86,3 +86,34 @@ def test_output_pitch_past_32_bit_offsets(dt, Ci, ks):
     assert ((got - near).abs() <= bound).all()
     assert (wide[..., Co:Co + 64] == 7).all()
     del wide
+
+
+# The pipelined 3x3 kernel's output through LDS (a fused stage, fp32 results): a tile of 20 rows of 16 positions.
+WIDE_TILE = dict(N=1, H=20, W=16, Ci=128, Co=16384, ks=3, stride=1, k=3)
+
+
+@pytest.mark.parametrize("out_dt,fused", [(wl.F16, True), (wl.F32, True), (wl.F32, False)])
+def test_output_pitch_past_31_bit_elements(out_dt, fused):
+    """Positions so far apart that those of one tile pass 2^31 elements: the same bits as side by side."""
+    s = WIDE_TILE
+    P, Co = s["H"] * s["W"], s["Co"]
+    pitch = (1 << 31) // (P - 20) // 8 * 8  # the tile's last 20 positions lie beyond
+    assert (P - 1) * pitch >= 1 << 31
+    torch.cuda.empty_cache()
+    need = P * pitch * wl.ELEM_BYTES[out_dt]
+    if torch.cuda.mem_get_info()[0] < need + (2 << 30):
+        pytest.skip("needs %d GB of device memory" % (need >> 30))
+    rng = np.random.default_rng(P)
+    masks = B.rtoss_pattern_dict(s["k"])
+    layer = GpuLayer(wl.round_to_dtype(rng.standard_normal((Co, s["Ci"], 3, 3)) / 16, wl.F16), wl.F16, masks, s["k"]).layer
+    x = pl.to_device(wl.round_to_dtype(rng.standard_normal((1, s["H"], s["W"], s["Ci"])), wl.F16), wl.F16)
+    stage = {}
+    if fused:
+        stage = dict(scale=torch.rand(Co, device="cuda") + 0.5, bias=torch.randn(Co, device="cuda"), act=B.ACT_SILU)
+    wide = torch.empty((1, s["H"], s["W"], pitch), dtype=pl.TORCH_DTYPE[out_dt], device="cuda")
+    wide[..., Co:Co + 64] = 7
+    got = layer.conv_fused(x, out_dt=out_dt, y=wide[..., :Co], **stage)
+    assert torch.equal(got, layer.conv_fused(x, out_dt=out_dt, **stage))
+    assert (wide[..., Co:Co + 64] == 7).all()
+    del wide, got
+    torch.cuda.empty_cache()

@@ -99,3 +99,10 @@ def test_calls_past_launch_limits_leave_the_kernel_with_the_limit():
              (wl.F16, 64800, 182, 182, 2, 1, 1, 1, 2)]
     calls = [call(dt, N, Ci, Co, H, W, ks, stride, k, dt, False) for dt, N, H, W, Ci, Co, ks, stride, k in below]
     assert families(routes.kernels(calls)) == ["conv3x3_sparse_sb", "conv3x3_sparse_sb", "conv3x3_dense", "conv1x1_mma"]
+
+
+def test_wide_tile_reaches_the_pipelined_kernel():
+    s = test_gpu_launch_limits.WIDE_TILE
+    calls = [call(wl.F16, s["N"], s["Ci"], s["Co"], s["H"], s["W"], s["ks"], s["stride"], s["k"], out_dt, fused)
+             for out_dt, fused in ((wl.F16, True), (wl.F32, True), (wl.F32, False))]
+    assert families(routes.kernels(calls)) == ["conv3x3_rows"] * 3
