@@ -36,6 +36,7 @@
 #include "fp32_split.h"
 #include "mma.h"
 #include "pack_plan.h"
+#include "row_pieces.h"
 
 namespace rtoss {
 
@@ -373,19 +374,24 @@ __device__ __forceinline__ void whole_rows(const T* __restrict__ x, TO* __restri
         } else {
             const int chunks = (row + 15) / 16;
             const uint32_t reciprocal = end == Co ? per_last_chunks : per_chunks;
-            const bool whole = row % 16 == 0 && (first * EB) % 16 == 0;  // (rows of several odd blocks are aligned to an element only)
-            const auto base = store_base(y + p0 * ep.ldy + first);
-            for (int i = tid; i < live * chunks; i += 256) {
-                const int r = chunks == 1 ? i : (int)__umulhi((uint32_t)i, reciprocal), at = (i - r * chunks) * 16;  // (i / chunks)
-                const char* in = smem + r * pitch + at;
-                if (whole) {
-                    store16_through(base, (uint32_t)r * ep.ldy * EB + at, *(const u32x4*)in);
-                    continue;
+            // piece(row of the tile, byte of the row, in LDS)
+            auto pieces = [&](auto&& piece) {
+                for (int i = tid; i < live * chunks; i += 256) {
+                    const int r = chunks == 1 ? i : (int)__umulhi((uint32_t)i, reciprocal), at = (i - r * chunks) * 16;  // (i / chunks)
+                    piece(r, at, smem + r * pitch + at);
                 }
-                char* out = (char*)(y + (p0 + r) * ep.ldy + first) + at;
-                if (at + 16 <= row) __builtin_memcpy(out, in, 16);
-                else
-                    for (int e = 0; e < (row - at) / EB; ++e) ((TO*)out)[e] = ((const TO*)in)[e];
+            };
+            // (whole sectors; else as the L2 puts them together, and rows may be aligned to an element only)
+            if (aligned_pieces((uintptr_t)y, row, first * EB, (int64_t)ep.ldy * EB, blocks == 1 && ep.ldy == Co ? 16 : kSector)) {
+                const auto base = store_base(y + p0 * ep.ldy + first);
+                pieces([&](int r, int at, const char* in) { store16_through(base, (uint32_t)r * ep.ldy * EB + at, *(const u32x4*)in); });
+            } else {
+                pieces([&](int r, int at, const char* in) {
+                    char* out = (char*)(y + (p0 + r) * ep.ldy + first) + at;
+                    if (at + 16 <= row) __builtin_memcpy(out, in, 16);
+                    else
+                        for (int e = 0; e < (row - at) / EB; ++e) ((TO*)out)[e] = ((const TO*)in)[e];
+                });
             }
         }
     }

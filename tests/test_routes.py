@@ -10,6 +10,7 @@ import test_gpu_fused
 import test_gpu_ksplit
 import test_gpu_ksplit1x1
 import test_gpu_launch_limits
+import test_gpu_slices
 import test_gpu_stride2_rows
 import test_gpu_strip
 from variants import OWN_TYPE_OUT, VARIANTS
@@ -79,6 +80,13 @@ def test_cases_made_for_a_kernel_reach_it(fused):
     assert families(routes.kernels(calls)) == ["conv3x3_sparse_sb"] * len(calls)
     calls = [call(c[0], *c[2:], 3, 2, c[1], c[0], fused) for c in test_gpu_stride2_rows.RESIDENT_CASES]
     assert families(routes.kernels(calls)) == ["conv3x3_resident"] * len(calls)
+
+
+def test_slices_reach_the_kernel_they_name():
+    for kernel, dt, N, Ci, Co, H, W, ks, stride, k in test_gpu_slices.CASES:
+        for out_dt in {wl.F32, dt}:
+            for fused in (False, True):
+                assert families(routes.kernels([call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, fused)])) == [kernel]
 
 
 def test_fused_cases_reach_the_kernel_they_name():
