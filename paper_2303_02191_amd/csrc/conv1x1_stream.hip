@@ -28,8 +28,8 @@
 //     us with stores from the accumulators / with tiles / with tiles past the write-back: 64 -> 64 channels on 102 400
 //     positions with SiLU 8.0  8.2  6.6, 128 -> 128 on 102 400 12.3  12.6  11.1, 256 -> 256 on 25 600 11.0  11.0  9.6.
 //   * 512 channels: two or three buffers a workgroup and a wave to a SIMD, so that a turn is the sum of its parts.  The consumers
-//     put the output stage of a buffer between the matrix instructions of the next one instead, and store from there (rows of
-//     64 bytes; a tile would be a turn more): 512 -> 256 on 6400 positions with SiLU 7.0 -> 6.2 us, 512 -> 512 9.4 -> 7.9.
+//     put the output stage of a buffer between the matrix instructions of the next one instead, and store from there (16-bit results
+//     in rows of 64 bytes; a tile would be a turn more): 512 -> 256 on 6400 positions with SiLU 7.0 -> 6.2 us, 512 -> 512 9.4 -> 7.9.
 //
 // fp32 tensors of 32 to 256 channels have a kernel of their own, on the bf16 matrix instruction (the second one here).  Those of
 // 16 and of 512 channels run through the first: a stage is then 16 channels (the same 64 bytes per position) and a fragment
@@ -280,20 +280,26 @@ __global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_strea
             const int64_t p = buffers.at(b) * PB + row;
             const bool live = p < P && co_lane < Co;  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
             if (ep.residual && live) epi_residual<TO, RUN>(v, ep, p, co_lane);
-            const auto base = store_base(y + buffers.at(b) * PB * ep.ldy);
-            const uint32_t at = live ? ((uint32_t)row * ep.ldy + co_lane) * EB : kNoStore;
+            if constexpr (EB == 4) {
+                // (fp32 results: an instruction writes 16 bytes of every 32, half sectors.  Past the write-back on tensors in no cache
+                // 512 -> 512 on 6400 positions 13.3 us, now 9.9; 512 -> 272 on 25 600 25.6, 17.7)
+                TO* const yp = y + p * ep.ldy + co_lane;
 #pragma unroll
-            for (int g = 0; g < RUN * EB / 16; ++g) {
-                u32x4 o;
-                if constexpr (EB == 4) {
-                    o = __builtin_bit_cast(u32x4, f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]});
-                } else {
+                for (int g = 0; g < RUN / 4; ++g)
+                    if (live) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+                return;
+            } else {
+                const auto base = store_base(y + buffers.at(b) * PB * ep.ldy);
+                const uint32_t at = live ? ((uint32_t)row * ep.ldy + co_lane) * EB : kNoStore;
+#pragma unroll
+                for (int g = 0; g < RUN / 8; ++g) {
+                    u32x4 o;
                     o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
                     o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
                     o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
                     o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
+                    store16_through(base, at + 16 * g, o);
                 }
-                store16_through(base, at + 16 * g, o);
             }
         };
         epi_by_form(ep, [&](auto form) {
