@@ -79,7 +79,7 @@ template <int KS, int WM> struct Plan {
     // faster (0.900 vs 0.907 ms with four and 0.915 ms with up to six buffers): its 48 KB let three workgroups share a
     // compute unit, and their helpers together keep more copies in flight than one deep ring can count.
     static constexpr int RING = 3;
-    static constexpr bool TILE = KS != 16;                         // outputs through LDS
+    static constexpr bool INTERLEAVED = KS == 16;                  // a buffer's output stage between the products of the next
     static constexpr int HELPERS = helper_waves(KS, WM);
     static constexpr int LANES = 64 * (4 + HELPERS);
     static_assert(COPIES >= 1 && COPIES * 16 == PB * KS, "a buffer is a whole number of copy instructions");
@@ -95,11 +95,10 @@ inline size_t frag_bytes(const rtoss_wdesc& d)
     return (size_t)stream_co_blocks_of(KS, d.Co) * stream_wm_of(KS, d.Co) * stream_mt_of(KS) * KS * kFrag;
 }
 
-template <typename T, typename TO, int KS, int WM>
-__global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y,
-                                                             const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                             int64_t P, int Co, int co_blocks, Share share, int total_wgs,
-                                                             int work_per_xcd, Epilogue ep)
+// TILE: outputs through LDS tiles and the helpers; else straight from the accumulators, as they are.
+template <typename T, typename TO, int KS, int WM, bool TILE>
+__device__ __forceinline__ void stream_outputs(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                               int64_t P, int Co, int co_blocks, const Share& share, int total_wgs, int work_per_xcd, const Epilogue& ep)
 {
     using PL = Plan<KS, WM>;
     constexpr int MT = PL::MT, NB = PL::NB, PB = PL::PB, BUF = PL::BUF, COPIES = PL::COPIES, RING = PL::RING;
@@ -116,7 +115,6 @@ __global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_strea
     const int64_t count = buffers.count;  // (64 bits: 32 measured 1 to 2 % slower in small launches)
 
     constexpr int EB = (int)sizeof(TO), SPAN = PL::SPAN;
-    constexpr bool TILE = PL::TILE;
     constexpr int CPR = SPAN * EB / 16;                        // 16-byte chunks of a row of the output tile
     constexpr int OUT = PB * SPAN * EB, STORES = OUT / 1024;   // bytes and store instructions of a tile
     char* out = smem + RING * BUF + EpiScaleBias<SPAN>::kBytes;  // two output tiles
@@ -247,7 +245,7 @@ __global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_strea
     const int co_lane = cb * PL::SPAN + wm * (16 * MT) + 4 * MT * qq;  // first of this lane's 4*MT channels
     const int co_local = wm * (16 * MT) + 4 * MT * qq;
 
-    if constexpr (!TILE) {
+    if constexpr (PL::INTERLEAVED) {
         // ---- each buffer's output stage between the matrix instructions of the next ----
         constexpr int RUN = 4 * MT;
         const int row = 16 * wn + nn;
@@ -385,20 +383,26 @@ __global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_strea
                 for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][0][e];
             epi_scale_bias_act_of<decltype(form)::value, 4 * MT>(v, ep, lds_ep + co_local, lds_ep + SPAN + co_local);
             const int row = 16 * wn + nn;
-            if (ep.residual) {
-                const int64_t p = buffers.at(b) * PB + row;
-                if (p < P && co_lane < Co) epi_residual<TO, 4 * MT>(v, ep, p, co_lane);
+            const int64_t p = buffers.at(b) * PB + row;
+            const auto live = [&] { return p < P && co_lane < Co; };  // Co is a multiple of 16 and the run is 16-aligned: all in or all out
+            if (ep.residual)
+                if (live()) epi_residual<TO, 4 * MT>(v, ep, p, co_lane);
+            if (!TILE && !live()) {
+                slot = slot + 1 == RING ? 0 : slot + 1;
+                continue;
             }
-            char* tile = out + (b & 1) * OUT;
+            // this lane's run: into its row of the tile, or of the output
+            char* const tile = out + (b & 1) * OUT;
+            TO* const yp = y + p * ep.ldy + co_lane;
+            auto piece = [&](int g) { return TILE ? tile + chunk_at(row, co_local * EB / 16 + g) * 16 : (char*)yp + 16 * g; };
             if constexpr (EB == 4) {
 #pragma unroll
-                for (int g = 0; g < MT; ++g)
-                    *(f32x4*)(tile + chunk_at(row, co_local / 4 + g) * 16) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+                for (int g = 0; g < MT; ++g) *(f32x4*)piece(g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
             } else if constexpr (MT == 1) {
                 uint2 o;
                 o.x = pack2_from_f32<TO>(v[0], v[1]);
                 o.y = pack2_from_f32<TO>(v[2], v[3]);
-                *(uint2*)(tile + chunk_at(row, co_local / 8) * 16 + (co_local & 4) * 2) = o;
+                *(uint2*)(piece(0) + (TILE ? (co_local & 4) * 2 : 0)) = o;
             } else {
 #pragma unroll
                 for (int g = 0; g < MT / 2; ++g) {
@@ -407,17 +411,34 @@ __global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_strea
                     o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
                     o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
                     o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
-                    *(u32x4*)(tile + chunk_at(row, co_local / 8 + g) * 16) = o;
+                    *(u32x4*)piece(g) = o;
                 }
             }
             slot = slot + 1 == RING ? 0 : slot + 1;
         }
     });
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_s_barrier();  // the last output tile is complete
-    asm volatile("" ::: "memory");
-    flush(count - 1, wave, std::integral_constant<int, 4>{});
+    if constexpr (TILE) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        __builtin_amdgcn_s_barrier();  // the last output tile is complete
+        asm volatile("" ::: "memory");
+        flush(count - 1, wave, std::integral_constant<int, 4>{});
+    }
+}
+
+template <typename T, typename TO, int KS, int WM>
+__global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+                                                                             const char* __restrict__ zeros, int64_t P, int Co, int co_blocks,
+                                                                             Share share, int total_wgs, int work_per_xcd, Epilogue ep)
+{
+    stream_outputs<T, TO, KS, WM, !Plan<KS, WM>::INTERLEAVED>(x, y, wfrag, zeros, P, Co, co_blocks, share, total_wgs, work_per_xcd, ep);
+}
+template <typename T, typename TO, int KS, int WM, bool TILE>
+__global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+                                                                             const char* __restrict__ zeros, int64_t P, int Co, int co_blocks,
+                                                                             Share share, int total_wgs, int work_per_xcd, Epilogue ep)
+{
+    stream_outputs<T, TO, KS, WM, TILE>(x, y, wfrag, zeros, P, Co, co_blocks, share, total_wgs, work_per_xcd, ep);
 }
 
 // fp32, 32 to 256 channels: products on the bf16 matrix instruction, every value split into three parts (fp32_split.h).
@@ -583,15 +604,34 @@ rtoss_status launch_f32(const rtoss_wdesc& d, const ConvParams& c, const char* w
     return check_hip(hipGetLastError(), "conv1x1 stream launch");
 }
 
-template <typename T, typename TO, int KS, int WM>
+// Launches whose outputs go straight from the accumulators, as they are: those of so few bytes that writing them back when the launch
+// ends costs less than the way through the tile (about 0.2 us, 1 MB).  Layers of 32 and 64 16-bit channels (deeper ones of that size
+// take the channel split) and of 16 fp32 channels.  us, from the accumulators / tile (MB of output in brackets):
+//     32 ->  64 (0.01) 2.34 2.57     64 ->  64, fp32 results (0.4) 3.12 3.40     64 -> 512 (1.6)               2.90 2.99
+//     32 -> 512 (1.6)  2.76 2.86     32 ->  64, fp32 results (1.6) 3.28 3.27     32 -> 512, fp32 results (3.3) 3.79 3.32
+// Where blocks of channels are full, the stores through the tile run beside SiLU (but for a 16-bit shortcut's loads) and beside the fp32
+// products:
+//     64 ->  64, SiLU (0.2)  3.50 3.54     64 -> 256, SiLU and shortcut (0.8)               3.99 4.26     fp32 16 -> 64 (1.6) 3.09 2.79
+//     32 -> 512, SiLU (1.6)  3.54 3.41     32 -> 256, SiLU and shortcut, fp32 results (1.6) 4.70 4.50     fp32 16 -> 16 (1.6) 3.16 3.61
+//     32 -> 144, SiLU, fp32 results (0.9) 3.42 3.73
+inline bool direct_outputs(const rtoss_wdesc& d, const ConvParams& c)
+{
+    const int KS = stage_count(d), span = 16 * stream_mt_of(KS) * stream_wm_of(KS, d.Co);
+    const bool full = d.Co % span == 0, covered = full && c.ep.act == 2 && (!c.ep.residual || c.out_dt == RTOSS_F32);
+    if (full && d.dt == RTOSS_F32) return false;
+    return (int64_t)c.N * c.H * c.W * d.Co * (int)elem_bytes(c.out_dt) <= (covered ? 1 << 19 : 2 << 20);
+}
+
+template <typename T, typename TO, int KS, int WM, bool... TILE>
 rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     using PL = Plan<KS, WM>;
     const int64_t P = (int64_t)c.N * c.H * c.W;
     const int64_t nbuf = (P + PL::PB - 1) / PL::PB;
     const int co_blocks = stream_co_blocks_of(KS, d.Co);
-    const size_t smem = (size_t)PL::RING * PL::BUF + EpiScaleBias<PL::SPAN>::kBytes + (PL::TILE ? 2 * PL::PB * PL::SPAN * sizeof(TO) : 0);
-    auto kern = conv1x1_stream_kernel<T, TO, KS, WM>;
+    constexpr bool tiles = !PL::INTERLEAVED && sizeof...(TILE) == 0;
+    const size_t smem = (size_t)PL::RING * PL::BUF + EpiScaleBias<PL::SPAN>::kBytes + (tiles ? 2 * PL::PB * PL::SPAN * sizeof(TO) : 0);
+    auto kern = conv1x1_stream_kernel<T, TO, KS, WM, TILE...>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv1x1 shared memory attribute")) return st;
     // Persistent workgroups: as many as are resident at once, but no fewer than 2 buffers each: every
@@ -627,15 +667,23 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     return check_hip(hipGetLastError(), "conv1x1 stream launch");
 }
 
+template <typename T, typename TO, int KS, int WM>
+rtoss_status launch_wm(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+{
+    if constexpr (KS <= (sizeof(T) == 4 ? 1 : 2))
+        if (direct_outputs(d, c)) return launch_plan<T, TO, KS, WM, false>(d, c, wfrag, x, y, s);
+    return launch_plan<T, TO, KS, WM>(d, c, wfrag, x, y, s);
+}
+
 template <typename T, typename TO, int KS>
 rtoss_status launch_ks(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     const int wm = stream_wm_of(KS, d.Co);
     if constexpr (KS <= 8)
-        if (wm == 1) return launch_plan<T, TO, KS, 1>(d, c, wfrag, x, y, s);
+        if (wm == 1) return launch_wm<T, TO, KS, 1>(d, c, wfrag, x, y, s);
     if constexpr (KS <= 16)
-        if (wm == 2) return launch_plan<T, TO, KS, 2>(d, c, wfrag, x, y, s);
-    return launch_plan<T, TO, KS, 4>(d, c, wfrag, x, y, s);
+        if (wm == 2) return launch_wm<T, TO, KS, 2>(d, c, wfrag, x, y, s);
+    return launch_wm<T, TO, KS, 4>(d, c, wfrag, x, y, s);
 }
 
 template <typename T, typename TO>

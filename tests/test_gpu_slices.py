@@ -20,6 +20,9 @@ CASES = [
     ("conv1x1_mma", wl.F16, 1, 24, 520, 29, 31, 1, 1, 2),
     ("conv1x1_mma", wl.F16, 1, 24, 512, 29, 31, 1, 1, 2),
     ("conv1x1_mma", wl.BF16, 1, 72, 240, 29, 31, 1, 1, 2),
+    ("conv1x1_stream", wl.F16, 1, 32, 144, 29, 31, 1, 1, 2),  # straight from the accumulators
+    ("conv1x1_stream", wl.BF16, 1, 64, 16, 29, 31, 1, 1, 2),
+    ("conv1x1_stream", wl.F16, 1, 64, 80, 131, 129, 1, 1, 2),
     ("conv1x1_stream", wl.F16, 1, 512, 208, 83, 85, 1, 1, 2),
     ("conv1x1_stream", wl.BF16, 1, 512, 64, 151, 153, 1, 1, 2),
 ]
