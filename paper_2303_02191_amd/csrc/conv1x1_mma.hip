@@ -36,7 +36,6 @@
 #include "fp32_split.h"
 #include "mma.h"
 #include "pack_plan.h"
-#include "row_pieces.h"
 
 namespace rtoss {
 

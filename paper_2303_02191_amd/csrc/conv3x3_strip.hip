@@ -72,12 +72,10 @@ template <int TN, int LAY, bool DB> struct Strip {
     static_assert(A_BYTES % 1024 == 0, "weight fragments are whole copy instructions");
 };
 
-template <typename T, typename TO, int TN, int LAY, bool DB>
-__global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
-                                                               const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                               int H, int W, int Ci, int Co, int m_tiles_total, int strips,
-                                                               int tiles_per_image, int co_blocks, int total, int work_per_xcd,
-                                                               Epilogue ep)
+template <typename T, typename TO, int TN, int LAY, bool DB, bool ROWS_OUT>
+__device__ __forceinline__ void strip_tile(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                           int H, int W, int Ci, int Co, int m_tiles_total, int strips, int tiles_per_image, int co_blocks, int total,
+                                           int work_per_xcd, const Epilogue& ep)
 {
     using P = Strip<TN, LAY, DB>;
     constexpr TapLayout LY = kLayouts[LAY == kDenseTaps ? 0 : LAY];
@@ -224,12 +222,11 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
     for (int stage = 1; stage < stages; ++stage) run_stage(std::false_type{}, stage);
 
     // ---- store: a lane holds column nn (position) and 16 consecutive channels of each of its rows ----
-    // 16-bit outputs leave in rows of 128 bytes, past the L2's write-back (RowTile, through the LDS buffer that the last stage does
-    // not read): stores of 16 bytes from the registers, written back when the launch ends, took 64 -> 64 channels on 16x80x80 with
+    // ROWS_OUT: in rows of 128 bytes, past the L2's write-back (RowTile, through the LDS buffer that the last stage does not read; the one
+    // buffer behind a barrier).  Stores of 16 bytes from the registers, written back when the launch ends, took 64 -> 64 channels on 16x80x80 with
     // SiLU and shortcut from 12.3 to 14.3 us, 128 -> 128 on 16x40x40 10.6 to 11.3, 256 -> 256 on 1x100x168 18.0 to 18.8, 1x50x84 10.2 to 10.4.
     const int co = 64 * cb + 16 * qq, ow = ow0 + nn;
     const bool live = co < Co && ow < W;  // (Co is a multiple of 16: a run of 16 channels is all in or all out)
-    constexpr bool ROWS_OUT = sizeof(TO) == 2;
     if (!ROWS_OUT && !live) return;
     if (ROWS_OUT && !DB) __syncthreads();  // everybody is done reading the last stage
     char* const area = smem + (DB ? (stages & 1) * P::BUF : 0) + wave * (TN * RowTile<TO>::kBytes);
@@ -258,9 +255,12 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
 #pragma unroll
                 for (int g = 0; g < 4; ++g) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
             } else {
-                RowTile<TO>::put(area + j * RowTile<TO>::kBytes, lane, v);
-            }
-            if constexpr (ROWS_OUT) {
+                const Run16<TO> o(v);
+                if constexpr (!ROWS_OUT) {
+                    o.store(yp);
+                    continue;
+                }
+                RowTile<TO>::put(area + j * RowTile<TO>::kBytes, lane, o);
                 const auto base = store_base(y + (((int64_t)n_img * H + oh0 + wave * TN + j) * W + ow0) * ep.ldy + 64 * cb);
                 RowTile<TO>::store(area + j * RowTile<TO>::kBytes, lane, base, [&](int row, int c) {
                     return ow0 + row < W && 64 * cb + 8 * c < Co ? (uint32_t)row * ep.ldy * 2 + c * 16 : kNoStore;
@@ -270,6 +270,25 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
     };
     if (ep.residual) epi_by_form<false>(ep, [&](auto form) { finish(std::true_type{}, form); });
     else epi_by_form<false>(ep, [&](auto form) { finish(std::false_type{}, form); });
+}
+
+// (ROWS: whether 16-bit outputs leave in rows, where both are there; two buffers and fp32 results know one way)
+template <typename T, typename TO, int TN, int LAY, bool DB>
+__global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+                                                               const char* __restrict__ zeros, int H, int W, int Ci, int Co, int m_tiles_total,
+                                                               int strips, int tiles_per_image, int co_blocks, int total, int work_per_xcd,
+                                                               Epilogue ep)
+{
+    strip_tile<T, TO, TN, LAY, DB, DB && sizeof(TO) == 2>(x, y, wfrag, zeros, H, W, Ci, Co, m_tiles_total, strips, tiles_per_image, co_blocks, total,
+                                                          work_per_xcd, ep);
+}
+template <typename T, typename TO, int TN, int LAY, bool DB, bool ROWS>
+__global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+                                                               const char* __restrict__ zeros, int H, int W, int Ci, int Co, int m_tiles_total,
+                                                               int strips, int tiles_per_image, int co_blocks, int total, int work_per_xcd,
+                                                               Epilogue ep)
+{
+    strip_tile<T, TO, TN, LAY, DB, ROWS>(x, y, wfrag, zeros, H, W, Ci, Co, m_tiles_total, strips, tiles_per_image, co_blocks, total, work_per_xcd, ep);
 }
 
 // Dense mode.  A tap's fragment is used for one product per row and tile and needs no transposition, so here the weights stay out
@@ -283,7 +302,7 @@ template <int ROWS> struct DenseStrip {
     static constexpr int LDS = 2 * BUF + EpiScaleBias<64>::kBytes;
 };
 
-template <typename T, typename TO, int ROWS>
+template <typename T, typename TO, int ROWS, bool ROWS_OUT>
 __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
                                                  const char* __restrict__ zeros, int H, int W, int Ci, int Co, int co_blocks, int cb,
                                                  int n_img, int oh0, int ow0, const Epilogue& ep, char* smem)
@@ -372,9 +391,8 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
     // ---- store: a lane holds 8 consecutive channels of one position per row ----
     const int co = 64 * cb + 16 * qq + 8 * pair, ow = ow0 + nn, oh = oh0 + half * RW;
     const bool live = co < Co && ow < W;  // (Co is a multiple of 16)
-    // (whole rows past the L2's write-back, as above, where the tiles are tall: 20 rows 2x256@100x168 34.2 -> 33.9 us, 1x256@100x168 20.8 -> 20.4;
+    // (ROWS_OUT: whole rows past the L2's write-back, as above, where the tiles are tall: 20 rows 2x256@100x168 34.2 -> 33.9 us, 1x256@100x168 20.8 -> 20.4;
     // 12 rows 4x128@60x80 9.4 -> 9.5)
-    constexpr bool ROWS_OUT = sizeof(TO) == 2 && ROWS >= 16;
     if (!ROWS_OUT && !live) return;
     if constexpr (ROWS_OUT) __syncthreads();  // everybody is done reading the last stage
     static_assert(ROWS * RowTile<TO>::kBytes <= 2 * P::BUF, "the outputs fit the buffers");
@@ -428,11 +446,10 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
 
 // (fp32: dense3x3_f32.h, eight rows)
 template <typename T, int ROWS> constexpr int dense_strip_lds = sizeof(T) == 4 ? F32Tile<1, ROWS>::LDS : DenseStrip<ROWS>::LDS;
-template <typename T, typename TO, int ROWS>
-__global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
-                                                               const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                               int H, int W, int Ci, int Co, int strips, int tiles_per_image,
-                                                               int co_blocks, int total, int work_per_xcd, Epilogue ep)
+template <typename T, typename TO, int ROWS, bool ROWS_OUT>
+__device__ __forceinline__ void dense_strip_work(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                                 int H, int W, int Ci, int Co, int strips, int tiles_per_image, int co_blocks, int total,
+                                                 int work_per_xcd, const Epilogue& ep)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
@@ -440,14 +457,30 @@ __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restri
     const int cb = work % co_blocks, tile = (work / co_blocks) % tiles_per_image, n_img = (work / co_blocks) / tiles_per_image;
     const int oh0 = (tile / strips) * ROWS, ow0 = (tile % strips) * kCols;
     if constexpr (sizeof(T) == 4) dense3x3_f32_tile<1, ROWS, false>(x, y, wfrag, zeros, H, W, Ci, Co, H, W, co_blocks, cb, n_img, oh0, ow0, ep, smem);
-    else dense_strip_tile<T, TO, ROWS>(x, y, wfrag, zeros, H, W, Ci, Co, co_blocks, cb, n_img, oh0, ow0, ep, smem);
+    else dense_strip_tile<T, TO, ROWS, ROWS_OUT>(x, y, wfrag, zeros, H, W, Ci, Co, co_blocks, cb, n_img, oh0, ow0, ep, smem);
+}
+template <typename T, typename TO, int ROWS>
+__global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
+                                                               const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                                               int H, int W, int Ci, int Co, int strips, int tiles_per_image,
+                                                               int co_blocks, int total, int work_per_xcd, Epilogue ep)
+{
+    dense_strip_work<T, TO, ROWS, false>(x, y, wfrag, zeros, H, W, Ci, Co, strips, tiles_per_image, co_blocks, total, work_per_xcd, ep);
+}
+template <typename T, typename TO, int ROWS, bool ROWS_OUT>
+__global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
+                                                               const char* __restrict__ wfrag, const char* __restrict__ zeros,
+                                                               int H, int W, int Ci, int Co, int strips, int tiles_per_image,
+                                                               int co_blocks, int total, int work_per_xcd, Epilogue ep)
+{
+    dense_strip_work<T, TO, ROWS, ROWS_OUT>(x, y, wfrag, zeros, H, W, Ci, Co, strips, tiles_per_image, co_blocks, total, work_per_xcd, ep);
 }
 
-template <typename T, typename TO, int ROWS>
+template <typename T, typename TO, int ROWS, bool... ROWS_OUT>
 rtoss_status launch_dense_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
 {
     const int strips = (c.W + kCols - 1) / kCols, rows = (c.H + ROWS - 1) / ROWS, co_blocks = (d.Co + 63) / 64;
-    auto kern = conv3x3_strip_kernel<T, TO, ROWS>;
+    auto kern = conv3x3_strip_kernel<T, TO, ROWS, ROWS_OUT...>;
     constexpr int lds = dense_strip_lds<T, ROWS>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
@@ -458,13 +491,13 @@ rtoss_status launch_dense_rows(const rtoss_wdesc& d, const ConvParams& c, const 
     return check_hip(hipGetLastError(), "conv3x3 strip launch");
 }
 
-template <typename T, typename TO, int TN, int LAY, bool DB>
+template <typename T, typename TO, int TN, int LAY, bool DB, bool... ROWS>
 rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
 {
     using P = Strip<TN, LAY, DB>;
     const int strips = (c.W + kCols - 1) / kCols, rows = (c.H + P::ROWS - 1) / P::ROWS;
     const int co_blocks = (d.Co + 63) / 64;
-    auto kern = conv3x3_strip_kernel<T, TO, TN, LAY, DB>;
+    auto kern = conv3x3_strip_kernel<T, TO, TN, LAY, DB, ROWS...>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, P::LDS, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)strips * rows * co_blocks * c.N;
@@ -478,14 +511,37 @@ rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* 
     return check_hip(hipGetLastError(), "conv3x3 strip launch");
 }
 
+// Whether 16-bit outputs leave in rows past the L2's write-back, where a kernel has both ways: not where blocks of channels share
+// sectors of memory (row_pieces.h; the dense mode, which gains least, by the pitch of a slice too), nor half-empty rows of up to 2 MB
+// behind a single stage, where the detour through LDS costs more than it saves.  us from the registers, in rows, of tensors in caches,
+// then of tensors in none:
+//     64 -> 208, 4 taps, on 16x80x80               31.3 30.2   34.6 40.7     64 -> 64, 4 taps, on 16x80x80                11.5 10.4   15.4 14.0
+//     128 -> 208, 5 taps, on 16x80x80              48.4 48.9   52.2 56.2     128 -> 128, 5 taps, on 16x80x80              31.1 30.3   33.7 33.6
+//     ... slice of 128 of 144, SiLU, on 16x80x80   31.9 32.9   37.2 40.6     128 -> 128, 4 taps, slice of 144, 4x100x168  22.9 21.4   27.1 26.3
+//     32 -> 32, 3 taps, on 16x28x28 (0.8 MB)       3.59 3.84   4.54 4.79     32 -> 32, slice of 48, SiLU, 4x100x168       6.83 6.38   9.27 7.95
+inline bool rows_out(const rtoss_wdesc& d, const ConvParams& c, bool dense, const void* y)
+{
+    if (!stores_in_reach(c)) return false;
+    if (d.Co <= 64) return d.Co == 64 || stage_count(d) > 1 || (int64_t)c.N * c.H * c.W * d.Co * 2 > 2 << 20;
+    return dense ? whole_sectors(y, d.Co, c.ep.ldy, 2) : d.Co * 2 % kSector == 0;
+}
+
+template <typename T, typename TO, int TN, int LAY>
+rtoss_status launch_one_buffer(const rtoss_wdesc& d, const ConvParams& c, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
+{
+    if constexpr (sizeof(TO) == 2)
+        if (rows_out(d, c, false, y)) return launch_rows<T, TO, TN, LAY, false, true>(d, c, wf, zeros, x, y, s);
+    return launch_rows<T, TO, TN, LAY, false>(d, c, wf, zeros, x, y, s);
+}
+
 template <typename T, typename TO, int LAY>
 rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, int plan, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
 {
     switch (plan) {
-    case 2: return launch_rows<T, TO, 2, LAY, false>(d, c, wf, zeros, x, y, s);
-    case 3: if constexpr (LAY != 0) return launch_rows<T, TO, 3, LAY, false>(d, c, wf, zeros, x, y, s); else break;
-    case 4: return launch_rows<T, TO, 4, LAY, false>(d, c, wf, zeros, x, y, s);
-    case 5: if constexpr (LAY != 0) return launch_rows<T, TO, 5, LAY, false>(d, c, wf, zeros, x, y, s); else break;
+    case 2: return launch_one_buffer<T, TO, 2, LAY>(d, c, wf, zeros, x, y, s);
+    case 3: if constexpr (LAY != 0) return launch_one_buffer<T, TO, 3, LAY>(d, c, wf, zeros, x, y, s); else break;
+    case 4: return launch_one_buffer<T, TO, 4, LAY>(d, c, wf, zeros, x, y, s);
+    case 5: if constexpr (LAY != 0) return launch_one_buffer<T, TO, 5, LAY>(d, c, wf, zeros, x, y, s); else break;
     case 2 + kTwoBuffers: if constexpr (LAY != kDenseTaps) return launch_rows<T, TO, 2, LAY, true>(d, c, wf, zeros, x, y, s); else break;
     case 3 + kTwoBuffers: if constexpr (LAY == 0) return launch_rows<T, TO, 3, LAY, true>(d, c, wf, zeros, x, y, s); else break;
     }
@@ -495,6 +551,10 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, int plan, c
 template <typename T, typename TO>
 rtoss_status launch_dense(const rtoss_wdesc& d, const ConvParams& c, int rows, const char* wf, const char* zeros, const void* x, void* y, hipStream_t s)
 {
+    if constexpr (sizeof(T) == 2 && sizeof(TO) == 2) {
+        if (rows == 16 && rows_out(d, c, true, y)) return launch_dense_rows<T, TO, 16, true>(d, c, wf, zeros, x, y, s);
+        if (rows == 20 && rows_out(d, c, true, y)) return launch_dense_rows<T, TO, 20, true>(d, c, wf, zeros, x, y, s);
+    }
     switch (rows) {
     case 8: return launch_dense_rows<T, TO, 8>(d, c, wf, zeros, x, y, s);
     case 12: if constexpr (sizeof(T) == 2) return launch_dense_rows<T, TO, 12>(d, c, wf, zeros, x, y, s); else break;

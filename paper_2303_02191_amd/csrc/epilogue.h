@@ -9,6 +9,7 @@
 #include "common.h"
 #include "dtypes.h"
 #include "mma.h"
+#include "row_pieces.h"
 
 namespace rtoss {
 
@@ -313,23 +314,29 @@ __device__ __forceinline__ void pair_pieces(u32x4& a, u32x4& b, bool odd)
     }
 }
 
+// A lane's run of 16 channels in 16 bits.
+template <typename TO> struct Run16 {
+    u32x4 half[2];
+    __device__ __forceinline__ explicit Run16(const float (&v)[16])
+    {
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) half[g][i] = pack2_from_f32<TO>(v[8 * g + 2 * i], v[8 * g + 2 * i + 1]);
+    }
+    __device__ __forceinline__ void store(TO* yp) const
+    {
+        *(u32x4*)yp = half[0];
+        *(u32x4*)(yp + 8) = half[1];
+    }
+};
+
 // Output of a tile of 16 positions x 64 channels (16-bit, 2 KB) by one wave in whole rows: put() takes a lane's run of 16 channels (position
 // lane % 16, run lane / 16), store() writes the tile 16 bytes a lane, eight lanes to a row of 128 bytes.  `area` is the wave's own.
 template <typename TO> struct RowTile {
     static constexpr int kBytes = 2048;
     static __device__ __forceinline__ int chunk_at(int row, int c) { return (row * 8 + (c ^ ((row >> 1) & 7))) * 16; }
-    static __device__ __forceinline__ void put(char* area, int lane, const float (&v)[16])
-    {
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            u32x4 o;
-            o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
-            o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
-            o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
-            o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
-            *(u32x4*)(area + chunk_at(lane & 15, (lane >> 4) * 2 + g)) = o;
-        }
-    }
+    static __device__ __forceinline__ void put(char* area, int lane, const Run16<TO>& run) { put(area, lane, run.half[0], run.half[1]); }
     static __device__ __forceinline__ void put(char* area, int lane, u32x4 a, u32x4 b)
     {
         *(u32x4*)(area + chunk_at(lane & 15, (lane >> 4) * 2)) = a;

@@ -16,4 +16,10 @@ constexpr bool aligned_pieces(unsigned long long at, int row, int first, long lo
     return ((at | (unsigned)row | (unsigned)first | (unsigned long long)pitch) & (unsigned)(unit - 1)) == 0;
 }
 
+// ... of the whole output of a layer of `channels` channels
+inline bool whole_sectors(const void* y, int channels, int pitch, int elem)
+{
+    return aligned_pieces((unsigned long long)y, channels * elem, 0, (long long)pitch * elem, kSector);
+}
+
 }  // namespace rtoss

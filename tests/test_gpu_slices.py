@@ -25,6 +25,15 @@ CASES = [
     ("conv1x1_stream", wl.F16, 1, 64, 80, 131, 129, 1, 1, 2),
     ("conv1x1_stream", wl.F16, 1, 512, 208, 83, 85, 1, 1, 2),
     ("conv1x1_stream", wl.BF16, 1, 512, 64, 151, 153, 1, 1, 2),
+    ("conv3x3_strip", wl.F16, 17, 64, 128, 17, 19, 3, 1, 4),  # one buffer, two blocks of channels
+    ("conv3x3_strip", wl.BF16, 49, 64, 208, 9, 19, 3, 1, 4),  # ... the last one of 16 channels
+    ("conv3x3_strip", wl.F16, 33, 64, 48, 17, 19, 3, 1, 4),  # ... one block
+    ("conv3x3_strip", wl.BF16, 33, 32, 48, 9, 19, 3, 1, 3),  # a single stage
+    ("conv3x3_strip", wl.F16, 33, 96, 128, 16, 18, 3, 1, 5),  # dense mode
+    ("conv3x3_strip", wl.BF16, 97, 96, 48, 17, 18, 3, 1, 5),
+    ("conv3x3_strip", wl.F16, 17, 64, 160, 9, 19, 3, 1, 3),  # two buffers
+    ("conv3x3_rows", wl.BF16, 2, 128, 224, 100, 167, 3, 1, 3),
+    ("conv3x3_sparse_sb", wl.F16, 9, 96, 80, 33, 35, 3, 2, 3),
 ]
 
 
