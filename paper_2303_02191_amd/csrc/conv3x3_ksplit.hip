@@ -61,6 +61,23 @@ template <int S, int TM, int RT, int CT, int LAY> struct KSplit {
     static_assert(LDS <= 160 * 1024, "a compute unit's LDS");
 };
 
+// Scale, bias and shortcut of a lane's 4 * M consecutive channels.
+template <typename TO, int M> struct OutputOperands {
+    EpiResidual<TO, 4 * M> shortcut;
+    float scale[4 * M], bias[4 * M];
+    static __device__ __forceinline__ bool any(const Epilogue& ep) { return (uintptr_t)ep.residual | (uintptr_t)ep.scale | (uintptr_t)ep.bias; }
+    __device__ __forceinline__ void load(const Epilogue& ep, int64_t pos, int co)
+    {
+        if (ep.residual) shortcut.load(ep, pos, co);
+        if (ep.scale)
+#pragma unroll
+            for (int g = 0; g < M; ++g) *(f32x4*)(scale + 4 * g) = *(const f32x4*)(ep.scale + co + 4 * g);
+        if (ep.bias)
+#pragma unroll
+            for (int g = 0; g < M; ++g) *(f32x4*)(bias + 4 * g) = *(const f32x4*)(ep.bias + co + 4 * g);
+    }
+};
+
 template <typename T, typename TO, int S, int TM, int RT, int CT, int LAY>
 __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                              const char* __restrict__ wfrag, const char* __restrict__ zeros,
@@ -147,18 +164,13 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
     // Scale, bias and shortcut of this lane's outputs come with the first stage, from memory no one has touched yet (asked for behind
     // the last stage instead: 128 -> 128 @ 40 with SiLU 4.82 us, now 4.52; stride 2, 256 -> 256 @ 40 6.36, 6.00).  One branch around all
     // three: a layer without them pays for each (fp32 64 -> 64 @ 56: three branches 5.84 us, one 5.78, none here 5.79).
+    // Not in the 16-bit dense mode at stride 2, where holding them through the stages costs each stage: 64 -> 64 @ 20 3.85 us early, 3.71
+    // late, 512 -> 512 @ 7 8.01 and 7.40, with SiLU 8.19 and 7.51.  (fp32: 256 -> 256 @ 7 10.70 and 10.45, 64 -> 64 @ 20 with shortcut, in
+    // no cache, 5.26 and 5.52)
+    constexpr bool EARLY = S == 1 || LAY != kDenseTaps || sizeof(T) == 4;
     constexpr int RUN = 4 * K::MPT;
-    EpiResidual<TO, RUN> shortcut;
-    float scale[RUN], bias[RUN];
-    if (((uintptr_t)ep.residual | (uintptr_t)ep.scale | (uintptr_t)ep.bias) && o_live) {
-        if (ep.residual) shortcut.load(ep, o_pos, o_co);
-        if (ep.scale)
-#pragma unroll
-            for (int g = 0; g < K::MPT; ++g) *(f32x4*)(scale + 4 * g) = *(const f32x4*)(ep.scale + o_co + 4 * g);
-        if (ep.bias)
-#pragma unroll
-            for (int g = 0; g < K::MPT; ++g) *(f32x4*)(bias + 4 * g) = *(const f32x4*)(ep.bias + o_co + 4 * g);
-    }
+    OutputOperands<TO, K::MPT> output;
+    if (EARLY && output.any(ep) && o_live) output.load(ep, o_pos, o_co);
 
     const int nn = lane & 15, qq = lane >> 4;
     const int pr = nn >> 2, pc = nn & 3;
@@ -266,6 +278,7 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
         }
     }
 
+    if (!EARLY && output.any(ep) && o_live) output.load(ep, o_pos, o_co);
     __syncthreads();  // everybody is done with the slots
 #pragma unroll
     for (int m = 0; m < TM; ++m)
@@ -283,8 +296,8 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[4 * m + e] = sum[e];
     }
-    epi_scale_bias_act<RUN>(v, ep, scale, bias);
-    if (ep.residual) shortcut.add(v);
+    epi_scale_bias_act<RUN>(v, ep, output.scale, output.bias);
+    if (ep.residual) output.shortcut.add(v);
     TO* yp = y + o_pos * ep.ldy + o_co;
     if constexpr (sizeof(TO) == 4) {
 #pragma unroll
