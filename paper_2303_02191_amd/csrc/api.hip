@@ -451,12 +451,13 @@ static rtoss_status conv_impl(const rtoss_wdesc* desc, const rtoss_cdesc* c, con
     if (rtoss_status st = current_device(&cp.dev)) return st;
     if (coherent) return launch_conv3x3_gather(*desc, cp, blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
     // The element-wise kernel reads section 0 and takes any strides (NCHW) and any size.
-    const bool fits = g.format == kFormatSparse24   ? sparse3x3_launch_ok(*desc, cp)
-                      : g.format == kFormatDense3x3 ? dense3x3_launch_ok(*desc, cp)
-                      : g.format == kFormatDense    ? dense1x1_launch_ok(*desc, cp)
-                      : g.format == kFormatStem     ? stem3x3_launch_ok(*desc, cp)
-                                                    : true;
-    if (c->layout == RTOSS_NCHW || !fits || !stores_in_reach(cp))
+    const bool fits = g.format == kFormatSparse24      ? sparse3x3_launch_ok(*desc, cp)
+                      : g.format == kFormatDense3x3    ? dense3x3_launch_ok(*desc, cp)
+                      : g.format == kFormatDense       ? dense1x1_launch_ok(*desc, cp)
+                      : g.format == kFormatStem        ? stem3x3_launch_ok(*desc, cp)
+                      : g.format == kFormatDenseStream ? stream1x1_launch_ok(*desc, cp)
+                                                       : true;
+    if (c->layout == RTOSS_NCHW || !fits)
         return launch_conv_direct(*desc, cp, dict, blob + g.live_off, (const uint8_t*)(blob + g.idx_off), x_dev, y_dev,
                                   (hipStream_t)hip_stream);
     if (g.format == kFormatSparse24)

@@ -119,6 +119,7 @@ rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, in
 // ... large stride-1 layers: pipelined kernel over strips of output rows (conv3x3_rows.hip); same packed section
 rtoss_status launch_conv3x3_rows(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
                                  hipStream_t s);
+bool rows3x3_needs_fused_stage(const ConvParams& c);
 
 // ... launches too small to fill the chip: input channels split over the waves of a workgroup (conv3x3_ksplit.hip).  Reads
 // the packed sections of the sparse kernels (layout 0 or 1) and of the dense-mode kernel (layout 2).
@@ -161,6 +162,7 @@ rtoss_status launch_conv1x1_mma(const rtoss_wdesc& d, const ConvParams& c, const
                                 hipStream_t s);
 
 // 1x1 convolution, streaming kernel with register-resident weights (conv1x1_stream.hip)
+bool stream1x1_launch_ok(const rtoss_wdesc& d, const ConvParams& c);
 bool stream1x1_shape_ok(const rtoss_wdesc& d);
 size_t stream1x1_section_bytes(const rtoss_wdesc& d);
 rtoss_status launch_conv1x1_stream(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,

@@ -381,7 +381,8 @@ __device__ __forceinline__ void whole_rows(const T* __restrict__ x, TO* __restri
                 }
             };
             // (whole sectors; else as the L2 puts them together, and rows may be aligned to an element only)
-            if (aligned_pieces((uintptr_t)y, row, first * EB, (int64_t)ep.ldy * EB, blocks == 1 && ep.ldy == Co ? 16 : kSector)) {
+            const int64_t apart = (int64_t)ep.ldy * EB;
+            if (aligned_pieces((uintptr_t)y, row, first * EB, apart, blocks == 1 && ep.ldy == Co ? 16 : kSector) && PT * apart < kNoStore) {
                 const auto base = store_base(y + p0 * ep.ldy + first);
                 pieces([&](int r, int at, const char* in) { store16_through(base, (uint32_t)r * ep.ldy * EB + at, *(const u32x4*)in); });
             } else {

@@ -618,6 +618,7 @@ inline bool direct_outputs(const rtoss_wdesc& d, const ConvParams& c)
 {
     const int KS = stage_count(d), span = 16 * stream_mt_of(KS) * stream_wm_of(KS, d.Co);
     const bool full = d.Co % span == 0, covered = full && c.ep.act == 2 && (!c.ep.residual || c.out_dt == RTOSS_F32);
+    if (!stores_in_reach(c)) return true;
     if (full && d.dt == RTOSS_F32) return false;
     return (int64_t)c.N * c.H * c.W * d.Co * (int)elem_bytes(c.out_dt) <= (covered ? 1 << 19 : 2 << 20);
 }
@@ -667,10 +668,11 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     return check_hip(hipGetLastError(), "conv1x1 stream launch");
 }
 
+constexpr bool has_direct_outputs(int KS, bool f32) { return KS <= (f32 ? 1 : 2); }
 template <typename T, typename TO, int KS, int WM>
 rtoss_status launch_wm(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
-    if constexpr (KS <= (sizeof(T) == 4 ? 1 : 2))
+    if constexpr (has_direct_outputs(KS, sizeof(T) == 4))
         if (direct_outputs(d, c)) return launch_plan<T, TO, KS, WM, false>(d, c, wfrag, x, y, s);
     return launch_plan<T, TO, KS, WM>(d, c, wfrag, x, y, s);
 }
@@ -714,6 +716,14 @@ bool stream1x1_shape_ok(const rtoss_wdesc& d)
 {
     const int KS = stage_count(d);
     return d.ksize == 1 && d.Ci * elem_bytes(d.dt) % 64 == 0 && d.Co % 16 == 0 && KS >= 1 && KS <= 32 && (KS & (KS - 1)) == 0;
+}
+
+// (fp32 results of 512 channels are stored at 64-bit addresses)
+bool stream1x1_launch_ok(const rtoss_wdesc& d, const ConvParams& c)
+{
+    const int KS = stage_count(d);
+    return stores_in_reach(c) || ksplit1x1_plan(d, c) || has_direct_outputs(KS, d.dt == RTOSS_F32) ||
+           (KS == 16 && d.dt != RTOSS_F32 && c.out_dt == RTOSS_F32);
 }
 
 size_t stream1x1_section_bytes(const rtoss_wdesc& d) { return frag_bytes(d) + zero_section_bytes(stage_count(d)); }

@@ -286,7 +286,7 @@ inline int64_t f32_groups(const rtoss_wdesc& d, const ConvParams& c, int rows)
 // Sums of few live products stay on the fp32 instruction, for their precision (8 -> 72 4x77x91, k = 2: 14.7 us, split 13.9; stride 2 8.5, 7.0).
 int f32_rows(const rtoss_wdesc& d, const ConvParams& c, int64_t cus)
 {
-    if (few_live_products(d)) return 0;
+    if (few_live_products(d) || (!ragged(d) && !stores_in_reach(c))) return 0;
     const int64_t g2 = f32_groups(d, c, 2);
     if (c.stride == 2) return g2 > cus / 2 ? 2 : 0;
     if (ragged(d) ? 2 * g2 < 3 * cus : 8 * g2 < 5 * cus) return 0;

@@ -625,6 +625,7 @@ rtoss_status launch_typed_ragged(const rtoss_wdesc& d, const ConvParams& c, cons
 inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
 {
     if (c.stride != 1 || d.Co <= 64 || d.Ci <= 64 || ragged(d)) return false;
+    if (!rows3x3_needs_fused_stage(c) && c.out_dt != RTOSS_F32 && !stores_in_reach(c)) return false;
     const int64_t tiles8 = (int64_t)((c.H + 15) / 16) * ((c.W + 15) / 16) * c.N * (((d.Co + 15) / 16 + 7) / 8);
     return tiles8 >= 200;
 }

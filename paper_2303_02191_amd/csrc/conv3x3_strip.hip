@@ -597,6 +597,9 @@ int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
     const int plan = plan_within_limits(d, c, layout);
     const int rows = plan > kDenseRows ? plan - kDenseRows : 4 * (plan % kTwoBuffers);
     if (plan == 0 || (int64_t)c.N * c.H * c.W * d.Ci * elem_bytes(d.dt) / 16 > kMaxChunks) return 0;
+    // (fp32, and 16-bit results of two buffers, know rows only)
+    const bool two_buffers = plan < kDenseRows && plan > kTwoBuffers;
+    if (!stores_in_reach(c) && (d.dt == RTOSS_F32 || (two_buffers && c.out_dt != RTOSS_F32))) return 0;
     return (int64_t)((c.W + kCols - 1) / kCols) * ((c.H + rows - 1) / rows) * ((d.Co + 63) / 64) * c.N <= kMaxGridGroups ? plan : 0;
 }
 

@@ -30,7 +30,8 @@ struct ConvParams : rtoss_cdesc {
     DeviceInfo dev;  // asked for once per call
 };
 
-// The matrix-core kernels' stores are 32-bit offsets from a position, of up to 64 positions from there.
+// Stores in whole rows are 32-bit offsets from a position, of up to 64 positions from there: an output pitch that passes them takes a
+// kernel that stores at 64-bit addresses.
 inline bool stores_in_reach(const ConvParams& c) { return (int64_t)c.ep.ldy * 64 * elem_bytes(c.out_dt) < kNoStore; }
 
 // v[i] / (1 + exp(-v[i])), each quotient correctly rounded, whatever type the result is stored in.

@@ -1,7 +1,8 @@
 // Which kernel a convolution call launches, without a GPU: librtoss.so linked against stand-ins for the few runtime calls it
 // makes, on a device of 256 compute units.  Reads calls, one a line,
 //     coherent Co Ci ksize k rule dt  N H W stride out_dt  fused
-// (dt + 16: packs the layer instead, with every allocation refused)
+// (fused: 1 a whole output stage into a channel slice, more the same at that pitch, less than 0 a pitch and nothing else; dt + 16: packs
+// the layer instead, with every allocation refused)
 // and prints the status, the launched kernel's handle (its offset in the library), the dynamic LDS it was launched with and the
 // limit that was set for it.
 #include <dlfcn.h>
@@ -61,7 +62,11 @@ int main()
         e.scale_dev = e.bias_dev = (const float*)base;
         e.residual_dev = y + ((size_t)1 << 42);
         e.act = RTOSS_ACT_SILU;
-        e.y_ld = e.residual_ld = (d.Co + 7) / 8 * 8 + 16;  // a channel slice
+        e.y_ld = e.residual_ld = fused > 1 ? fused : (d.Co + 7) / 8 * 8 + 16;
+        if (fused < 0) {
+            e = rtoss_epilogue{};
+            e.y_ld = -fused;
+        }
         g_kernel = nullptr;
         g_lds = 0;
         g_refuse = dt & 16;

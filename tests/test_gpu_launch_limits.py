@@ -61,31 +61,62 @@ def test_calls_past_a_kernels_launch_limits(case):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("dt,Ci,ks", [(wl.F16, 64, 1), (wl.BF16, 512, 1), (wl.F32, 64, 1), (wl.F16, 72, 1), (wl.BF16, 128, 3), (wl.F32, 64, 3)],
-                         ids=lambda v: str(v))
-def test_output_pitch_past_32_bit_offsets(dt, Ci, ks):
-    """Positions so far apart that 64 of them span 4 GiB: by the element-wise kernel, equal within the rounding of the stored value and
-    the fp32 sums."""
-    P, Co, k = 70, 32, 2
-    pitch = (1 << 32) // 64 // wl.ELEM_BYTES[dt]
+# Output pitches past the 32-bit offsets of stores in whole rows: dt, out_dt, N, Ci, Co, H, W, ks, stride, k, fused, coherent; the kernel
+# while 64 positions are within 32 bits, and beyond (test_routes.py)
+PITCH_CASES = [
+    (wl.F16, wl.F16, 1, 64, 48, 1, 70, 1, 1, 2, True, False, "conv1x1_stream<2,1,false>", "conv1x1_stream<2,1,false>"),
+    (wl.F16, wl.F16, 1, 128, 640, 4, 500, 1, 1, 2, True, False, "conv1x1_stream<4,4>", "conv_direct<1,1,0>"),
+    (wl.F32, wl.F32, 1, 16, 64, 1, 70, 1, 1, 2, True, False, "conv1x1_stream<1,1>", "conv1x1_stream<1,1,false>"),
+    (wl.F16, wl.F16, 1, 72, 32, 1, 70, 1, 1, 2, False, False, "conv1x1_mma<1,2,true>", "conv1x1_mma<1,2,true>"),
+    (wl.F16, wl.F16, 1, 128, 16384, 20, 16, 3, 1, 3, False, False, "conv3x3_rows<false>", "conv3x3_sparse_sb<1,4,2,2,4,true,0,true,false>"),
+    (wl.F16, wl.F16, 1, 128, 16384, 20, 16, 3, 1, 3, True, False, "conv3x3_rows<true>", "conv3x3_rows<true>"),
+    (wl.BF16, wl.BF16, 1, 128, 8192, 20, 16, 3, 1, 3, True, False, "conv3x3_strip<3,0,true>", "conv3x3_sparse_sb<1,4,2,2,4,true,0,true,false>"),
+    (wl.BF16, wl.BF16, 1, 128, 16384, 20, 16, 3, 1, 5, False, False, "conv3x3_strip<20,true>", "conv3x3_strip<20>"),
+    (wl.F32, wl.F32, 1, 64, 16384, 20, 16, 3, 1, 3, False, False, "conv3x3_strip<8>", "conv3x3_dense<1,1,1,4,false>"),
+    (wl.F32, wl.F32, 1, 64, 2048, 20, 16, 3, 1, 3, True, False, "conv3x3_dense<1,4,false>", "conv3x3_dense<1,1,1,4,false>"),
+    (wl.BF16, wl.BF16, 1, 256, 16384, 20, 16, 3, 1, 3, False, True, "conv3x3_gather_rows<>", "conv3x3_gather<1>"),
+    (wl.BF16, wl.BF16, 1, 128, 32, 1, 70, 3, 1, 2, True, False, "conv3x3_ksplit<1,1,1,2,0>", "conv3x3_ksplit<1,1,1,2,0>"),
+    (wl.F16, wl.F16, 1, 3, 32, 9, 17, 3, 1, 2, True, False, "conv3x3_stem<1,2,3>", "conv3x3_stem<1,2,3>"),
+]
+
+
+@pytest.mark.parametrize("case", PITCH_CASES, ids=lambda c: "-".join(map(str, c[:10])))
+@pytest.mark.parametrize("rows", [64, 15], ids=lambda r: "%d_rows" % r)
+def test_output_pitch_past_32_bit_offsets(case, rows):
+    """Positions so far apart that 64 (15) of them span 4 GiB, where an offset of 32 bits would wrap: equal within the rounding of the
+    stored value and the fp32 sums (another kernel may take the call)."""
+    dt, out_dt, N, Ci, Co, H, W, ks, stride, k, fused, coherent = case[:12]
+    P, eb = H * W, wl.ELEM_BYTES[out_dt]
+    pitch = -(-(1 << 32) // rows // (eb * 16)) * 16
+    if rows == 15 and P > 400:
+        pytest.skip("64 rows apart are enough for a buffer of %d GB" % (P * pitch * eb >> 30))
     torch.cuda.empty_cache()
-    if torch.cuda.mem_get_info()[0] < (P + 1) * pitch * wl.ELEM_BYTES[dt] + (2 << 30):
-        pytest.skip("needs %d GB of device memory" % (P * pitch * wl.ELEM_BYTES[dt] >> 30))
+    if P * pitch * eb + (4 << 30) > torch.cuda.mem_get_info()[0]:
+        pytest.skip("needs %d GB of device memory" % (P * pitch * eb >> 30))
     rng = np.random.default_rng(Ci)
     masks = B.rtoss_pattern_dict(k)
-    ws = wl.round_to_dtype(rng.standard_normal((Co, Ci, ks, ks)), dt)
-    layer = GpuLayer(ws, dt, masks, k).layer
-    xs = wl.round_to_dtype(rng.standard_normal((1, Ci, 1, P)), dt)
-    x = pl.to_device(wl.nchw_to_nhwc(xs), dt)
-    wide = torch.empty((1, 1, P, pitch), dtype=pl.TORCH_DTYPE[dt], device="cuda")
+    ws = wl.round_to_dtype(rng.standard_normal((Co, Ci, ks, ks)) / np.sqrt(Ci * k), dt)
+    packed = GpuLayer(ws, dt, masks, k)
+    layer = packed.layer
+    x = pl.to_device(wl.round_to_dtype(rng.standard_normal((N, H, W, Ci)), dt), dt)
+    stage = dict(scale=torch.rand(Co, device="cuda") + 0.5, bias=torch.randn(Co, device="cuda"), act=B.ACT_SILU) if fused else {}
+    wide = torch.empty((N, H, W, pitch), dtype=pl.TORCH_DTYPE[out_dt], device="cuda")
     wide[..., Co:Co + 64] = 7
-    got = layer.conv_fused(x, y=wide[..., :Co]).float()
-    near = layer.conv_fused(x).float()
+    near = layer.conv_fused(x, out_dt=out_dt, **stage).float()
+    if coherent:
+        layer = pl.CoherentLayer(Co, Ci, k, dt, masks).pack(packed.w, packed.idx)
+        e = B.EpilogueDesc(None, None, B.ACT_NONE, None, pitch, 0)
+        B.rtoss_conv2d_pattern_coherent(layer.wdesc, B.CDesc(N, H, W, stride, ks // 2, B.NHWC, out_dt, 0), e, masks, layer.blob.data_ptr(),
+                                        x.data_ptr(), wide.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        got = wide[..., :Co].float()
+    else:
+        got = layer.conv_fused(x, out_dt=out_dt, y=wide[..., :Co], **stage).float()
     peak = float(near.abs().max())
-    bound = 1e-5 * peak + near.abs() * {wl.F32: 0.0, wl.F16: 2.0 ** -10, wl.BF16: 2.0 ** -7}[dt]
+    bound = 1e-5 * peak + near.abs() * {wl.F32: 0.0, wl.F16: 2.0 ** -10, wl.BF16: 2.0 ** -7}[out_dt]
     assert ((got - near).abs() <= bound).all()
     assert (wide[..., Co:Co + 64] == 7).all()
     del wide
+    torch.cuda.empty_cache()
 
 
 # The pipelined 3x3 kernel's output through LDS (a fused stage, fp32 results): a tile of 20 rows of 16 positions.

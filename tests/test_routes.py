@@ -17,7 +17,7 @@ from variants import OWN_TYPE_OUT, VARIANTS
 
 
 def call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, fused, coherent=False, rule=B.RULE_CONNECTED4):
-    return (dt, N, Ci, Co, H, W, ks, stride, k, rule, out_dt, int(fused), int(coherent))
+    return (dt, N, Ci, Co, H, W, ks, stride, k, rule, out_dt, int(fused), int(coherent))  # (fused: route_probe.cpp)
 
 
 def split(kernel):
@@ -114,3 +114,23 @@ def test_wide_tile_reaches_the_pipelined_kernel():
     calls = [call(wl.F16, s["N"], s["Ci"], s["Co"], s["H"], s["W"], s["ks"], s["stride"], s["k"], out_dt, fused)
              for out_dt, fused in ((wl.F16, True), (wl.F32, True), (wl.F32, False))]
     assert families(routes.kernels(calls)) == ["conv3x3_rows"] * 3
+
+
+def test_output_pitches_past_32_bit_offsets():
+    """Kernels that store whole rows at 32-bit offsets take a call up to the longest pitch of which 64 positions are within them, and
+    no further; those that do not are not asked to leave it.  (A pitch: more than 1 with a whole output stage, less than 0 alone.)"""
+    for case in test_gpu_launch_limits.PITCH_CASES:
+        dt, out_dt, N, Ci, Co, H, W, ks, stride, k, fused, coherent, within, beyond = case
+        longest = (0xffffff00 - 1) // 64 // 64 * 64 // wl.ELEM_BYTES[out_dt]  # (whole sectors of 64 bytes)
+        for pitch, want in ((longest, within), (longest + 64, beyond)):
+            got = routes.kernels([call(dt, N, Ci, Co, H, W, ks, stride, k, out_dt, pitch if fused else -pitch, coherent)])[0]
+            assert split(got)[0] == want, (case, pitch)
+    # larger launches than a test has memory for; the resident stride-2 kernel's own limit: four rows of outputs
+    for call_args, longest, within, beyond in (
+            ((wl.F32, 1, 64, 64, 160, 160, 1, 1, 2, wl.F32), (0xffffff00 - 1) // 256 // 16 * 16, "conv1x1_stream<4>", "conv_direct<1,1,0>"),
+            ((wl.BF16, 1, 512, 16, 120, 130, 1, 1, 2, wl.F32), (0xffffff00 - 1) // 256 // 16 * 16, "conv1x1_stream<16,2>", "conv1x1_stream<16,2>"),
+            ((wl.BF16, 1, 512, 16, 120, 130, 1, 1, 2, wl.BF16), (0xffffff00 - 1) // 128 // 32 * 32, "conv1x1_stream<16,2>", "conv_direct<1,1,0>"),
+            ((wl.F16, 1, 64, 448, 180, 180, 3, 2, 2, wl.F16), (0xffffff00 - 1) // (2 * (3 * 90 + 4)) // 32 * 32, "conv3x3_resident<2>",
+             "conv3x3_sparse_sb<2,4,1,1,4,true,0,false,false>")):
+        got = routes.kernels([call(*call_args, -pitch) for pitch in (longest, longest + 64)])
+        assert [split(g)[0] for g in got] == [within, beyond]
