@@ -11,6 +11,7 @@ import test_gpu_ksplit
 import test_gpu_ksplit1x1
 import test_gpu_launch_limits
 import test_gpu_slices
+import test_gpu_stream1x1
 import test_gpu_stride2_rows
 import test_gpu_strip
 from variants import OWN_TYPE_OUT, VARIANTS
@@ -80,6 +81,26 @@ def test_cases_made_for_a_kernel_reach_it(fused):
     assert families(routes.kernels(calls)) == ["conv3x3_sparse_sb"] * len(calls)
     calls = [call(c[0], *c[2:], 3, 2, c[1], c[0], fused) for c in test_gpu_stride2_rows.RESIDENT_CASES]
     assert families(routes.kernels(calls)) == ["conv3x3_resident"] * len(calls)
+    calls = [call(dt, 1, Ci, Co, 1, P, 1, 1, 2, out_dt, fused) for dt, Ci, Co, P in test_gpu_stream1x1.CASES for out_dt in (dt, wl.F32)]
+    assert families(routes.kernels(calls)) == ["conv1x1_stream"] * len(calls)
+
+
+def test_streaming_cases_cover_the_turns():
+    """The buffers of a workgroup in test_gpu_stream1x1's cases, with one helper wave and with two: one, two, three and more, with at
+    least two and at most four workgroups a compute unit (16 positions a wave along positions; at least two buffers a workgroup)."""
+    calls = [call(dt, 1, Ci, Co, 1, P, 1, 1, 2, dt, True) for dt, Ci, Co, P in test_gpu_stream1x1.CASES]
+    turns = {1: set(), 2: set()}
+    for (dt, Ci, Co, P), kernel in zip(test_gpu_stream1x1.CASES, routes.kernels(calls)):
+        args = split(kernel)[0][:-1].split("<")[1].split(",")
+        if len(args) == 1:
+            continue  # (the fp32 kernel without helpers)
+        KS, WM = int(args[0]), int(args[1])
+        helpers = 2 if KS >= 8 or 4 // WM * KS >= 16 else 1
+        buffers, blocks = -(-P * WM // 64), -(-Co // (16 * WM * {32: 1, 16: 2}.get(KS, 4)))
+        for per_cu in (2, 3, 4):
+            groups = max(1, min((buffers + 1) // 2, 256 * per_cu // blocks))
+            turns[helpers] |= {min(4, buffers // groups), min(4, -(-buffers // groups))}
+    assert turns == {1: {1, 2, 3, 4}, 2: {1, 2, 3, 4}}
 
 
 def test_slices_reach_the_kernel_they_name():
