@@ -137,12 +137,7 @@ __global__ __launch_bounds__(256) void conv1x1_ksplit_kernel(const T* __restrict
             } else {
 #pragma unroll
                 for (int g8 = 0; g8 < RUNT / 2; ++g8) {
-                    u32x4 o;
-                    o.x = pack2_from_f32<TO>(v[8 * g8 + 0], v[8 * g8 + 1]);
-                    o.y = pack2_from_f32<TO>(v[8 * g8 + 2], v[8 * g8 + 3]);
-                    o.z = pack2_from_f32<TO>(v[8 * g8 + 4], v[8 * g8 + 5]);
-                    o.w = pack2_from_f32<TO>(v[8 * g8 + 6], v[8 * g8 + 7]);
-                    *(u32x4*)(yp + 8 * g8) = o;
+                    *(u32x4*)(yp + 8 * g8) = pack8_from_f32<TO>(v + 8 * g8);
                 }
             }
         }

@@ -291,12 +291,7 @@ __device__ __forceinline__ void stream_outputs(const T* __restrict__ x, TO* __re
                 const uint32_t at = live ? ((uint32_t)row * ep.ldy + co_lane) * EB : kNoStore;
 #pragma unroll
                 for (int g = 0; g < RUN / 8; ++g) {
-                    u32x4 o;
-                    o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
-                    o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
-                    o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
-                    o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
-                    store16_through(base, at + 16 * g, o);
+                    store16_through(base, at + 16 * g, pack8_from_f32<TO>(v + 8 * g));
                 }
             }
         };
@@ -406,12 +401,7 @@ __device__ __forceinline__ void stream_outputs(const T* __restrict__ x, TO* __re
             } else {
 #pragma unroll
                 for (int g = 0; g < MT / 2; ++g) {
-                    u32x4 o;
-                    o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
-                    o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
-                    o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
-                    o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
-                    *(u32x4*)piece(g) = o;
+                    *(u32x4*)piece(g) = pack8_from_f32<TO>(v + 8 * g);
                 }
             }
             slot = slot + 1 == RING ? 0 : slot + 1;

@@ -310,12 +310,7 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
     } else {
 #pragma unroll
         for (int g = 0; g < K::MPT / 2; ++g) {
-            u32x4 o;
-            o.x = pack2_from_f32<TO>(v[8 * g + 0], v[8 * g + 1]);
-            o.y = pack2_from_f32<TO>(v[8 * g + 2], v[8 * g + 3]);
-            o.z = pack2_from_f32<TO>(v[8 * g + 4], v[8 * g + 5]);
-            o.w = pack2_from_f32<TO>(v[8 * g + 6], v[8 * g + 7]);
-            *(u32x4*)(yp + 8 * g) = o;
+            *(u32x4*)(yp + 8 * g) = pack8_from_f32<TO>(v + 8 * g);
         }
     }
 }

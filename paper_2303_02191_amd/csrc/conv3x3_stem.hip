@@ -154,12 +154,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(cons
                         *(f32x4*)(yp + 16 * mp) = f32x4{vv[0], vv[1], vv[2], vv[3]};
                         *(f32x4*)(yp + 16 * mp + 4) = f32x4{vv[4], vv[5], vv[6], vv[7]};
                     } else {
-                        u32x4 o;
-                        o.x = pack2_from_f32<TO>(vv[0], vv[1]);
-                        o.y = pack2_from_f32<TO>(vv[2], vv[3]);
-                        o.z = pack2_from_f32<TO>(vv[4], vv[5]);
-                        o.w = pack2_from_f32<TO>(vv[6], vv[7]);
-                        *(u32x4*)(yp + 16 * mp) = o;
+                        *(u32x4*)(yp + 16 * mp) = pack8_from_f32<TO>(vv);
                     }
                 }
             }

@@ -418,11 +418,7 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
 #pragma unroll
                 for (int g = 0; g < 2; ++g) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
             } else {
-                u32x4 o;
-                o.x = pack2_from_f32<TO>(v[0], v[1]);
-                o.y = pack2_from_f32<TO>(v[2], v[3]);
-                o.z = pack2_from_f32<TO>(v[4], v[5]);
-                o.w = pack2_from_f32<TO>(v[6], v[7]);
+                const u32x4 o = pack8_from_f32<TO>(v);
                 if constexpr (ROWS_OUT) *(u32x4*)(smem + (half * RW + j) * RowTile<TO>::kBytes + RowTile<TO>::chunk_at(nn, 2 * qq + pair)) = o;
                 else *(u32x4*)yp = o;
             }

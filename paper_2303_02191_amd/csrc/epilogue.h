@@ -34,6 +34,14 @@ struct ConvParams : rtoss_cdesc {
 // kernel that stores at 64-bit addresses.
 inline bool stores_in_reach(const ConvParams& c) { return (int64_t)c.ep.ldy * 64 * elem_bytes(c.out_dt) < kNoStore; }
 
+template <typename TO> __device__ __forceinline__ u32x4 pack8_from_f32(const float* v)
+{
+    u32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = pack2_from_f32<TO>(v[2 * i], v[2 * i + 1]);
+    return o;
+}
+
 // v[i] / (1 + exp(-v[i])), each quotient correctly rounded, whatever type the result is stored in.
 //
 // The IEEE division is ten vector instructions, four cycles each, and would be most of the output stage (a 57-layer
@@ -42,23 +50,31 @@ inline bool stores_in_reach(const ConvParams& c) { return (int64_t)c.ep.ldy * 64
 // Dev. 34, 1990) makes up for that: compared with the division for every one of the 2^32 values of v on the device, no bit
 // differs.  That holds while nothing in between leaves the normal range, so runs with a large |v| take the division.
 // (The remainder is formed as d * q - v: with the other sign -0 would turn into +0.)
+constexpr float kSiluInRange = 80.f;  // the largest |v| that takes the corrected reciprocal
+__device__ __forceinline__ float silu_divided(float v) { return v / (1.f + __expf(-v)); }
+// (d: 1 + exp(-v); r: its reciprocal)
+__device__ __forceinline__ float silu_corrected(float v, float d, float r)
+{
+    const float q = v * r;
+    return __builtin_fmaf(-__builtin_fmaf(d, q, -v), r, q);
+}
 template <int N> __device__ __forceinline__ void epi_silu(float (&v)[N])
 {
     float top = 0.f;
 #pragma unroll
     for (int i = 0; i < N; ++i) top = __builtin_fmaxf(top, __builtin_fabsf(v[i]));  // (a NaN stays one either way)
-    if (__builtin_expect(__ballot(top > 80.f) != 0, 0)) {  // (the whole wave: a scalar branch)
+    if (__builtin_expect(__ballot(top > kSiluInRange) != 0, 0)) {  // (the whole wave: a scalar branch)
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             asm volatile("" : "+v"(v[i]));  // keeps the exponentials, which both sides need, from being held across the branch
-            v[i] = v[i] / (1.f + __expf(-v[i]));
+            v[i] = silu_divided(v[i]);
         }
         return;
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const float d = 1.f + __expf(-v[i]), r = __builtin_amdgcn_rcpf(d), q = v[i] * r;
-        v[i] = __builtin_fmaf(-__builtin_fmaf(d, q, -v[i]), r, q);
+        const float d = 1.f + __expf(-v[i]);
+        v[i] = silu_corrected(v[i], d, __builtin_amdgcn_rcpf(d));
     }
 }
 // The same in N + 2 parts without a branch, for kernels that put matrix instructions between them, and an end: part J takes value
@@ -72,18 +88,15 @@ __device__ __forceinline__ void epi_silu_part(const float (&u)[N], float (&v)[N]
         d[J] = 1.f + __expf(-u[J]);
     }
     if constexpr (J >= 1 && J - 1 < N) v[J - 1] = __builtin_amdgcn_rcpf(d[J - 1]);
-    if constexpr (J >= 2) {
-        const float r = v[J - 2], q = u[J - 2] * r;
-        v[J - 2] = __builtin_fmaf(-__builtin_fmaf(d[J - 2], q, -u[J - 2]), r, q);
-    }
+    if constexpr (J >= 2) v[J - 2] = silu_corrected(u[J - 2], d[J - 2], v[J - 2]);
 }
 template <int N> __device__ __forceinline__ void epi_silu_end(const float (&u)[N], float (&v)[N], float top)
 {
 #pragma unroll
     for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));  // keeps the parts in front of the branch
-    if (__builtin_expect(__ballot(top > 80.f) != 0, 0)) {
+    if (__builtin_expect(__ballot(top > kSiluInRange) != 0, 0)) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = u[i] / (1.f + __expf(-u[i]));
+        for (int i = 0; i < N; ++i) v[i] = silu_divided(u[i]);
     }
 }
 // (one uniform branch per activation around the whole run, not one per value)
@@ -101,7 +114,7 @@ template <int N> __device__ __forceinline__ void epi_act(float (&v)[N], int act)
 // multiples of 4).  Scale, bias and activation; the branches are uniform over the launch.  `scale` and `bias` point at
 // the run's first channel (in device memory, or at a copy in LDS) and are read only where ep has them.
 template <int N>
-__device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
+__device__ __forceinline__ void epi_scale_bias(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
 {
     static_assert(N % 4 == 0, "runs of 4 channels");
     if (ep.scale) {
@@ -120,6 +133,11 @@ __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue
             for (int i = 0; i < 4; ++i) v[4 * g + i] += b[i];
         }
     }
+}
+template <int N>
+__device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
+{
+    epi_scale_bias<N>(v, ep, scale, bias);
     epi_act<N>(v, ep.act);
 }
 template <int N> __device__ __forceinline__ void epi_scale_bias_act(float (&v)[N], const Epilogue& ep, int co)
@@ -140,22 +158,6 @@ template <bool NONE = true, typename F> __device__ __forceinline__ void epi_by_f
     else run(std::integral_constant<int, kEpiAny>{});
 }
 template <int FORM, int N>
-__device__ __forceinline__ void epi_scale_bias_act_of(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
-{
-    if constexpr (FORM == kEpiSilu) {
-#pragma unroll
-        for (int g = 0; g < N / 4; ++g) {
-            const f32x4 s = *(const f32x4*)(scale + 4 * g), b = *(const f32x4*)(bias + 4 * g);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[4 * g + i] = __builtin_fmaf(v[4 * g + i], s[i], b[i]);
-        }
-        epi_silu<N>(v);
-    } else if constexpr (FORM == kEpiAny) {
-        epi_scale_bias_act<N>(v, ep, scale, bias);
-    }
-}
-
-template <int FORM, int N>
 __device__ __forceinline__ void epi_scale_bias_of(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
 {
     if constexpr (FORM == kEpiSilu) {
@@ -166,23 +168,15 @@ __device__ __forceinline__ void epi_scale_bias_of(float (&v)[N], const Epilogue&
             for (int i = 0; i < 4; ++i) v[4 * g + i] = __builtin_fmaf(v[4 * g + i], s[i], b[i]);
         }
     } else if constexpr (FORM == kEpiAny) {
-        if (ep.scale) {
-#pragma unroll
-            for (int g = 0; g < N / 4; ++g) {
-                const f32x4 s = *(const f32x4*)(scale + 4 * g);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[4 * g + i] *= s[i];
-            }
-        }
-        if (ep.bias) {
-#pragma unroll
-            for (int g = 0; g < N / 4; ++g) {
-                const f32x4 b = *(const f32x4*)(bias + 4 * g);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[4 * g + i] += b[i];
-            }
-        }
+        epi_scale_bias<N>(v, ep, scale, bias);
     }
+}
+template <int FORM, int N>
+__device__ __forceinline__ void epi_scale_bias_act_of(float (&v)[N], const Epilogue& ep, const float* scale, const float* bias)
+{
+    epi_scale_bias_of<FORM, N>(v, ep, scale, bias);
+    if constexpr (FORM == kEpiSilu) epi_silu<N>(v);
+    else if constexpr (FORM == kEpiAny) epi_act<N>(v, ep.act);
 }
 
 // Adds the residual's N consecutive channels, starting at channel co, of position number `pos` (n, oh, ow
@@ -318,13 +312,7 @@ __device__ __forceinline__ void pair_pieces(u32x4& a, u32x4& b, bool odd)
 // A lane's run of 16 channels in 16 bits.
 template <typename TO> struct Run16 {
     u32x4 half[2];
-    __device__ __forceinline__ explicit Run16(const float (&v)[16])
-    {
-#pragma unroll
-        for (int g = 0; g < 2; ++g)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) half[g][i] = pack2_from_f32<TO>(v[8 * g + 2 * i], v[8 * g + 2 * i + 1]);
-    }
+    __device__ __forceinline__ explicit Run16(const float (&v)[16]) : half{pack8_from_f32<TO>(v), pack8_from_f32<TO>(v + 8)} {}
     __device__ __forceinline__ void store(TO* yp) const
     {
         *(u32x4*)yp = half[0];
