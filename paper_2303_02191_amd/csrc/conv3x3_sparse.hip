@@ -369,20 +369,21 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
 #pragma unroll
                     for (int g = 0; g < 4; ++g) *(f32x4*)(yp + co + 4 * g) = f32x4{vv[4 * g], vv[4 * g + 1], vv[4 * g + 2], vv[4 * g + 3]};
                 } else {
-                    Run16<TO> o(vv);
+                    u32x4 o[2] = {pack8_from_f32<TO>(vv), pack8_from_f32<TO>(vv + 8)};
                     if constexpr (!PATCH) {
                         if (!mine) continue;
-                        o.store(yp + co);
+#pragma unroll
+                        for (int g = 0; g < 2; ++g) *(u32x4*)(yp + co + 8 * g) = o[g];
                         continue;
                     }
                     // stride 2: rows of 128 bytes past the L2's write-back (us before, with; 16 images: 32 -> 64 @ 320 44.8 42.7, 64 -> 128 @ 160
                     // 30.2 29.7, 128 -> 256 @ 80 27.6 26.8, 256 -> 512 @ 40 22.4 21.6; stride 1, 32 -> 32 @ 160: 25.5 26.4)
                     const int odd = lane & 1;  // (the column's parity too)
-                    pair_pieces(o.half[0], o.half[1], odd);
+                    pair_pieces(o[0], o[1], odd);
                     const bool row = row_inside && co < Co;
                     TO* yc = yp - odd * (int64_t)ep.ldy + co + 8 * odd;
-                    if (row && ow - odd < Wo) store16_through(yc, o.half[0]);
-                    if (row && ow - odd + 1 < Wo) store16_through(yc + ep.ldy, o.half[1]);
+                    if (row && ow - odd < Wo) store16_through(yc, o[0]);
+                    if (row && ow - odd + 1 < Wo) store16_through(yc + ep.ldy, o[1]);
                 }
             }
         }
@@ -538,15 +539,15 @@ __global__ __launch_bounds__(64 * Resident<STAGES>::WAVES) __attribute__((amdgpu
                 for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][e];
             epi_scale_bias_act_of<decltype(form)::value, 16>(v, ep, lds_ep + 16 * qq, lds_ep + 64 + 16 * qq);
             if (row_inside && ow0 + pc < Wo) epi_residual<T, 16>(v, ep, pos0 + pr * Wo + pc, 64 * cb + 16 * qq);
-            Run16<T> o(v);
-            pair_pieces(o.half[0], o.half[1], odd);
+            u32x4 o[2] = {pack8_from_f32<T>(v), pack8_from_f32<T>(v + 8)};
+            pair_pieces(o[0], o[1], odd);
             const auto base = store_base(y + pos0 * ep.ldy + 64 * cb);
             const uint32_t to = (uint32_t)((pr * Wo + pc - odd) * ep.ldy + 16 * qq + 8 * odd) * 2;  // (within 32 bits: resident_ok)
             uint32_t to0 = row_inside && ow0 + pc - odd < Wo ? to : kNoStore, to1 = row_inside && ow0 + pc - odd + 1 < Wo ? to + 2 * ep.ldy : kNoStore;
             asm("" : "+v"(to0), "+v"(to1));  // (always two stores, for the count above: not a branch around each)
             __builtin_amdgcn_sched_barrier(0);
-            store16_through(base, to0, o.half[0]);
-            store16_through(base, to1, o.half[1]);
+            store16_through(base, to0, o[0]);
+            store16_through(base, to1, o[1]);
             __builtin_amdgcn_sched_barrier(0);
         }
     });
