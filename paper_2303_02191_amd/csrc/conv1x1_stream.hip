@@ -27,6 +27,7 @@
 //     them back (copies of 13 MB: 6.1 us, past it 5.4).  In pieces of 16 bytes that would cost more than it saves.
 //     us with stores from the accumulators / with tiles / with tiles past the write-back: 64 -> 64 channels on 102 400
 //     positions with SiLU 8.0  8.2  6.6, 128 -> 128 on 102 400 12.3  12.6  11.1, 256 -> 256 on 25 600 11.0  11.0  9.6.
+//     Outputs of up to 2 MB, which are written back in no time, stay with the first way (direct_outputs).
 //   * 512 channels: two or three buffers a workgroup and a wave to a SIMD, so that a turn is the sum of its parts.  The consumers
 //     put the output stage of a buffer between the matrix instructions of the next one instead, and store from there (16-bit results
 //     in rows of 64 bytes; a tile would be a turn more): 512 -> 256 on 6400 positions with SiLU 7.0 -> 6.2 us, 512 -> 512 9.4 -> 7.9.
@@ -417,16 +418,16 @@ __device__ __forceinline__ void stream_outputs(const T* __restrict__ x, TO* __re
 }
 
 template <typename T, typename TO, int KS, int WM>
-__global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
-                                                                             const char* __restrict__ zeros, int64_t P, int Co, int co_blocks,
-                                                                             Share share, int total_wgs, int work_per_xcd, Epilogue ep)
+__global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM)))
+void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros, int64_t P,
+                           int Co, int co_blocks, Share share, int total_wgs, int work_per_xcd, Epilogue ep)
 {
     stream_outputs<T, TO, KS, WM, !Plan<KS, WM>::INTERLEAVED>(x, y, wfrag, zeros, P, Co, co_blocks, share, total_wgs, work_per_xcd, ep);
 }
 template <typename T, typename TO, int KS, int WM, bool TILE>
-__global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM))) void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
-                                                                             const char* __restrict__ zeros, int64_t P, int Co, int co_blocks,
-                                                                             Share share, int total_wgs, int work_per_xcd, Epilogue ep)
+__global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM)))
+void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros, int64_t P,
+                           int Co, int co_blocks, Share share, int total_wgs, int work_per_xcd, Epilogue ep)
 {
     stream_outputs<T, TO, KS, WM, TILE>(x, y, wfrag, zeros, P, Co, co_blocks, share, total_wgs, work_per_xcd, ep);
 }
@@ -638,7 +639,8 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
         // The dispatcher spreads a workgroup's waves over the four SIMDs but does not fill every hole: of `waves` that fit a SIMD,
         // workgroups of five were resident at two per compute unit for four, three for five and four for six, one less
         // than the query says.  Workgroups beyond that are a second round of a launch planned for one
-        // (128 -> 128 on 102 400 positions: 13.5 us with 768 of which 512 fit, 12.3 with 512).
+        // (128 -> 128 on 102 400 positions: 13.5 us with 768 of which 512 fit, 12.3 with 512; 280 shapes 0.96 of the time with the
+        // query's number.  Workgroups of six come out at the query's number or within 2 % of its time).
         int waves = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&waves, (const void*)kern, 256, 0) == hipSuccess)
             per_cu = std::max(1, std::min(per_cu, (4 * waves - 4 + PL::HELPERS) / (4 + PL::HELPERS)));

@@ -603,7 +603,7 @@ __device__ __forceinline__ void gather_rows_body(char* smem, const T* __restrict
             // the last matrix instructions must have written their accumulators before anything reads them
             asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
             // ---- epilogue: a lane holds 16 consecutive channels of its block for column nn of each of its rows
-            // (the packer dealt the rows that way): 32 contiguous bytes per lane ----
+            // (the packer dealt the rows that way) ----
             {
                 int lane_e = lane;
                 asm volatile("" : "+v"(lane_e));

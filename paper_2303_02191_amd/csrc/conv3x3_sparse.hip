@@ -30,8 +30,9 @@
 // (8 channels of one tap) and the 4x4 (tap, channel) blocks are transposed in registers
 // with byte permutes so that one lane holds, for 4 channels, the 4 taps of a group.
 //
-// This file holds the single-buffered kernel (stride 2, but for shallow layers in large launches, which have one of their own here; ragged channel counts, and stride-1 layers of up to 64 input or
-// output channels in launches of many rounds): a plain loop nest with small tiles, several workgroups per compute unit.
+// This file holds the single-buffered kernel (stride 2, but for shallow layers in large launches, which have one of their own
+// here; ragged channel counts, and stride-1 layers of up to 64 input or output channels in launches of many rounds): a plain
+// loop nest with small tiles, several workgroups per compute unit.
 // Large stride-1 layers take the pipelined kernel of conv3x3_rows.hip, launches of medium size the strips of
 // conv3x3_strip.hip, and those that cannot fill the chip conv3x3_ksplit.hip; all read the same packed section.
 #include <algorithm>
@@ -376,8 +377,9 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
                         for (int g = 0; g < 2; ++g) *(u32x4*)(yp + co + 8 * g) = o[g];
                         continue;
                     }
-                    // stride 2: rows of 128 bytes past the L2's write-back (us before, with; 16 images: 32 -> 64 @ 320 44.8 42.7, 64 -> 128 @ 160
-                    // 30.2 29.7, 128 -> 256 @ 80 27.6 26.8, 256 -> 512 @ 40 22.4 21.6; stride 1, 32 -> 32 @ 160: 25.5 26.4)
+                    // stride 2: rows of 128 bytes past the L2's write-back (us before, with, 16 images with SiLU, tensors in caches, then in
+                    // none: 128 -> 256 @ 80 24.7 23.2, 31.7 31.4, 256 -> 512 @ 40 19.6 19.0, 25.8 26.0; not at stride 1: 32 -> 32 @ 160 in a
+                    // 57-layer forward 25.5 26.4)
                     const int odd = lane & 1;  // (the column's parity too)
                     pair_pieces(o[0], o[1], odd);
                     const bool row = row_inside && co < Co;
@@ -393,11 +395,12 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     else epi_by_form(ep, [&](auto form) { finish(std::false_type{}, form); });
 }
 
-// Stride 2, layers of one or two stages of input channels in large launches: half of what the kernel above copies for 64 positions is weights,
-// and its workgroups are chains of copy, products and stores.  Here a workgroup keeps the weights of its 64 channels, and its waves go over
-// blocks of 4x4 positions by themselves, without a barrier: while a wave multiplies a stage's 9x9 patch, the next one is on its way into
-// a buffer of its own.  32 -> 64 on 16x320x320 with SiLU 42.3 -> 34.3 us (4.6 TB/s, the rate of a copy), 64 -> 128 on 16x160x160 33.6 -> 28.3: bound by the
-// instructions around the products there (block numbers by division instead of addition: 29.4; three buffers a wave: 30.3).
+// Stride 2, layers of one or two stages of input channels in large launches: half of what the kernel above copies for 64
+// positions is weights, and its workgroups are chains of copy, products and stores.  Here a workgroup keeps the weights of its 64
+// channels, and its waves go over blocks of 4x4 positions by themselves, without a barrier: while a wave multiplies a stage's
+// 9x9 patch, the next one is on its way into a buffer of its own.  With SiLU, tensors in no cache: 32 -> 64 on 16x320x320 42.9 ->
+// 34.7 us (4.5 TB/s, the rate of a copy), 64 -> 128 on 16x160x160 34.0 -> 27.7: bound by the instructions around the products there
+// (block numbers by division instead of addition 4 % more, three buffers a wave 7 %).
 template <int STAGES> struct Resident {
     static constexpr int WAVES = 8, BUFS = 2;
     static constexpr int A_BYTES = 4 * layout_tile_bytes(kLayouts[0]);
@@ -407,10 +410,10 @@ template <int STAGES> struct Resident {
 };
 
 template <typename T, int STAGES>
-__global__ __launch_bounds__(64 * Resident<STAGES>::WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void conv3x3_resident_kernel(const T* __restrict__ x, T* __restrict__ y, const char* __restrict__ wfrag,
-                                                                               const char* __restrict__ zeros, int H, int W, int Co, int Ho, int Wo,
-                                                                               int m_tiles_total, int blocks_c, int blocks_per_image, int co_blocks,
-                                                                               int blocks, int blocks_per_xcd, Epilogue ep)
+__global__ __launch_bounds__(64 * Resident<STAGES>::WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void conv3x3_resident_kernel(const T* __restrict__ x, T* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros, int H, int W,
+                             int Co, int Ho, int Wo, int m_tiles_total, int blocks_c, int blocks_per_image, int co_blocks, int blocks,
+                             int blocks_per_xcd, Epilogue ep)
 {
     using R = Resident<STAGES>;
     constexpr TapLayout LY = kLayouts[0];
@@ -618,7 +621,7 @@ inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
 
 // Stride 2, one or two blocks per wave: three workgroups per compute unit with one, two with two, whose rounds take about 4/3 as
 // long (two halve the weights a block reads from LDS).  Two where that is the smaller sum; not for one or two stages, which
-// the memory bounds (us, one and two; layout 0 / 1, batch x channels in -> out @ image):
+// the memory bounds (us, one and two, plain, in a loop over the same tensors; layout 0 / 1, batch x channels in -> out @ image):
 //     16x256->256@40  12.7 16.4 / 15.4 19.2  one    16x256->512@40 25.6 20.8 / 31.3 24.5  two     4x64->128@112x140  6.1 8.0 / 6.8 8.6  one
 //     4x128->256@56x70 7.2  9.7 /  8.5 11.0  one    4x128->256@112x140 15.4 13.1 / 17.6 14.4  two  16x64->128@160   25.9 28.5 / 29.7 31.3  one
 inline bool two_blocks_per_wave(const rtoss_wdesc& d, const ConvParams& c)
@@ -628,12 +631,13 @@ inline bool two_blocks_per_wave(const rtoss_wdesc& d, const ConvParams& c)
     return d.Ci > 64 && 4 * two <= 3 * one;
 }
 
-// Stride 2, one or two stages: resident weights from one and a half blocks a wave on (us, the single-buffered kernel and the resident one; blocks of 64
-// channels x 16 positions a wave in brackets; batch x channels in -> out @ image):
-//     16x32->64@320 (12.5) 42.3 34.3    16x64->128@160 (6.3) 33.6 28.3    16x64->256@80 (3.1) 15.6 13.5    2x64->256@160 (1.6) 11.3 8.9
-//     16x32->32@160 (3.1)  13.0 11.0    4x64->128@160 (1.6)  11.6  9.3    3x64->128@160 (1.2)  8.5  9.2 stays   1x32->512@112x150 (1.0)  5.6 5.4 stays
-//     4x64->448@90 (2.0)   10.4 10.4    4x32->64@240x250 (1.8) 9.1 7.5    2x32->128@203x211 (1.4) 5.9 6.4 stays 4x64->128@112x140 (1.0) 7.1 6.9 stays
-// (offsets of a block's stores within 32 bits)
+// Stride 2, one or two stages: resident weights from one and a half blocks a wave on (us with SiLU, the single-buffered kernel and the
+// resident one, tensors in caches, then in none; blocks of 64 channels x 16 positions a wave in brackets; batch x channels in -> out @ image):
+//     16x32->64@320 (12.5)    35.9 27.1  42.9 34.7    16x64->128@160 (6.3)   28.3 22.0  34.0 27.7    16x64->256@80 (3.1)     16.1 13.2  19.1 16.8
+//     16x32->32@160 (3.1)     10.8  9.4  13.6 11.8    4x64->448@90 (2.0)     10.8 10.9  13.1 12.7    4x32->64@240x250 (1.8)   7.9  6.2  10.5  8.9
+//     2x64->256@160 (1.6)     10.3  8.1  12.1 10.0    4x64->128@160 (1.6)    10.4  8.1  12.8 10.6
+//     2x32->128@203x211 (1.4)  6.0  6.1   7.3  7.2    3x64->128@160 (1.2)     8.2  8.0  10.1 10.3    4x64->128@112x140 (1.0)  6.2  6.1   8.7  7.6
+// (the last line stays: plain layers of its first two lose 8 % in no cache.  Offsets of a block's stores within 32 bits.)
 inline bool resident_ok(const rtoss_wdesc& d, const ConvParams& c)
 {
     const int64_t Ho = (c.H - 1) / 2 + 1, Wo = (c.W - 1) / 2 + 1, blocks = (Ho + 3) / 4 * ((Wo + 3) / 4) * c.N, co_blocks = (d.Co + 63) / 64;

@@ -391,8 +391,8 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
     // ---- store: a lane holds 8 consecutive channels of one position per row ----
     const int co = 64 * cb + 16 * qq + 8 * pair, ow = ow0 + nn, oh = oh0 + half * RW;
     const bool live = co < Co && ow < W;  // (Co is a multiple of 16)
-    // (ROWS_OUT: whole rows past the L2's write-back, as above, where the tiles are tall: 20 rows 2x256@100x168 34.2 -> 33.9 us, 1x256@100x168 20.8 -> 20.4;
-    // 12 rows 4x128@60x80 9.4 -> 9.5)
+    // (ROWS_OUT: whole rows past the L2's write-back, as above, where the tiles are tall: 20 rows 2x256@100x168 34.2 -> 33.9 us,
+    // 1x256@100x168 20.8 -> 20.4; 12 rows 4x128@60x80 9.4 -> 9.5)
     if (!ROWS_OUT && !live) return;
     if constexpr (ROWS_OUT) __syncthreads();  // everybody is done reading the last stage
     static_assert(ROWS * RowTile<TO>::kBytes <= 2 * P::BUF, "the outputs fit the buffers");
@@ -443,9 +443,9 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
 // (fp32: dense3x3_f32.h, eight rows)
 template <typename T, int ROWS> constexpr int dense_strip_lds = sizeof(T) == 4 ? F32Tile<1, ROWS>::LDS : DenseStrip<ROWS>::LDS;
 template <typename T, typename TO, int ROWS, bool ROWS_OUT>
-__device__ __forceinline__ void dense_strip_work(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                 int H, int W, int Ci, int Co, int strips, int tiles_per_image, int co_blocks, int total,
-                                                 int work_per_xcd, const Epilogue& ep)
+__device__ __forceinline__ void dense_strip_work(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+                                                 const char* __restrict__ zeros, int H, int W, int Ci, int Co, int strips, int tiles_per_image,
+                                                 int co_blocks, int total, int work_per_xcd, const Epilogue& ep)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
