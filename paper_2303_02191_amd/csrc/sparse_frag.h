@@ -10,11 +10,15 @@ namespace rtoss {
 // 2-of-4 group of the sparse instruction (legal for a dictionary when no pattern has more than 2 live taps in
 // any set; a set of 3 leaves its fourth slot empty), and optionally the centre tap as a dense K-slot.  Per
 // 32 input channels a layout costs 2 sparse steps per group + 1 dense step for the centre, against 9 dense
-// steps.  An exhaustive search over all partitions of the taps gives, for the edge-connected dictionaries:
+// steps.  An exhaustive search over all partitions of the taps (every tap in one group) gives, for the
+// edge-connected dictionaries:
 //   2 and 3 entries: 5 steps (two groups of 4 + the centre: layout 0, corners / edge midpoints);
 //   4 entries:       6 steps (three groups of 3, no tap left over: layout 1; the T shapes have 3 edge
 //                    midpoints, so layout 0 does not fit them);
-//   5 and more:      no partition is cheaper than the 9 dense steps.
+//   5 entries:       no partition is cheaper than the 9 dense steps.
+// A tap may also stand in two groups, and the packer choose its group per pattern: {0,1,3,5} {0,2,4,6} {1,4,7,8}
+// place every edge-connected pattern of 2 to 5 entries with at most two live taps a group, 6 steps.  No kernel
+// takes such a layout yet, so 5 entries stay in dense mode.
 struct TapLayout {
     int groups;     // sparse groups
     int centre;     // 1: tap 4 is a dense step of its own
