@@ -137,6 +137,11 @@ int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout);
 rtoss_status launch_conv3x3_strip(const rtoss_wdesc& d, const ConvParams& c, int layout, int plan, const void* section, const void* zeros,
                                   const void* x, void* y, hipStream_t s);
 
+// ... with helper waves (conv3x3_ring.hip): rows of a wave, 0 = another kernel serves the launch better
+int ring3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout);
+rtoss_status launch_conv3x3_ring(const rtoss_wdesc& d, const ConvParams& c, int layout, int plan, const void* section, const void* zeros,
+                                 const void* x, void* y, hipStream_t s);
+
 // 3x3 convolution with live taps gathered onto the dense matrix instruction, for block-shared patterns
 // (conv3x3_gather.hip); its own blob format, chosen by the caller (rtoss_pack_coherent)
 bool gather3x3_shape_ok(const rtoss_wdesc& d);

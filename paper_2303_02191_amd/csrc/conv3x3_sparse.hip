@@ -712,9 +712,12 @@ rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, in
     const bool f32out = c.out_dt == RTOSS_F32;
     if (const int plan = ksplit3x3_plan(d, c, layout))
         return launch_conv3x3_ksplit(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
-    if (layout != 0 || !takes_pipelined_kernel(d, c))
+    if (layout != 0 || !takes_pipelined_kernel(d, c)) {
+        if (const int plan = ring3x3_plan(d, c, layout))
+            return launch_conv3x3_ring(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
         if (const int plan = strip3x3_plan(d, c, layout))
             return launch_conv3x3_strip(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
+    }
     if (layout == 1) {
         if (d.dt == RTOSS_F16)
             return f32out ? launch_typed_layout1<f16_t, float>(d, c, wf, x, y, s) : launch_typed_layout1<f16_t, f16_t>(d, c, wf, x, y, s);

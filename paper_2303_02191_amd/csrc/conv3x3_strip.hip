@@ -33,14 +33,13 @@
 #include "mma.h"
 #include "pack_plan.h"
 #include "sparse_frag.h"
+#include "strip_output.h"
 
 namespace rtoss {
 
 namespace {
 
-constexpr int kTM = 4;         // channel tiles of a workgroup (64 channels)
-constexpr int kCols = 16;      // output columns of a workgroup
-constexpr int kLW = kCols + 2; // input columns
+constexpr int kTM = kStripTM, kCols = kStripCols, kLW = kStripLW;
 constexpr int kDenseTaps = kNumLayouts;
 constexpr int kTwoBuffers = 8; // in a plan: rows per wave + kTwoBuffers
 constexpr int kDenseRows = 16; // in a plan of the dense mode without weights in LDS: rows of a workgroup + kDenseRows
@@ -225,51 +224,10 @@ __device__ __forceinline__ void strip_tile(const T* __restrict__ x, TO* __restri
     // ROWS_OUT: in rows of 128 bytes, past the L2's write-back (RowTile, through the LDS buffer that the last stage does not read; the one
     // buffer behind a barrier).  Stores of 16 bytes from the registers, written back when the launch ends, took 64 -> 64 channels on 16x80x80 with
     // SiLU and shortcut from 12.3 to 14.3 us, 128 -> 128 on 16x40x40 10.6 to 11.3, 256 -> 256 on 1x100x168 18.0 to 18.8, 1x50x84 10.2 to 10.4.
-    const int co = 64 * cb + 16 * qq, ow = ow0 + nn;
-    const bool live = co < Co && ow < W;  // (Co is a multiple of 16: a run of 16 channels is all in or all out)
-    if (!ROWS_OUT && !live) return;
     if (ROWS_OUT && !DB) __syncthreads();  // everybody is done reading the last stage
     char* const area = smem + (DB ? (stages & 1) * P::BUF : 0) + wave * (TN * RowTile<TO>::kBytes);
     static_assert(4 * TN * RowTile<TO>::kBytes <= P::BUF, "the tiles of all waves fit a buffer");
-    auto finish = [&](auto shortcut_tag, auto form) {
-        constexpr bool SHORTCUT = decltype(shortcut_tag)::value;
-        EpiResidual<TO, 16> shortcut[TN];
-        const int64_t pos0 = ((int64_t)n_img * H + oh0 + wave * TN) * W + ow;
-        if constexpr (SHORTCUT) {  // its loads go out together, before any of them is needed
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                if (live && oh0 + wave * TN + j < H) shortcut[j].load(ep, pos0 + (int64_t)j * W, co);
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            if (oh0 + wave * TN + j >= H) break;
-            TO* yp = y + (pos0 + (int64_t)j * W) * ep.ldy + co;
-            float v[16];
-#pragma unroll
-            for (int m = 0; m < kTM; ++m)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * m + e] = acc[m][j][e];
-            epi_scale_bias_act_of<decltype(form)::value, 16>(v, ep, lds_ep + 16 * qq, lds_ep + 64 + 16 * qq);
-            if constexpr (SHORTCUT) shortcut[j].add(v);
-            if constexpr (sizeof(TO) == 4) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) *(f32x4*)(yp + 4 * g) = f32x4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
-            } else {
-                const Run16<TO> o(v);
-                if constexpr (!ROWS_OUT) {
-                    o.store(yp);
-                    continue;
-                }
-                RowTile<TO>::put(area + j * RowTile<TO>::kBytes, lane, o);
-                const auto base = store_base(y + (((int64_t)n_img * H + oh0 + wave * TN + j) * W + ow0) * ep.ldy + 64 * cb);
-                RowTile<TO>::store(area + j * RowTile<TO>::kBytes, lane, base, [&](int row, int c) {
-                    return ow0 + row < W && 64 * cb + 8 * c < Co ? (uint32_t)row * ep.ldy * 2 + c * 16 : kNoStore;
-                });
-            }
-        }
-    };
-    if (ep.residual) epi_by_form<false>(ep, [&](auto form) { finish(std::true_type{}, form); });
-    else epi_by_form<false>(ep, [&](auto form) { finish(std::false_type{}, form); });
+    strip_output<TO, TN, ROWS_OUT>(acc, area, lds_ep, y, H, W, Co, cb, n_img, oh0 + wave * TN, ow0, lane, ep);
 }
 
 // (ROWS: whether 16-bit outputs leave in rows, where both are there; two buffers and fp32 results know one way)

@@ -14,6 +14,7 @@ import test_gpu_slices
 import test_gpu_stream1x1
 import test_gpu_stride2_rows
 import test_gpu_strip
+import test_gpu_strip_ring
 from variants import OWN_TYPE_OUT, VARIANTS
 
 
@@ -83,6 +84,12 @@ def test_cases_made_for_a_kernel_reach_it(fused):
     assert families(routes.kernels(calls)) == ["conv3x3_resident"] * len(calls)
     calls = [call(dt, 1, Ci, Co, 1, P, 1, 1, 2, out_dt, fused) for dt, Ci, Co, P in test_gpu_stream1x1.CASES for out_dt in (dt, wl.F32)]
     assert families(routes.kernels(calls)) == ["conv1x1_stream"] * len(calls)
+
+
+def test_ring_cases_reach_the_height_they_name():
+    calls = [call(dt, N, Ci, Co, H, W, 3, 1, k, dt, fused) for tn, dt, N, Ci, Co, H, W, k in test_gpu_strip_ring.CASES for fused in (False, True)]
+    want = ["conv3x3_strip<%d,%d>" % (c[0], c[-1] == 4) for c in test_gpu_strip_ring.CASES for fused in (False, True)]
+    assert [split(k)[0] for k in routes.kernels(calls)] == want
 
 
 def test_streaming_cases_cover_the_turns():
