@@ -112,7 +112,8 @@ static unsigned reverse9(unsigned m)
     return r;
 }
 
-// Of every 9-bit mask: its taps, and the 2-of-4 layouts (sparse_frag.h) it fits, one bit each: at most two live taps in each set.
+// Of every 9-bit mask: its taps, and the 2-of-4 layouts (sparse_frag.h) it fits, one bit each; with the layout's repeated taps, kNumLayouts
+// bits higher.
 struct MaskTable {
     uint8_t taps[512] = {}, layouts[512] = {};
 };
@@ -122,14 +123,9 @@ static constexpr MaskTable make_mask_table()
     for (unsigned m = 0; m < 512; ++m) {
         for (unsigned r = m; r; r &= r - 1) ++t.taps[m];
         for (int l = 0; l < kNumLayouts; ++l) {
-            bool fits = true;
-            for (int g = 0; g < kLayouts[l].groups; ++g) {
-                int live = 0;
-                for (int f = 0; f < 4; ++f)
-                    if (kLayouts[l].tap[g][f] >= 0) live += m >> kLayouts[l].tap[g][f] & 1u;
-                fits = fits && live <= 2;
-            }
-            if (fits) t.layouts[m] |= 1u << l;
+            const int choice = tap_choice(kLayouts[l], m);
+            if (choice == 0) t.layouts[m] |= 1u << l;
+            if (choice >= 0) t.layouts[m] |= 1u << (l + kNumLayouts);
         }
     }
     return t;
@@ -156,7 +152,8 @@ static rtoss_status load_dict(const uint16_t* masks_host, int P, Dict* out)
     }
     out->P = P;
     out->k = k;
-    out->layout = layouts ? __builtin_ctz(layouts) : -1;
+    out->layout = layouts ? __builtin_ctz(layouts) % kNumLayouts : -1;
+    out->repeats = layouts && !(layouts & ((1u << kNumLayouts) - 1));
     return RTOSS_OK;
 }
 
@@ -189,7 +186,7 @@ rtoss_status blob_geometry(const rtoss_wdesc* d, const Dict& dict, BlobGeometry*
         g->mat_off = end;
         g->mat_bytes = gather3x3_section_bytes(*d);
         end = align_up(end + g->mat_bytes, 256);
-    } else if (sparse3x3_shape_ok(*d) && dict.layout >= 0) {
+    } else if (sparse3x3_shape_ok(*d, dict)) {
         g->format = kFormatSparse24;
         g->mat_off = end;
         g->mat_bytes = sparse3x3_section_bytes(*d, dict.layout);
@@ -451,7 +448,7 @@ static rtoss_status conv_impl(const rtoss_wdesc* desc, const rtoss_cdesc* c, con
     if (rtoss_status st = current_device(&cp.dev)) return st;
     if (coherent) return launch_conv3x3_gather(*desc, cp, blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
     // The element-wise kernel reads section 0 and takes any strides (NCHW) and any size.
-    const bool fits = g.format == kFormatSparse24      ? sparse3x3_launch_ok(*desc, cp)
+    const bool fits = g.format == kFormatSparse24      ? sparse3x3_launch_ok(*desc, dict, cp)
                       : g.format == kFormatDense3x3    ? dense3x3_launch_ok(*desc, cp)
                       : g.format == kFormatDense       ? dense1x1_launch_ok(*desc, cp)
                       : g.format == kFormatStem        ? stem3x3_launch_ok(*desc, cp)

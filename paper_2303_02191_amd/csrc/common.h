@@ -22,6 +22,7 @@ struct Dict {
     int P;
     int k;
     int layout;  // tap layout of the 2-of-4 fragments (sparse_frag.h) that fits every pattern, cheapest first; -1: none
+    bool repeats;  // ... for some of them with the layout's repeated taps only
 };
 
 // Decoded dictionary for the convolution kernels: tap[p][j] = j-th live tap of pattern p
@@ -110,15 +111,17 @@ rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, 
 // within the kernel's limits, or of a shape that the kernel alone serves (which then reports the error).
 
 // 3x3 convolution on the sparse matrix instruction (conv3x3_sparse.hip)
-bool sparse3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c);
-bool sparse3x3_shape_ok(const rtoss_wdesc& d);
+bool sparse3x3_launch_ok(const rtoss_wdesc& d, const Dict& dict, const ConvParams& c);
+bool sparse3x3_shape_ok(const rtoss_wdesc& d, const Dict& dict);
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout);
 rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, int layout, const void* section, const void* x,
                                    void* y, hipStream_t s);
 
 // ... large stride-1 layers: pipelined kernel over strips of output rows (conv3x3_rows.hip); same packed section
-rtoss_status launch_conv3x3_rows(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
+rtoss_status launch_conv3x3_rows(const rtoss_wdesc& d, const ConvParams& c, int layout, const void* section, const void* x, void* y,
                                  hipStream_t s);
+rtoss_status launch_conv3x3_rows_groups(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
+                                        hipStream_t s);  // (its part for layout 1)
 bool rows3x3_needs_fused_stage(const ConvParams& c);
 
 // ... launches too small to fill the chip: input channels split over the waves of a workgroup (conv3x3_ksplit.hip).  Reads

@@ -249,7 +249,7 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
                 for (int j = 0; j < TN; ++j) {
                     u32x4 r[4];
 #pragma unroll
-                    for (int f = 0; f < 4; ++f) r[f] = x_at(j, LY.tap[g][f] >= 0 ? LY.tap[g][f] : LY.tap[g][0]);  // (empty slots weigh 0)
+                    for (int f = 0; f < 4; ++f) r[f] = x_at(j, LY.tap[g][f]);
 #pragma unroll
                     for (int half = 0; half < 2; ++half) bf[half][j] = sparse_operand(r, half);
                 }

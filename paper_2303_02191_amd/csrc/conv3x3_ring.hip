@@ -72,7 +72,7 @@ template <int TN, int LAY> struct RingSchedule {
     static constexpr int group(int p) { return p < LY.centre ? -1 : (p - LY.centre) / 2; }
     static constexpr int half(int p) { return (p - LY.centre) % 2; }
     static constexpr int fragment(int p) { return p < LY.centre ? 2 * LY.groups : p - LY.centre; }
-    static constexpr int tap(int g, int f) { return LY.tap[g][f] >= 0 ? LY.tap[g][f] : LY.tap[g][0]; }  // (an empty slot weighs 0)
+    static constexpr int tap(int g, int f) { return LY.tap[g][f]; }
     // a slot of the stage, or of the one before where that is too early
     static constexpr int place(int slot) { return slot >= 0 ? slot : slot + SLOTS > BARRIER ? slot + 2 * SLOTS : BARRIER + 1 + SLOTS; }
     // 16-byte reads of input row i at column shift kw

@@ -65,7 +65,7 @@ constexpr int patch_copies(int TN) { return (TN * kPatch + 1023) / 1024; }
 // workgroups share a compute unit and hide each other's copy latency and epilogue.  Used for stride 2, for ragged channel
 // counts and for layers too shallow or narrow for the pipelined kernel's 128-channel, 8-stage appetite: TM = 4 covers 64
 // output channels per workgroup.
-// LAY: tap layout (sparse_frag.h).  Layout 1 (4-entry dictionaries) has three tap groups and no dense centre
+// LAY: tap layout (sparse_frag.h).  Layout 1 (4 and 5 entries) has three tap groups and no dense centre
 // step; it always takes the one-group-at-a-time schedule.
 // DB: two LDS buffers; the copies of the next stage are issued right after the barrier that opens a stage and land
 // while it is multiplied (one barrier per stage).  For deep stride-1 layers, whose schedule with operand reads ahead
@@ -241,8 +241,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
-                    // (an empty slot carries weight 0: it reads the group's first tap, any finite value does)
-                    const int t = LY.tap[group][f] >= 0 ? LY.tap[group][f] : LY.tap[group][0];
+                    const int t = LY.tap[group][f];
                     rr[group][j][f] = read_tap(j, t);
                 }
         };
@@ -610,7 +609,9 @@ rtoss_status launch_typed_ragged(const rtoss_wdesc& d, const ConvParams& c, cons
 }
 
 // Large stride-1 layers (more than 64 channels in and out, enough 16x16 x 128-channel tiles to give most
-// compute units one) take the pipelined kernel of conv3x3_rows.hip.
+// compute units one) take the pipelined kernel of conv3x3_rows.hip, whatever the layout.  (us, the kernels for smaller launches and the
+// pipelined one, bf16, 3 entries / 4: 2x128@100x168, 154 tiles 10.3 12.1 / 11.8 13.9, 1x256@100x168, 154 tiles 15.4 18.8 / 18.2 21.3, 4x256@80x80,
+// 200 tiles 22.3 19.5 / 27.0 23.2, 2x256@100x168, 308 tiles 38.1 24.1 / 32.6 28.5.)
 inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
 {
     if (c.stride != 1 || d.Co <= 64 || d.Ci <= 64 || ragged(d)) return false;
@@ -645,7 +646,7 @@ inline bool resident_ok(const rtoss_wdesc& d, const ConvParams& c)
     return blocks * co_blocks >= 12 * c.dev.cus;
 }
 
-// Layout 1 (three tap groups, 4-entry dictionaries): the single-buffered kernel for every shape.
+// Layout 1 (three tap groups): the single-buffered kernel for every shape.
 template <typename T, typename TO>
 rtoss_status launch_typed_layout1(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y,
                                   hipStream_t s)
@@ -685,16 +686,22 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 
 // ---- host-visible entry points of this file ----
 
-bool sparse3x3_shape_ok(const rtoss_wdesc& d)
+// Dictionaries that need the repeated taps of layout 1 (5 entries): from 64 channels in and 96 out (or the other way round) on.  Below, and
+// for ragged counts, the dense mode's shorter chain is as fast or faster (us, dense mode and 2-of-4, bf16: 1x32@28x36 3.1 3.6, 4x32@20x30
+// 3.2 4.0, 1x24->80@50 3.6 5.9, 2x40->36@60 4.2 7.9, 4x64@20x30 3.8 4.0, 16x64@80 10.1 10.2; from there on 4x96@20x30 4.5 4.7, 1x96@56x70 5.3 4.9,
+// 4x96@100x168 16.3 14.6, 1x256@56x70 10.5 9.7, 16x128@40 11.0 9.8, 2x256@100x168 33.5 28.4, and at stride 2 4x64->128@112x150 16.7 6.8,
+// 1x128->256@56x70 7.3 7.7, 4x128->256@112x150 39.2 17.8, 4x256->512@40 23.4 13.3).
+bool sparse3x3_shape_ok(const rtoss_wdesc& d, const Dict& dict)
 {
     // (rows of 16-byte multiples: the activation copies move 8 channels per lane)
-    return d.ksize == 3 && (d.dt == RTOSS_F16 || d.dt == RTOSS_BF16) && d.Ci % 8 == 0;
+    if (d.ksize != 3 || (d.dt != RTOSS_F16 && d.dt != RTOSS_BF16) || d.Ci % 8 || dict.layout < 0) return false;
+    return !dict.repeats || (!ragged(d) && d.Ci >= 64 && d.Co >= 64 && d.Ci + (int64_t)d.Co > 128);
 }
 
-bool sparse3x3_launch_ok(const rtoss_wdesc& d, const ConvParams& c)
+bool sparse3x3_launch_ok(const rtoss_wdesc& d, const Dict& dict, const ConvParams& c)
 {
-    if (!ragged(d)) return true;
-    // launch_typed_ragged's tiles (stride 2: four blocks, at least as many positions as a tile of 4x16)
+    if (!ragged(d) && !dict.repeats) return true;
+    // the smallest tiles (launch_typed_ragged's; stride 2: four blocks, at least as many positions as a tile of 4x16)
     const int Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1, rows = c.stride == 1 ? 8 : 4;
     return (int64_t)c.N * c.H * c.W * d.Ci / 8 <= kMaxChunks &&
            (int64_t)((Ho + rows - 1) / rows) * ((Wo + 15) / 16) * ((d.Co + 63) / 64) * c.N <= kMaxGridGroups;
@@ -712,19 +719,20 @@ rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, in
     const bool f32out = c.out_dt == RTOSS_F32;
     if (const int plan = ksplit3x3_plan(d, c, layout))
         return launch_conv3x3_ksplit(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
-    if (layout != 0 || !takes_pipelined_kernel(d, c)) {
+    const bool pipelined = takes_pipelined_kernel(d, c);
+    if (!pipelined) {
         if (const int plan = ring3x3_plan(d, c, layout))
             return launch_conv3x3_ring(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
         if (const int plan = strip3x3_plan(d, c, layout))
             return launch_conv3x3_strip(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
     }
+    if (layout != 0 && layout != 1) return fail(RTOSS_EINVAL, "conv: unknown tap layout %d", layout);
+    if (pipelined) return launch_conv3x3_rows(d, c, layout, section, x, y, s);
     if (layout == 1) {
         if (d.dt == RTOSS_F16)
             return f32out ? launch_typed_layout1<f16_t, float>(d, c, wf, x, y, s) : launch_typed_layout1<f16_t, f16_t>(d, c, wf, x, y, s);
         return f32out ? launch_typed_layout1<bf16_t, float>(d, c, wf, x, y, s) : launch_typed_layout1<bf16_t, bf16_t>(d, c, wf, x, y, s);
     }
-    if (layout != 0) return fail(RTOSS_EINVAL, "conv: unknown tap layout %d", layout);
-    if (takes_pipelined_kernel(d, c)) return launch_conv3x3_rows(d, c, section, x, y, s);
     if (d.dt == RTOSS_F16)
         return f32out ? launch_typed<f16_t, float>(d, c, wf, x, y, s) : launch_typed<f16_t, f16_t>(d, c, wf, x, y, s);
     return f32out ? launch_typed<bf16_t, float>(d, c, wf, x, y, s) : launch_typed<bf16_t, bf16_t>(d, c, wf, x, y, s);

@@ -52,7 +52,7 @@ constexpr int first_phase(const TapLayout& l, int tn, int i, int kw)
     if (l.centre && reads(4)) return 0;
     for (int g = 0; g < l.groups; ++g)
         for (int f = 0; f < 4; ++f)
-            if (l.tap[g][f] >= 0 && reads(l.tap[g][f])) return g + l.centre;
+            if (reads(l.tap[g][f])) return g + l.centre;
     return -1;
 }
 
@@ -203,7 +203,7 @@ __device__ __forceinline__ void strip_tile(const T* __restrict__ x, TO* __restri
                         u32x4 r[4];
 #pragma unroll
                         for (int f = 0; f < 4; ++f) {
-                            const int t = LY.tap[g][f] >= 0 ? LY.tap[g][f] : LY.tap[g][0];  // (an empty slot weighs 0)
+                            const int t = LY.tap[g][f];
                             r[f] = R[j + t / 3][t % 3];
                         }
                         const u32x8 b[2] = {sparse_operand(r, 0), sparse_operand(r, 1)};

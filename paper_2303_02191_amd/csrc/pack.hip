@@ -146,15 +146,24 @@ __device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigne
     // live taps at slots 0 and 1: padding values of 0 may point anywhere, as long as the two differ)
     constexpr unsigned kNoTaps = 15u | (15u << 4) | (0u << 8) | (1u << 10);
     if (SPARSE && tables) {
+        unsigned taken[kTapGroups];  // taps of every group, by the pattern's choice (tap_choice)
+        static_for<lay.groups>([&](auto g) { taken[g] = group_taps(lay, g, 0); });
+        if constexpr (lay.repeats) {
+            static_for<kTapChoices>([&](auto n) {
+                constexpr int c = kTapChoices - 1 - n;
+                bool fits = true;
+                static_for<lay.groups>([&](auto g) { fits = fits && __builtin_popcount(mask & group_taps(lay, g, c)) <= 2; });
+                static_for<lay.groups>([&](auto g) { taken[g] = fits ? group_taps(lay, g, c) : taken[g]; });
+            });
+        }
 #pragma unroll
         for (int g = 0; g < lay.groups; ++g) {
             unsigned t0 = 15u, t1 = 15u, f0 = 0u, f1 = 1u;
             int n = 0;
 #pragma unroll
             for (int sl = 0; sl < 4; ++sl) {
-                if (lay.tap[g][sl] < 0) continue;
                 const unsigned tt = (unsigned)lay.tap[g][sl];
-                const bool live = ((mask >> tt) & 1u) && n < 2;
+                const bool live = ((mask & taken[g]) >> tt & 1u) && n < 2;
                 t0 = live && n == 0 ? tt : t0;
                 f0 = live && n == 0 ? (unsigned)sl : f0;
                 t1 = live && n == 1 ? tt : t1;

@@ -6,29 +6,56 @@
 
 namespace rtoss {
 
-// How the 9 taps of a kernel are laid onto the matrix instructions: `groups` sets of up to 4 taps, each a
-// 2-of-4 group of the sparse instruction (legal for a dictionary when no pattern has more than 2 live taps in
-// any set; a set of 3 leaves its fourth slot empty), and optionally the centre tap as a dense K-slot.  Per
-// 32 input channels a layout costs 2 sparse steps per group + 1 dense step for the centre, against 9 dense
-// steps.  An exhaustive search over all partitions of the taps (every tap in one group) gives, for the
-// edge-connected dictionaries:
-//   2 and 3 entries: 5 steps (two groups of 4 + the centre: layout 0, corners / edge midpoints);
-//   4 entries:       6 steps (three groups of 3, no tap left over: layout 1; the T shapes have 3 edge
-//                    midpoints, so layout 0 does not fit them);
-//   5 entries:       no partition is cheaper than the 9 dense steps.
-// A tap may also stand in two groups, and the packer choose its group per pattern: {0,1,3,5} {0,2,4,6} {1,4,7,8}
-// place every edge-connected pattern of 2 to 5 entries with at most two live taps a group, 6 steps.  No kernel
-// takes such a layout yet, so 5 entries stay in dense mode.
+// How the 9 taps of a kernel are laid onto the matrix instructions: `groups` sets of 4 taps, each a 2-of-4
+// group of the sparse instruction (legal for a dictionary when no pattern has more than 2 live taps in any set),
+// and optionally the centre tap as a dense K-slot.  Per 32 input channels a layout costs 2 sparse steps per group
+// + 1 dense step for the centre, against 9 dense steps.
+//   Layout 0, corners / edge midpoints / centre: 5 steps.  Fits the edge-connected patterns of 2 and 3 entries
+//   (the T shapes of 4 entries have 3 edge midpoints).
+//   Layout 1, three groups: 6 steps.  Three groups of four have twelve slots for nine taps: the last slot of a group
+//   repeats a tap that stands in another group, and the packer takes it from there where the pattern needs that (tap_choice).
+//   An exhaustive search over three sets of four taps: with every tap in one group {0,4,8} {1,5,6} {2,3,7} place all 36
+//   edge-connected patterns of 4 entries, none places the 49 of 5; with repeats, 451 of the 512 masks fit the best choices, those 49 and
+//   everything that {0,4,8} {1,5,6} {2,3,7} place among them.  (6 entries: the matrix instruction's 6 live taps a channel, but not all 48 fit.)
 struct TapLayout {
     int groups;     // sparse groups
     int centre;     // 1: tap 4 is a dense step of its own
-    int tap[3][4];  // taps of each group's 4 slots, -1 = empty slot
+    int repeats;    // 1: the last slot of every group repeats a tap of another group
+    int tap[3][4];  // taps of each group's 4 slots
 };
 constexpr int kNumLayouts = 2;
 constexpr TapLayout kLayouts[kNumLayouts] = {
-    {2, 1, {{0, 2, 6, 8}, {1, 3, 5, 7}, {-1, -1, -1, -1}}},
-    {3, 0, {{0, 4, 8, -1}, {1, 5, 6, -1}, {2, 3, 7, -1}}},
+    {2, 1, 0, {{0, 2, 6, 8}, {1, 3, 5, 7}, {-1, -1, -1, -1}}},
+    {3, 0, 1, {{0, 4, 8, 7}, {1, 5, 6, 8}, {2, 3, 7, 5}}},
 };
+// A choice: bit g set = group g takes the tap of its last slot from the group that it stands in first.  The taps that a group has
+// under a choice, as a mask.
+constexpr int kTapChoices = 8;
+__host__ __device__ constexpr unsigned group_taps(const TapLayout& l, int g, int choice)
+{
+    unsigned taps = 0;
+    for (int f = 0; f < 4; ++f) {
+        bool here = !l.repeats || f < 3 || (choice >> g & 1);
+        if (l.repeats && f < 3)
+            for (int o = 0; o < l.groups; ++o) here = here && !(l.tap[o][3] == l.tap[g][f] && (choice >> o & 1));
+        if (here) taps |= 1u << l.tap[g][f];
+    }
+    return taps;
+}
+// The first choice under which a pattern has at most two live taps in every group; -1: none.
+constexpr int tap_choice(const TapLayout& l, unsigned mask)
+{
+    for (int c = 0; c < (l.repeats ? kTapChoices : 1); ++c) {
+        bool fits = true;
+        for (int g = 0; g < l.groups; ++g) {
+            int live = 0;
+            for (unsigned m = mask & group_taps(l, g, c); m; m &= m - 1) ++live;
+            fits = fits && live <= 2;
+        }
+        if (fits) return c;
+    }
+    return -1;
+}
 // Packed weight fragments: per (stage of 32 input channels, tile of 16 output channels)
 //   operand fragments of 64 lanes x 16 bytes: [group][step 0/1] ..., then the centre's if the layout has one
 //   then one index word per lane and group: [group][lane]; low half = step 0, high = step 1
@@ -36,7 +63,6 @@ constexpr TapLayout kLayouts[kNumLayouts] = {
 constexpr int kFragBytes = 1024;
 constexpr int layout_fragments(const TapLayout& l) { return 2 * l.groups + l.centre; }
 constexpr int layout_tile_bytes(const TapLayout& l) { return layout_fragments(l) * kFragBytes + l.groups * 64 * 4; }
-constexpr int kTileBytes = layout_tile_bytes(kLayouts[0]);  // 5632: layout 0, the only one the pipelined kernel takes
 
 // Output channel held by row r of channel tile mt.  Within a group of 4 tiles (64 channels) the rows
 // are dealt so that the accumulator values one lane holds after the multiplication -- rows

@@ -24,7 +24,7 @@ CASES = [
     (wl.BF16, 3, 64, 64, 65, 81, 4),     # three tap groups: two, ...
     (wl.F16, 4, 64, 256, 49, 65, 4),     # ... three,
     (wl.F16, 4, 64, 128, 99, 129, 4),    # ... four,
-    (wl.BF16, 2, 96, 256, 99, 161, 4),   # ... five rows per wave
+    (wl.BF16, 2, 64, 256, 99, 161, 4),   # ... five rows per wave
     (wl.F16, 4, 64, 64, 79, 80, 5),      # dense mode: two rows and buffers,
     (wl.BF16, 3, 64, 112, 81, 97, 5),    # ... two rows,
     (wl.F16, 4, 64, 256, 49, 65, 5),     # ... three,
