@@ -13,6 +13,9 @@ HOST = os.path.join(HERE, "_host.so")
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",  # never emit packed-fp32 VALU ops
+    # A kernel's first 14 words of arguments come with the dispatch instead of through a load that no cache has yet: 0.05 to 0.1 us a launch
+    # (fp32 64 -> 64 @ 56 5.77 -> 5.66 us, 20 launches of a pyramid 154.5 -> 152.8, four of 30 us 119.1 -> 118.0).
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wextra", "-Wno-unused-parameter", "-Wno-unknown-warning-option", "-Wno-unused-command-line-argument",
 ]
 
