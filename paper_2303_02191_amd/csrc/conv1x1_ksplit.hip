@@ -16,6 +16,7 @@
 #include "epilogue.h"
 #include "fp32_split.h"
 #include "mma.h"
+#include "work_order.h"
 #include "pack_plan.h"
 
 namespace rtoss {
@@ -26,7 +27,7 @@ constexpr int kFrag = 1024;  // 64 lanes x 16 bytes = 16 output channels x 64 by
 
 template <typename T, typename TO, int KS, int TM, int TN>
 __global__ __launch_bounds__(256) void conv1x1_ksplit_kernel(const T* __restrict__ x, TO* __restrict__ y,
-                                                             const char* __restrict__ wfrag, int P, int Co, int co_blocks,
+                                                             const char* __restrict__ wfrag, int P, int Co, Divisor co_blocks,
                                                              int total, int work_per_xcd, Epilogue ep)
 {
     constexpr int MINE = KS / 4;                        // stages of a wave
@@ -41,8 +42,8 @@ __global__ __launch_bounds__(256) void conv1x1_ksplit_kernel(const T* __restrict
     // XCD-contiguous work order, channel block fastest: the workgroups of one position tile share an L2
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total) return;
-    const int f0 = (work % co_blocks) * TM;             // first channel tile
-    const int p0 = (work / co_blocks) * (16 * TN);
+    const int all_tile = co_blocks.quotient(work), p0 = all_tile * (16 * TN);
+    const int f0 = co_blocks.remainder(work, all_tile) * TM;  // first channel tile
     const int nn = lane & 15, qq = lane >> 4;
 
     const char* a_src = wfrag + ((int64_t)f0 * KS + wave) * kFrag + lane * 16;
@@ -160,7 +161,7 @@ rtoss_status launch_variant(const rtoss_wdesc& d, const ConvParams& c, const cha
     if (P > 0x7fffff00 || total > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv1x1: too many positions");
     const int work_per_xcd = (int)((total + 7) / 8);
     dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
-    conv1x1_ksplit_kernel<T, TO, KS, TM, TN><<<grid, block, 0, s>>>((const T*)x, (TO*)y, wf, (int)P, d.Co, co_blocks, (int)total,
+    conv1x1_ksplit_kernel<T, TO, KS, TM, TN><<<grid, block, 0, s>>>((const T*)x, (TO*)y, wf, (int)P, d.Co, Divisor(co_blocks), (int)total,
                                                                     work_per_xcd, c.ep);
     return check_hip(hipGetLastError(), "conv1x1 K-split launch");
 }

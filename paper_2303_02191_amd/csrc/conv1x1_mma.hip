@@ -35,6 +35,7 @@
 #include "epilogue.h"
 #include "fp32_split.h"
 #include "mma.h"
+#include "work_order.h"
 #include "pack_plan.h"
 
 namespace rtoss {
@@ -50,7 +51,7 @@ inline size_t frag_bytes(const rtoss_wdesc& d) { return (size_t)stage_count(d) *
 template <typename T, typename TO, int TM>
 __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                           const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                          int64_t P, int Ci, int Co, int m_tiles_total, int co_blocks,
+                                                          int64_t P, int Ci, int Co, int m_tiles_total, Divisor co_blocks,
                                                           int total_work, int work_per_xcd, Epilogue ep)
 {
     constexpr int TN = 2;                                // 16-position blocks per wave
@@ -67,8 +68,8 @@ __global__ __launch_bounds__(256) void conv1x1_mma_kernel(const T* __restrict__ 
     // XCD-contiguous work order (channel blocks of one position tile, and neighbouring tiles, share an L2)
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total_work) return;
-    const int cblk = work % co_blocks;
-    const int64_t p0 = (int64_t)(work / co_blocks) * kTilePos;
+    const int all_tile = co_blocks.quotient(work), cblk = co_blocks.remainder(work, all_tile);
+    const int64_t p0 = (int64_t)all_tile * kTilePos;
     const int mt0 = cblk * TM;
     const int row_bytes = Ci * (int)sizeof(T);
     const int stages = row_bytes / 64;
@@ -489,7 +490,7 @@ rtoss_status launch_tm(const rtoss_wdesc& d, const ConvParams& c, const char* wf
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, smem, lds_once, c.dev.device, "conv1x1 shared memory attribute")) return st;
     dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Ci, d.Co, ring_padded_tiles(d.Co),
-                                   co_blocks, (int)total, work_per_xcd, c.ep);
+                                   Divisor(co_blocks), (int)total, work_per_xcd, c.ep);
     return check_hip(hipGetLastError(), "conv1x1 launch");
 }
 

@@ -47,6 +47,7 @@
 #include "epilogue.h"
 #include "fp32_split.h"
 #include "mma.h"
+#include "work_order.h"
 #include "pack_plan.h"
 #include "share.h"
 
@@ -99,7 +100,7 @@ inline size_t frag_bytes(const rtoss_wdesc& d)
 // TILE: outputs through LDS tiles and the helpers; else straight from the accumulators, as they are.
 template <typename T, typename TO, int KS, int WM, bool TILE>
 __device__ __forceinline__ void stream_outputs(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                               int64_t P, int Co, int co_blocks, const Share& share, int total_wgs, int work_per_xcd, const Epilogue& ep)
+                                               int64_t P, int Co, Divisor co_blocks, const Share& share, int total_wgs, int work_per_xcd, const Epilogue& ep)
 {
     using PL = Plan<KS, WM>;
     constexpr int MT = PL::MT, NB = PL::NB, PB = PL::PB, BUF = PL::BUF, COPIES = PL::COPIES, RING = PL::RING;
@@ -111,7 +112,7 @@ __device__ __forceinline__ void stream_outputs(const T* __restrict__ x, TO* __re
     // XCD-contiguous order: the channel blocks of one share's positions meet in an L2
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total_wgs) return;
-    const int cb = work % co_blocks, part = work / co_blocks;
+    const int part = co_blocks.quotient(work), cb = co_blocks.remainder(work, part);
     const Buffers buffers = share.of(part);
     const int64_t count = buffers.count;  // (64 bits: 32 measured 1 to 2 % slower in small launches)
 
@@ -420,14 +421,14 @@ __device__ __forceinline__ void stream_outputs(const T* __restrict__ x, TO* __re
 template <typename T, typename TO, int KS, int WM>
 __global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM)))
 void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros, int64_t P,
-                           int Co, int co_blocks, Share share, int total_wgs, int work_per_xcd, Epilogue ep)
+                           int Co, Divisor co_blocks, Share share, int total_wgs, int work_per_xcd, Epilogue ep)
 {
     stream_outputs<T, TO, KS, WM, !Plan<KS, WM>::INTERLEAVED>(x, y, wfrag, zeros, P, Co, co_blocks, share, total_wgs, work_per_xcd, ep);
 }
 template <typename T, typename TO, int KS, int WM, bool TILE>
 __global__ __launch_bounds__(64 * (4 + helper_waves(KS, WM)))
 void conv1x1_stream_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros, int64_t P,
-                           int Co, int co_blocks, Share share, int total_wgs, int work_per_xcd, Epilogue ep)
+                           int Co, Divisor co_blocks, Share share, int total_wgs, int work_per_xcd, Epilogue ep)
 {
     stream_outputs<T, TO, KS, WM, TILE>(x, y, wfrag, zeros, P, Co, co_blocks, share, total_wgs, work_per_xcd, ep);
 }
@@ -448,7 +449,7 @@ constexpr int f32_positions(int KS) { return KS == 2 ? 64 : 32; }
 
 template <typename T, typename TO, int KS>
 __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(const float* __restrict__ x, float* __restrict__ y,
-                                                             const char* __restrict__ wfrag, int64_t P, int Co, int co_blocks,
+                                                             const char* __restrict__ wfrag, int64_t P, int Co, Divisor co_blocks,
                                                              Share share, int total_wgs, int work_per_xcd, Epilogue ep)
 {
     constexpr int KK = KS / 2, PB = f32_positions(KS), TN = PB / 16;  // steps of 32 channels; blocks of 16 positions
@@ -464,7 +465,7 @@ __global__ __launch_bounds__(256, KS <= 8 ? 4 : 2) void conv1x1_stream_kernel(co
     // XCD-contiguous order: the channel blocks of one share's positions meet in an L2
     const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
     if (work >= total_wgs) return;
-    const int cb = work % co_blocks, part = work / co_blocks;
+    const int part = co_blocks.quotient(work), cb = co_blocks.remainder(work, part);
     const Buffers buffers = share.of(part);
 
     u32x4 raw[U][2];
@@ -590,7 +591,7 @@ rtoss_status launch_f32(const rtoss_wdesc& d, const ConvParams& c, const char* w
     const int work_per_xcd = (total + 7) / 8;
     if (P * d.Ci * 4 / PB > 0x7fffffffffffll || nbuf > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv1x1: too many positions");
     dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
-    kern<<<grid, block, 0, s>>>((const float*)x, (float*)y, wfrag, P, d.Co, co_blocks, Share(nbuf, wgs_per_cb), total, work_per_xcd,
+    kern<<<grid, block, 0, s>>>((const float*)x, (float*)y, wfrag, P, d.Co, Divisor(co_blocks), Share(nbuf, wgs_per_cb), total, work_per_xcd,
                              c.ep);
     return check_hip(hipGetLastError(), "conv1x1 stream launch");
 }
@@ -655,7 +656,7 @@ rtoss_status launch_plan(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const int work_per_xcd = (total + 7) / 8;
     if (P * d.Ci * (int)sizeof(T) / PL::PB > 0x7fffffffffffll || nbuf > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv1x1: too many positions");
     dim3 grid((unsigned)(work_per_xcd * 8)), block(PL::LANES);
-    kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Co, co_blocks,
+    kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), P, d.Co, Divisor(co_blocks),
                                    Share(nbuf, wgs_per_cb), total, work_per_xcd, c.ep);
     return check_hip(hipGetLastError(), "conv1x1 stream launch");
 }

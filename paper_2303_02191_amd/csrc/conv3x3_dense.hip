@@ -39,6 +39,7 @@
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
+#include "work_order.h"
 #include "pack_plan.h"
 #include "tile3x3.h"
 
@@ -62,7 +63,7 @@ template <typename T, typename TO, int S, int TM, int RT, int CT, bool RAG>
 __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                             const char* __restrict__ wfrag, const char* __restrict__ zeros,
                                                             int H, int W, int Ci, int Co, int Ho, int Wo, int cblocks,
-                                                            int tiles_c, Epilogue ep)
+                                                            Divisor tiles_c, Epilogue ep)
 {
     using G = Geom<S, RT, CT>;
     constexpr int kTN = RT * CT / 4;                            // position blocks per wave
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(256) void conv3x3_dense_kernel(const T* __restrict_
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tile_r = blockIdx.x / tiles_c, tile_c = blockIdx.x % tiles_c;
+    const int tile_r = tiles_c.quotient(blockIdx.x), tile_c = tiles_c.remainder(blockIdx.x, tile_r);
     const int cb = blockIdx.y / (kTM / TM), m_first = (blockIdx.y % (kTM / TM)) * TM, n_img = blockIdx.z;
     const int oh0 = tile_r * G::TH, ow0 = tile_c * G::TW;
     const int ih0 = oh0 * S - 1, iw0 = ow0 * S - 1;
@@ -207,7 +208,7 @@ rtoss_status launch_shape(const rtoss_wdesc& d, const ConvParams& c, const char*
     if (c.N > 65535 || ygrid > 65535) return fail(RTOSS_ESHAPE, "conv: batch or channel count too large");
     dim3 grid((unsigned)(tiles_r * tiles_c), (unsigned)ygrid, (unsigned)c.N), block(256);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + frag_bytes(d), c.H, c.W, d.Ci, d.Co, Ho, Wo, cblocks,
-                                   tiles_c, c.ep);
+                                   Divisor(tiles_c), c.ep);
     return check_hip(hipGetLastError(), "conv3x3 dense launch");
 }
 
@@ -215,17 +216,15 @@ rtoss_status launch_shape(const rtoss_wdesc& d, const ConvParams& c, const char*
 template <typename T, typename TO, int S, int R, bool RAG>
 __global__ __launch_bounds__(256, 2) void conv3x3_dense_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                                const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                               int H, int W, int Ci, int Co, int Ho, int Wo, int cblocks,
-                                                               int tiles_c, int tiles_per_image, int total, int work_per_xcd,
-                                                               Epilogue ep)
+                                                               int H, int W, int Ci, int Co, int Ho, int Wo, WorkOrder order, Epilogue ep)
 {
     static_assert(sizeof(T) == 4 && sizeof(TO) == 4, "fp32");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    // XCD-contiguous work order, channel block fastest: the workgroups of one activation tile share an L2
-    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
-    if (work >= total) return;
-    const int cb = work % cblocks, tile = (work / cblocks) % tiles_per_image, n_img = (work / cblocks) / tiles_per_image;
-    dense3x3_f32_tile<S, R, RAG>(x, y, wfrag, zeros, H, W, Ci, Co, Ho, Wo, cblocks, cb, n_img, (tile / tiles_c) * R, (tile % tiles_c) * 16, ep, smem);
+    const int work = order.item();
+    if (work >= order.total) return;
+    const int all_tile = order.co_blocks.quotient(work), cblocks = order.co_blocks.by, cb = order.co_blocks.remainder(work, all_tile);
+    const WorkOrder::Tile tile = order.tile(all_tile);
+    dense3x3_f32_tile<S, R, RAG>(x, y, wfrag, zeros, H, W, Ci, Co, Ho, Wo, cblocks, cb, tile.n_img, tile.row * R, tile.col * 16, ep, smem);
 }
 
 template <int S, int R, bool RAG>
@@ -239,9 +238,8 @@ rtoss_status launch_f32_rows(const rtoss_wdesc& d, const ConvParams& c, const ch
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, c.dev.device, "conv3x3 dense shared memory attribute")) return st;
     if (c.N > 65535 || cblocks * kTM > 65535) return fail(RTOSS_ESHAPE, "conv: batch or channel count too large");  // (as above)
     const int64_t total = (int64_t)tiles_r * tiles_c * cblocks * c.N;  // (at most kMaxGridGroups: dense3x3_launch_ok)
-    const int work_per_xcd = (int)((total + 7) / 8);
-    kern<<<dim3((unsigned)(work_per_xcd * 8)), dim3(256), lds, s>>>((const float*)x, (float*)y, wfrag, wfrag + frag_bytes(d), c.H, c.W, d.Ci, d.Co,
-                                                                   Ho, Wo, cblocks, tiles_c, tiles_r * tiles_c, (int)total, work_per_xcd, c.ep);
+    const WorkOrder order(total, cblocks, tiles_r * tiles_c, tiles_c);
+    kern<<<dim3(order.grid()), dim3(256), lds, s>>>((const float*)x, (float*)y, wfrag, wfrag + frag_bytes(d), c.H, c.W, d.Ci, d.Co, Ho, Wo, order, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 dense launch");
 }
 

@@ -30,6 +30,7 @@
 #include "pack_live.h"
 #include "rows_plan.h"
 #include "sparse_frag.h"
+#include "work_order.h"
 #include "tile3x3.h"
 
 namespace rtoss {
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(256) void conv3x3_gather_kernel(const T* __restrict
                                                              const GatherHeader* __restrict__ headers,
                                                              const char* __restrict__ wfrag, const char* __restrict__ zeros,
                                                              int H, int W, int Ci, int Co, int Ho, int Wo, int cblocks,
-                                                             int tiles_c, Epilogue ep)
+                                                             Divisor tiles_c, Epilogue ep)
 {
     constexpr int RT = 4, CT = 4, TM = kTM;
     using G = Geom<S, RT, CT>;
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(256) void conv3x3_gather_kernel(const T* __restrict
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tile_r = blockIdx.x / tiles_c, tile_c = blockIdx.x % tiles_c;
+    const int tile_r = tiles_c.quotient(blockIdx.x), tile_c = tiles_c.remainder(blockIdx.x, tile_r);
     const int cb = blockIdx.y, n_img = blockIdx.z;
     const int oh0 = tile_r * G::TH, ow0 = tile_c * G::TW;
     const int ih0 = oh0 * S - 1, iw0 = ow0 * S - 1;
@@ -745,7 +746,7 @@ rtoss_status launch_gather(const rtoss_wdesc& d, const ConvParams& c, const char
     dim3 grid((unsigned)(tiles_r * tiles_c), (unsigned)cblocks, (unsigned)c.N), block(256);
     const char* frags = section + header_bytes(d);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, (const GatherHeader*)section, frags, frags + frag_bytes(d), c.H, c.W,
-                                   d.Ci, d.Co, Ho, Wo, cblocks, tiles_c, c.ep);
+                                   d.Ci, d.Co, Ho, Wo, cblocks, Divisor(tiles_c), c.ep);
     return check_hip(hipGetLastError(), "conv3x3 gather launch");
 }
 

@@ -28,6 +28,7 @@
 #include "epilogue.h"
 #include "mma.h"
 #include "sparse_frag.h"
+#include "work_order.h"
 #include "tile3x3.h"
 
 namespace rtoss {
@@ -82,9 +83,7 @@ template <typename T, typename TO, int S, int TM, int RT, int CT, int LAY>
 __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                              const char* __restrict__ wfrag, const char* __restrict__ zeros,
                                                              int H, int W, int Ci, int Co, int Ho, int Wo, int m_tiles_total,
-                                                             int tiles_c, int tiles_per_image, int co_blocks, int total,
-                                                             int work_per_xcd, const char* __restrict__ headers,
-                                                             Epilogue ep)
+                                                             WorkOrder order, const char* __restrict__ headers, Epilogue ep)
 {
     using K = KSplit<S, TM, RT, CT, LAY>;
     using G = typename K::G;
@@ -95,13 +94,12 @@ __global__ __launch_bounds__(256) void conv3x3_ksplit_kernel(const T* __restrict
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // XCD-contiguous work order, channel block fastest: the workgroups of one activation tile share an L2
-    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
-    if (work >= total) return;
-    const int mt0 = (work % co_blocks) * TM;
-    const int tile = (work / co_blocks) % tiles_per_image;
-    const int n_img = (work / co_blocks) / tiles_per_image;
-    const int oh0 = (tile / tiles_c) * G::TH, ow0 = (tile % tiles_c) * G::TW;
+    const int work = order.item();
+    if (work >= order.total) return;
+    const int all_tile = order.co_blocks.quotient(work);
+    const int mt0 = order.co_blocks.remainder(work, all_tile) * TM;
+    const WorkOrder::Tile tile = order.tile(all_tile);
+    const int n_img = tile.n_img, oh0 = tile.row * G::TH, ow0 = tile.col * G::TW;
     const int ih0 = oh0 * S - 1, iw0 = ow0 * S - 1;
     const int stages = Ci / (4 * PER);
     char* mine = smem + wave * K::SLOT;
@@ -330,11 +328,10 @@ rtoss_status launch_variant(const rtoss_wdesc& d, const ConvParams& c, const cha
     const int64_t total = (int64_t)tiles_r * tiles_c * co_blocks * c.N;
     if (total > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
     if ((int64_t)c.N * c.H * c.W * d.Ci * (int)sizeof(T) / 16 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
-    const int work_per_xcd = (int)((total + 7) / 8);
-    dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
+    const WorkOrder order(total, co_blocks, tiles_r * tiles_c, tiles_c);
+    dim3 grid(order.grid()), block(256);
     kern<<<grid, block, K::LDS, s>>>((const T*)x, (TO*)y, wfrag, zeros, c.H, c.W, d.Ci, d.Co, Ho, Wo,
-                                     LAY >= kDenseTaps ? channel_tiles(d.Co) : padded_m_tiles(d.Co), tiles_c, tiles_r * tiles_c, co_blocks, (int)total, work_per_xcd,
-                                     headers, c.ep);
+                                     LAY >= kDenseTaps ? channel_tiles(d.Co) : padded_m_tiles(d.Co), order, headers, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 K-split launch");
 }
 

@@ -18,6 +18,7 @@
 #include "epilogue.h"
 #include "mma.h"
 #include "sparse_frag.h"
+#include "work_order.h"
 #include "strip_output.h"
 
 namespace rtoss {
@@ -117,8 +118,7 @@ template <int TN, int LAY> struct RingSchedule {
 template <int TN, int LAY, typename T, typename TO>
 __global__ __launch_bounds__(512, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
                                                                const char* __restrict__ zeros, int H, int W, int Ci, int Co, int m_tiles_total,
-                                                               int strips, int tiles_per_image, int co_blocks, int total, int work_per_xcd,
-                                                               Epilogue ep)
+                                                               WorkOrder order, Epilogue ep)
 {
     using P = Ring<TN, LAY>;
     constexpr TapLayout LY = kLayouts[LAY];
@@ -128,13 +128,11 @@ __global__ __launch_bounds__(512, 2) void conv3x3_strip_kernel(const T* __restri
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // XCD-contiguous work order, channel block fastest: the workgroups of one activation tile share an L2
-    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
-    if (work >= total) return;
-    const int cb = work % co_blocks;
-    const int tile = (work / co_blocks) % tiles_per_image;
-    const int n_img = (work / co_blocks) / tiles_per_image;
-    const int oh0 = (tile / strips) * P::ROWS, ow0 = (tile % strips) * kCols;
+    const int work = order.item();
+    if (work >= order.total) return;
+    const int all_tile = order.co_blocks.quotient(work), cb = order.co_blocks.remainder(work, all_tile);
+    const WorkOrder::Tile tile = order.tile(all_tile);
+    const int n_img = tile.n_img, oh0 = tile.row * P::ROWS, ow0 = tile.col * kCols;
     const int stages = Ci / 32;
 
     // Barrier s, which every wave of the workgroup passes: stage s is in LDS, and nobody reads stage s - 1 any more.
@@ -283,9 +281,8 @@ rtoss_status launch_ring(const rtoss_wdesc& d, const ConvParams& c, const char* 
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, P::LDS, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)strips * rows * co_blocks * c.N;
-    const int work_per_xcd = (int)((total + 7) / 8);
-    kern<<<dim3((unsigned)(work_per_xcd * 8)), dim3(512), P::LDS, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, padded_m_tiles(d.Co), strips,
-                                                                       strips * rows, co_blocks, (int)total, work_per_xcd, c.ep);
+    const WorkOrder order(total, co_blocks, strips * rows, strips);
+    kern<<<dim3(order.grid()), dim3(512), P::LDS, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, padded_m_tiles(d.Co), order, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 strip launch");
 }
 

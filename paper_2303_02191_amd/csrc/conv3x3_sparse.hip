@@ -43,6 +43,7 @@
 #include "epilogue.h"
 #include "mma.h"
 #include "sparse_frag.h"
+#include "work_order.h"
 #include "tile3x3.h"
 
 namespace rtoss {
@@ -78,8 +79,7 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
                                                                 const char* __restrict__ wfrag,
                                                                 const char* __restrict__ zeros, int H, int W, int Ci,
                                                                 int Co, int Ho, int Wo, int m_tiles_total,
-                                                                int tiles_c, int tiles_per_image, int co_blocks, int total,
-                                                                int work_per_xcd, int blocks, Epilogue ep)
+                                                                WorkOrder order, int blocks, Epilogue ep)
 {
     using G = Geom<S, RT, CT>;
     static_assert(RT * CT == 4 * TN, "four waves share the position blocks of a workgroup");
@@ -100,29 +100,28 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Workgroups are dealt to the 8 XCDs in turn.  Work items are numbered with the channel block
-    // fastest and each XCD takes a contiguous range, so the workgroups that read the same activation
-    // tile (one per channel block) run on one XCD at about the same time and share its L2.
-    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
-    if (work >= total) return;
-    const int mt0 = (work % co_blocks) * TM;
+    const int work = order.item();
+    if (work >= order.total) return;
+    const int all_tile = order.co_blocks.quotient(work), mt0 = order.co_blocks.remainder(work, all_tile) * TM;
     // this wave's blocks of 4x4 output positions
     int n_of[TN], oh_of[TN], ow_of[TN];
     bool live[TN];
+    const WorkOrder::Tile tile = order.tile(all_tile);  // (stride 1)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        if constexpr (PATCH) {  // (tiles_c, tiles_per_image: blocks)
-            const int blk = work / co_blocks * (4 * TN) + wave * TN + j, at = blk % tiles_per_image;
+        if constexpr (PATCH) {  // (the order's tiles are blocks)
+            const int blk = all_tile * (4 * TN) + wave * TN + j;
+            const WorkOrder::Tile at = order.tile(blk);
             live[j] = blk < blocks;
-            n_of[j] = blk / tiles_per_image;
-            oh_of[j] = 4 * (at / tiles_c);
-            ow_of[j] = 4 * (at % tiles_c);
+            n_of[j] = at.n_img;
+            oh_of[j] = 4 * at.row;
+            ow_of[j] = 4 * at.col;
         } else {
-            const int blk = wave * TN + j, tile = (work / co_blocks) % tiles_per_image;
+            const int blk = wave * TN + j;
             live[j] = true;
-            n_of[j] = work / co_blocks / tiles_per_image;
-            oh_of[j] = tile / tiles_c * G::TH + 4 * (blk / CT);
-            ow_of[j] = tile % tiles_c * G::TW + 4 * (blk % CT);
+            n_of[j] = tile.n_img;
+            oh_of[j] = tile.row * G::TH + 4 * (blk / CT);
+            ow_of[j] = tile.col * G::TW + 4 * (blk % CT);
         }
     }
     const int stages = RAG ? (Ci + 31) / 32 : Ci / 32;
@@ -161,11 +160,10 @@ __global__ __launch_bounds__(256) void conv3x3_sparse_sb_kernel(const T* __restr
             inside = c < TN * kPatch / 16 && (second ? live[TN - 1] : live[0]);
         } else {
             const int c = (k * 4 + wave) * 64 + lane, pos = c / G::kChunks;
-            const int tile = (work / co_blocks) % tiles_per_image;
             q = c % G::kChunks;
             n = n_of[0];
-            ih = tile / tiles_c * G::TH - 1 + pos / G::LW;
-            iw = tile % tiles_c * G::TW - 1 + pos % G::LW;
+            ih = tile.row * G::TH - 1 + pos / G::LW;
+            iw = tile.col * G::TW - 1 + pos % G::LW;
             inside = pos / G::LW < G::IH && pos % G::LW < G::IW;
         }
         if (RAG && (stages - 1) * 32 + 8 * q < Ci) tail_ok |= 1u << k;
@@ -590,11 +588,10 @@ rtoss_status launch_variant_sb(const rtoss_wdesc& d, const ConvParams& c, const 
     const int64_t total = (S == 2 ? (blocks + 4 * TN - 1) / (4 * TN) : blocks) * co_blocks;
     if (total > 0x3fffffff || blocks > 0x7fffff00) return fail(RTOSS_ESHAPE, "conv: too many tiles");
     if ((int64_t)c.N * c.H * c.W * d.Ci / 8 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
-    const int work_per_xcd = (int)((total + 7) / 8);
-    dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
+    const WorkOrder order(total, co_blocks, tiles_r * tiles_c, tiles_c);
+    dim3 grid(order.grid()), block(256);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + fragment_bytes(d, LAY), c.H, c.W, d.Ci, d.Co, Ho, Wo,
-                                   m_tiles_total, tiles_c, tiles_r * tiles_c, co_blocks, (int)total, work_per_xcd, (int)blocks,
-                                   c.ep);
+                                   m_tiles_total, order, (int)blocks, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 sparse launch");
 }
 

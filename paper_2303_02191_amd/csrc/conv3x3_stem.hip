@@ -18,6 +18,7 @@
 #include "dtypes.h"
 #include "epilogue.h"
 #include "mma.h"
+#include "work_order.h"
 #include "stem_rows.h"
 
 namespace rtoss {
@@ -32,7 +33,7 @@ constexpr int kTH = 8, kTW = 32;  // output tile: 8 rows x 32 columns = 16 block
 template <typename T, typename TO, int S, int TM, int Ci>
 __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                            const char* __restrict__ wfrag, int H, int W, int Co,
-                                                           int Ho, int Wo, int tiles_c, int odd_image, Epilogue ep)
+                                                           int Ho, int Wo, Divisor tiles_c, int odd_image, Epilogue ep)
 {
     constexpr int IH = (kTH - 1) * S + 3, IW = (kTW - 1) * S + 3;
     constexpr int kRow = IW * Ci;                 // halves of an input row of the tile
@@ -46,7 +47,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 6 : 4) void conv3x3_stem_kernel(cons
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tile_r = blockIdx.x / tiles_c, tile_c = blockIdx.x % tiles_c;
+    const int tile_r = tiles_c.quotient(blockIdx.x), tile_c = tiles_c.remainder(blockIdx.x, tile_r);
     const int n_img = blockIdx.y;
     const int oh0 = tile_r * kTH, ow0 = tile_c * kTW;
     const int ih0 = oh0 * S - 1, iw0 = ow0 * S - 1;
@@ -169,7 +170,7 @@ rtoss_status launch_stem_ci(const rtoss_wdesc& d, const ConvParams& c, const cha
     const int tiles_r = (Ho + kTH - 1) / kTH, tiles_c = (Wo + kTW - 1) / kTW;
     if (c.N > 65535) return fail(RTOSS_ESHAPE, "conv: batch too large");
     dim3 grid((unsigned)(tiles_r * tiles_c), (unsigned)c.N), block(256);
-    conv3x3_stem_kernel<T, TO, S, TM, Ci><<<grid, block, 0, s>>>((const T*)x, (TO*)y, wfrag, c.H, c.W, d.Co, Ho, Wo, tiles_c,
+    conv3x3_stem_kernel<T, TO, S, TM, Ci><<<grid, block, 0, s>>>((const T*)x, (TO*)y, wfrag, c.H, c.W, d.Co, Ho, Wo, Divisor(tiles_c),
                                                                  c.N & c.H & c.W & Ci & 1 ? c.N - 1 : -1, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 stem launch");
 }

@@ -33,6 +33,7 @@
 #include "mma.h"
 #include "pack_plan.h"
 #include "sparse_frag.h"
+#include "work_order.h"
 #include "strip_output.h"
 
 namespace rtoss {
@@ -73,8 +74,7 @@ template <int TN, int LAY, bool DB> struct Strip {
 
 template <typename T, typename TO, int TN, int LAY, bool DB, bool ROWS_OUT>
 __device__ __forceinline__ void strip_tile(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                           int H, int W, int Ci, int Co, int m_tiles_total, int strips, int tiles_per_image, int co_blocks, int total,
-                                           int work_per_xcd, const Epilogue& ep)
+                                           int H, int W, int Ci, int Co, int m_tiles_total, WorkOrder order, const Epilogue& ep)
 {
     using P = Strip<TN, LAY, DB>;
     constexpr TapLayout LY = kLayouts[LAY == kDenseTaps ? 0 : LAY];
@@ -85,13 +85,11 @@ __device__ __forceinline__ void strip_tile(const T* __restrict__ x, TO* __restri
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // XCD-contiguous work order, channel block fastest: the workgroups of one activation tile share an L2
-    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
-    if (work >= total) return;
-    const int cb = work % co_blocks;
-    const int tile = (work / co_blocks) % tiles_per_image;
-    const int n_img = (work / co_blocks) / tiles_per_image;
-    const int oh0 = (tile / strips) * P::ROWS, ow0 = (tile % strips) * kCols;
+    const int work = order.item();
+    if (work >= order.total) return;
+    const int all_tile = order.co_blocks.quotient(work), cb = order.co_blocks.remainder(work, all_tile);
+    const WorkOrder::Tile tile = order.tile(all_tile);
+    const int n_img = tile.n_img, oh0 = tile.row * P::ROWS, ow0 = tile.col * kCols;
     const int stages = Ci / (4 * PER);
 
     EpiScaleBias<16 * kTM> scale_bias;
@@ -234,19 +232,16 @@ __device__ __forceinline__ void strip_tile(const T* __restrict__ x, TO* __restri
 template <typename T, typename TO, int TN, int LAY, bool DB>
 __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
                                                                const char* __restrict__ zeros, int H, int W, int Ci, int Co, int m_tiles_total,
-                                                               int strips, int tiles_per_image, int co_blocks, int total, int work_per_xcd,
-                                                               Epilogue ep)
+                                                               WorkOrder order, Epilogue ep)
 {
-    strip_tile<T, TO, TN, LAY, DB, DB && sizeof(TO) == 2>(x, y, wfrag, zeros, H, W, Ci, Co, m_tiles_total, strips, tiles_per_image, co_blocks, total,
-                                                          work_per_xcd, ep);
+    strip_tile<T, TO, TN, LAY, DB, DB && sizeof(TO) == 2>(x, y, wfrag, zeros, H, W, Ci, Co, m_tiles_total, order, ep);
 }
 template <typename T, typename TO, int TN, int LAY, bool DB, bool ROWS>
 __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
                                                                const char* __restrict__ zeros, int H, int W, int Ci, int Co, int m_tiles_total,
-                                                               int strips, int tiles_per_image, int co_blocks, int total, int work_per_xcd,
-                                                               Epilogue ep)
+                                                               WorkOrder order, Epilogue ep)
 {
-    strip_tile<T, TO, TN, LAY, DB, ROWS>(x, y, wfrag, zeros, H, W, Ci, Co, m_tiles_total, strips, tiles_per_image, co_blocks, total, work_per_xcd, ep);
+    strip_tile<T, TO, TN, LAY, DB, ROWS>(x, y, wfrag, zeros, H, W, Ci, Co, m_tiles_total, order, ep);
 }
 
 // Dense mode.  A tap's fragment is used for one product per row and tile and needs no transposition, so here the weights stay out
@@ -402,32 +397,30 @@ __device__ __forceinline__ void dense_strip_tile(const T* __restrict__ x, TO* __
 template <typename T, int ROWS> constexpr int dense_strip_lds = sizeof(T) == 4 ? F32Tile<1, ROWS>::LDS : DenseStrip<ROWS>::LDS;
 template <typename T, typename TO, int ROWS, bool ROWS_OUT>
 __device__ __forceinline__ void dense_strip_work(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
-                                                 const char* __restrict__ zeros, int H, int W, int Ci, int Co, int strips, int tiles_per_image,
-                                                 int co_blocks, int total, int work_per_xcd, const Epilogue& ep)
+                                                 const char* __restrict__ zeros, int H, int W, int Ci, int Co, WorkOrder order, const Epilogue& ep)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int work = (blockIdx.x % 8) * work_per_xcd + blockIdx.x / 8;
-    if (work >= total) return;
-    const int cb = work % co_blocks, tile = (work / co_blocks) % tiles_per_image, n_img = (work / co_blocks) / tiles_per_image;
-    const int oh0 = (tile / strips) * ROWS, ow0 = (tile % strips) * kCols;
+    const int work = order.item();
+    if (work >= order.total) return;
+    const int all_tile = order.co_blocks.quotient(work), co_blocks = order.co_blocks.by, cb = order.co_blocks.remainder(work, all_tile);
+    const WorkOrder::Tile tile = order.tile(all_tile);
+    const int n_img = tile.n_img, oh0 = tile.row * ROWS, ow0 = tile.col * kCols;
     if constexpr (sizeof(T) == 4) dense3x3_f32_tile<1, ROWS, false>(x, y, wfrag, zeros, H, W, Ci, Co, H, W, co_blocks, cb, n_img, oh0, ow0, ep, smem);
     else dense_strip_tile<T, TO, ROWS, ROWS_OUT>(x, y, wfrag, zeros, H, W, Ci, Co, co_blocks, cb, n_img, oh0, ow0, ep, smem);
 }
 template <typename T, typename TO, int ROWS>
 __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                                const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                               int H, int W, int Ci, int Co, int strips, int tiles_per_image,
-                                                               int co_blocks, int total, int work_per_xcd, Epilogue ep)
+                                                               int H, int W, int Ci, int Co, WorkOrder order, Epilogue ep)
 {
-    dense_strip_work<T, TO, ROWS, false>(x, y, wfrag, zeros, H, W, Ci, Co, strips, tiles_per_image, co_blocks, total, work_per_xcd, ep);
+    dense_strip_work<T, TO, ROWS, false>(x, y, wfrag, zeros, H, W, Ci, Co, order, ep);
 }
 template <typename T, typename TO, int ROWS, bool ROWS_OUT>
 __global__ __launch_bounds__(256, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y,
                                                                const char* __restrict__ wfrag, const char* __restrict__ zeros,
-                                                               int H, int W, int Ci, int Co, int strips, int tiles_per_image,
-                                                               int co_blocks, int total, int work_per_xcd, Epilogue ep)
+                                                               int H, int W, int Ci, int Co, WorkOrder order, Epilogue ep)
 {
-    dense_strip_work<T, TO, ROWS, ROWS_OUT>(x, y, wfrag, zeros, H, W, Ci, Co, strips, tiles_per_image, co_blocks, total, work_per_xcd, ep);
+    dense_strip_work<T, TO, ROWS, ROWS_OUT>(x, y, wfrag, zeros, H, W, Ci, Co, order, ep);
 }
 
 template <typename T, typename TO, int ROWS, bool... ROWS_OUT>
@@ -439,9 +432,8 @@ rtoss_status launch_dense_rows(const rtoss_wdesc& d, const ConvParams& c, const 
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, lds, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)strips * rows * co_blocks * c.N;  // (at most kMaxGridGroups: strip3x3_plan)
-    const int work_per_xcd = (int)((total + 7) / 8);
-    kern<<<dim3((unsigned)(work_per_xcd * 8)), dim3(256), lds, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, strips,
-                                                                   strips * rows, co_blocks, (int)total, work_per_xcd, c.ep);
+    const WorkOrder order(total, co_blocks, strips * rows, strips);
+    kern<<<dim3(order.grid()), dim3(256), lds, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, order, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 strip launch");
 }
 
@@ -457,11 +449,10 @@ rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* 
     const int64_t total = (int64_t)strips * rows * co_blocks * c.N;
     if (total > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
     if ((int64_t)c.N * c.H * c.W * d.Ci * (int)sizeof(T) / 16 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
-    const int work_per_xcd = (int)((total + 7) / 8);
-    dim3 grid((unsigned)(work_per_xcd * 8)), block(256);
+    const WorkOrder order(total, co_blocks, strips * rows, strips);
+    dim3 grid(order.grid()), block(256);
     kern<<<grid, block, P::LDS, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co,
-                                     LAY == kDenseTaps ? kTM * co_blocks : padded_m_tiles(d.Co), strips, strips * rows, co_blocks,
-                                     (int)total, work_per_xcd, c.ep);
+                                     LAY == kDenseTaps ? kTM * co_blocks : padded_m_tiles(d.Co), order, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 strip launch");
 }
 
