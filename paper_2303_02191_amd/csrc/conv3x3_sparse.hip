@@ -609,6 +609,9 @@ rtoss_status launch_typed_ragged(const rtoss_wdesc& d, const ConvParams& c, cons
 // compute units one) take the pipelined kernel of conv3x3_rows.hip, whatever the layout.  (us, the kernels for smaller launches and the
 // pipelined one, bf16, 3 entries / 4: 2x128@100x168, 154 tiles 10.3 12.1 / 11.8 13.9, 1x256@100x168, 154 tiles 15.4 18.8 / 18.2 21.3, 4x256@80x80,
 // 200 tiles 22.3 19.5 / 27.0 23.2, 2x256@100x168, 308 tiles 38.1 24.1 / 32.6 28.5.)
+// What the strips with helper waves hold in one round is theirs, whatever its tiles (conv3x3_ring.hip; us, pipelined and there: 16x512@20x20 33.6
+// 25.8 / 39.9 31.9, 25x256@20x20 18.3 14.2 / 20.9 16.9, 64x128@20x32 12.7 10.4 / 15.4 12.1, with half a block of 128 channels empty
+// 4x192@80x80 15.6 13.0 / 17.2 14.4, 25x256->320@20x20 21.0 14.4 / 24.2 17.0): it spreads over the units in strips of 64 channels.
 inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
 {
     if (c.stride != 1 || d.Co <= 64 || d.Ci <= 64 || ragged(d)) return false;
@@ -716,10 +719,10 @@ rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, in
     const bool f32out = c.out_dt == RTOSS_F32;
     if (const int plan = ksplit3x3_plan(d, c, layout))
         return launch_conv3x3_ksplit(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
+    if (const int plan = ring3x3_plan(d, c, layout))
+        return launch_conv3x3_ring(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
     const bool pipelined = takes_pipelined_kernel(d, c);
     if (!pipelined) {
-        if (const int plan = ring3x3_plan(d, c, layout))
-            return launch_conv3x3_ring(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
         if (const int plan = strip3x3_plan(d, c, layout))
             return launch_conv3x3_strip(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
     }

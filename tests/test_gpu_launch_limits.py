@@ -68,11 +68,11 @@ PITCH_CASES = [
     (wl.F16, wl.F16, 1, 128, 640, 4, 500, 1, 1, 2, True, False, "conv1x1_stream<4,4>", "conv_direct<1,1,0>"),
     (wl.F32, wl.F32, 1, 16, 64, 1, 70, 1, 1, 2, True, False, "conv1x1_stream<1,1>", "conv1x1_stream<1,1,false>"),
     (wl.F16, wl.F16, 1, 72, 32, 1, 70, 1, 1, 2, False, False, "conv1x1_mma<1,2,true>", "conv1x1_mma<1,2,true>"),
-    (wl.F16, wl.F16, 1, 128, 16384, 20, 16, 3, 1, 3, False, False, "conv3x3_rows<false,0>", "conv3x3_sparse_sb<1,4,2,2,4,true,0,true,false>"),
-    (wl.F16, wl.F16, 1, 128, 16384, 20, 16, 3, 1, 3, True, False, "conv3x3_rows<true,0>", "conv3x3_rows<true,0>"),
+    (wl.F16, wl.F16, 1, 128, 16512, 20, 16, 3, 1, 3, False, False, "conv3x3_rows<false,0>", "conv3x3_sparse_sb<1,4,2,2,4,true,0,true,false>"),
+    (wl.F16, wl.F16, 1, 128, 16512, 20, 16, 3, 1, 3, True, False, "conv3x3_rows<true,0>", "conv3x3_rows<true,0>"),
     (wl.BF16, wl.BF16, 1, 128, 8192, 20, 16, 3, 1, 3, True, False, "conv3x3_strip<3,0>", "conv3x3_sparse_sb<1,4,2,2,4,true,0,true,false>"),
     (wl.BF16, wl.BF16, 1, 128, 16384, 20, 16, 3, 1, 6, False, False, "conv3x3_strip<20,true>", "conv3x3_strip<20>"),
-    (wl.F16, wl.F16, 1, 128, 16384, 20, 16, 3, 1, 5, False, False, "conv3x3_rows<false,1>", "conv3x3_strip<3,1,false>"),
+    (wl.F16, wl.F16, 1, 128, 16512, 20, 16, 3, 1, 5, False, False, "conv3x3_rows<false,1>", "conv3x3_strip<5,1,false>"),
     (wl.F32, wl.F32, 1, 64, 16384, 20, 16, 3, 1, 3, False, False, "conv3x3_strip<8>", "conv3x3_dense<1,1,1,4,false>"),
     (wl.F32, wl.F32, 1, 64, 2048, 20, 16, 3, 1, 3, True, False, "conv3x3_dense<1,4,false>", "conv3x3_dense<1,1,1,4,false>"),
     (wl.BF16, wl.BF16, 1, 256, 16384, 20, 16, 3, 1, 3, False, True, "conv3x3_gather_rows<>", "conv3x3_gather<1>"),
@@ -121,7 +121,7 @@ def test_output_pitch_past_32_bit_offsets(case, rows):
 
 
 # The pipelined 3x3 kernel's output through LDS (a fused stage, fp32 results): a tile of 20 rows of 16 positions.
-WIDE_TILE = dict(N=1, H=20, W=16, Ci=128, Co=16384, ks=3, stride=1, k=3)
+WIDE_TILE = dict(N=1, H=20, W=16, Ci=128, Co=16512, ks=3, stride=1, k=3)
 
 
 @pytest.mark.parametrize("out_dt,fused", [(wl.F16, True), (wl.F32, True), (wl.F32, False)])

@@ -24,6 +24,13 @@ CASES = [
 ]
 
 
+# as many tiles as the pipelined kernel takes otherwise, which computes their fp32 results: the same sums, an output stage of its own
+WIDE_CASES = [
+    (5, wl.F16, 15, 512, 496, 20, 19, 3),
+    (5, wl.BF16, 24, 256, 272, 19, 20, 5),
+]
+
+
 @pytest.mark.parametrize("case", CASES, ids=str)
 def test_ring_against_strips(case):
     tn, dt, N, Ci, Co, H, W, k = case
@@ -42,3 +49,21 @@ def test_ring_against_strips(case):
     want = layer.conv_fused(x, scale=scale, bias=bias, act=B.ACT_SILU, residual=res.float(), out_dt=wl.F32).to(T)
     assert torch.equal(buf[..., 8:8 + Co], want)
     assert bool((buf[..., :8] == 7.0).all()) and bool((buf[..., 8 + Co:] == 7.0).all())
+
+
+@pytest.mark.parametrize("case", WIDE_CASES, ids=str)
+def test_ring_against_the_pipelined_kernel(case):
+    tn, dt, N, Ci, Co, H, W, k = case
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Ci + H)
+    T = pl.TORCH_DTYPE[dt]
+    masks = B.rtoss_pattern_dict(k)
+    w = (torch.randn((Co, Ci, 3, 3), generator=g, device="cuda") / Ci ** 0.5).to(T)
+    layer = pl.PackedLayer(Co, Ci, 3, k, dt, masks).pack(w, pl.select_patterns(w, dt, masks))
+    x = torch.randn((N, H, W, Ci), generator=g, device="cuda").to(T)
+    assert torch.equal(layer.conv(x, relu=True), layer.conv(x, relu=True, out_dt=wl.F32).to(T))
+    stage = dict(scale=torch.rand(Co, generator=g, device="cuda") + 0.5, bias=torch.randn(Co, generator=g, device="cuda"), act=B.ACT_SILU)
+    want = layer.conv_fused(x, out_dt=wl.F32, **stage)
+    # one rounding to the stored type (half a unit), and the fp32 roundings of two orders of one output stage
+    bound = want.abs() * {wl.F16: 2.0 ** -11, wl.BF16: 2.0 ** -8}[dt] + 1e-5 * want.abs().max()
+    assert ((layer.conv_fused(x, **stage).float() - want).abs() <= bound).all()

@@ -86,9 +86,12 @@ def test_cases_made_for_a_kernel_reach_it(fused):
     assert families(routes.kernels(calls)) == ["conv1x1_stream"] * len(calls)
 
 
+RING_CASES = test_gpu_strip_ring.CASES + test_gpu_strip_ring.WIDE_CASES
+
+
 def test_ring_cases_reach_the_height_they_name():
-    calls = [call(dt, N, Ci, Co, H, W, 3, 1, k, dt, fused) for tn, dt, N, Ci, Co, H, W, k in test_gpu_strip_ring.CASES for fused in (False, True)]
-    want = ["conv3x3_strip<%d,%d>" % (c[0], c[-1] == 4) for c in test_gpu_strip_ring.CASES for fused in (False, True)]
+    calls = [call(dt, N, Ci, Co, H, W, 3, 1, k, dt, fused) for tn, dt, N, Ci, Co, H, W, k in RING_CASES for fused in (False, True)]
+    want = ["conv3x3_strip<%d,%d>" % (c[0], c[-1] >= 4) for c in RING_CASES for fused in (False, True)]
     assert [split(k)[0] for k in routes.kernels(calls)] == want
 
 
