@@ -81,3 +81,21 @@ def test_sparse_pack_of_tensors_aligned_to_their_element_only():
     got = pl.PackedLayer(Co, Ci, 3, k, dt, masks).pack(w2, idx2)
     torch.cuda.synchronize()
     assert torch.equal(got.blob, ref.blob)
+
+
+@pytest.mark.parametrize("dt,Co,Ci,ks,k", [(wl.BF16, 144, 64, 3, 5), (wl.F16, 40, 24, 3, 4), (wl.F16, 33, 70, 1, 2), (wl.F32, 16, 48, 1, 3)])
+def test_layers_saved_with_other_private_sections(dt, Co, Ci, ks, k):
+    """A layer's state without the mark of today's private sections: packed again from the public one."""
+    masks = B.rtoss_pattern_dict(k)
+    rng = np.random.default_rng(Co)
+    w = pl.to_device(wl.round_to_dtype(rng.standard_normal((Co, Ci, ks, ks)) * 0.1, dt), dt)
+    layer = pl.PackedLayer(Co, Ci, ks, k, dt, masks).pack(w, pl.select_patterns(w, dt, masks))
+    x = torch.randn((2, 9, 11, Ci), device="cuda").to(pl.TORCH_DTYPE[dt])
+    state = dict(layer.__getstate__())
+    del state["private_format"]
+    groups = Co * Ci * ks * ks // 9
+    public = -(-groups * k * wl.ELEM_BYTES[dt] // 256) * 256 + groups
+    state["blob"] = layer.blob[:public].clone()
+    other = pl.PackedLayer.__new__(pl.PackedLayer)
+    other.__setstate__(state)
+    assert torch.equal(other.conv(x), layer.conv(x))
