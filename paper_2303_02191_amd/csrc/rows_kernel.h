@@ -371,13 +371,25 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
                             // this stage's first ten units and this unit's operands were read in unit 18; the
                             // wave waits for its copies and its reads, meets the others at a bare barrier (the
                             // next stage's data is now complete and nobody reads this stage's region any more)
-                            // and issues the next stage's first reads, which complete under the rest of this unit.
+                            // and issues the next stage's first reads (below), which complete under the rest of this unit.
                             asm volatile("" ::: "memory");
                             __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): copies landed, reads of this region done
                             __builtin_amdgcn_s_barrier();
                             asm volatile("" ::: "memory");
-                            load_stage_prologue(gpar ^ 1, xrd);
                         }
+                    }
+                    if constexpr (u == 19) {
+                        // The next stage's first reads (load_stage_prologue), one or two behind each instruction.  All behind the first they kept
+                        // the matrix pipe waiting for their issue: 256 -> 256 on 4x100x168 42.5 us, now 41.6, on 2x100x168 22.5, 22.2.
+                        constexpr int kReads = 2 + kTall + 8, first = i * kReads / UNIT;
+                        const char* const nA = smem + (gpar ^ 1) * REGION + lane * 16;
+                        const char* const nX = smem + (gpar ^ 1) * REGION + A_BYTES + xrd;
+                        static_for<(i + 1) * kReads / UNIT - first>([&](auto k_tag) {
+                            constexpr int n = first + decltype(k_tag)::value, centre = n - 1, side = n - 2 - kTall;
+                            if constexpr (n < 2) a_nxt[n] = *(const u32x4*)(nA + n * TILE + 4 * kFragBytes);
+                            else if constexpr (side < 0) R[centre][1] = *(const u32x4*)(nX + (centre * kLW + 1) * kPosBytes);
+                            else R[side / 2][side % 2 * 2] = *(const u32x4*)(nX + (side / 2 * kLW + side % 2 * 2) * kPosBytes);
+                        });
                     }
                     // this instruction's share of the unit's 16 * perm_count permutes
                     constexpr int o_begin = i * 16 * perm_count / UNIT, o_end = (i + 1) * 16 * perm_count / UNIT;
