@@ -68,15 +68,18 @@ RowPlan make_plan(int N, int H, int W, int co_blocks, int sa, int a5, int a4, in
 
 // Searches the cuts (n5 tall + n4 short tiles covering H rows with no tile to spare) for the two strip
 // classes and the number of strips of the first class; results are remembered per launch shape.
-RowPlan plan_rows(int N, int H, int W, int co_blocks, int stages, int slots)
+RowPlan plan_rows(int N, int H, int W, int co_blocks, int stages, int slots, double* cost)
 {
     static std::mutex mu;
-    static std::map<PlanKey, RowPlan> cache;
+    static std::map<PlanKey, std::pair<RowPlan, double>> cache;
     const PlanKey key{N, H, W, co_blocks, stages, slots};
     {
         std::lock_guard<std::mutex> lock(mu);
         auto it = cache.find(key);
-        if (it != cache.end()) return it->second;
+        if (it != cache.end()) {
+            if (cost) *cost = it->second.second;
+            return it->second.first;
+        }
     }
     struct Cut {
         int n5, n4;
@@ -106,18 +109,19 @@ RowPlan plan_rows(int N, int H, int W, int co_blocks, int stages, int slots)
         }
     std::lock_guard<std::mutex> lock(mu);
     if (cache.size() > 4096) cache.clear();
-    cache[key] = best;
+    cache[key] = {best, best_cost};
+    if (cost) *cost = best_cost;
     return best;
 }
 
-RowPlan plan_rows_for_device(int N, int H, int W, int co_blocks, int stages, int cus, int* slots_out)
+RowPlan plan_rows_for_device(int N, int H, int W, int co_blocks, int stages, int cus, int* slots_out, double* cost)
 {
     // one workgroup per compute unit (a workgroup owns nearly all of a unit's LDS)
     const int full = std::max(8, cus) / 8;
-    RowPlan plan = plan_rows(N, H, W, co_blocks, stages, full);
+    RowPlan plan = plan_rows(N, H, W, co_blocks, stages, full, cost);
     // (fewer entries than workgroups: launch only as many slots per XCD as the longer list needs)
     const int slots = std::max(1, std::min(full, std::max(plan.tall_per_xcd, plan.short_per_xcd)));
-    if (slots != full) plan = plan_rows(N, H, W, co_blocks, stages, slots);
+    if (slots != full) plan = plan_rows(N, H, W, co_blocks, stages, slots, cost);
     *slots_out = slots;
     return plan;
 }

@@ -54,9 +54,10 @@ __device__ __forceinline__ TileCoord decode_entry(const RowPlan& p, bool tall, i
 
 // The cut of a launch shape into tall and short tiles with the smallest busiest-workgroup cost, for `slots`
 // workgroups per XCD and `stages` stages of 32 input channels per tile; results are remembered per shape.
-RowPlan plan_rows(int N, int H, int W, int co_blocks, int stages, int slots);
+// cost (where asked for): the busiest workgroup's.
+RowPlan plan_rows(int N, int H, int W, int co_blocks, int stages, int slots, double* cost = nullptr);
 // One workgroup per compute unit, fewer when the tile lists are shorter: sets *slots (workgroups per XCD; the grid
 // is 8 * slots) and returns the plan for it.
-RowPlan plan_rows_for_device(int N, int H, int W, int co_blocks, int stages, int cus, int* slots);
+RowPlan plan_rows_for_device(int N, int H, int W, int co_blocks, int stages, int cus, int* slots, double* cost = nullptr);
 
 }  // namespace rtoss

@@ -10,6 +10,7 @@ import test_gpu_fused
 import test_gpu_ksplit
 import test_gpu_ksplit1x1
 import test_gpu_launch_limits
+import test_gpu_rows_groups
 import test_gpu_slices
 import test_gpu_stream1x1
 import test_gpu_stride2_rows
@@ -138,6 +139,16 @@ def test_calls_past_launch_limits_leave_the_kernel_with_the_limit():
              (wl.F16, 64800, 182, 182, 2, 1, 1, 1, 2)]
     calls = [call(dt, N, Ci, Co, H, W, ks, stride, k, dt, False) for dt, N, H, W, Ci, Co, ks, stride, k in below]
     assert families(routes.kernels(calls)) == ["conv3x3_sparse_sb", "conv3x3_sparse_sb", "conv3x3_dense", "conv1x1_mma"]
+
+
+def test_cases_of_three_groups_reach_the_pipelined_kernel():
+    calls = [call(dt, N, Ci, Co, H, W, 3, 1, k, out_dt, fused) for dt, N, Ci, Co, H, W, k in test_gpu_rows_groups.CASES
+             for out_dt in (dt, wl.F32) for fused in (False, True)]
+    assert families(routes.kernels(calls)) == ["conv3x3_rows"] * len(calls)
+    # launches whose tiles would be mostly empty stay with the strips
+    calls = [call(wl.BF16, N, Ci, Co, H, W, 3, 1, 4, wl.BF16, False) for N, Ci, Co, H, W in
+             ((200, 96, 112, 5, 3), (200, 128, 128, 8, 16), (40, 96, 256, 24, 17), (4, 160, 144, 112, 162), (2, 128, 256, 33, 330))]
+    assert families(routes.kernels(calls)) == ["conv3x3_strip"] * len(calls)
 
 
 def test_wide_tile_reaches_the_pipelined_kernel():
