@@ -145,18 +145,19 @@ class PackedLayer(_Layer):
         if state.get("private_format") == self.PRIVATE_FORMAT or not self.blob.is_cuda:
             return
         d = self.wdesc
-        groups, taps = d.Co * d.Ci * d.ksize ** 2 // 9, [[t for t in range(9) if int(m) >> t & 1] for m in self.masks]
-        eb = torch.empty(0, dtype=TORCH_DTYPE[self.dt]).element_size()
-        at = -(-groups * d.k * eb // 256) * 256
-        live = self.blob[:groups * d.k * eb].view(TORCH_DTYPE[self.dt]).reshape(groups, d.k)
-        idx = self.blob[at:at + groups].clone()
-        w = torch.zeros(d.Co * d.Ci * d.ksize ** 2, dtype=live.dtype, device=self.blob.device)
-        taps = torch.tensor(taps, device=self.blob.device)[idx.long().clamp(max=len(taps) - 1)]  # (a layer that was never packed: anything)
-        w[:9 * groups].view(groups, 9).scatter_(1, taps, live)
-        self.packed_bytes, self.workspace_bytes = B.rtoss_pack_size(d, self.masks)
-        self.blob = torch.empty(self.packed_bytes, dtype=torch.uint8, device=self.blob.device)
-        self.private_format = self.PRIVATE_FORMAT
-        self.pack(w, idx)
+        with torch.cuda.device(self.blob.device):  # (and that device's current stream, whatever the caller's are)
+            groups, taps = d.Co * d.Ci * d.ksize ** 2 // 9, [[t for t in range(9) if int(m) >> t & 1] for m in self.masks]
+            eb = torch.empty(0, dtype=TORCH_DTYPE[self.dt]).element_size()
+            at = -(-groups * d.k * eb // 256) * 256
+            live = self.blob[:groups * d.k * eb].view(TORCH_DTYPE[self.dt]).reshape(groups, d.k)
+            idx = self.blob[at:at + groups].clone()
+            w = torch.zeros(d.Co * d.Ci * d.ksize ** 2, dtype=live.dtype, device=self.blob.device)
+            taps = torch.tensor(taps, device=self.blob.device)[idx.long().clamp(max=len(taps) - 1)]  # (a layer that was never packed: anything)
+            w[:9 * groups].view(groups, 9).scatter_(1, taps, live)
+            self.packed_bytes, self.workspace_bytes = B.rtoss_pack_size(d, self.masks)
+            self.blob = torch.empty(self.packed_bytes, dtype=torch.uint8, device=self.blob.device)
+            self.private_format = self.PRIVATE_FORMAT
+            self.pack(w, idx)
 
     def pack(self, w, idx, stream=None):
         """stream: raw HIP stream handle (default: torch's current stream)."""

@@ -99,3 +99,23 @@ def test_layers_saved_with_other_private_sections(dt, Co, Ci, ks, k):
     other = pl.PackedLayer.__new__(pl.PackedLayer)
     other.__setstate__(state)
     assert torch.equal(other.conv(x), layer.conv(x))
+
+
+def test_packed_again_on_the_blobs_device(monkeypatch):
+    """... and on that device's current stream, which its inputs were made on, whatever device the caller is on."""
+    dt, Co, Ci, k = wl.BF16, 144, 64, 5
+    masks = B.rtoss_pattern_dict(k)
+    w = pl.to_device(wl.round_to_dtype(np.random.default_rng(3).standard_normal((Co, Ci, 3, 3)) * 0.1, dt), dt)
+    layer = pl.PackedLayer(Co, Ci, 3, k, dt, masks).pack(w, pl.select_patterns(w, dt, masks))
+    state = dict(layer.__getstate__())
+    del state["private_format"]
+    state["blob"] = torch.cat([layer.blob, layer.blob[:512]])  # (another size: other sections)
+    inside, packed, enter, leave, pack = [], [], torch.cuda.device.__enter__, torch.cuda.device.__exit__, B.rtoss_pack
+    monkeypatch.setattr(torch.cuda.device, "__enter__", lambda guard: (inside.append(guard.idx), enter(guard))[1])
+    monkeypatch.setattr(torch.cuda.device, "__exit__", lambda guard, *a: (inside.pop(), leave(guard, *a))[1])
+    monkeypatch.setattr(B, "rtoss_pack", lambda *a: (packed.append(inside[-1:]), pack(*a)))
+    other = pl.PackedLayer.__new__(pl.PackedLayer)
+    other.__setstate__(state)
+    assert packed == [[layer.blob.device.index]]
+    x = torch.randn((2, 9, 11, Ci), device="cuda").to(pl.TORCH_DTYPE[dt])
+    assert torch.equal(other.conv(x), layer.conv(x))
