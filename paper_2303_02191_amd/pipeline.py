@@ -4,12 +4,15 @@ No arithmetic happens here: torch is used for device memory and the current stre
 selection, packing and convolution all run in librtoss.so.  The calls a forward repeats go
 through one native function each (csrc/host_ext.cpp).
 """
+import threading
+
 import torch
 
 from . import binding as B
 
 TORCH_DTYPE = {B.F32: torch.float32, B.F16: torch.float16, B.BF16: torch.bfloat16}
 _host = None  # binding.host(), once there is a layer
+_repacking = threading.Lock()
 
 
 def _stream():
@@ -78,8 +81,11 @@ class _Layer:
         _host = B.host()
         self._native = None
         # (a dictionary that is no uint16 array, such as a list, is converted at every call instead)
-        if B.dictionary(self.masks) is self.masks:
+        if self._readable() and B.dictionary(self.masks) is self.masks:
             self._native = self._bound()
+
+    def _readable(self):
+        return True
 
     def __setattr__(self, name, value):
         object.__setattr__(self, name, value)
@@ -130,38 +136,65 @@ class PackedLayer(_Layer):
         self.masks = masks
         self.dt = dt
         self.packed_bytes, self.workspace_bytes = B.rtoss_pack_size(self.wdesc, masks)
+        self.private_format = self.PRIVATE_FORMAT
         self._bind()
         # torch's caching allocator returns 512-byte aligned blocks
         self.blob = torch.empty(self.packed_bytes, dtype=torch.uint8, device=device)
         self.workspace = torch.empty(max(self.workspace_bytes, 1), dtype=torch.uint8, device=device)
-        self.private_format = self.PRIVATE_FORMAT
 
     # Of the blob's private sections: raised when a kernel's operand format changes.  A layer saved with another is packed again from its
-    # blob's public section, which holds the surviving weights and the pattern indices.
+    # blob's public section, which holds the surviving weights and the pattern indices: when it is loaded or, where its blob comes back in
+    # host memory, at the first call behind the blob's move to a GPU.  Until then it has no native handle, so that every call comes by here.
     PRIVATE_FORMAT = 1
 
+    def _readable(self):
+        return self.private_format == self.PRIVATE_FORMAT
+
+    def _bound(self):
+        if not self._readable():
+            self._pack_again()
+        return super()._bound()
+
     def __setstate__(self, state):
-        super().__setstate__(state)
-        if state.get("private_format") == self.PRIVATE_FORMAT or not self.blob.is_cuda:
-            return
+        self.__dict__.update(state)
+        saved = state.get("private_format", 0)
+        # (the formats so far differ only for layers whose packed size differs too)
+        same = saved == self.PRIVATE_FORMAT or self.blob.numel() == B.rtoss_pack_size(self.wdesc, self.masks)[0]
+        self.private_format = self.PRIVATE_FORMAT if same else saved
+        self._bind()
+        if not same and self.blob.is_cuda:
+            self._pack_again()
+
+    def _pack_again(self):
+        if not self.blob.is_cuda:
+            raise RuntimeError("a layer saved by another build is packed again on the GPU: move its blob there first")
         d = self.wdesc
-        with torch.cuda.device(self.blob.device):  # (and that device's current stream, whatever the caller's are)
+        # (the blob's device and that device's current stream, whatever the caller's are)
+        with _repacking, torch.cuda.device(self.blob.device):
+            if self._readable():
+                return  # (by another thread, meanwhile)
             groups, taps = d.Co * d.Ci * d.ksize ** 2 // 9, [[t for t in range(9) if int(m) >> t & 1] for m in self.masks]
             eb = torch.empty(0, dtype=TORCH_DTYPE[self.dt]).element_size()
             at = -(-groups * d.k * eb // 256) * 256
             live = self.blob[:groups * d.k * eb].view(TORCH_DTYPE[self.dt]).reshape(groups, d.k)
-            idx = self.blob[at:at + groups].clone()
+            idx = self.blob[at:at + groups].clamp(max=len(taps) - 1)  # (a layer that was never packed: anything)
             w = torch.zeros(d.Co * d.Ci * d.ksize ** 2, dtype=live.dtype, device=self.blob.device)
-            taps = torch.tensor(taps, device=self.blob.device)[idx.long().clamp(max=len(taps) - 1)]  # (a layer that was never packed: anything)
+            taps = torch.tensor(taps, device=self.blob.device)[idx.long()]
             w[:9 * groups].view(groups, 9).scatter_(1, taps, live)
-            self.packed_bytes, self.workspace_bytes = B.rtoss_pack_size(d, self.masks)
-            self.blob = torch.empty(self.packed_bytes, dtype=torch.uint8, device=self.blob.device)
+            size, workspace_size = B.rtoss_pack_size(d, self.masks)
+            blob = torch.empty(size, dtype=torch.uint8, device=self.blob.device)
+            workspace = torch.empty(max(workspace_size, 1), dtype=torch.uint8, device=self.blob.device)
+            B.rtoss_pack(d, w.data_ptr(), idx.data_ptr(), self.masks, blob.data_ptr(), size, workspace.data_ptr(), workspace_size, _stream())
+            torch.cuda.current_stream().synchronize()  # calls on other streams follow
+            self.packed_bytes, self.workspace_bytes, self.blob, self.workspace = size, workspace_size, blob, workspace
             self.private_format = self.PRIVATE_FORMAT
-            self.pack(w, idx)
+            self._bind()
 
     def pack(self, w, idx, stream=None):
         """stream: raw HIP stream handle (default: torch's current stream)."""
         assert w.is_cuda and w.is_contiguous() and idx.is_cuda
+        if not self._readable():
+            self._pack_again()  # (today's size)
         B.rtoss_pack(self.wdesc, w.data_ptr(), idx.data_ptr(), self.masks, self.blob.data_ptr(), self.packed_bytes,
                      self.workspace.data_ptr(), self.workspace_bytes, _stream() if stream is None else stream)
         return self

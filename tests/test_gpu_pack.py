@@ -119,3 +119,22 @@ def test_packed_again_on_the_blobs_device(monkeypatch):
     assert packed == [[layer.blob.device.index]]
     x = torch.randn((2, 9, 11, Ci), device="cuda").to(pl.TORCH_DTYPE[dt])
     assert torch.equal(other.conv(x), layer.conv(x))
+
+def test_layers_of_another_build_moved_to_the_gpu():
+    """... restored in host memory first: packed again at the first call, of whatever kind."""
+    dt, Co, Ci, k = wl.BF16, 144, 64, 5
+    masks = B.rtoss_pattern_dict(k)
+    w = pl.to_device(wl.round_to_dtype(np.random.default_rng(3).standard_normal((Co, Ci, 3, 3)) * 0.1, dt), dt)
+    idx = pl.select_patterns(w, dt, masks)
+    layer = pl.PackedLayer(Co, Ci, 3, k, dt, masks).pack(w, idx)
+    x = torch.randn((2, 9, 11, Ci), device="cuda").to(pl.TORCH_DTYPE[dt])
+    state = dict(layer.__getstate__())
+    del state["private_format"]
+    public = -(-Co * Ci * k * wl.ELEM_BYTES[dt] // 256) * 256 + Co * Ci
+    state["blob"] = torch.cat([layer.blob[:public].cpu(), torch.zeros(layer.packed_bytes + 512 - public, dtype=torch.uint8)])
+    for call in (lambda l: l.conv(x), lambda l: l.conv_fused(x), lambda l: pl.pack_layers([l], [w], [idx])[0].conv(x)):
+        other = pl.PackedLayer.__new__(pl.PackedLayer)
+        other.__setstate__(dict(state))
+        other.blob = other.blob.cuda()
+        assert torch.equal(call(other), layer.conv(x)) and torch.equal(other.conv(x), layer.conv(x))
+        assert other.blob.numel() == layer.packed_bytes and other.private_format == layer.private_format

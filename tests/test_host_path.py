@@ -147,6 +147,27 @@ def test_calls_follow_a_layers_attributes(make):
     assert "pattern 2 keeps 2 taps" in refusal(layer)
 
 
+def test_a_layer_of_another_build_in_host_memory_reaches_no_kernel():
+    """Its private sections would be read as today's: calls refuse it until its blob is on a GPU, where it is packed again.  (Of another
+    build: without the mark of today's sections, and of another size.)"""
+    layer = pl.PackedLayer(64, 96, 3, 5, B.BF16, B.rtoss_pattern_dict(5), device="cpu")
+    state = layer.__getstate__()
+    del state["private_format"]
+    kept = pl.PackedLayer.__new__(pl.PackedLayer)
+    kept.__setstate__(dict(state))
+    assert "taps" not in refusal(kept) and kept.blob is layer.blob  # the same size: the same sections
+    old = pl.PackedLayer.__new__(pl.PackedLayer)
+    old.__setstate__(dict(state, blob=torch.zeros(layer.packed_bytes + 512, dtype=torch.uint8)))
+    for other in (old, copy.copy(old), pickle.loads(pickle.dumps(old))):
+        other.masks = list(other.masks)
+        with FakeTensorMode():
+            x = torch.empty(1, 4, 4, 96, dtype=torch.bfloat16, device="cuda")
+        for call in (lambda: other.conv(x), lambda: other.conv_fused(x), lambda: refusal(other)):
+            with pytest.raises(RuntimeError, match="another build"):
+                call()
+    assert layer.private_format == pl.PackedLayer.PRIVATE_FORMAT and copy.copy(layer).private_format == layer.private_format
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("make", KINDS)
 def test_copies_compute_and_follow_their_attributes(make):
