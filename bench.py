@@ -60,7 +60,7 @@ def measured_traffic(summary_name):
             fields[k.strip()] = v.strip()
     try:
         h = hashlib.sha256()
-        for f in ("conv3x3_rows.hip", "rows_kernel.h", "rows_plan.h", "sparse_frag.h", "mma.h", "dtypes.h", "common.h", "epilogue.h"):
+        for f in ("conv3x3_rows.hip", "rows_kernel.h", "rows_plan.h", "rows_cut.h", "sparse_frag.h", "mma.h", "dtypes.h", "common.h", "epilogue.h"):
             h.update(open(os.path.join(here, "paper_2303_02191_amd", "csrc", f), "rb").read())
         if h.hexdigest() != fields.get("kernel_source_sha256"):
             return None

@@ -118,10 +118,12 @@ rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, in
                                    void* y, hipStream_t s);
 
 // ... large stride-1 layers: pipelined kernel over strips of output rows (conv3x3_rows.hip); same packed section
-rtoss_status launch_conv3x3_rows(const rtoss_wdesc& d, const ConvParams& c, int layout, const void* section, const void* x, void* y,
-                                 hipStream_t s);
-rtoss_status launch_conv3x3_rows_groups(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y,
-                                        hipStream_t s);  // (its part for layout 1)
+// planned: its cut where the caller has it (rows_plan.h), or nullptr
+struct RowsLaunch;
+rtoss_status launch_conv3x3_rows(const rtoss_wdesc& d, const ConvParams& c, int layout, const RowsLaunch* planned, const void* section,
+                                 const void* x, void* y, hipStream_t s);
+rtoss_status launch_conv3x3_rows_groups(const rtoss_wdesc& d, const ConvParams& c, const RowsLaunch* planned, const void* section, const void* x,
+                                        void* y, hipStream_t s);  // (its part for layout 1)
 bool rows3x3_needs_fused_stage(const ConvParams& c);
 
 // ... launches too small to fill the chip: input channels split over the waves of a workgroup (conv3x3_ksplit.hip).  Reads

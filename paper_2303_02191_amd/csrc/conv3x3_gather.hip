@@ -772,13 +772,12 @@ rtoss_status launch_gather_rows(const rtoss_wdesc& d, const ConvParams& c, const
     if (c.stride != 1 || d.Ci % 32 || d.Ci < 96) return fail(RTOSS_ESHAPE, "conv: the pipelined kernel needs stride 1 and three or more stages of 32 input channels");
     if ((int64_t)c.N * c.H * c.W * d.Ci / 8 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
     if ((int64_t)c.N * ((c.W + 15) / 16) * ((c.H + 15) / 16 + 1) * co_blocks > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
-    int slots = 0;
-    const RowPlan plan = plan_rows_for_device(c.N, c.H, c.W, co_blocks, d.Ci / 32, dev.cus, &slots);
+    const RowsLaunch launch = plan_rows_for_device(c.N, c.H, c.W, d.Co, d.Ci / 32, dev.cus);
     const char* frags = section + header_bytes(d);
     const float relu_floor = c.ep.act == 1 ? 0.f : -__builtin_inff();
-    dim3 grid((unsigned)(slots * 8)), block(64 * kGrWaves);
+    dim3 grid((unsigned)(launch.slots * 8)), block(64 * kGrWaves);
     kern<<<grid, block, kGrSmem, s>>>((const T*)x, (T*)y, (const GatherHeader*)section, frags, frags + frag_bytes(d), c.H, c.W, d.Ci,
-                                      d.Co, channel_blocks(d.Co), plan, relu_floor, c.ep.ldy, d.k <= kGrFew);
+                                      d.Co, channel_blocks(d.Co), launch.plan, relu_floor, c.ep.ldy, d.k <= kGrFew);
     return check_hip(hipGetLastError(), "conv3x3 gather rows launch");
 }
 

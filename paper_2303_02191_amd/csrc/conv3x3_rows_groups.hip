@@ -4,9 +4,10 @@
 
 namespace rtoss {
 
-rtoss_status launch_conv3x3_rows_groups(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y, hipStream_t s)
+rtoss_status launch_conv3x3_rows_groups(const rtoss_wdesc& d, const ConvParams& c, const RowsLaunch* planned, const void* section, const void* x,
+                                        void* y, hipStream_t s)
 {
-    return launch_rows_typed<1>(d, c, section, x, y, s);
+    return launch_rows_typed<1>(d, c, planned, section, x, y, s);
 }
 
 }  // namespace rtoss

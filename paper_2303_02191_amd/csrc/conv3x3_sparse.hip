@@ -622,21 +622,17 @@ inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
 }
 
 // Layout 1: where the strips without helpers would not be faster, because they waste less of small or oddly sized images and of half-empty
-// channel blocks.  us: 0.6 and 0.54 a unit of the pipelined kernel's busiest workgroup (plan_rows); 3 and, per stage and round of two workgroups a
+// channel blocks.  us: 0.6 and 0.54 a unit of the pipelined kernel's busiest workgroup; 3 and, per stage and round of two workgroups a
 // unit, 1.75, 2.3, 2.75 and 3.85 of strips of 8, 12, 16 and 20 rows (1.0 where eight rows fit once).  Measured, strips and pipelined, 4 entries:
 //     200x96->112@5x3 8.2 12.0   200x128@8x16 9.9 14.0   40x96->256@24x17 18.6 21.2   4x160->144@112x162 36.3 43.1   2x128->256@33x330 13.8 15.0
 //     100x256@13x13 25.0 21.6    100x128@17x17 17.9 15.9   4x96@100x168 16.1 14.6    2x256@100x168 33.8 28.2       3x320@80x80 31.7 28.3
-inline bool strips_are_faster(const rtoss_wdesc& d, const ConvParams& c, int plan)
+inline bool strips_are_faster(const rtoss_wdesc& d, const ConvParams& c, int plan, const RowsLaunch& rows)
 {
     const int tn = plan % 8;  // rows of a wave (strip3x3_plan, which gives layout 1 no other plans)
-    if (plan == 0 || tn < 2 || tn > 5) return false;
     const int stages = d.Ci / 32;
-    int slots = 0;
-    double units = 0;
-    plan_rows_for_device(c.N, c.H, c.W, ((d.Co + 15) / 16 + kRowsTM - 1) / kRowsTM, stages, c.dev.cus, &slots, &units);
     const int64_t groups = (int64_t)((c.W + 15) / 16) * ((c.H + 4 * tn - 1) / (4 * tn)) * ((d.Co + 63) / 64) * c.N, cus = c.dev.cus;
     const double stage = tn == 2 ? (groups <= cus ? 1.0 : 1.75) : tn == 3 ? 2.3 : tn == 4 ? 2.75 : 3.85;
-    return 3 + stages * stage * (double)((groups + 2 * cus - 1) / (2 * cus)) < 0.6 + 0.54 * units;
+    return 3 + stages * stage * (double)((groups + 2 * cus - 1) / (2 * cus)) < 0.6 + 0.54 * rows.cost;
 }
 
 // Stride 2, one or two blocks per wave: three workgroups per compute unit with one, two with two, whose rounds take about 4/3 as
@@ -740,13 +736,20 @@ rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, in
         return launch_conv3x3_ksplit(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
     if (const int plan = ring3x3_plan(d, c, layout))
         return launch_conv3x3_ring(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
-    const bool large = takes_pipelined_kernel(d, c), pipelined = large && !(layout == 1 && strips_are_faster(d, c, strip3x3_plan(d, c, layout)));
-    if (!pipelined) {
-        if (const int plan = strip3x3_plan(d, c, layout))
-            return launch_conv3x3_strip(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
+    bool pipelined = takes_pipelined_kernel(d, c);
+    RowsLaunch rows;
+    const RowsLaunch* planned = nullptr;
+    if (!pipelined || layout == 1) {
+        const int plan = strip3x3_plan(d, c, layout);
+        if (pipelined && plan) {  // (a launch within the limits of strips)
+            rows = plan_rows_for_device(c.N, c.H, c.W, d.Co, d.Ci / 32, c.dev.cus);
+            planned = &rows;
+            pipelined = !strips_are_faster(d, c, plan, rows);
+        }
+        if (plan && !pipelined) return launch_conv3x3_strip(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
     }
     if (layout != 0 && layout != 1) return fail(RTOSS_EINVAL, "conv: unknown tap layout %d", layout);
-    if (pipelined) return launch_conv3x3_rows(d, c, layout, section, x, y, s);
+    if (pipelined) return launch_conv3x3_rows(d, c, layout, planned, section, x, y, s);
     if (layout == 1) {
         if (d.dt == RTOSS_F16)
             return f32out ? launch_typed_layout1<f16_t, float>(d, c, wf, x, y, s) : launch_typed_layout1<f16_t, f16_t>(d, c, wf, x, y, s);

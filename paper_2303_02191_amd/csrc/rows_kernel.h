@@ -22,7 +22,7 @@
 //
 // Workgroups are persistent, one per compute unit.  Rows of a strip are cut into tall tiles (TN = 5:
 // 20 rows) and short ones (TN = 4: 16 rows); the host picks the cut per strip so that every workgroup's
-// share of tiles takes about the same time (see plan_rows below): a workgroup runs its tall tiles, then
+// share of tiles takes about the same time (rows_cut.h): a workgroup runs its tall tiles, then
 // its short ones.
 #pragma once
 #include <type_traits>
@@ -695,7 +695,7 @@ __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restric
 }
 
 template <typename T, typename TO, bool FUSED, int LAY>
-rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* wfrag, const void* x, void* y, hipStream_t s)
+rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const RowsLaunch* planned, const char* wfrag, const void* x, void* y, hipStream_t s)
 {
     const size_t smem = Region<LAY>::LDS;
     auto kern = conv3x3_rows_kernel<T, TO, FUSED, LAY>;
@@ -706,21 +706,20 @@ rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, const char* 
     if (c.stride != 1 || d.Ci % 32 || d.Ci < 96) return fail(RTOSS_ESHAPE, "conv: the pipelined kernel needs stride 1 and three or more stages of 32 input channels");
     if ((int64_t)c.N * c.H * c.W * d.Ci / 8 > 0x7fffffff) return fail(RTOSS_ESHAPE, "conv: input too large for 32-bit chunk offsets");
     if ((int64_t)c.N * ((c.W + 15) / 16) * ((c.H + 15) / 16 + 1) * co_blocks > 0x3fffffff) return fail(RTOSS_ESHAPE, "conv: too many tiles");
-    int slots = 0;
-    const RowPlan plan = plan_rows_for_device(c.N, c.H, c.W, co_blocks, d.Ci / 32, dev.cus, &slots);
-    dim3 grid((unsigned)(slots * 8)), block(256);
+    const RowsLaunch launch = planned ? *planned : plan_rows_for_device(c.N, c.H, c.W, d.Co, d.Ci / 32, dev.cus);
+    dim3 grid((unsigned)(launch.slots * 8)), block(256);
     kern<<<grid, block, smem, s>>>((const T*)x, (TO*)y, wfrag, wfrag + fragment_bytes(d, LAY), c.H, c.W, d.Ci, d.Co,
-                                   padded_m_tiles(d.Co), plan, c.ep);
+                                   padded_m_tiles(d.Co), launch.plan, c.ep);
     return check_hip(hipGetLastError(), "conv3x3 rows launch");
 }
 
 template <int LAY>
-rtoss_status launch_rows_typed(const rtoss_wdesc& d, const ConvParams& c, const void* section, const void* x, void* y, hipStream_t s)
+rtoss_status launch_rows_typed(const rtoss_wdesc& d, const ConvParams& c, const RowsLaunch* planned, const void* section, const void* x, void* y, hipStream_t s)
 {
     const char* wf = (const char*)section;
     const bool f32out = c.out_dt == RTOSS_F32;
     const bool fused = rows3x3_needs_fused_stage(c);
-#define RTOSS_ROWS(T, TO) (fused ? launch_rows<T, TO, true, LAY>(d, c, wf, x, y, s) : launch_rows<T, TO, false, LAY>(d, c, wf, x, y, s))
+#define RTOSS_ROWS(T, TO) (fused ? launch_rows<T, TO, true, LAY>(d, c, planned, wf, x, y, s) : launch_rows<T, TO, false, LAY>(d, c, planned, wf, x, y, s))
     if (d.dt == RTOSS_F16) return f32out ? RTOSS_ROWS(f16_t, float) : RTOSS_ROWS(f16_t, f16_t);
     return f32out ? RTOSS_ROWS(bf16_t, float) : RTOSS_ROWS(bf16_t, bf16_t);
 #undef RTOSS_ROWS

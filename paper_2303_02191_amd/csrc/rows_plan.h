@@ -3,24 +3,13 @@
 #pragma once
 
 #include "common.h"
+#include "rows_cut.h"
 
 namespace rtoss {
 
-constexpr int kTall = 5, kShort = 4;  // output rows per wave of the two tile classes
 constexpr int kRowsTM = 8;             // channel tiles per workgroup (128 channels)
 constexpr int kLW = 18;               // LDS row pitch of the activation tile in positions: 16 columns + halo
 constexpr int kPosBytes = 64;         // one position of a stage: 32 channels x 2 bytes
-
-// How the rows of the strips are cut into tiles, and how the tiles are dealt to the workgroups.
-// A strip is 16 output columns of one image.  Strips [0, sa) are cut into a5 tall tiles followed by a4
-// short ones, the other strips into b5 tall and b4 short.  A list entry is (tile, channel block) with the
-// channel block fastest; each class has its own list, cut into 8 contiguous ranges, one per XCD, so that
-// the channel blocks of a tile, and neighbouring tiles, meet in one L2.
-struct RowPlan {
-    int col_strips, co_blocks, strips;
-    int sa, a5, a4, b5, b4;
-    int tall_total, tall_per_xcd, short_total, short_per_xcd;
-};
 
 struct TileCoord {
     int n_img, mt0, oh0, ow0;
@@ -52,12 +41,13 @@ __device__ __forceinline__ TileCoord decode_entry(const RowPlan& p, bool tall, i
 }
 
 
-// The cut of a launch shape into tall and short tiles with the smallest busiest-workgroup cost, for `slots`
-// workgroups per XCD and `stages` stages of 32 input channels per tile; results are remembered per shape.
-// cost (where asked for): the busiest workgroup's.
-RowPlan plan_rows(int N, int H, int W, int co_blocks, int stages, int slots, double* cost = nullptr);
-// One workgroup per compute unit, fewer when the tile lists are shorter: sets *slots (workgroups per XCD; the grid
-// is 8 * slots) and returns the plan for it.
-RowPlan plan_rows_for_device(int N, int H, int W, int co_blocks, int stages, int cus, int* slots, double* cost = nullptr);
+// A launch shape's cut into tall and short tiles with the smallest busiest-workgroup cost (cut_rows), for workgroups of 128 channels and
+// `stages` stages of 32 input channels per tile: one workgroup per compute unit, fewer when the tile lists are shorter.
+struct RowsLaunch {
+    RowPlan plan;
+    int slots;    // workgroups per XCD; the grid is 8 * slots
+    double cost;  // the busiest workgroup's
+};
+RowsLaunch plan_rows_for_device(int N, int H, int W, int Co, int stages, int cus);
 
 }  // namespace rtoss

@@ -250,7 +250,7 @@ def test_coherent_path_argument_errors():
     assert e.value.status == B.EINVAL
 
 
-@pytest.mark.parametrize("check", ["stem_rows_check", "share_check", "row_pieces_check", "work_order_check"])
+@pytest.mark.parametrize("check", ["stem_rows_check", "share_check", "row_pieces_check", "work_order_check", "rows_cut_check"])
 def test_index_arithmetic(tmp_path, check):
     """tests/<check>.cpp walks a header of the kernels on the CPU."""
     exe = str(tmp_path / check)
