@@ -308,11 +308,14 @@ rtoss_status launch_rows(const rtoss_wdesc& d, const ConvParams& c, int plan, co
 }  // namespace
 
 // The smallest TN whose workgroups the compute units hold at once, one each, where its stages are faster than those of the kernels without helpers by
-// more than its longer start and end.  us a stage, layout 0 (layout 1: 1.25 times): here 0.58, 0.79, 1.0, 1.21 with TN = 2 .. 5; there 0.82 with
-// eight rows once over the chip, 1.09 with twelve once, 1.4 and 1.87 twice, 3.1 in taller strips; the start costs 0.35 us more per TN here.
+// more than its longer start and end.  us a stage, layout 0 (layout 1: 1.2 times): here 0.58, 0.79, 1.0, 1.21 with TN = 2 .. 5; there 0.82 with
+// eight rows once over the chip, 1.09 with twelve once, 1.29 and 1.87 twice, 3.1 in taller strips; the start costs 0.35 us more per TN here.
 // (bf16, without helpers and with: 1x256@50x84 9.8 8.5, 16x256@20x20 11.9 10.6, 1x256@100x168 18.2 15.7, 1x512@50x84 20.6 18.3, 16x512@20x20
 // 33.3 25.8, 1x128@100x168 7.8 7.4; layout 1: 11.5 9.8, 15.6 12.6, 21.4 18.5, 27.6 21.8, 39.1 31.5, 9.5 8.4.  Not 4x128@80x80, 8.6 8.7, nor
-// 16x128@40x40, 8.8 9.9: eight rows twice over the chip.)
+// 16x128@40x40, 8.8 9.9: eight rows twice over the chip.  Where eight rows go twice over the chip and 16 once, means of 22 to 30 launches of 64 to
+// 384 output channels, on tensors in caches and in none: 3 stages 1.03 times as long with helpers (layout 1), 4 1.03 (layout 1: 1.01), 5 0.99 (0.98),
+// 6 0.99 (0.97), 8 0.94 (0.93).)
+// The pipelined kernel is not asked about: its least unit of work, a tile of 16 rows and 128 channels, takes 2.5 us a stage.
 int ring3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
 {
     if (c.stride != 1 || d.Ci % 32 || d.Co % 16 || d.Ci < 64) return 0;
@@ -326,11 +329,11 @@ int ring3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
     if (tn > 5) return 0;
     const double there = groups(2) <= cus                             ? 0.82
                          : layout == 0 && groups(3) <= cus            ? 1.09
-                         : groups(2) <= 2 * cus                       ? 1.4
+                         : groups(2) <= 2 * cus                       ? 1.29
                          : groups(3) <= 2 * cus                       ? 1.87
                                                                       : 3.1;
     const double gain = there - (0.16 + 0.21 * tn);
-    return d.Ci / 32 * (layout == 0 ? 1 : 1.25) * gain > 0.35 * tn ? tn : 0;
+    return d.Ci / 32 * (layout == 0 ? 1 : 1.2) * gain > 0.35 * tn ? tn : 0;
 }
 
 rtoss_status launch_conv3x3_ring(const rtoss_wdesc& d, const ConvParams& c, int layout, int plan, const void* section, const void* zeros,

@@ -96,6 +96,16 @@ def test_ring_cases_reach_the_height_they_name():
     assert [split(k)[0] for k in routes.kernels(calls)] == want
 
 
+def test_shallow_launches_of_two_rounds_stay_without_helpers():
+    """Eight rows a workgroup go over the chip twice, 16 once: with helpers from five stages on, where they are as fast (four of 16: 3 % slower)."""
+    for k, least in ((2, 5), (3, 5), (4, 5), (5, 5)):
+        for stages in (3, 4, 5, 8):
+            calls = [call(wl.BF16, N, 32 * stages, Co, H, W, 3, 1, k, wl.BF16, fused) for fused in (False, True)
+                     for N, Co, H, W in ((1, 192, 100, 168), (4, 336, 40, 40), (2, 208, 80, 80), (17, 64, 43, 50))]
+            want = "conv3x3_strip<4,%d>" % (k >= 4) if stages >= least else "conv3x3_strip<2,%d,true>" % (k >= 4)
+            assert {split(r)[0] for r in routes.kernels(calls)} == {want}, (k, stages)
+
+
 def test_streaming_cases_cover_the_turns():
     """The buffers of a workgroup in test_gpu_stream1x1's cases, with one helper wave and with two: one, two, three and more, with at
     least two and at most four workgroups a compute unit (16 positions a wave along positions; at least two buffers a workgroup)."""
