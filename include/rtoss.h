@@ -202,7 +202,7 @@ rtoss_status rtoss_pack_size(const rtoss_wdesc* desc, const uint16_t* masks_host
  * Further sections (each starting at a multiple of 256 bytes) are private to the
  * convolution kernels: tiles of the pruned weights arranged as matrix-core operand
  * fragments, dense with explicit zeros or 2-of-4 compressed when every pattern of the
- * dictionary allows it.  They are read by the build of the library that packed them: a blob
+ * dictionary allows it, or both, of which a call reads one.  They are read by the build of the library that packed them: a blob
  * saved by another is packed again from section 0.
  * Errors: RTOSS_EINVAL (NULL, bad dictionary, popcount != desc->k, misaligned blob),
  * RTOSS_ESHAPE (ksize not 1 or 3, non-positive extents), RTOSS_ENOSPACE.

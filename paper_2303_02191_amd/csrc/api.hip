@@ -191,6 +191,10 @@ rtoss_status blob_geometry(const rtoss_wdesc* d, const Dict& dict, BlobGeometry*
         g->mat_off = end;
         g->mat_bytes = sparse3x3_section_bytes(*d, dict.layout);
         end = align_up(end + g->mat_bytes, 256);
+        if (dict.repeats) {
+            g->dense_off = end;
+            end = align_up(end + dense3x3_section_bytes(*d), 256);
+        }
     } else if (stem3x3_shape_ok(*d)) {
         g->format = kFormatStem;
         g->mat_off = end;
@@ -447,6 +451,10 @@ static rtoss_status conv_impl(const rtoss_wdesc* desc, const rtoss_cdesc* c, con
     if (coherent && c->layout != RTOSS_NHWC) return fail(RTOSS_ELAYOUT, "the coherent path takes channels-last tensors");
     if (rtoss_status st = current_device(&cp.dev)) return st;
     if (coherent) return launch_conv3x3_gather(*desc, cp, blob + g.mat_off, x_dev, y_dev, (hipStream_t)hip_stream);
+    if (g.dense_off && !sparse3x3_is_faster(*desc, dict, cp)) {
+        g.format = kFormatDense3x3;
+        g.mat_off = g.dense_off;
+    }
     // The element-wise kernel reads section 0 and takes any strides (NCHW) and any size.
     const bool fits = g.format == kFormatSparse24      ? sparse3x3_launch_ok(*desc, dict, cp)
                       : g.format == kFormatDense3x3    ? dense3x3_launch_ok(*desc, cp)

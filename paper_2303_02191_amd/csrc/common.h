@@ -59,6 +59,7 @@ struct BlobGeometry {
     MatrixFormat format;
     size_t mat_off;     // matrix-core section (0 if none)
     size_t mat_bytes;
+    size_t dense_off;   // kFormatSparse24: the same weights in the dense mode's format as well (0: not)
     size_t total;
 };
 
@@ -113,6 +114,7 @@ rtoss_status launch_pack(const PackItem* items, const BlobGeometry* geo, int n, 
 // 3x3 convolution on the sparse matrix instruction (conv3x3_sparse.hip)
 bool sparse3x3_launch_ok(const rtoss_wdesc& d, const Dict& dict, const ConvParams& c);
 bool sparse3x3_shape_ok(const rtoss_wdesc& d, const Dict& dict);
+bool sparse3x3_is_faster(const rtoss_wdesc& d, const Dict& dict, const ConvParams& c);  // (of a layer with both sections)
 size_t sparse3x3_section_bytes(const rtoss_wdesc& d, int layout);
 rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, int layout, const void* section, const void* x,
                                    void* y, hipStream_t s);
@@ -139,6 +141,7 @@ rtoss_status launch_conv3x3_ksplit_gather(const rtoss_wdesc& d, const ConvParams
 // ... stride 1, launches of medium size: strips of output rows (conv3x3_strip.hip); same sections and layouts.
 // strip3x3_plan: variant to launch, 0 = another kernel serves the launch better.
 int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout);
+int strip3x3_rows(int plan);  // output rows of a workgroup
 rtoss_status launch_conv3x3_strip(const rtoss_wdesc& d, const ConvParams& c, int layout, int plan, const void* section, const void* zeros,
                                   const void* x, void* y, hipStream_t s);
 

@@ -626,14 +626,14 @@ inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
 // unit, 1.75, 2.3, 2.75 and 3.85 of strips of 8, 12, 16 and 20 rows (1.0 where eight rows fit once).  Measured, strips and pipelined, 4 entries:
 //     200x96->112@5x3 8.2 12.0   200x128@8x16 9.9 14.0   40x96->256@24x17 18.6 21.2   4x160->144@112x162 36.3 43.1   2x128->256@33x330 13.8 15.0
 //     100x256@13x13 25.0 21.6    100x128@17x17 17.9 15.9   4x96@100x168 16.1 14.6    2x256@100x168 33.8 28.2       3x320@80x80 31.7 28.3
-inline bool strips_are_faster(const rtoss_wdesc& d, const ConvParams& c, int plan, const RowsLaunch& rows)
+inline double strips_us(const rtoss_wdesc& d, const ConvParams& c, int plan)
 {
-    const int tn = plan % 8;  // rows of a wave (strip3x3_plan, which gives layout 1 no other plans)
-    const int stages = d.Ci / 32;
-    const int64_t groups = (int64_t)((c.W + 15) / 16) * ((c.H + 4 * tn - 1) / (4 * tn)) * ((d.Co + 63) / 64) * c.N, cus = c.dev.cus;
-    const double stage = tn == 2 ? (groups <= cus ? 1.0 : 1.75) : tn == 3 ? 2.3 : tn == 4 ? 2.75 : 3.85;
-    return 3 + stages * stage * (double)((groups + 2 * cus - 1) / (2 * cus)) < 0.6 + 0.54 * rows.cost;
+    const int rows = strip3x3_rows(plan);
+    const int64_t groups = (int64_t)((c.W + 15) / 16) * ((c.H + rows - 1) / rows) * ((d.Co + 63) / 64) * c.N, cus = c.dev.cus;
+    const double stage = rows == 8 ? (groups <= cus ? 1.0 : 1.75) : rows == 12 ? 2.3 : rows == 16 ? 2.75 : 3.85;
+    return 3 + d.Ci / 32 * stage * (double)((groups + 2 * cus - 1) / (2 * cus));
 }
+inline double pipelined_us(const RowsLaunch& rows) { return 0.6 + 0.54 * rows.cost; }
 
 // Stride 2, one or two blocks per wave: three workgroups per compute unit with one, two with two, whose rounds take about 4/3 as
 // long (two halve the weights a block reads from LDS).  Two where that is the smaller sum; not for one or two stages, which
@@ -701,16 +701,59 @@ rtoss_status launch_typed(const rtoss_wdesc& d, const ConvParams& c, const char*
 
 // ---- host-visible entry points of this file ----
 
-// Dictionaries that need the repeated taps of layout 1 (5 entries): from 64 channels in and 96 out (or the other way round) on.  Below, and
-// for ragged counts, the dense mode's shorter chain is as fast or faster (us, dense mode and 2-of-4, bf16: 1x32@28x36 3.1 3.6, 4x32@20x30
-// 3.2 4.0, 1x24->80@50 3.6 5.9, 2x40->36@60 4.2 7.9, 4x64@20x30 3.8 4.0, 16x64@80 10.1 10.2; from there on 4x96@20x30 4.5 4.7, 1x96@56x70 5.3 4.9,
-// 4x96@100x168 16.3 14.6, 1x256@56x70 10.5 9.7, 16x128@40 11.0 9.8, 2x256@100x168 33.5 28.4, and at stride 2 4x64->128@112x150 16.7 6.8,
-// 1x128->256@56x70 7.3 7.7, 4x128->256@112x150 39.2 17.8, 4x256->512@40 23.4 13.3).
+// Dictionaries that need the repeated taps of layout 1 (5 entries): whole stages and channel tiles, at least 64 channels in and out and more in one
+// of them.  Below, and for ragged counts, the dense mode's shorter chain is as fast or faster at every size (us, dense mode and 2-of-4,
+// bf16: 1x32@28x36 3.1 3.6, 4x32@20x30 3.2 4.0, 1x24->80@50 3.6 5.9, 2x40->36@60 4.2 7.9, 4x64@20x30 3.8 4.0, 16x64@80 10.1 10.2), and
+// only its section is packed; from there on it depends on the launch (sparse3x3_is_faster).
 bool sparse3x3_shape_ok(const rtoss_wdesc& d, const Dict& dict)
 {
     // (rows of 16-byte multiples: the activation copies move 8 channels per lane)
     if (d.ksize != 3 || (d.dt != RTOSS_F16 && d.dt != RTOSS_BF16) || d.Ci % 8 || dict.layout < 0) return false;
     return !dict.repeats || (!ragged(d) && d.Ci >= 64 && d.Co >= 64 && d.Ci + (int64_t)d.Co > 128);
+}
+
+constexpr int kDenseTaps = 2;  // the dense mode, as a layout of the other files' plans
+
+// Of a dictionary that needs the repeated taps both sections are packed, for at odd sizes the dense mode has the better tiles: smaller ones in
+// small launches, strips of fewer rows on low images.  Which, by the plans of both (1480 launches of 64 to 512 channels on 4 to 220 rows and
+// columns, bf16 and fp16: the slower one by more than 3 % in 60 of them; always the 2-of-4 steps, up to 1.78 times as long; always dense mode, 21 %
+// on average).  Packing both takes a call of 256 -> 256 channels 5.7 -> 6.7 us, four of them 6.7 -> 8.6.  us, dense mode and 2-of-4:
+//     Channels split over the waves: 32 channels a workgroup against 16 of the dense mode's split (256@1x20x46 4.86 5.11), or against its small
+//     tiles while two of them a unit hold the launch, where the split's four waves are unevenly deep (96@2x30x35 3.92 4.41, 64->80@1x56x56 3.65
+//     4.32, 160@2x24x28 4.85 5.20; 160@2x30x37, 576 tiles 6.24 5.41; four stages 128@1x40x53 4.59 4.62; seven 224@1x22x49 5.92 5.62).
+//     Stride 2: the small tiles while two a unit hold the launch (64->256@2x11x149 4.79 5.10, 192->384@2x32x61 7.87 9.91, 320->128@5x13x104
+//     10.6 14.5; 576 tiles 128->256@2x47x65 8.5 7.6, 192->384@3x28x34 11.3 9.8).
+//     Strips, eight rows once over the chip: the small tiles while three a unit hold the launch (128@3x32x48 5.53 6.47, 160@2x31x53 6.75 7.25;
+//     128@1x65x96, 816 tiles 7.56 6.58), from nine stages on not.
+//     Strips of more rows: the dense mode's, of 8, 12, 16 or 20 rows (weights past LDS), take 3.4 us and 0.07 a row, and per round of one a
+//     unit 0.02 a row and, a stage, 0.28 and 0.064 a row; the others strips_us or 0.84 of pipelined_us, which fills its tiles better than
+//     those are cut (192->160@200x7x6 16.5 29.4, 256->96@49x5x118 27.4 44.9, 96->256@40x24x17 15.9 18.4; 256@2x100x168 33.5 28.4).
+// By the shape alone: results of either type, with an output stage or into a slice, add in one order.
+bool sparse3x3_is_faster(const rtoss_wdesc& d, const Dict& dict, const ConvParams& call)
+{
+    if (!sparse3x3_launch_ok(d, dict, call)) return false;
+    ConvParams c = call;
+    c.out_dt = d.dt;
+    c.ep = Epilogue{nullptr, nullptr, nullptr, 0, d.Co, d.Co};
+    const int64_t cus = c.dev.cus;
+    const int stages = d.Ci / 32, Ho = (c.H - 1) / c.stride + 1, Wo = (c.W - 1) / c.stride + 1;
+    const auto groups = [&](int rows, int cols, int channels) {
+        return (int64_t)((Ho + rows - 1) / rows) * ((Wo + cols - 1) / cols) * ((d.Co + channels - 1) / channels) * c.N;
+    };
+    const int64_t small = 4 * groups(4, 16, 64);   // the dense mode's small tiles, of 16 channels in blocks of 64, ...
+    const bool tall = groups(16, 16, 64) >= 256;   // ... which larger launches do not take (conv3x3_dense.hip)
+    const int split = ksplit3x3_plan(d, c, 1), dense_split = ksplit3x3_plan(d, c, kDenseTaps);
+    if (c.stride == 2) return split || dense_split || tall || small > 2 * cus;
+    if (split) return groups(4, 8, 16) <= cus || !(dense_split || (stages <= 5 && stages != 4 && small <= 2 * cus));
+    const int dense = strip3x3_plan(d, c, kDenseTaps), plan = strip3x3_plan(d, c, 1);
+    if (!dense) return tall || stages > 8 || small > 3 * cus;
+    if (stages == 2 || !plan || ring3x3_plan(d, c, 1)) return true;
+    const int rows = strip3x3_rows(dense);
+    const double rounds = (double)((groups(rows, 16, 64) + cus - 1) / cus);
+    const double dense_us = 3.4 + 0.07 * rows + rounds * ((0.28 + 0.064 * rows) * stages + 0.02 * rows);
+    double us = strips_us(d, c, plan);
+    if (takes_pipelined_kernel(d, c)) us = std::min(us, 0.84 * pipelined_us(plan_rows_for_device(c.N, c.H, c.W, d.Co, stages, c.dev.cus)));
+    return us <= dense_us;
 }
 
 bool sparse3x3_launch_ok(const rtoss_wdesc& d, const Dict& dict, const ConvParams& c)
@@ -744,7 +787,7 @@ rtoss_status launch_conv3x3_sparse(const rtoss_wdesc& d, const ConvParams& c, in
         if (pipelined && plan) {  // (a launch within the limits of strips)
             rows = plan_rows_for_device(c.N, c.H, c.W, d.Co, d.Ci / 32, c.dev.cus);
             planned = &rows;
-            pipelined = !strips_are_faster(d, c, plan, rows);
+            pipelined = strips_us(d, c, plan) >= pipelined_us(rows);
         }
         if (plan && !pipelined) return launch_conv3x3_strip(d, c, layout, plan, section, wf + fragment_bytes(d, layout), x, y, s);
     }

@@ -535,12 +535,14 @@ rtoss_status launch_layout(const rtoss_wdesc& d, const ConvParams& c, int plan, 
 // 40.3.  Dense mode: below.)
 static int plan_within_limits(const rtoss_wdesc& d, const ConvParams& c, int layout);
 
+int strip3x3_rows(int plan) { return plan > kDenseRows ? plan - kDenseRows : 4 * (plan % kTwoBuffers); }
+
 int strip3x3_plan(const rtoss_wdesc& d, const ConvParams& c, int layout)
 {
     if (c.stride != 1 || d.Ci * elem_bytes(d.dt) % 64 || d.Co % 16) return 0;
     // (the dense-mode kernel has neither limit)
     const int plan = plan_within_limits(d, c, layout);
-    const int rows = plan > kDenseRows ? plan - kDenseRows : 4 * (plan % kTwoBuffers);
+    const int rows = strip3x3_rows(plan);
     if (plan == 0 || (int64_t)c.N * c.H * c.W * d.Ci * elem_bytes(d.dt) / 16 > kMaxChunks) return 0;
     // (fp32, and 16-bit results of two buffers, know rows only)
     const bool two_buffers = plan < kDenseRows && plan > kTwoBuffers;

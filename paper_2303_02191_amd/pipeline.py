@@ -145,7 +145,7 @@ class PackedLayer(_Layer):
     # Of the blob's private sections: raised when a kernel's operand format changes.  A layer saved with another is packed again from its
     # blob's public section, which holds the surviving weights and the pattern indices: when it is loaded or, where its blob comes back in
     # host memory, at the first call behind the blob's move to a GPU.  Until then it has no native handle, so that every call comes by here.
-    PRIVATE_FORMAT = 1
+    PRIVATE_FORMAT = 2
 
     def _readable(self):
         return self.private_format == self.PRIVATE_FORMAT

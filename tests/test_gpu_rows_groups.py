@@ -15,7 +15,7 @@ CASES = [
     (wl.BF16, 2, 96, 256, 99, 161, 5),
     (wl.F16, 1, 128, 208, 161, 159, 4),
     (wl.BF16, 70, 288, 112, 19, 31, 5),
-    (wl.F16, 33, 160, 240, 33, 31, 5),
+    (wl.F16, 33, 160, 240, 37, 31, 5),
     (wl.BF16, 140, 96, 112, 20, 15, 5),
     (wl.F16, 2, 192, 448, 97, 95, 4),
 ]

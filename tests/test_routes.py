@@ -6,6 +6,7 @@ from paper_2303_02191_amd import binding as B
 from paper_2303_02191_amd import workloads as wl
 
 import routes
+import test_gpu_both_sections
 import test_gpu_fused
 import test_gpu_ksplit
 import test_gpu_ksplit1x1
@@ -98,7 +99,7 @@ def test_ring_cases_reach_the_height_they_name():
 
 def test_shallow_launches_of_two_rounds_stay_without_helpers():
     """Eight rows a workgroup go over the chip twice, 16 once: with helpers from five stages on, where they are as fast (four of 16: 3 % slower)."""
-    for k, least in ((2, 5), (3, 5), (4, 5), (5, 5)):
+    for k, least in ((2, 5), (3, 5), (4, 5)):
         for stages in (3, 4, 5, 8):
             calls = [call(wl.BF16, N, 32 * stages, Co, H, W, 3, 1, k, wl.BF16, fused) for fused in (False, True)
                      for N, Co, H, W in ((1, 192, 100, 168), (4, 336, 40, 40), (2, 208, 80, 80), (17, 64, 43, 50))]
@@ -159,6 +160,27 @@ def test_cases_of_three_groups_reach_the_pipelined_kernel():
     calls = [call(wl.BF16, N, Ci, Co, H, W, 3, 1, 4, wl.BF16, False) for N, Ci, Co, H, W in
              ((200, 96, 112, 5, 3), (200, 128, 128, 8, 16), (40, 96, 256, 24, 17), (4, 160, 144, 112, 162), (2, 128, 256, 33, 330))]
     assert families(routes.kernels(calls)) == ["conv3x3_strip"] * len(calls)
+
+
+def test_layers_with_both_sections_take_the_faster_one():
+    """Dictionaries that need repeated taps: by the shape alone, so that results of either type, with an output stage or into a slice, add in
+    one order.  Dense mode: conv3x3_dense, layout 2 of the K split and of the strips, strips named by their rows."""
+    def mode(kernel):
+        name, args = split(kernel)[0][:-1].split("<")
+        args = [a for a in args.split(",") if a not in ("true", "false")]
+        if name in ("conv3x3_sparse_sb", "conv3x3_rows", "conv3x3_ksplit"):
+            return "dense" if args[-1] == "2" else "2-of-4"
+        return "dense" if name == "conv3x3_dense" or len(args) == 1 or args[1] == "2" else "2-of-4"
+
+    for want, stride, shapes in test_gpu_both_sections.ROUTES:
+        for N, Ci, Co, H, W in shapes:
+            calls = [call(dt, N, Ci, Co, H, W, 3, stride, 5, out_dt, fused) for dt in (wl.F16, wl.BF16) for out_dt in (dt, wl.F32)
+                     for fused in (0, 1, -(1 << 25))]
+            assert {mode(k) for k in routes.kernels(calls)} == {want}, (N, Ci, Co, H, W, stride)
+    # past the 2-of-4 kernels' limits (chunks of input; workgroups): the dense kernel
+    calls = [call(wl.BF16, N, 64, 128, H, W, 3, stride, 5, wl.BF16, False)
+             for N, H, W, stride in ((1, 16385, 16400, 1), (65535, 66, 64, 2), (65535, 1, 2064, 1))]
+    assert families(routes.kernels(calls)) == ["conv3x3_dense"] * len(calls)
 
 
 def test_wide_tile_reaches_the_pipelined_kernel():

@@ -21,7 +21,10 @@ def expected(masks):
     corners, edges = 0b101000101, 0b010101010
     if all(bin(m & corners).count("1") <= 2 and bin(m & edges).count("1") <= 2 for m in masks):
         return 5 * 1024 + 2 * 256
-    return 6 * 1024 + 3 * 256 if all(places(m, GROUPS) for m in masks) else 9 * 1024
+    if all(places(m, [g[:3] for g in GROUPS]) for m in masks):
+        return 6 * 1024 + 3 * 256
+    # (where a tap is needed in its second group: the dense fragments as well)
+    return 6 * 1024 + 3 * 256 + 9 * 1024 if all(places(m, GROUPS) for m in masks) else 9 * 1024
 
 
 def tile_bytes(masks):
@@ -47,4 +50,4 @@ def test_dictionaries(rule):
             continue
         assert expected(masks) <= tile_bytes(masks) < expected(masks) + 64, k
     masks = [int(m) for m in B.rtoss_pattern_dict(5, B.RULE_CONNECTED4)]
-    assert expected(masks) == 6 * 1024 + 3 * 256
+    assert expected(masks) == 6 * 1024 + 3 * 256 + 9 * 1024
