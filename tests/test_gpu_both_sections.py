@@ -18,7 +18,7 @@ ROUTES = [
     ("2-of-4", 1, [(1, 96, 144, 17, 33), (2, 64, 80, 9, 19), (1, 512, 80, 41, 43), (9, 96, 240, 7, 33), (1, 256, 256, 49, 83), (2, 96, 208, 99, 161),
                    (16, 128, 256, 39, 41), (5, 64, 96, 81, 79)]),
     ("dense", 2, [(1, 96, 144, 61, 129), (1, 224, 448, 33, 57)]),
-    ("2-of-4", 2, [(1, 96, 144, 11, 13), (2, 64, 144, 21, 67), (4, 64, 128, 101, 135), (3, 192, 400, 71, 91)]),
+    ("2-of-4", 2, [(1, 96, 144, 11, 13), (2, 64, 144, 21, 67), (4, 64, 128, 101, 135), (3, 192, 400, 71, 91), (65, 96, 80, 41, 29)]),
 ]
 LAYERS = sorted({(Ci, Co) for _, _, shapes in ROUTES for _, Ci, Co, _, _ in shapes})
 

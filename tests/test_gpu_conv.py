@@ -104,16 +104,18 @@ def test_conv3x3_matrix_core_shapes(dt, case):
 
 
 DENSE_MODE = [
-    # dictionaries with three corners or three edge midpoints in one pattern: three tap groups where they fit
-    # (the 4-entry edge-connected patterns), else dense mode (every tap a dense step, pruned weights explicit zeros)
+    # dictionaries with three corners or three edge midpoints in one pattern: three tap groups where they fit (the edge-connected patterns of
+    # 4 entries, and of 5 in layers wide enough), else dense mode (every tap a dense step, pruned weights explicit zeros)
     # N, Ci, Co,  H,  W, stride, k, rule, relu
     (1, 32, 16, 4, 4, 1, 4, B.RULE_CONNECTED4, False),
     (2, 96, 48, 19, 21, 1, 4, B.RULE_CONNECTED4, True),
     (1, 64, 144, 33, 18, 1, 5, B.RULE_CONNECTED4, False),
+    (1, 64, 144, 33, 18, 1, 6, B.RULE_CONNECTED4, False),
     (3, 64, 128, 16, 35, 1, 3, B.RULE_ALL, False),
     (1, 256, 256, 20, 24, 1, 4, B.RULE_CONNECTED8, True),
     (1, 32, 16, 7, 9, 2, 4, B.RULE_CONNECTED4, False),
     (2, 64, 80, 37, 41, 2, 5, B.RULE_CONNECTED4, True),
+    (2, 64, 80, 37, 41, 2, 6, B.RULE_CONNECTED4, True),
     (1, 128, 256, 40, 40, 2, 4, B.RULE_CONNECTED4, False),
     (1, 32, 32, 1, 1, 1, 8, B.RULE_CONNECTED4, False),
 ]

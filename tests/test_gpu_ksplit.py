@@ -31,9 +31,12 @@ CASES = [
     (wl.F16, 1, 64, 64, 57, 70, 1, 4),
     (wl.F16, 1, 96, 160, 21, 23, 2, 4),
     (wl.BF16, 1, 128, 256, 56, 58, 2, 4),
-    (wl.F16, 1, 256, 128, 20, 21, 1, 5),    # one dense step per tap
+    (wl.F16, 1, 256, 128, 20, 21, 1, 5),    # ... with taps in their second group
     (wl.BF16, 1, 64, 96, 27, 30, 2, 5),
     (wl.F16, 2, 128, 160, 33, 35, 2, 5),
+    (wl.F16, 1, 256, 128, 20, 21, 1, 6),    # one dense step per tap
+    (wl.BF16, 1, 64, 96, 27, 30, 2, 6),
+    (wl.F16, 2, 128, 160, 33, 35, 2, 6),
     (wl.F32, 1, 64, 64, 23, 26, 1, 3),      # fp32
     (wl.F32, 1, 80, 48, 11, 9, 1, 4),
     (wl.F32, 1, 64, 64, 31, 33, 2, 3),

@@ -29,7 +29,8 @@ CASES = [
     ("conv3x3_strip", wl.BF16, 49, 64, 208, 9, 19, 3, 1, 4),  # ... the last one of 16 channels
     ("conv3x3_strip", wl.F16, 33, 64, 48, 17, 19, 3, 1, 4),  # ... one block
     ("conv3x3_strip", wl.BF16, 33, 32, 48, 9, 19, 3, 1, 3),  # a single stage
-    ("conv3x3_strip", wl.F16, 33, 96, 128, 16, 18, 3, 1, 5),  # dense mode
+    ("conv3x3_strip", wl.F16, 33, 96, 128, 16, 18, 3, 1, 5),
+    ("conv3x3_strip", wl.F16, 33, 96, 128, 16, 18, 3, 1, 6),  # dense mode
     ("conv3x3_strip", wl.BF16, 97, 96, 48, 17, 18, 3, 1, 5),
     ("conv3x3_strip", wl.F16, 17, 64, 160, 9, 19, 3, 1, 3),  # two buffers
     ("conv3x3_rows", wl.BF16, 2, 128, 224, 100, 167, 3, 1, 3),

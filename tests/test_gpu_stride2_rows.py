@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 # dt, k, N, Ci, Co, H, W: the single-buffered kernel's, and the resident one's (images of one block, several channel blocks, a last turn of few blocks)
 CASES = [(wl.F16, 3, 17, 32, 16, 18, 17), (wl.BF16, 2, 520, 64, 112, 1, 1), (wl.F16, 2, 40, 32, 48, 5, 31), (wl.BF16, 4, 9, 32, 80, 33, 35),
-         (wl.F16, 3, 40, 128, 272, 42, 41)]
+         (wl.F16, 3, 40, 128, 272, 42, 41), (wl.F16, 5, 12, 64, 80, 45, 43), (wl.BF16, 5, 65, 96, 80, 41, 29)]
 RESIDENT_CASES = [(wl.F16, 3, 17, 32, 16, 107, 109), (wl.BF16, 2, 10, 64, 144, 79, 85), (wl.F16, 2, 100, 32, 80, 5, 140),
                   (wl.BF16, 3, 3201, 64, 64, 1, 1), (wl.F16, 3, 9, 64, 320, 66, 67)]
 

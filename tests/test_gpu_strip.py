@@ -25,11 +25,15 @@ CASES = [
     (wl.F16, 4, 64, 256, 49, 65, 4),     # ... three,
     (wl.F16, 4, 64, 128, 99, 129, 4),    # ... four,
     (wl.BF16, 2, 64, 256, 99, 161, 4),   # ... five rows per wave
-    (wl.F16, 4, 64, 64, 79, 80, 5),      # dense mode: two rows and buffers,
-    (wl.BF16, 3, 64, 112, 81, 97, 5),    # ... two rows,
+    (wl.F16, 4, 64, 64, 79, 80, 5),      # dense mode: weights past LDS, eight rows
+    (wl.BF16, 3, 64, 112, 81, 97, 5),    # three groups, taps in the second of theirs: two rows per wave,
     (wl.F16, 4, 64, 256, 49, 65, 5),     # ... three,
     (wl.BF16, 4, 64, 128, 99, 129, 5),   # ... four,
     (wl.F16, 2, 64, 256, 100, 167, 5),   # ... five
+    (wl.BF16, 3, 64, 112, 81, 97, 6),    # dense mode, weights through LDS: two,
+    (wl.F16, 4, 64, 256, 49, 65, 6),     # ... three,
+    (wl.BF16, 4, 64, 128, 99, 129, 6),   # ... four,
+    (wl.F16, 2, 64, 256, 100, 167, 6),   # ... five
     (wl.F32, 4, 32, 256, 59, 65, 3),     # fp32: five rows per wave
     (wl.F32, 2, 48, 208, 99, 97, 4),
 ]

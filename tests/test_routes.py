@@ -7,6 +7,7 @@ from paper_2303_02191_amd import workloads as wl
 
 import routes
 import test_gpu_both_sections
+import test_gpu_conv
 import test_gpu_fused
 import test_gpu_ksplit
 import test_gpu_ksplit1x1
@@ -86,6 +87,29 @@ def test_cases_made_for_a_kernel_reach_it(fused):
     assert families(routes.kernels(calls)) == ["conv3x3_resident"] * len(calls)
     calls = [call(dt, 1, Ci, Co, 1, P, 1, 1, 2, out_dt, fused) for dt, Ci, Co, P in test_gpu_stream1x1.CASES for out_dt in (dt, wl.F32)]
     assert families(routes.kernels(calls)) == ["conv1x1_stream"] * len(calls)
+
+
+def test_cases_reach_the_layout_they_name():
+    """Rows and tap layout of the strips (2: dense mode, its weights in LDS; a number alone: past it, that many rows), steps of the channel split,
+    blocks a wave and layout at stride 2."""
+    def variants(calls):
+        return [split(k)[0].split("<")[1][:-1].split(",") for k in routes.kernels(calls)]
+
+    strips = ["2,0", "2,0", "3,0", "3,0", "4,0", "2,1", "3,1", "4,1", "5,1", "8", "2,1", "3,1", "4,1", "5,1", "2,2", "3,2", "4,2", "5,2", "8", "8"]
+    for fused in (False, True):
+        got = variants([call(c[0], *c[1:6], 3, 1, c[-1], wl.F32, fused) for c in test_gpu_strip.CASES])
+        assert [",".join(v[:2]) for v in got] == strips
+        got = variants([call(c[0], *c[1:6], 3, c[6], c[-1], wl.F32, fused) for c in test_gpu_ksplit.CASES])
+        assert [v[-1] for v in got] == ["0"] * 10 + ["1"] * 8 + ["2"] * 7
+        got = variants([call(c[0], *c[2:], 3, 2, c[1], c[0], fused) for c in test_gpu_stride2_rows.CASES])
+        assert [(v[2], v[6]) for v in got] == [("1", "0")] * 3 + [("1", "1"), ("2", "0"), ("1", "1"), ("2", "1")]
+        got = variants([call(*c[1:], c[1], fused) for c in test_gpu_slices.CASES if c[0] == "conv3x3_strip"])
+        assert [v[0] if v[0] in ("16", "20") else v[1] for v in got] == ["1", "1", "1", "0", "1", "16", "20", "0"]
+    dense_mode = [[split(k)[0] for k in routes.kernels([call(dt, *c[:5], 3, c[5], c[6], wl.F32, False, rule=c[7]) for c in test_gpu_conv.DENSE_MODE])]
+                  for dt in (wl.F16, wl.BF16)]
+    dense = "conv3x3_dense<1,1,1,4,false>"
+    assert dense_mode[0] == dense_mode[1] == ["conv3x3_ksplit<1,1,1,2,1>"] * 2 + ["conv3x3_ksplit<1,2,1,2,1>", dense, dense, "conv3x3_ksplit<1,1,1,2,1>"] + \
+        ["conv3x3_ksplit<2,2,1,1,1>"] * 2 + ["conv3x3_ksplit<2,2,1,1,2>", "conv3x3_ksplit<2,2,1,1,1>", dense]
 
 
 RING_CASES = test_gpu_strip_ring.CASES + test_gpu_strip_ring.WIDE_CASES
