@@ -116,7 +116,7 @@ template <int TN, int LAY> struct RingSchedule {
 };
 
 template <int TN, int LAY, typename T, typename TO>
-__global__ __launch_bounds__(512, 2) void conv3x3_strip_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
+__global__ __launch_bounds__(512, 2) void conv3x3_ring_kernel(const T* __restrict__ x, TO* __restrict__ y, const char* __restrict__ wfrag,
                                                                const char* __restrict__ zeros, int H, int W, int Ci, int Co, int m_tiles_total,
                                                                WorkOrder order, Epilogue ep)
 {
@@ -267,6 +267,9 @@ __global__ __launch_bounds__(512, 2) void conv3x3_strip_kernel(const T* __restri
     for (int stage = 0; stage + 1 < stages; ++stage) run_stage(std::false_type{}, stage);
     run_stage(std::true_type{}, stages - 1);
 
+    // (past the L2's write-back whatever the channels: half sectors cost the stores more on tensors in no cache, and the launch is still faster than
+    // one that leaves them to the L2; us, strips with stores from the registers and here, tensors in caches, then in none, 4 entries: 256 -> 208
+    // on 1x100x168 21.3 17.7, 23.7 20.1; 256 -> 80 on 1x200x168 21.7 19.0, 24.5 19.9; 128 -> 208 on 1x100x168 14.2 12.0, 15.2 13.8)
     constexpr bool ROWS_OUT = sizeof(TO) == 2;
     char* const area = smem + stages % NB * P::BUF + wave * (TN * RowTile<TO>::kBytes);  // (a buffer that the last stage does not read)
     strip_output<TO, TN, ROWS_OUT>(acc, area, lds_ep, y, H, W, Co, cb, n_img, oh0 + wave * TN, ow0, lane, ep);
@@ -277,13 +280,13 @@ rtoss_status launch_ring(const rtoss_wdesc& d, const ConvParams& c, const char* 
 {
     using P = Ring<TN, LAY>;
     const int strips = (c.W + kCols - 1) / kCols, rows = (c.H + P::ROWS - 1) / P::ROWS, co_blocks = (d.Co + 63) / 64;
-    auto kern = conv3x3_strip_kernel<TN, LAY, T, TO>;
+    auto kern = conv3x3_ring_kernel<TN, LAY, T, TO>;
     static LaunchOnce lds_once;  // per instantiation
     if (rtoss_status st = ensure_dynamic_lds((const void*)kern, P::LDS, lds_once, c.dev.device, "conv3x3 shared memory attribute")) return st;
     const int64_t total = (int64_t)strips * rows * co_blocks * c.N;
     const WorkOrder order(total, co_blocks, strips * rows, strips);
     kern<<<dim3(order.grid()), dim3(512), P::LDS, s>>>((const T*)x, (TO*)y, wf, zeros, c.H, c.W, d.Ci, d.Co, padded_m_tiles(d.Co), order, c.ep);
-    return check_hip(hipGetLastError(), "conv3x3 strip launch");
+    return check_hip(hipGetLastError(), "conv3x3 ring launch");
 }
 
 template <int TN, int LAY>

@@ -33,7 +33,7 @@
 // This file holds the single-buffered kernel (stride 2, but for shallow layers in large launches, which have one of their own
 // here; ragged channel counts, and stride-1 layers of up to 64 input or output channels in launches of many rounds): a plain
 // loop nest with small tiles, several workgroups per compute unit.
-// Large stride-1 layers take the pipelined kernel of conv3x3_rows.hip, launches of medium size the strips of
+// Large stride-1 layers take the pipelined kernel of conv3x3_rows.hip, launches of medium size the strips of conv3x3_ring.hip and
 // conv3x3_strip.hip, and those that cannot fill the chip conv3x3_ksplit.hip; all read the same packed section.
 #include <algorithm>
 #include <type_traits>
@@ -626,6 +626,8 @@ inline bool takes_pipelined_kernel(const rtoss_wdesc& d, const ConvParams& c)
 // unit, 1.75, 2.3, 2.75 and 3.85 of strips of 8, 12, 16 and 20 rows (1.0 where eight rows fit once).  Measured, strips and pipelined, 4 entries:
 //     200x96->112@5x3 8.2 12.0   200x128@8x16 9.9 14.0   40x96->256@24x17 18.6 21.2   4x160->144@112x162 36.3 43.1   2x128->256@33x330 13.8 15.0
 //     100x256@13x13 25.0 21.6    100x128@17x17 17.9 15.9   4x96@100x168 16.1 14.6    2x256@100x168 33.8 28.2       3x320@80x80 31.7 28.3
+// (Tensors in caches.  In none, with half sectors a position and three or four stages, the pipelined kernel's rows past the write-back cost up to 5 %
+// more than the strips: 96->240@1x200x168 19.2 20.2, in caches 17.3 15.3; 128->176@4x100x168 32.2 33.3, 30.4 29.6.)
 inline double strips_us(const rtoss_wdesc& d, const ConvParams& c, int plan)
 {
     const int rows = strip3x3_rows(plan);

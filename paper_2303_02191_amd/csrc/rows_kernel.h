@@ -135,8 +135,6 @@ template <int TN> struct GroupSchedule {
     static_assert(permuted_behind_reads(), "read in an earlier slot");
 };
 
-// FUSED: scale / bias / SiLU / residual in the epilogue.  The plain instantiation (ReLU or nothing) keeps
-// its branch-free epilogue; the fused one pays for generality with a few uniform branches per tile.
 // One pipeline buffer.  Copies past the last (a wave has as many as any other) repeat it.
 template <int LAY> struct Region {
     static constexpr int TILE = layout_tile_bytes(kLayouts[LAY]);
@@ -156,6 +154,8 @@ template <int LAY> struct Region {
     static_assert(LDS <= 160 * 1024, "a compute unit's LDS");
 };
 
+// FUSED: scale / bias / SiLU / residual in the epilogue.  The plain instantiation (ReLU or nothing) keeps
+// its branch-free epilogue; the fused one pays for generality with a few uniform branches per tile.
 // LAY: tap layout (sparse_frag.h)
 template <typename T, typename TO, bool FUSED, int LAY>
 __global__ __launch_bounds__(256, 1) void conv3x3_rows_kernel(const T* __restrict__ x, TO* __restrict__ y,

@@ -70,7 +70,7 @@ PITCH_CASES = [
     (wl.F16, wl.F16, 1, 72, 32, 1, 70, 1, 1, 2, False, False, "conv1x1_mma<1,2,true>", "conv1x1_mma<1,2,true>"),
     (wl.F16, wl.F16, 1, 128, 16512, 20, 16, 3, 1, 3, False, False, "conv3x3_rows<false,0>", "conv3x3_sparse_sb<1,4,2,2,4,true,0,true,false>"),
     (wl.F16, wl.F16, 1, 128, 16512, 20, 16, 3, 1, 3, True, False, "conv3x3_rows<true,0>", "conv3x3_rows<true,0>"),
-    (wl.BF16, wl.BF16, 1, 128, 8192, 20, 16, 3, 1, 3, True, False, "conv3x3_strip<3,0>", "conv3x3_sparse_sb<1,4,2,2,4,true,0,true,false>"),
+    (wl.BF16, wl.BF16, 1, 128, 8192, 20, 16, 3, 1, 3, True, False, "conv3x3_ring<3,0>", "conv3x3_sparse_sb<1,4,2,2,4,true,0,true,false>"),
     (wl.BF16, wl.BF16, 1, 128, 16384, 20, 16, 3, 1, 6, False, False, "conv3x3_strip<20,true>", "conv3x3_strip<20>"),
     (wl.F16, wl.F16, 1, 128, 16512, 20, 16, 3, 1, 5, False, False, "conv3x3_rows<false,1>", "conv3x3_strip<5,1,false>"),
     (wl.F32, wl.F32, 1, 64, 16384, 20, 16, 3, 1, 3, False, False, "conv3x3_strip<8>", "conv3x3_dense<1,1,1,4,false>"),

@@ -117,7 +117,7 @@ RING_CASES = test_gpu_strip_ring.CASES + test_gpu_strip_ring.WIDE_CASES
 
 def test_ring_cases_reach_the_height_they_name():
     calls = [call(dt, N, Ci, Co, H, W, 3, 1, k, dt, fused) for tn, dt, N, Ci, Co, H, W, k in RING_CASES for fused in (False, True)]
-    want = ["conv3x3_strip<%d,%d>" % (c[0], c[-1] >= 4) for c in RING_CASES for fused in (False, True)]
+    want = ["conv3x3_ring<%d,%d>" % (c[0], c[-1] >= 4) for c in RING_CASES for fused in (False, True)]
     assert [split(k)[0] for k in routes.kernels(calls)] == want
 
 
@@ -127,7 +127,7 @@ def test_shallow_launches_of_two_rounds_stay_without_helpers():
         for stages in (3, 4, 5, 8):
             calls = [call(wl.BF16, N, 32 * stages, Co, H, W, 3, 1, k, wl.BF16, fused) for fused in (False, True)
                      for N, Co, H, W in ((1, 192, 100, 168), (4, 336, 40, 40), (2, 208, 80, 80), (17, 64, 43, 50))]
-            want = "conv3x3_strip<4,%d>" % (k >= 4) if stages >= least else "conv3x3_strip<2,%d,true>" % (k >= 4)
+            want = "conv3x3_ring<4,%d>" % (k >= 4) if stages >= least else "conv3x3_strip<2,%d,true>" % (k >= 4)
             assert {split(r)[0] for r in routes.kernels(calls)} == {want}, (k, stages)
 
 
