@@ -59,7 +59,7 @@ struct BlobGeometry {
     MatrixFormat format;
     size_t mat_off;     // matrix-core section (0 if none)
     size_t mat_bytes;
-    size_t dense_off;   // kFormatSparse24: the same weights in the dense mode's format as well (0: not)
+    size_t dense_off;   // the same weights in the dense mode's format beside kFormatSparse24 (0: not); with kFormatDense3x3: that section alone
     size_t total;
 };
 

@@ -39,7 +39,7 @@ struct PackEntry {
     uint32_t idx_off, mat_off;  // sections of the blob, in units of 256 bytes
     int Co, Ci;
     uint32_t items;             // 3x3: (stage, channel tile) pairs; 1x1 and stem: 16-byte pieces of the fragments
-    uint8_t format, a, b, c;    // MatrixFormat; 3x3: tap layout, dense section as well; streaming 1x1: log2 of KS, of MT; without fragments: weights per kernel
+    uint8_t format, a, b, c;    // MatrixFormat; 3x3: tap layout, fragments alone; streaming 1x1: log2 of KS, of MT; without fragments: weights per kernel
 };
 constexpr int kPackMax = 60, kPackFew = 8;
 template <int N> struct PackTable {
@@ -182,7 +182,7 @@ __device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigne
 #pragma unroll
     for (int i = 0; i < IDX_PER; ++i) {
         const int c = (tid + 256 * i) % SC, r = (tid + 256 * i) / SC, co = tile_row_channel(mt, r);
-        if (co >= Co || c >= channels) continue;
+        if (co >= Co || c >= channels || en.b) continue;
         const int64_t g = (int64_t)co * Ci + SC * stage + c;
         live_idx[g] = iv[i];
         const uint64_t taps = L.taps[entry[i]];
@@ -230,13 +230,9 @@ __device__ __forceinline__ void pack_tile3x3(const PackEntry& en, int k, unsigne
             __builtin_memcpy(&pk, vals, 16);
             store16_through(tile_out + step * kFragBytes + lane * 16, pk);
         }
-    }
-    // (of both, the dense section lies behind the other, its channel tiles padded to blocks of 4 instead of 8)
-    const int stages = (Ci + SC - 1) / SC, dense_tiles = 4 * dense_channel_blocks(Co);
-    if (!SPARSE || (LAY == 1 && en.b && mt < dense_tiles)) {
+    } else {
         constexpr int PER = 16 / (int)sizeof(T);
-        char* tile_out = out + (size_t)(stage * dense_tiles + mt) * kDenseTileBytes;
-        if constexpr (SPARSE) tile_out += (size_t)en.items * layout_tile_bytes(lay) + zero_section_bytes(stages);
+        char* tile_out = out + (size_t)tile * kDenseTileBytes;
         for (int item = tid; item < 64 * 9; item += 256) {
             const int lane = item % 64, t = item / 64;
             const int r = lane % 16, q = lane / 16;
@@ -376,13 +372,9 @@ __global__ __launch_bounds__(256) void pack_kernel(PackTable<N> tab, D dict)
             pack_tile3x3<T, kDenseTaps, SMALL>(en, dict.k, mask, masks, block, m_tiles, lds.tile);
             return;
         }
-        // the block behind the tiles writes the block of zeros, or both
+        // the block behind the tiles writes the block of zeros
         const size_t end = (size_t)en.items * (en.format == kFormatSparse24 ? layout_tile_bytes(kLayouts[en.a]) : kDenseTileBytes);
-        const size_t end2 = end + zero_section_bytes(stages) + (size_t)stages * 4 * dense_channel_blocks(en.Co) * kDenseTileBytes;
-        for (int b = tid * 16; b < zero_section_bytes(stages); b += 4096) {
-            *(u32x4*)(section + end + b) = u32x4{0, 0, 0, 0};
-            if (en.format == kFormatSparse24 && en.b) *(u32x4*)(section + end2 + b) = u32x4{0, 0, 0, 0};
-        }
+        for (int b = tid * 16; b < zero_section_bytes(stages); b += 4096) *(u32x4*)(section + end + b) = u32x4{0, 0, 0, 0};
         return;
     }
     __syncthreads();  // masks  (3x3 tiles have a barrier of their own in front of their first use)
@@ -462,11 +454,11 @@ rtoss_status make_entry(const PackItem& it, const BlobGeometry& g, int layout, P
     switch (g.format) {
     case kFormatSparse24:
         en->a = (uint8_t)layout;
-        en->b = g.dense_off != 0;
         items = (int64_t)stages * padded_m_tiles(d.Co);
         *blocks = items + 1;
         break;
     case kFormatDense3x3:
+        en->b = g.dense_off != 0;
         items = (int64_t)stages * 4 * dense_channel_blocks(d.Co);
         *blocks = items + 1;
         break;

@@ -13,7 +13,7 @@ __host__ __device__ inline int zero_section_bytes(int stages) { return (64 * sta
 
 // ---- 3x3, one dense step per tap: blocks of 4 channel tiles, [stage][block][tile][tap][lane] ----
 constexpr int kDenseTileBytes = 9 * kFragBytes;
-__host__ __device__ inline int dense_channel_blocks(int Co) { return (Co + 63) / 64; }
+inline int dense_channel_blocks(int Co) { return (Co + 63) / 64; }
 
 // ---- 1x1, streaming kernel: [channel block][wave slice][fragment][stage][lane] ----
 constexpr int stream_mt_of(int KS) { return KS <= 8 ? 4 : (KS == 16 ? 2 : 1); }  // fragments per wave along output channels
