@@ -326,7 +326,7 @@ rtoss_status rtoss_pack_size(const rtoss_wdesc* desc, const uint16_t* masks_host
 }
 
 // A layer with fragments in both formats is packed as two, side by side, the second without the public section.  (One that writes both takes the length
-// of both: four layers 256 -> 256, 5 entries, 6.7 us with the 2-of-4 fragments alone, 8.6 in one, 7.4 in two; one layer 5.6, 6.7, 5.7.)
+// of both: four layers 256 -> 256, 5 entries, 6.7 us with the 2-of-4 fragments alone, 8.6 in one, 7.2 in two; one layer 5.6, 6.7, 5.6.)
 static BlobGeometry dense_section(const BlobGeometry& both)
 {
     BlobGeometry g = both;

@@ -719,7 +719,7 @@ constexpr int kDenseTaps = 2;  // the dense mode, as a layout of the other files
 // Of a dictionary that needs the repeated taps both sections are packed, for at odd sizes the dense mode has the better tiles: smaller ones in
 // small launches, strips of fewer rows on low images.  Which, by the plans of both (1480 launches of 64 to 512 channels on 4 to 220 rows and
 // columns, bf16 and fp16: the slower one by more than 3 % in 60 of them; always the 2-of-4 steps, up to 1.78 times as long; always dense mode, 21 %
-// on average).  Packing both takes four layers 256 -> 256 6.7 -> 7.4 us, two of 512 8.0 -> 10.1.  us, dense mode and 2-of-4:
+// on average).  Packing both takes four layers 256 -> 256 6.7 -> 7.2 us, two of 512 8.0 -> 10.1.  us, dense mode and 2-of-4:
 //     Channels split over the waves: 32 channels a workgroup against 16 of the dense mode's split (256@1x20x46 4.86 5.11), or against its small
 //     tiles while two of them a unit hold the launch, where the split's four waves are unevenly deep (96@2x30x35 3.92 4.41, 64->80@1x56x56 3.65
 //     4.32, 160@2x24x28 4.85 5.20; 160@2x30x37, 576 tiles 6.24 5.41; four stages 128@1x40x53 4.59 4.62; seven 224@1x22x49 5.92 5.62).
