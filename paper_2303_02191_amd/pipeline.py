@@ -159,7 +159,8 @@ class PackedLayer(_Layer):
         self.__dict__.update(state)
         saved = state.get("private_format", 0)
         # (the formats so far differ only for layers whose packed size differs too)
-        same = saved == self.PRIVATE_FORMAT or self.blob.numel() == B.rtoss_pack_size(self.wdesc, self.masks)[0]
+        same = saved == self.PRIVATE_FORMAT or (saved < self.PRIVATE_FORMAT
+                                                and self.blob.numel() == B.rtoss_pack_size(self.wdesc, self.masks)[0])
         self.private_format = self.PRIVATE_FORMAT if same else saved
         self._bind()
         if not same and self.blob.is_cuda:

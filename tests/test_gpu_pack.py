@@ -120,6 +120,7 @@ def test_packed_again_on_the_blobs_device(monkeypatch):
     x = torch.randn((2, 9, 11, Ci), device="cuda").to(pl.TORCH_DTYPE[dt])
     assert torch.equal(other.conv(x), layer.conv(x))
 
+
 def test_layers_of_another_build_moved_to_the_gpu():
     """... restored in host memory first: packed again at the first call, of whatever kind."""
     dt, Co, Ci, k = wl.BF16, 144, 64, 5

@@ -158,7 +158,9 @@ def test_a_layer_of_another_build_in_host_memory_reaches_no_kernel():
     assert "taps" not in refusal(kept) and kept.blob is layer.blob  # the same size: the same sections
     old = pl.PackedLayer.__new__(pl.PackedLayer)
     old.__setstate__(dict(state, blob=torch.zeros(layer.packed_bytes + 512, dtype=torch.uint8)))
-    for other in (old, copy.copy(old), pickle.loads(pickle.dumps(old))):
+    later = pl.PackedLayer.__new__(pl.PackedLayer)
+    later.__setstate__(dict(state, private_format=pl.PackedLayer.PRIVATE_FORMAT + 1))
+    for other in (old, copy.copy(old), pickle.loads(pickle.dumps(old)), later):
         other.masks = list(other.masks)
         with FakeTensorMode():
             x = torch.empty(1, 4, 4, 96, dtype=torch.bfloat16, device="cuda")
